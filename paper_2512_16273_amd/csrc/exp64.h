@@ -6,6 +6,8 @@
 // run at full rate on gfx950: rounding to an integer and the scaling are done with a "magic number"
 // addition and an exponent-field construction instead of rint / convert / ldexp, which issue at a
 // quarter of the rate there.
+//
+// pow_exp is the same function for the long sums, through a table that a workgroup builds in LDS.
 #pragma once
 #include <stdint.h>
 #include <string.h>
@@ -49,6 +51,64 @@ TSLT_HD double exp64(double x) {
   double scale;
   memcpy(&scale, &sb, 8);
   return p * scale;
+}
+
+// exp(x) for a finite x with |x| <= 700 (in the kernels an fp32 value) through a table of 2^(i/2048):
+// x = n * ln2/2048 + r, |r| <= ln2/4096, exp(x) = 2^(n div 2048) * table[n mod 2048] * (1 + r + r^2/2 + r^3/6) (the
+// series is cut below 2^-54).  Half the fp64 operations of exp64, for one 8-byte read from LDS; within about 1.5
+// ulp.  An entry is 2^(i/2048) with i << 9 taken off its high word, so that adding n << 9 there scales by
+// 2^(n div 2048) without n's low bits having to be masked out.
+constexpr int kPowEntries = 2048;
+TSLT_HD uint64_t pow_entry(int i) {
+  // 2^(i/2048) = 2^m * exp(r), m = 0 or 1, r = (i - 2048 m) * ln2/2048 as a sum rh + rl (rh exact) with |r| <= ln2/2;
+  // exp(r) = 1 + rh + c, where rounding in c counts for little and the last addition is the only one at full size
+  const int m = i > kPowEntries / 2 ? 1 : 0;
+  const double k = double(i - m * kPowEntries);
+  const double rh = k * (6.93147180369123816490e-01 / kPowEntries);
+  const double rl = k * (1.90821492927058770002e-10 / kPowEntries);
+  double p = 1.1470745597729725e-11;                              // 1/14!
+  p = __builtin_fma(p, rh, 1.6059043836821613e-10);
+  p = __builtin_fma(p, rh, 2.08767569878681e-09);
+  p = __builtin_fma(p, rh, 2.505210838544172e-08);
+  p = __builtin_fma(p, rh, 2.755731922398589e-07);
+  p = __builtin_fma(p, rh, 2.7557319223985893e-06);
+  p = __builtin_fma(p, rh, 2.48015873015873e-05);
+  p = __builtin_fma(p, rh, 1.984126984126984e-04);
+  p = __builtin_fma(p, rh, 1.388888888888889e-03);
+  p = __builtin_fma(p, rh, 8.333333333333333e-03);
+  p = __builtin_fma(p, rh, 4.1666666666666664e-02);
+  p = __builtin_fma(p, rh, 1.6666666666666666e-01);
+  p = __builtin_fma(p, rh, 0.5);
+  const double c0 = rh * rh * p;                                  // exp(rh) - 1 - rh
+  const double c = c0 + rl * (1.0 + (rh + c0));
+  const double big = 1.0 + rh;
+  const double v = big + ((rh - (big - 1.0)) + c);
+  uint64_t b;
+  memcpy(&b, &v, 8);
+  return b + (uint64_t(uint32_t(m << 20) - (uint32_t(i) << 9)) << 32);
+}
+TSLT_HD double pow_exp(float s, const uint64_t* table) {
+  const double x = double(s);
+  const double kMagic = 6755399441055744.0;
+  const double t = __builtin_fma(x, 1.44269504088896338700e+00 * kPowEntries, kMagic);
+  const double n = t - kMagic;
+  uint64_t tb;
+  memcpy(&tb, &t, 8);
+  const uint32_t ni = uint32_t(tb);
+  double r = __builtin_fma(n, -6.93147180369123816490e-01 / kPowEntries, x);
+  r = __builtin_fma(n, -1.90821492927058770002e-10 / kPowEntries, r);
+  double q = __builtin_fma(r, 1.6666666666666666e-01, 0.5);
+  q = __builtin_fma(q, r, 1.0);
+  q = q * r;
+  const uint64_t e = table[ni & (kPowEntries - 1)];
+#if defined(__HIP_DEVICE_COMPILE__)
+  const double v = __hiloint2double(int(uint32_t(e >> 32) + (ni << 9)), int(uint32_t(e)));
+#else
+  const uint64_t b = (uint64_t(uint32_t(e >> 32) + (ni << 9)) << 32) | uint32_t(e);
+  double v;
+  memcpy(&v, &b, 8);
+#endif
+  return __builtin_fma(v, q, v);
 }
 
 }  // namespace tslt

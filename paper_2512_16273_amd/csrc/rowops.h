@@ -52,15 +52,21 @@ struct VerifyShared {
 constexpr int kMaxPieces = kBlock;                                 // segments of a row that is sampled, plus its two edges
 constexpr int kMaxItems = (kMaxPieces - 2) * kSubChunks + 2;       // its runs, plus the two edges
 
-// A table of exp(s), s = fl32(z / T), for every 16-bit logit z of a magnitude range that holds the bulk of
-// a row: the fp64 sums over the row then cost one LDS read per element instead of an fp64 exponential.
+// The fp64 terms of a row are made in one of two ways, both referenced to 0 rather than to the row maximum,
+// which is safe while |s| <= kTabMaxS; a row (tree: a group of segments) that holds a larger |s| is redone by
+// the maximum-referenced path.
+//
+// BitTerms, 16-bit rows: a table of exp(s), s = fl32(z / T), for every logit z of a magnitude range that holds
+// the bulk of a row; a term costs five instructions and one LDS read.
 //   bfloat16  2^-14 <= |z| < 2^7   5376 values, 42 KB  (logits centred on 0 have many small values)
 //   binary16  2^-2 <= |z| < 2^5  14336 values, 112 KB
 // With the 16 bits of an element rotated left by one (sign in bit 0), entry 1 + (rotated - 2*kLo) holds
 // its value; entries 0 and kEntries + 1 hold NaN and stand for everything below and above the table's
-// domain (tiny, huge, -inf, NaN), which is evaluated directly.  Terms are referenced to 0 rather than to
-// the row maximum, which is safe while |s| <= kTabMaxS; a segment that holds a larger |s| is redone by
-// the maximum-referenced path.
+// domain (tiny, huge, -inf, NaN), which is evaluated directly.
+//
+// PowTerms, every type: exp64.h's pow_exp on a table of 2^(i/2048) (16 KB).  19 instructions per term and one LDS
+// read instead of the 30 of exp64; bound by the vector units.  Resampling 48 fp32 rows of 151936: 53.7 us by
+// exp64, 29.9 so; the 2400 sampled nodes of two fp32 trees of 1365: 534 and 340 us.
 constexpr float kTabMaxS = 600.0f;
 template <typename T> struct ExpTab {
   static constexpr bool kHas = false;
@@ -89,6 +95,7 @@ template <> struct ExpTab<F16> {
   static constexpr bool kSampled = true;           // a row whose bulk lies near 0 is mostly below the range
   static __device__ __forceinline__ float widen(uint32_t bits) { return f16_lo(bits); }
 };
+// Whether a launch may make its terms through the bit table: every entry's |s| is within the range.
 template <typename T> inline bool exp_table_usable(float rT) {
   if constexpr (ExpTab<T>::kHas) return ExpTab<T>::kMaxAbs * rT <= kTabMaxS;
   return false;
@@ -170,6 +177,91 @@ __device__ __forceinline__ double table_vec_redo(const uint4& d, float rT, int& 
   }
   return s;
 }
+__device__ __forceinline__ float max3_nan(float a, float b, float c) {      // v_maximum3_f32: a NaN among them is kept
+  return __builtin_elementwise_maximum(__builtin_elementwise_maximum(a, b), c);
+}
+
+// How a sweep makes its terms.  build() fills the LDS table (all `threads` threads of the workgroup, the caller
+// synchronises; `half` as for build_exp_table); run_sum() gives the sum over a wave's run, of which every lane
+// holds kSegVecs vectors (vector i is vector vbase + 64 i of the row and counts if that is below nvec), and
+// raises flags: 1 = NaN or +inf among the elements, 2 = the row has to be swept by its maxima (which finds NaN
+// and +inf for itself).
+template <typename T> struct BitTerms {
+  static constexpr bool kBits = true;
+  static constexpr size_t kBytes = ExpTab<T>::kBytes;
+  static __device__ __forceinline__ void build(double* table, float rT, int threads, int half = -1) {
+    build_exp_table<T>(table, rT, threads, half);
+  }
+  // (the four vectors' look-ups go out together and one look at their total says whether a value was outside
+  // the table)
+  static __device__ __forceinline__ double run_sum(const uint4 (&q)[kSegVecs], uint32_t vbase, uint32_t nvec,
+                                                   const double* table, float rT, int& flags) {
+    double sv[kSegVecs];
+#pragma unroll
+    for (int i = 0; i < kSegVecs; ++i) sv[i] = table_vec_sum_raw<T>(q[i], table);
+#pragma unroll
+    for (int i = 0; i < kSegVecs; ++i) sv[i] = vbase + i * 64 < nvec ? sv[i] : 0.0;
+    double acc = (sv[0] + sv[1]) + (sv[2] + sv[3]);
+    if (acc != acc) {
+      acc = 0.0;
+#pragma unroll
+      for (int i = 0; i < kSegVecs; ++i)
+        if (vbase + i * 64 < nvec) acc += sv[i] == sv[i] ? sv[i] : table_vec_redo<T>(q[i], rT, flags);
+    }
+    return wave_sum_f64(acc);
+  }
+};
+template <typename T> struct PowTerms {
+  static constexpr bool kBits = false;
+  static constexpr size_t kBytes = size_t(kPowEntries) * sizeof(uint64_t);
+  static __device__ __forceinline__ void build(double* table, float, int threads, int half = -1) {
+    uint64_t* t = reinterpret_cast<uint64_t*>(table);
+    const int lo = half == 1 ? kPowEntries / 2 : 0, hi = half == 0 ? kPowEntries / 2 : kPowEntries;
+    for (int i = lo + threadIdx.x; i < hi; i += threads) t[i] = pow_entry(i);
+  }
+  // A term is made of max(s, -690), so that masked elements (-inf) need no branch: what they and other far ones
+  // add, 2e-300 each, is nothing beside any s >= -kTabMaxS.  A run without such an s is masked throughout (its
+  // sum is 0) or lies below the range.
+  static __device__ __forceinline__ double run_sum(const uint4 (&q)[kSegVecs], uint32_t vbase, uint32_t nvec,
+                                                   const double* table, float rT, int& flags) {
+    constexpr int E = ElemTraits<T>::kPerVec;
+    const uint64_t* t = reinterpret_cast<const uint64_t*>(table);
+    double acc = 0.0;
+    float top = -INFINITY;
+#pragma unroll
+    for (int i = 0; i < kSegVecs; ++i) {
+      float v[E];
+      unpack<T>(q[i], v);
+      double s0 = 0.0, s1 = 0.0;
+#pragma unroll
+      for (int e = 0; e < E; e += 2) {
+        const float a = __fmul_rn(v[e], rT), b = __fmul_rn(v[e + 1], rT);
+        top = max3_nan(a, b, top);
+        const double ta = pow_exp(__builtin_amdgcn_fmed3f(a, -690.0f, 690.0f), t);
+        const double tb = pow_exp(__builtin_amdgcn_fmed3f(b, -690.0f, 690.0f), t);
+        s0 = e == 0 ? ta : s0 + ta;
+        s1 = e == 0 ? tb : s1 + tb;
+      }
+      acc += vbase + i * 64 < nvec ? s0 + s1 : 0.0;
+    }
+    flags |= top <= kTabMaxS ? 0 : 2;                   // NaN too
+    double sum = wave_sum_f64(acc);
+    if (sum < 1e-262) {                                 // (the same in all lanes; e^-600 is 2.7e-261)
+#pragma unroll
+      for (int i = 0; i < kSegVecs; ++i) {
+        uint4 w = q[i];
+        asm volatile("" : "+v"(w.x), "+v"(w.y), "+v"(w.z), "+v"(w.w));      // not to be done for every run
+        float v[E];
+        unpack<T>(w, v);
+#pragma unroll
+        for (int e = 0; e < E; ++e) flags |= v[e] > -INFINITY && vbase + i * 64 < nvec ? 2 : 0;
+      }
+      sum = 0.0;
+    }
+    return sum;
+  }
+};
+
 // Three sums over the workgroup with one pair of barriers.
 template <int NW>
 __device__ __forceinline__ void block_sum3_f64(double& a, double& b, double& c, BlockScratch& s) {
@@ -454,70 +546,56 @@ __device__ __forceinline__ void sweep_segments_direct(const RowSplit& rs, int se
 }
 
 // Segments group*kGroupSegs .. +kGroupSegs-1 of a row (all 256 threads of a workgroup); group 0 also does
-// the two edge pieces.  `table` is the bf16 exp table in LDS or null.  Through the table the terms are
-// referenced to 0: a segment then reports smax = 0 (-inf if it has no mass).
-template <typename T>
+// the two edge pieces.  `table` is the terms' table in LDS.  The terms are referenced to 0: a segment then
+// reports smax = 0 (-inf if it has no mass).
+template <typename T, typename Terms>
 __device__ __forceinline__ void sweep_group(const void* row, const RowSplit& rs, int group, bool check, float rT,
                                             const double* table, SegResult* segs, double* subs, VerifyShared& sh) {
   const int tid = threadIdx.x;
   const int n_seg_row = int((rs.nvec + kSegVecsTotal - 1) / kSegVecsTotal);
   const int seg0 = group * kGroupSegs;
   const int n_here = n_seg_row - seg0 < kGroupSegs ? n_seg_row - seg0 : kGroupSegs;   // may be <= 0
-  bool direct = n_here > 0;
-  if constexpr (ExpTab<T>::kHas) {
-    if (table != nullptr && n_here > 0) {
-      // (every request unconditional: a vector past the row's end is read from the row's last vector and its
-      // sum dropped; the four vectors' look-ups of a lane go out together and one look at their total says
-      // whether a value was outside the table)
-      int flags = 0;
-      const uint32_t nvec = uint32_t(rs.nvec), last_vec = nvec - 1;
-      auto request = [&](int seg, uint4 (&q)[kSegVecs]) {
-        const uint32_t vb = uint32_t(seg) * kSegVecsTotal + wave_id() * kRunVecs + lane_id();
+  bool direct = false;
+  if (n_here > 0) {
+    // (every request unconditional: a vector past the row's end is read from the row's last vector and its
+    // sum dropped)
+    int flags = 0;
+    const uint32_t nvec = uint32_t(rs.nvec), last_vec = nvec - 1;
+    auto request = [&](int seg, uint4 (&q)[kSegVecs]) {
+      const uint32_t vb = uint32_t(seg) * kSegVecsTotal + wave_id() * kRunVecs + lane_id();
 #pragma unroll
-        for (int i = 0; i < kSegVecs; ++i) {
-          const uint32_t vi = vb + i * 64;
-          q[i] = load_vec(&rs.body[vi < last_vec ? vi : last_vec]);
-        }
-      };
-      uint4 d[kSegVecs], dn[kSegVecs];
-      request(seg0, d);
-#pragma unroll
-      for (int k = 0; k < kGroupSegs; ++k) {
-        if (k < n_here) {
-          request(k + 1 < n_here ? seg0 + k + 1 : seg0 + k, dn);
-          const uint32_t vbase = uint32_t(seg0 + k) * kSegVecsTotal + wave_id() * kRunVecs + lane_id();
-          double sv[kSegVecs];
-#pragma unroll
-          for (int i = 0; i < kSegVecs; ++i) sv[i] = table_vec_sum_raw<T>(d[i], table);
-#pragma unroll
-          for (int i = 0; i < kSegVecs; ++i) sv[i] = vbase + i * 64 < nvec ? sv[i] : 0.0;
-          double run = (sv[0] + sv[1]) + (sv[2] + sv[3]);
-          if (run != run) {
-            run = 0.0;
-#pragma unroll
-            for (int i = 0; i < kSegVecs; ++i)
-              if (vbase + i * 64 < nvec) run += sv[i] == sv[i] ? sv[i] : table_vec_redo<T>(d[i], rT, flags);
-          }
-          const double run_sum = wave_sum_f64(run);
-          if (lane_id() == 0) {
-            subs[size_t(seg0 + k) * kSubChunks + wave_id()] = run_sum;
-            sh.red.d[k * kWaves + wave_id()] = run_sum;
-          }
-#pragma unroll
-          for (int i = 0; i < kSegVecs; ++i) d[i] = dn[i];
-        }
+      for (int i = 0; i < kSegVecs; ++i) {
+        const uint32_t vi = vb + i * 64;
+        q[i] = load_vec(&rs.body[vi < last_vec ? vi : last_vec]);
       }
-      flags = block_or_i32<kWaves>(flags, sh.red);      // its barriers also publish the run sums
-      direct = (flags & 2) != 0;
-      if (!direct && tid < n_here) {
-        const int bad = (flags & 1) && check ? 1 : 0;
-        double t = 0.0;
-        for (int w = 0; w < kWaves; ++w) t += sh.red.d[tid * kWaves + w];
-        SegResult& o = segs[1 + seg0 + tid];
-        o.sum = bad ? 0.0 : t; o.smax = (t > 0.0 && !bad) ? 0.0f : -INFINITY; o.bad = bad;
+    };
+    uint4 d[kSegVecs], dn[kSegVecs];
+    request(seg0, d);
+    constexpr int kUnroll = Terms::kBits ? kGroupSegs : 1;
+#pragma unroll kUnroll
+    for (int k = 0; k < kGroupSegs; ++k) {
+      if (k < n_here) {
+        request(k + 1 < n_here ? seg0 + k + 1 : seg0 + k, dn);
+        const uint32_t vbase = uint32_t(seg0 + k) * kSegVecsTotal + wave_id() * kRunVecs + lane_id();
+        const double run_sum = Terms::run_sum(d, vbase, nvec, table, rT, flags);
+        if (lane_id() == 0) {
+          subs[size_t(seg0 + k) * kSubChunks + wave_id()] = run_sum;
+          sh.red.d[k * kWaves + wave_id()] = run_sum;
+        }
+#pragma unroll
+        for (int i = 0; i < kSegVecs; ++i) d[i] = dn[i];
       }
-      __syncthreads();
     }
+    flags = block_or_i32<kWaves>(flags, sh.red);      // its barriers also publish the run sums
+    direct = (flags & 2) != 0;
+    if (!direct && tid < n_here) {
+      const int bad = (flags & 1) && check ? 1 : 0;
+      double t = 0.0;
+      for (int w = 0; w < kWaves; ++w) t += sh.red.d[tid * kWaves + w];
+      SegResult& o = segs[1 + seg0 + tid];
+      o.sum = bad ? 0.0 : t; o.smax = (t > 0.0 && !bad) ? 0.0f : -INFINITY; o.bad = bad;
+    }
+    __syncthreads();
   }
   if (direct) sweep_segments_direct<T>(rs, seg0, n_here, check, rT, segs, subs, sh);
   if (group == 0 && tid == 0) {
@@ -564,8 +642,8 @@ struct FinishArgs {
   float u;
   int unusable;             // the row is known to be unusable: no token
   double* item_val;         // LDS scratch of the caller, kMaxItems doubles
-  const double* table;      // the exp table in LDS if the row's run sums were made through it (then every
-                            // piece is referenced to 0), else null
+  const double* table;      // the bit table in LDS if the row's run sums were made through it, else null: the
+                            // terms are then made anew by exp64
 };
 
 // The set's entries as finish_core needs them, one slot per (thread, k): token index (-1 if unused or out

@@ -54,7 +54,6 @@ struct TreeParams {
   int tasks;              // rows sampled per tree: n_nodes (all nodes) or 1 (path only)
   int all_nodes;
   int n_seg, n_seg_grid;
-  int use_table;          // kernel S sums bf16 rows through the exp table
 };
 
 inline size_t tree_workspace_bytes(int64_t B, int64_t n_nodes, int64_t V, bool all_nodes) {
@@ -272,18 +271,13 @@ __global__ __launch_bounds__(64) void tree_walk_kernel(const TreeParams p) {
 // ---------------------------------------------------------------------------------------------
 // Kernels S and F: sample the output of the nodes that need it
 // ---------------------------------------------------------------------------------------------
-template <typename T>
-__global__ __launch_bounds__(kBlock) void tree_sweep_kernel(const TreeParams p) {
+template <typename T, typename Terms>
+__global__ __launch_bounds__(kBlock, Terms::kBits ? 1 : 4) void tree_sweep_kernel(const TreeParams p) {
   __shared__ VerifyShared sh;
   extern __shared__ __align__(16) unsigned char dyn_lds[];
-  double* table = nullptr;
-  if constexpr (ExpTab<T>::kHas) {
-    if (p.use_table) {
-      table = reinterpret_cast<double*>(dyn_lds);
-      build_exp_table<T>(table, p.rT, kBlock);
-      __syncthreads();
-    }
-  }
+  double* table = reinterpret_cast<double*>(dyn_lds);
+  Terms::build(table, p.rT, kBlock);
+  __syncthreads();
   const int64_t n_items = p.B * p.tasks * p.n_seg_grid;
   for (int64_t item = blockIdx.x; item < n_items; item += gridDim.x) {      // persistent workgroups
     const int64_t task = item / p.n_seg_grid;                    // (b, t)
@@ -294,8 +288,8 @@ __global__ __launch_bounds__(kBlock) void tree_sweep_kernel(const TreeParams p) 
     const void* row = tree_row<T>(p, b, node);
     const RowSplit rs = split_row<T>(row, p.V);
     // non-leaf rows were validated by kernel M; leaves are seen here for the first time
-    sweep_group<T>(row, rs, seg, node >= p.n_int, p.rT, table, p.segs + size_t(task) * (p.n_seg + 2),
-                     p.subs + size_t(task) * p.n_seg * kSubChunks, sh);
+    sweep_group<T, Terms>(row, rs, seg, node >= p.n_int, p.rT, table, p.segs + size_t(task) * (p.n_seg + 2),
+                          p.subs + size_t(task) * p.n_seg * kSubChunks, sh);
     __syncthreads();
   }
 }
@@ -371,10 +365,15 @@ template <typename T> hipError_t launch_verify_tree(TreeParams p, hipStream_t s)
   int n_seg = int((p.V / E + 1 + kSegVecsTotal - 1) / kSegVecsTotal);
   if (n_seg > p.n_seg) n_seg = p.n_seg;
   p.n_seg_grid = (n_seg + kGroupSegs - 1) / kGroupSegs;
-  // the binary16 table would leave one workgroup of 256 threads per compute unit: bf16 rows only
-  p.use_table = std::is_same<T, Bf16>::value && exp_table_usable<T>(p.rT) ? 1 : 0;
   const int64_t grid = std::min<int64_t>(p.B * p.tasks * p.n_seg_grid, sweep_grid_limit());
-  hipLaunchKernelGGL(tree_sweep_kernel<T>, dim3(unsigned(grid)), dim3(kBlock), p.use_table ? ExpTab<T>::kBytes : 0, s, p);
+  auto sweep = [&](auto kernel, size_t lds) { hipLaunchKernelGGL(kernel, dim3(unsigned(grid)), dim3(kBlock), lds, s, p); };
+  // the binary16 bit table would leave one workgroup of 256 threads per compute unit: bf16 rows only
+  if constexpr (std::is_same<T, Bf16>::value) {
+    if (exp_table_usable<T>(p.rT)) sweep(tree_sweep_kernel<T, BitTerms<T>>, BitTerms<T>::kBytes);
+    else sweep(tree_sweep_kernel<T, PowTerms<T>>, PowTerms<T>::kBytes);
+  } else {
+    sweep(tree_sweep_kernel<T, PowTerms<T>>, PowTerms<T>::kBytes);
+  }
   if ((e = hipGetLastError()) != hipSuccess) return e;
   hipLaunchKernelGGL(tree_finish_kernel<T>, dim3(unsigned(p.B * p.tasks)), dim3(kBlock), 0, s, p);
   if ((e = hipGetLastError()) != hipSuccess) return e;

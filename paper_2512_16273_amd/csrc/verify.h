@@ -34,7 +34,6 @@ struct VerifyParams {
   // workspace
   int32_t* flags;        // [B, gamma] 1 accepted, 0 rejected, 2 row unusable, 3 not examined (staged mode)
   int32_t* row_status;   // [B, gamma]
-  int use_table;         // kernel B sums bf16 rows through the exp table
   int stage0;            // staged mode: positions in the first stage (0 = all positions in one launch)
   int j_begin, j_count;  // the positions one launch of kernel A covers
 };
@@ -91,8 +90,8 @@ __global__ __launch_bounds__(kBlock, kAccWavesPerSimd) void verify_accept_kernel
   bool ok;
   // A format whose exp table covers a part of its range only: the first batch of the row (kAccVecs * kBlock
   // vectors) says whether kernel B should use the table on this row.  A wave pays for one value outside
-  // the table as if its whole vector were outside, so the table loses to the direct path once about 1
-  // value in 500 is outside.
+  // the table as if its whole vector were outside, so the table loses to the terms made without it once
+  // about 1 value in 500 is outside.
   int miss = 0;
   eval_row_on_set<T>(row, rs, p.V, p.rT, p.k2, p.q_idx + size_t(r) * p.k_cap, p.q_logit + size_t(r) * p.k_cap, count, sh,
                      p_s, q_s, yi, p_out, ok, st, &miss);
@@ -142,8 +141,11 @@ constexpr int kResThreads = 1024;
 constexpr int kResWaves = kResThreads / 64;
 constexpr int kMaxSegs = kBlock - 2;          // finish_core handles at most kBlock pieces (segments + 2 edges)
 
-template <typename T>
+// kBits: the launch's temperature lets 16-bit rows be summed through the bit table (BitTerms; a binary16 row that
+// lies largely outside it is summed by PowTerms all the same); otherwise every row is summed by PowTerms.
+template <typename T, bool kBits>
 __global__ __launch_bounds__(kResThreads) void verify_resample_kernel(const VerifyParams p) {
+  using Pow = PowTerms<T>;
   constexpr int E = ElemTraits<T>::kPerVec;
   __shared__ VerifyShared sh;
   __shared__ double subs_l[kMaxSegs * kSubChunks];     // mass of every run, in its segment's units
@@ -169,13 +171,10 @@ __global__ __launch_bounds__(kResThreads) void verify_resample_kernel(const Veri
   const int32_t* fl_b = p.flags + b * p.gamma;
   int f0 = lane < p.gamma ? fl_b[lane] : 1;
   if (tid == 0) { flags_l = 0; next_run = kResWaves; }
-  double* table = nullptr;
-  if constexpr (ExpTab<T>::kHas && !ExpTab<T>::kSampled) {
-    if (p.use_table) {
-      table = reinterpret_cast<double*>(dyn_lds);
-      build_exp_table<T>(table, p.rT, kResThreads, 0);      // the second half: behind the first requests of the sweep
-    }
-  }
+  double* table = reinterpret_cast<double*>(dyn_lds);
+  // (the first half; the second half: behind the first requests of the sweep)
+  if constexpr (!kBits) Pow::build(table, p.rT, kResThreads, 0);
+  else if constexpr (!ExpTab<T>::kSampled) BitTerms<T>::build(table, p.rT, kResThreads, 0);
   int j0 = f0 != 1 ? lane : p.gamma;
   if (p.gamma > 64 && ballot(f0 != 1) == 0) {
     for (int j = lane + 64; j < p.gamma; j += 64)
@@ -183,12 +182,12 @@ __global__ __launch_bounds__(kResThreads) void verify_resample_kernel(const Veri
   }
   const int jstar = -wave_max_i32(-j0);        // the smallest over the wave
   const bool residual = jstar < p.gamma;
-  if constexpr (ExpTab<T>::kSampled) {
-    // kernel A has looked at a sample of the row (the bonus row it has not seen: the table is tried)
-    if (p.use_table && !(residual && (p.row_status[b * p.gamma + jstar] & kRowTablePoor))) {
-      table = reinterpret_cast<double*>(dyn_lds);
-      build_exp_table<T>(table, p.rT, kResThreads, 0);
-    }
+  bool bits = kBits;
+  if constexpr (kBits && ExpTab<T>::kSampled) {
+    // kernel A has looked at a sample of the row (the bonus row it has not seen: the bit table is tried)
+    bits = !(residual && (p.row_status[b * p.gamma + jstar] & kRowTablePoor));
+    if (bits) BitTerms<T>::build(table, p.rT, kResThreads, 0);
+    else Pow::build(table, p.rT, kResThreads, 0);
   }
   // the decision at that position, from the lane that holds it (a position beyond the first 64 is read again)
   const bool unusable = residual && (jstar < 64 ? __shfl(f0, jstar, 64) : fl_b[jstar]) == 2;
@@ -218,93 +217,81 @@ __global__ __launch_bounds__(kResThreads) void verify_resample_kernel(const Veri
     my_tv = load_elem<T>(row, my_valid ? my_y : 0);
     tv_requested = true;
   };
-  bool wrote_set = false;
   auto write_set = [&]() {          // this thread's set entry, for the waves that finish
     if (!tv_requested) request_target_at_index();
     set.yi[tid] = my_valid ? my_y : -1;
     set.ql[tid] = tid < count ? my_ql : 0.0f;
     set.tv[tid] = my_valid ? my_tv : -INFINITY;
-    wrote_set = true;
   };
-  bool direct = !unusable;          // the row is swept with fp64 exponentials (no table, or values beyond its domain)
-  int tab_bad = 0;
-  if constexpr (ExpTab<T>::kHas) {
-    if (table != nullptr) {
-      // ---- the sweep through the table.  A wave takes run `wave` first and then whichever run is next
-      // (a counter in LDS), so that the waves end together.  Every request of the loop is unconditional (a
-      // vector past the row's end is read from the row's last vector and its sum dropped; a run past the last
-      // is the last one again, to no effect): with requests inside branches the number in flight is not
-      // known where a wait is placed, and the wait for the current run would wait for the run requested
-      // ahead as well.
-      int flags = 0;
-      if (!unusable && n_runs > 0) {
-        const uint32_t last_vec = uint32_t(rs.nvec - 1), nvec = uint32_t(rs.nvec);
-        auto request = [&](int run, uint4 (&q)[kSegVecs]) {
-          const uint32_t vbase = uint32_t(run < n_runs ? run : n_runs - 1) * kRunVecs + lane;
+  // ---- the sweep.  A wave takes run `wave` first and then whichever run is next (a counter in LDS), so that
+  // the waves end together.  Every request of the loop is unconditional (a vector past the row's end is read
+  // from the row's last vector and its sum dropped; a run past the last is the last one again, to no effect):
+  // with requests inside branches the number in flight is not known where a wait is placed, and the wait for
+  // the current run would wait for the run requested ahead as well.
+  int flags = 0;
+  auto sweep = [&](auto terms) {
+    using Terms = decltype(terms);
+    const uint32_t last_vec = uint32_t(rs.nvec - 1), nvec = uint32_t(rs.nvec);
+    auto request = [&](int run, uint4 (&q)[kSegVecs]) {
+      const uint32_t vbase = uint32_t(run < n_runs ? run : n_runs - 1) * kRunVecs + lane;
 #pragma unroll
-          for (int i = 0; i < kSegVecs; ++i) {
-            const uint32_t vi = vbase + i * 64;
-            q[i] = load_vec(&rs.body[vi < last_vec ? vi : last_vec]);
-          }
-        };
-        // the four vectors' lookups are independent: all are requested before any is added up, and one look
-        // at the total says whether an element was outside the table
-        auto consume = [&](int run, const uint4 (&q)[kSegVecs]) {
-          const uint32_t vbase = uint32_t(run) * kRunVecs + lane;
-          double sv[kSegVecs];
-#pragma unroll
-          for (int i = 0; i < kSegVecs; ++i) sv[i] = table_vec_sum_raw<T>(q[i], table);
-#pragma unroll
-          for (int i = 0; i < kSegVecs; ++i) sv[i] = vbase + i * 64 < nvec ? sv[i] : 0.0;
-          double acc = (sv[0] + sv[1]) + (sv[2] + sv[3]);
-          if (acc != acc) {
-            acc = 0.0;
-#pragma unroll
-            for (int i = 0; i < kSegVecs; ++i)
-              if (vbase + i * 64 < nvec) acc += sv[i] == sv[i] ? sv[i] : table_vec_redo<T>(q[i], p.rT, flags);
-          }
-          const double run_sum = wave_sum_f64(acc);
-          if (lane == 0 && run < n_runs) subs_l[run] = run_sum;
-        };
-        auto next = [&]() {
-          int nr = 0;
-          if (lane == 0) nr = atomicAdd(&next_run, 1);
-          return __builtin_amdgcn_readfirstlane(nr);
-        };
-        uint4 d[kSegVecs], dn[kSegVecs];
-        int cur = wave;
-        request(cur, d);
-        build_exp_table<T>(table, p.rT, kResThreads, 1);    // the table's second half, while the requests travel
-        __syncthreads();                    // the table is complete
-        // the first run apart: behind it the set entry's target logit is requested, whose index has arrived
-        // by then
-        int nxt = next();
-        request(nxt, dn);
-        consume(cur, d);
-        request_target_at_index();
-#pragma unroll
-        for (int i = 0; i < kSegVecs; ++i) d[i] = dn[i];
-        cur = nxt;
-        while (cur < n_runs) {
-          nxt = next();
-          request(nxt, dn);
-          consume(cur, d);
-#pragma unroll
-          for (int i = 0; i < kSegVecs; ++i) d[i] = dn[i];
-          cur = nxt;
-        }
-        flags = wave_or_i32(flags);
-        if (lane == 0 && flags) atomicOr(&flags_l, flags);
+      for (int i = 0; i < kSegVecs; ++i) {
+        const uint32_t vi = vbase + i * 64;
+        q[i] = load_vec(&rs.body[vi < last_vec ? vi : last_vec]);
       }
-      write_set();
-      __syncthreads();                      // run sums, flags and set entries are out
-      const int fl = flags_l;
-      direct = !unusable && (fl & 2) != 0;
-      tab_bad = (fl & 1) && check ? 1 : 0;
+    };
+    auto consume = [&](int run, const uint4 (&q)[kSegVecs]) {
+      const double run_sum = Terms::run_sum(q, uint32_t(run) * kRunVecs + lane, nvec, table, p.rT, flags);
+      if (lane == 0 && run < n_runs) subs_l[run] = run_sum;
+    };
+    auto next = [&]() {
+      int nr = 0;
+      if (lane == 0) nr = atomicAdd(&next_run, 1);
+      return __builtin_amdgcn_readfirstlane(nr);
+    };
+    uint4 d[kSegVecs], dn[kSegVecs];
+    int cur = wave;
+    request(cur, d);
+    Terms::build(table, p.rT, kResThreads, 1);    // the table's second half, while the requests travel
+    __syncthreads();                    // the table is complete
+    // the first run apart: behind it the set entry's target logit is requested, whose index has arrived
+    // by then
+    int nxt = next();
+    request(nxt, dn);
+    consume(cur, d);
+    request_target_at_index();
+#pragma unroll
+    for (int i = 0; i < kSegVecs; ++i) d[i] = dn[i];
+    cur = nxt;
+    while (cur < n_runs) {
+      nxt = next();
+      request(nxt, dn);
+      consume(cur, d);
+#pragma unroll
+      for (int i = 0; i < kSegVecs; ++i) d[i] = dn[i];
+      cur = nxt;
     }
+    flags = wave_or_i32(flags);
+    if (lane == 0 && flags) atomicOr(&flags_l, flags);
+  };
+  if (!unusable && n_runs > 0) {
+    if constexpr (kBits && ExpTab<T>::kSampled) {
+      if (bits) sweep(BitTerms<T>{});
+      else sweep(Pow{});
+    } else if constexpr (kBits) {
+      sweep(BitTerms<T>{});
+    } else {
+      sweep(Pow{});
+    }
+  } else {
+    __syncthreads();                      // flags_l is set up
   }
+  write_set();
+  __syncthreads();                        // run sums, flags and set entries are out
+  const int fl = flags_l;
+  const bool direct = !unusable && (fl & 2) != 0;   // |s| beyond kTabMaxS: the row is swept again, by its maxima
+  const int tab_bad = (fl & 1) && check ? 1 : 0;
   if (direct) {
-    if (table == nullptr) __syncthreads();      // flags_l is set up (a table sweep has had its barriers)
     // a run's four vectors per lane; a vector past the row's end reads as -inf
     auto load_run = [&](int run, uint4 (&q)[kSegVecs]) {
       const int64_t vbase = int64_t(run) * kRunVecs + lane;
@@ -361,12 +348,6 @@ __global__ __launch_bounds__(kResThreads) void verify_resample_kernel(const Veri
       __syncthreads();                          // run_max is reused by the next round
     }
   }
-  if (!wrote_set) {
-    write_set();
-    __syncthreads();
-  } else if (direct) {
-    __syncthreads();
-  }
   if (__builtin_amdgcn_readfirstlane(wave) >= kWaves) return;     // whole waves end here
 
   // ---- the first four waves: the pieces' masses, inverse CDF and outputs --------------------------
@@ -380,7 +361,7 @@ __global__ __launch_bounds__(kResThreads) void verify_resample_kernel(const Veri
         o.sum = bad_row ? 0.0 : t;
         o.bad = bad_row;
       } else {
-        // through the table the terms are referenced to 0: a segment reports that, or that it has no mass
+        // the terms are referenced to 0: a segment reports that, or that it has no mass
         for (int r = tid * kSubChunks; r < (tid + 1) * kSubChunks && r < n_runs; ++r) t += subs_l[r];
         for (int r = n_runs; r < (tid + 1) * kSubChunks; ++r) if (r >= tid * kSubChunks) subs_l[r] = 0.0;
         o.sum = tab_bad ? 0.0 : t;
@@ -438,7 +419,7 @@ __global__ __launch_bounds__(kResThreads) void verify_resample_kernel(const Veri
   a.n_cands = 0;
   a.u = u_res;
   a.unusable = unusable;
-  a.table = direct ? nullptr : table;
+  a.table = direct || !bits ? nullptr : table;
   const int token = finish_core<T>(a, sh, st, &se);
 
   int32_t* ot = p.out_tokens + size_t(b) * (p.gamma + 1);
@@ -470,10 +451,18 @@ template <typename T> hipError_t launch_verify(VerifyParams p, hipStream_t s, in
     }
   }
   if (phases & 2) {
-    p.use_table = exp_table_usable<T>(p.rT) ? 1 : 0;
-    const size_t lds = p.use_table ? ExpTab<T>::kBytes : 0;
-    if (lds > 48 * 1024 && (e = allow_dynamic_lds<&verify_resample_kernel<T>>(int(lds))) != hipSuccess) return e;
-    hipLaunchKernelGGL(verify_resample_kernel<T>, dim3(unsigned(p.B)), dim3(kResThreads), lds, s, p);
+    // binary16: building the table (14336 exponentials in 112 KB) costs as much as summing some 100 000 elements
+    // without it (V = 32000, one sequence: 13.2 us by PowTerms, 19.0 through the table; 45696, 455 sequences: 29.5
+    // and 40.6; 103188: 24.2 and 25.0; 128256, 200 sequences: 29.9 and 27.9)
+    const bool bits = exp_table_usable<T>(p.rT) && (!ExpTab<T>::kSampled || p.V >= 114688);
+    const size_t lds = bits ? ExpTab<T>::kBytes : PowTerms<T>::kBytes;
+    if constexpr (ExpTab<T>::kHas) {
+      if (bits) {
+        if (lds > 48 * 1024 && (e = allow_dynamic_lds<&verify_resample_kernel<T, true>>(int(lds))) != hipSuccess) return e;
+        hipLaunchKernelGGL((verify_resample_kernel<T, true>), dim3(unsigned(p.B)), dim3(kResThreads), lds, s, p);
+      }
+    }
+    if (!bits) hipLaunchKernelGGL((verify_resample_kernel<T, false>), dim3(unsigned(p.B)), dim3(kResThreads), lds, s, p);
     e = hipGetLastError();
   }
   return e;

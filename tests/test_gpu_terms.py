@@ -1,0 +1,76 @@
+"""The terms of the fp64 sweeps at the edges of the range in which they may be referenced to 0 (|s| <= 600): values
+beyond it on either side, masked and broken rows, temperatures at which the 16-bit tables cannot be used, and
+ragged vocabularies, for chains and for trees, against the oracle."""
+import numpy as np
+import pytest
+import torch
+
+from paper_2512_16273_amd import workloads as W
+from tests import _parity as P
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda:0"
+
+
+def t32(a):
+    return torch.from_numpy(np.ascontiguousarray(a)).to(DEV)
+
+
+def edge_rows(t):
+    """Rows that leave the range, one way per sequence or node (t [n, V] fp32)."""
+    t[0, ::7] = -700.0                        # far below: exp is 0 beside the rest of the row
+    t[1] += 650.0                             # the whole row above the range
+    t[2, 100:] = -float("inf")                # mostly masked
+    t[3] -= 640.0                             # the whole row below the range
+    t[4, 3::5] = -float("inf")
+    t[5, 0] = -599.0                          # just inside, and just outside
+    t[5, -1] = -601.0
+    return t
+
+
+@pytest.mark.parametrize("dtype,V,T", [("f32", 9001, 1.0), ("f32", 4096, 0.7), ("f32", 1000, 1.0), ("bf16", 9001, 0.15),
+                                       ("f16", 9001, 0.05), ("f16", 9001, 1.0), ("f16", 120000, 1.0)])
+def test_chain_terms(tslt, dtype, V, T):
+    w = W.scaled(W.WORKLOADS["chain_topk"], B=7, V=V, gamma=3, dtype=dtype, T=T)
+    if T < 0.5:                               # scaled values as at T = 1
+        w = W.scaled(w, sigma=w.sigma * T, zipf=w.zipf * T, noise_t=w.noise_t * T)
+    chain = W.make_chain(w, 19, DEV)
+    target = chain["target"].float()
+    target[:6, 0] = edge_rows(target[:6, 0].clone())
+    target[:6, 3] = edge_rows(target[:6, 3].clone())        # the bonus rows
+    chain["target"] = target.to(W.torch_dtype(dtype))
+    u_acc = chain["u_accept"].clone()
+    u_acc[:, 0] = 0.9995
+    u_acc[:2] = 0.0
+    chain["u_accept"] = u_acc
+    ref = P.oracle_chain(P.to_np(chain["draft"]), P.to_np(chain["target"]), w.T, w.top_k, w.top_p, w.k_cap,
+                         P.to_np(chain["u_sample"]), P.to_np(u_acc), P.to_np(chain["u_resample"]))
+    out = tslt.verify(chain["target"], w.T, t32(ref["q_idx"]), t32(ref["q_logit"]), t32(ref["q_count"]), t32(ref["tokens"]),
+                      u_acc, chain["u_resample"])
+    torch.cuda.synchronize()
+    # a rate below fp32's range cannot be told from 0 in the fp32 output
+    ref["verify"]["beta_hat"] = ref["verify"]["beta_hat"].astype(np.float32)
+    print(P.compare_verify(out, ref["verify"], label=f"{dtype} {V} {T}"), ref["verify"]["accept_len"])
+
+
+@pytest.mark.parametrize("dtype,V,T", [("f32", 9001, 1.0), ("f32", 4097, 0.6), ("f16", 9001, 0.9), ("bf16", 9001, 0.15)])
+def test_tree_terms(tslt, dtype, V, T):
+    w = W.scaled(W.WORKLOADS["tree"], B=2, V=V, expansion=(3, 2), top_k=8, k_cap=8, dtype=dtype, T=T)
+    if T < 0.5:
+        w = W.scaled(w, sigma=w.sigma * T, zipf=w.zipf * T, noise_t=w.noise_t * T)
+    tree = W.make_tree(w, 23, DEV)
+    target = tree["target"].float()
+    target[0, 4:10] = edge_rows(target[0, 4:10].clone())             # the leaves
+    rows = target[1, :6].clone()                                     # the non-leaf nodes, without the shifted rows (there
+    rows[[0, 4, 2, 1, 3, 5]] = edge_rows(rows[[0, 4, 2, 1, 3, 5]])   # the fp32 pass over the row rounds by |z| / 2^24)
+    target[1, :4] = torch.stack([rows[0], rows[4], rows[2], rows[5]])
+    tree["target"] = target.to(W.torch_dtype(dtype))
+    ref = P.oracle_tree(P.to_np(tree["draft"]), P.to_np(tree["target"]), w.T, w.top_k, w.top_p, w.k_cap, w.expansion,
+                        P.to_np(tree["u_sample"]), P.to_np(tree["u_accept"]), P.to_np(tree["u_resample"]), False, False)
+    args = [tree["target"], w.T, w.expansion, t32(ref["q_idx"]), t32(ref["q_logit"]), t32(ref["q_count"]), t32(ref["cands"]),
+            tree["u_accept"], tree["u_resample"]]
+    out = tslt.verify_tree(*args, all_nodes=True)
+    path = tslt.verify_tree(*args, all_nodes=False)
+    torch.cuda.synchronize()
+    print(P.compare_tree(out, ref, w.expansion, all_nodes=True, label=f"{dtype} {V} {T}"))
+    assert torch.equal(path["seq"], out["seq"]) and torch.equal(path["len"], out["len"])
