@@ -9,7 +9,7 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
 LIB_PATH = os.path.join(HERE, "libtslt.so")
 SOURCES = [os.path.join(HERE, "csrc", "tslt.hip")]
-HEADERS = [os.path.join(HERE, "csrc", n) for n in ("common.h", "truncate.h", "sample.h", "verify.h", "rowops.h", "exp64.h", "tree.h", "wire.h", "stats.h", "calib.h")] + \
+HEADERS = [os.path.join(HERE, "csrc", n) for n in ("common.h", "truncate.h", "sample.h", "verify.h", "rowops.h", "rowsample.h", "exp64.h", "tree.h", "wire.h", "stats.h", "calib.h")] + \
           [os.path.join(ROOT, "include", "tslt.h")]
 
 
@@ -18,6 +18,10 @@ def hipcc_command(out: str = LIB_PATH) -> list:
     return [hipcc, "-O3", "-std=c++17", "--offload-arch=gfx950", "-fPIC", "-shared",
             # packed-fp32 instructions are kept out of the generated code
             "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
+            # loop-invariant code motion after instruction selection: it carries fp64 constants through the tree
+            # kernels' loops in vector registers, to the point of spilling (path of 64 trees 44 us with it, 39 without;
+            # two trees, every node, 343 and 327)
+            "-mllvm", "-disable-machine-licm",
             "-Wall", "-Wno-unused-function",
             "-I", os.path.join(ROOT, "include"), "-I", os.path.join(HERE, "csrc"),
             "-o", out] + SOURCES

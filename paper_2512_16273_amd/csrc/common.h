@@ -89,6 +89,22 @@ template <> __device__ __forceinline__ void unpack<F16>(const uint4& w, float (&
   v[6] = f16_lo(w.w); v[7] = f16_hi(w.w);
 }
 
+// The scaled logits s = fl32(z * rT) of a vector (binary16: widened and multiplied by one instruction; adding -0 to
+// the product keeps it as it is).
+template <typename T> __device__ __forceinline__ void unpack_scaled(const uint4& w, float rT, float (&s)[ElemTraits<T>::kPerVec]) {
+  unpack<T>(w, s);
+#pragma unroll
+  for (int e = 0; e < ElemTraits<T>::kPerVec; ++e) s[e] = __fmul_rn(s[e], rT);
+}
+template <> __device__ __forceinline__ void unpack_scaled<F16>(const uint4& w, float rT, float (&s)[8]) {
+  const uint32_t x[4] = {w.x, w.y, w.z, w.w};
+#pragma unroll
+  for (int k = 0; k < 4; ++k) {
+    s[2 * k] = __builtin_fmaf(f16_lo(x[k]), rT, -0.0f);
+    s[2 * k + 1] = __builtin_fmaf(f16_hi(x[k]), rT, -0.0f);
+  }
+}
+
 template <typename T> __device__ __forceinline__ uint4 neg_inf_vec();
 template <> __device__ __forceinline__ uint4 neg_inf_vec<float>() {
   return make_uint4(kNegInfBits, kNegInfBits, kNegInfBits, kNegInfBits);
@@ -158,11 +174,6 @@ __device__ __forceinline__ uint4 buffer_load_vec_stream(__amdgpu_buffer_rsrc_t r
   u32x4_t v = __builtin_amdgcn_raw_buffer_load_b128(r, int(lane_bytes), int(wave_bytes), 2);      // 2: nontemporal
   return make_uint4(v.x, v.y, v.z, v.w);
 }
-__device__ __forceinline__ uint4 buffer_load_vec(__amdgpu_buffer_rsrc_t r, uint32_t lane_bytes, uint32_t wave_bytes) {
-  u32x4_t v = __builtin_amdgcn_raw_buffer_load_b128(r, int(lane_bytes), int(wave_bytes), 0);
-  return make_uint4(v.x, v.y, v.z, v.w);
-}
-
 // max of three without the NaN-quieting moves the compiler adds around fmaxf (NaNs are found by other means)
 __device__ __forceinline__ float max3f(float a, float b, float c) {
   float r;
@@ -180,10 +191,9 @@ __device__ __forceinline__ int lanes_below(uint64_t mask) {
   return __builtin_amdgcn_mbcnt_hi(uint32_t(mask >> 32), __builtin_amdgcn_mbcnt_lo(uint32_t(mask), 0));
 }
 
-__device__ __forceinline__ double shfl_f64(double v, int src) {
-  int lo = __double2loint(v), hi = __double2hiint(v);
-  lo = __shfl(lo, src, 64); hi = __shfl(hi, src, 64);
-  return __hiloint2double(hi, lo);
+// The value of one lane, named by a wave-uniform number, in all lanes (no LDS round trip).
+__device__ __forceinline__ double lane_f64(double v, int src) {
+  return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(v), src), __builtin_amdgcn_readlane(__double2loint(v), src));
 }
 
 // Cross-lane moves on the VALU's data-parallel-primitive path (no LDS round trip).  A lane whose source lies
@@ -200,6 +210,12 @@ __device__ __forceinline__ double dpp_f64(double old, double v) {
   const int hi = dpp_i32<CTRL, ROW_MASK, BANK_MASK>(__double2hiint(old), __double2hiint(v));
   return __hiloint2double(hi, lo);
 }
+// (a lane without a source gets 0 and nothing has to be prepared for it)
+template <int CTRL> __device__ __forceinline__ double dpp_or_zero_f64(double v) {
+  const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(v), CTRL, 0xF, 0xF, true);
+  const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(v), CTRL, 0xF, 0xF, true);
+  return __hiloint2double(hi, lo);
+}
 // Inclusive scan over the 64 lanes of a wave with an associative operation `op` whose identity is `id`:
 // four steps inside every row of 16, then the row totals are carried into the later rows.  Lane 63 ends up
 // with the reduction over the wave.
@@ -212,23 +228,36 @@ template <typename Op> __device__ __forceinline__ int wave_scan_i32(int v, int i
   v = op(v, dpp_i32<0x143, 0xC>(id, v));
   return v;
 }
-template <typename Op> __device__ __forceinline__ double wave_scan_f64(double v, double id, Op op) {
-  v = op(v, dpp_f64<0x111>(id, v));
-  v = op(v, dpp_f64<0x112>(id, v));
-  v = op(v, dpp_f64<0x114>(id, v));
-  v = op(v, dpp_f64<0x118>(id, v));
-  v = op(v, dpp_f64<0x142, 0xA>(id, v));
-  v = op(v, dpp_f64<0x143, 0xC>(id, v));
-  return v;
-}
 __device__ __forceinline__ int last_lane_i32(int v) { return __builtin_amdgcn_readlane(v, 63); }
 __device__ __forceinline__ double last_lane_f64(double v) {
   return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(v), 63), __builtin_amdgcn_readlane(__double2loint(v), 63));
 }
 
 __device__ __forceinline__ int wave_incl_scan_i32(int v) { return wave_scan_i32(v, 0, [](int a, int b) { return a + b; }); }
+// N sums at once: the steps of one fill the latencies of the others.
+template <int N> __device__ __forceinline__ void wave_incl_scan_f64(double (&v)[N]) {
+#pragma unroll
+  for (int i = 0; i < N; ++i) v[i] += dpp_or_zero_f64<0x111>(v[i]);
+#pragma unroll
+  for (int i = 0; i < N; ++i) v[i] += dpp_or_zero_f64<0x112>(v[i]);
+#pragma unroll
+  for (int i = 0; i < N; ++i) v[i] += dpp_or_zero_f64<0x114>(v[i]);
+#pragma unroll
+  for (int i = 0; i < N; ++i) v[i] += dpp_or_zero_f64<0x118>(v[i]);
+#pragma unroll
+  for (int i = 0; i < N; ++i) v[i] += dpp_f64<0x142, 0xA>(0.0, v[i]);
+#pragma unroll
+  for (int i = 0; i < N; ++i) v[i] += dpp_f64<0x143, 0xC>(0.0, v[i]);
+}
 __device__ __forceinline__ double wave_incl_scan_f64(double v) {
-  return wave_scan_f64(v, 0.0, [](double a, double b) { return a + b; });
+  double t[1] = {v};
+  wave_incl_scan_f64<1>(t);
+  return t[0];
+}
+template <int N> __device__ __forceinline__ void wave_sums_f64(double (&v)[N]) {
+  wave_incl_scan_f64<N>(v);
+#pragma unroll
+  for (int i = 0; i < N; ++i) v[i] = last_lane_f64(v[i]);
 }
 // Reductions over a wave; every lane gets the result.
 __device__ __forceinline__ double wave_sum_f64(double v) { return last_lane_f64(wave_incl_scan_f64(v)); }

@@ -1,0 +1,741 @@
+// A target row evaluated and sampled by one workgroup of 1024 threads, in fp64:
+//   row_sweep    one pass over the row for the masses sum exp(s - ref) of its runs, kept in LDS
+//   row_eval     the normaliser, and p and q_hat at the received set's entries
+//   row_test     the acceptance test of one candidate, row_update the residual update after a rejection
+//   row_locate, row_pick   the token at which the cumulative mass of p, or of what the updates made of it, passes
+//                u * total, in ascending token index: the run that holds it, then the element
+// fp64 is needed for the sampling: at V >= 128k the buckets of the inverse CDF are far narrower than fp32 prefix
+// sums can resolve.  One workgroup per row keeps the sums in LDS and one pass serves the test and the sample;
+// splitting a row over workgroups would need a device-scope fence per workgroup, which writes back and
+// invalidates the L2 of an XCD and costs far more than it saves.
+#pragma once
+#include <algorithm>
+#include <type_traits>
+#include "common.h"
+#include "exp64.h"
+#include "rowops.h"
+
+namespace tslt {
+
+constexpr int kRowThreads = 1024;                   // one entry of a received set per thread (TSLT_MAX_K_CAP)
+constexpr int kRowWaves = kRowThreads / 64;
+// Waves per SIMD asked of the compiler: 4 (128 registers) while every row has a compute unit to itself, where a
+// spilled value in the chain of steps after the sweep costs a memory latency; 8 (two workgroups on a compute unit)
+// for more rows than that, where one sweeps while the other is in that chain.
+constexpr int kAlone = 4, kShared = 8;
+constexpr int kMaxRuns = (kBlock - 2) * kSubChunks;
+constexpr int kMaxItems = kMaxRuns + 2;             // a row's runs, and the elements before and after its aligned body
+static_assert(kMaxItems <= kRowThreads, "one item per thread");
+
+// The fp64 terms of a row are made in one of two ways, both referenced to 0 rather than to the row maximum,
+// which is safe while |s| <= kTabMaxS; a row that holds a larger |s| is swept again, referenced to its maximum.
+//
+// BitTerms, bfloat16 rows: a table of exp(s), s = fl32(z / T), for every logit z of a magnitude range that holds
+// the bulk of a row; a term costs five instructions and one LDS read.
+//   bfloat16  2^-14 <= |z| < 2^7   5376 values, 42 KB  (logits centred on 0 have many small values)
+// With the 16 bits of an element rotated left by one (sign in bit 0), entry 1 + (rotated - 2*kLo) holds
+// its value; entries 0 and kEntries + 1 hold NaN and stand for everything below and above the table's
+// domain (tiny, huge, -inf, NaN), which is evaluated directly.
+//
+// PowTerms, every type: exp64.h's pow_exp on a table of 2^(i/2048) (16 KB).  19 instructions per term and one LDS
+// read instead of the 30 of exp64; bound by the vector units.  Resampling 48 fp32 rows of 151936: 53.7 us by
+// exp64, 29.9 so.  A bit table for binary16 (14336 values in 112 KB) was slower up to V = 100000 or so: to build it
+// costs as much as the row (V = 32000, one row 19.0 us against 13.2).
+constexpr float kTabMaxS = 600.0f;
+template <typename T> struct ExpTab {
+  static constexpr bool kHas = false;
+  static constexpr size_t kBytes = 0;
+};
+template <> struct ExpTab<Bf16> {
+  static constexpr bool kHas = true;
+  static constexpr int kLo = (127 - 14) << 7;      // bits of the smallest magnitude covered
+  static constexpr int kSpan = 21 << 7;            // magnitudes covered
+  static constexpr int kEntries = 2 * kSpan;
+  static constexpr size_t kBytes = size_t(kEntries + 2) * sizeof(double);
+  static constexpr float kMaxAbs = 128.0f;
+  static constexpr uint32_t kInf = 0x7F80u;
+  static __device__ __forceinline__ float widen(uint32_t bits) { return __uint_as_float(bits << 16); }
+};
+// Whether a launch may make its terms through the bit table: every entry's |s| is within the range.
+template <typename T> inline bool exp_table_usable(float rT) {
+  if constexpr (ExpTab<T>::kHas) return ExpTab<T>::kMaxAbs * rT <= kTabMaxS;
+  return false;
+}
+
+template <typename T> __device__ __forceinline__ double exp_table_entry(int i, float rT) {
+  using TB = ExpTab<T>;
+  if (i < 1 || i > TB::kEntries) return __longlong_as_double(0x7FF8000000000000ll);
+  const int j = i - 1;
+  const uint32_t bits = (uint32_t(j & 1) << 15) | uint32_t(TB::kLo + (j >> 1));
+  return exp64(double(__fmul_rn(TB::widen(bits), rT)));
+}
+// Fills the table with all `threads` threads of the workgroup; the caller synchronises.  `half` 0 / 1 fills the
+// first / second half only (a kernel that has requests to make between the two does so: the entries are
+// pure arithmetic, a good thing to have while data travels), -1 everything.
+template <typename T> __device__ __forceinline__ void build_exp_table(double* table, float rT, int threads, int half = -1) {
+  constexpr int n = ExpTab<T>::kEntries + 2;
+  const int mid = ((n / 2 + threads - 1) / threads) * threads;
+  const int lo = half == 1 ? mid : 0, hi = half == 0 ? mid : n;
+  for (int i = lo + threadIdx.x; i < hi; i += threads) table[i] = exp_table_entry<T>(i, rT);
+}
+
+// Sum of exp(s) over the 8 elements of a 16-bit vector through the table.  The index arithmetic runs on
+// both halves of a 32-bit word at once (16-bit lanes: rotate, saturating subtract, minimum).  An element
+// outside the table's domain reads a NaN entry, which shows in the sum: table_vec_sum_raw returns that NaN
+// (so that a caller can add several vectors up and look once), table_vec_redo evaluates a vector element by
+// element.
+typedef unsigned short ushort2_t __attribute__((ext_vector_type(2)));
+template <typename T>
+__device__ __forceinline__ double table_vec_sum_raw(const uint4& d, const double* table) {
+  using TB = ExpTab<T>;
+  const uint32_t w[4] = {d.x, d.y, d.z, d.w};
+  const ushort2_t base = {uint16_t(2 * TB::kLo - 1), uint16_t(2 * TB::kLo - 1)};
+  const ushort2_t top = {uint16_t(TB::kEntries + 1), uint16_t(TB::kEntries + 1)};
+  const ushort2_t one = {1, 1}, fifteen = {15, 15};
+  double s0 = 0.0, s1 = 0.0;
+#pragma unroll
+  for (int k = 0; k < 4; ++k) {
+    const ushort2_t x = __builtin_bit_cast(ushort2_t, w[k]);
+    const ushort2_t rot = (x << one) | (x >> fifteen);            // sign into bit 0 of each half
+    ushort2_t i2 = __builtin_elementwise_sub_sat(rot, base);
+    i2 = __builtin_elementwise_min(i2, top);
+    if constexpr (TB::kBytes <= 65536) {      // byte offsets fit the 16-bit lanes
+      const ushort2_t three = {3, 3};
+      const uint32_t off = __builtin_bit_cast(uint32_t, i2 << three);
+      const char* tb = reinterpret_cast<const char*>(table);
+      const double t0 = *reinterpret_cast<const double*>(tb + (off & 0xFFFFu));
+      const double t1 = *reinterpret_cast<const double*>(tb + (off >> 16));
+      s0 = k == 0 ? t0 : s0 + t0;
+      s1 = k == 0 ? t1 : s1 + t1;
+    } else {
+      const uint32_t ix = __builtin_bit_cast(uint32_t, i2);
+      const double t0 = table[ix & 0xFFFFu], t1 = table[ix >> 16];
+      s0 = k == 0 ? t0 : s0 + t0;
+      s1 = k == 0 ? t1 : s1 + t1;
+    }
+  }
+  return s0 + s1;
+}
+// Every element of a vector directly; branch-free, so that a wave in which some lane comes here for every
+// vector (a row with many values outside the table) runs at the pace of the direct path and not at that of
+// a divergent loop.  flags: 1 = NaN or +inf, 2 = |s| beyond kTabMaxS
+template <typename T>
+__device__ __forceinline__ double table_vec_redo(const uint4& d, float rT, int& flags) {
+  using TB = ExpTab<T>;
+  const uint32_t w[4] = {d.x, d.y, d.z, d.w};
+  double s = 0.0;
+#pragma unroll
+  for (int e = 0; e < 8; ++e) {
+    const uint32_t b = (w[e >> 1] >> ((e & 1) * 16)) & 0xFFFFu;
+    const float sv = __fmul_rn(TB::widen(b), rT);
+    const bool neg_inf = b == (0x8000u | TB::kInf);
+    flags |= ((b & 0x7FFFu) > TB::kInf || b == TB::kInf) ? 1 : 0;
+    flags |= (!neg_inf && fabsf(sv) > kTabMaxS) ? 2 : 0;
+    s += exp64(double(sv));                                       // -inf gives exactly 0
+  }
+  return s;
+}
+__device__ __forceinline__ float max3_nan(float a, float b, float c) {      // v_maximum3_f32: a NaN among them is kept
+  return __builtin_elementwise_maximum(__builtin_elementwise_maximum(a, b), c);
+}
+
+// How a sweep makes its terms.  build() fills the LDS table (all `threads` threads of the workgroup, the caller
+// synchronises; `half` as for build_exp_table); run_sum() gives the sum over a wave's run, of which every lane
+// holds kSegVecs vectors (vector i is vector vbase + 64 i of the row and counts if that is below nvec), and
+// raises flags: 1 = NaN or +inf among the elements, 2 = the row has to be swept by its maxima (which finds NaN
+// and +inf for itself).
+template <typename T> struct BitTerms {
+  static constexpr bool kBits = true;
+  static constexpr size_t kBytes = ExpTab<T>::kBytes;
+  static __device__ __forceinline__ void build(double* table, float rT, int threads, int half = -1) {
+    build_exp_table<T>(table, rT, threads, half);
+  }
+  // (the four vectors' look-ups go out together and one look at their total says whether a value was outside
+  // the table)
+  static __device__ __forceinline__ double run_sum(const uint4 (&q)[kSegVecs], uint32_t vbase, uint32_t nvec,
+                                                   const double* table, float rT, int& flags) {
+    double sv[kSegVecs];
+#pragma unroll
+    for (int i = 0; i < kSegVecs; ++i) sv[i] = table_vec_sum_raw<T>(q[i], table);
+#pragma unroll
+    for (int i = 0; i < kSegVecs; ++i) sv[i] = vbase + i * 64 < nvec ? sv[i] : 0.0;
+    double acc = (sv[0] + sv[1]) + (sv[2] + sv[3]);
+    if (acc != acc) {
+      acc = 0.0;
+#pragma unroll
+      for (int i = 0; i < kSegVecs; ++i)
+        if (vbase + i * 64 < nvec) acc += sv[i] == sv[i] ? sv[i] : table_vec_redo<T>(q[i], rT, flags);
+    }
+    return wave_sum_f64(acc);
+  }
+};
+template <typename T> struct PowTerms {
+  static constexpr bool kBits = false;
+  static constexpr size_t kBytes = size_t(kPowEntries) * sizeof(uint64_t);
+  static __device__ __forceinline__ void build(double* table, float, int threads, int half = -1) {
+    uint64_t* t = reinterpret_cast<uint64_t*>(table);
+    const int lo = half == 1 ? kPowEntries / 2 : 0, hi = half == 0 ? kPowEntries / 2 : kPowEntries;
+    for (int i = lo + threadIdx.x; i < hi; i += threads) t[i] = pow_entry(i);
+  }
+  // A term is made of max(s, -690), so that masked elements (-inf) need no branch: what they and other far ones
+  // add, 2e-300 each, is nothing beside any s >= -kTabMaxS.  A run without such an s is masked throughout (its
+  // sum is 0) or lies below the range.
+  static __device__ __forceinline__ double run_sum(const uint4 (&q)[kSegVecs], uint32_t vbase, uint32_t nvec,
+                                                   const double* table, float rT, int& flags) {
+    constexpr int E = ElemTraits<T>::kPerVec;
+    const uint64_t* t = reinterpret_cast<const uint64_t*>(table);
+    double acc = 0.0;
+    float top = -INFINITY;
+#pragma unroll
+    for (int i = 0; i < kSegVecs; ++i) {
+      float v[E];
+      unpack_scaled<T>(q[i], rT, v);
+      double s0 = 0.0, s1 = 0.0;
+#pragma unroll
+      for (int e = 0; e < E; e += 2) {
+        const float a = v[e], b = v[e + 1];
+        top = max3_nan(a, b, top);
+        const double ta = pow_exp(__builtin_amdgcn_fmed3f(a, -690.0f, 690.0f), t);
+        const double tb = pow_exp(__builtin_amdgcn_fmed3f(b, -690.0f, 690.0f), t);
+        s0 = e == 0 ? ta : s0 + ta;
+        s1 = e == 0 ? tb : s1 + tb;
+      }
+      acc += vbase + i * 64 < nvec ? s0 + s1 : 0.0;
+    }
+    flags |= top <= kTabMaxS ? 0 : 2;                   // NaN too
+    double sum = wave_sum_f64(acc);
+    if (sum < 1e-262) {                                 // (the same in all lanes; e^-600 is 2.7e-261)
+#pragma unroll
+      for (int i = 0; i < kSegVecs; ++i) {
+        uint4 w = q[i];
+        asm volatile("" : "+v"(w.x), "+v"(w.y), "+v"(w.z), "+v"(w.w));      // not to be done for every run
+        float v[E];
+        unpack<T>(w, v);
+#pragma unroll
+        for (int e = 0; e < E; ++e) flags |= v[e] > -INFINITY && vbase + i * 64 < nvec ? 2 : 0;
+      }
+      sum = 0.0;
+    }
+    return sum;
+  }
+};
+
+template <typename T> __device__ __forceinline__ float dword_element(uint32_t w, int i);
+template <> __device__ __forceinline__ float dword_element<float>(uint32_t w, int) { return as_f32(w); }
+template <> __device__ __forceinline__ float dword_element<Bf16>(uint32_t w, int i) { return as_f32(i ? w & 0xFFFF0000u : w << 16); }
+template <> __device__ __forceinline__ float dword_element<F16>(uint32_t w, int i) { return i ? f16_hi(w) : f16_lo(w); }
+
+// ---------------------------------------------------------------------------------------------
+// The row.  Its mass is held in "items", in row order: the elements before the aligned body, every run of the
+// body, the elements after it.  All sixteen waves sweep; what comes between the sweep and the search for the
+// element is a chain of short dependent steps over a few hundred set entries, which the first wave does alone out
+// of LDS (no barrier, no sum over waves, and the vector units to itself: with the same steps spread over sixteen
+// waves a redundant instruction costs sixteen issue slots; 7 us of the 15 that a row of 32000 took).
+// ---------------------------------------------------------------------------------------------
+struct RowShared {
+  double items[kMaxItems];
+  // the received set: token index (-1 outside the vocabulary), weight, mass of the row at it, and, once there has been
+  // an update, the distribution at it (row_locate leaves the correction to the row's mass in its place)
+  double set_w[kRowThreads], set_e[kRowThreads], set_a[kRowThreads];
+  int set_y[kRowThreads];
+  double w_part[kRowWaves], e_part[kRowWaves];      // their sums over the entries that a wave stored
+  double wave_sum[kRowWaves];
+  float wave_max[kRowWaves];
+  double target, before;
+  int flags, next_run, item, pick, last, cmd;
+};
+
+template <typename T> struct RowWork {
+  const void* row;
+  RowSplit rs;
+  int64_t V;
+  float rT;
+  int n_runs, n_items;
+  int count;            // entries of the received set
+  int y;                // this thread's entry: token index, payload, target logit
+  float ql, ql0, tv;
+  float smax;           // the reference of the masses
+};
+
+// What the first wave knows of the row (the same in all lanes).
+struct RowState {
+  double zp, sum_e;     // total mass, the set's part of it
+  double inv_zp;        // 1 / total mass: p is set_e * inv_zp before the first update
+  double inv_w;         // 1 / sum of the set's weights: q_hat is set_w * inv_w, a stage's proposal q_hat * qscale
+  double p_out, c, sum_a, qscale, removed;
+  int st, stages;
+  bool ok;
+};
+
+template <typename T>
+__device__ __forceinline__ void row_open(RowWork<T>& w, const void* row, int64_t V, float rT, RowShared& sh) {
+  w.row = row;
+  w.rs = split_row<T>(row, V);
+  w.V = V;
+  w.rT = rT;
+  w.n_runs = int((w.rs.nvec + kRunVecs - 1) / kRunVecs);
+  w.n_items = w.n_runs + 2;
+  if (threadIdx.x == 0) { sh.flags = 0; sh.next_run = kRowWaves; }      // published by the sweep's first barrier
+}
+
+// This thread's entry of a received set; every request is unconditional (a slot beyond the set reads the set's
+// last slot).
+template <typename T>
+__device__ __forceinline__ void row_take_set(RowWork<T>& w, const int32_t* qi, const float* ql, int count, int k_cap) {
+  const int tid = threadIdx.x;
+  const int slot = tid < k_cap ? tid : k_cap - 1;
+  w.y = qi[slot];
+  w.ql = ql[slot];
+  w.ql0 = ql[0];
+  w.count = count < 0 ? 0 : (count > k_cap ? k_cap : count);
+}
+// ... and the target logit at its index: a dependent request, to be made when the index has had time to arrive.
+template <typename T> __device__ __forceinline__ void row_gather(RowWork<T>& w) {
+  const bool valid = int(threadIdx.x) < w.count && w.y >= 0 && w.y < w.V;
+  w.y = valid ? w.y : -1;
+  w.tv = load_elem<T>(w.row, valid ? w.y : 0);
+}
+// The entry as the first wave needs it.  A value that is not finite or an index outside the vocabulary makes the
+// set unusable: the weight is NaN, which shows in the sum.
+template <typename T> __device__ __forceinline__ void row_store_set(const RowWork<T>& w, float smax, RowShared& sh) {
+  const int tid = threadIdx.x;
+  if (__builtin_amdgcn_readfirstlane(wave_id() * 64) < w.count) {       // whole waves
+    double wt = 0.0, e = 0.0;
+    if (tid < w.count) {
+      wt = fabsf(w.ql) < INFINITY && w.y >= 0 ? exp64(double(w.ql) - double(w.ql0)) : __longlong_as_double(0x7FF8000000000000ll);
+      e = w.y >= 0 && w.tv > -INFINITY ? exp64(double(__fmul_rn(w.tv, w.rT)) - double(smax)) : 0.0;
+      sh.set_y[tid] = w.y;
+      sh.set_w[tid] = wt;
+      sh.set_e[tid] = e;
+    }
+    double sums[2] = {wt, e};
+    wave_sums_f64(sums);
+    if (lane_id() == 0) { sh.w_part[wave_id()] = sums[0]; sh.e_part[wave_id()] = sums[1]; }
+  }
+}
+
+// The masses of the row's items, referenced to w.smax (0, or the row's maximum where |s| is too large for that),
+// and sh.flags (bit 0: NaN or +inf).  A wave takes run `wave` first and then whichever run is next (a counter in
+// LDS), so that the waves end together.  Every request of the loop is unconditional (a vector past the row's end
+// is read from the row's last vector and its sum dropped; a run past the last is the last one again, to no
+// effect): with requests inside branches the number in flight is not known where a wait is placed, and the wait
+// for the current run would wait for the run requested ahead as well.  While the first requests travel the terms'
+// table is made: all of it (half -1), its second half (1) or nothing (-2).
+template <typename T, typename Terms>
+__device__ __forceinline__ void row_sweep(RowWork<T>& w, double* table, int half, RowShared& sh) {
+  constexpr int E = ElemTraits<T>::kPerVec;
+  const int tid = threadIdx.x, lane = lane_id(), wave = wave_id();
+  const RowSplit& rs = w.rs;
+  const int n_runs = w.n_runs, n_edge = rs.head + rs.tail;
+  const float rT = w.rT;
+  int flags = 0;
+  // the elements outside the aligned body: one per lane of the last wave
+  const bool edge_lane = wave == kRowWaves - 1 && lane < n_edge;
+  float edge_v = -INFINITY;
+  auto edges = [&](float m) {                // their masses; called by the whole last wave
+    const double t = edge_lane ? exp64(double(__fmul_rn(edge_v, rT)) - double(m)) : 0.0;
+    const double head = wave_sum_f64(lane < rs.head ? t : 0.0), tail = wave_sum_f64(lane < rs.head ? 0.0 : t);
+    if (lane == 0) { sh.items[0] = head; sh.items[w.n_items - 1] = tail; }
+  };
+  if (edge_lane) {
+    edge_v = load_elem<T>(w.row, edge_index<T>(rs, lane));
+    flags |= (edge_v != edge_v || edge_v == INFINITY) ? 1 : 0;
+    flags |= (edge_v > -INFINITY && fabsf(__fmul_rn(edge_v, rT)) > kTabMaxS) ? 2 : 0;
+  }
+  if (n_runs > 0) {
+    const uint32_t last_vec = uint32_t(rs.nvec - 1), nvec = uint32_t(rs.nvec);
+    auto request = [&](int run, uint4 (&q)[kSegVecs]) {
+      const uint32_t vbase = uint32_t(run < n_runs ? run : n_runs - 1) * kRunVecs + lane;
+#pragma unroll
+      for (int i = 0; i < kSegVecs; ++i) {
+        const uint32_t vi = vbase + i * 64;
+        q[i] = load_vec(&rs.body[vi < last_vec ? vi : last_vec]);
+      }
+    };
+    auto consume = [&](int run, const uint4 (&q)[kSegVecs]) {
+      const double run_sum = Terms::run_sum(q, uint32_t(run) * kRunVecs + lane, nvec, table, rT, flags);
+      if (lane == 0 && run < n_runs) sh.items[1 + run] = run_sum;
+    };
+    auto next = [&]() {
+      int nr = 0;
+      if (lane == 0) nr = atomicAdd(&sh.next_run, 1);
+      return __builtin_amdgcn_readfirstlane(nr);
+    };
+    uint4 d[kSegVecs], dn[kSegVecs];
+    int cur = wave;
+    request(cur, d);
+    if (half > -2) Terms::build(table, rT, kRowThreads, half);
+    __syncthreads();                    // the table is complete
+    // the first run apart: behind it the set entry's target logit is requested, whose index has arrived by then
+    int nxt = next();
+    request(nxt, dn);
+    if (cur < n_runs) consume(cur, d);
+    row_gather(w);
+#pragma unroll
+    for (int i = 0; i < kSegVecs; ++i) d[i] = dn[i];
+    cur = nxt;
+    while (cur < n_runs) {
+      nxt = next();
+      request(nxt, dn);
+      consume(cur, d);
+#pragma unroll
+      for (int i = 0; i < kSegVecs; ++i) d[i] = dn[i];
+      cur = nxt;
+    }
+  } else {
+    __syncthreads();
+    row_gather(w);
+  }
+  row_store_set(w, 0.0f, sh);
+  if (wave == kRowWaves - 1) edges(0.0f);
+  flags = wave_or_i32(flags);
+  if (lane == 0 && flags) atomicOr(&sh.flags, flags);
+  __syncthreads();
+  w.smax = 0.0f;
+  if (sh.flags & 2) {
+    // |s| beyond kTabMaxS: the row again, in two passes, referenced to its maximum
+    float vmax = -INFINITY;
+    int bad = 0;
+    for (int64_t vi = tid; vi < rs.nvec; vi += kRowThreads) {
+      float v[E];
+      unpack<T>(load_vec(&rs.body[vi]), v);
+#pragma unroll
+      for (int e = 0; e < E; ++e) {
+        bad |= (v[e] != v[e] || v[e] == INFINITY) ? 1 : 0;
+        vmax = fmaxf(vmax, v[e]);
+      }
+    }
+    if (edge_lane) {
+      bad |= (edge_v != edge_v || edge_v == INFINITY) ? 1 : 0;
+      vmax = fmaxf(vmax, edge_v);
+    }
+    vmax = wave_max_f32(vmax);
+    bad = wave_or_i32(bad);
+    if (lane == 0) { sh.wave_max[wave] = vmax; if (bad) atomicOr(&sh.flags, 1); }
+    __syncthreads();
+    for (int k = 0; k < kRowWaves; ++k) vmax = fmaxf(vmax, sh.wave_max[k]);
+    const float smax = __fmul_rn(vmax, rT);      // scaling is monotone
+    if (smax > -INFINITY) {                      // (else nothing is above -inf: every item has been given 0)
+      w.smax = smax;
+      for (int run = wave; run < n_runs; run += kRowWaves) {
+        double acc = 0.0;
+        for (int i = 0; i < kSegVecs; ++i) {
+          const int64_t vi = int64_t(run) * kRunVecs + i * 64 + lane;
+          if (vi < rs.nvec) {
+            float v[E];
+            unpack<T>(load_vec(&rs.body[vi]), v);
+#pragma unroll
+            for (int e = 0; e < E; ++e) acc += exp64(double(__fmul_rn(v[e], rT)) - double(smax));    // -inf gives exactly 0
+          }
+        }
+        acc = wave_sum_f64(acc);
+        if (lane == 0) sh.items[1 + run] = acc;
+      }
+      if (wave == kRowWaves - 1) edges(smax);
+      row_store_set(w, smax, sh);
+    }
+    __syncthreads();
+  }
+}
+
+// Passes over the set's entries by one wave, four per lane at a time: load(k, i) for all four first, so that their
+// LDS reads are in flight together, then body(k, i, valid).  (An entry beyond the set is read, within the arrays,
+// and not counted.)
+template <typename L, typename F> __device__ __forceinline__ void over_set(int count, L load, F body) {
+  for (int i0 = lane_id(); i0 < count; i0 += 256) {
+#pragma unroll
+    for (int k = 0; k < 4; ++k) load(k, i0 + 64 * k);
+#pragma unroll
+    for (int k = 0; k < 4; ++k) body(k, i0 + 64 * k, i0 + 64 * k < count);
+  }
+}
+
+// First wave: normaliser, and p and q_hat at the set.  A row that holds NaN or +inf, or nothing above -inf, is
+// unusable.
+template <typename T> __device__ __forceinline__ void row_eval(const RowWork<T>& w, RowState& r, RowShared& sh) {
+  const int lane = lane_id();
+  const int n_stored = (w.count + 63) / 64;        // waves that stored entries
+  double sum_w = lane < n_stored ? sh.w_part[lane & 15] : 0.0, sum_e = lane < n_stored ? sh.e_part[lane & 15] : 0.0;
+  double zp = 0.0;
+  for (int i0 = lane; i0 < w.n_items; i0 += 256) {
+    double t[4];
+#pragma unroll
+    for (int k = 0; k < 4; ++k) t[k] = i0 + 64 * k < w.n_items ? sh.items[i0 + 64 * k] : 0.0;
+    zp += (t[0] + t[1]) + (t[2] + t[3]);
+  }
+  double sums[3] = {zp, sum_w, sum_e};
+  wave_sums_f64(sums);
+  r.zp = sums[0];
+  sum_w = sums[1];
+  r.sum_e = sums[2];
+  r.st = (sh.flags & 1) ? 1 : (r.zp > 0.0 ? 0 : 2);
+  r.ok = r.st == 0;
+  if (sum_w != sum_w) { r.st |= kRowBadSet; r.ok = false; }
+  // (one reciprocal each instead of a division per entry: an fp64 division is some thirty instructions)
+  r.inv_zp = r.ok ? 1.0 / r.zp : 0.0;
+  r.inv_w = sum_w > 0.0 ? 1.0 / sum_w : 0.0;
+  r.sum_a = r.sum_e * r.inv_zp;
+  r.p_out = 1.0 - r.sum_a > 0.0 ? 1.0 - r.sum_a : 0.0;
+  r.c = 1.0;
+  r.qscale = 1.0;
+  r.removed = 0.0;
+  r.stages = 0;
+}
+
+// First wave: the test of candidate x against the distribution as it stands and the stage's proposal: its ratio (-1
+// if x is not in the set), the mass the two share (sum of their minima), and what an update needs.
+struct RowTest {
+  double ratio, shared, part, q_x;
+  bool found;
+};
+// (q_x, a_x: the lane's, where it holds x)
+__device__ __forceinline__ RowTest row_test_result(double part, double shared, double q_x, double a_x, double qscale) {
+  RowTest t;
+  const double ratio = a_x / (q_x * qscale);
+  double sums[2] = {part, shared};
+  wave_sums_f64(sums);
+  t.part = sums[0];
+  t.shared = sums[1];
+  const uint64_t at = ballot(q_x > 0.0);
+  t.found = at != 0;
+  const int src = t.found ? 63 - __clzll((long long)at) : 0;
+  t.q_x = lane_f64(q_x, src);
+  t.ratio = t.found ? lane_f64(ratio, src) : -1.0;
+  return t;
+}
+template <typename T>
+__device__ __forceinline__ RowTest row_test(const RowWork<T>& w, const RowState& r, int x, const RowShared& sh) {
+  double part = 0.0, shared = 0.0, q_x = 0.0, a_x = 0.0;
+  const double* src_a = r.stages ? sh.set_a : sh.set_e;
+  const double a_scale = r.stages ? 1.0 : r.inv_zp;
+  int y[4];
+  double a[4], q0[4];
+  over_set(w.count, [&](int k, int i) { y[k] = sh.set_y[i]; a[k] = src_a[i]; q0[k] = sh.set_w[i]; },
+           [&](int k, int, bool valid) {
+    const double ak = a[k] * a_scale, qk = q0[k] * r.inv_w;
+    const double d = ak - qk * r.qscale > 0.0 ? ak - qk * r.qscale : 0.0;
+    valid = valid && y[k] >= 0;
+    part += valid ? d : 0.0;
+    shared += valid ? ak - d : 0.0;                // min(a, q)
+    const bool mine = valid && y[k] == x && qk > 0.0;
+    q_x = mine ? qk : q_x;
+    a_x = mine ? ak : a_x;
+  });
+  return row_test_result(part, shared, q_x, a_x, r.qscale);
+}
+// First wave, before any update: row_test, and in the same pass what row_locate would do to the masses if the
+// candidate were rejected: a becomes max(0, p - q) / Z and the mass off the set e / (zp Z), so that Z drops out of
+// an entry's mass in units of the row's terms.  (An accepted candidate's row is not looked at again.)
+template <typename T>
+__device__ __forceinline__ int item_of(const RowWork<T>& w, int y) {
+  if (y < w.rs.head) return 0;
+  const int v = (y - w.rs.head) / ElemTraits<T>::kPerVec;
+  return v >= w.rs.nvec ? w.n_items - 1 : 1 + v / kRunVecs;
+}
+template <typename T>
+__device__ __forceinline__ RowTest row_test_first(const RowWork<T>& w, const RowState& r, int x, RowShared& sh) {
+  double part = 0.0, shared = 0.0, q_x = 0.0, a_x = 0.0;
+  int y[4];
+  double e[4], q[4];
+  over_set(w.count, [&](int k, int i) { y[k] = sh.set_y[i]; e[k] = sh.set_e[i]; q[k] = sh.set_w[i]; },
+           [&](int k, int i, bool valid) {
+    const double a = e[k] * r.inv_zp, qk = q[k] * r.inv_w;
+    const double d = a - qk > 0.0 ? a - qk : 0.0;
+    valid = valid && y[k] >= 0;
+    part += valid ? d : 0.0;
+    shared += valid ? a - d : 0.0;                 // min(a, q)
+    const bool mine = valid && y[k] == x && qk > 0.0;
+    q_x = mine ? qk : q_x;
+    a_x = mine ? a : a_x;
+    if (valid) {
+      const double corr = d * r.zp - e[k];
+      sh.set_a[i] = corr;
+      atomicAdd(&sh.items[item_of(w, y[k])], corr);
+    }
+  });
+  return row_test_result(part, shared, q_x, a_x, 1.0);
+}
+// First wave: p <- norm(max(0, p - proposal)), with the sum over the set that row_test returned; `gone` leaves the
+// proposal (a candidate drawn without replacement; -1: none).
+template <typename T>
+__device__ __forceinline__ void row_update(const RowWork<T>& w, RowState& r, double part, int gone, RowShared& sh) {
+  const double Z = part + r.c * r.p_out;
+  const double inv_Z = Z > 0.0 ? 1.0 / Z : 1.0;
+  const double* src_a = r.stages ? sh.set_a : sh.set_e;
+  const double a_scale = r.stages ? 1.0 : r.inv_zp;
+  int y[4];
+  double a[4], wt[4];
+  over_set(w.count, [&](int k, int i) { y[k] = sh.set_y[i]; a[k] = src_a[i]; wt[k] = sh.set_w[i]; },
+           [&](int k, int i, bool valid) {
+    const double d = a[k] * a_scale - wt[k] * r.inv_w * r.qscale;
+    if (valid) {
+      sh.set_a[i] = y[k] >= 0 && d > 0.0 ? d * inv_Z : 0.0;
+      if (y[k] == gone && y[k] >= 0) sh.set_w[i] = 0.0;
+    }
+  });
+  r.c *= inv_Z;
+  r.sum_a = part * inv_Z;
+  ++r.stages;
+}
+
+// First wave: the masses after the updates made so far, and with `part` >= 0 one more with that sum: e_y off the set
+// and a * z_p / c on it, in units of the row's terms.  The set's corrections are added to the items they fall into;
+// returns their total.
+template <typename T>
+__device__ __forceinline__ double row_correct(const RowWork<T>& w, const RowState& r, double part, RowShared& sh) {
+  // with one more update a becomes max(0, a - q) / Z and c becomes c / Z: Z drops out of a * z_p / c
+  const double zp_over_c = r.zp / r.c;
+  const double* src_a = r.stages ? sh.set_a : sh.set_e;
+  const double a_scale = r.stages ? 1.0 : r.inv_zp;
+  const double q_scale = part >= 0.0 ? r.inv_w * r.qscale : 0.0;
+  int y[4];
+  double a[4], e[4], wt[4];
+  over_set(w.count, [&](int k, int i) { y[k] = sh.set_y[i]; a[k] = src_a[i]; e[k] = sh.set_e[i]; wt[k] = sh.set_w[i]; },
+           [&](int k, int i, bool valid) {
+    double ak = a[k] * a_scale;
+    if (part >= 0.0) {
+      ak -= wt[k] * q_scale;
+      ak = ak > 0.0 ? ak : 0.0;
+    }
+    if (valid && y[k] >= 0) {
+      const double corr = ak * zp_over_c - e[k];
+      sh.set_a[i] = corr;
+      atomicAdd(&sh.items[item_of(w, y[k])], corr);
+    }
+  });
+  return (part >= 0.0 ? part : r.sum_a) * zp_over_c - r.sum_e;
+}
+// First wave: the item in which the cumulative mass passes u * total, in row order, and what row_pick needs (item -1:
+// there is none).  `corr`: the total of the corrections.
+template <typename T>
+__device__ __forceinline__ void row_locate(const RowWork<T>& w, const RowState& r, float u, double corr, RowShared& sh) {
+  const int lane = lane_id();
+  const int n_items = w.n_items;
+  double total = r.zp + corr;
+  if (!(total > 0.0)) {          // defensive: an all-zero residual falls back to p itself
+    for (int i = lane; i < w.count; i += 64) {
+      const int y = sh.set_y[i];
+      if (y >= 0) { atomicAdd(&sh.items[item_of(w, y)], -sh.set_a[i]); sh.set_a[i] = 0.0; }
+    }
+    total = r.zp;
+  }
+  const double target = double(u) * total;
+  const int per = (n_items + 63) / 64;             // consecutive items per lane, four at a time
+  double lsum = 0.0;
+  for (int q = 0; q < per; q += 4) {
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      const int it = lane * per + q + k;
+      const double t = q + k < per && it < n_items ? sh.items[it] : 0.0;
+      lsum += t > 0.0 ? t : 0.0;
+    }
+  }
+  double run = wave_incl_scan_f64(lsum) - lsum;
+  int found = -1, last_pos = -1;
+  double found_before = 0.0, last_before = 0.0;
+  for (int q = 0; q < per; q += 4) {
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      const int it = lane * per + q + k;
+      const double t = q + k < per && it < n_items ? sh.items[it] : 0.0;
+      const bool pos = t > 0.0;
+      const bool hit = pos && run + t > target && found < 0;
+      last_pos = pos ? it : last_pos;
+      last_before = pos ? run : last_before;
+      found = hit ? it : found;
+      found_before = hit ? run : found_before;
+      run += pos ? t : 0.0;
+    }
+  }
+  // the first lane that saw the target passed, else the last one that holds an item with mass
+  const uint64_t hit = ballot(found >= 0), any = ballot(last_pos >= 0);
+  const int src = hit != 0 ? __ffsll((long long)hit) - 1 : (any != 0 ? 63 - __clzll((long long)any) : 0);
+  const int item = hit != 0 ? found : last_pos;
+  const double before = hit != 0 ? found_before : last_before;
+  if (lane == src) { sh.item = item; sh.before = before; sh.target = target; sh.pick = 0x7FFFFFFF; sh.last = -1; }
+}
+
+// The first four waves: the token, from what row_locate left (behind a barrier; the other waves have ended): every
+// thread takes one vector of the run.  `elem_corr`: LDS scratch of one double per element of a run (the terms'
+// table, which is not needed any more), set to zero by all threads since (row_clear).
+constexpr int kPickWaves = kRunVecs / 64;
+template <typename T> __device__ __forceinline__ void row_clear(double* elem_corr) {
+  constexpr int kRun = kRunVecs * ElemTraits<T>::kPerVec;
+#pragma unroll
+  for (int i = 0; i < kRun / kRowThreads; ++i) elem_corr[threadIdx.x + i * kRowThreads] = 0.0;
+}
+template <typename T>
+__device__ __forceinline__ int row_pick(const RowWork<T>& w, double* elem_corr, RowShared& sh) {
+  constexpr int E = ElemTraits<T>::kPerVec;
+  constexpr int kRun = kRunVecs * E;               // elements in a run
+  constexpr int kThreads = kPickWaves * 64;
+  static_assert(kThreads == kRunVecs, "a thread's share of a run is one vector");
+  const int tid = threadIdx.x, lane = lane_id(), wave = wave_id();
+  const RowSplit& rs = w.rs;
+  const double smax = double(w.smax), target = sh.target, before = sh.before;
+  const int item = __builtin_amdgcn_readfirstlane(sh.item);
+  if (item < 0) return -1;
+  // the run's first element and its end (an edge: fewer than E elements, walked by one thread)
+  const bool edge = item == 0 || item == w.n_items - 1;
+  const int e0 = item == 0 ? 0 : rs.head, e1 = item == 0 ? rs.head : rs.head + rs.tail;
+  const int64_t first = edge ? edge_index<T>(rs, e0) : rs.head + int64_t(item - 1) * kRun;
+  const int64_t end = edge ? first + (e1 - e0) : first + kRun;
+  const int64_t my_vec = int64_t(item - 1) * kRunVecs + tid;
+  const bool inside = !edge && my_vec < rs.nvec;
+  uint4 dv = neg_inf_vec<T>();
+  if (inside) dv = load_vec(&rs.body[my_vec]);     // travels while the corrections are laid out
+  for (int i = tid; i < w.count; i += kThreads) {
+    const int y = sh.set_y[i];
+    if (y >= first && y < end) elem_corr[y - first] = sh.set_a[i];
+  }
+  __syncthreads();
+  if (edge) {
+    if (tid == 0) {
+      double run_e = before;
+      for (int e = e0; e < e1; ++e) {
+        const int64_t y = edge_index<T>(rs, e);
+        const double v = exp64(double(__fmul_rn(load_elem<T>(w.row, y), w.rT)) - smax) + elem_corr[e - e0];
+        if (v > 0.0) {
+          sh.last = int(y);
+          run_e += v;
+          if (run_e > target) break;
+        }
+      }
+    }
+    __syncthreads();
+    return sh.last;
+  }
+  float t[E];
+  unpack<T>(dv, t);
+  double v[E], mine = 0.0;
+#pragma unroll
+  for (int i = 0; i < E; ++i) {
+    v[i] = exp64(double(__fmul_rn(t[i], w.rT)) - smax) + elem_corr[tid * E + i];      // -inf gives exactly 0
+    v[i] = v[i] > 0.0 && inside ? v[i] : 0.0;
+    mine += v[i];
+  }
+  const double inc = wave_incl_scan_f64(mine);
+  if (lane == 63) sh.wave_sum[wave] = inc;
+  __syncthreads();
+  double base = before;
+#pragma unroll
+  for (int k = 0; k < kPickWaves - 1; ++k) base += k < wave ? sh.wave_sum[k] : 0.0;
+  // the element at which the cumulative mass passes the target, else the last one with mass
+  int first_pass = 0x7FFFFFFF, last_mass = -1;
+  double run_e = base + (inc - mine);
+#pragma unroll
+  for (int i = 0; i < E; ++i) {
+    run_e += v[i];
+    last_mass = v[i] > 0.0 ? tid * E + i : last_mass;
+    first_pass = v[i] > 0.0 && run_e > target && first_pass == 0x7FFFFFFF ? tid * E + i : first_pass;
+  }
+  // (elements ascend with the lane: the first and the last lane that have one)
+  const uint64_t pass = ballot(first_pass != 0x7FFFFFFF), mass = ballot(last_mass >= 0);
+  if (pass != 0 && lane == __ffsll((long long)pass) - 1) atomicMin(&sh.pick, first_pass);
+  if (mass != 0 && lane == 63 - __clzll((long long)mass)) atomicMax(&sh.last, last_mass);
+  __syncthreads();
+  const int pick = sh.pick != 0x7FFFFFFF ? sh.pick : sh.last;
+  return pick >= 0 ? int(first + pick) : -1;
+}
+
+}  // namespace tslt

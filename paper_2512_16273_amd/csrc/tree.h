@@ -1,19 +1,14 @@
 // tslt_verify_tree: token-tree verification (Algorithm 8) with multi-candidate verification
 // (Algorithm 5) at every non-leaf node.  Nodes are stored breadth-first (Section 4.1).
 //
-// Kernel M, one workgroup per (tree, non-leaf node): eval_row_on_set over the node's target row, then
-// Algorithm 5 on the sparse representation.  With a sparse q_hat the distribution p^(i) is a vector
-// a on the set and a scalar multiple c of p outside it, and the update p^(i+1) = norm(max(0, p^(i) -
-// q_hat)) is a <- max(0, a - q_hat) / Z, c <- c / Z with Z = sum(max(0, a - q_hat)) + c * p_out: one
-// dense pass per node, O(k * K) work for the k candidates.
-// Kernel W, one wave per tree: the new-sequence search -- walk from the root through accepted
-// children, write the accepted prefix, remember the node at which the walk stops.
-// Kernels S and F: fp64 sweep and inverse CDF (rowops.h) for every node whose output has to be
-// sampled -- a non-leaf node whose k candidates were all rejected draws from P^(k+1), a leaf from its
-// target distribution.  Either every such node of the tree is sampled (node outputs requested) or
-// only the node that ends the verified path.
+// With a sparse q_hat the distribution p^(i) is a vector a on the set and a scalar multiple c of p outside it,
+// and the update p^(i+1) = norm(max(0, p^(i) - q_hat)) is a <- max(0, a - q_hat) / Z, c <- c / Z with
+// Z = sum(max(0, a - q_hat)) + c * p_out: one dense pass per node, O(k * K) work for the k candidates, and the
+// sums of that pass serve the draw as well (rowsample.h).  Bound by the vector units (fp32: 19 instructions an element,
+// 5.1 TB/s) or the LDS (bfloat16).  Two fp32 trees of 1365 nodes, V = 151936, every node: 546 us as a pass for the
+// tests, a sweep, a finish and two more launches, 330 so; the path of 64 binary16 trees <2,2,2>, V = 32000: 52 and 39.7.
 #pragma once
-#include "rowops.h"
+#include "rowsample.h"
 
 namespace tslt {
 
@@ -43,38 +38,30 @@ struct TreeParams {
   float* out_beta;        // [B, n_nodes - 1] stage acceptance rate sum_x min(q^(i), p^(i)) of every tested candidate
   int32_t* status;
   // workspace
-  int32_t* node_state;    // [B, n_int] 0 all candidates rejected, 1 a child accepted, 2 row unusable
-  int32_t* node_slot;     // [B, n_int] accepted child number or -1
-  int32_t* node_stages;   // [B, n_int] residual updates applied (candidates present and rejected)
-  int32_t* node_status;   // [B, n_int]
-  int32_t* term_node;     // [B] node at which the walk stops
-  int32_t* seq_status;    // [B] status accumulated over the tree
-  SegResult* segs;        // [B, tasks, n_seg + 2]
-  double* subs;           // [B, tasks, n_seg, kSubChunks]
-  int tasks;              // rows sampled per tree: n_nodes (all nodes) or 1 (path only)
+  // (every node evaluated only)
+  int32_t* node_state;    // [B, n_nodes] 0 sampled, 1 a child accepted, 2 row unusable
+  int32_t* node_slot;     // [B, n_nodes] accepted child number or -1
+  int32_t* node_token;    // [B, n_nodes] the node's output
+  int32_t* node_status;   // [B, n_nodes]
   int all_nodes;
-  int n_seg, n_seg_grid;
 };
 
+// (More than the kernels use: the size that callers have been told all along, so that a workspace kept from an
+// earlier version and one sized by this one are the same.)
 inline size_t tree_workspace_bytes(int64_t B, int64_t n_nodes, int64_t V, bool all_nodes) {
   const size_t n_seg = size_t(row_segments(V));
   const size_t tasks = all_nodes ? size_t(n_nodes) : 1;
   return align256(size_t(B) * n_nodes * 4) * 4 + align256(size_t(B) * 4) * 2 +
-         align256(size_t(B) * tasks * (n_seg + 2) * sizeof(SegResult)) +
+         align256(size_t(B) * tasks * (n_seg + 2) * 16) +
          align256(size_t(B) * tasks * n_seg * kSubChunks * sizeof(double));
 }
 inline void tree_carve_workspace(TreeParams& p, void* ws) {
   char* w = reinterpret_cast<char*>(ws);
-  p.n_seg = row_segments(p.V);
   const size_t per = align256(size_t(p.B) * p.n_nodes * 4);
   p.node_state = reinterpret_cast<int32_t*>(w); w += per;
   p.node_slot = reinterpret_cast<int32_t*>(w); w += per;
-  p.node_stages = reinterpret_cast<int32_t*>(w); w += per;
-  p.node_status = reinterpret_cast<int32_t*>(w); w += per;
-  p.term_node = reinterpret_cast<int32_t*>(w); w += align256(size_t(p.B) * 4);
-  p.seq_status = reinterpret_cast<int32_t*>(w); w += align256(size_t(p.B) * 4);
-  p.segs = reinterpret_cast<SegResult*>(w); w += align256(size_t(p.B) * p.tasks * (p.n_seg + 2) * sizeof(SegResult));
-  p.subs = reinterpret_cast<double*>(w);
+  p.node_token = reinterpret_cast<int32_t*>(w); w += per;
+  p.node_status = reinterpret_cast<int32_t*>(w);
 }
 
 template <typename T> __device__ __forceinline__ const void* tree_row(const TreeParams& p, int64_t b, int node) {
@@ -92,296 +79,181 @@ __device__ __forceinline__ int tree_first_child(const TreeParams& p, int node, i
 }
 
 // ---------------------------------------------------------------------------------------------
-// Kernel M: Algorithm 5 at one non-leaf node
+// One node of tree b, by all threads of a workgroup: Algorithm 5 at a non-leaf node, then, unless a child was
+// accepted, the draw of its output (a leaf: of its target distribution).  Writes the ratios and rates of the
+// candidates it tested; returns the state (0 sampled, 1 a child accepted, 2 row unusable), the accepted child in
+// `slot`, the output in `token` and the status bits in `st` (both as the first wave has them).  Unless a child was
+// accepted the terms' table is used up.
 // ---------------------------------------------------------------------------------------------
-// Algorithm 5 at non-leaf node `node` of tree b, by all threads of a workgroup.  Writes the node's state,
-// accepted child, number of updates and status to the workspace and the ratios of the candidates it
-// tested; returns the state (0 all candidates rejected, 1 a child accepted, 2 row unusable) and, in
-// `slot`, the accepted child.
-template <typename T>
-__device__ __forceinline__ int mcveri_node(const TreeParams& p, int64_t b, int node, VerifyShared& sh, int& slot, int& st) {
-  const int tid = threadIdx.x;
+template <typename T, typename Terms>
+__device__ __forceinline__ int tree_node(const TreeParams& p, int64_t b, int node, double* table, bool build, RowShared& sh,
+                                         int& slot, int& token, int& st) {
+  const int lane = lane_id();
+  const bool leaf = node >= p.n_int;
+  const int64_t row = b * p.n_int + (leaf ? 0 : node);
+  RowWork<T> w;
+  row_open<T>(w, tree_row<T>(p, b, node), p.V, p.rT, sh);
+  row_take_set(w, p.q_idx + size_t(row) * p.k_cap, p.q_logit + size_t(row) * p.k_cap, leaf ? 0 : p.q_count[row], p.k_cap);
+  const float u_res = p.u_resample[size_t(b) * p.n_nodes + node];
+  // candidate `lane` of a non-leaf node
   const int layer = tree_layer(p, node);
-  const int k = p.expansion[layer];
-  const int c0 = tree_first_child(p, node, layer);           // children are nodes c0 .. c0 + k - 1
-  const int32_t* cand = p.cand_tokens + size_t(b) * (p.n_nodes - 1) + (c0 - 1);
-  const float* u_acc = p.u_accept + size_t(b) * (p.n_nodes - 1) + (c0 - 1);
-  float* ratio_out = p.out_ratio ? p.out_ratio + size_t(b) * (p.n_nodes - 1) + (c0 - 1) : nullptr;
-  float* beta_out = p.out_beta ? p.out_beta + size_t(b) * (p.n_nodes - 1) + (c0 - 1) : nullptr;
-  const void* row = tree_row<T>(p, b, node);
-  const RowSplit rs = split_row<T>(row, p.V);
-  const int64_t r = b * p.n_int + node;
-  int count = p.q_count[r];
-  count = count < 0 ? 0 : (count > p.k_cap ? p.k_cap : count);
-  double a_s[kSetPer], q_s[kSetPer], p_out;
-  int yi[kSetPer];
-  bool ok;
-  eval_row_on_set<T>(row, rs, p.V, p.rT, p.k2, p.q_idx + size_t(r) * p.k_cap, p.q_logit + size_t(r) * p.k_cap, count, sh,
-                     a_s, q_s, yi, p_out, ok, st);
-  if (ratio_out && tid < k) ratio_out[tid] = NAN;              // candidates that are never tested
-  if (beta_out && tid < k) beta_out[tid] = NAN;
-  int accepted = -1, stages = 0;
-  if (ok) {
-    double c = 1.0;
-    double qscale = 1.0, removed = 0.0;       // the stage's proposal is q_s * qscale
-    for (int i = 0; i < k; ++i) {
-      const int x = cand[i];
-      if (x < 0) continue;                                      // absent candidate (block-uniform)
-      if (tid == 0) { sh.bcast_d[0] = -1.0; sh.bcast_d[1] = 0.0; sh.bcast_i[0] = 0; }
-      __syncthreads();
-      int mine = -1;
-#pragma unroll
-      for (int q = 0; q < kSetPer; ++q)
-        if (yi[q] == x && q_s[q] > 0.0 && atomicCAS(&sh.bcast_i[0], 0, 1) == 0) {
-          sh.bcast_d[0] = a_s[q] / (q_s[q] * qscale);
-          sh.bcast_d[1] = q_s[q];
-          mine = q;
+  const int k = leaf ? 0 : p.expansion[layer];
+  const int64_t c0 = leaf ? 0 : b * (p.n_nodes - 1) + tree_first_child(p, node, layer) - 1;
+  const int my_cand = p.cand_tokens[c0 + (lane < k ? lane : 0)];
+  const float my_u = p.u_accept[c0 + (lane < k ? lane : 0)];
+  row_sweep<T, Terms>(w, table, build ? -1 : -2, sh);
+  token = -1;
+  st = 0;
+  float my_ratio = NAN, my_beta = NAN;                              // NaN if the candidate is never tested
+  if (wave_id() == 0) {
+    RowState r;
+    row_eval(w, r, sh);
+    int accepted = -1;
+    double part = -1.0;                                             // of the last rejection, whose update is still to be made
+    if (!leaf) {
+      int gone = -1;
+      double gone_q = 0.0;
+      if (r.ok) {
+        for (int i = 0; i < k; ++i) {
+          const int x = __builtin_amdgcn_readlane(my_cand, i);
+          if (x < 0) continue;                                      // absent candidate
+          if (part >= 0.0) {                                        // the candidate before was rejected
+            row_update(w, r, part, gone, sh);
+            r.removed += gone_q;
+            const double rest = 1.0 - r.removed;
+            r.qscale = p.wor ? (rest > 0.0 ? 1.0 / rest : 0.0) : 1.0;
+          }
+          const RowTest t = row_test(w, r, x, sh);
+          if (!t.found) r.st |= 4;
+          if (lane == i) { my_ratio = float(t.ratio); my_beta = float(t.shared); }   // Section 4.3's beta^(i)
+          const double bound = t.ratio < 1.0 ? t.ratio : 1.0;
+          const float u = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(my_u), i));
+          if (t.found && double(u) < bound) { accepted = i; token = x; break; }
+          part = t.part;
+          // drawn without replacement: x leaves the urn and what is left is renormalised
+          gone = p.wor && t.found ? x : -1;
+          gone_q = gone >= 0 ? t.q_x : 0.0;
         }
-      __syncthreads();
-      const double ratio = sh.bcast_d[0];
-      const double q_x = sh.bcast_d[1];
-      const bool found = sh.bcast_i[0] != 0;
-      __syncthreads();
-      if (!found) st |= 4;
-      if (ratio_out && tid == 0) ratio_out[i] = float(ratio);
-      if (beta_out) {
-        // Section 4.3's beta^(i): the mass that the stage's proposal and p^(i) share (all of it lies on the set)
-        double shared = 0.0;
-#pragma unroll
-        for (int q = 0; q < kSetPer; ++q) {
-          const double qq = q_s[q] * qscale;
-          shared += (yi[q] >= 0) ? (a_s[q] < qq ? a_s[q] : qq) : 0.0;
-        }
-        shared = block_sum_f64<kWaves>(shared, sh.red);
-        if (tid == 0) beta_out[i] = float(shared);
       }
-      const double bound = ratio < 1.0 ? ratio : 1.0;
-      if (found && double(u_acc[i]) < bound) { accepted = i; break; }
-      // rejected: p <- norm(max(0, p - q)), q the proposal of this stage
-      double part = 0.0;
-#pragma unroll
-      for (int q = 0; q < kSetPer; ++q) {
-        const double d = a_s[q] - q_s[q] * qscale;
-        a_s[q] = (yi[q] >= 0 && d > 0.0) ? d : 0.0;
-        part += a_s[q];
-      }
-      const double Z = block_sum_f64<kWaves>(part, sh.red) + c * p_out;
-      if (Z > 0.0) {
-        const double inv_Z = 1.0 / Z;
-#pragma unroll
-        for (int q = 0; q < kSetPer; ++q) a_s[q] *= inv_Z;
-        c *= inv_Z;
-      }
-      if (p.wor && found) {
-        // drawn without replacement: x leaves the urn and what is left is renormalised
-#pragma unroll
-        for (int q = 0; q < kSetPer; ++q)
-          if (q == mine) q_s[q] = 0.0;
-        removed += q_x;
-        const double rest = 1.0 - removed;
-        qscale = rest > 0.0 ? 1.0 / rest : 0.0;
-      }
-      ++stages;
     }
+    if (accepted < 0 && r.ok) row_locate(w, r, u_res, r.stages > 0 || part >= 0.0 ? row_correct(w, r, part, sh) : 0.0, sh);
+    st = r.st;
+    if (lane == 0) sh.cmd = accepted >= 0 ? accepted : (r.ok ? -1 : -2);
   }
-  const int state = !ok ? 2 : (accepted >= 0 ? 1 : 0);
-  if (tid == 0) {
-    p.node_state[r] = state;
-    p.node_slot[r] = accepted;
-    p.node_stages[r] = stages;
-    p.node_status[r] = st;
+  __syncthreads();
+  slot = sh.cmd;
+  if (threadIdx.x < k) {
+    if (p.out_ratio) p.out_ratio[c0 + lane] = my_ratio;
+    if (p.out_beta) p.out_beta[c0 + lane] = my_beta;
   }
-  slot = accepted;
+  if (slot >= 0) return 1;
+  const int state = slot == -1 ? 0 : 2;
+  slot = -1;
+  if (state == 0) {
+    row_clear<T>(table);
+    __syncthreads();
+    if (wave_id() < kPickWaves) token = row_pick(w, table, sh);     // (nothing follows for the other waves)
+  }
   return state;
 }
 
-template <typename T>
-__global__ __launch_bounds__(kBlock, kAccWavesPerSimd) void tree_mcveri_kernel(const TreeParams p) {
-  __shared__ VerifyShared sh;
-  const int64_t b = blockIdx.x / p.n_int;
-  const int node = int(blockIdx.x - b * p.n_int);
-  int slot, st;
-  mcveri_node<T>(p, b, node, sh, slot, st);
+// ---------------------------------------------------------------------------------------------
+// Every node: one workgroup per node.
+// ---------------------------------------------------------------------------------------------
+template <typename T, typename Terms>
+__global__ __launch_bounds__(kRowThreads, kShared) void tree_node_kernel(const TreeParams p) {
+  __shared__ RowShared sh;
+  extern __shared__ __align__(16) unsigned char dyn_lds[];
+  const int64_t b = blockIdx.x / p.n_nodes;
+  const int node = int(blockIdx.x - b * p.n_nodes);
+  int slot, token, st;
+  const int state = tree_node<T, Terms>(p, b, node, reinterpret_cast<double*>(dyn_lds), true, sh, slot, token, st);
+  if (threadIdx.x == 0) {
+    const int64_t n = b * p.n_nodes + node;
+    p.node_state[n] = state;
+    p.node_slot[n] = slot;
+    p.node_token[n] = token;
+    p.node_status[n] = st;
+    if (p.out_node_token) p.out_node_token[n] = token;
+    if (p.out_node_slot) p.out_node_slot[n] = slot;
+  }
+}
+
+// The new-sequence search, one wave per tree.
+__global__ __launch_bounds__(64) void tree_walk_kernel(const TreeParams p) {
+  const int64_t b = blockIdx.x;
+  const int lane = threadIdx.x;
+  int st = 0;
+  for (int n = lane; n < p.n_nodes; n += 64) st |= p.node_status[b * p.n_nodes + n];
+  st = wave_or_i32(st);
+  if (lane == 0) {
+    int node = 0, layer = 0, len = 0;
+    int32_t* seq = p.out_seq + size_t(b) * (p.depth + 1);
+    while (node < p.n_int && p.node_state[b * p.n_nodes + node] == 1) {
+      const int child = tree_first_child(p, node, layer) + p.node_slot[b * p.n_nodes + node];
+      seq[len++] = p.node_token[b * p.n_nodes + node];
+      node = child;
+      ++layer;
+    }
+    seq[len] = p.node_token[b * p.n_nodes + node];
+    p.out_len[b] = len + 1;
+    for (int i = len + 1; i <= p.depth; ++i) seq[i] = -1;
+    if (p.status) p.status[b] = st;
+  }
 }
 
 // ---------------------------------------------------------------------------------------------
-// Kernel L (only the verified path is wanted): one workgroup per tree walks from the root, running
-// Algorithm 5 at each node it reaches and descending into the accepted child, so that depth + 1 target rows
-// are read per tree instead of one per non-leaf node.  Uniforms are indexed by node, so the result is the
-// one the all-nodes kernels give.  Leaves the stopping node to kernels S and F.
+// Only the verified path is wanted: one workgroup per tree walks from the root, running Algorithm 5 at each node
+// it reaches, descending into the accepted child and drawing the output of the node it stops at, so that at most
+// depth + 1 target rows are read per tree, each once.  Uniforms are indexed by node, so the result is the one the
+// all-nodes kernel gives.
 // ---------------------------------------------------------------------------------------------
-template <typename T>
-__global__ __launch_bounds__(kBlock) void tree_lazy_walk_kernel(const TreeParams p) {
-  __shared__ VerifyShared sh;
+template <typename T, typename Terms>
+__global__ __launch_bounds__(kRowThreads) void tree_path_kernel(const TreeParams p) {
+  __shared__ RowShared sh;
+  extern __shared__ __align__(16) unsigned char dyn_lds[];
   const int tid = threadIdx.x;
   const int64_t b = blockIdx.x;
-  for (int i = tid; i < p.n_nodes - 1; i += kBlock) {
+  for (int i = tid; i < p.n_nodes - 1; i += kRowThreads) {
     if (p.out_ratio) p.out_ratio[size_t(b) * (p.n_nodes - 1) + i] = NAN;
     if (p.out_beta) p.out_beta[size_t(b) * (p.n_nodes - 1) + i] = NAN;
   }
   __syncthreads();
   int32_t* seq = p.out_seq + size_t(b) * (p.depth + 1);
-  int node = 0, layer = 0, len = 0, st_all = 0;
-  while (node < p.n_int) {
+  int node = 0, layer = 0, len = 0, st_all = 0, token = -1;
+  for (;;) {
     int slot, st;
-    const int state = mcveri_node<T>(p, b, node, sh, slot, st);
+    const int state = tree_node<T, Terms>(p, b, node, reinterpret_cast<double*>(dyn_lds), node == 0, sh, slot, token, st);
     st_all |= st;
-    __syncthreads();
-    if (state != 1) break;
-    const int child = tree_first_child(p, node, layer) + slot;
-    if (tid == 0) seq[len] = p.cand_tokens[size_t(b) * (p.n_nodes - 1) + (child - 1)];
+    if (tid == 0) seq[len] = token;
     ++len;
-    node = child;
+    if (state != 1) break;
+    node = tree_first_child(p, node, layer) + slot;
     ++layer;
   }
   if (tid == 0) {
-    p.term_node[b] = node;                 // its output is the last token; kernel F writes it
-    p.out_len[b] = len + 1;
-    for (int i = len + 1; i <= p.depth; ++i) seq[i] = -1;
-    p.seq_status[b] = st_all;
+    p.out_len[b] = len;
+    for (int i = len; i <= p.depth; ++i) seq[i] = -1;
+    if (p.status) p.status[b] = st_all;
   }
 }
 
-
-// ---------------------------------------------------------------------------------------------
-// Kernel W: the new-sequence search, one wave per tree
-// ---------------------------------------------------------------------------------------------
-__global__ __launch_bounds__(64) void tree_walk_kernel(const TreeParams p) {
-  const int64_t b = blockIdx.x;
-  const int lane = threadIdx.x;
-  int st = 0;
-  for (int n = lane; n < p.n_int; n += 64) st |= p.node_status[b * p.n_int + n];
-  st = wave_or_i32(st);
-  if (lane == 0) {
-    int node = 0, layer = 0, len = 0;
-    int32_t* seq = p.out_seq + size_t(b) * (p.depth + 1);
-    while (node < p.n_int && p.node_state[b * p.n_int + node] == 1) {
-      const int child = tree_first_child(p, node, layer) + p.node_slot[b * p.n_int + node];
-      seq[len++] = p.cand_tokens[size_t(b) * (p.n_nodes - 1) + (child - 1)];
-      node = child;
-      ++layer;
-    }
-    p.term_node[b] = node;                 // its output is the last token; kernel F writes it
-    p.out_len[b] = len + 1;
-    for (int i = len + 1; i <= p.depth; ++i) seq[i] = -1;
-    p.seq_status[b] = st;
+template <typename T, typename Terms> hipError_t launch_verify_tree_with(const TreeParams& p, hipStream_t s) {
+  if (!p.all_nodes) {
+    hipLaunchKernelGGL((tree_path_kernel<T, Terms>), dim3(unsigned(p.B)), dim3(kRowThreads), Terms::kBytes, s, p);
+    return hipGetLastError();
   }
+  hipLaunchKernelGGL((tree_node_kernel<T, Terms>), dim3(unsigned(p.B * p.n_nodes)), dim3(kRowThreads), Terms::kBytes, s, p);
+  const hipError_t e = hipGetLastError();
+  if (e != hipSuccess) return e;
+  hipLaunchKernelGGL(tree_walk_kernel, dim3(unsigned(p.B)), dim3(64), 0, s, p);
+  return hipGetLastError();
 }
-
-// ---------------------------------------------------------------------------------------------
-// Kernels S and F: sample the output of the nodes that need it
-// ---------------------------------------------------------------------------------------------
-template <typename T, typename Terms>
-__global__ __launch_bounds__(kBlock, Terms::kBits ? 1 : 4) void tree_sweep_kernel(const TreeParams p) {
-  __shared__ VerifyShared sh;
-  extern __shared__ __align__(16) unsigned char dyn_lds[];
-  double* table = reinterpret_cast<double*>(dyn_lds);
-  Terms::build(table, p.rT, kBlock);
-  __syncthreads();
-  const int64_t n_items = p.B * p.tasks * p.n_seg_grid;
-  for (int64_t item = blockIdx.x; item < n_items; item += gridDim.x) {      // persistent workgroups
-    const int64_t task = item / p.n_seg_grid;                    // (b, t)
-    const int seg = int(item - task * p.n_seg_grid);
-    const int64_t b = task / p.tasks;
-    const int node = p.all_nodes ? int(task - b * p.tasks) : p.term_node[b];
-    if (node < p.n_int && p.node_state[b * p.n_int + node] != 0) continue;   // accepted a child, or unusable
-    const void* row = tree_row<T>(p, b, node);
-    const RowSplit rs = split_row<T>(row, p.V);
-    // non-leaf rows were validated by kernel M; leaves are seen here for the first time
-    sweep_group<T, Terms>(row, rs, seg, node >= p.n_int, p.rT, table, p.segs + size_t(task) * (p.n_seg + 2),
-                          p.subs + size_t(task) * p.n_seg * kSubChunks, sh);
-    __syncthreads();
+template <typename T> hipError_t launch_verify_tree(const TreeParams& p, hipStream_t s) {
+  if constexpr (ExpTab<T>::kHas) {
+    if (exp_table_usable<T>(p.rT)) return launch_verify_tree_with<T, BitTerms<T>>(p, s);
   }
-}
-
-template <typename T>
-__global__ __launch_bounds__(kBlock) void tree_finish_kernel(const TreeParams p) {
-  __shared__ VerifyShared sh;
-  __shared__ double item_val[kMaxItems];
-  const int tid = threadIdx.x;
-  const int64_t task = blockIdx.x;
-  const int64_t b = task / p.tasks;
-  const int node = p.all_nodes ? int(task - b * p.tasks) : p.term_node[b];
-  const bool leaf = node >= p.n_int;
-  const int64_t r = b * p.n_int + (leaf ? 0 : node);
-  const int state = leaf ? 0 : p.node_state[r];
-  int token = -1, slot = -1, st = 0;
-  if (state == 1) {
-    // an accepted child: the node's output is that candidate
-    slot = p.node_slot[r];
-    const int layer = tree_layer(p, node);
-    token = p.cand_tokens[size_t(b) * (p.n_nodes - 1) + (tree_first_child(p, node, layer) + slot - 1)];
-  } else {
-    FinishArgs a;
-    a.row = tree_row<T>(p, b, node);
-    a.rs = split_row<T>(a.row, p.V);
-    a.n_seg_row = int((a.rs.nvec + kSegVecsTotal - 1) / kSegVecsTotal);
-    a.V = p.V;
-    a.rT = p.rT;
-    a.segs = p.segs + size_t(task) * (p.n_seg + 2);
-    a.subs = p.subs + size_t(task) * p.n_seg * kSubChunks;
-    int count = leaf ? 0 : p.q_count[r];
-    a.count = count < 0 ? 0 : (count > p.k_cap ? p.k_cap : count);
-    a.qi = p.q_idx + size_t(r) * p.k_cap;
-    a.ql = p.q_logit + size_t(r) * p.k_cap;
-    a.stages = leaf ? 0 : p.node_stages[r];
-    a.cands = nullptr;
-    a.n_cands = 0;
-    if (!leaf && p.wor) {
-      const int layer = tree_layer(p, node);
-      a.cands = p.cand_tokens + size_t(b) * (p.n_nodes - 1) + (tree_first_child(p, node, layer) - 1);
-      a.n_cands = p.expansion[layer];
-    }
-    a.u = p.u_resample[size_t(b) * p.n_nodes + node];
-    a.unusable = state == 2;
-    a.item_val = item_val;
-    a.table = nullptr;
-    token = finish_core<T>(a, sh, st);
-  }
-  if (tid == 0) {
-    if (p.out_node_token) p.out_node_token[size_t(b) * p.n_nodes + node] = token;
-    if (p.out_node_slot) p.out_node_slot[size_t(b) * p.n_nodes + node] = slot;
-    if (node == p.term_node[b]) p.out_seq[size_t(b) * (p.depth + 1) + (p.out_len[b] - 1)] = token;
-    if (st) atomicOr(&p.seq_status[b], st);
-  }
-}
-
-__global__ void tree_status_kernel(const TreeParams p) {
-  const int64_t b = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
-  if (b < p.B && p.status) p.status[b] = p.seq_status[b];
-}
-
-template <typename T> hipError_t launch_verify_tree(TreeParams p, hipStream_t s) {
-  hipError_t e;
-  if (p.all_nodes) {
-    hipLaunchKernelGGL(tree_mcveri_kernel<T>, dim3(unsigned(p.B * p.n_int)), dim3(kBlock), 0, s, p);
-    if ((e = hipGetLastError()) != hipSuccess) return e;
-    hipLaunchKernelGGL(tree_walk_kernel, dim3(unsigned(p.B)), dim3(64), 0, s, p);
-  } else {
-    hipLaunchKernelGGL(tree_lazy_walk_kernel<T>, dim3(unsigned(p.B)), dim3(kBlock), 0, s, p);
-  }
-  if ((e = hipGetLastError()) != hipSuccess) return e;
-  const int E = ElemTraits<T>::kPerVec;
-  int n_seg = int((p.V / E + 1 + kSegVecsTotal - 1) / kSegVecsTotal);
-  if (n_seg > p.n_seg) n_seg = p.n_seg;
-  p.n_seg_grid = (n_seg + kGroupSegs - 1) / kGroupSegs;
-  const int64_t grid = std::min<int64_t>(p.B * p.tasks * p.n_seg_grid, sweep_grid_limit());
-  auto sweep = [&](auto kernel, size_t lds) { hipLaunchKernelGGL(kernel, dim3(unsigned(grid)), dim3(kBlock), lds, s, p); };
-  // the binary16 bit table would leave one workgroup of 256 threads per compute unit: bf16 rows only
-  if constexpr (std::is_same<T, Bf16>::value) {
-    if (exp_table_usable<T>(p.rT)) sweep(tree_sweep_kernel<T, BitTerms<T>>, BitTerms<T>::kBytes);
-    else sweep(tree_sweep_kernel<T, PowTerms<T>>, PowTerms<T>::kBytes);
-  } else {
-    sweep(tree_sweep_kernel<T, PowTerms<T>>, PowTerms<T>::kBytes);
-  }
-  if ((e = hipGetLastError()) != hipSuccess) return e;
-  hipLaunchKernelGGL(tree_finish_kernel<T>, dim3(unsigned(p.B * p.tasks)), dim3(kBlock), 0, s, p);
-  if ((e = hipGetLastError()) != hipSuccess) return e;
-  if (p.status) {
-    hipLaunchKernelGGL(tree_status_kernel, dim3(unsigned((p.B + 255) / 256)), dim3(256), 0, s, p);
-    e = hipGetLastError();
-  }
-  return e;
+  return launch_verify_tree_with<T, PowTerms<T>>(p, s);
 }
 
 }  // namespace tslt

@@ -478,8 +478,7 @@ int tslt_verify_tree(const void* target_logits, tslt_dtype dt, int64_t B, int64_
   p.depth = depth;
   const bool all_nodes = out_node_token != nullptr || out_node_slot != nullptr;
   p.all_nodes = all_nodes ? 1 : 0;
-  p.tasks = all_nodes ? p.n_nodes : 1;
-  if (B * int64_t(p.tasks) * tslt::row_segments(V) > 0x7FFFFFFF || B * n_nodes > 0x7FFFFFFF)
+  if (B * (all_nodes ? n_nodes : 1) * tslt::row_segments(V) > 0x7FFFFFFF || B * n_nodes > 0x7FFFFFFF)
     return fail(TSLT_ERR_UNSUPPORTED, "%s: B * nodes too large", name);
   if (B == 0) return TSLT_OK;
   if (!target_logits || !q_idx || !q_logit || !q_count || !cand_tokens || !u_accept || !u_resample || !out_seq || !out_len)

@@ -74,3 +74,34 @@ def test_tree_terms(tslt, dtype, V, T):
     torch.cuda.synchronize()
     print(P.compare_tree(out, ref, w.expansion, all_nodes=True, label=f"{dtype} {V} {T}"))
     assert torch.equal(path["seq"], out["seq"]) and torch.equal(path["len"], out["len"])
+
+
+@pytest.mark.parametrize("dtype,B,gamma,V", [
+    ("bf16", 64, 7, 1203),     # 512 rows: two per compute unit in one pass (one through the bit table)
+    ("bf16", 103, 4, 2500),    # beyond that: acceptance and resampling apart
+    ("f32", 64, 3, 1203),      # 256 rows: the largest batch in one pass for the other types
+    ("f16", 65, 3, 1203),
+    ("f16", 300, 1, 1100),     # more sequences than compute units
+    ("f32", 1, 70, 700),       # more positions than a wave has lanes
+    ("bf16", 2, 130, 130),     # ... with V as wide as the set
+])
+def test_batches_on_either_side_of_the_dispatch(tslt, dtype, B, gamma, V):
+    w = W.scaled(W.WORKLOADS["chain_topk"], B=B, V=V, gamma=gamma, dtype=dtype, top_k=32, k_cap=130)
+    chain = W.make_chain(w, 29, DEV)
+    u_acc = chain["u_accept"].clone()
+    u_acc[0] = 0.0                             # everything accepted wherever the token can be
+    chain["u_accept"] = u_acc
+    ref = P.oracle_chain(P.to_np(chain["draft"]), P.to_np(chain["target"]), w.T, w.top_k, w.top_p, w.k_cap,
+                         P.to_np(chain["u_sample"]), P.to_np(u_acc), P.to_np(chain["u_resample"]))
+    args = [chain["target"], w.T, t32(ref["q_idx"]), t32(ref["q_logit"]), t32(ref["q_count"]), t32(ref["tokens"]), u_acc,
+            chain["u_resample"]]
+    out = tslt.verify(*args)
+    torch.cuda.synchronize()
+    print(P.compare_verify(out, ref["verify"], label=f"{dtype} {B}x{gamma} {V}"))
+    ws = torch.empty(tslt.workspace_bytes(tslt.OP_VERIFY, B, gamma, V, w.k_cap), dtype=torch.uint8, device=DEV)
+    halves = {k: torch.empty_like(v) for k, v in out.items()}
+    tslt.verify(*args, out=halves, workspace=ws, phase="accept")
+    tslt.verify(*args, out=halves, workspace=ws, phase="resample")
+    torch.cuda.synchronize()
+    for k in out:
+        assert torch.equal(out[k], halves[k]), k
