@@ -24,6 +24,7 @@ template <auto Kernel> inline hipError_t allow_dynamic_lds(int bytes) {
   if (e == hipSuccess) granted[d].store(bytes, std::memory_order_relaxed);
   return e;
 }
+template <auto Kernel> struct KernelTag { static constexpr auto value = Kernel; };      // names a kernel in an argument
 // Compute units of the current device (256 if the query fails).
 inline int compute_units() {
   static std::atomic<int> cus[kMaxDevices];

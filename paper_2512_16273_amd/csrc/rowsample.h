@@ -30,17 +30,19 @@ static_assert(kMaxItems <= kRowThreads, "one item per thread");
 // The fp64 terms of a row are made in one of two ways, both referenced to 0 rather than to the row maximum,
 // which is safe while |s| <= kTabMaxS; a row that holds a larger |s| is swept again, referenced to its maximum.
 //
-// BitTerms, bfloat16 rows: a table of exp(s), s = fl32(z / T), for every logit z of a magnitude range that holds
+// BitTerms, 16-bit rows: a table of exp(s), s = fl32(z / T), for every logit z of a magnitude range that holds
 // the bulk of a row; a term costs five instructions and one LDS read.
 //   bfloat16  2^-14 <= |z| < 2^7   5376 values, 42 KB  (logits centred on 0 have many small values)
+//   binary16  2^-2  <= |z| < 2^5  14336 values, 112 KB: for the large batches of very long rows only (verify.h)
 // With the 16 bits of an element rotated left by one (sign in bit 0), entry 1 + (rotated - 2*kLo) holds
 // its value; entries 0 and kEntries + 1 hold NaN and stand for everything below and above the table's
 // domain (tiny, huge, -inf, NaN), which is evaluated directly.
 //
 // PowTerms, every type: exp64.h's pow_exp on a table of 2^(i/2048) (16 KB).  19 instructions per term and one LDS
 // read instead of the 30 of exp64; bound by the vector units.  Resampling 48 fp32 rows of 151936: 53.7 us by
-// exp64, 29.9 so.  A bit table for binary16 (14336 values in 112 KB) was slower up to V = 100000 or so: to build it
-// costs as much as the row (V = 32000, one row 19.0 us against 13.2).
+// exp64, 29.9 so.  A bit table for binary16 (14336 values in 112 KB) costs as much
+// as 100000 terms to build, and its gain on longer rows (40 x 5, V = 152064: 32.9 / 29.2 us) is lost twice over where
+// a row's bulk lies near 0, outside it (32.8 / 59.9).
 constexpr float kTabMaxS = 600.0f;
 template <typename T> struct ExpTab {
   static constexpr bool kHas = false;
@@ -55,6 +57,16 @@ template <> struct ExpTab<Bf16> {
   static constexpr float kMaxAbs = 128.0f;
   static constexpr uint32_t kInf = 0x7F80u;
   static __device__ __forceinline__ float widen(uint32_t bits) { return __uint_as_float(bits << 16); }
+};
+template <> struct ExpTab<F16> {
+  static constexpr bool kHas = true;
+  static constexpr int kLo = (15 - 2) << 10;
+  static constexpr int kSpan = 7 << 10;
+  static constexpr int kEntries = 2 * kSpan;
+  static constexpr size_t kBytes = size_t(kEntries + 2) * sizeof(double);
+  static constexpr float kMaxAbs = 32.0f;
+  static constexpr uint32_t kInf = 0x7C00u;
+  static __device__ __forceinline__ float widen(uint32_t bits) { return f16_lo(bits); }
 };
 // Whether a launch may make its terms through the bit table: every entry's |s| is within the range.
 template <typename T> inline bool exp_table_usable(float rT) {
@@ -219,6 +231,9 @@ template <typename T> struct PowTerms {
     return sum;
   }
 };
+
+// A table beyond the LDS that a launch may ask for without leave.
+template <typename Terms> constexpr bool kLargeTable = Terms::kBytes > 48 * 1024;
 
 template <typename T> __device__ __forceinline__ float dword_element(uint32_t w, int i);
 template <> __device__ __forceinline__ float dword_element<float>(uint32_t w, int) { return as_f32(w); }

@@ -44,6 +44,8 @@ struct TreeParams {
   int32_t* node_token;    // [B, n_nodes] the node's output
   int32_t* node_status;   // [B, n_nodes]
   int all_nodes;
+  int n_eval;             // nodes of a tree that tree_node_kernel evaluates: whole layers from the root
+  int n_eval_layers;
 };
 
 // (More than the kernels use: the size that callers have been told all along, so that a workspace kept from an
@@ -158,14 +160,14 @@ __device__ __forceinline__ int tree_node(const TreeParams& p, int64_t b, int nod
 }
 
 // ---------------------------------------------------------------------------------------------
-// Every node: one workgroup per node.
+// Every node of the layers wanted: one workgroup per node.
 // ---------------------------------------------------------------------------------------------
 template <typename T, typename Terms>
 __global__ __launch_bounds__(kRowThreads, kShared) void tree_node_kernel(const TreeParams p) {
   __shared__ RowShared sh;
   extern __shared__ __align__(16) unsigned char dyn_lds[];
-  const int64_t b = blockIdx.x / p.n_nodes;
-  const int node = int(blockIdx.x - b * p.n_nodes);
+  const int64_t b = blockIdx.x / p.n_eval;
+  const int node = int(blockIdx.x - b * p.n_eval);
   int slot, token, st;
   const int state = tree_node<T, Terms>(p, b, node, reinterpret_cast<double*>(dyn_lds), true, sh, slot, token, st);
   if (threadIdx.x == 0) {
@@ -179,51 +181,105 @@ __global__ __launch_bounds__(kRowThreads, kShared) void tree_node_kernel(const T
   }
 }
 
-// The new-sequence search, one wave per tree.
-__global__ __launch_bounds__(64) void tree_walk_kernel(const TreeParams p) {
-  const int64_t b = blockIdx.x;
-  const int lane = threadIdx.x;
-  int st = 0;
-  for (int n = lane; n < p.n_nodes; n += 64) st |= p.node_status[b * p.n_nodes + n];
-  st = wave_or_i32(st);
-  if (lane == 0) {
-    int node = 0, layer = 0, len = 0;
-    int32_t* seq = p.out_seq + size_t(b) * (p.depth + 1);
-    while (node < p.n_int && p.node_state[b * p.n_nodes + node] == 1) {
-      const int child = tree_first_child(p, node, layer) + p.node_slot[b * p.n_nodes + node];
-      seq[len++] = p.node_token[b * p.n_nodes + node];
-      node = child;
-      ++layer;
+// The new-sequence search through the layers that have been evaluated: lane 0 of the calling wave appends the outputs
+// to out_seq and notes the candidates that were tested.
+struct TreeWalk {
+  int first_cand[kMaxTreeDepth + 1], n_cand[kMaxTreeDepth + 1];      // of every node passed
+  int n_passed, node, layer, len, status, done;
+};
+__device__ __forceinline__ void tree_walk(const TreeParams& p, int64_t b, TreeWalk& w) {
+  int32_t* seq = p.out_seq + size_t(b) * (p.depth + 1);
+  int node = 0, layer = 0, len = 0, st = 0, done = 0;
+  while (!done && layer < p.n_eval_layers) {
+    const int64_t n = b * p.n_nodes + node;
+    st |= p.node_status[n];
+    seq[len++] = p.node_token[n];
+    done = 1;
+    if (node >= p.n_int) break;
+    const int child = tree_first_child(p, node, layer);
+    w.first_cand[layer] = child - 1;
+    w.n_cand[layer] = p.expansion[layer];
+    ++layer;
+    if (p.node_state[n] == 1) {
+      node = child + p.node_slot[n];
+      done = 0;
     }
-    seq[len] = p.node_token[b * p.n_nodes + node];
-    p.out_len[b] = len + 1;
-    for (int i = len + 1; i <= p.depth; ++i) seq[i] = -1;
-    if (p.status) p.status[b] = st;
+  }
+  w.n_passed = layer;
+  w.node = node;
+  w.layer = layer;
+  w.len = len;
+  w.status = st;
+  w.done = done;
+}
+// The ratios and rates of the candidates of all other nodes: NaN.
+__device__ __forceinline__ void tree_clear_others(const TreeParams& p, int64_t b, const TreeWalk& w) {
+  for (int i = threadIdx.x; i < p.n_nodes - 1; i += blockDim.x) {
+    bool tested = false;
+    for (int l = 0; l < w.n_passed; ++l) tested |= i >= w.first_cand[l] && i < w.first_cand[l] + w.n_cand[l];
+    if (tested) continue;
+    if (p.out_ratio) p.out_ratio[size_t(b) * (p.n_nodes - 1) + i] = NAN;
+    if (p.out_beta) p.out_beta[size_t(b) * (p.n_nodes - 1) + i] = NAN;
   }
 }
 
+// One wave per tree, after every node has been evaluated.
+__global__ __launch_bounds__(64) void tree_walk_kernel(const TreeParams p) {
+  __shared__ TreeWalk w;
+  const int64_t b = blockIdx.x;
+  const int lane = threadIdx.x;
+  int st = 0;
+  if (p.all_nodes) {
+    for (int n = lane; n < p.n_nodes; n += 64) st |= p.node_status[b * p.n_nodes + n];
+    st = wave_or_i32(st);
+  }
+  if (lane == 0) {
+    tree_walk(p, b, w);
+    p.out_len[b] = w.len;
+    for (int i = w.len; i <= p.depth; ++i) p.out_seq[size_t(b) * (p.depth + 1) + i] = -1;
+    if (p.status) p.status[b] = p.all_nodes ? st : w.status;
+  }
+  if (p.all_nodes) return;
+  __syncthreads();
+  tree_clear_others(p, b, w);
+}
+
 // ---------------------------------------------------------------------------------------------
-// Only the verified path is wanted: one workgroup per tree walks from the root, running Algorithm 5 at each node
-// it reaches, descending into the accepted child and drawing the output of the node it stops at, so that at most
-// depth + 1 target rows are read per tree, each once.  Uniforms are indexed by node, so the result is the one the
-// all-nodes kernel gives.
+// Only the verified path is wanted: one workgroup per tree walks through the layers that have been evaluated (none or
+// the first few), then from node to node, running Algorithm 5 at each node it reaches, descending into the accepted
+// child and drawing the output of the node it stops at, so that a target row below those layers is read only where
+// it counts.  Uniforms are indexed by node, so the result is the one that evaluating every node gives.  (kHead: layers
+// have been evaluated.  The walk through them is not compiled into the other form, whose registers it costs.)
 // ---------------------------------------------------------------------------------------------
-template <typename T, typename Terms>
+template <typename T, typename Terms, bool kHead>
 __global__ __launch_bounds__(kRowThreads) void tree_path_kernel(const TreeParams p) {
   __shared__ RowShared sh;
   extern __shared__ __align__(16) unsigned char dyn_lds[];
   const int tid = threadIdx.x;
   const int64_t b = blockIdx.x;
-  for (int i = tid; i < p.n_nodes - 1; i += kRowThreads) {
-    if (p.out_ratio) p.out_ratio[size_t(b) * (p.n_nodes - 1) + i] = NAN;
-    if (p.out_beta) p.out_beta[size_t(b) * (p.n_nodes - 1) + i] = NAN;
+  int node = 0, layer = 0, len = 0, st_all = 0, token = -1, first = 0;
+  bool done = false;
+  if constexpr (kHead) {
+    __shared__ TreeWalk walk;
+    if (tid == 0) tree_walk(p, b, walk);
+    __syncthreads();
+    tree_clear_others(p, b, walk);
+    node = first = walk.node;
+    layer = walk.layer;
+    len = walk.len;
+    st_all = walk.status;
+    done = walk.done;
+  } else {
+    for (int i = tid; i < p.n_nodes - 1; i += kRowThreads) {
+      if (p.out_ratio) p.out_ratio[size_t(b) * (p.n_nodes - 1) + i] = NAN;
+      if (p.out_beta) p.out_beta[size_t(b) * (p.n_nodes - 1) + i] = NAN;
+    }
   }
   __syncthreads();
   int32_t* seq = p.out_seq + size_t(b) * (p.depth + 1);
-  int node = 0, layer = 0, len = 0, st_all = 0, token = -1;
-  for (;;) {
+  while (!done) {
     int slot, st;
-    const int state = tree_node<T, Terms>(p, b, node, reinterpret_cast<double*>(dyn_lds), node == 0, sh, slot, token, st);
+    const int state = tree_node<T, Terms>(p, b, node, reinterpret_cast<double*>(dyn_lds), node == first, sh, slot, token, st);
     st_all |= st;
     if (tid == 0) seq[len] = token;
     ++len;
@@ -238,19 +294,39 @@ __global__ __launch_bounds__(kRowThreads) void tree_path_kernel(const TreeParams
   }
 }
 
-template <typename T, typename Terms> hipError_t launch_verify_tree_with(const TreeParams& p, hipStream_t s) {
-  if (!p.all_nodes) {
-    hipLaunchKernelGGL((tree_path_kernel<T, Terms>), dim3(unsigned(p.B)), dim3(kRowThreads), Terms::kBytes, s, p);
-    return hipGetLastError();
+// How many layers of a tree whose path is wanted are evaluated at once, every node of them, before the path is walked:
+// rows on the chip together take one row's time where the walk takes one for every layer.  The whole tree, where it
+// comes to one row per compute unit, or two unless they are binary16 rows of two layers; else, for rows of 100000
+// and more, the largest head of at least two layers that comes to one, where as many are left at most.  us a call,
+// layers one by one / at once (V = 32000, then 152064): 8 trees <2,2,2>, all layers, binary16 35.9 / 22.7 and 94 / 32,
+// fp32 36.4 / 19.4 and 94 / 34.6; 30 such trees, fp32 37.0 / 27.6 and 95 / 70, bfloat16 29 / 24.3 and 58 / 40; 34
+// trees <4,2> binary16 29.4 / 34.2 and 55 / 58; two of the four layers of 64 trees <2,2,2>: binary16 39 / 45 and
+// 100 / 95, fp32 36.8 / 37.8 and 96 / 84, bfloat16 28.6 / 33.2 and 59 / 56.
+template <typename T> inline int layers_at_once(const TreeParams& p) {
+  const int64_t cus = compute_units();
+  const bool two = p.depth >= 3 || !std::is_same<T, F16>::value;
+  if (p.B * p.n_nodes <= cus * (two ? 2 : 1)) return p.depth + 1;
+  if (p.V < 100000) return 0;
+  int l = p.depth;
+  while (l > 0 && p.B * p.offsets[l] > cus) --l;
+  return l >= 2 && 2 * l >= p.depth + 1 ? l : 0;
+}
+
+template <typename T, typename Terms> hipError_t launch_verify_tree_with(TreeParams p, hipStream_t s) {
+  p.n_eval_layers = p.all_nodes ? p.depth + 1 : layers_at_once<T>(p);
+  p.n_eval = p.offsets[p.n_eval_layers];
+  hipError_t e = hipSuccess;
+  if (p.n_eval > 0) {
+    hipLaunchKernelGGL((tree_node_kernel<T, Terms>), dim3(unsigned(p.B * p.n_eval)), dim3(kRowThreads), Terms::kBytes, s, p);
+    if ((e = hipGetLastError()) != hipSuccess) return e;
   }
-  hipLaunchKernelGGL((tree_node_kernel<T, Terms>), dim3(unsigned(p.B * p.n_nodes)), dim3(kRowThreads), Terms::kBytes, s, p);
-  const hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(tree_walk_kernel, dim3(unsigned(p.B)), dim3(64), 0, s, p);
+  if (p.n_eval == 0) hipLaunchKernelGGL((tree_path_kernel<T, Terms, false>), dim3(unsigned(p.B)), dim3(kRowThreads), Terms::kBytes, s, p);
+  else if (p.n_eval_layers <= p.depth) hipLaunchKernelGGL((tree_path_kernel<T, Terms, true>), dim3(unsigned(p.B)), dim3(kRowThreads), Terms::kBytes, s, p);
+  else hipLaunchKernelGGL(tree_walk_kernel, dim3(unsigned(p.B)), dim3(64), 0, s, p);
   return hipGetLastError();
 }
 template <typename T> hipError_t launch_verify_tree(const TreeParams& p, hipStream_t s) {
-  if constexpr (ExpTab<T>::kHas) {
+  if constexpr (std::is_same<T, Bf16>::value) {
     if (exp_table_usable<T>(p.rT)) return launch_verify_tree_with<T, BitTerms<T>>(p, s);
   }
   return launch_verify_tree_with<T, PowTerms<T>>(p, s);

@@ -290,21 +290,27 @@ __global__ __launch_bounds__(64) void verify_select_kernel(const VerifyParams p)
 }
 
 // Largest batch, in rows B * (gamma + 1), that is verified by verify_round_kernel: one row per compute unit, and two
-// through the bit table, whose sweep is bound by the LDS and leaves the vector units to the other row's steps.
+// through bfloat16's bit table, whose sweep is bound by the LDS and leaves the vector units to the other row's steps.
 // Measured, us a round, this way / by kernels A and B (V = 128256, k_cap 256): bfloat16 384 rows 33.3 / 38.2, 512 36.2 / 40.2, 896 65.6 / 59.3; binary16 384 55.5 / 45.4; fp32 384
 // 55.7 / 58.3, 512 63.8 / 62.8.
-template <typename Terms> inline int64_t round_rows() { return int64_t(compute_units()) * (Terms::kBits ? 2 : 1); }
+template <typename Terms> inline int64_t round_rows() { return int64_t(compute_units()) * (Terms::kBits && !kLargeTable<Terms> ? 2 : 1); }
 
 // phases: bit 0 = acceptance decisions (kernel A), bit 1 = resampling and outputs (kernel B)
 template <typename T, typename Terms> hipError_t launch_verify_with(VerifyParams p, hipStream_t s, int phases) {
   hipError_t e = hipSuccess;
   const int64_t cus = compute_units();
   auto by_rows = [&](auto alone, auto shared, int64_t rows) -> hipError_t {      // one workgroup per row
-    hipLaunchKernelGGL(rows <= cus ? alone : shared, dim3(unsigned(rows)), dim3(kRowThreads), Terms::kBytes, s, p);
+    // (binary16's table leaves a compute unit to one workgroup in any case)
+    if constexpr (kLargeTable<Terms>) {
+      if ((e = allow_dynamic_lds<decltype(alone)::value>(int(Terms::kBytes))) != hipSuccess) return e;
+    }
+    hipLaunchKernelGGL(kLargeTable<Terms> || rows <= cus ? alone.value : shared.value, dim3(unsigned(rows)), dim3(kRowThreads),
+                       Terms::kBytes, s, p);
     return hipGetLastError();
   };
   auto round = [&]() {
-    return by_rows(&verify_round_kernel<T, Terms, kAlone>, &verify_round_kernel<T, Terms, kShared>, p.B * p.j_count);
+    return by_rows(KernelTag<&verify_round_kernel<T, Terms, kAlone>>{}, KernelTag<&verify_round_kernel<T, Terms, kShared>>{},
+                   p.B * p.j_count);
   };
   const bool by_row = p.B * (p.gamma + 1) <= round_rows<Terms>();
   if (by_row && phases == 3 && p.stage0 == 0) {
@@ -334,13 +340,18 @@ template <typename T, typename Terms> hipError_t launch_verify_with(VerifyParams
     }
   }
   if (phases & 2) {
-    e = by_rows(&verify_resample_kernel<T, Terms, kAlone>, &verify_resample_kernel<T, Terms, kShared>, p.B);
+    e = by_rows(KernelTag<&verify_resample_kernel<T, Terms, kAlone>>{}, KernelTag<&verify_resample_kernel<T, Terms, kShared>>{},
+                p.B);
   }
   return e;
 }
+// Binary16 batches beyond round_rows() of rows this long: the bit table (128 x 5, V = 152064 64.6 / 60.6 us, 256000
+// 96.2 / 86.5; 100000 47.9 either way).
+constexpr int64_t kBitMinV16 = 147456;
 template <typename T> hipError_t launch_verify(VerifyParams p, hipStream_t s, int phases) {
   if constexpr (ExpTab<T>::kHas) {
-    if (exp_table_usable<T>(p.rT)) return launch_verify_with<T, BitTerms<T>>(p, s, phases);
+    const bool chosen = !std::is_same<T, F16>::value || (p.V >= kBitMinV16 && p.B * (p.gamma + 1) > round_rows<PowTerms<T>>());
+    if (chosen && exp_table_usable<T>(p.rT)) return launch_verify_with<T, BitTerms<T>>(p, s, phases);
   }
   return launch_verify_with<T, PowTerms<T>>(p, s, phases);
 }

@@ -105,3 +105,50 @@ def test_batches_on_either_side_of_the_dispatch(tslt, dtype, B, gamma, V):
     torch.cuda.synchronize()
     for k in out:
         assert torch.equal(out[k], halves[k]), k
+
+
+@pytest.mark.parametrize("dtype,B,expansion,V", [
+    ("f32", 34, (2, 2, 2), 2000),      # 510 nodes: every node at once, then the walk
+    ("f32", 35, (2, 2, 2), 2000),      # 525: node after node
+    ("f16", 19, (4, 2), 1500),         # 247 nodes of a tree of two layers
+    ("f16", 20, (4, 2), 1500),         # 260
+    ("f32", 35, (2, 2, 2), 100001),    # two layers at once, then node after node
+    ("f16", 30, (3, 3), 100000),       # the same of a tree of two layers
+    ("bf16", 170, (1, 1), 900),        # 510
+    ("bf16", 171, (1, 1), 900),        # 513
+])
+def test_path_on_either_side_of_the_dispatch(tslt, dtype, B, expansion, V):
+    """The verified path alone gives what the evaluation of every node gives along it, and NaN off it."""
+    w = W.scaled(W.WORKLOADS["tree"], B=B, V=V, expansion=expansion, top_k=8, k_cap=8, dtype=dtype)
+    tree = W.make_tree(w, 31, DEV)
+    offsets, width = [0], 1
+    for k in expansion + (0,):
+        offsets.append(offsets[-1] + width)
+        width *= k
+    n_int, n = offsets[-2], offsets[-1]
+    draft = tree["draft"].reshape(B * n_int, V)
+    u = W.uniforms((B * n_int, max(expansion)), 5, 2, 3, DEV)
+    sets = tslt.truncate(draft, w.T, 8, 0.0, 8, u=u)
+    token = sets["token"].view(B, n_int, -1)
+    cands = torch.cat([token[:, lo:hi, :k].reshape(B, -1) for k, lo, hi in zip(expansion, offsets, offsets[1:])], 1).contiguous()
+    args = [tree["target"], w.T, expansion, sets["idx"].view(B, n_int, 8), sets["logit"].view(B, n_int, 8),
+            sets["count"].view(B, n_int), cands, tree["u_accept"], tree["u_resample"]]
+    out = {k: P.to_np(v) for k, v in tslt.verify_tree(*args, all_nodes=True).items()}
+    path = {k: P.to_np(v) for k, v in tslt.verify_tree(*args, all_nodes=False).items() if v is not None}
+    assert np.array_equal(path["seq"], out["seq"]) and np.array_equal(path["len"], out["len"])
+    lengths = set()
+    for b in range(B):
+        on = np.zeros(n - 1, bool)
+        node = 0
+        for layer, k in enumerate(expansion):
+            child = offsets[layer + 1] + (node - offsets[layer]) * k
+            on[child - 1:child - 1 + k] = True
+            if out["node_slot"][b, node] < 0:
+                break
+            node = child + out["node_slot"][b, node]
+        lengths.add(int(out["len"][b]))
+        for k in ("ratio", "beta"):
+            assert np.isnan(path[k][b][~on]).all()
+            # fp64 sums of terms within 1.5 ulp by either table, rounded to fp32
+            np.testing.assert_allclose(path[k][b][on], out[k][b][on], rtol=2.5e-7)
+    assert len(lengths) > 1 and (path["status"] == 0).all()
