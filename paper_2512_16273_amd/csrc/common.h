@@ -376,8 +376,8 @@ template <int NW> __device__ __forceinline__ int block_excl_scan_i32(int v, Bloc
 // room for k_keep records plus the population of the bin that straddles that boundary; the function
 // returns false, leaving `in` intact, when tmp_cap is too small for that.  `in` and `out` may be the
 // same array; `tmp` must be distinct from both.  hist, start and cursor are 256-entry LDS arrays.
-// Work per thread is about n/256 + k_keep/256 * mean bin population; values crowded into one bin cost
-// more, bounded by n^2/256 comparisons per thread.  NT = threads of the workgroup (64, 128 or 256).
+// Work per thread is about n/NT + k_keep/NT * mean bin population; values crowded into one bin cost
+// more, bounded by n^2/NT comparisons per thread.  NT = threads of the workgroup (64 to 512).
 __device__ __forceinline__ int value_bin(uint64_t c, float vmin, float scale) {
   // fp32 subtraction and multiplication are monotone, which is all the binning has to be
   const int b = int((cand_value(c) - vmin) * scale);
@@ -388,7 +388,8 @@ __device__ __forceinline__ bool bucket_sort_desc(const uint64_t* in, int n, uint
                                                  int k_keep, uint32_t* hist, uint32_t* start, uint32_t* cursor,
                                                  BlockScratch& red) {
   constexpr int NW = NT / 64;
-  constexpr int BPT = 256 / NT;      // bins per thread: thread t owns bins 255 - t*BPT - j, j < BPT
+  constexpr int BPT = NT < 256 ? 256 / NT : 1;      // bins per thread: thread t owns bins 255 - t*BPT - j, j < BPT
+  const bool has_bin = NT <= 256 || int(threadIdx.x) < 256;
   if (n <= 0) return true;
   const int tid = threadIdx.x;
   uint32_t kmin = 0xFFFFFFFFu, kmax = 0u;
@@ -400,13 +401,13 @@ __device__ __forceinline__ bool bucket_sort_desc(const uint64_t* in, int n, uint
   kmax = wave_max_u32(kmax);
   kmin = ~wave_max_u32(~kmin);
   for (int b = tid; b < 256; b += NT) hist[b] = 0;
-  if (lane_id() == 0) { red.i[wave_id()] = int(kmin); red.i[8 + wave_id()] = int(kmax); }
+  if (lane_id() == 0) { red.i[wave_id()] = int(kmin); red.f[wave_id()] = as_f32(kmax); }
   __syncthreads();
-  kmin = uint32_t(red.i[0]); kmax = uint32_t(red.i[8]);
+  kmin = uint32_t(red.i[0]); kmax = as_u32(red.f[0]);
 #pragma unroll
   for (int w = 1; w < NW; ++w) {
     kmin = uint32_t(red.i[w]) < kmin ? uint32_t(red.i[w]) : kmin;
-    kmax = uint32_t(red.i[8 + w]) > kmax ? uint32_t(red.i[8 + w]) : kmax;
+    kmax = as_u32(red.f[w]) > kmax ? as_u32(red.f[w]) : kmax;
   }
   const float vmin = key_to_f32(kmin);
   const float span = key_to_f32(kmax) - vmin;            // may overflow to +inf: then one bin
@@ -416,13 +417,15 @@ __device__ __forceinline__ bool bucket_sort_desc(const uint64_t* in, int n, uint
   int total;
   int h[BPT], mine = 0;
 #pragma unroll
-  for (int j = 0; j < BPT; ++j) { h[j] = int(hist[255 - tid * BPT - j]); mine += h[j]; }
+  for (int j = 0; j < BPT; ++j) { h[j] = has_bin ? int(hist[255 - tid * BPT - j]) : 0; mine += h[j]; }
   const int excl = block_excl_scan_i32<NW>(mine, red, total);   // bins in descending order
   int run = excl, moved = 0;
 #pragma unroll
   for (int j = 0; j < BPT; ++j) {
-    start[255 - tid * BPT - j] = uint32_t(run);
-    cursor[255 - tid * BPT - j] = uint32_t(run);
+    if (has_bin) {
+      start[255 - tid * BPT - j] = uint32_t(run);
+      cursor[255 - tid * BPT - j] = uint32_t(run);
+    }
     if (run < k_keep) moved += h[j];      // records in the bins that start before place k_keep
     run += h[j];
   }

@@ -27,10 +27,18 @@ constexpr int kGroup = 2;        // tiles (one 16-byte vector per thread each) i
 // allows that many (k_cap of a few hundred).  "Deep": four stages in flight and four waves per SIMD; for the
 // launches whose candidate arrays leave room for fewer workgroups (k_cap 1024: three per compute unit), which
 // then need more requests in flight each to keep the memory busy.
+//   "Tall": 512 threads and four stages, for batches that leave the chip to one or two rows per compute unit, bound by
+// a row's own latency: twice the requests in flight, rows shorter than the sample's distances through the same pipeline
+// (they went pair by pair, a memory latency each), the threshold three bits at a time.  us by 256 / 512 threads: 1 row
+// binary16 V = 32000 14.8 / 13.0, 64 bfloat16 V = 128256 27.0 / 21.7, 200 28.1 / 23.2, 400 34.3 / 32.3, 700 42.1 / 46.7;
+// 100 fp32 V = 151936 40.6 / 27.8, 400 51.2 / 51.2.  1024 threads are slower again (14.9, 23.4, 25.6 us).
+constexpr int kTallThreads = 512;
 constexpr int kStagesWide = 2, kWavesWide = 8;
 constexpr int kStagesDeep = 4, kWavesDeep = 4;
-constexpr int kRing = 96;      // vectors a wave can park
-constexpr int kRingExpand = 58; // expanded when it holds more than this: one pass of 64 lanes, nearly all busy
+// Vectors a wave can park.  256 threads: expanded when there are more than kRingExpand, one pass of 64 lanes, nearly all
+// busy; a row in which they come faster than that loses some and is redone.  512: expanded before there would be no
+// room for the next ones.
+constexpr int kRingSmall = 96, kRingExpand = 58, kRingTall = 64;
 
 struct TruncateParams {
   const void* logits;
@@ -44,9 +52,7 @@ struct TruncateParams {
   int jprime;        // rank (1-based) among the 256 per-thread sample maxima that gives tau0; 0 = always exact path
   int tau_bits;      // number of leading key bits resolved by the threshold search
   int sort_cap;      // capacity of the candidate array
-  int lds_recs;      // records that fit in the candidate region; those past sort_cap are sort scratch
-  int ring_bytes;    // size of the ring space at the start of dynamic LDS (ring_bytes_for the workgroup's waves)
-  int tmp_in_ring;   // the sort scratch is the ring space behind the tables
+  int ring_bytes;    // size of the ring space at the start of dynamic LDS
   int32_t* out_idx;
   float* out_logit;
   float* out_prob;
@@ -61,12 +67,15 @@ struct TruncateParams {
   int32_t* out_slot;
 };
 
-// Dynamic LDS: [ rings ] [ candidates, then sort scratch ].  The ring space is
-// reused for the sort's three 256-entry tables and, before the pass, for the per-thread sample maxima.
-constexpr int ring_bytes_for(int n_waves) { return n_waves * (kRing * 20); }      // per slot a vector and its index
-static_assert(ring_bytes_for(2) >= 3 * 256 * 4, "ring space must hold the sort tables");
-inline size_t truncate_lds_bytes(int ring_bytes, int lds_recs) { return size_t(ring_bytes) + size_t(8) * lds_recs; }
+// Dynamic LDS: [ rings ] [ candidates ].  The ring space is reused for the sort's three 256-entry tables and its
+// scratch records behind them and, before the pass, for the per-thread sample maxima.
+constexpr int kTablesBytes = 3 * 256 * 4;
 inline int truncate_sort_scratch(int k_sel) { return k_sel + k_sel / 2 + 64; }   // records the sort may need
+inline int truncate_ring_bytes(int n_waves, int k_sel) {
+  const int rings = n_waves * (kRingSmall * 20), sort = (kTablesBytes + 8 * truncate_sort_scratch(k_sel) + 15) & ~15;
+  return rings > sort ? rings : sort;                                            // per ring slot a vector and its index
+}
+inline size_t truncate_lds_bytes(int ring_bytes, int sort_cap) { return size_t(ring_bytes) + size_t(8) * sort_cap; }
 
 struct TruncateShared {
   BlockScratch red;
@@ -375,46 +384,34 @@ __global__ __launch_bounds__(NT, kWavesPerSimd) void truncate_kernel(const Trunc
   static_assert(kBatch == 4, "the sample tiles are handled as two pairs");
   extern __shared__ __align__(16) unsigned char dyn_lds[];
   __shared__ TruncateShared sh;
+  constexpr bool kTall = NT > kTruncThreads;
+  constexpr int kRing = kTall ? kRingTall : kRingSmall;
   uint4* ring_all = reinterpret_cast<uint4*>(dyn_lds);
   uint32_t* ring_vidx_all = reinterpret_cast<uint32_t*>(dyn_lds + NW * kRing * 16);
   uint32_t* tables = reinterpret_cast<uint32_t*>(dyn_lds);          // 3 x 256 entries, aliasing the rings
   uint64_t* cand = reinterpret_cast<uint64_t*>(dyn_lds + p.ring_bytes);
-  // sort scratch: what is left of the ring space behind the tables, or (if that is too small for the
-  // requested k) the records behind the candidate capacity
-  uint64_t* sort_tmp = p.tmp_in_ring ? reinterpret_cast<uint64_t*>(dyn_lds + 3 * 256 * 4) : cand + p.sort_cap;
-  const int sort_tmp_cap = p.tmp_in_ring ? (p.ring_bytes - 3 * 256 * 4) / 8 : p.lds_recs - p.sort_cap;
+  uint64_t* sort_tmp = reinterpret_cast<uint64_t*>(dyn_lds + kTablesBytes);
+  const int sort_tmp_cap = (p.ring_bytes - kTablesBytes) / 8;
 
   const int tid = threadIdx.x;
   const int lane = lane_id();
   const int wave = wave_id();
   const int64_t row_i = blockIdx.x;
-  // The sample: the first tile of kBatch batches at equal distances; a row with fewer than 4*kBatch
-  // complete batches uses its first kBatch tiles.
-  // (Every load of the pass below is unconditional: an address past the row's end is replaced by that of
-  // the row's last vector and the value by -inf afterwards.  With conditional loads the number of loads in
-  // flight is not known where a wait is placed, and a wait for one batch waits for all that were
-  // requested after it as well.)
-  auto load_sample = [&](const RowSplit& r, uint4 (&q)[kBatch]) {
-    const uint32_t nv = uint32_t(r.nvec);            // > 0 here
-    const uint32_t nf = nv / (kBatch * NT);
-    const uint32_t stride = nf >= 4 ? (nf / 4) * kBatch : 1;
-#pragma unroll
-    for (int u = 0; u < kBatch; ++u) {
-      const uint32_t vi = u * stride * NT + tid;
-      q[u] = load_vec_stream(&r.body[vi < nv ? vi : nv - 1]);
-    }
-#pragma unroll
-    for (int u = 0; u < kBatch; ++u)
-      if (u * stride * NT + tid >= nv) q[u] = neg_inf_vec<T>();
-  };
   const void* row = reinterpret_cast<const char*>(p.logits) + size_t(row_i) * size_t(p.row_stride) * ElemTraits<T>::kBytes;
   const RowSplit rs = split_row<T>(row, p.V);
   const int n_edge = rs.head + rs.tail;
   const uint32_t nvec = uint32_t(rs.nvec);
   const uint32_t n_tiles = (nvec + NT - 1) / NT;
-  const uint32_t n_full = nvec / (kBatch * NT);        // batches of kBatch complete, consecutive tiles
-  const bool long_row = n_full >= 4;
-  const uint32_t s_stride = long_row ? (n_full / 4) * kBatch : 1;   // distance of the sample tiles, in tiles
+  // The sample: kBatch tiles at equal distances, each the first of a stage; a row of fewer than kBatch complete stages
+  // uses its first kBatch tiles.
+  // (Every load of the pass below is unconditional: an address past the row's end is replaced by that of
+  // the row's last vector and the value by -inf afterwards.  With conditional loads the number of loads in
+  // flight is not known where a wait is placed, and a wait for one batch waits for all that were
+  // requested after it as well.)
+  constexpr int kUnit = kTall ? kGroup : kBatch;      // tiles that the distance is a multiple of
+  const uint32_t n_full = nvec / (kUnit * NT);
+  const bool long_row = n_full >= kBatch;
+  const uint32_t s_stride = long_row ? (n_full / kBatch) * kUnit : 1;    // distance of the sample tiles, in tiles
 
   int st = 0;
   int n_cand = 0;
@@ -426,19 +423,33 @@ __global__ __launch_bounds__(NT, kWavesPerSimd) void truncate_kernel(const Trunc
   if (fast_ok) {
     // ---- the sample: per-thread maxima ----------------------------------------------------------
     uint4 d[kBatch];
+    auto load_sample = [&](const RowSplit& r, uint4 (&q)[kBatch]) {
+      const uint32_t nv = uint32_t(r.nvec);            // > 0 here
+      const uint32_t nf = nv / (kUnit * NT);
+      const uint32_t stride = nf >= 4 ? (nf / 4) * kUnit : 1;
+#pragma unroll
+      for (int u = 0; u < kBatch; ++u) {
+        const uint32_t vi = u * stride * NT + tid;
+        q[u] = load_vec_stream(&r.body[vi < nv ? vi : nv - 1]);
+      }
+#pragma unroll
+      for (int u = 0; u < kBatch; ++u)
+        if (u * stride * NT + tid >= nv) q[u] = neg_inf_vec<T>();
+    };
     load_sample(rs, d);
-    // The pass keeps kStages stages of kGroup tiles in flight per thread; the first ones are requested now, so
-    // that they travel while the threshold is being worked out.  A sample tile is the first tile of its stage
-    // (the sample tiles lie a multiple of kBatch tiles apart) and is not read again.  A long row's ragged end
-    // (the last tile possibly incomplete, the last stage possibly half empty) is the last stage.
-    static_assert(kBatch % kGroup == 0 && kGroup == 2, "a stage is a pair of tiles; sample tiles start a stage");
-    uint4 pipe[kStages][kGroup];
-    const uint32_t n_stage = long_row ? (n_tiles + kGroup - 1) / kGroup : 0u;
-    uint32_t skip_g = 0, skips_left = kBatch;
-    const uint32_t stride_g = s_stride / kGroup;
     const uint32_t last_vec = nvec - 1;
+    // The pass keeps kStages stages of kGroup tiles in flight per thread; the first ones are requested now, so
+    // that they travel while the threshold is being worked out.  In a long row a sample tile is the first tile of
+    // its stage and is not read again; in a short one (512 threads) the stages begin behind the sample.  The row's ragged end
+    // (the last tile possibly incomplete, the last stage possibly half empty) is the last stage.
+    static_assert(kGroup == 2, "a stage is a pair of tiles");
+    uint4 pipe[kStages][kGroup];
+    const uint32_t tile0 = long_row || !kTall ? 0u : uint32_t(kBatch);          // of the first stage
+    const uint32_t n_stage = (long_row || kTall) && n_tiles > tile0 ? (n_tiles - tile0 + kGroup - 1) / kGroup : 0u;
+    uint32_t skip_g = 0, skips_left = long_row || !kTall ? kBatch : 0;
+    const uint32_t stride_g = s_stride / kGroup;
     auto issue = [&](uint32_t g, uint4 (&q)[kGroup]) {
-      const uint32_t v0 = g * (kGroup * NT) + tid;
+      const uint32_t v0 = (tile0 + g * kGroup) * NT + tid;
       // the first tile of a sample stage is in registers already: its slot repeats the second tile's load
       const bool skip = skips_left > 0 && g == skip_g;
       if (skip) { skip_g += stride_g; --skips_left; }
@@ -463,17 +474,34 @@ __global__ __launch_bounds__(NT, kWavesPerSimd) void truncate_kernel(const Trunc
     for (int u = 0; u < kBatch; ++u) asm volatile("" : "+v"(d[u].x), "+v"(d[u].y), "+v"(d[u].z), "+v"(d[u].w));
     tables[tid] = mono_key(tmax);
     __syncthreads();
-    // ---- tau0: the jprime-th largest of the 256 per-thread sample maxima (every wave redundantly)
+    // ---- tau0: the jprime-th largest of the per-thread sample maxima
     uint32_t kq[NW];
 #pragma unroll
     for (int q = 0; q < NW; ++q) kq[q] = tables[lane + 64 * q];
     uint32_t tau_key = 0;
-    for (int bit = 31; bit >= 32 - p.tau_bits; --bit) {
-      const uint32_t trial = tau_key | (1u << bit);
+    auto reach = [&](uint32_t trial) {                 // how many of them reach `trial`
       int cnt = 0;
 #pragma unroll
       for (int q = 0; q < NW; ++q) cnt += __popcll(ballot(kq[q] >= trial));
-      if (cnt >= p.jprime) tau_key = trial;
+      return cnt;
+    };
+    if constexpr (!kTall) {                            // a bit at a time, every wave for itself
+      for (int bit = 31; bit >= 32 - p.tau_bits; --bit) {
+        const uint32_t trial = tau_key | (1u << bit);
+        if (reach(trial) >= p.jprime) tau_key = trial;
+      }
+    } else {                                           // three bits at a time, every wave tries one of their values
+      static_assert(NW == 8, "a wave per value");
+      int shift = 32;
+      for (int step = 0; shift > 32 - p.tau_bits; ++step) {
+        shift -= 3;
+        int* reached = step & 1 ? reinterpret_cast<int*>(sh.red.f) : sh.red.i;
+        const int cnt = reach(tau_key | (uint32_t(wave) << shift));
+        if (lane == 0) reached[wave] = cnt;
+        __syncthreads();
+        const int of_lane = lane < NW ? reached[lane] : 0;                   // falls with the value
+        tau_key |= uint32_t(__popcll(ballot(lane > 0 && of_lane >= p.jprime))) << shift;
+      }
     }
     uint32_t top_key = kq[0];   // the sample maximum
 #pragma unroll
@@ -492,14 +520,14 @@ __global__ __launch_bounds__(NT, kWavesPerSimd) void truncate_kernel(const Trunc
       // fp32 sums live for a few vectors only and are then added to an fp64 total: a long-lived fp32
       // accumulator that has met one large term rounds away the many small ones that follow
       double dacc = 0.0;
-      int wave_cnt = 0;                                // pairs parked in this wave's ring
+      int wave_cnt = 0;                                // vectors parked in this wave's ring
       bool lost = false;                               // wave-uniform: a ring overflowed
       uint4* ring = ring_all + wave * kRing;
       uint32_t* ring_vidx = ring_vidx_all + wave * kRing;
       const uint32_t head = uint32_t(rs.head);
 
       // Two vectors at a time: their exp2 terms go to the partial sums; a vector with an element above
-      // tau0 is parked in the ring, which is expanded when it holds about a wave's worth of vectors.
+      // tau0 is parked in the ring, which is expanded when it has no room for the next ones.
       // (returns the sum of the pair's exp2 terms)
       auto process_pair = [&](const uint4& w0, const uint4& w1, uint32_t vidx0, uint32_t vidx1) -> float {
         float a[E], b[E];
@@ -518,7 +546,20 @@ __global__ __launch_bounds__(NT, kWavesPerSimd) void truncate_kernel(const Trunc
           for (int e = 0; e < w; ++e) t[e] += t[e + w];
         const float pair_sum = t[0];
         const uint64_t mask_a = ballot(hit_a), mask_b = ballot(hit_b);
-        if ((mask_a | mask_b) != 0) {
+        if constexpr (kTall) {
+          auto park = [&](bool hit, uint64_t mask, const uint4& w, uint32_t vidx) {
+            const int n = __popcll(mask);
+            if (wave_cnt + n > kRing) {                // wave-uniform; n is 64 at most
+              expand_ring<T>(ring, ring_vidx, wave_cnt, tau0, head, cand, p.sort_cap, sh);
+              wave_cnt = 0;
+            }
+            const int pos = wave_cnt + lanes_below(mask);
+            if (hit) { ring[pos] = w; ring_vidx[pos] = vidx; }
+            wave_cnt += n;
+          };
+          if (mask_a != 0) park(hit_a, mask_a, w0, vidx0);
+          if (mask_b != 0) park(hit_b, mask_b, w1, vidx1);
+        } else if ((mask_a | mask_b) != 0) {
           const int n_a = __popcll(mask_a);
           const int pos_a = wave_cnt + lanes_below(mask_a);
           const int pos_b = wave_cnt + n_a + lanes_below(mask_b);
@@ -545,10 +586,10 @@ __global__ __launch_bounds__(NT, kWavesPerSimd) void truncate_kernel(const Trunc
         const float s23 = process_pair(d[2], d[3], t2 * NT + tid, t3 * NT + tid);
         dacc += double(s01 + s23);
       }
-      uint32_t first_generic_tile = kBatch;             // short rows: everything after the sample tiles
-      if (long_row) {
-        uint32_t seen_g = 0, seen_left = kBatch;
-        const uint32_t ragged_g = n_full * (kBatch / kGroup);        // from here on a vector may lie past the row's end
+      if (kTall || long_row) {
+        uint32_t seen_g = 0, seen_left = long_row || !kTall ? kBatch : 0;
+        // from here on a vector may lie past the row's end
+        const uint32_t ragged_g = nvec / NT > tile0 ? (nvec / NT - tile0) / kGroup : 0u;
         static_assert(kStages % 2 == 0, "the fp32 sums of two stages are added up before they go to the fp64 total");
         for (uint32_t g0 = 0; g0 < n_stage; g0 += kStages) {
           float two = 0.0f;
@@ -556,7 +597,7 @@ __global__ __launch_bounds__(NT, kWavesPerSimd) void truncate_kernel(const Trunc
           for (int s = 0; s < kStages; ++s) {
             const uint32_t g = g0 + s;
             if (g < n_stage) {                                        // wave-uniform, no loads inside
-              const uint32_t v0 = g * (kGroup * NT) + tid;
+              const uint32_t v0 = (tile0 + g * kGroup) * NT + tid;
               if (seen_left > 0 && g == seen_g) {                     // a sample stage: its first tile is done
                 seen_g += stride_g; --seen_left;
                 pipe[s][0] = neg_inf_vec<T>();
@@ -572,16 +613,16 @@ __global__ __launch_bounds__(NT, kWavesPerSimd) void truncate_kernel(const Trunc
             issue(g + kStages, pipe[s]);
           }
         }
-        first_generic_tile = n_tiles;
-      }
-      // short rows: the tiles after the sample, which may be incomplete
-      for (uint32_t t = first_generic_tile; t < n_tiles; t += 2) {
-        const uint32_t v0 = t * NT + tid, v1 = v0 + NT;
-        d[0] = neg_inf_vec<T>();
-        d[1] = neg_inf_vec<T>();
-        if (v0 < nvec) d[0] = load_vec_stream(&rs.body[v0]);
-        if (v1 < nvec) d[1] = load_vec_stream(&rs.body[v1]);
-        dacc += double(process_pair(d[0], d[1], v0, v1));
+      } else {
+        // a short row: the tiles after the sample, which may be incomplete
+        for (uint32_t t = kBatch; t < n_tiles; t += 2) {
+          const uint32_t v0 = t * NT + tid, v1 = v0 + NT;
+          d[0] = neg_inf_vec<T>();
+          d[1] = neg_inf_vec<T>();
+          if (v0 < nvec) d[0] = load_vec_stream(&rs.body[v0]);
+          if (v1 < nvec) d[1] = load_vec_stream(&rs.body[v1]);
+          dacc += double(process_pair(d[0], d[1], v0, v1));
+        }
       }
       expand_ring<T>(ring, ring_vidx, wave_cnt < kRing ? wave_cnt : kRing, tau0, head, cand, p.sort_cap, sh);
       if (lost && lane == 0) sh.overflow = 1;

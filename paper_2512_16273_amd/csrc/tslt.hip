@@ -3,6 +3,7 @@
 
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cmath>
 #include <cstdarg>
 #include <cstdio>
@@ -72,26 +73,19 @@ size_t plan_truncate(tslt_dtype dt, int64_t V, int nt, tslt::TruncateParams& p) 
   p.tau_bits = dt == TSLT_BF16 ? 16 : (dt == TSLT_F16 ? 19 : 20);
   p.jprime = 0;
   // candidate capacity: always room for the fallback's 1024 group maxima and for 2 * k_sel records.
-  // The sort needs about 1.5 * k_sel records of scratch: the ring space behind the sort's tables if
-  // that is large enough, else extra records behind the candidates.
   const int min_cap = (1024 + 16 > 2 * p.k_sel) ? 1024 + 16 : 2 * p.k_sel;
-  const int scratch = tslt::truncate_sort_scratch(p.k_sel);
-  p.ring_bytes = tslt::ring_bytes_for(nt / 64);
-  p.tmp_in_ring = (p.ring_bytes - 3 * 256 * 4) / 8 >= scratch ? 1 : 0;
-  const int extra = p.tmp_in_ring ? 0 : scratch;
+  p.ring_bytes = tslt::truncate_ring_bytes(nt / 64, p.k_sel);
   p.sort_cap = min_cap;
-  p.lds_recs = min_cap + extra;
   if (jprime <= int(0.8 * G)) {
     const double j_eff = -G * std::log(1.0 - double(jprime) / G);
     int sort_cap = int((j_eff + 5.0 * std::sqrt(j_eff) + 4.0) / f) + 16;   // mean + 5 sigma of the hits
     if (sort_cap < min_cap) sort_cap = min_cap;
-    if (tslt::truncate_lds_bytes(p.ring_bytes, sort_cap + extra) + sizeof(tslt::TruncateShared) + 256 <= kMaxLds) {
+    if (tslt::truncate_lds_bytes(p.ring_bytes, sort_cap) + sizeof(tslt::TruncateShared) + 256 <= kMaxLds) {
       p.jprime = jprime;
       p.sort_cap = sort_cap;
-      p.lds_recs = sort_cap + extra;
     }
   }
-  return tslt::truncate_lds_bytes(p.ring_bytes, p.lds_recs);
+  return tslt::truncate_lds_bytes(p.ring_bytes, p.sort_cap);
 }
 
 // Device address of `scratch` on the current device, looked up once per device.
@@ -117,12 +111,41 @@ hipError_t scratch_on_current_device(void** out) {
 
 constexpr int kLargeLds = int(kMaxLds - 4096);
 
-// The two shapes of the truncation kernel for one element type (see truncate.h).
-template <typename T, int NT, bool kWide> struct TruncKernel {
-  static constexpr auto fn = kWide ? &tslt::truncate_kernel<T, NT, tslt::kStagesWide, tslt::kWavesWide>
-                                   : &tslt::truncate_kernel<T, NT, tslt::kStagesDeep, tslt::kWavesDeep>;
-  hipError_t allow(int bytes) const { return tslt::allow_dynamic_lds<fn>(bytes); }
-};
+// One shape of the truncation kernel (see truncate.h): NT threads to a row.
+template <typename T, int NT, int kStages, int kWavesPerSimd>
+hipError_t launch_truncate_shape(const tslt::TruncateParams& p, size_t lds, hipStream_t s) {
+  constexpr auto fn = &tslt::truncate_kernel<T, NT, kStages, kWavesPerSimd>;
+  if (lds + sizeof(tslt::TruncateShared) > 48 * 1024) {
+    const hipError_t e = tslt::allow_dynamic_lds<fn>(kLargeLds);
+    if (e != hipSuccess) return e;
+  }
+  hipLaunchKernelGGL(fn, dim3(unsigned(p.rows)), dim3(NT), lds, s, p);
+  return hipSuccess;
+}
+// Whether a row's vectors with an element above the threshold come so thinly that a ring of kRingSmall slots, expanded
+// beyond kRingExpand, loses one less than once in a million rows.
+bool sparse_hits(tslt_dtype dt, int64_t V, int nt, const tslt::TruncateParams& p) {
+  const int E = 16 / elem_bytes(dt);
+  const double f = std::min(1.0, double(tslt::kBatch) * nt * E / double(V));
+  const double hits = -nt * std::log(1.0 - double(p.jprime) / nt) / f;         // expected above the threshold
+  const double h = 1.0 - std::pow(1.0 - std::min(1.0, hits / double(V)), E);   // ... of a vector
+  return 128.0 * h + 5.0 * std::sqrt(128.0 * h) <= tslt::kRingSmall - tslt::kRingExpand;
+}
+// The shapes of the truncation kernel (see truncate.h).  Up to three rows for two compute units: 512 threads a row.
+// (Not where a row of 256 threads may be redone, which its status tells: the path a row takes does not depend on the
+// size of its batch.)  Else 256: eight workgroups of this footprint on a compute unit, the wide shape; else the deep one.
+template <typename T> hipError_t launch_truncate(tslt_dtype dt, tslt::TruncateParams& p, hipStream_t s) {
+  constexpr int NT = tslt::kTruncThreads, TT = tslt::kTallThreads;
+  const size_t lds = plan_truncate(dt, p.V, NT, p);
+  if (2 * p.rows <= 3 * int64_t(tslt::compute_units()) && p.jprime > 0 && sparse_hits(dt, p.V, NT, p)) {
+    tslt::TruncateParams tall = p;
+    const size_t tall_lds = plan_truncate(dt, p.V, TT, tall);
+    if (tall.jprime > 0) return launch_truncate_shape<T, TT, tslt::kStagesDeep, tslt::kWavesDeep>(tall, tall_lds, s);
+  }
+  if (8 * (lds + sizeof(tslt::TruncateShared) + 256) <= kMaxLds)
+    return launch_truncate_shape<T, NT, tslt::kStagesWide, tslt::kWavesWide>(p, lds, s);
+  return launch_truncate_shape<T, NT, tslt::kStagesDeep, tslt::kWavesDeep>(p, lds, s);
+}
 
 }  // namespace
 
@@ -175,31 +198,9 @@ static int truncate_impl(const void* logits, tslt_dtype dt, int64_t rows, int64_
   p.out_mass = out_mass; p.status = status;
   p.u = u; p.n_samples = n_samples; p.without_replacement = without_replacement ? 1 : 0;
   p.out_token = out_token; p.out_slot = out_slot;
-  constexpr int NT = tslt::kTruncThreads;
-  const size_t lds = plan_truncate(dt, V, NT, p);
-
   hipStream_t s = reinterpret_cast<hipStream_t>(stream);
-  hipError_t e;
-  const bool big_lds = lds + sizeof(tslt::TruncateShared) > 48 * 1024;
-  (void)ws; (void)ws_bytes;
-  const dim3 grid{unsigned(rows)}, block{unsigned(NT)};
-  // eight workgroups of this footprint on a compute unit: the wide shape; else the deep one
-  const bool wide = 8 * (lds + sizeof(tslt::TruncateShared) + 256) <= kMaxLds;
-  auto launch = [&](auto kernel_wide, auto kernel_deep) -> hipError_t {
-    if (wide) {
-      hipLaunchKernelGGL(kernel_wide.fn, grid, block, lds, s, p);
-      return hipSuccess;
-    }
-    if (big_lds) {
-      const hipError_t err = kernel_deep.allow(kLargeLds);
-      if (err != hipSuccess) return err;
-    }
-    hipLaunchKernelGGL(kernel_deep.fn, grid, block, lds, s, p);
-    return hipSuccess;
-  };
-  if (dt == TSLT_BF16) e = launch(TruncKernel<tslt::Bf16, NT, true>{}, TruncKernel<tslt::Bf16, NT, false>{});
-  else if (dt == TSLT_F16) e = launch(TruncKernel<tslt::F16, NT, true>{}, TruncKernel<tslt::F16, NT, false>{});
-  else e = launch(TruncKernel<float, NT, true>{}, TruncKernel<float, NT, false>{});
+  hipError_t e = dt == TSLT_BF16 ? launch_truncate<tslt::Bf16>(dt, p, s)
+                 : dt == TSLT_F16 ? launch_truncate<tslt::F16>(dt, p, s) : launch_truncate<float>(dt, p, s);
   if (e != hipSuccess) return hip_fail(e, "hipFuncSetAttribute");
   if ((e = hipGetLastError()) != hipSuccess) return hip_fail(e, "tslt_truncate launch");
   return TSLT_OK;

@@ -206,3 +206,27 @@ def test_large_vocab_full_size_sampled_rows(tslt):
     frac_exact = float((out["status"] & 256).ne(0).float().mean())
     print("rows on the exact multi-pass path:", frac_exact)
     assert frac_exact < 0.05
+
+
+@pytest.mark.parametrize("dtype,V,k_cap,top_p", [
+    ("bf16", 63, 4, 0.0), ("bf16", 4095, 16, 0.0),             # less than one tile of 512 threads
+    ("f16", 16384, 64, 0.9), ("f16", 16391, 64, 0.0),          # the four tiles of the sample, and a little more
+    ("bf16", 32768, 100, 0.9), ("bf16", 32761, 100, 0.9),      # eight tiles: the sample spread over the row, or not quite
+    ("f32", 16384, 32, 0.0), ("f32", 16379, 32, 0.9), ("f32", 40003, 64, 0.9),
+    ("bf16", 70001, 256, 0.9), ("f16", 100003, 300, 0.95),
+])
+def test_truncate_in_small_batches_as_in_large_ones(tslt, dtype, V, k_cap, top_p):
+    """Up to 384 rows are taken by workgroups of 512 threads, more by 256: the same sets and draws, row for row."""
+    w = W.scaled(W.WORKLOADS["chain_topk"], V=V, dtype=dtype)
+    z = rows_like(w, 390, 7)
+    z[3, V // 2:] = -float("inf")
+    z[4] = 1.0
+    u = W.uniforms((390, 2), 5, 2, 7, DEV)
+    many = tslt.truncate(z, 0.8, 0 if top_p else k_cap, top_p, k_cap, u=u)
+    few = tslt.truncate(z[:130], 0.8, 0 if top_p else k_cap, top_p, k_cap, u=u[:130])
+    torch.cuda.synchronize()
+    for k in ("idx", "logit", "count", "token", "slot"):
+        assert torch.equal(few[k], many[k][:130]), k
+    # the kept mass: fp32 terms of the tail in another order (half an ulp each), rounded to fp32
+    torch.testing.assert_close(few["mass"], many["mass"][:130], rtol=2.5e-7, atol=0)
+    P.compare_truncate({k: v[:20] for k, v in few.items()}, z[:20], 0.8, 0 if top_p else k_cap, top_p, k_cap, label=f"{dtype} {V}")
