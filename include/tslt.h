@@ -168,6 +168,7 @@ int tslt_truncate_sample(const void* logits, tslt_dtype dt, int64_t rows, int64_
  *   out_row_offset         [rows + 1] int64: first word of every row; entry `rows` is the total, so that
  *                          32 * out_row_offset[rows] bits travel, of which sum_r count_r * (b_idx + 16) are
  *                          Section 2.2's D
+ * tslt_pack_cleared is tslt_pack, and sets the words behind the stream, up to tslt_pack_bound_words, to 0.
  * tslt_unpack is the inverse: out_idx / out_logit / out_count as tslt_truncate writes them (-1 / -inf beyond
  * count).  A count that exceeds k_cap, or what its row's words hold, is cut to that.
  * Workspace: none.
@@ -176,6 +177,9 @@ int64_t tslt_pack_bound_words(int64_t rows, int32_t k_cap, int64_t V);
 int tslt_pack(const int32_t* idx, const float* logit, const int32_t* count, int64_t rows, int32_t k_cap, int64_t V,
               tslt_dtype payload, uint32_t* out_words, int64_t out_capacity_words, int64_t* out_row_offset,
               void* stream);
+int tslt_pack_cleared(const int32_t* idx, const float* logit, const int32_t* count, int64_t rows, int32_t k_cap, int64_t V,
+                      tslt_dtype payload, uint32_t* out_words, int64_t out_capacity_words, int64_t* out_row_offset,
+                      void* stream);
 int tslt_unpack(const uint32_t* words, const int64_t* row_offset, int64_t rows, int32_t k_cap, int64_t V,
                 tslt_dtype payload, int32_t* out_idx, float* out_logit, int32_t* out_count, void* stream);
 

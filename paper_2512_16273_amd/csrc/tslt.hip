@@ -231,9 +231,9 @@ int64_t tslt_pack_bound_words(int64_t rows, int32_t k_cap, int64_t V) {
   return rows * tslt::wire_row_words(k_cap, tslt::wire_index_bits(V));
 }
 
-int tslt_pack(const int32_t* idx, const float* logit, const int32_t* count, int64_t rows, int32_t k_cap, int64_t V,
-              tslt_dtype payload, uint32_t* out_words, int64_t out_capacity_words, int64_t* out_row_offset,
-              void* stream) {
+static int pack_impl(bool clear, const int32_t* idx, const float* logit, const int32_t* count, int64_t rows, int32_t k_cap,
+                     int64_t V, tslt_dtype payload, uint32_t* out_words, int64_t out_capacity_words, int64_t* out_row_offset,
+                     void* stream) {
   if (rows < 0 || V < 1 || V > 0x7FFFFFFF) return fail(TSLT_ERR_INVALID_ARG, "tslt_pack: bad shape");
   if (k_cap < 1 || k_cap > TSLT_MAX_K_CAP) return fail(TSLT_ERR_UNSUPPORTED, "tslt_pack: k_cap must be in 1..%d", TSLT_MAX_K_CAP);
   if (payload != TSLT_BF16 && payload != TSLT_F16) return fail(TSLT_ERR_INVALID_ARG, "tslt_pack: the value format must be bfloat16 or binary16");
@@ -245,15 +245,24 @@ int tslt_pack(const int32_t* idx, const float* logit, const int32_t* count, int6
   tslt::WireParams p{};
   p.idx = idx; p.logit = logit; p.count = count; p.rows = rows; p.k_cap = k_cap; p.b_idx = tslt::wire_index_bits(V);
   p.payload = int(payload); p.words = out_words; p.row_offset = out_row_offset;
-  hipStream_t s = reinterpret_cast<hipStream_t>(stream);
-  hipError_t e;
-  hipLaunchKernelGGL(tslt::wire_offsets_kernel, dim3(1), dim3(1024), 0, s, p);
-  if ((e = hipGetLastError()) != hipSuccess) return hip_fail(e, "tslt_pack launch");
-  if (rows > 0) {
-    hipLaunchKernelGGL(tslt::wire_pack_kernel, dim3(unsigned(rows)), dim3(64), 0, s, p);
-    if ((e = hipGetLastError()) != hipSuccess) return hip_fail(e, "tslt_pack launch");
-  }
+  p.clear = clear ? 1 : 0;
+  p.rows_per = tslt::wire_rows_per_group(rows);
+  const int64_t groups = rows > 0 ? (rows + p.rows_per - 1) / p.rows_per : 1;      // (no rows: the total alone)
+  hipLaunchKernelGGL(tslt::wire_pack_kernel, dim3(unsigned(groups)), dim3(tslt::kPackThreads), 0, reinterpret_cast<hipStream_t>(stream), p);
+  const hipError_t e = hipGetLastError();
+  if (e != hipSuccess) return hip_fail(e, "tslt_pack launch");
   return TSLT_OK;
+}
+
+int tslt_pack(const int32_t* idx, const float* logit, const int32_t* count, int64_t rows, int32_t k_cap, int64_t V,
+              tslt_dtype payload, uint32_t* out_words, int64_t out_capacity_words, int64_t* out_row_offset, void* stream) {
+  return pack_impl(false, idx, logit, count, rows, k_cap, V, payload, out_words, out_capacity_words, out_row_offset, stream);
+}
+
+int tslt_pack_cleared(const int32_t* idx, const float* logit, const int32_t* count, int64_t rows, int32_t k_cap, int64_t V,
+                      tslt_dtype payload, uint32_t* out_words, int64_t out_capacity_words, int64_t* out_row_offset,
+                      void* stream) {
+  return pack_impl(true, idx, logit, count, rows, k_cap, V, payload, out_words, out_capacity_words, out_row_offset, stream);
 }
 
 int tslt_unpack(const uint32_t* words, const int64_t* row_offset, int64_t rows, int32_t k_cap, int64_t V,

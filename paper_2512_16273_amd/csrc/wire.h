@@ -12,8 +12,6 @@
 namespace tslt {
 
 constexpr int kPayloadF32 = 0, kPayloadBf16 = 1, kPayloadF16 = 2;    // numbered as tslt_dtype
-constexpr int kWireMaxEntryBits = 31 + 16;
-constexpr int kWireMaxRowWords = (16 + 1024 * kWireMaxEntryBits + 31) / 32;
 
 // A scaled logit as it travels: rounded to nearest-even to the 16-bit format, clamped to its finite range,
 // and returned as the fp32 value the receiver decodes.
@@ -58,6 +56,8 @@ struct WireParams {
   int payload;
   uint32_t* words;
   int64_t* row_offset;
+  int64_t rows_per;      // of one workgroup
+  int clear;             // the words behind the stream, up to the bound, are set to 0
   // unpack
   const uint32_t* in_words;
   const int64_t* in_row_offset;
@@ -68,63 +68,94 @@ struct WireParams {
 
 __device__ __forceinline__ int wire_clamped_count(int c, int k_cap) { return c < 0 ? 0 : (c > k_cap ? k_cap : c); }
 
-// row_offset[r] = words of rows 0..r-1: one workgroup of 1024 threads scans the rows in chunks.
-__global__ __launch_bounds__(1024) void wire_offsets_kernel(const WireParams p) {
-  __shared__ long long wave_tot[16];
-  __shared__ long long base_s;
+// Packing in one launch: a workgroup of four waves takes rows_per consecutive rows, adds up the words of all rows before
+// them (their counts come out of the L2: 4 bytes a row), scans its own and packs a row per wave at a time.  A lane makes
+// a whole word out of the entries that lie in it (E > 16 bits: three at most), so that nothing is assembled in LDS and
+// every store is a full line.  With `clear`, a row zeroes as many words as it falls short of a full row's, counted from
+// the end of out_words: together all those behind the stream.  Bound by its launch at the sizes of a round: packing
+// and unpacking 2048 rows of k_cap 256 take 23.4 us a call through the binding, 30.8 with a launch for the offsets, one
+// for the rows and a fill before them; 12 rows take 23.4 and 30.2.
+constexpr int kPackThreads = 256, kPackWaves = kPackThreads / 64;
+constexpr int kPackGroups = 1024;             // workgroups beyond which they take more than one row per wave
+inline int64_t wire_rows_per_group(int64_t rows) {
+  const int64_t r = (rows + kPackGroups - 1) / kPackGroups;
+  return r > kPackWaves ? r : kPackWaves;
+}
+__device__ __forceinline__ int wire_words_of(int count, const WireParams& p) {
+  return (16 + wire_clamped_count(count, p.k_cap) * (p.b_idx + 16) + 31) >> 5;
+}
+__global__ __launch_bounds__(kPackThreads) void wire_pack_kernel(const WireParams p) {
+  __shared__ long long before_s[kPackWaves];
+  __shared__ int wave_tot[kPackWaves], count_s[kPackThreads], off_s[kPackThreads];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  if (tid == 0) base_s = 0;
-  __syncthreads();
-  for (int64_t r0 = 0; r0 < p.rows; r0 += 1024) {
-    const int64_t r = r0 + tid;
-    long long mine = 0;
-    if (r < p.rows) mine = (16 + (long long)wire_clamped_count(p.count[r], p.k_cap) * (p.b_idx + 16) + 31) / 32;
-    long long inc = mine;
+  const int64_t r0 = int64_t(blockIdx.x) * p.rows_per;
+  const int64_t r1 = r0 + p.rows_per < p.rows ? r0 + p.rows_per : p.rows;
+  if (p.rows == 0 && tid == 0) p.row_offset[0] = 0;
+  const int E = p.b_idx + 16;
+  const int row_max = (16 + p.k_cap * E + 31) >> 5;
+  long long base = 0;
+  for (int64_t r = tid; r < r0; r += kPackThreads) base += wire_words_of(p.count[r], p);
 #pragma unroll
-    for (int d = 1; d < 64; d <<= 1) {
-      const long long up = __shfl_up(inc, d, 64);
-      if (lane >= d) inc += up;
-    }
+  for (int d = 32; d >= 1; d >>= 1) base += __shfl_xor(base, d, 64);
+  if (lane == 0) before_s[wave] = base;
+  __syncthreads();
+  base = 0;
+#pragma unroll
+  for (int w = 0; w < kPackWaves; ++w) base += before_s[w];
+  const uint32_t inv_E = uint32_t(0xFFFFFFFFu / uint32_t(E)) + 1u;      // x / E = umulhi(x, inv_E) for x < 2^16
+  for (int64_t c0 = r0; c0 < r1; c0 += kPackThreads) {
+    const int64_t mine = c0 + tid;
+    const int my_count = mine < r1 ? wire_clamped_count(p.count[mine], p.k_cap) : 0;
+    const int my_words = mine < r1 ? wire_words_of(my_count, p) : 0;
+    const int inc = wave_incl_scan_i32(my_words);
+    __syncthreads();                                                    // the last chunk's rows are packed
     if (lane == 63) wave_tot[wave] = inc;
     __syncthreads();
-    long long before = base_s;
-    for (int w = 0; w < wave; ++w) before += wave_tot[w];
-    if (r < p.rows) p.row_offset[r] = before + inc - mine;
+    int before = 0, total = 0;
+#pragma unroll
+    for (int w = 0; w < kPackWaves; ++w) {
+      before += w < wave ? wave_tot[w] : 0;
+      total += wave_tot[w];
+    }
+    count_s[tid] = my_count;
+    off_s[tid] = before + inc - my_words;
+    if (mine < r1) {
+      p.row_offset[mine] = base + before + inc - my_words;
+      if (mine == p.rows - 1) p.row_offset[p.rows] = base + before + inc;
+    }
     __syncthreads();
-    if (tid == 1023) base_s = before + inc;
-    __syncthreads();
+    const int n = int(r1 - c0 < kPackThreads ? r1 - c0 : kPackThreads);
+    for (int k = wave; k < n; k += kPackWaves) {
+      const int64_t r = c0 + k;
+      const int c = count_s[k];
+      const int n_words = (16 + c * E + 31) >> 5;
+      const long long off = base + off_s[k];
+      const int32_t* ix = p.idx + size_t(r) * p.k_cap;
+      const float* lg = p.logit + size_t(r) * p.k_cap;
+      uint32_t* out = p.words + off;
+      for (int w = lane; w < n_words; w += 64) {
+        const int b0 = w * 32 - 16;                                     // of the entries' own bit stream
+        const int first = b0 > 0 ? int(__umulhi(uint32_t(b0), inv_E)) : 0;
+        uint32_t word = w == 0 ? uint32_t(c) : 0u;
+#pragma unroll
+        for (int t = 0; t < 3; ++t) {
+          const int i = first + t;
+          const int at = i < c ? i : 0;
+          const uint64_t entry = (uint64_t(uint32_t(ix[at])) & ((uint64_t(1) << p.b_idx) - 1)) |
+                                 (uint64_t(payload_bits16(lg[at], p.payload)) << p.b_idx);
+          const int sh = i * E - b0;                                    // where the entry begins in the word
+          const uint32_t piece = sh >= 0 ? uint32_t(entry << (sh & 31)) : uint32_t(entry >> (-sh & 63));
+          word |= i < c && sh < 32 ? piece : 0u;
+        }
+        out[w] = word;
+      }
+      if (p.clear) {
+        uint32_t* tail = p.words + (p.rows * row_max - ((r + 1) * row_max - (off + n_words)));
+        for (int w = lane; w < row_max - n_words; w += 64) tail[w] = 0u;
+      }
+    }
+    base += total;
   }
-  if (tid == 0) p.row_offset[p.rows] = base_s;
-}
-
-// One wave per row: the row's stream is assembled in LDS (entries never share a bit, so OR-ing their pieces
-// into the words is order-free) and copied out.
-__global__ __launch_bounds__(64) void wire_pack_kernel(const WireParams p) {
-  __shared__ uint32_t buf[kWireMaxRowWords];
-  const int64_t r = blockIdx.x;
-  const int lane = threadIdx.x;
-  const int c = wire_clamped_count(p.count[r], p.k_cap);
-  const int E = p.b_idx + 16;
-  const int n_words = int((16 + (long long)c * E + 31) / 32);
-  for (int w = lane; w < n_words; w += 64) buf[w] = 0;
-  __syncthreads();
-  if (lane == 0) buf[0] = uint32_t(c);
-  __syncthreads();
-  const int32_t* ix = p.idx + size_t(r) * p.k_cap;
-  const float* lg = p.logit + size_t(r) * p.k_cap;
-  for (int i = lane; i < c; i += 64) {
-    const uint64_t entry = (uint64_t(uint32_t(ix[i])) & ((uint64_t(1) << p.b_idx) - 1)) |
-                           (uint64_t(payload_bits16(lg[i], p.payload)) << p.b_idx);
-    const long long bit = 16 + (long long)i * E;
-    const int w = int(bit >> 5), sh = int(bit & 31);
-    atomicOr(&buf[w], uint32_t(entry << sh));
-    const uint64_t rest = sh ? (entry >> (32 - sh)) : (entry >> 16 >> 16);
-    if (uint32_t(rest) != 0u) atomicOr(&buf[w + 1], uint32_t(rest));
-    if ((rest >> 32) != 0u) atomicOr(&buf[w + 2], uint32_t(rest >> 32));
-  }
-  __syncthreads();
-  uint32_t* out = p.words + p.row_offset[r];
-  for (int w = lane; w < n_words; w += 64) out[w] = buf[w];
 }
 
 __global__ __launch_bounds__(64) void wire_unpack_kernel(const WireParams p) {

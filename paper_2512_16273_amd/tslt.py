@@ -23,7 +23,7 @@ MAX_K_CAP = 1024
 PAYLOAD = {"f32": 0, "bf16": 1, "f16": 2}       # tslt_dtype codes of the formats a payload can travel in
 
 EXPORTS = ("tslt_version", "tslt_last_error", "tslt_workspace_bytes", "tslt_truncate", "tslt_truncate_sample", "tslt_sample",
-           "tslt_pack_bound_words", "tslt_pack", "tslt_unpack",
+           "tslt_pack_bound_words", "tslt_pack", "tslt_pack_cleared", "tslt_unpack",
            "tslt_verify", "tslt_verify_accept", "tslt_verify_resample", "tslt_verify_staged", "tslt_verify_accept_staged",
            "tslt_verify_static", "tslt_truncation_stats", "tslt_multicandidate_stats", "tslt_calibrate_read", "tslt_verify_tree")
 
@@ -56,8 +56,9 @@ def load(path: Optional[str] = None):
     lib.tslt_truncate.argtypes = [vp, c.c_int, i64, i64, i64, f32, i32, f32, i32, c.c_int, vp, vp, vp, vp, vp, vp, vp, sz, vp]
     lib.tslt_pack_bound_words.restype = i64
     lib.tslt_pack_bound_words.argtypes = [i64, i32, i64]
-    lib.tslt_pack.restype = c.c_int
-    lib.tslt_pack.argtypes = [vp, vp, vp, i64, i32, i64, c.c_int, vp, i64, vp, vp]
+    for fn in (lib.tslt_pack, lib.tslt_pack_cleared):
+        fn.restype = c.c_int
+        fn.argtypes = [vp, vp, vp, i64, i32, i64, c.c_int, vp, i64, vp, vp]
     lib.tslt_unpack.restype = c.c_int
     lib.tslt_unpack.argtypes = [vp, vp, i64, i32, i64, c.c_int, vp, vp, vp, vp]
     lib.tslt_truncate_sample.restype = c.c_int
@@ -188,9 +189,10 @@ def pack(idx: torch.Tensor, logit: torch.Tensor, count: torch.Tensor, V: int, pa
     _dev(idx, torch.int32, "idx"); _dev(logit, torch.float32, "logit"); _dev(count, torch.int32, "count")
     rows, k_cap = idx.shape
     cap = int(lib.tslt_pack_bound_words(rows, k_cap, V))
-    words = torch.zeros(max(cap, 1), dtype=torch.int32, device=idx.device)
+    # (the library clears what lies behind the stream; without rows, or with arguments that it refuses, there is none)
+    words = torch.empty(cap, dtype=torch.int32, device=idx.device) if cap > 0 else torch.zeros(1, dtype=torch.int32, device=idx.device)
     offs = torch.empty(rows + 1, dtype=torch.int64, device=idx.device)
-    _check(lib.tslt_pack(_ptr(idx), _ptr(logit), _ptr(count), rows, k_cap, int(V), PAYLOAD[payload], _ptr(words), cap,
+    _check(lib.tslt_pack_cleared(_ptr(idx), _ptr(logit), _ptr(count), rows, k_cap, int(V), PAYLOAD[payload], _ptr(words), cap,
                          _ptr(offs), _stream()))
     return {"words": words, "row_offset": offs}
 

@@ -119,3 +119,27 @@ def test_calibrate_read_runs_and_checks_its_arguments(tslt):
         tslt.calibrate_read(buf[:1000], 1, sink)
     with pytest.raises(tslt.TsltError):
         tslt.calibrate_read(buf[8:8 + 16384], 1, sink)        # not 16-byte aligned
+
+
+@pytest.mark.parametrize("rows,k_cap,V", [(1, 1, 1), (4, 5, 2), (5, 64, 65536), (1030, 33, 128256), (4097, 16, 32000),
+                                          (262150, 2, 32000)])
+def test_pack_over_the_workgroups(tslt, rows, k_cap, V):
+    """Rows over one and several workgroups and, at the last size, over several chunks of one: every row's words are
+    those it has when it is packed alone, at the offset that the counts give, and nothing but zeros behind them."""
+    g = torch.Generator().manual_seed(rows)
+    idx = torch.randint(0, V, (rows, k_cap), generator=g, dtype=torch.int32).to(DEV)
+    logit = (torch.randn(rows, k_cap, generator=g) * 5).to(DEV)
+    count = torch.randint(-1, k_cap + 2, (rows,), generator=g, dtype=torch.int32).to(DEV)
+    pk = tslt.pack(idx, logit, count, V, "f16")
+    kept = count.clamp(0, k_cap).long()
+    offs = torch.cat([torch.zeros(1, dtype=torch.int64, device=DEV), ((16 + kept * (O.index_bits(V) + 16) + 31) // 32).cumsum(0)])
+    assert torch.equal(pk["row_offset"], offs)
+    assert not pk["words"][int(offs[-1]):].any()
+    for r in {0, rows // 3, rows // 2, rows - 1}:
+        alone = tslt.pack(idx[r:r + 1], logit[r:r + 1], count[r:r + 1], V, "f16")["words"]
+        n = int(offs[r + 1] - offs[r])
+        assert torch.equal(pk["words"][int(offs[r]):int(offs[r + 1])], alone[:n]), r
+    un = tslt.unpack(pk["words"], pk["row_offset"], rows, k_cap, V, "f16")
+    on = torch.arange(k_cap, device=DEV) < kept[:, None]
+    assert torch.equal(un["count"].long(), kept) and torch.equal(un["idx"], torch.where(on, idx, -1))
+    assert torch.equal(un["logit"], torch.where(on, logit.half().float(), -float("inf")))
