@@ -73,8 +73,8 @@ __device__ __forceinline__ int wire_clamped_count(int c, int k_cap) { return c <
 // a whole word out of the entries that lie in it (E > 16 bits: three at most), so that nothing is assembled in LDS and
 // every store is a full line.  With `clear`, a row zeroes as many words as it falls short of a full row's, counted from
 // the end of out_words: together all those behind the stream.  Bound by its launch at the sizes of a round: packing
-// and unpacking 2048 rows of k_cap 256 take 23.4 us a call through the binding, 30.8 with a launch for the offsets, one
-// for the rows and a fill before them; 12 rows take 23.4 and 30.2.
+// and unpacking 2048 rows of k_cap 256 took 30.8 us a call through the binding with a launch for the offsets, one for the
+// rows and a fill before them, 23.4 so (and 18.2 since the binding hands plain integers over); 14 rows 31.9 and 18.2.
 constexpr int kPackThreads = 256, kPackWaves = kPackThreads / 64;
 constexpr int kPackGroups = 1024;             // workgroups beyond which they take more than one row per wave
 inline int64_t wire_rows_per_group(int64_t rows) {
