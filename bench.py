@@ -277,7 +277,7 @@ class TreePlan:
             ver_bytes = B * n_int * V * s + R * K * 8
             leaf_bytes = B * (n_nodes - n_int) * V * s
             self.ops = [("truncate", "truncate_kernel", self.truncate, R * V * s + sparse),
-                        ("verify_tree", "tree_mcveri_kernel", self.verify, ver_bytes + leaf_bytes)]
+                        ("verify_tree", "tree_node_kernel", self.verify, ver_bytes + leaf_bytes)]
             self.total_bytes = R * V * s + sparse + ver_bytes + leaf_bytes
             mode = "every node verified (one target row per node; leaves sampled from their target rows)"
         else:
@@ -287,7 +287,7 @@ class TreePlan:
             path_rows = B * (len(w.expansion) + 1)
             self.positions = None
             self.ops = [("truncate", "truncate_kernel", self.truncate, R * V * s + sparse),
-                        ("verify_tree", "tree_lazy_walk_kernel", self.verify, path_rows * V * s + path_rows * K * 8)]
+                        ("verify_tree", "tree_path_kernel", self.verify, path_rows * V * s + path_rows * K * 8)]
             self.total_bytes = R * V * s + sparse + path_rows * V * s + path_rows * K * 8
             mode = "only the verified path is verified and sampled (positions = candidates actually tested)"
         self.describe = (f"{w.name}: B={B} trees, expansion={tuple(w.expansion)} ({n_int} non-leaf of {n_nodes} nodes), V={V} "
