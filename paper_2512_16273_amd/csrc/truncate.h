@@ -192,6 +192,74 @@ __device__ int exact_select(const void* row, int64_t V, int k_sel, float k2, uin
 }
 
 // ---------------------------------------------------------------------------------------------
+// The threshold of a large set, whose rank is too near the 1024 groups' number to come out among a few more than k
+// elements: up to 4096 groups (no fewer than two per element of the set), their maxima's keys in LDS where the candidates
+// will be, the k-th largest by bisection.  2048 bfloat16 rows of 32000, k_cap 1024: 809 us by the radix selection, 133 so; 500
+// fp32 rows of 12000, k_cap 800: 111 and 39.
+// Returns false with `st` set for an unusable row.
+template <typename T, int NT>
+__device__ bool many_groups_threshold(const void* row, const RowSplit& rs, int k_sel, uint32_t* group, int cap,
+                                                   TruncateShared& sh, float& tau, float& vmax, int& st) {
+  constexpr int E = ElemTraits<T>::kPerVec;
+  constexpr int NW = NT / 64;
+  const int tid = threadIdx.x;
+  const int n_edge = rs.head + rs.tail;
+  const int64_t n_tiles = (rs.nvec + NT - 1) / NT;
+  const int per = 2 * cap / NT < 4096 / NT ? 2 * cap / NT : 4096 / NT;      // a thread's groups
+  for (int u = 0; u < per; ++u) group[u * NT + tid] = 0u;                   // (its own throughout: no barrier)
+  int fin = 0, bad = 0;
+  vmax = -INFINITY;
+  int slot = 0;
+  for (int64_t t0 = 0; t0 < n_tiles; t0 += 4) {
+    uint4 d[4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      const int64_t vi = (t0 + u) * NT + tid;
+      d[u] = neg_inf_vec<T>();
+      if (vi < rs.nvec) d[u] = load_vec(&rs.body[vi]);
+    }
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      float v[E], m = -INFINITY;
+      unpack<T>(d[u], v);
+#pragma unroll
+      for (int e = 0; e < E; ++e) {
+        bad |= (v[e] != v[e] || v[e] == INFINITY) ? 1 : 0;
+        fin += v[e] > -INFINITY ? 1 : 0;
+        m = fmaxf(m, v[e]);
+      }
+      vmax = fmaxf(vmax, m);
+      const uint32_t key = m > -INFINITY ? mono_key(m + 0.0f) : 0u;
+      uint32_t* g = &group[slot * NT + tid];
+      *g = *g > key ? *g : key;
+      slot = slot + 1 == per ? 0 : slot + 1;
+    }
+  }
+  if (tid < n_edge) {
+    const float v = load_elem<T>(row, edge_index<T>(rs, tid));
+    bad |= (v != v || v == INFINITY) ? 1 : 0;
+    fin += v > -INFINITY ? 1 : 0;
+    vmax = fmaxf(vmax, v);
+    const uint32_t key = v > -INFINITY ? mono_key(v + 0.0f) : 0u;
+    group[tid] = group[tid] > key ? group[tid] : key;
+  }
+  bad = block_or_i32<NW>(bad, sh.red);
+  fin = block_sum_i32<NW>(fin, sh.red);
+  if (bad) { st |= 1; return false; }
+  if (fin == 0) { st |= 2; return false; }
+  const int k_eff = k_sel < fin ? k_sel : fin;
+  vmax = block_max_f32<NW>(vmax, sh.red);
+  uint32_t key = 0;
+  for (int bit = 31; bit >= 0; --bit) {
+    const uint32_t trial = key | (1u << bit);
+    int n = 0;
+    for (int u = 0; u < per; ++u) n += group[u * NT + tid] >= trial ? 1 : 0;
+    if (block_sum_i32<NW>(n, sh.red) >= k_eff) key = trial;
+  }
+  tau = key > kKeyNegInf ? key_to_f32(key) : -INFINITY;                     // fewer than k_eff groups: everything
+  return true;
+}
+
 // ---------------------------------------------------------------------------------------------
 // Two-pass selection, the first fallback.  Pass 1 takes the maximum of 1024 disjoint groups of the
 // row (4 per thread); the k-th largest of those maxima is a threshold that at least k elements reach,
@@ -199,7 +267,7 @@ __device__ int exact_select(const void* row, int64_t V, int k_sel, float k2, uin
 // row is full of ties.  Pass 2 collects them.  Returns the number of candidates, 0 with `st` set for
 // an unusable row, or -1 when the candidates do not fit (then the radix selection is used).
 // ---------------------------------------------------------------------------------------------
-template <typename T, int NT>
+template <typename T, int NT, bool kLarge>
 __device__ int two_pass_select(const void* row, const RowSplit& rs, int k_sel, float k2, uint64_t* cand, int cap,
                                uint64_t* sort_tmp, int sort_tmp_cap, uint32_t* tables, TruncateShared& sh,
                                bool need_sum, float& c_ref, double& z_c, int& st) {
@@ -211,62 +279,71 @@ __device__ int two_pass_select(const void* row, const RowSplit& rs, int k_sel, f
   const int64_t n_tiles = (rs.nvec + NT - 1) / NT;
   if (cap < GPT * NT + 2 * E) return -1;
   // pass 1
-  float gmax[GPT];
-#pragma unroll
-  for (int u = 0; u < GPT; ++u) gmax[u] = -INFINITY;
-  int fin = 0, bad = 0;
-  for (int64_t t0 = 0; t0 < n_tiles; t0 += GPT) {
-    uint4 d[GPT];
-#pragma unroll
-    for (int u = 0; u < GPT; ++u) {
-      const int64_t vi = (t0 + u) * NT + tid;
-      d[u] = neg_inf_vec<T>();
-      if (vi < rs.nvec) d[u] = load_vec(&rs.body[vi]);
-    }
-#pragma unroll
-    for (int u = 0; u < GPT; ++u) {
-      float v[E];
-      unpack<T>(d[u], v);
-#pragma unroll
-      for (int e = 0; e < E; ++e) {
-        bad |= (v[e] != v[e] || v[e] == INFINITY) ? 1 : 0;
-        fin += v[e] > -INFINITY ? 1 : 0;
-        gmax[u] = fmaxf(gmax[u], v[e]);
-      }
-    }
-  }
   float edge_v = -INFINITY;
   int64_t edge_i = 0;
   if (tid < n_edge) {
     edge_i = edge_index<T>(rs, tid);
     edge_v = load_elem<T>(row, edge_i);
-    bad |= (edge_v != edge_v || edge_v == INFINITY) ? 1 : 0;
-    fin += edge_v > -INFINITY ? 1 : 0;
   }
-  bad = block_or_i32<NW>(bad, sh.red);
-  fin = block_sum_i32<NW>(fin, sh.red);
-  if (bad) { st |= 1; return 0; }
-  if (fin == 0) { st |= 2; return 0; }
-  const int k_eff = k_sel < fin ? k_sel : fin;
-  float vmax = gmax[0];
+  float tau, vmax;
+  // (beyond 768 the k-th largest of 1024 maxima is exceeded by nearly twice k elements or more, which do not fit; of g
+  // groups it is where 1.25 k is more than g)
+  if (kLarge && k_sel > 768 && 5 * int64_t(k_sel) <= 4 * (rs.nvec < 2 * int64_t(cap) ? rs.nvec : 2 * int64_t(cap))) {
+    if (!many_groups_threshold<T, NT>(row, rs, k_sel, reinterpret_cast<uint32_t*>(cand), cap, sh, tau, vmax, st)) return 0;
+  } else {
+    float gmax[GPT];
 #pragma unroll
-  for (int u = 1; u < GPT; ++u) vmax = fmaxf(vmax, gmax[u]);
-  vmax = block_max_f32<NW>(fmaxf(vmax, edge_v), sh.red);
-  // the k_eff-th largest group maximum (edge elements are groups of their own; empty groups are left out)
-  if (tid == 0) sh.cand_count = 0;
-  __syncthreads();
+    for (int u = 0; u < GPT; ++u) gmax[u] = -INFINITY;
+    int fin = 0, bad = 0;
+    for (int64_t t0 = 0; t0 < n_tiles; t0 += GPT) {
+      uint4 d[GPT];
 #pragma unroll
-  for (int u = 0; u < GPT; ++u)
-    if (gmax[u] > -INFINITY) cand[atomicAdd(&sh.cand_count, 1)] = make_cand(gmax[u], uint32_t(tid * GPT + u));
-  if (tid < n_edge && edge_v > -INFINITY) cand[atomicAdd(&sh.cand_count, 1)] = make_cand(edge_v, uint32_t(GPT * NT + tid));
-  __syncthreads();
-  const int n_groups = sh.cand_count;
-  float tau = -INFINITY;                               // fewer than k_eff non-empty groups: take everything
-  if (n_groups >= k_eff) {
-    if (!bucket_sort_desc<NT>(cand, n_groups, sort_tmp, sort_tmp_cap, cand, k_eff, tables, tables + 256, tables + 512,
-                          sh.red))
-      return -1;
-    tau = cand_value(cand[k_eff - 1]);
+      for (int u = 0; u < GPT; ++u) {
+        const int64_t vi = (t0 + u) * NT + tid;
+        d[u] = neg_inf_vec<T>();
+        if (vi < rs.nvec) d[u] = load_vec(&rs.body[vi]);
+      }
+#pragma unroll
+      for (int u = 0; u < GPT; ++u) {
+        float v[E];
+        unpack<T>(d[u], v);
+#pragma unroll
+        for (int e = 0; e < E; ++e) {
+          bad |= (v[e] != v[e] || v[e] == INFINITY) ? 1 : 0;
+          fin += v[e] > -INFINITY ? 1 : 0;
+          gmax[u] = fmaxf(gmax[u], v[e]);
+        }
+      }
+    }
+    if (tid < n_edge) {
+      bad |= (edge_v != edge_v || edge_v == INFINITY) ? 1 : 0;
+      fin += edge_v > -INFINITY ? 1 : 0;
+    }
+    bad = block_or_i32<NW>(bad, sh.red);
+    fin = block_sum_i32<NW>(fin, sh.red);
+    if (bad) { st |= 1; return 0; }
+    if (fin == 0) { st |= 2; return 0; }
+    const int k_eff = k_sel < fin ? k_sel : fin;
+    vmax = gmax[0];
+#pragma unroll
+    for (int u = 1; u < GPT; ++u) vmax = fmaxf(vmax, gmax[u]);
+    vmax = block_max_f32<NW>(fmaxf(vmax, edge_v), sh.red);
+    // the k_eff-th largest group maximum (edge elements are groups of their own; empty groups are left out)
+    if (tid == 0) sh.cand_count = 0;
+    __syncthreads();
+#pragma unroll
+    for (int u = 0; u < GPT; ++u)
+      if (gmax[u] > -INFINITY) cand[atomicAdd(&sh.cand_count, 1)] = make_cand(gmax[u], uint32_t(tid * GPT + u));
+    if (tid < n_edge && edge_v > -INFINITY) cand[atomicAdd(&sh.cand_count, 1)] = make_cand(edge_v, uint32_t(GPT * NT + tid));
+    __syncthreads();
+    const int n_groups = sh.cand_count;
+    tau = -INFINITY;                               // fewer than k_eff non-empty groups: take everything
+    if (n_groups >= k_eff) {
+      if (!bucket_sort_desc<NT>(cand, n_groups, sort_tmp, sort_tmp_cap, cand, k_eff, tables, tables + 256, tables + 512,
+                            sh.red))
+        return -1;
+      tau = cand_value(cand[k_eff - 1]);
+    }
   }
   __syncthreads();
   // pass 2
@@ -647,7 +724,7 @@ __global__ __launch_bounds__(NT, kWavesPerSimd) void truncate_kernel(const Trunc
   if (!fast_ok) {
     st |= 256;
     const bool need_sum = !(z_c > 0.0 && z_c < INFINITY);
-    n_cand = two_pass_select<T, NT>(row, rs, p.k_sel, p.k2, cand, p.sort_cap, sort_tmp, sort_tmp_cap, tables, sh, need_sum,
+    n_cand = two_pass_select<T, NT, kWavesPerSimd == 4>(row, rs, p.k_sel, p.k2, cand, p.sort_cap, sort_tmp, sort_tmp_cap, tables, sh, need_sum,
                                 c_ref, z_c, st);
     if (n_cand < 0) n_cand = exact_select<T, NT>(row, p.V, p.k_sel, p.k2, cand, tables, sh, c_ref, z_c, st);
   }

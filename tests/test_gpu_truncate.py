@@ -230,3 +230,23 @@ def test_truncate_in_small_batches_as_in_large_ones(tslt, dtype, V, k_cap, top_p
     # the kept mass: fp32 terms of the tail in another order (half an ulp each), rounded to fp32
     torch.testing.assert_close(few["mass"], many["mass"][:130], rtol=2.5e-7, atol=0)
     P.compare_truncate({k: v[:20] for k, v in few.items()}, z[:20], 0.8, 0 if top_p else k_cap, top_p, k_cap, label=f"{dtype} {V}")
+
+
+@pytest.mark.parametrize("dtype,V,k_cap", [("bf16", 32000, 1024), ("f32", 15001, 1024), ("f16", 12001, 800), ("bf16", 5000, 700),
+                                           ("f32", 2100, 1024)])
+def test_truncate_large_sets_by_groups(tslt, dtype, V, k_cap):
+    """Sets too large a part of the row for the sampled threshold (a rank beyond 0.8 * 256 thread maxima; fp32 rows of 15001
+    with 1024 kept ask for 217 of 204, of 20003 only for 189): the k-th largest of up to 4096 group maxima; at the
+    smallest sizes there are too few groups and the radix selection follows.  Ties, masked and broken rows among them."""
+    w = W.scaled(W.WORKLOADS["chain_topk"], V=V, dtype=dtype)
+    z = rows_like(w, 12, 9)
+    z[1] = torch.round(z[1].float() / 2).to(z.dtype)           # a few dozen values
+    z[2, k_cap // 2:] = -float("inf")
+    z[3] = 0.5
+    z[4, V // 3] = float("nan")
+    z[5] = -float("inf")
+    z[6, ::2] = -float("inf")
+    out = tslt.truncate(z, 1.0, k_cap, 0.0, k_cap)
+    torch.cuda.synchronize()
+    res = P.compare_truncate(out, z, 1.0, k_cap, 0.0, k_cap, label=f"{dtype} {V} {k_cap}")
+    assert res["exact_path_rows"] >= 10
