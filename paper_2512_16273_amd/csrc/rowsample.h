@@ -257,7 +257,7 @@ struct RowShared {
   double wave_sum[kRowWaves];
   float wave_max[kRowWaves];
   double target, before;
-  int flags, next_run, item, pick, last, cmd;
+  int flags, next_run, item, n_corr, pick, last, cmd;
 };
 
 template <typename T> struct RowWork {
@@ -621,17 +621,20 @@ __device__ __forceinline__ double row_correct(const RowWork<T>& w, const RowStat
   return (part >= 0.0 ? part : r.sum_a) * zp_over_c - r.sum_e;
 }
 // First wave: the item in which the cumulative mass passes u * total, in row order, and what row_pick needs (item -1:
-// there is none).  `corr`: the total of the corrections.
+// there is none).  `corrected`: corrections have been added to the items, `corr` in all, and are in set_a; without them
+// nothing has been written there.
 template <typename T>
-__device__ __forceinline__ void row_locate(const RowWork<T>& w, const RowState& r, float u, double corr, RowShared& sh) {
+__device__ __forceinline__ void row_locate(const RowWork<T>& w, const RowState& r, float u, bool corrected, double corr,
+                                           RowShared& sh) {
   const int lane = lane_id();
   const int n_items = w.n_items;
-  double total = r.zp + corr;
+  double total = corrected ? r.zp + corr : r.zp;
   if (!(total > 0.0)) {          // defensive: an all-zero residual falls back to p itself
     for (int i = lane; i < w.count; i += 64) {
       const int y = sh.set_y[i];
-      if (y >= 0) { atomicAdd(&sh.items[item_of(w, y)], -sh.set_a[i]); sh.set_a[i] = 0.0; }
+      if (y >= 0) atomicAdd(&sh.items[item_of(w, y)], -sh.set_a[i]);
     }
+    corrected = false;
     total = r.zp;
   }
   const double target = double(u) * total;
@@ -667,7 +670,10 @@ __device__ __forceinline__ void row_locate(const RowWork<T>& w, const RowState& 
   const int src = hit != 0 ? __ffsll((long long)hit) - 1 : (any != 0 ? 63 - __clzll((long long)any) : 0);
   const int item = hit != 0 ? found : last_pos;
   const double before = hit != 0 ? found_before : last_before;
-  if (lane == src) { sh.item = item; sh.before = before; sh.target = target; sh.pick = 0x7FFFFFFF; sh.last = -1; }
+  if (lane == src) {
+    sh.item = item; sh.before = before; sh.target = target; sh.pick = 0x7FFFFFFF; sh.last = -1;
+    sh.n_corr = corrected ? w.count : 0;
+  }
 }
 
 // The first four waves: the token, from what row_locate left (behind a barrier; the other waves have ended): every
@@ -699,7 +705,8 @@ __device__ __forceinline__ int row_pick(const RowWork<T>& w, double* elem_corr, 
   const bool inside = !edge && my_vec < rs.nvec;
   uint4 dv = neg_inf_vec<T>();
   if (inside) dv = load_vec(&rs.body[my_vec]);     // travels while the corrections are laid out
-  for (int i = tid; i < w.count; i += kThreads) {
+  const int n_corr = sh.n_corr;
+  for (int i = tid; i < n_corr; i += kThreads) {
     const int y = sh.set_y[i];
     if (y >= first && y < end) elem_corr[y - first] = sh.set_a[i];
   }

@@ -138,7 +138,10 @@ __device__ __forceinline__ int tree_node(const TreeParams& p, int64_t b, int nod
         }
       }
     }
-    if (accepted < 0 && r.ok) row_locate(w, r, u_res, r.stages > 0 || part >= 0.0 ? row_correct(w, r, part, sh) : 0.0, sh);
+    if (accepted < 0 && r.ok) {
+      const bool updated = r.stages > 0 || part >= 0.0;             // not at a leaf or where every candidate is absent
+      row_locate(w, r, u_res, updated, updated ? row_correct(w, r, part, sh) : 0.0, sh);
+    }
     st = r.st;
     if (lane == 0) sh.cmd = accepted >= 0 ? accepted : (r.ok ? -1 : -2);
   }

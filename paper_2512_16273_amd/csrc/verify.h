@@ -165,7 +165,7 @@ __global__ __launch_bounds__(kRowThreads, kWavesPerSimd) void verify_resample_ke
       RowState rst;
       row_eval(w, rst, sh);
       if (rst.ok) {
-        row_locate(w, rst, u_res, residual ? row_test_first(w, rst, -1, sh).part * rst.zp - rst.sum_e : 0.0, sh);
+        row_locate(w, rst, u_res, residual, residual ? row_test_first(w, rst, -1, sh).part * rst.zp - rst.sum_e : 0.0, sh);
       }
       if (lane == 0) { sh.cmd = rst.ok ? 1 : 0; sh.flags = rst.st; }
     }
@@ -238,7 +238,7 @@ __global__ __launch_bounds__(kRowThreads, kWavesPerSimd) void verify_round_kerne
       flag = t.found && double(u_acc) < bound ? 1 : 0;
       corr = t.part * rst.zp - rst.sum_e;
     }
-    if (flag == 0 && p.draws) row_locate(w, rst, u_res, corr, sh);
+    if (flag == 0 && p.draws) row_locate(w, rst, u_res, !bonus, corr, sh);
     st = rst.st;
     if (lane_id() == 0) sh.cmd = flag;
   }

@@ -182,3 +182,30 @@ def test_tree_config_shape_few_trees(tslt):
     torch.cuda.synchronize()
     print(P.compare_tree(out, ref, w.expansion, label="config4 renormalised"), "lens", ref["verify"]["len"],
           "nodes that rejected every candidate:", int(np.count_nonzero(ref["verify"]["node_slot"][:, :n_int] < 0)))
+
+
+@pytest.mark.parametrize("dtype,B,rule", [("f32", 3, False), ("bf16", 3, True), ("f16", 3, False),
+                                          ("f32", 80, True), ("bf16", 80, False), ("f16", 80, True)])
+def test_tree_nodes_without_any_candidate(tslt, dtype, B, rule):
+    """A pruned tree: nodes all of whose candidates are absent (-1) but whose set is not empty draw from their target
+    distribution itself, whatever the node before them left behind; roots and inner nodes, evaluated all at once and (80
+    trees of 7 nodes are too many for that) in a walk, first and after accepted candidates."""
+    w = W.scaled(W.WORKLOADS["tree"], B=B, V=1500, expansion=(2, 2), top_k=64, k_cap=64, dtype=dtype, sigma=0.5, noise_t=0.3,
+                 zipf=0.3, without_replacement=rule)
+    tree = W.make_tree(w, 37, DEV)
+    tree["u_accept"] = tree["u_accept"] * 0.2           # most walks reach the second layer
+    ref = oracle_for(w, tree, renormalised_rule=rule)
+    cands = ref["cands"].copy()
+    cands[::3, :2] = -1                                 # the root's
+    cands[1::3, 2:] = -1                                # both nodes' of the layer below
+    cands[2::3, 2:4] = -1                               # one of them
+    ref["cands"] = cands
+    ref["verify"] = O.verify_tree(P.to_np(tree["target"]), w.T, w.expansion, ref["q_idx"], ref["q_logit"], ref["q_count"], cands,
+                                  P.to_np(tree["u_accept"]), P.to_np(tree["u_resample"]), rule)
+    assert (ref["verify"]["len"][1::3] == 2).any()
+    out = run_tree(tslt, w, tree, ref, renormalised_rule=rule)
+    path_only = run_tree(tslt, w, tree, ref, all_nodes=False, renormalised_rule=rule)
+    torch.cuda.synchronize()
+    print(P.compare_tree(out, ref, w.expansion, label="pruned"), np.bincount(ref["verify"]["len"]))
+    walked = {k: path_only[k] for k in ("seq", "len")}          # (the ratios off the path are NaN)
+    P.compare_tree(walked, ref, w.expansion, all_nodes=False, label="pruned, path only")
