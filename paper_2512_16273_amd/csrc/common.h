@@ -192,6 +192,9 @@ __device__ __forceinline__ int lanes_below(uint64_t mask) {
   return __builtin_amdgcn_mbcnt_hi(uint32_t(mask >> 32), __builtin_amdgcn_mbcnt_lo(uint32_t(mask), 0));
 }
 
+// A condition that is the same in all lanes of a wave, as such: the compiler branches on it without masking lanes.
+__device__ __forceinline__ bool same_in_wave(bool b) { return __builtin_amdgcn_readfirstlane(int(b)) != 0; }
+
 // The value of one lane, named by a wave-uniform number, in all lanes (no LDS round trip).
 __device__ __forceinline__ double lane_f64(double v, int src) {
   return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(v), src), __builtin_amdgcn_readlane(__double2loint(v), src));

@@ -256,7 +256,8 @@ struct RowShared {
   double w_part[kRowWaves], e_part[kRowWaves];      // their sums over the entries that a wave stored
   double wave_sum[kRowWaves];
   float wave_max[kRowWaves];
-  double target, before;
+  double target, before, none;
+  double removed;                       // q_hat of the candidates that have left the proposal
   int flags, next_run, item, n_corr, pick, last, cmd;
 };
 
@@ -272,12 +273,19 @@ template <typename T> struct RowWork {
   float smax;           // the reference of the masses
 };
 
+// A residual of no more than this share of the row's mass is none: what is left to draw from, or to test the next
+// candidate against, stays the distribution that it was taken from.  The masses are sums of terms within 1.5 ulp through
+// about thirty additions on the longest way (a lane's terms, the wave, the items), the set's part of them of terms within
+// an ulp through twenty: where the two should cancel they leave up to 6e-15 of the row.  (The least that a rejection of a
+// token of the set leaves is the share 2^-24 of its q_hat.)
+constexpr double kNoResidual = 0x1p-47;
+
 // What the first wave knows of the row (the same in all lanes).
 struct RowState {
   double zp, sum_e;     // total mass, the set's part of it
   double inv_zp;        // 1 / total mass: p is set_e * inv_zp before the first update
   double inv_w;         // 1 / sum of the set's weights: q_hat is set_w * inv_w, a stage's proposal q_hat * qscale
-  double p_out, c, sum_a, qscale, removed;
+  double p_out, c, sum_a, qscale;
   int st, stages;
   bool ok;
 };
@@ -493,7 +501,7 @@ template <typename T> __device__ __forceinline__ void row_eval(const RowWork<T>&
   r.p_out = 1.0 - r.sum_a > 0.0 ? 1.0 - r.sum_a : 0.0;
   r.c = 1.0;
   r.qscale = 1.0;
-  r.removed = 0.0;
+  sh.removed = 0.0;
   r.stages = 0;
 }
 
@@ -570,55 +578,57 @@ __device__ __forceinline__ RowTest row_test_first(const RowWork<T>& w, const Row
   });
   return row_test_result(part, shared, q_x, a_x, 1.0);
 }
-// First wave: p <- norm(max(0, p - proposal)), with the sum over the set that row_test returned; `gone` leaves the
-// proposal (a candidate drawn without replacement; -1: none).
+// First wave: whether max(0, p - proposal), with the sum over the set that row_test returned, holds any mass.
+__device__ __forceinline__ bool row_has_residual(const RowState& r, double part) {
+  return same_in_wave(part + r.c * r.p_out > kNoResidual * r.c);
+}
+// First wave: p <- norm(max(0, p - proposal)), or p if that holds none; `gone` leaves the proposal (a candidate drawn
+// without replacement; -1: none).
 template <typename T>
 __device__ __forceinline__ void row_update(const RowWork<T>& w, RowState& r, double part, int gone, RowShared& sh) {
-  const double Z = part + r.c * r.p_out;
-  const double inv_Z = Z > 0.0 ? 1.0 / Z : 1.0;
+  const bool holds = row_has_residual(r, part);
+  const double inv_Z = holds ? 1.0 / (part + r.c * r.p_out) : 1.0;
+  const double q_scale = holds ? r.inv_w * r.qscale : 0.0;
   const double* src_a = r.stages ? sh.set_a : sh.set_e;
   const double a_scale = r.stages ? 1.0 : r.inv_zp;
   int y[4];
   double a[4], wt[4];
   over_set(w.count, [&](int k, int i) { y[k] = sh.set_y[i]; a[k] = src_a[i]; wt[k] = sh.set_w[i]; },
            [&](int k, int i, bool valid) {
-    const double d = a[k] * a_scale - wt[k] * r.inv_w * r.qscale;
+    const double d = a[k] * a_scale - wt[k] * q_scale;
     if (valid) {
       sh.set_a[i] = y[k] >= 0 && d > 0.0 ? d * inv_Z : 0.0;
       if (y[k] == gone && y[k] >= 0) sh.set_w[i] = 0.0;
     }
   });
   r.c *= inv_Z;
-  r.sum_a = part * inv_Z;
+  r.sum_a = holds ? part * inv_Z : r.sum_a;
   ++r.stages;
 }
 
-// First wave: the masses after the updates made so far, and with `part` >= 0 one more with that sum: e_y off the set
-// and a * z_p / c on it, in units of the row's terms.  The set's corrections are added to the items they fall into;
+// First wave: the masses after the updates made so far, and after one more with the sum `part` if it is pending: e_y off
+// the set and a * z_p / c on it, in units of the row's terms.  The set's corrections are added to the items they fall into;
 // returns their total.
 template <typename T>
-__device__ __forceinline__ double row_correct(const RowWork<T>& w, const RowState& r, double part, RowShared& sh) {
+__device__ __forceinline__ double row_correct(const RowWork<T>& w, const RowState& r, bool pending, double part, RowShared& sh) {
   // with one more update a becomes max(0, a - q) / Z and c becomes c / Z: Z drops out of a * z_p / c
   const double zp_over_c = r.zp / r.c;
   const double* src_a = r.stages ? sh.set_a : sh.set_e;
   const double a_scale = r.stages ? 1.0 : r.inv_zp;
-  const double q_scale = part >= 0.0 ? r.inv_w * r.qscale : 0.0;
+  const double q_scale = pending ? r.inv_w * r.qscale : 0.0;
   int y[4];
   double a[4], e[4], wt[4];
   over_set(w.count, [&](int k, int i) { y[k] = sh.set_y[i]; a[k] = src_a[i]; e[k] = sh.set_e[i]; wt[k] = sh.set_w[i]; },
            [&](int k, int i, bool valid) {
-    double ak = a[k] * a_scale;
-    if (part >= 0.0) {
-      ak -= wt[k] * q_scale;
-      ak = ak > 0.0 ? ak : 0.0;
-    }
+    double ak = a[k] * a_scale - wt[k] * q_scale;
+    ak = ak > 0.0 ? ak : 0.0;
     if (valid && y[k] >= 0) {
       const double corr = ak * zp_over_c - e[k];
       sh.set_a[i] = corr;
       atomicAdd(&sh.items[item_of(w, y[k])], corr);
     }
   });
-  return (part >= 0.0 ? part : r.sum_a) * zp_over_c - r.sum_e;
+  return (pending ? part : r.sum_a) * zp_over_c - r.sum_e;
 }
 // First wave: the item in which the cumulative mass passes u * total, in row order, and what row_pick needs (item -1:
 // there is none).  `corrected`: corrections have been added to the items, `corr` in all, and are in set_a; without them
@@ -629,7 +639,7 @@ __device__ __forceinline__ void row_locate(const RowWork<T>& w, const RowState& 
   const int lane = lane_id();
   const int n_items = w.n_items;
   double total = corrected ? r.zp + corr : r.zp;
-  if (!(total > 0.0)) {          // defensive: an all-zero residual falls back to p itself
+  if (same_in_wave(corrected && !(total > kNoResidual * r.zp))) {      // the items as they were, and p itself
     for (int i = lane; i < w.count; i += 64) {
       const int y = sh.set_y[i];
       if (y >= 0) atomicAdd(&sh.items[item_of(w, y)], -sh.set_a[i]);
@@ -638,41 +648,54 @@ __device__ __forceinline__ void row_locate(const RowWork<T>& w, const RowState& 
     total = r.zp;
   }
   const double target = double(u) * total;
-  const int per = (n_items + 63) / 64;             // consecutive items per lane, four at a time
-  double lsum = 0.0;
-  for (int q = 0; q < per; q += 4) {
-#pragma unroll
-    for (int k = 0; k < 4; ++k) {
-      const int it = lane * per + q + k;
-      const double t = q + k < per && it < n_items ? sh.items[it] : 0.0;
-      lsum += t > 0.0 ? t : 0.0;
-    }
+  if (lane == 0) {                                   // (what is seldom looked at again waits in LDS, not in registers)
+    sh.target = target; sh.none = kNoResidual * r.zp; sh.n_corr = corrected ? w.count : 0;
+    sh.item = sh.last = -1; sh.pick = 0x7FFFFFFF;
   }
-  double run = wave_incl_scan_f64(lsum) - lsum;
-  int found = -1, last_pos = -1;
-  double found_before = 0.0, last_before = 0.0;
-  for (int q = 0; q < per; q += 4) {
+  const int per = (n_items + 63) / 64;               // consecutive items per lane, four at a time
+  for (;;) {
+    double lsum = 0.0;
+    for (int q = 0; q < per; q += 4) {
 #pragma unroll
-    for (int k = 0; k < 4; ++k) {
-      const int it = lane * per + q + k;
-      const double t = q + k < per && it < n_items ? sh.items[it] : 0.0;
-      const bool pos = t > 0.0;
-      const bool hit = pos && run + t > target && found < 0;
-      last_pos = pos ? it : last_pos;
-      last_before = pos ? run : last_before;
-      found = hit ? it : found;
-      found_before = hit ? run : found_before;
-      run += pos ? t : 0.0;
+      for (int k = 0; k < 4; ++k) {
+        const int it = lane * per + q + k;
+        const double t = q + k < per && it < n_items ? sh.items[it] : 0.0;
+        lsum += t > 0.0 ? t : 0.0;
+      }
     }
-  }
-  // the first lane that saw the target passed, else the last one that holds an item with mass
-  const uint64_t hit = ballot(found >= 0), any = ballot(last_pos >= 0);
-  const int src = hit != 0 ? __ffsll((long long)hit) - 1 : (any != 0 ? 63 - __clzll((long long)any) : 0);
-  const int item = hit != 0 ? found : last_pos;
-  const double before = hit != 0 ? found_before : last_before;
-  if (lane == src) {
-    sh.item = item; sh.before = before; sh.target = target; sh.pick = 0x7FFFFFFF; sh.last = -1;
-    sh.n_corr = corrected ? w.count : 0;
+    double run = wave_incl_scan_f64(lsum) - lsum;
+    int found = -1, last_pos = -1;
+    double found_before = 0.0, last_before = 0.0;
+    for (int q = 0; q < per; q += 4) {
+#pragma unroll
+      for (int k = 0; k < 4; ++k) {
+        const int it = lane * per + q + k;
+        const double t = q + k < per && it < n_items ? sh.items[it] : 0.0;
+        const bool pos = t > 0.0;
+        const bool hit = pos && run + t > target && found < 0;
+        last_pos = pos ? it : last_pos;
+        last_before = pos ? run : last_before;
+        found = hit ? it : found;
+        found_before = hit ? run : found_before;
+        run += pos ? t : 0.0;
+      }
+    }
+    // the first lane that saw the target passed, else the last one that holds an item with mass
+    const uint64_t hit = ballot(found >= 0), any = ballot(last_pos >= 0);
+    const int src = hit != 0 ? __ffsll((long long)hit) - 1 : (any != 0 ? 63 - __clzll((long long)any) : 0);
+    const int item = __builtin_amdgcn_readlane(hit != 0 ? found : last_pos, src);
+    if (item < 0) {                                  // every one has been emptied: p in the last of them
+      sh.n_corr = 0;
+      return;
+    }
+    if (lane == src) { sh.item = item; sh.before = hit != 0 ? found_before : last_before; }
+    const double mass = sh.items[item];
+    if (same_in_wave(sh.n_corr == 0 || mass > sh.none)) return;
+    // so little: is it more than what rounding leaves where the corrections take an item's whole mass away?
+    double e = 0.0;
+    for (int i = lane; i < w.count; i += 64) e += sh.set_y[i] >= 0 && item_of(w, sh.set_y[i]) == item ? sh.set_e[i] : 0.0;
+    if (same_in_wave(mass > kNoResidual * wave_sum_f64(e))) return;
+    sh.items[item] = 0.0;
   }
 }
 

@@ -114,16 +114,16 @@ __device__ __forceinline__ int tree_node(const TreeParams& p, int64_t b, int nod
     double part = -1.0;                                             // of the last rejection, whose update is still to be made
     if (!leaf) {
       int gone = -1;
-      double gone_q = 0.0;
       if (r.ok) {
         for (int i = 0; i < k; ++i) {
           const int x = __builtin_amdgcn_readlane(my_cand, i);
           if (x < 0) continue;                                      // absent candidate
           if (part >= 0.0) {                                        // the candidate before was rejected
             row_update(w, r, part, gone, sh);
-            r.removed += gone_q;
-            const double rest = 1.0 - r.removed;
-            r.qscale = p.wor ? (rest > 0.0 ? 1.0 / rest : 0.0) : 1.0;
+            if (p.wor) {
+              const double rest = 1.0 - sh.removed;
+              r.qscale = rest > 0.0 ? 1.0 / rest : 0.0;
+            }
           }
           const RowTest t = row_test(w, r, x, sh);
           if (!t.found) r.st |= 4;
@@ -134,13 +134,14 @@ __device__ __forceinline__ int tree_node(const TreeParams& p, int64_t b, int nod
           part = t.part;
           // drawn without replacement: x leaves the urn and what is left is renormalised
           gone = p.wor && t.found ? x : -1;
-          gone_q = gone >= 0 ? t.q_x : 0.0;
+          if (gone >= 0) sh.removed += t.q_x;
         }
       }
     }
     if (accepted < 0 && r.ok) {
-      const bool updated = r.stages > 0 || part >= 0.0;             // not at a leaf or where every candidate is absent
-      row_locate(w, r, u_res, updated, updated ? row_correct(w, r, part, sh) : 0.0, sh);
+      const bool pending = part >= 0.0 && row_has_residual(r, part);
+      const bool updated = r.stages > 0 || pending;                 // not at a leaf or where every candidate is absent
+      row_locate(w, r, u_res, updated, updated ? row_correct(w, r, pending, part, sh) : 0.0, sh);
     }
     st = r.st;
     if (lane == 0) sh.cmd = accepted >= 0 ? accepted : (r.ok ? -1 : -2);
