@@ -406,6 +406,7 @@ __device__ __forceinline__ void row_sweep(RowWork<T>& w, double* table, int half
       cur = nxt;
     }
   } else {
+    if (half > -2) Terms::build(table, rT, kRowThreads, half);      // (the next row of a walk may have runs)
     __syncthreads();
     row_gather(w);
   }

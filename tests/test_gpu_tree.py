@@ -209,3 +209,19 @@ def test_tree_nodes_without_any_candidate(tslt, dtype, B, rule):
     print(P.compare_tree(out, ref, w.expansion, label="pruned"), np.bincount(ref["verify"]["len"]))
     walked = {k: path_only[k] for k in ("seq", "len")}          # (the ratios off the path are NaN)
     P.compare_tree(walked, ref, w.expansion, all_nodes=False, label="pruned, path only")
+
+
+@pytest.mark.parametrize("dtype,V", [("f16", 9), ("f16", 13), ("bf16", 9), ("f32", 5)])
+def test_tree_path_over_rows_with_and_without_a_whole_vector(tslt, dtype, V):
+    """Vocabularies of a vector and a little more: whether a row holds a whole aligned vector depends on where it starts, so
+    a walk meets its first one at any of its nodes (180 trees of 3 or 5 nodes are walked node after node)."""
+    w = W.scaled(W.WORKLOADS["tree"], B=180, V=V, expansion=(1, 1, 1, 1) if dtype != "f32" else (1, 1), top_k=4, k_cap=4, dtype=dtype,
+                 zipf=0.3, sigma=0.5, noise_t=0.3, without_replacement=False)
+    tree = W.make_tree(w, 41, DEV)
+    tree["u_accept"] = tree["u_accept"] * 0.3
+    ref = oracle_for(w, tree)
+    out = run_tree(tslt, w, tree, ref)
+    path_only = run_tree(tslt, w, tree, ref, all_nodes=False)
+    torch.cuda.synchronize()
+    print(P.compare_tree(out, ref, w.expansion, label="tiny"), np.bincount(ref["verify"]["len"]))
+    P.compare_tree({k: path_only[k] for k in ("seq", "len")}, ref, w.expansion, all_nodes=False, label="tiny, path only")
