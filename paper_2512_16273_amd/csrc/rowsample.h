@@ -258,7 +258,7 @@ struct RowShared {
   float wave_max[kRowWaves];
   double target, before, none;
   double removed;                       // q_hat of the candidates that have left the proposal
-  int flags, next_run, item, n_corr, pick, last, cmd;
+  int flags, next_run, item, n_corr, pick, last, cmd, st;
 };
 
 template <typename T> struct RowWork {

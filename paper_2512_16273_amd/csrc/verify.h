@@ -167,19 +167,19 @@ __global__ __launch_bounds__(kRowThreads, kWavesPerSimd) void verify_resample_ke
       if (rst.ok) {
         row_locate(w, rst, u_res, residual, residual ? row_test_first(w, rst, -1, sh).part * rst.zp - rst.sum_e : 0.0, sh);
       }
-      if (lane == 0) { sh.cmd = rst.ok ? 1 : 0; sh.flags = rst.st; }
+      if (lane == 0) { sh.cmd = rst.ok ? 1 : 0; sh.st = rst.st; }      // (another wave may still look at sh.flags)
     }
     row_clear<T>(table);
     __syncthreads();
     if (wave_id() >= kPickWaves) return;
     if (sh.cmd) token = row_pick(w, table, sh);
   } else {
-    if (tid == 0) sh.flags = 0;
+    if (tid == 0) sh.st = 0;
     __syncthreads();
   }
   if (wave_id() != 0) return;
   // status bits of the positions up to the one that decided
-  int st = residual ? 0 : sh.flags;
+  int st = residual ? 0 : sh.st;
   for (int j = lane; j <= jstar && j < p.gamma; j += 64) st |= j == lane ? st_first : p.row_status[b * p.gamma + j];
   st = wave_or_i32(st);
   int32_t* ot = p.out_tokens + size_t(b) * (p.gamma + 1);

@@ -354,3 +354,24 @@ def test_verify_tiny_vocabularies(tslt, dtype, V):
     assert t["top_p_near_ties"] == 0 and np.array_equal(P.to_np(tr["token"]).reshape(w.B, w.gamma), ref["tokens"])
     res = P.compare_verify(out, ref["verify"], label=f"tiny {dtype} {V}")
     assert res["accept_near_ties"] == 0 and ref["verify"]["accept_len"][0] == w.gamma
+
+
+@pytest.mark.parametrize("dtype,B", [("f32", 300), ("bf16", 600), ("f16", 300)])
+def test_verify_empty_bonus_rows_of_a_large_batch(tslt, dtype, B):
+    """Batches beyond the one-pass rounds in which every token is accepted and every other bonus row holds nothing above -inf
+    (or NaN): no token from it, its status bit, and the sequences between them as ever."""
+    V = 1300
+    w = W.scaled(W.WORKLOADS["chain_topk"], B=B, V=V, gamma=1, dtype=dtype, top_k=8, k_cap=8)
+    chain = W.make_chain(w, 43, DEV)
+    chain["target"][::4, 1] = -float("inf")
+    chain["target"][2::4, 1, 700] = float("nan")
+    u_acc = torch.zeros_like(chain["u_accept"])
+    ref = P.oracle_chain(P.to_np(chain["draft"]), P.to_np(chain["target"]), w.T, w.top_k, w.top_p, w.k_cap,
+                         P.to_np(chain["u_sample"]), P.to_np(u_acc), P.to_np(chain["u_resample"]))
+    for _ in range(3):
+        out = tslt.verify(chain["target"], w.T, t32(ref["q_idx"]), t32(ref["q_logit"]), t32(ref["q_count"]), t32(ref["tokens"]),
+                          u_acc, chain["u_resample"])
+        torch.cuda.synchronize()
+        P.compare_verify(out, ref["verify"], label="empty bonus rows")
+        st = P.to_np(out["status"])
+        assert np.all(st[::4] == 2) and np.all(st[2::4] == 1) and np.all(st[1::2] == 0)
