@@ -28,7 +28,8 @@ constexpr int kMaxItems = kMaxRuns + 2;             // a row's runs, and the ele
 static_assert(kMaxItems <= kRowThreads, "one item per thread");
 
 // The fp64 terms of a row are made in one of two ways, both referenced to 0 rather than to the row maximum,
-// which is safe while |s| <= kTabMaxS; a row that holds a larger |s| is swept again, referenced to its maximum.
+// which is safe while s <= kTabMaxS and something lies above -kTabMaxS (what lies below is nothing beside it); a row
+// that holds a larger s, or nothing but smaller ones, is swept again, referenced to its maximum.
 //
 // BitTerms, 16-bit rows: a table of exp(s), s = fl32(z / T), for every logit z of a magnitude range that holds
 // the bulk of a row; a term costs five instructions and one LDS read.
@@ -43,7 +44,12 @@ static_assert(kMaxItems <= kRowThreads, "one item per thread");
 // exp64, 29.9 so.  A bit table for binary16 (14336 values in 112 KB) costs as much
 // as 100000 terms to build, and its gain on longer rows (40 x 5, V = 152064: 32.9 / 29.2 us) is lost twice over where
 // a row's bulk lies near 0, outside it (32.8 / 59.9).
+//
+// Values below the range are the ordinary case: masks of a type's lowest value, or -1e9.  8 x 9 rows of 128255 with the last
+// five masked: 67.6 us (fp32) and 50.9 (bfloat16) where one such value asked for the second sweep, 27.2 and 21.0 so; nine
+// tenths of the row masked 69.7 and 74.9, 27.1 and 45.6; nothing masked 26.7 and 20.3.
 constexpr float kTabMaxS = 600.0f;
+constexpr double kSomeMass = 1e-238;      // e^-546: terms below e^-600, 2^31 of them, are less than an ulp beside it
 template <typename T> struct ExpTab {
   static constexpr bool kHas = false;
   static constexpr size_t kBytes = 0;
@@ -130,7 +136,7 @@ __device__ __forceinline__ double table_vec_sum_raw(const uint4& d, const double
 }
 // Every element of a vector directly; branch-free, so that a wave in which some lane comes here for every
 // vector (a row with many values outside the table) runs at the pace of the direct path and not at that of
-// a divergent loop.  flags: 1 = NaN or +inf, 2 = |s| beyond kTabMaxS
+// a divergent loop.  flags: as of run_sum, below
 template <typename T>
 __device__ __forceinline__ double table_vec_redo(const uint4& d, float rT, int& flags) {
   using TB = ExpTab<T>;
@@ -140,9 +146,8 @@ __device__ __forceinline__ double table_vec_redo(const uint4& d, float rT, int& 
   for (int e = 0; e < 8; ++e) {
     const uint32_t b = (w[e >> 1] >> ((e & 1) * 16)) & 0xFFFFu;
     const float sv = __fmul_rn(TB::widen(b), rT);
-    const bool neg_inf = b == (0x8000u | TB::kInf);
     flags |= ((b & 0x7FFFu) > TB::kInf || b == TB::kInf) ? 1 : 0;
-    flags |= (!neg_inf && fabsf(sv) > kTabMaxS) ? 2 : 0;
+    flags |= sv > kTabMaxS ? 2 : (sv < -kTabMaxS ? 4 : 0);
     s += exp64(double(sv));                                       // -inf gives exactly 0
   }
   return s;
@@ -155,7 +160,7 @@ __device__ __forceinline__ float max3_nan(float a, float b, float c) {      // v
 // synchronises; `half` as for build_exp_table); run_sum() gives the sum over a wave's run, of which every lane
 // holds kSegVecs vectors (vector i is vector vbase + 64 i of the row and counts if that is below nvec), and
 // raises flags: 1 = NaN or +inf among the elements, 2 = the row has to be swept by its maxima (which finds NaN
-// and +inf for itself).
+// and +inf for itself), 4 = so it has if the row turns out to hold nothing above the range's lower end.
 template <typename T> struct BitTerms {
   static constexpr bool kBits = true;
   static constexpr size_t kBytes = ExpTab<T>::kBytes;
@@ -190,8 +195,7 @@ template <typename T> struct PowTerms {
     for (int i = lo + threadIdx.x; i < hi; i += threads) t[i] = pow_entry(i);
   }
   // A term is made of max(s, -690), so that masked elements (-inf) need no branch: what they and other far ones
-  // add, 2e-300 each, is nothing beside any s >= -kTabMaxS.  A run without such an s is masked throughout (its
-  // sum is 0) or lies below the range.
+  // add, 2e-300 each, is nothing beside any s >= -kTabMaxS.  A run without such an s counts as 0.
   static __device__ __forceinline__ double run_sum(const uint4 (&q)[kSegVecs], uint32_t vbase, uint32_t nvec,
                                                    const double* table, float rT, int& flags) {
     constexpr int E = ElemTraits<T>::kPerVec;
@@ -215,20 +219,10 @@ template <typename T> struct PowTerms {
       acc += vbase + i * 64 < nvec ? s0 + s1 : 0.0;
     }
     flags |= top <= kTabMaxS ? 0 : 2;                   // NaN too
-    double sum = wave_sum_f64(acc);
-    if (sum < 1e-262) {                                 // (the same in all lanes; e^-600 is 2.7e-261)
-#pragma unroll
-      for (int i = 0; i < kSegVecs; ++i) {
-        uint4 w = q[i];
-        asm volatile("" : "+v"(w.x), "+v"(w.y), "+v"(w.z), "+v"(w.w));      // not to be done for every run
-        float v[E];
-        unpack<T>(w, v);
-#pragma unroll
-        for (int e = 0; e < E; ++e) flags |= v[e] > -INFINITY && vbase + i * 64 < nvec ? 2 : 0;
-      }
-      sum = 0.0;
-    }
-    return sum;
+    const double sum = wave_sum_f64(acc);
+    const bool below = sum < 1e-262;                    // (the same in all lanes; e^-600 is 2.7e-261)
+    flags |= below ? 4 : 0;
+    return below ? 0.0 : sum;
   }
 };
 
@@ -363,7 +357,8 @@ __device__ __forceinline__ void row_sweep(RowWork<T>& w, double* table, int half
   if (edge_lane) {
     edge_v = load_elem<T>(w.row, edge_index<T>(rs, lane));
     flags |= (edge_v != edge_v || edge_v == INFINITY) ? 1 : 0;
-    flags |= (edge_v > -INFINITY && fabsf(__fmul_rn(edge_v, rT)) > kTabMaxS) ? 2 : 0;
+    const float s = __fmul_rn(edge_v, rT);
+    flags |= s > kTabMaxS ? 2 : (s < -kTabMaxS ? 4 : 0);
   }
   if (n_runs > 0) {
     const uint32_t last_vec = uint32_t(rs.nvec - 1), nvec = uint32_t(rs.nvec);
@@ -416,8 +411,14 @@ __device__ __forceinline__ void row_sweep(RowWork<T>& w, double* table, int half
   if (lane == 0 && flags) atomicOr(&sh.flags, flags);
   __syncthreads();
   w.smax = 0.0f;
-  if (sh.flags & 2) {
-    // |s| beyond kTabMaxS: the row again, in two passes, referenced to its maximum
+  const int seen = __builtin_amdgcn_readfirstlane(sh.flags);
+  if (seen & 6) {
+    // beyond the range: the row again, in two passes, referenced to its maximum, if it has to be
+    if (!(seen & 2)) {
+      if (ballot(tid < w.n_items && sh.items[tid] > kSomeMass) != 0 && lane == 0) atomicOr(&sh.flags, 8);
+      __syncthreads();
+      if (__builtin_amdgcn_readfirstlane(sh.flags) & 8) return;
+    }
     float vmax = -INFINITY;
     int bad = 0;
     for (int64_t vi = tid; vi < rs.nvec; vi += kRowThreads) {

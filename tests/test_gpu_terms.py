@@ -152,3 +152,69 @@ def test_path_on_either_side_of_the_dispatch(tslt, dtype, B, expansion, V):
             # fp64 sums of terms within 1.5 ulp by either table, rounded to fp32
             np.testing.assert_allclose(path[k][b][on], out[k][b][on], rtol=2.5e-7)
     assert len(lengths) > 1 and (path["status"] == 0).all()
+
+
+def mask_rows(t, low):
+    """Rows masked with a finite value far below the range, one way per sequence or node (t [n, V] fp32)."""
+    V = t.shape[1]
+    t[0, -5:] = low                            # the vocabulary's padding
+    t[1, V // 10:] = low                       # whole runs
+    t[2, ::97] = low                           # a few elements of nearly every vector's neighbourhood
+    t[3, :V // 2] = -float("inf")              # masks of both kinds
+    t[3, V // 2:V - 40] = low
+    t[4] = low                                 # nothing but masks: every token alike
+    t[5, :V - 9] = low                         # ... and a few tokens that are not in whole vectors
+    t[5, V - 9:] -= 700.0                      # below the range as well: the row by its maximum
+    return t
+
+
+@pytest.mark.parametrize("dtype,V,B", [("f32", 9001, 7), ("bf16", 9001, 7), ("f16", 9001, 7), ("f32", 2003, 300), ("bf16", 2003, 300),
+                                       ("f16", 2003, 300)])
+def test_chain_finite_masks(tslt, dtype, V, B):
+    low = -60000.0 if dtype == "f16" else -1.0e9
+    w = W.scaled(W.WORKLOADS["chain_topk"], B=B, V=V, gamma=2, dtype=dtype, T=0.9, top_k=16, k_cap=16)
+    chain = W.make_chain(w, 47, DEV)
+    target = chain["target"].float()
+    target[:6, 0] = mask_rows(target[:6, 0].clone(), low)
+    target[:6, 2] = mask_rows(target[:6, 2].clone(), low)       # the bonus rows
+    chain["target"] = target.to(W.torch_dtype(dtype))
+    u_acc = chain["u_accept"].clone()
+    u_acc[:, 0] = 0.9995
+    chain["u_accept"] = u_acc
+    ref = P.oracle_chain(P.to_np(chain["draft"]), P.to_np(chain["target"]), w.T, w.top_k, w.top_p, w.k_cap,
+                         P.to_np(chain["u_sample"]), P.to_np(u_acc), P.to_np(chain["u_resample"]))
+    out = tslt.verify(chain["target"], w.T, t32(ref["q_idx"]), t32(ref["q_logit"]), t32(ref["q_count"]), t32(ref["tokens"]),
+                      u_acc, chain["u_resample"])
+    # the bonus rows: the same positions with nearly everything accepted (a token whose p is 0 is not)
+    u0 = torch.full_like(u_acc, 1e-3)
+    ref0 = P.oracle_chain(P.to_np(chain["draft"]), P.to_np(chain["target"]), w.T, w.top_k, w.top_p, w.k_cap,
+                          P.to_np(chain["u_sample"]), P.to_np(u0), P.to_np(chain["u_resample"]))
+    out0 = tslt.verify(chain["target"], w.T, t32(ref0["q_idx"]), t32(ref0["q_logit"]), t32(ref0["q_count"]), t32(ref0["tokens"]),
+                       u0, chain["u_resample"])
+    torch.cuda.synchronize()
+    for o, r in ((out, ref), (out0, ref0)):
+        r["verify"]["beta_hat"] = r["verify"]["beta_hat"].astype(np.float32)
+        print(P.compare_verify(o, r["verify"], label=f"{dtype} {V} {B}"), r["verify"]["accept_len"][:7])
+
+
+@pytest.mark.parametrize("dtype,B", [("f32", 2), ("bf16", 2), ("f16", 2), ("f32", 60), ("bf16", 60), ("f16", 60)])
+def test_tree_finite_masks(tslt, dtype, B):
+    """Leaves and non-leaf nodes; 60 trees of 10 nodes are walked node after node."""
+    low = -60000.0 if dtype == "f16" else -1.0e9
+    w = W.scaled(W.WORKLOADS["tree"], B=B, V=3001, expansion=(3, 2), top_k=8, k_cap=8, dtype=dtype, T=0.9)
+    tree = W.make_tree(w, 53, DEV)
+    target = tree["target"].float()
+    target[0, 4:10] = mask_rows(target[0, 4:10].clone(), low)
+    rows = mask_rows(target[1, :6].clone(), low)
+    target[1, :4] = rows[[0, 1, 5, 4]]
+    target[0, :4] = rows[[2, 3, 4, 5]]
+    tree["target"] = target.to(W.torch_dtype(dtype))
+    ref = P.oracle_tree(P.to_np(tree["draft"]), P.to_np(tree["target"]), w.T, w.top_k, w.top_p, w.k_cap, w.expansion,
+                        P.to_np(tree["u_sample"]), P.to_np(tree["u_accept"]), P.to_np(tree["u_resample"]), False, False)
+    args = [tree["target"], w.T, w.expansion, t32(ref["q_idx"]), t32(ref["q_logit"]), t32(ref["q_count"]), t32(ref["cands"]),
+            tree["u_accept"], tree["u_resample"]]
+    out = tslt.verify_tree(*args, all_nodes=True)
+    path = tslt.verify_tree(*args, all_nodes=False)
+    torch.cuda.synchronize()
+    print(P.compare_tree(out, ref, w.expansion, all_nodes=True, label=f"{dtype} {B}"))
+    assert torch.equal(path["seq"], out["seq"]) and torch.equal(path["len"], out["len"])
