@@ -283,7 +283,7 @@ __device__ __forceinline__ int wave_or_i32(int v) { return last_lane_i32(wave_sc
 // Small per-block scratch for reductions and scans; one instance lives in static LDS.
 // `NW` is the number of waves of the workgroup that calls the helpers.
 struct BlockScratch {
-  double d[16];
+  double d[24];
   float f[16];
   int i[16];
 };

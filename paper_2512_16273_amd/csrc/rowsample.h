@@ -252,7 +252,7 @@ struct RowShared {
   float wave_max[kRowWaves];
   double target, before, none;
   double removed;                       // q_hat of the candidates that have left the proposal
-  int flags, next_run, item, n_corr, pick, last, cmd, st;
+  int flags, next_run, item, n_corr, pick, last, cmd, st, fetched;
 };
 
 template <typename T> struct RowWork {
@@ -331,39 +331,40 @@ template <typename T> __device__ __forceinline__ void row_store_set(const RowWor
   }
 }
 
-// The masses of the row's items, referenced to w.smax (0, or the row's maximum where |s| is too large for that),
-// and sh.flags (bit 0: NaN or +inf).  A wave takes run `wave` first and then whichever run is next (a counter in
+// The masses of the row's items, referenced to 0: of its runs run0 .. run1 - 1, and with `ends` of the elements before and
+// after its aligned body; and sh.flags, as of run_sum.  A wave takes run run0 + `wave` first and then whichever run is next (a counter in
 // LDS), so that the waves end together.  Every request of the loop is unconditional (a vector past the row's end
 // is read from the row's last vector and its sum dropped; a run past the last is the last one again, to no
 // effect): with requests inside branches the number in flight is not known where a wait is placed, and the wait
 // for the current run would wait for the run requested ahead as well.  While the first requests travel the terms'
 // table is made: all of it (half -1), its second half (1) or nothing (-2).
+// The elements outside the aligned body, one per lane of the last wave; their masses, referenced to m.
+template <typename T> __device__ __forceinline__ bool row_edge_lane(const RowWork<T>& w) {
+  return wave_id() == kRowWaves - 1 && lane_id() < w.rs.head + w.rs.tail;
+}
+template <typename T> __device__ __forceinline__ void row_edges(const RowWork<T>& w, float edge_v, float m, RowShared& sh) {
+  const int lane = lane_id();
+  const double t = row_edge_lane(w) ? exp64(double(__fmul_rn(edge_v, w.rT)) - double(m)) : 0.0;
+  const double head = wave_sum_f64(lane < w.rs.head ? t : 0.0), tail = wave_sum_f64(lane < w.rs.head ? 0.0 : t);
+  if (lane == 0) { sh.items[0] = head; sh.items[w.n_items - 1] = tail; }
+}
 template <typename T, typename Terms>
-__device__ __forceinline__ void row_sweep(RowWork<T>& w, double* table, int half, RowShared& sh) {
-  constexpr int E = ElemTraits<T>::kPerVec;
-  const int tid = threadIdx.x, lane = lane_id(), wave = wave_id();
+__device__ __forceinline__ void row_pass(RowWork<T>& w, double* table, int half, int run0, int run1, bool ends, RowShared& sh) {
+  const int lane = lane_id(), wave = wave_id();
   const RowSplit& rs = w.rs;
-  const int n_runs = w.n_runs, n_edge = rs.head + rs.tail;
   const float rT = w.rT;
   int flags = 0;
-  // the elements outside the aligned body: one per lane of the last wave
-  const bool edge_lane = wave == kRowWaves - 1 && lane < n_edge;
   float edge_v = -INFINITY;
-  auto edges = [&](float m) {                // their masses; called by the whole last wave
-    const double t = edge_lane ? exp64(double(__fmul_rn(edge_v, rT)) - double(m)) : 0.0;
-    const double head = wave_sum_f64(lane < rs.head ? t : 0.0), tail = wave_sum_f64(lane < rs.head ? 0.0 : t);
-    if (lane == 0) { sh.items[0] = head; sh.items[w.n_items - 1] = tail; }
-  };
-  if (edge_lane) {
+  if (ends && row_edge_lane(w)) {
     edge_v = load_elem<T>(w.row, edge_index<T>(rs, lane));
     flags |= (edge_v != edge_v || edge_v == INFINITY) ? 1 : 0;
     const float s = __fmul_rn(edge_v, rT);
     flags |= s > kTabMaxS ? 2 : (s < -kTabMaxS ? 4 : 0);
   }
-  if (n_runs > 0) {
+  if (run0 < run1) {
     const uint32_t last_vec = uint32_t(rs.nvec - 1), nvec = uint32_t(rs.nvec);
     auto request = [&](int run, uint4 (&q)[kSegVecs]) {
-      const uint32_t vbase = uint32_t(run < n_runs ? run : n_runs - 1) * kRunVecs + lane;
+      const uint32_t vbase = uint32_t(run < run1 ? run : run1 - 1) * kRunVecs + lane;
 #pragma unroll
       for (int i = 0; i < kSegVecs; ++i) {
         const uint32_t vi = vbase + i * 64;
@@ -372,27 +373,27 @@ __device__ __forceinline__ void row_sweep(RowWork<T>& w, double* table, int half
     };
     auto consume = [&](int run, const uint4 (&q)[kSegVecs]) {
       const double run_sum = Terms::run_sum(q, uint32_t(run) * kRunVecs + lane, nvec, table, rT, flags);
-      if (lane == 0 && run < n_runs) sh.items[1 + run] = run_sum;
+      if (lane == 0 && run < run1) sh.items[1 + run] = run_sum;
     };
     auto next = [&]() {
       int nr = 0;
       if (lane == 0) nr = atomicAdd(&sh.next_run, 1);
-      return __builtin_amdgcn_readfirstlane(nr);
+      return run0 + __builtin_amdgcn_readfirstlane(nr);
     };
     uint4 d[kSegVecs], dn[kSegVecs];
-    int cur = wave;
+    int cur = run0 + wave;
     request(cur, d);
     if (half > -2) Terms::build(table, rT, kRowThreads, half);
     __syncthreads();                    // the table is complete
     // the first run apart: behind it the set entry's target logit is requested, whose index has arrived by then
     int nxt = next();
     request(nxt, dn);
-    if (cur < n_runs) consume(cur, d);
+    if (cur < run1) consume(cur, d);
     row_gather(w);
 #pragma unroll
     for (int i = 0; i < kSegVecs; ++i) d[i] = dn[i];
     cur = nxt;
-    while (cur < n_runs) {
+    while (cur < run1) {
       nxt = next();
       request(nxt, dn);
       consume(cur, d);
@@ -406,10 +407,21 @@ __device__ __forceinline__ void row_sweep(RowWork<T>& w, double* table, int half
     row_gather(w);
   }
   row_store_set(w, 0.0f, sh);
-  if (wave == kRowWaves - 1) edges(0.0f);
+  if (ends && wave == kRowWaves - 1) row_edges(w, edge_v, 0.0f, sh);
   flags = wave_or_i32(flags);
   if (lane == 0 && flags) atomicOr(&sh.flags, flags);
   __syncthreads();
+}
+// The masses of all the row's items, referenced to w.smax (0, or the row's maximum where it needs that), and sh.flags
+// (bit 0: NaN or +inf).
+template <typename T, typename Terms>
+__device__ __forceinline__ void row_sweep(RowWork<T>& w, double* table, int half, RowShared& sh) {
+  constexpr int E = ElemTraits<T>::kPerVec;
+  row_pass<T, Terms>(w, table, half, 0, w.n_runs, true, sh);
+  const int tid = threadIdx.x, lane = lane_id(), wave = wave_id();
+  const RowSplit& rs = w.rs;
+  const int n_runs = w.n_runs;
+  const float rT = w.rT;
   w.smax = 0.0f;
   const int seen = __builtin_amdgcn_readfirstlane(sh.flags);
   if (seen & 6) {
@@ -430,7 +442,9 @@ __device__ __forceinline__ void row_sweep(RowWork<T>& w, double* table, int half
         vmax = fmaxf(vmax, v[e]);
       }
     }
-    if (edge_lane) {
+    float edge_v = -INFINITY;
+    if (row_edge_lane(w)) {
+      edge_v = load_elem<T>(w.row, edge_index<T>(rs, lane));
       bad |= (edge_v != edge_v || edge_v == INFINITY) ? 1 : 0;
       vmax = fmaxf(vmax, edge_v);
     }
@@ -456,11 +470,27 @@ __device__ __forceinline__ void row_sweep(RowWork<T>& w, double* table, int half
         acc = wave_sum_f64(acc);
         if (lane == 0) sh.items[1 + run] = acc;
       }
-      if (wave == kRowWaves - 1) edges(smax);
+      if (wave == kRowWaves - 1) row_edges(w, edge_v, smax, sh);
       row_store_set(w, smax, sh);
     }
     __syncthreads();
   }
+}
+
+// The row as row_sweep leaves it, from masses that other workgroups have made of it (row_pass, then stored; NaN where a
+// part met something that asks for a sweep by the row's maximum).  sh.fetched is 0, as published by a barrier.
+template <typename T, typename Terms>
+__device__ __forceinline__ void row_fetch(RowWork<T>& w, const double* items, double* table, RowShared& sh) {
+  const int tid = threadIdx.x, lane = lane_id();
+  const double mass = items[tid < w.n_items ? tid : 0];
+  row_gather(w);
+  if (tid < w.n_items) sh.items[tid] = mass;
+  w.smax = 0.0f;
+  row_store_set(w, 0.0f, sh);
+  const int seen = (ballot(mass != mass) != 0 ? 1 : 0) | (ballot(mass > kSomeMass) != 0 ? 2 : 0);
+  if (lane == 0 && seen) atomicOr(&sh.fetched, seen);
+  __syncthreads();
+  if (__builtin_amdgcn_readfirstlane(sh.fetched) != 2) row_sweep<T, Terms>(w, table, -1, sh);
 }
 
 // Passes over the set's entries by one wave, four per lane at a time: load(k, i) for all four first, so that their

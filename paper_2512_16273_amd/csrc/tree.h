@@ -7,7 +7,9 @@
 // sums of that pass serve the draw as well (rowsample.h).  Bound by the vector units (fp32: 19 instructions an element,
 // 5.1 TB/s) or the LDS (bfloat16).  Two fp32 trees of 1365 nodes, V = 151936, every node: 546 us as a pass for the
 // tests, a sweep, a finish and two more launches, 330 so; the path of 64 binary16 trees <2,2,2>, V = 32000: 52 and 39.7.
+// Paths over long rows take the tests on the way from an fp32 pass (rowops.h) and sweep the last node alone.
 #pragma once
+#include "rowops.h"
 #include "rowsample.h"
 
 namespace tslt {
@@ -43,13 +45,20 @@ struct TreeParams {
   int32_t* node_slot;     // [B, n_nodes] accepted child number or -1
   int32_t* node_token;    // [B, n_nodes] the node's output
   int32_t* node_status;   // [B, n_nodes]
+  // (path only, tree_quick_kernel first)
+  int32_t* walk_node;     // [B] where the quick walk stopped
+  int32_t* walk_status;   // [B] status bits of the nodes before it
+  double* items;          // [B, items_stride] masses of that node's row
+  int64_t items_stride;
+  int parts;              // workgroups that share that row
   int all_nodes;
   int n_eval;             // nodes of a tree that tree_node_kernel evaluates: whole layers from the root
   int n_eval_layers;
 };
 
-// (More than the kernels use: the size that callers have been told all along, so that a workspace kept from an
-// earlier version and one sized by this one are the same.)
+// (Evaluating every node uses the node arrays alone.  The rest, two words a tree and the masses of a row's items, is for the
+// path; with node outputs it is still asked for once a node: the size that callers have been told all along, so that a
+// workspace kept from an earlier version and one sized by this one are the same.)
 inline size_t tree_workspace_bytes(int64_t B, int64_t n_nodes, int64_t V, bool all_nodes) {
   const size_t n_seg = size_t(row_segments(V));
   const size_t tasks = all_nodes ? size_t(n_nodes) : 1;
@@ -63,7 +72,11 @@ inline void tree_carve_workspace(TreeParams& p, void* ws) {
   p.node_state = reinterpret_cast<int32_t*>(w); w += per;
   p.node_slot = reinterpret_cast<int32_t*>(w); w += per;
   p.node_token = reinterpret_cast<int32_t*>(w); w += per;
-  p.node_status = reinterpret_cast<int32_t*>(w);
+  p.node_status = reinterpret_cast<int32_t*>(w); w += per;
+  p.walk_node = reinterpret_cast<int32_t*>(w); w += align256(size_t(p.B) * 4);
+  p.walk_status = reinterpret_cast<int32_t*>(w); w += align256(size_t(p.B) * 4);
+  p.items = reinterpret_cast<double*>(w);
+  p.items_stride = int64_t(row_segments(p.V)) * kSubChunks + 2;
 }
 
 template <typename T> __device__ __forceinline__ const void* tree_row(const TreeParams& p, int64_t b, int node) {
@@ -85,11 +98,11 @@ __device__ __forceinline__ int tree_first_child(const TreeParams& p, int node, i
 // accepted, the draw of its output (a leaf: of its target distribution).  Writes the ratios and rates of the
 // candidates it tested; returns the state (0 sampled, 1 a child accepted, 2 row unusable), the accepted child in
 // `slot`, the output in `token` and the status bits in `st` (both as the first wave has them).  Unless a child was
-// accepted the terms' table is used up.
+// accepted the terms' table is used up.  `items`: the row's masses, where they have been made already (else null).
 // ---------------------------------------------------------------------------------------------
 template <typename T, typename Terms>
 __device__ __forceinline__ int tree_node(const TreeParams& p, int64_t b, int node, double* table, bool build, RowShared& sh,
-                                         int& slot, int& token, int& st) {
+                                         int& slot, int& token, int& st, const double* items = nullptr) {
   const int lane = lane_id();
   const bool leaf = node >= p.n_int;
   const int64_t row = b * p.n_int + (leaf ? 0 : node);
@@ -103,7 +116,8 @@ __device__ __forceinline__ int tree_node(const TreeParams& p, int64_t b, int nod
   const int64_t c0 = leaf ? 0 : b * (p.n_nodes - 1) + tree_first_child(p, node, layer) - 1;
   const int my_cand = p.cand_tokens[c0 + (lane < k ? lane : 0)];
   const float my_u = p.u_accept[c0 + (lane < k ? lane : 0)];
-  row_sweep<T, Terms>(w, table, build ? -1 : -2, sh);
+  if (items != nullptr) row_fetch<T, Terms>(w, items, table, sh);
+  else row_sweep<T, Terms>(w, table, build ? -1 : -2, sh);
   token = -1;
   st = 0;
   float my_ratio = NAN, my_beta = NAN;                              // NaN if the candidate is never tested
@@ -249,30 +263,161 @@ __global__ __launch_bounds__(64) void tree_walk_kernel(const TreeParams p) {
 }
 
 // ---------------------------------------------------------------------------------------------
-// Only the verified path is wanted: one workgroup per tree walks through the layers that have been evaluated (none or
-// the first few), then from node to node, running Algorithm 5 at each node it reaches, descending into the accepted
-// child and drawing the output of the node it stops at, so that a target row below those layers is read only where
-// it counts.  Uniforms are indexed by node, so the result is the one that evaluating every node gives.  (kHead: layers
-// have been evaluated.  The walk through them is not compiled into the other form, whose registers it costs.)
+// The quick walk, for paths only: one workgroup per tree (of 512 threads, or 256 where trees outnumber compute units) runs
+// Algorithm 5 from the root on as long as a candidate is accepted, on rowops.h's pass of fp32 terms.  It stops at a leaf,
+// at a node that accepts none (whose output has to be drawn) and wherever the fp32 terms have nothing to say: an unusable
+// row or set, or a rejection that leaves less than kQuickResidual.  From there on the fp64 kernels decide for themselves.
 // ---------------------------------------------------------------------------------------------
-template <typename T, typename Terms, bool kHead>
+constexpr double kQuickResidual = 0x1p-10;
+template <typename T, int NT>
+__device__ __forceinline__ int tree_quick_node(const TreeParams& p, int64_t b, int node, int layer, VerifyShared& sh, int& st) {
+  constexpr int kPer = 1024 / NT;
+  const int tid = threadIdx.x;
+  const int k = p.expansion[layer];
+  const int64_t c0 = b * (p.n_nodes - 1) + tree_first_child(p, node, layer) - 1;
+  const void* row = tree_row<T>(p, b, node);
+  const RowSplit rs = split_row<T>(row, p.V);
+  const int64_t r = b * p.n_int + node;
+  int count = p.q_count[r];
+  count = count < 0 ? 0 : (count > p.k_cap ? p.k_cap : count);
+  double a_s[kPer], q_s[kPer], p_out;
+  int yi[kPer];
+  bool ok;
+  eval_row_on_set<T, true, NT>(row, rs, p.V, p.rT, p.k2, p.q_idx + size_t(r) * p.k_cap, p.q_logit + size_t(r) * p.k_cap, count, sh,
+                           a_s, q_s, yi, p_out, ok, st);
+  if (!ok) return -1;
+  double c = 1.0, qscale = 1.0, removed = 0.0;       // the stage's proposal is q_s * qscale
+  for (int i = 0; i < k; ++i) {
+    const int x = p.cand_tokens[c0 + i];
+    if (x < 0) continue;                             // absent candidate (block-uniform)
+    if (tid == 0) { sh.bcast_d[0] = -1.0; sh.bcast_d[1] = 0.0; sh.bcast_i[0] = 0; }
+    __syncthreads();
+    double shared = 0.0, part = 0.0;
+    int mine = -1;
+#pragma unroll
+    for (int q = 0; q < kPer; ++q) {
+      const double qq = q_s[q] * qscale, d = a_s[q] - qq > 0.0 ? a_s[q] - qq : 0.0;
+      shared += yi[q] >= 0 ? a_s[q] - d : 0.0;       // min(a, q)
+      part += yi[q] >= 0 ? d : 0.0;
+      if (yi[q] == x && q_s[q] > 0.0 && atomicCAS(&sh.bcast_i[0], 0, 1) == 0) {
+        sh.bcast_d[0] = a_s[q] / qq;
+        sh.bcast_d[1] = q_s[q];
+        mine = q;
+      }
+    }
+    double none = 0.0;
+    block_sum3_f64<NT / 64>(shared, part, none, sh.red);      // (and its barriers)
+    const double ratio = sh.bcast_d[0], q_x = sh.bcast_d[1];
+    const bool found = sh.bcast_i[0] != 0;
+    __syncthreads();
+    if (!found) st |= 4;
+    if (tid == 0) {
+      if (p.out_ratio) p.out_ratio[c0 + i] = float(ratio);
+      if (p.out_beta) p.out_beta[c0 + i] = float(shared);    // Section 4.3's beta^(i)
+    }
+    const double bound = ratio < 1.0 ? ratio : 1.0;
+    if (found && double(p.u_accept[c0 + i]) < bound) return i;
+    const double Z = part + c * p_out;
+    if (!(Z > kQuickResidual * c)) return -1;
+    const double inv_Z = 1.0 / Z;
+#pragma unroll
+    for (int q = 0; q < kPer; ++q) {
+      const double d = a_s[q] - q_s[q] * qscale;
+      a_s[q] = yi[q] >= 0 && d > 0.0 ? d * inv_Z : 0.0;
+      if (p.wor && found && q == mine) q_s[q] = 0.0;         // drawn without replacement: x leaves the urn
+    }
+    c *= inv_Z;
+    if (p.wor && found) {
+      removed += q_x;
+      const double rest = 1.0 - removed;
+      qscale = rest > 0.0 ? 1.0 / rest : 0.0;
+    }
+  }
+  return -1;
+}
+template <typename T, int NT>
+__global__ __launch_bounds__(NT) void tree_quick_kernel(const TreeParams p) {
+  __shared__ VerifyShared sh;
+  const int tid = threadIdx.x;
+  const int64_t b = blockIdx.x;
+  for (int i = tid; i < p.n_nodes - 1; i += NT) {
+    if (p.out_ratio) p.out_ratio[size_t(b) * (p.n_nodes - 1) + i] = NAN;
+    if (p.out_beta) p.out_beta[size_t(b) * (p.n_nodes - 1) + i] = NAN;
+  }
+  __syncthreads();
+  int node = 0, layer = 0, st_all = 0;
+  while (node < p.n_int) {
+    int st;
+    const int slot = tree_quick_node<T, NT>(p, b, node, layer, sh, st);
+    if (slot < 0) break;                     // (its ratios are written again by the node's evaluation)
+    st_all |= st;
+    node = tree_first_child(p, node, layer) + slot;
+    if (tid == 0) p.out_seq[size_t(b) * (p.depth + 1) + layer] = p.cand_tokens[b * (p.n_nodes - 1) + node - 1];
+    ++layer;
+  }
+  if (tid == 0) {
+    p.walk_node[b] = node;
+    p.walk_status[b] = st_all;
+  }
+}
+// The row of the node at which it stopped, shared by p.parts workgroups: the masses of its items.
+template <typename T, typename Terms>
+__global__ __launch_bounds__(kRowThreads, kAlone) void tree_part_kernel(const TreeParams p) {
+  __shared__ RowShared sh;
+  extern __shared__ __align__(16) unsigned char dyn_lds[];
+  const int64_t b = blockIdx.x / p.parts;
+  const int part = int(blockIdx.x - b * p.parts);
+  RowWork<T> w;
+  row_open<T>(w, tree_row<T>(p, b, p.walk_node[b]), p.V, p.rT, sh);
+  w.count = 0;
+  w.y = -1;
+  w.ql = w.ql0 = 0.0f;
+  const int per = (w.n_runs + p.parts - 1) / p.parts;
+  const int run0 = part * per, run1 = run0 + per < w.n_runs ? run0 + per : w.n_runs;
+  row_pass<T, Terms>(w, reinterpret_cast<double*>(dyn_lds), -1, run0, run1, part == 0, sh);
+  double* out = p.items + b * p.items_stride;
+  const bool broken = (sh.flags & 3) != 0;
+  const double bad = __longlong_as_double(0x7FF8000000000000ll);
+  for (int i = run0 + threadIdx.x; i < run1; i += kRowThreads) out[1 + i] = broken ? bad : sh.items[1 + i];
+  if (part == 0 && threadIdx.x < 2) {
+    const int i = threadIdx.x == 0 ? 0 : w.n_items - 1;
+    out[i] = broken ? bad : sh.items[i];
+  }
+}
+
+// ---------------------------------------------------------------------------------------------
+// Only the verified path is wanted: one workgroup per tree takes up the walk where it has got to, then goes from node to
+// node, running Algorithm 5 at each node it reaches, descending into the accepted child and drawing the output of the
+// node it stops at, so that a target row is read only where it counts.  Uniforms are indexed by node, so the result is
+// the one that evaluating every node gives.  (The walk through evaluated layers is not compiled into the other forms,
+// whose registers it costs.)
+// ---------------------------------------------------------------------------------------------
+enum { kFromRoot = 0, kFromHead = 1, kFromQuick = 2 };      // nothing done yet; the first layers evaluated; the quick walk
+template <typename T, typename Terms, int kFrom>
 __global__ __launch_bounds__(kRowThreads) void tree_path_kernel(const TreeParams p) {
   __shared__ RowShared sh;
   extern __shared__ __align__(16) unsigned char dyn_lds[];
   const int tid = threadIdx.x;
   const int64_t b = blockIdx.x;
-  int node = 0, layer = 0, len = 0, st_all = 0, token = -1, first = 0;
+  int node = 0, layer = 0, len = 0, st_all = 0, token = -1;
   bool done = false;
-  if constexpr (kHead) {
+  const double* items = nullptr;
+  if constexpr (kFrom == kFromHead) {
     __shared__ TreeWalk walk;
     if (tid == 0) tree_walk(p, b, walk);
     __syncthreads();
     tree_clear_others(p, b, walk);
-    node = first = walk.node;
+    node = walk.node;
     layer = walk.layer;
     len = walk.len;
     st_all = walk.status;
     done = walk.done;
+  } else if constexpr (kFrom == kFromQuick) {
+    node = p.walk_node[b];
+    layer = len = tree_layer(p, node);
+    st_all = p.walk_status[b];
+    if (p.parts > 1) items = p.items + b * p.items_stride;
+    if (tid == 0) sh.fetched = 0;
   } else {
     for (int i = tid; i < p.n_nodes - 1; i += kRowThreads) {
       if (p.out_ratio) p.out_ratio[size_t(b) * (p.n_nodes - 1) + i] = NAN;
@@ -281,9 +426,12 @@ __global__ __launch_bounds__(kRowThreads) void tree_path_kernel(const TreeParams
   }
   __syncthreads();
   int32_t* seq = p.out_seq + size_t(b) * (p.depth + 1);
+  bool build = true;                         // the terms' table is still to be made
   while (!done) {
     int slot, st;
-    const int state = tree_node<T, Terms>(p, b, node, reinterpret_cast<double*>(dyn_lds), node == first, sh, slot, token, st);
+    const int state = tree_node<T, Terms>(p, b, node, reinterpret_cast<double*>(dyn_lds), build, sh, slot, token, st, items);
+    build = items != nullptr;
+    items = nullptr;
     st_all |= st;
     if (tid == 0) seq[len] = token;
     ++len;
@@ -316,8 +464,31 @@ template <typename T> inline int layers_at_once(const TreeParams& p) {
   return l >= 2 && 2 * l >= p.depth + 1 ? l : 0;
 }
 
+// Whether a path that does not fit the chip at once is walked quickly first.  With terms from the bit table a node's fp64
+// sweep costs no more than the fp32 pass; the others' is bound by the vector units (19 instructions a term), and one
+// compute unit to a tree takes them all.  So: long rows of several layers; where trees outnumber compute units, shorter
+// ones too.  Where more than half of the layers fit the chip at once they are evaluated so (unless few layers of the
+// longest 16-bit rows).  us a call, in fp64 node by node (head layers at once from 100000 on) / quick walk:
+//   binary16  64 <4,2> 64000 41.7 / 43.4, 99968 57.4 / 47;  64 <2,2,2> 48000 45.7 / 43.4, 64000 54.5 / 48, 152064 81.9 / 68;
+//             20 <4,2,2,1> 256000 179.8 / 102;  12 <4,4,4> 152064 65.3 / 71.4, 256000 103 / 84;  8 <2,2,2,2,2,2> 256000 107 / 139;
+//             300 <2,2,2> 32000 56.6 / 58.6, 64000 84.3 / 82.9;  512 <1,1,1,1> 16000 63.4 / 56.5, 32000 84.9 / 69
+//   fp32      64 <2,2,2> 64000 50.8 / 51.5, 99968 70.3 / 61;  128 <2,2,2> 99968 70.2 / 72.1;  128 <3,3> 152064 74.2 / 71.3;
+//             512 <1,1,1,1> 16000 62.4 / 60.1, 32000 85.7 / 77.9;  400 <4,2> 64000 79.1 / 81.7, 99968 111.9 / 105.4
+// Against the walk of fp64 sums the ratios' error stays what it was (2.4e-8 to 4.3e-8, the outputs' rounding).
+template <typename T, typename Terms> inline bool quick_walk(const TreeParams& p, int layers_first) {
+  if (Terms::kBits || p.depth < 2) return false;
+  const int64_t cus = compute_units();
+  if (ElemTraits<T>::kBytes == 2) {
+    if (2 * layers_first > p.depth + 1) return p.V >= 200000 && p.depth <= 3;
+    return p.V >= (p.B >= 2 * cus ? 12000 : (2 * p.B >= 3 * cus ? 32000 : (p.depth > 2 ? 64000 : 80000)));
+  }
+  if (2 * layers_first > p.depth + 1) return false;
+  return p.V >= (p.B >= 2 * cus ? 32000 : (p.B > cus || 4 * p.B <= cus ? 96000 : 150000));
+}
 template <typename T, typename Terms> hipError_t launch_verify_tree_with(TreeParams p, hipStream_t s) {
   p.n_eval_layers = p.all_nodes ? p.depth + 1 : layers_at_once<T>(p);
+  const bool quick = p.n_eval_layers <= p.depth && quick_walk<T, Terms>(p, p.n_eval_layers);
+  if (quick) p.n_eval_layers = 0;
   p.n_eval = p.offsets[p.n_eval_layers];
   hipError_t e = hipSuccess;
   if (p.n_eval > 0) {
@@ -327,9 +498,28 @@ template <typename T, typename Terms> hipError_t launch_verify_tree_with(TreePar
                        dim3(kRowThreads), Terms::kBytes, s, p);
     if ((e = hipGetLastError()) != hipSuccess) return e;
   }
-  if (p.n_eval == 0) hipLaunchKernelGGL((tree_path_kernel<T, Terms, false>), dim3(unsigned(p.B)), dim3(kRowThreads), Terms::kBytes, s, p);
-  else if (p.n_eval_layers <= p.depth) hipLaunchKernelGGL((tree_path_kernel<T, Terms, true>), dim3(unsigned(p.B)), dim3(kRowThreads), Terms::kBytes, s, p);
-  else hipLaunchKernelGGL(tree_walk_kernel, dim3(unsigned(p.B)), dim3(64), 0, s, p);
+  auto walk = [&](auto fn) {
+    hipLaunchKernelGGL(fn, dim3(unsigned(p.B)), dim3(kRowThreads), Terms::kBytes, s, p);
+    return hipGetLastError();
+  };
+  if constexpr (!Terms::kBits) {
+    if (quick) {
+      if (p.B <= compute_units()) hipLaunchKernelGGL((tree_quick_kernel<T, 512>), dim3(unsigned(p.B)), dim3(512), 0, s, p);
+      else hipLaunchKernelGGL((tree_quick_kernel<T, 256>), dim3(unsigned(p.B)), dim3(256), 0, s, p);
+      if ((e = hipGetLastError()) != hipSuccess) return e;
+      // as many workgroups to a row as fill the chip, a run for every wave at least
+      const int64_t runs = p.V / (ElemTraits<T>::kPerVec * kRunVecs) + 1;
+      p.parts = int(std::max<int64_t>(1, std::min<int64_t>(compute_units() / p.B, (runs + kRowWaves - 1) / kRowWaves)));
+      if (p.parts > 1) {
+        hipLaunchKernelGGL((tree_part_kernel<T, Terms>), dim3(unsigned(p.B * p.parts)), dim3(kRowThreads), Terms::kBytes, s, p);
+        if ((e = hipGetLastError()) != hipSuccess) return e;
+      }
+      return walk(tree_path_kernel<T, Terms, kFromQuick>);
+    }
+  }
+  if (p.n_eval == 0) return walk(tree_path_kernel<T, Terms, kFromRoot>);
+  if (p.n_eval_layers <= p.depth) return walk(tree_path_kernel<T, Terms, kFromHead>);
+  hipLaunchKernelGGL(tree_walk_kernel, dim3(unsigned(p.B)), dim3(64), 0, s, p);
   return hipGetLastError();
 }
 template <typename T> hipError_t launch_verify_tree(const TreeParams& p, hipStream_t s) {

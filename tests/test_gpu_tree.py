@@ -225,3 +225,76 @@ def test_tree_path_over_rows_with_and_without_a_whole_vector(tslt, dtype, V):
     torch.cuda.synchronize()
     print(P.compare_tree(out, ref, w.expansion, label="tiny"), np.bincount(ref["verify"]["len"]))
     P.compare_tree({k: path_only[k] for k in ("seq", "len")}, ref, w.expansion, all_nodes=False, label="tiny, path only")
+
+
+@pytest.mark.parametrize("dtype,B,expansion,V,rule", [
+    ("f16", 60, (2, 2, 2), 64003, False),      # a row shared by three workgroups
+    ("f16", 45, (3, 3), 80001, True),
+    ("f16", 400, (2, 2), 32003, True),         # more trees than compute units: a workgroup to a row
+    ("f32", 40, (2, 2, 2), 96001, False),
+    ("f32", 200, (1, 1), 150001, True),
+    ("f32", 520, (1, 1), 32001, False),
+    ("bf16", 60, (2, 2, 2), 64001, True),      # a temperature at which the table of exp(s) cannot be used
+])
+def test_tree_path_walked_quickly(tslt, dtype, B, expansion, V, rule):
+    """Sizes at which a path is walked with fp32 terms until a node has to be drawn from: what the evaluation of every node
+    gives along it, with pruned nodes, masked, broken and shifted rows, unusable sets, candidates outside their set and
+    rejections without a residual on the way."""
+    T = 0.15 if dtype == "bf16" else 1.0
+    scale = T if dtype == "bf16" else 1.0
+    w = W.scaled(W.WORKLOADS["tree"], B=B, V=V, expansion=expansion, top_k=24, k_cap=32, dtype=dtype, T=T, sigma=1.5 * scale,
+                 zipf=1.0 * scale, noise_t=0.5 * scale)
+    tree = W.make_tree(w, 59, DEV)
+    lay = O.tree_layout(expansion)
+    offsets, n_int, n = lay["offsets"], lay["n_internal"], lay["n_nodes"]
+    draft = tree["draft"].reshape(B * n_int, V)
+    sets = tslt.truncate(draft, T, 24, 0.0, 32, u=tree["u_sample"].reshape(B * n_int, -1).contiguous(), without_replacement=rule)
+    token = sets["token"].view(B, n_int, -1)
+    q_idx, q_logit = sets["idx"].view(B, n_int, 32), sets["logit"].view(B, n_int, 32)
+    cands = torch.cat([token[:, lo:hi, :k].reshape(B, -1) for k, lo, hi in zip(expansion, offsets, offsets[1:])], 1).contiguous()
+    target, low = tree["target"], -60000.0 if dtype == "f16" else -1.0e9
+    target[1, 0, V // 2] = float("nan")
+    target[2, n_int:, 5] = float("inf")                        # leaves
+    target[3, 1] = -float("inf")
+    target[4, :, 100:] = low                                   # whole runs, finite masks; the sets mostly outside
+    target[5, :, -3:] = low
+    cands[6, :expansion[0]] = -1                               # a pruned root
+    cands[7, expansion[0]:] = -1                               # everything below the first layer
+    q_logit[8, 0, 3] = float("nan")
+    cands[9, 0] = V - 1 if int(q_idx[9, 0].max()) != V - 1 else 0
+    if dtype != "bf16":
+        target[10] += 650.0                                    # beyond the range
+        target[11] -= 640.0
+    for b in range(12, 18):                                    # nothing allowed but the set, q_hat equal to p there
+        target[b] = -float("inf")
+        for node in range(n_int):
+            keep = q_idx[b, node, :1 + b % 3].long()
+            target[b, node, keep] = draft.view(B, n_int, V)[b, node, keep]
+            q_idx[b, node, 1 + b % 3:], q_logit[b, node, 1 + b % 3:] = -1, -float("inf")
+        target[b, n_int:, 17] = 1.0
+        cands[b, ::2] = V - 2
+    count = (q_idx >= 0).sum(-1).int()
+    u_acc = tree["u_accept"] * 0.6                             # long walks
+    args = [target, T, expansion, q_idx, q_logit, count, cands, u_acc, tree["u_resample"]]
+    out = {k: P.to_np(v) for k, v in tslt.verify_tree(*args, all_nodes=True, without_replacement=rule).items()}
+    path = {k: P.to_np(v) for k, v in tslt.verify_tree(*args, all_nodes=False, without_replacement=rule).items() if v is not None}
+    torch.cuda.synchronize()
+    differ = np.nonzero((path["len"] != out["len"]) | (path["seq"] != out["seq"]).any(1))[0]
+    assert differ.size == 0, (differ[:8], path["seq"][differ[:4]], out["seq"][differ[:4]])
+    assert np.all((path["status"] & ~out["status"]) == 0) and path["status"][1] == 1 and path["status"][8] & 8
+    lengths = np.bincount(path["len"], minlength=len(expansion) + 2)
+    assert np.count_nonzero(lengths) > 2, lengths
+    for b in range(B):
+        on = np.zeros(n - 1, bool)
+        node = 0
+        for layer, k in enumerate(expansion):
+            child = offsets[layer + 1] + (node - offsets[layer]) * k
+            on[child - 1:child - 1 + k] = True
+            if out["node_slot"][b, node] < 0:
+                break
+            node = child + out["node_slot"][b, node]
+        for k in ("ratio", "beta"):
+            assert np.isnan(path[k][b][~on]).all()
+            # random errors of the terms (2^-24 of an exponent up to 40, over hundreds of terms), the outputs' rounding,
+            # and both magnified by what an earlier stage's residual divides by
+            np.testing.assert_allclose(path[k][b][on], out[k][b][on], rtol=1e-6, atol=1e-9, err_msg=f"tree {b}")
