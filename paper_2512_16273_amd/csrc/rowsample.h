@@ -348,7 +348,7 @@ template <typename T> __device__ __forceinline__ void row_edges(const RowWork<T>
   const double head = wave_sum_f64(lane < w.rs.head ? t : 0.0), tail = wave_sum_f64(lane < w.rs.head ? 0.0 : t);
   if (lane == 0) { sh.items[0] = head; sh.items[w.n_items - 1] = tail; }
 }
-template <typename T, typename Terms>
+template <typename T, typename Terms, bool kOneCopy = false>
 __device__ __forceinline__ void row_pass(RowWork<T>& w, double* table, int half, int run0, int run1, bool ends, RowShared& sh) {
   const int lane = lane_id(), wave = wave_id();
   const RowSplit& rs = w.rs;
@@ -385,21 +385,33 @@ __device__ __forceinline__ void row_pass(RowWork<T>& w, double* table, int half,
     request(cur, d);
     if (half > -2) Terms::build(table, rT, kRowThreads, half);
     __syncthreads();                    // the table is complete
-    // the first run apart: behind it the set entry's target logit is requested, whose index has arrived by then
-    int nxt = next();
-    request(nxt, dn);
-    if (cur < run1) consume(cur, d);
-    row_gather(w);
-#pragma unroll
-    for (int i = 0; i < kSegVecs; ++i) d[i] = dn[i];
-    cur = nxt;
-    while (cur < run1) {
+    // Behind the first run the set entry's target logit is requested, whose index has arrived by then.  kOneCopy: that run is
+    // not apart, so that the code of a run (PowTerms of 16-bit rows: 700 instructions) is there once; a second copy, first met by the few
+    // waves that take a second run, misses the instruction cache line by line.  Not where registers are short.  11 x 3
+    // binary16 rows of 41445 17.9 us with two copies, 16.7 with one; resampling 300 of 128256, 64 registers, 65 and 77.
+    int nxt;
+    auto step = [&]() {
       nxt = next();
       request(nxt, dn);
-      consume(cur, d);
+      if (cur < run1) consume(cur, d);
+    };
+    auto advance = [&]() {
 #pragma unroll
       for (int i = 0; i < kSegVecs; ++i) d[i] = dn[i];
       cur = nxt;
+    };
+    if constexpr (Terms::kBits || !kOneCopy || ElemTraits<T>::kPerVec < 8) {
+      step();
+      row_gather(w);
+      advance();
+      while (cur < run1) { step(); advance(); }
+    } else {
+      bool gathered = false;
+      do {
+        step();
+        if (!gathered) { row_gather(w); gathered = true; }
+        advance();
+      } while (cur < run1);
     }
   } else {
     if (half > -2) Terms::build(table, rT, kRowThreads, half);      // (the next row of a walk may have runs)
@@ -414,17 +426,17 @@ __device__ __forceinline__ void row_pass(RowWork<T>& w, double* table, int half,
 }
 // The masses of all the row's items, referenced to w.smax (0, or the row's maximum where it needs that), and sh.flags
 // (bit 0: NaN or +inf).
-template <typename T, typename Terms>
+template <typename T, typename Terms, bool kOneCopy = false>
 __device__ __forceinline__ void row_sweep(RowWork<T>& w, double* table, int half, RowShared& sh) {
   constexpr int E = ElemTraits<T>::kPerVec;
-  row_pass<T, Terms>(w, table, half, 0, w.n_runs, true, sh);
+  row_pass<T, Terms, kOneCopy>(w, table, half, 0, w.n_runs, true, sh);
   const int tid = threadIdx.x, lane = lane_id(), wave = wave_id();
   const RowSplit& rs = w.rs;
   const int n_runs = w.n_runs;
   const float rT = w.rT;
   w.smax = 0.0f;
   const int seen = __builtin_amdgcn_readfirstlane(sh.flags);
-  if (seen & 6) {
+  if (__builtin_expect(seen & 6, 0)) {
     // beyond the range: the row again, in two passes, referenced to its maximum, if it has to be
     if (!(seen & 2)) {
       if (ballot(tid < w.n_items && sh.items[tid] > kSomeMass) != 0 && lane == 0) atomicOr(&sh.flags, 8);

@@ -100,7 +100,7 @@ __device__ __forceinline__ int tree_first_child(const TreeParams& p, int node, i
 // `slot`, the output in `token` and the status bits in `st` (both as the first wave has them).  Unless a child was
 // accepted the terms' table is used up.  `items`: the row's masses, where they have been made already (else null).
 // ---------------------------------------------------------------------------------------------
-template <typename T, typename Terms>
+template <typename T, typename Terms, bool kOneCopy = false>
 __device__ __forceinline__ int tree_node(const TreeParams& p, int64_t b, int node, double* table, bool build, RowShared& sh,
                                          int& slot, int& token, int& st, const double* items = nullptr) {
   const int lane = lane_id();
@@ -117,7 +117,7 @@ __device__ __forceinline__ int tree_node(const TreeParams& p, int64_t b, int nod
   const int my_cand = p.cand_tokens[c0 + (lane < k ? lane : 0)];
   const float my_u = p.u_accept[c0 + (lane < k ? lane : 0)];
   if (items != nullptr) row_fetch<T, Terms>(w, items, table, sh);
-  else row_sweep<T, Terms>(w, table, build ? -1 : -2, sh);
+  else row_sweep<T, Terms, kOneCopy>(w, table, build ? -1 : -2, sh);
   token = -1;
   st = 0;
   float my_ratio = NAN, my_beta = NAN;                              // NaN if the candidate is never tested
@@ -187,7 +187,7 @@ __global__ __launch_bounds__(kRowThreads, kWavesPerSimd) void tree_node_kernel(c
   const int64_t b = blockIdx.x / p.n_eval;
   const int node = int(blockIdx.x - b * p.n_eval);
   int slot, token, st;
-  const int state = tree_node<T, Terms>(p, b, node, reinterpret_cast<double*>(dyn_lds), true, sh, slot, token, st);
+  const int state = tree_node<T, Terms, kWavesPerSimd == kAlone>(p, b, node, reinterpret_cast<double*>(dyn_lds), true, sh, slot, token, st);
   if (threadIdx.x == 0) {
     const int64_t n = b * p.n_nodes + node;
     p.node_state[n] = state;

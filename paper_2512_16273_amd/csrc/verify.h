@@ -160,7 +160,7 @@ __global__ __launch_bounds__(kRowThreads, kWavesPerSimd) void verify_resample_ke
   if (!unusable) {
     row_open<T>(w, target_row<T>(p, b, jstar), p.V, p.rT, sh);
     row_take_set(w, p.q_idx + size_t(r) * p.k_cap, p.q_logit + size_t(r) * p.k_cap, residual ? p.q_count[r] : 0, p.k_cap);
-    row_sweep<T, Terms>(w, table, 1, sh);
+    row_sweep<T, Terms, kWavesPerSimd == kAlone>(w, table, 1, sh);
     if (wave_id() == 0) {
       RowState rst;
       row_eval(w, rst, sh);
@@ -220,7 +220,7 @@ __global__ __launch_bounds__(kRowThreads, kWavesPerSimd) void verify_round_kerne
   const int count = p.q_count[r], x = p.draft_tokens[r];
   const float u_acc = p.u_accept[r], u_res = p.u_resample[b * (p.gamma + 1) + j];
   row_take_set(w, p.q_idx + size_t(r) * p.k_cap, p.q_logit + size_t(r) * p.k_cap, bonus ? 0 : count, p.k_cap);
-  row_sweep<T, Terms>(w, table, -1, sh);
+  row_sweep<T, Terms, kWavesPerSimd == kAlone>(w, table, -1, sh);
   // (nothing is stored to memory before the last barrier, which would wait for it)
   int st = 0, flag = 0;
   float ratio = NAN, beta = NAN;
