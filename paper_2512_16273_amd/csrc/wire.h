@@ -70,13 +70,17 @@ __device__ __forceinline__ int wire_clamped_count(int c, int k_cap) { return c <
 
 // Packing in one launch: a workgroup of four waves takes rows_per consecutive rows, adds up the words of all rows before
 // them (their counts come out of the L2: 4 bytes a row), scans its own and packs a row per wave at a time.  A lane makes
-// a whole word out of the entries that lie in it (E > 16 bits: three at most), so that nothing is assembled in LDS and
+// a whole word out of the entries that lie in it (three at most, two from 31 bits an entry on), so that nothing is assembled in LDS and
 // every store is a full line.  With `clear`, a row zeroes as many words as it falls short of a full row's, counted from
 // the end of out_words: together all those behind the stream.  Bound by its launch at the sizes of a round: packing
 // and unpacking 2048 rows of k_cap 256 took 30.8 us a call through the binding with a launch for the offsets, one for the
 // rows and a fill before them, 23.4 so (and 18.2 since the binding hands plain integers over); 14 rows 31.9 and 18.2.
 constexpr int kPackThreads = 256, kPackWaves = kPackThreads / 64;
-constexpr int kPackGroups = 1024;             // workgroups beyond which they take more than one row per wave
+// Workgroups beyond which they take more than one row per wave: what fills the chip (each adds up all counts before its
+// rows, so that more cost: 4 million rows of 2 entries 5.2 ms, 7.8 with 4096).  With 1024 and three entries to every word
+// wide rows were slower than by the launch for offsets and a row assembled in LDS: 16384 rows of k_cap 1024, packed
+// and unpacked, 106 us so, 135 by 1024, 104 now; 8192 rows 56, 60, 46; 16384 of 256 52, 46, 39.
+constexpr int kPackGroups = 2048;
 inline int64_t wire_rows_per_group(int64_t rows) {
   const int64_t r = (rows + kPackGroups - 1) / kPackGroups;
   return r > kPackWaves ? r : kPackWaves;
@@ -139,6 +143,7 @@ __global__ __launch_bounds__(kPackThreads) void wire_pack_kernel(const WireParam
         uint32_t word = w == 0 ? uint32_t(c) : 0u;
 #pragma unroll
         for (int t = 0; t < 3; ++t) {
+          if (t == 2 && E >= 31) break;                                 // two cover 32 bits wherever they begin
           const int i = first + t;
           const int at = i < c ? i : 0;
           const uint64_t entry = (uint64_t(uint32_t(ix[at])) & ((uint64_t(1) << p.b_idx) - 1)) |

@@ -375,3 +375,101 @@ def test_verify_empty_bonus_rows_of_a_large_batch(tslt, dtype, B):
         P.compare_verify(out, ref["verify"], label="empty bonus rows")
         st = P.to_np(out["status"])
         assert np.all(st[::4] == 2) and np.all(st[2::4] == 1) and np.all(st[1::2] == 0)
+
+
+@pytest.mark.parametrize("V,shift", [(147457, 0.0), (147456, 11.0), (150001, 0.0)])
+def test_verify_binary16_through_the_bit_table(tslt, V, shift):
+    """Batches of more binary16 rows than compute units, of 147456 logits and more, are resampled through a table of 14336
+    values in 112 KB: rows inside its range, rows centred on 0 (every vector evaluated again), and edges of its domain."""
+    B, gamma = 130, 1
+    w = W.scaled(W.WORKLOADS["chain_topp"], B=B, V=V, gamma=gamma, dtype="f16", T=1.0, shift=shift)
+    chain = W.make_chain(w, 61, DEV)
+    target = chain["target"].float()
+    target[0] *= 1e-3                                  # everything below the table
+    target[1, :, ::3] = 0.0
+    target[1, :, 1::3] = 3e-6                          # subnormal
+    target[2, :, ::7] = -500.0
+    target[3, :, 100:V // 2] = -60000.0                # finite masks
+    target[4, :, 5::1001] = 40.0                       # just above the table
+    target[5, 0, 9] = float("nan")
+    target[6, 1] = -float("inf")
+    target[7, 1, V - 1] = float("inf")
+    chain["target"] = target.half()
+    del target
+    u_acc = chain["u_accept"].clone()
+    u_acc[:] = 0.9995
+    u_acc[6:8] = 0.0
+    u_acc[8:12] = 0.0
+    chain["u_accept"] = u_acc
+    sel = np.concatenate([np.arange(12), [50, 129]])
+    args = {k: chain[k][torch.from_numpy(sel).to(DEV)] for k in chain}
+    ref = P.oracle_chain(P.to_np(args["draft"]), P.to_np(args["target"]), w.T, w.top_k, w.top_p, w.k_cap, P.to_np(args["u_sample"]),
+                         P.to_np(args["u_accept"]), P.to_np(args["u_resample"]))
+    tr = tslt.truncate(chain["draft"].view(B * gamma, V), w.T, w.top_k, w.top_p, w.k_cap, u=chain["u_sample"].view(B * gamma, 1))
+    q_idx, q_logit = tr["idx"].view(B, gamma, -1).clone(), tr["logit"].view(B, gamma, -1).clone()
+    q_count, toks = tr["count"].view(B, gamma).clone(), tr["token"].view(B, gamma).clone()
+    at = torch.from_numpy(sel).to(DEV)
+    q_idx[at], q_logit[at], q_count[at], toks[at] = t32(ref["q_idx"]), t32(ref["q_logit"]), t32(ref["q_count"]), t32(ref["tokens"])
+    out = tslt.verify(chain["target"], w.T, q_idx, q_logit, q_count, toks, u_acc, chain["u_resample"])
+    torch.cuda.synchronize()
+    print(P.compare_verify(out, ref["verify"], seqs=sel, label=f"bit table {V}"), ref["verify"]["accept_len"], ref["verify"]["status"])
+    assert (P.to_np(out["tokens"])[12:, 0] >= 0).all()
+
+
+@pytest.mark.parametrize("dtype,B,gamma", [("f32", 65, 3), ("f16", 65, 3), ("bf16", 103, 4)])
+def test_large_batches_with_broken_rows_and_sets(tslt, dtype, B, gamma):
+    """Just past the one-pass rounds (acceptance in fp32 terms, then one row per sequence): malformed sets, NaN, infinities, masked
+    and empty rows, tokens outside their sets and values at the edges of the terms' ranges, in one call, in two halves
+    and in stages."""
+    V = 1303
+    w = W.scaled(W.WORKLOADS["chain_topk"], B=B, V=V, gamma=gamma, dtype=dtype, T=1.0, top_k=24, k_cap=40)
+    chain = W.make_chain(w, 67, DEV)
+    low = -60000.0 if dtype == "f16" else -1.0e9
+    target = chain["target"].float()
+    target[0, 0, 17] = float("nan")
+    target[1, gamma, 5] = float("inf")
+    target[2, 1] = -float("inf")
+    target[3, 0, 40:] = -float("inf")
+    target[4, 0, V // 2:] = low
+    target[5, :, -4:] = low
+    target[6, 0] = low
+    target[7, 0] -= 620.0
+    target[8, 0, ::3] = 0.0
+    target[8, 0, 1::3] = 3e-6 if dtype == "f16" else 1e-39
+    target[9, gamma] = -float("inf")
+    chain["target"] = target.to(W.torch_dtype(dtype))
+    u_acc = chain["u_accept"].clone()
+    u_acc[:9] = 0.9995
+    u_acc[1] = u_acc[9] = u_acc[10] = u_acc[16:20] = 0.0
+    chain["u_accept"] = u_acc
+    oracle = lambda sets, toks: O.verify_chain(P.to_np(chain["target"]), w.T, *sets, toks, P.to_np(u_acc), P.to_np(chain["u_resample"]))  # noqa: E731
+    ref = P.oracle_chain(P.to_np(chain["draft"]), P.to_np(chain["target"]), w.T, w.top_k, w.top_p, w.k_cap,
+                         P.to_np(chain["u_sample"]), P.to_np(u_acc), P.to_np(chain["u_resample"]))
+    toks, q_idx, q_logit, q_count = ref["tokens"].copy(), ref["q_idx"].copy(), ref["q_logit"].copy(), ref["q_count"].copy()
+    toks[11, 0] = int(np.setdiff1d(np.arange(V), q_idx[11, 0])[0])
+    q_count[12, 0] = 0                                  # an empty set
+    v = oracle((q_idx, q_logit, q_count), toks)
+    q_logit[13, 0, 3] = np.nan                          # unusable positions: compared below, without the oracle
+    q_logit[14, 1, 2] = np.inf
+    q_idx[15, 0, 1] = V
+    args = [chain["target"], w.T, t32(q_idx), t32(q_logit), t32(q_count), t32(toks), u_acc, chain["u_resample"]]
+    out = tslt.verify(*args)
+    ws = torch.empty(tslt.workspace_bytes(tslt.OP_VERIFY, B, gamma, V, w.k_cap), dtype=torch.uint8, device=DEV)
+    halves = {k: torch.empty_like(x) for k, x in out.items()}
+    tslt.verify(*args, out=halves, workspace=ws, phase="accept")
+    tslt.verify(*args, out=halves, workspace=ws, phase="resample")
+    staged = tslt.verify(*args, first_stage=1)
+    torch.cuda.synchronize()
+    for k in out:
+        assert torch.equal(out[k], halves[k]) or torch.allclose(out[k], halves[k], rtol=0, atol=0, equal_nan=True), k
+    for k in ("accept_len", "tokens", "status"):
+        assert torch.equal(out[k], staged[k]), k
+    st, n, tok = P.to_np(out["status"]), P.to_np(out["accept_len"]), P.to_np(out["tokens"])
+    for b, j in ((13, 0), (14, 1), (15, 0)):
+        if n[b] == j:
+            assert st[b] & 8 and tok[b, j] == -1
+    assert st[13] & 8 and st[15] & 8
+    rest = np.array([b for b in range(B) if b not in (13, 14, 15)])
+    v = {k: x[rest] for k, x in v.items()}
+    v["beta_hat"] = v["beta_hat"].astype(np.float32)
+    print(P.compare_verify(out, v, seqs=rest, label=f"{dtype} large, broken"), v["status"][:13])

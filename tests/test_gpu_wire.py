@@ -143,3 +143,9 @@ def test_pack_over_the_workgroups(tslt, rows, k_cap, V):
     on = torch.arange(k_cap, device=DEV) < kept[:, None]
     assert torch.equal(un["count"].long(), kept) and torch.equal(un["idx"], torch.where(on, idx, -1))
     assert torch.equal(un["logit"], torch.where(on, logit.half().float(), -float("inf")))
+
+
+@pytest.mark.parametrize("rows,k_cap,V", [(3, 1024, 16384), (9000, 64, 9000), (700, 1000, 16385), (20, 1024, 65537), (8200, 40, 4)])
+def test_pack_entries_of_every_width(tslt, rows, k_cap, V):
+    """Entries of 18, 30, 31 and 33 bits, at whole rows' width: three of them in a word, or two."""
+    test_pack_over_the_workgroups(tslt, rows, k_cap, V)
