@@ -35,6 +35,11 @@
  *     cumulative weight exceeds u * total, accumulated in fp64.  Dense distributions are scanned in
  *     ascending token index, sparse ones in canonical order.  Uniforms are indexed by position /
  *     node, never by control flow, so results do not depend on evaluation order.
+ *   - Sums are made in the way that is fastest for the size of a batch: small rounds of verification and trees in fp64,
+ *     large rounds with fp32 terms added up in fp64.  A ratio, a beta or a mass may differ in its last bits between a
+ *     small batch and a large one, and a decision with it where u lies that close to its bound (a few 1e-7).  A
+ *     residual of less than 2^-47 of a row's mass (possible only where a token outside its set was rejected, or by
+ *     rounding) counts as none: what is drawn from is then the distribution it was taken from.
  */
 #ifndef TSLT_H
 #define TSLT_H
@@ -64,7 +69,8 @@ enum {
   TSLT_ROW_TOKEN_NOT_IN_SET = 4, /* a draft token / candidate that is not in its sparse set: rejected */
   TSLT_ROW_BAD_SET = 8,          /* a received set with a value that is not finite or an index outside [0, V): the
                                     position counts as unusable (as for TSLT_ROW_NONFINITE) */
-  TSLT_ROW_EXACT_PATH = 256      /* informational: the row took the multi-pass selection path */
+  TSLT_ROW_EXACT_PATH = 256      /* informational: the row took the multi-pass selection path (the same row may take
+                                    it in a large batch and not in a small one; its set is the same) */
 };
 
 enum {

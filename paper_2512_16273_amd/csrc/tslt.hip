@@ -131,13 +131,25 @@ bool sparse_hits(tslt_dtype dt, int64_t V, int nt, const tslt::TruncateParams& p
   const double h = 1.0 - std::pow(1.0 - std::min(1.0, hits / double(V)), E);   // ... of a vector
   return 128.0 * h + 5.0 * std::sqrt(128.0 * h) <= tslt::kRingSmall - tslt::kRingExpand;
 }
-// The shapes of the truncation kernel (see truncate.h).  Up to three rows for two compute units: 512 threads a row.
-// (Not where a row of 256 threads may be redone, which its status tells: the path a row takes does not depend on the
-// size of its batch.)  Else 256: eight workgroups of this footprint on a compute unit, the wide shape; else the deep one.
+// Whether 512 threads take a row: where every row has a compute unit to itself (but for the shortest, of few tiles more than
+// the sample or less than that: 70 fp32 rows of 9088 10.2 us by 256 threads, 10.7 by 512; binary16 9.8 / 10.2; 16000
+// 12.1 / 11.4 and 10.5 / 10.2),
+// and up to three rows for two compute units if a row is neither short nor very long (us by 256 / 512 threads, 306
+// rows: bfloat16 16000 11.3 / 12.2, 60000 19.0 / 20.4, 128256 28.0 / 27.5, 213696 39.8 / 38.3; fp32 25240 16.3 / 17.4, 60000
+// 24.2 / 22.6, 128256 39.9 / 38.2, 213696 55.8 / 58.9).
+bool tall_rows(tslt_dtype dt, int64_t V, int64_t rows) {
+  const int64_t cus = tslt::compute_units(), kb = V * elem_bytes(dt) >> 10;
+  if (rows <= cus) return V >= 10240;
+  return 2 * rows <= 3 * cus && kb >= 160 && kb < 700;
+}
+// The shapes of the truncation kernel (see truncate.h): 512 threads for such rows, but not where a row may be redone under
+// 256 threads because its large logits are many (sets of more than a few per cent of the row: its status tells, and does
+// not depend on the batch.  A row whose large logits are crowded together may still lose ring slots under 256 threads
+// alone, and say so).  Else 256: eight workgroups of this footprint on a compute unit, the wide shape; else the deep one.
 template <typename T> hipError_t launch_truncate(tslt_dtype dt, tslt::TruncateParams& p, hipStream_t s) {
   constexpr int NT = tslt::kTruncThreads, TT = tslt::kTallThreads;
   const size_t lds = plan_truncate(dt, p.V, NT, p);
-  if (2 * p.rows <= 3 * int64_t(tslt::compute_units()) && p.jprime > 0 && sparse_hits(dt, p.V, NT, p)) {
+  if (tall_rows(dt, p.V, p.rows) && p.jprime > 0 && sparse_hits(dt, p.V, NT, p)) {
     tslt::TruncateParams tall = p;
     const size_t tall_lds = plan_truncate(dt, p.V, TT, tall);
     if (tall.jprime > 0) return launch_truncate_shape<T, TT, tslt::kStagesDeep, tslt::kWavesDeep>(tall, tall_lds, s);

@@ -61,8 +61,8 @@ def test_tree_terms(tslt, dtype, V, T):
     tree = W.make_tree(w, 23, DEV)
     target = tree["target"].float()
     target[0, 4:10] = edge_rows(target[0, 4:10].clone())             # the leaves
-    rows = target[1, :6].clone()                                     # the non-leaf nodes, without the shifted rows (there
-    rows[[0, 4, 2, 1, 3, 5]] = edge_rows(rows[[0, 4, 2, 1, 3, 5]])   # the fp32 pass over the row rounds by |z| / 2^24)
+    rows = target[1, :6].clone()                                     # the non-leaf nodes (the shifted rows among them:
+    rows[[0, 4, 2, 1, 3, 5]] = edge_rows(rows[[0, 4, 2, 1, 3, 5]])   # test_tree_terms_at_every_inner_node)
     target[1, :4] = torch.stack([rows[0], rows[4], rows[2], rows[5]])
     tree["target"] = target.to(W.torch_dtype(dtype))
     ref = P.oracle_tree(P.to_np(tree["draft"]), P.to_np(tree["target"]), w.T, w.top_k, w.top_p, w.k_cap, w.expansion,
@@ -217,4 +217,31 @@ def test_tree_finite_masks(tslt, dtype, B):
     path = tslt.verify_tree(*args, all_nodes=False)
     torch.cuda.synchronize()
     print(P.compare_tree(out, ref, w.expansion, all_nodes=True, label=f"{dtype} {B}"))
+    assert torch.equal(path["seq"], out["seq"]) and torch.equal(path["len"], out["len"])
+
+
+@pytest.mark.parametrize("dtype,B,wor", [("f32", 2, False), ("f32", 90, True), ("bf16", 90, False), ("f16", 2, True), ("f16", 90, False)])
+def test_tree_terms_at_every_inner_node(tslt, dtype, B, wor):
+    """The rows of edge_rows at non-leaf nodes: candidates tested, updates made and tokens drawn on a row that was swept again by
+    its maximum, and the walk going on from such a node (90 trees of 6 nodes are walked node after node)."""
+    w = W.scaled(W.WORKLOADS["tree"], B=B, V=4097, expansion=(2, 1), top_k=8, k_cap=8, dtype=dtype, T=1.0, without_replacement=wor)
+    tree = W.make_tree(w, 71, DEV)
+    target = tree["target"].float()
+    for first, b in ((0, 0), (3, 1)):                                # tree 0: nodes 0, 1, 2 get rows 0 to 2, tree 1 rows 3 to 5
+        six = edge_rows(target[b, :3].repeat(2, 1).clone())
+        target[b, :3] = six[first:first + 3]
+    if B > 2:
+        for b in range(2, 50):                                       # the shifted rows at every node, in every order
+            target[b, :3] = target[b, :3] + torch.tensor([[650.0, 0.0, -640.0], [0.0, -640.0, 650.0], [-640.0, 650.0, 0.0]],
+                                                         device=DEV)[b % 3][:, None]
+    tree["target"] = target.to(W.torch_dtype(dtype))
+    tree["u_accept"] = tree["u_accept"] * 0.9
+    ref = P.oracle_tree(P.to_np(tree["draft"]), P.to_np(tree["target"]), w.T, w.top_k, w.top_p, w.k_cap, w.expansion,
+                        P.to_np(tree["u_sample"]), P.to_np(tree["u_accept"]), P.to_np(tree["u_resample"]), wor, wor)
+    args = [tree["target"], w.T, w.expansion, t32(ref["q_idx"]), t32(ref["q_logit"]), t32(ref["q_count"]), t32(ref["cands"]),
+            tree["u_accept"], tree["u_resample"]]
+    out = tslt.verify_tree(*args, all_nodes=True, without_replacement=wor)
+    path = tslt.verify_tree(*args, all_nodes=False, without_replacement=wor)
+    torch.cuda.synchronize()
+    print(P.compare_tree(out, ref, w.expansion, all_nodes=True, label=f"{dtype} {B}"), np.bincount(ref["verify"]["len"]))
     assert torch.equal(path["seq"], out["seq"]) and torch.equal(path["len"], out["len"])

@@ -250,3 +250,19 @@ def test_truncate_large_sets_by_groups(tslt, dtype, V, k_cap):
     torch.cuda.synchronize()
     res = P.compare_truncate(out, z, 1.0, k_cap, 0.0, k_cap, label=f"{dtype} {V} {k_cap}")
     assert res["exact_path_rows"] >= 10
+
+
+@pytest.mark.parametrize("dtype,V,rows", [("bf16", 81920, 300), ("bf16", 81919, 300), ("f32", 10240, 256), ("f32", 10239, 256),
+                                          ("f32", 10240, 257), ("f16", 100001, 384)])
+def test_truncate_on_either_side_of_the_shapes(tslt, dtype, V, rows):
+    """Rows and row lengths at which the workgroups' size changes: the same sets and draws as in a batch of 390 rows."""
+    w = W.scaled(W.WORKLOADS["chain_topk"], V=V, dtype=dtype)
+    z = rows_like(w, 390, 11)
+    u = W.uniforms((390, 1), 5, 2, 11, DEV)
+    many = tslt.truncate(z, 0.9, 0, 0.9, 64, u=u)
+    few = tslt.truncate(z[:rows], 0.9, 0, 0.9, 64, u=u[:rows])
+    torch.cuda.synchronize()
+    for k in ("idx", "logit", "count", "token", "slot"):
+        assert torch.equal(few[k], many[k][:rows]), k
+    torch.testing.assert_close(few["mass"], many["mass"][:rows], rtol=2.5e-7, atol=0)      # fp32 terms in another order
+    P.compare_truncate({k: x[:8] for k, x in few.items()}, z[:8], 0.9, 0, 0.9, 64, label=f"{dtype} {V}")
