@@ -55,8 +55,8 @@ TSLT_HD double exp64(double x) {
 
 // exp(x) for a finite x with |x| <= 700 (in the kernels an fp32 value) through a table of 2^(i/2048):
 // x = n * ln2/2048 + r, |r| <= ln2/4096, exp(x) = 2^(n div 2048) * table[n mod 2048] * (1 + r + r^2/2 + r^3/6) (the
-// series is cut below 2^-54).  Half the fp64 operations of exp64, for one 8-byte read from LDS; within about 1.5
-// ulp.  An entry is 2^(i/2048) with i << 9 taken off its high word, so that adding n << 9 there scales by
+// series is cut below 2^-54).  Half the fp64 operations of exp64, for one 8-byte read from LDS; within about 1.3
+// ulp (exp64: 0.9).  An entry is 2^(i/2048) with i << 9 taken off its high word, so that adding n << 9 there scales by
 // 2^(n div 2048) without n's low bits having to be masked out.
 constexpr int kPowEntries = 2048;
 TSLT_HD uint64_t pow_entry(int i) {

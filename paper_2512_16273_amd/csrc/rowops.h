@@ -1,4 +1,4 @@
-// Row-level building block of chain verification in large batches and of the statistics:
+// Row-level building block of chain verification in large batches, of the quick walk through a tree and of the statistics:
 //   eval_row_on_set  one streaming pass over a target row for its softmax normaliser, then p and
 //                    q_hat at the indices of a received sparse set, in fp64;
 #pragma once

@@ -5,9 +5,9 @@
 //   row_locate, row_pick   the token at which the cumulative mass of p, or of what the updates made of it, passes
 //                u * total, in ascending token index: the run that holds it, then the element
 // fp64 is needed for the sampling: at V >= 128k the buckets of the inverse CDF are far narrower than fp32 prefix
-// sums can resolve.  One workgroup per row keeps the sums in LDS and one pass serves the test and the sample;
-// splitting a row over workgroups would need a device-scope fence per workgroup, which writes back and
-// invalidates the L2 of an XCD and costs far more than it saves.
+// sums can resolve.  One workgroup per row keeps the sums in LDS and one pass serves the test and the sample.  Inside a
+// launch, workgroups that share a row would have to hand their sums over through a device-scope fence each; where a
+// second launch follows anyway its boundary does that (row_fetch; trees only).
 #pragma once
 #include <algorithm>
 #include <type_traits>

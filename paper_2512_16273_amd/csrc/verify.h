@@ -291,8 +291,9 @@ __global__ __launch_bounds__(64) void verify_select_kernel(const VerifyParams p)
 
 // Largest batch, in rows B * (gamma + 1), that is verified by verify_round_kernel: one row per compute unit, and two
 // through bfloat16's bit table, whose sweep is bound by the LDS and leaves the vector units to the other row's steps.
-// Measured, us a round, this way / by kernels A and B (V = 128256, k_cap 256): bfloat16 384 rows 33.3 / 38.2, 512 36.2 / 40.2, 896 65.6 / 59.3; binary16 384 55.5 / 45.4; fp32 384
-// 55.7 / 58.3, 512 63.8 / 62.8.
+// Measured, us a round, this way / by kernels A and B (V = 128256, k_cap 256): bfloat16 384 rows 33.3 / 38.2, 512 36.2 /
+// 40.2, 896 65.6 / 59.3; binary16 384 55.5 / 45.4; fp32 384 55.7 / 58.3, 512 63.8 / 62.8 (fp32 keeps binary16's line: 4 %
+// in a narrow range).
 template <typename Terms> inline int64_t round_rows() { return int64_t(compute_units()) * (Terms::kBits && !kLargeTable<Terms> ? 2 : 1); }
 
 // phases: bit 0 = acceptance decisions (kernel A), bit 1 = resampling and outputs (kernel B)
@@ -345,8 +346,8 @@ template <typename T, typename Terms> hipError_t launch_verify_with(VerifyParams
   }
   return e;
 }
-// Binary16 batches beyond round_rows() of rows this long: the bit table (128 x 5, V = 152064 64.6 / 60.6 us, 256000
-// 96.2 / 86.5; 100000 47.9 either way).
+// Binary16 batches beyond round_rows() of rows this long: the bit table (128 x 5 by PowTerms / by it, V = 152064 63.4 / 60.2
+// us, 256000 95.5 / 86.2; 100000 47.9 either way), at the price of rows centred on 0, outside its range (63.3 / 91.9, 95.6 / 139.2).
 constexpr int64_t kBitMinV16 = 147456;
 template <typename T> hipError_t launch_verify(VerifyParams p, hipStream_t s, int phases) {
   if constexpr (ExpTab<T>::kHas) {
