@@ -372,38 +372,39 @@ template <int NW> __device__ __forceinline__ int block_excl_scan_i32(int v, Bloc
   return base + inc - v;
 }
 
-// Sort of n candidate records held in LDS, descending, by a 256-bin counting sort on the value
-// (bins divide the interval [min, max] of the values present evenly; any monotone binning keeps the
-// result exact) followed by an exact rank inside each bin.  The largest min(n, k_keep) records end up
-// in out[0..) in order.  Only the bins that can reach the first k_keep places are moved: `tmp` needs
-// room for k_keep records plus the population of the bin that straddles that boundary; the function
-// returns false, leaving `in` intact, when tmp_cap is too small for that.  `in` and `out` may be the
-// same array; `tmp` must be distinct from both.  hist, start and cursor are 256-entry LDS arrays.
-// Work per thread is about n/NT + k_keep/NT * mean bin population; values crowded into one bin cost
-// more, bounded by n^2/NT comparisons per thread.  NT = threads of the workgroup (64 to 512).
-__device__ __forceinline__ int value_bin(uint64_t c, float vmin, float scale) {
+// Sort of n candidate records held in LDS, descending, by a counting sort over NT linear value bins (they
+// divide the interval [min, max] of the values present evenly; any monotone binning keeps the result exact)
+// followed by an exact rank inside each bin.  The largest min(n, k_keep) records end up in out[0..) in order.  Only
+// the bins that can reach the first k_keep places are moved: `tmp` needs room for k_keep records plus the population
+// of the bin that straddles that boundary; the function returns false, leaving `in` intact, when tmp_cap is too small
+// for that (kRankAhead records more behind tmp_cap are written and read).  `in` and `out` may be the same array; `tmp`
+// must be distinct from both.  `bins` holds NT words of LDS, NT = threads of the workgroup.
+// Bound by latencies: six barriers, and in the rank the population of a bin (tens of records where bfloat16 leaves few
+// values apart), which is therefore read kRankAhead records at a time.
+constexpr int kRankAhead = 4;
+template <int kBins> __device__ __forceinline__ int value_bin(uint64_t c, float vmin, float scale) {
   // fp32 subtraction and multiplication are monotone, which is all the binning has to be
   const int b = int((cand_value(c) - vmin) * scale);
-  return b > 255 ? 255 : (b < 0 ? 0 : b);
+  return b > kBins - 1 ? kBins - 1 : (b < 0 ? 0 : b);
 }
 template <int NT>
 __device__ __forceinline__ bool bucket_sort_desc(const uint64_t* in, int n, uint64_t* tmp, int tmp_cap, uint64_t* out,
-                                                 int k_keep, uint32_t* hist, uint32_t* start, uint32_t* cursor,
-                                                 BlockScratch& red) {
+                                                 int k_keep, uint32_t* bins, BlockScratch& red) {
   constexpr int NW = NT / 64;
-  constexpr int BPT = NT < 256 ? 256 / NT : 1;      // bins per thread: thread t owns bins 255 - t*BPT - j, j < BPT
-  const bool has_bin = NT <= 256 || int(threadIdx.x) < 256;
+  static_assert(NW + 2 <= 16, "room in the scratch");
   if (n <= 0) return true;
   const int tid = threadIdx.x;
   uint32_t kmin = 0xFFFFFFFFu, kmax = 0u;
+  const uint32_t* key = reinterpret_cast<const uint32_t*>(in) + 1;      // the high word of a record
+#pragma unroll 4
   for (int i = tid; i < n; i += NT) {
-    const uint32_t k = uint32_t(in[i] >> 32);
+    const uint32_t k = key[2 * i];
     kmin = k < kmin ? k : kmin;
     kmax = k > kmax ? k : kmax;
   }
   kmax = wave_max_u32(kmax);
   kmin = ~wave_max_u32(~kmin);
-  for (int b = tid; b < 256; b += NT) hist[b] = 0;
+  bins[tid] = 0;
   if (lane_id() == 0) { red.i[wave_id()] = int(kmin); red.f[wave_id()] = as_f32(kmax); }
   __syncthreads();
   kmin = uint32_t(red.i[0]); kmax = as_u32(red.f[0]);
@@ -414,41 +415,44 @@ __device__ __forceinline__ bool bucket_sort_desc(const uint64_t* in, int n, uint
   }
   const float vmin = key_to_f32(kmin);
   const float span = key_to_f32(kmax) - vmin;            // may overflow to +inf: then one bin
-  const float scale = (span > 0.0f && span < 3.0e38f) ? 255.0f / span : 0.0f;
-  for (int i = tid; i < n; i += NT) atomicAdd(&hist[value_bin(in[i], vmin, scale)], 1u);
+  const float scale = (span > 0.0f && span < 3.0e38f) ? float(NT - 1) / span : 0.0f;
+  for (int i = tid; i < n; i += NT) atomicAdd(&bins[value_bin<NT>(in[i], vmin, scale)], 1u);
   __syncthreads();
-  int total;
-  int h[BPT], mine = 0;
+  // where each bin begins, in descending order; the one that holds place k_keep (the last, if there are fewer records)
+  const int b_mine = NT - 1 - tid, mine = int(bins[b_mine]);
+  const int inc = wave_incl_scan_i32(mine);
+  if (lane_id() == 63) red.i[wave_id()] = inc;
+  __syncthreads();
+  int run = inc - mine;
 #pragma unroll
-  for (int j = 0; j < BPT; ++j) { h[j] = has_bin ? int(hist[255 - tid * BPT - j]) : 0; mine += h[j]; }
-  const int excl = block_excl_scan_i32<NW>(mine, red, total);   // bins in descending order
-  int run = excl, moved = 0;
-#pragma unroll
-  for (int j = 0; j < BPT; ++j) {
-    if (has_bin) {
-      start[255 - tid * BPT - j] = uint32_t(run);
-      cursor[255 - tid * BPT - j] = uint32_t(run);
-    }
-    if (run < k_keep) moved += h[j];      // records in the bins that start before place k_keep
-    run += h[j];
-  }
-  const int n_moved = block_sum_i32<NW>(moved, red);
+  for (int w = 0; w < NW; ++w) run += w < wave_id() ? red.i[w] : 0;
+  const int place = n < k_keep ? n : k_keep;
+  bins[b_mine] = uint32_t(run);
+  if (run < place && run + mine >= place) { red.f[0] = __int_as_float(run + mine); red.f[1] = __int_as_float(b_mine); }
+  __syncthreads();
+  const int n_moved = __float_as_int(red.f[0]), last_bin = __float_as_int(red.f[1]);
   if (n_moved > tmp_cap) return false;
-  __syncthreads();
   for (int i = tid; i < n; i += NT) {
     const uint64_t c = in[i];
-    const int b = value_bin(c, vmin, scale);
-    if (int(start[b]) < k_keep) tmp[atomicAdd(&cursor[b], 1u)] = c;
+    const int b = value_bin<NT>(c, vmin, scale);
+    if (b >= last_bin) tmp[atomicAdd(&bins[b], 1u)] = c;
   }
+  if (tid < kRankAhead) tmp[n_moved + tid] = 0;          // smaller than every record
   __syncthreads();
+  // (a bin's word is now where it ends.  Records behind a bin are smaller, so that a step past its end counts nothing.)
   for (int i = tid; i < n_moved; i += NT) {
     const uint64_t c = tmp[i];
-    const int b = value_bin(c, vmin, scale);
-    const int s0 = int(start[b]);
-    const int s1 = s0 + int(hist[b]);
-    int r = 0;
-    for (int j = s0; j < s1; ++j) r += tmp[j] > c ? 1 : 0;
-    if (s0 + r < k_keep) out[s0 + r] = c;
+    const int b = value_bin<NT>(c, vmin, scale);
+    const int s0 = b == NT - 1 ? 0 : int(bins[b + 1]), s1 = int(bins[b]);
+    int r = s0;
+    for (int j = s1 - s0 > 1 ? s0 : s1; j < s1; j += kRankAhead) {      // (alone in its bin: nothing to look at)
+      uint64_t t[kRankAhead];
+#pragma unroll
+      for (int u = 0; u < kRankAhead; ++u) t[u] = tmp[j + u];
+#pragma unroll
+      for (int u = 0; u < kRankAhead; ++u) r += t[u] > c ? 1 : 0;
+    }
+    if (r < k_keep) out[r] = c;
   }
   __syncthreads();
   return true;

@@ -12,7 +12,16 @@
 // sorting them; otherwise (ties, masked rows, unlucky sample, overflow of a buffer) the row is redone
 // by an exact radix selection that makes several passes.  Either way the kept entries are then
 // evaluated in fp64, which is also where Top-rho and the renormalisation are decided.
+//
+// Bound by memory in large batches (2048 bfloat16 rows of 128256: 92 us, of which 81 are the reading), by the instructions a
+// row's waves issue one after the other in small ones.  The pass is written for the second: an fma takes its operands from
+// vector registers without a sign to change (2.7 cycles a wave, 4.4 otherwise), binary16 is tested against the threshold as
+// packed halves and never widened, addresses are a scalar offset into a buffer, the complete stages have a loop without a
+// check for the row's end, and every exchange between waves behind the pass is one barrier (12 in all, 24 before).  us
+// before / now: 1 binary16 row of 32000, k 320 12.3 / 11.5; 64 bfloat16 rows of 128256, k 256 20.7 / 18.7; 19 binary16 rows of
+// 223104 27.6 / 23.6; 600 binary16 rows of 32000 17.7 / 15.8; 4096 bfloat16 rows of 256000, k 1024 407 / 396.
 #pragma once
+#include <type_traits>
 #include "common.h"
 #include "wire.h"
 #include "exp64.h"
@@ -67,9 +76,11 @@ struct TruncateParams {
   int32_t* out_slot;
 };
 
-// Dynamic LDS: [ rings ] [ candidates ].  The ring space is reused for the sort's three 256-entry tables and its
-// scratch records behind them and, before the pass, for the per-thread sample maxima.
-constexpr int kTablesBytes = 3 * 256 * 4;
+// Dynamic LDS: [ rings ] [ candidates ].  The ring space is reused for the sort's table and its scratch records behind it
+// and, before the pass, for the per-thread sample maxima.
+constexpr int kMaxDraws = 16;      // TSLT_MAX_BRANCH
+constexpr int kTablesBytes = 3 * 256 * 4;             // also the few records behind the scratch
+static_assert(kTallThreads * 4 + kRankAhead * 8 <= kTablesBytes, "the sort's table and those records");
 inline int truncate_sort_scratch(int k_sel) { return k_sel + k_sel / 2 + 64; }   // records the sort may need
 inline int truncate_ring_bytes(int n_waves, int k_sel) {
   const int rings = n_waves * (kRingSmall * 20), sort = (kTablesBytes + 8 * truncate_sort_scratch(k_sel) + 15) & ~15;
@@ -92,7 +103,7 @@ struct TruncateShared {
 // candidates written to cand[] (exactly k_eff), or 0 with `st` set.
 // ---------------------------------------------------------------------------------------------
 template <typename T, int NT>
-__device__ int exact_select(const void* row, int64_t V, int k_sel, float k2, uint64_t* cand, uint32_t* hist,
+__device__ __forceinline__ int exact_select(const void* row, int64_t V, int k_sel, float k2, uint64_t* cand, uint32_t* hist,
                             TruncateShared& sh, float& c_ref, double& z_c, int& st) {
   constexpr int NW = NT / 64;
   const int tid = threadIdx.x;
@@ -198,7 +209,7 @@ __device__ int exact_select(const void* row, int64_t V, int k_sel, float k2, uin
 // fp32 rows of 12000, k_cap 800: 111 and 39.
 // Returns false with `st` set for an unusable row.
 template <typename T, int NT>
-__device__ bool many_groups_threshold(const void* row, const RowSplit& rs, int k_sel, uint32_t* group, int cap,
+__device__ __forceinline__ bool many_groups_threshold(const void* row, const RowSplit& rs, int k_sel, uint32_t* group, int cap,
                                                    TruncateShared& sh, float& tau, float& vmax, int& st) {
   constexpr int E = ElemTraits<T>::kPerVec;
   constexpr int NW = NT / 64;
@@ -268,7 +279,7 @@ __device__ bool many_groups_threshold(const void* row, const RowSplit& rs, int k
 // an unusable row, or -1 when the candidates do not fit (then the radix selection is used).
 // ---------------------------------------------------------------------------------------------
 template <typename T, int NT, bool kLarge>
-__device__ int two_pass_select(const void* row, const RowSplit& rs, int k_sel, float k2, uint64_t* cand, int cap,
+__device__ __forceinline__ int two_pass_select(const void* row, const RowSplit& rs, int k_sel, float k2, uint64_t* cand, int cap,
                                uint64_t* sort_tmp, int sort_tmp_cap, uint32_t* tables, TruncateShared& sh,
                                bool need_sum, float& c_ref, double& z_c, int& st) {
   constexpr int E = ElemTraits<T>::kPerVec;
@@ -339,8 +350,7 @@ __device__ int two_pass_select(const void* row, const RowSplit& rs, int k_sel, f
     const int n_groups = sh.cand_count;
     tau = -INFINITY;                               // fewer than k_eff non-empty groups: take everything
     if (n_groups >= k_eff) {
-      if (!bucket_sort_desc<NT>(cand, n_groups, sort_tmp, sort_tmp_cap, cand, k_eff, tables, tables + 256, tables + 512,
-                            sh.red))
+      if (!bucket_sort_desc<NT>(cand, n_groups, sort_tmp, sort_tmp_cap, cand, k_eff, tables, sh.red))
         return -1;
       tau = cand_value(cand[k_eff - 1]);
     }
@@ -454,6 +464,37 @@ __device__ __forceinline__ float vec_max8(const float (&v)[8]) {
 template <> __device__ __forceinline__ float vec_max<Bf16>(const float (&v)[8]) { return vec_max8(v); }
 template <> __device__ __forceinline__ float vec_max<F16>(const float (&v)[8]) { return vec_max8(v); }
 
+// Whether an element of a vector is above the threshold.  `at` makes the threshold what the test compares with, once a row.
+// binary16: the maximum of the packed halves, two at a time, against the largest binary16 value that is not above the
+// threshold; nothing is widened for it.  (bfloat16 has no such instructions, and its bits are not to be taken for
+// binary16: -inf would be a NaN.)  A NaN among the elements may or may not be a hit: its row is redone in any case.
+template <typename T> struct HitTest {
+  using Threshold = float;
+  static __device__ __forceinline__ float at(float tau0) { return tau0; }
+  static __device__ __forceinline__ bool hit(const uint4& w, float tau) {
+    float v[ElemTraits<T>::kPerVec];
+    unpack<T>(w, v);
+    return vec_max<T>(v) > tau;
+  }
+};
+typedef _Float16 half2_t __attribute__((ext_vector_type(2)));
+template <> struct HitTest<F16> {
+  using Threshold = _Float16;
+  static __device__ __forceinline__ _Float16 at(float tau0) {
+    const _Float16 h = _Float16(tau0);                                    // to nearest; one step down if that is above
+    uint16_t b = __builtin_bit_cast(uint16_t, h);
+    if (float(h) > tau0) b = (b & 0x8000u) ? b + 1 : (b == 0 ? 0x8001u : b - 1);
+    return __builtin_bit_cast(_Float16, b);
+  }
+  static __device__ __forceinline__ bool hit(const uint4& w, _Float16 tau) {
+    const half2_t x = __builtin_bit_cast(half2_t, w.x), y = __builtin_bit_cast(half2_t, w.y);
+    const half2_t z = __builtin_bit_cast(half2_t, w.z), u = __builtin_bit_cast(half2_t, w.w);
+    half2_t m = __builtin_elementwise_maximum(__builtin_elementwise_maximum(x, y), z);
+    m = __builtin_elementwise_maximum(m, u);
+    return __builtin_elementwise_max(m.x, m.y) > tau;
+  }
+};
+
 template <typename T, int NT, int kStages, int kWavesPerSimd>
 __global__ __launch_bounds__(NT, kWavesPerSimd) void truncate_kernel(const TruncateParams p) {
   constexpr int E = ElemTraits<T>::kPerVec;
@@ -465,9 +506,9 @@ __global__ __launch_bounds__(NT, kWavesPerSimd) void truncate_kernel(const Trunc
   constexpr int kRing = kTall ? kRingTall : kRingSmall;
   uint4* ring_all = reinterpret_cast<uint4*>(dyn_lds);
   uint32_t* ring_vidx_all = reinterpret_cast<uint32_t*>(dyn_lds + NW * kRing * 16);
-  uint32_t* tables = reinterpret_cast<uint32_t*>(dyn_lds);          // 3 x 256 entries, aliasing the rings
+  uint32_t* tables = reinterpret_cast<uint32_t*>(dyn_lds);          // aliasing the rings
   uint64_t* cand = reinterpret_cast<uint64_t*>(dyn_lds + p.ring_bytes);
-  uint64_t* sort_tmp = reinterpret_cast<uint64_t*>(dyn_lds + kTablesBytes);
+  uint64_t* sort_tmp = reinterpret_cast<uint64_t*>(dyn_lds + kTablesBytes - kRankAhead * 8);
   const int sort_tmp_cap = (p.ring_bytes - kTablesBytes) / 8;
 
   const int tid = threadIdx.x;
@@ -514,30 +555,42 @@ __global__ __launch_bounds__(NT, kWavesPerSimd) void truncate_kernel(const Trunc
         if (u * stride * NT + tid >= nv) q[u] = neg_inf_vec<T>();
     };
     load_sample(rs, d);
-    const uint32_t last_vec = nvec - 1;
     // The pass keeps kStages stages of kGroup tiles in flight per thread; the first ones are requested now, so
     // that they travel while the threshold is being worked out.  In a long row a sample tile is the first tile of
     // its stage and is not read again; in a short one (512 threads) the stages begin behind the sample.  The row's ragged end
     // (the last tile possibly incomplete, the last stage possibly half empty) is the last stage.
     static_assert(kGroup == 2, "a stage is a pair of tiles");
     uint4 pipe[kStages][kGroup];
-    const uint32_t tile0 = long_row || !kTall ? 0u : uint32_t(kBatch);          // of the first stage
-    const uint32_t n_stage = (long_row || kTall) && n_tiles > tile0 ? (n_tiles - tile0 + kGroup - 1) / kGroup : 0u;
-    uint32_t skip_g = 0, skips_left = long_row || !kTall ? kBatch : 0;
+    const uint32_t tile0 = long_row ? 0u : uint32_t(kBatch);                    // of the first stage
+    const uint32_t n_stage = n_tiles > tile0 ? (n_tiles - tile0 + kGroup - 1) / kGroup : 0u;
     const uint32_t stride_g = s_stride / kGroup;
+    // (the row as a buffer: no vector instruction goes into addresses; what lies past the row's end comes back as zeros)
+    const __amdgpu_buffer_rsrc_t body = row_buffer(rs.body, nvec);
+    const uint32_t lane_bytes = uint32_t(tid) * 16u;
+    // stages 0, stride_g, 2 stride_g, 3 stride_g begin with a sample tile
+    constexpr uint32_t kNever = 0xFFFFFFFFu;
+    uint32_t skip_g = long_row ? 0u : kNever, issue_at = tile0 * (NT * 16u);
+    auto next_sample = [&](uint32_t g) { return g == (kBatch - 1) * stride_g ? kNever : g + stride_g; };
+    // (called with g = 0, 1, 2, ...: its scalar instructions count where a pair of fp32 vectors has eight logits)
     auto issue = [&](uint32_t g, uint4 (&q)[kGroup]) {
-      const uint32_t v0 = (tile0 + g * kGroup) * NT + tid;
       // the first tile of a sample stage is in registers already: its slot repeats the second tile's load
-      const bool skip = skips_left > 0 && g == skip_g;
-      if (skip) { skip_g += stride_g; --skips_left; }
-      const uint32_t va = skip ? v0 + NT : v0, vb = v0 + NT;
-      q[0] = load_vec_stream(&rs.body[va < last_vec ? va : last_vec]);
-      q[1] = load_vec_stream(&rs.body[vb < last_vec ? vb : last_vec]);
+      uint32_t at_a = issue_at;
+      const uint32_t at_b = issue_at + NT * 16u;
+      if (__builtin_expect(g == skip_g, 0)) {
+        at_a = at_b;
+        skip_g = next_sample(g);
+      }
+      issue_at = at_b + NT * 16u;
+      q[0] = buffer_load_vec_stream(body, lane_bytes, at_a);
+      q[1] = buffer_load_vec_stream(body, lane_bytes, at_b);
     };
-    if (n_stage > 0) {
+    // (not yet for the short rows of a large batch, whose sample it would hold up: 2000 fp32 rows of 16000 27.2 and 25.6 us)
+    const bool early = kTall || long_row;
+    auto issue_first = [&]() {
 #pragma unroll
       for (int s = 0; s < kStages; ++s) issue(uint32_t(s), pipe[s]);
-    }
+    };
+    if (n_stage > 0 && early) issue_first();
     float tmax = -INFINITY;
 #pragma unroll
     for (int u = 0; u < kBatch; ++u) {
@@ -555,13 +608,17 @@ __global__ __launch_bounds__(NT, kWavesPerSimd) void truncate_kernel(const Trunc
     uint32_t kq[NW];
 #pragma unroll
     for (int q = 0; q < NW; ++q) kq[q] = tables[lane + 64 * q];
-    uint32_t tau_key = 0;
+    uint32_t top_key = kq[0];                          // the sample's maximum
+#pragma unroll
+    for (int q = 1; q < NW; ++q) top_key = kq[q] > top_key ? kq[q] : top_key;
+    top_key = wave_max_u32(top_key);
     auto reach = [&](uint32_t trial) {                 // how many of them reach `trial`
       int cnt = 0;
 #pragma unroll
       for (int q = 0; q < NW; ++q) cnt += __popcll(ballot(kq[q] >= trial));
       return cnt;
     };
+    uint32_t tau_key = 0;
     if constexpr (!kTall) {                            // a bit at a time, every wave for itself
       for (int bit = 31; bit >= 32 - p.tau_bits; --bit) {
         const uint32_t trial = tau_key | (1u << bit);
@@ -569,7 +626,17 @@ __global__ __launch_bounds__(NT, kWavesPerSimd) void truncate_kernel(const Trunc
       }
     } else {                                           // three bits at a time, every wave tries one of their values
       static_assert(NW == 8, "a wave per value");
-      int shift = 32;
+      // the leading bits that all of them share need no search: half of them where a row's large logits are within a few
+      // powers of two, a barrier for every three
+      uint32_t low_key = kq[0];
+#pragma unroll
+      for (int q = 1; q < NW; ++q) low_key = kq[q] < low_key ? kq[q] : low_key;
+      low_key = ~wave_max_u32(~low_key);
+      const int first_bit = top_key != low_key ? 31 - __builtin_clz(top_key ^ low_key) : 0;
+      int shift = 32 - 3 * ((31 - first_bit) / 3);     // the groups of three above the first bit
+      tau_key = shift < 32 ? top_key & ~((1u << shift) - 1u) : 0u;
+      const int last = 32 - 3 * ((p.tau_bits + 2) / 3);
+      if (shift < last) { shift = last; tau_key = top_key & ~((1u << last) - 1u); }
       for (int step = 0; shift > 32 - p.tau_bits; ++step) {
         shift -= 3;
         int* reached = step & 1 ? reinterpret_cast<int*>(sh.red.f) : sh.red.i;
@@ -580,10 +647,6 @@ __global__ __launch_bounds__(NT, kWavesPerSimd) void truncate_kernel(const Trunc
         tau_key |= uint32_t(__popcll(ballot(lane > 0 && of_lane >= p.jprime))) << shift;
       }
     }
-    uint32_t top_key = kq[0];   // the sample maximum
-#pragma unroll
-    for (int q = 1; q < NW; ++q) top_key = kq[q] > top_key ? kq[q] : top_key;
-    top_key = wave_max_u32(top_key);
     const float smax = key_to_f32(top_key);
     const float tau0 = tau_key <= kKeyNegInf ? -INFINITY : key_to_f32(tau_key);
     fast_ok = smax > -INFINITY && smax < INFINITY;   // false for NaN too
@@ -592,8 +655,11 @@ __global__ __launch_bounds__(NT, kWavesPerSimd) void truncate_kernel(const Trunc
 
     if (fast_ok) {
       // ---- the pass -------------------------------------------------------------------------
-      const float neg_c = -c_ref;
-      const float k2 = p.k2;
+      // (The two operands that every term's fma shares stand in vector registers, without a sign to change: from a scalar
+      // register, or negated on the way, it would issue at half the rate.)
+      float k2 = p.k2, neg_c = -c_ref;
+      asm volatile("" : "+v"(k2), "+v"(neg_c));
+      const typename HitTest<T>::Threshold tau = HitTest<T>::at(tau0);
       // fp32 sums live for a few vectors only and are then added to an fp64 total: a long-lived fp32
       // accumulator that has met one large term rounds away the many small ones that follow
       double dacc = 0.0;
@@ -602,106 +668,134 @@ __global__ __launch_bounds__(NT, kWavesPerSimd) void truncate_kernel(const Trunc
       uint4* ring = ring_all + wave * kRing;
       uint32_t* ring_vidx = ring_vidx_all + wave * kRing;
       const uint32_t head = uint32_t(rs.head);
-
-      // Two vectors at a time: their exp2 terms go to the partial sums; a vector with an element above
-      // tau0 is parked in the ring, which is expanded when it has no room for the next ones.
-      // (returns the sum of the pair's exp2 terms)
-      auto process_pair = [&](const uint4& w0, const uint4& w1, uint32_t vidx0, uint32_t vidx1) -> float {
-        float a[E], b[E];
+      auto expand = [&]() {
+        expand_ring<T>(ring, ring_vidx, wave_cnt, tau0, head, cand, p.sort_cap, sh);
+        wave_cnt = 0;
+      };
+      // A vector with an element above tau0 is parked in the ring, which is expanded when it has no room for the next ones.
+      auto put = [&](bool hit, uint64_t mask, const uint4& w, uint32_t vidx) {
+        if (hit) {
+          const int pos = wave_cnt + lanes_below(mask);
+          ring[pos] = w;
+          ring_vidx[pos] = vidx;
+        }
+        wave_cnt += __popcll(mask);
+      };
+      auto park = [&](bool hit_a, bool hit_b, const uint4& w0, const uint4& w1, uint32_t vidx0, uint32_t vidx1) {
+        const uint64_t mask_a = ballot(hit_a), mask_b = ballot(hit_b);
+        if constexpr (kTall) {
+          if (mask_a != 0) {
+            if (wave_cnt + __popcll(mask_a) > kRing) expand();        // wave-uniform; 64 at most
+            put(hit_a, mask_a, w0, vidx0);
+          }
+          if (mask_b != 0) {
+            if (wave_cnt + __popcll(mask_b) > kRing) expand();
+            put(hit_b, mask_b, w1, vidx1);
+          }
+        } else if ((mask_a | mask_b) != 0) {
+          if (wave_cnt + __popcll(mask_a) + __popcll(mask_b) > kRing) {      // wave-uniform: the row is to be redone
+            lost = true;
+            wave_cnt = 0;
+          } else {
+            put(hit_a, mask_a, w0, vidx0);
+            put(hit_b, mask_b, w1, vidx1);
+            if (wave_cnt > kRingExpand) expand();
+          }
+        }
+      };
+      // The sum of a vector's, or of a pair's, exp2 terms, in a tree without an addition of zero.
+      auto sum_of = [&](auto& t) -> float {
+#pragma unroll
+        for (int w = int(sizeof(t) / sizeof(t[0])) / 2; w >= 1; w >>= 1)
+#pragma unroll
+          for (int e = 0; e < w; ++e) t[e] += t[e + w];
+        return t[0];
+      };
+      auto process_pair = [&](uint4 w0, uint4 w1, uint32_t vidx0, uint32_t vidx1, auto packed) -> float {
+        float a[E], b[E], t[2 * E];
+        const bool hit_a = HitTest<T>::hit(w0, tau), hit_b = HitTest<T>::hit(w1, tau);
+        if constexpr (decltype(packed)::value) {       // registers are short: the vectors wait in their packed form
+          park(hit_a, hit_b, w0, w1, vidx0, vidx1);
+          asm volatile("" : "+v"(w0.x), "+v"(w0.y), "+v"(w0.z), "+v"(w0.w), "+v"(w1.x), "+v"(w1.y), "+v"(w1.z), "+v"(w1.w));
+        }
         unpack<T>(w0, a);
         unpack<T>(w1, b);
-        const bool hit_a = vec_max<T>(a) > tau0, hit_b = vec_max<T>(b) > tau0;
-        float t[2 * E];
 #pragma unroll
         for (int e = 0; e < E; ++e) {
           t[e] = fast_exp2(__builtin_fmaf(a[e], k2, neg_c));
           t[E + e] = fast_exp2(__builtin_fmaf(b[e], k2, neg_c));
         }
-#pragma unroll
-        for (int w = E; w >= 1; w >>= 1)          // a tree: 2E - 1 additions, none of them with a zero
-#pragma unroll
-          for (int e = 0; e < w; ++e) t[e] += t[e + w];
-        const float pair_sum = t[0];
-        const uint64_t mask_a = ballot(hit_a), mask_b = ballot(hit_b);
-        if constexpr (kTall) {
-          auto park = [&](bool hit, uint64_t mask, const uint4& w, uint32_t vidx) {
-            const int n = __popcll(mask);
-            if (wave_cnt + n > kRing) {                // wave-uniform; n is 64 at most
-              expand_ring<T>(ring, ring_vidx, wave_cnt, tau0, head, cand, p.sort_cap, sh);
-              wave_cnt = 0;
-            }
-            const int pos = wave_cnt + lanes_below(mask);
-            if (hit) { ring[pos] = w; ring_vidx[pos] = vidx; }
-            wave_cnt += n;
-          };
-          if (mask_a != 0) park(hit_a, mask_a, w0, vidx0);
-          if (mask_b != 0) park(hit_b, mask_b, w1, vidx1);
-        } else if ((mask_a | mask_b) != 0) {
-          const int n_a = __popcll(mask_a);
-          const int pos_a = wave_cnt + lanes_below(mask_a);
-          const int pos_b = wave_cnt + n_a + lanes_below(mask_b);
-          if (hit_a) {
-            if (pos_a < kRing) { ring[pos_a] = w0; ring_vidx[pos_a] = vidx0; }
-          }
-          if (hit_b) {
-            if (pos_b < kRing) { ring[pos_b] = w1; ring_vidx[pos_b] = vidx1; }
-          }
-          wave_cnt += n_a + __popcll(mask_b);
-          lost |= wave_cnt > kRing;                    // some vector found no slot
-          if (wave_cnt > kRingExpand) {                // wave-uniform
-            expand_ring<T>(ring, ring_vidx, wave_cnt < kRing ? wave_cnt : kRing, tau0, head, cand, p.sort_cap, sh);
-            wave_cnt = 0;
-          }
-        }
+        const float pair_sum = sum_of(t);
+        if constexpr (!decltype(packed)::value) park(hit_a, hit_b, w0, w1, vidx0, vidx1);
         return pair_sum;
       };
+      // the second vector of a pair whose first is done
+      auto process_second = [&](const uint4& w1, uint32_t vidx1) -> float {
+        float b[E];
+        unpack<T>(w1, b);
+        const bool hit_b = HitTest<T>::hit(w1, tau);
+#pragma unroll
+        for (int e = 0; e < E; ++e) b[e] = fast_exp2(__builtin_fmaf(b[e], k2, neg_c));
+        const float sum = sum_of(b);
+        park(false, hit_b, w1, w1, vidx1, vidx1);
+        return sum;
+      };
 
+      if (n_stage > 0 && !early) issue_first();
       // the sample tiles, already in registers
       {
-        const uint32_t t1 = s_stride, t2 = 2 * s_stride, t3 = 3 * s_stride;
-        const float s01 = process_pair(d[0], d[1], tid, t1 * NT + tid);
-        const float s23 = process_pair(d[2], d[3], t2 * NT + tid, t3 * NT + tid);
-        dacc += double(s01 + s23);
+        const uint32_t t1 = s_stride;
+        float both = 0.0f;
+#pragma unroll 1
+        for (uint32_t t = 0; t <= 2 * t1; t += 2 * t1) {              // (s_stride > 0)
+          both += process_pair(d[0], d[1], t * NT + tid, (t + t1) * NT + tid, std::bool_constant<(kWavesPerSimd >= 8 && std::is_same<T, Bf16>::value)>{});
+          d[0] = d[2];
+          d[1] = d[3];
+        }
+        dacc += double(both);
       }
-      if (kTall || long_row) {
-        uint32_t seen_g = 0, seen_left = long_row || !kTall ? kBatch : 0;
-        // from here on a vector may lie past the row's end
-        const uint32_t ragged_g = nvec / NT > tile0 ? (nvec / NT - tile0) / kGroup : 0u;
-        static_assert(kStages % 2 == 0, "the fp32 sums of two stages are added up before they go to the fp64 total");
-        for (uint32_t g0 = 0; g0 < n_stage; g0 += kStages) {
-          float two = 0.0f;
+      uint32_t seen_g = long_row ? 0u : kNever;
+      // stages before this one are complete
+      const uint32_t ragged_g = nvec / NT > tile0 ? (nvec / NT - tile0) / kGroup : 0u;
+      // (a short row's stages go to the fp64 total one by one where 256 threads take it)
+      const bool apart = !kTall && !long_row;
+      static_assert(kStages % 2 == 0, "the fp32 sums of two stages are added up before they go to the fp64 total");
+      auto sample_stage = [&](uint32_t g) {                         // its first tile is done
+        const bool seen = __builtin_expect(g == seen_g, 0);
+        if (seen) seen_g = next_sample(g);
+        return seen;
+      };
+      uint32_t g0 = 0;
+      for (; g0 + kStages <= ragged_g; g0 += kStages) {
+        float two = 0.0f;
 #pragma unroll
-          for (int s = 0; s < kStages; ++s) {
-            const uint32_t g = g0 + s;
-            if (g < n_stage) {                                        // wave-uniform, no loads inside
-              const uint32_t v0 = (tile0 + g * kGroup) * NT + tid;
-              if (seen_left > 0 && g == seen_g) {                     // a sample stage: its first tile is done
-                seen_g += stride_g; --seen_left;
-                pipe[s][0] = neg_inf_vec<T>();
-              }
-              if (g >= ragged_g) {                                    // the ragged end
-                if (v0 >= nvec) pipe[s][0] = neg_inf_vec<T>();
-                if (v0 + NT >= nvec) pipe[s][1] = neg_inf_vec<T>();
-              }
-              const float ps = process_pair(pipe[s][0], pipe[s][1], v0, v0 + NT);
-              two = (s & 1) ? two + ps : ps;
-            }
-            if ((s & 1) && g0 + s - 1 < n_stage) dacc += double(two);   // (a lone last stage left its sum in `two`)
-            issue(g + kStages, pipe[s]);
-          }
-        }
-      } else {
-        // a short row: the tiles after the sample, which may be incomplete
-        for (uint32_t t = kBatch; t < n_tiles; t += 2) {
-          const uint32_t v0 = t * NT + tid, v1 = v0 + NT;
-          d[0] = neg_inf_vec<T>();
-          d[1] = neg_inf_vec<T>();
-          if (v0 < nvec) d[0] = load_vec_stream(&rs.body[v0]);
-          if (v1 < nvec) d[1] = load_vec_stream(&rs.body[v1]);
-          dacc += double(process_pair(d[0], d[1], v0, v1));
+        for (int s = 0; s < kStages; ++s) {
+          const uint32_t g = g0 + s;
+          const uint32_t v0 = (tile0 + g * kGroup) * NT + tid;
+          // (their distance is a multiple of kUnit tiles)
+          const bool seen = s % (kUnit / kGroup) == 0 && sample_stage(g);
+          const float ps = seen ? process_second(pipe[s][1], v0 + NT) : process_pair(pipe[s][0], pipe[s][1], v0, v0 + NT, std::false_type{});
+          two = (s & 1) && !apart ? two + ps : ps;
+          if ((s & 1) || apart) dacc += double(two);
+          issue(g + kStages, pipe[s]);
         }
       }
-      expand_ring<T>(ring, ring_vidx, wave_cnt < kRing ? wave_cnt : kRing, tau0, head, cand, p.sort_cap, sh);
+      // the row's end: fewer than kStages complete stages, then perhaps one that is not
+      float two = 0.0f;
+#pragma unroll 1
+      for (uint32_t g = g0; g < n_stage; ++g) {
+        const uint32_t v0 = (tile0 + g * kGroup) * NT + tid;
+        if (sample_stage(g)) pipe[0][0] = neg_inf_vec<T>();
+        if (v0 >= nvec) pipe[0][0] = neg_inf_vec<T>();
+        if (v0 + NT >= nvec) pipe[0][1] = neg_inf_vec<T>();
+        const float ps = process_pair(pipe[0][0], pipe[0][1], v0, v0 + NT, std::false_type{});
+        const bool odd = (g - g0) & 1;
+        two = odd && !apart ? two + ps : ps;
+        if (odd || apart || g + 1 == n_stage) dacc += double(two);    // (a lone last stage's sum is added as it is)
+#pragma unroll
+        for (int s = 0; s + 1 < kStages; ++s) { pipe[s][0] = pipe[s + 1][0]; pipe[s][1] = pipe[s + 1][1]; }
+      }
+      expand();
       if (lost && lane == 0) sh.overflow = 1;
       // edge elements (row not 16-byte aligned, or V not a whole number of vectors)
       if (tid < n_edge) {
@@ -713,36 +807,43 @@ __global__ __launch_bounds__(NT, kWavesPerSimd) void truncate_kernel(const Trunc
           if (pos < p.sort_cap) cand[pos] = make_cand(edge_v, uint32_t(edge_i));
         }
       }
-      z_c = block_sum_f64<NW>(dacc, sh.red);
+      dacc = wave_sum_f64(dacc);
+      if (lane == 0) sh.red.d[wave] = dacc;
       __syncthreads();
+#pragma unroll
+      for (int w = 0; w < NW; ++w) z_c += sh.red.d[w];
       n_cand = sh.cand_count;
       fast_ok = !sh.overflow && n_cand <= p.sort_cap && n_cand >= p.k_sel && z_c > 0.0 && z_c < INFINITY;
-      __syncthreads();
     }
   }
 
+  // a row's uniforms, one per lane, travel during the sort
+  static_assert(kMaxDraws <= 64, "a lane to a draw");
+  const float u_lane = p.u && lane < p.n_samples ? p.u[size_t(row_i) * p.n_samples + lane] : 0.0f;
   if (!fast_ok) {
+    __syncthreads();                                  // the counts and sums above have been read
     st |= 256;
     const bool need_sum = !(z_c > 0.0 && z_c < INFINITY);
     n_cand = two_pass_select<T, NT, kWavesPerSimd == 4>(row, rs, p.k_sel, p.k2, cand, p.sort_cap, sort_tmp, sort_tmp_cap, tables, sh, need_sum,
                                 c_ref, z_c, st);
-    if (n_cand < 0) n_cand = exact_select<T, NT>(row, p.V, p.k_sel, p.k2, cand, tables, sh, c_ref, z_c, st);
   }
 
   // ---- sort the candidates into canonical order ------------------------------------------------
-  __syncthreads();
-  if (!bucket_sort_desc<NT>(cand, n_cand, sort_tmp, sort_tmp_cap, cand, p.k_sel, tables, tables + 256, tables + 512,
-                        sh.red)) {
+  // (behind a barrier since the candidates were written; what the sort writes first is not what was read since)
+  for (;;) {
+    if (n_cand < 0) n_cand = exact_select<T, NT>(row, p.V, p.k_sel, p.k2, cand, tables, sh, c_ref, z_c, st);
+    if (bucket_sort_desc<NT>(cand, n_cand, sort_tmp, sort_tmp_cap, cand, p.k_sel, tables, sh.red)) break;
     // the bin at the k-th place is too crowded for the scratch space (a row full of ties): radix selection
     // delivers exactly k candidates, which always fit
     st |= 256;
-    n_cand = exact_select<T, NT>(row, p.V, p.k_sel, p.k2, cand, tables, sh, c_ref, z_c, st);
-    bucket_sort_desc<NT>(cand, n_cand, sort_tmp, sort_tmp_cap, cand, p.k_sel, tables, tables + 256, tables + 512, sh.red);
+    n_cand = -1;
   }
   const int k_eff = n_cand < p.k_sel ? n_cand : p.k_sel;
 
   // ---- fp64 evaluation of the kept head: Top-rho, renormalisation, outputs -----------------------
   // thread t owns entries [t*per, t*per + per) so that a block scan gives prefix masses in order
+  // (Every exchange between waves below is one barrier: what a wave leaves in sh.red is read behind it, and is not written
+  // again until another has passed.)
   const int per = (k_eff + NT - 1) / NT;       // 0..kMaxPer
   constexpr int kMaxPer = 1024 / NT;
   double e64[kMaxPer];
@@ -768,9 +869,21 @@ __global__ __launch_bounds__(NT, kWavesPerSimd) void truncate_kernel(const Trunc
       head32 += double(fast_exp2(__builtin_fmaf(v, p.k2, -c_ref)));
     }
   }
-  double head64;
-  const double excl = block_excl_scan_f64<NW>(local, sh.red, head64);
-  head32 = block_sum_f64<NW>(head32, sh.red);
+  double excl = wave_incl_scan_f64(local), head64 = 0.0;
+  head32 = wave_sum_f64(head32);
+  if (lane == 63) { sh.red.d[wave] = excl; sh.red.d[NW + wave] = head32; }
+  __syncthreads();
+  {
+    double base = 0.0;
+    head32 = 0.0;
+#pragma unroll
+    for (int w = 0; w < NW; ++w) {
+      base += w < wave ? sh.red.d[w] : 0.0;
+      head64 += sh.red.d[w];
+      head32 += sh.red.d[NW + w];
+    }
+    excl = base + excl - local;
+  }
   // normaliser relative to the row maximum: fp32 tail rescaled to that reference + fp64 head
   double tail = z_c - head32;
   if (tail < 0.0) tail = 0.0;
@@ -789,7 +902,12 @@ __global__ __launch_bounds__(NT, kWavesPerSimd) void truncate_kernel(const Trunc
         below += run < thr ? 1 : 0;
       }
     }
-    below = block_sum_i32<NW>(below, sh.red);
+    below = wave_sum_i32(below);
+    if (lane == 0) sh.red.i[wave] = below;
+    __syncthreads();
+    below = 0;
+#pragma unroll
+    for (int w = 0; w < NW; ++w) below += sh.red.i[w];
     count = below + 1 < k_eff ? below + 1 : k_eff;
   }
   // mass of the kept set: inclusive prefix at entry count-1
@@ -811,6 +929,19 @@ __global__ __launch_bounds__(NT, kWavesPerSimd) void truncate_kernel(const Trunc
   // the rounded values (q_hat is the softmax of what the receiver gets)
   double pw[kMaxPer];
   double p_excl = excl, p_total = c_sel;
+  auto scan_again = [&](double v, double& before, double& total) {      // block_excl_scan_f64 with one barrier
+    const double inc = wave_incl_scan_f64(v);
+    if (lane == 63) sh.red.d[wave] = inc;
+    __syncthreads();
+    double base = 0.0;
+    total = 0.0;
+#pragma unroll
+    for (int w = 0; w < NW; ++w) {
+      base += w < wave ? sh.red.d[w] : 0.0;
+      total += sh.red.d[w];
+    }
+    before = base + inc - v;
+  };
 #pragma unroll
   for (int r = 0; r < kMaxPer; ++r) pw[r] = e64[r];
   if (p.payload != kPayloadF32) {
@@ -826,7 +957,7 @@ __global__ __launch_bounds__(NT, kWavesPerSimd) void truncate_kernel(const Trunc
         mine += pw[r];
       }
     }
-    p_excl = block_excl_scan_f64<NW>(mine, sh.red, p_total);
+    scan_again(mine, p_excl, p_total);
     if (!(p_total > 0.0)) p_total = 1.0;
   }
 
@@ -858,7 +989,7 @@ __global__ __launch_bounds__(NT, kWavesPerSimd) void truncate_kernel(const Trunc
     double w_total = count > 0 ? p_total : 0.0;
     for (int c = 0; c < p.n_samples; ++c) {
       const size_t o = size_t(row_i) * p.n_samples + c;
-      const double target = double(p.u[o]) * w_total;
+      const double target = double(__int_as_float(__builtin_amdgcn_readlane(__float_as_int(u_lane), c))) * w_total;
       int not_above = 0, last_pos = -1;
       double run = p_excl;
 #pragma unroll
@@ -870,8 +1001,20 @@ __global__ __launch_bounds__(NT, kWavesPerSimd) void truncate_kernel(const Trunc
           if (pw[r] > 0.0) last_pos = i;
         }
       }
-      int slot = w_total > 0.0 ? block_sum_i32<NW>(not_above, sh.red) : -1;
-      if (slot >= count) slot = block_max_i32<NW>(last_pos, sh.red);   // only for u >= 1 (uniform branch)
+      int slot = -1;
+      if (w_total > 0.0) {                                             // uniform
+        int* part = c & 1 ? reinterpret_cast<int*>(sh.red.f) : sh.red.i;
+        not_above = wave_sum_i32(not_above);
+        if (lane == 0) part[wave] = not_above;
+        __syncthreads();
+        slot = 0;
+#pragma unroll
+        for (int w = 0; w < NW; ++w) slot += part[w];
+      }
+      if (slot >= count) {                                             // only for u >= 1 (uniform branch)
+        slot = block_max_i32<NW>(last_pos, sh.red);
+        __syncthreads();
+      }
 #pragma unroll
       for (int r = 0; r < kMaxPer; ++r)
         if (r < per && tid * per + r == slot) p.out_token[o] = int32_t(idx[r]);
@@ -887,7 +1030,7 @@ __global__ __launch_bounds__(NT, kWavesPerSimd) void truncate_kernel(const Trunc
           if (r < per && i == slot) pw[r] = 0.0;
           if (r < per && i < count) rest += pw[r];
         }
-        p_excl = block_excl_scan_f64<NW>(rest, sh.red, w_total);
+        scan_again(rest, p_excl, w_total);
       }
     }
   }

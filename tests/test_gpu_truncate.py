@@ -266,3 +266,23 @@ def test_truncate_on_either_side_of_the_shapes(tslt, dtype, V, rows):
         assert torch.equal(few[k], many[k][:rows]), k
     torch.testing.assert_close(few["mass"], many["mass"][:rows], rtol=2.5e-7, atol=0)      # fp32 terms in another order
     P.compare_truncate({k: x[:8] for k, x in few.items()}, z[:8], 0.9, 0, 0.9, 64, label=f"{dtype} {V}")
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f16", "f32"])
+@pytest.mark.parametrize("rows", [3, 520])
+def test_truncate_at_the_ends_of_a_rows_stages(tslt, dtype, rows):
+    """Rows that end at, before and behind a tile (16 bytes a thread), a stage (two tiles) and a turn of the pipeline,
+    by 512 threads (3 rows) and by 256 (520), with thresholds of either sign."""
+    per = 4 if dtype == "f32" else 8
+    tiles = 256 * per
+    for n, (V, shift) in enumerate([(4 * tiles, 0.0), (4 * tiles + 1, -12.0), (5 * tiles - 7, 12.0), (6 * tiles + tiles - per, 0.0),
+                                    (10 * tiles, -3.0), (16 * tiles, 2.0), (17 * tiles + 9, 0.0), (19 * tiles - per, -30.0),
+                                    (22 * tiles + tiles // 2 + 1, 0.0), (33 * tiles - 1, 5.0)]):
+        w = W.scaled(W.WORKLOADS["chain_topk"], V=V, dtype=dtype)
+        z = rows_like(w, rows, 40 + n) + shift
+        k = (16, 40, 200)[n % 3]
+        out = tslt.truncate(z, 0.8, 0, 0.95, k)
+        torch.cuda.synchronize()
+        some = [0, 1, rows // 2, rows - 1]
+        got = {name: t[some] for name, t in out.items() if t is not None}
+        P.compare_truncate(got, z[some], 0.8, 0, 0.95, k, label=f"{dtype} V={V} rows={rows} shift={shift}")
