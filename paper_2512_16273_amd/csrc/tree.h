@@ -199,36 +199,63 @@ __global__ __launch_bounds__(kRowThreads, kWavesPerSimd) void tree_node_kernel(c
   }
 }
 
-// The new-sequence search through the layers that have been evaluated: lane 0 of the calling wave appends the outputs
-// to out_seq and notes the candidates that were tested.
+// The new-sequence search through the layers that have been evaluated: all threads of the calling workgroup; the first
+// appends the outputs to out_seq and notes the candidates that were tested.  The nodes' accepted children, outputs and
+// status words are brought into LDS first, all at once, where they fit (`room` words at `nodes`): one memory latency in
+// place of one for every layer (two trees of 1365 nodes in six layers: 12 us by one thread out of memory, 5 so).
 struct TreeWalk {
   int first_cand[kMaxTreeDepth + 1], n_cand[kMaxTreeDepth + 1];      // of every node passed
   int n_passed, node, layer, len, status, done;
+  int all_status;                                                    // of every node evaluated (if they were looked at)
 };
-__device__ __forceinline__ void tree_walk(const TreeParams& p, int64_t b, TreeWalk& w) {
-  int32_t* seq = p.out_seq + size_t(b) * (p.depth + 1);
-  int node = 0, layer = 0, len = 0, st = 0, done = 0;
-  while (!done && layer < p.n_eval_layers) {
-    const int64_t n = b * p.n_nodes + node;
-    st |= p.node_status[n];
-    seq[len++] = p.node_token[n];
-    done = 1;
-    if (node >= p.n_int) break;
-    const int child = tree_first_child(p, node, layer);
-    w.first_cand[layer] = child - 1;
-    w.n_cand[layer] = p.expansion[layer];
-    ++layer;
-    if (p.node_state[n] == 1) {
-      node = child + p.node_slot[n];
-      done = 0;
+__device__ __forceinline__ void tree_walk(const TreeParams& p, int64_t b, TreeWalk& w, int32_t* nodes, int room) {
+  const int tid = threadIdx.x, n = p.n_eval;
+  const bool here = 3 * n <= room;
+  if (tid == 0) w.all_status = 0;
+  __syncthreads();
+  if (here || p.all_nodes) {
+    int st = 0;
+    for (int i = tid; i < n; i += blockDim.x) {
+      const int64_t at = b * p.n_nodes + i;
+      const int status = p.node_status[at];
+      st |= status;
+      if (here) {
+        nodes[i] = p.node_slot[at];
+        nodes[n + i] = p.node_token[at];
+        nodes[2 * n + i] = status;
+      }
     }
+    st = wave_or_i32(st);
+    if (lane_id() == 0 && st) atomicOr(&w.all_status, st);
   }
-  w.n_passed = layer;
-  w.node = node;
-  w.layer = layer;
-  w.len = len;
-  w.status = st;
-  w.done = done;
+  __syncthreads();
+  if (tid == 0) {
+    int32_t* seq = p.out_seq + size_t(b) * (p.depth + 1);
+    int node = 0, layer = 0, len = 0, st = 0, done = 0;
+    while (!done && layer < p.n_eval_layers) {
+      const int64_t at = b * p.n_nodes + node;
+      st |= here ? nodes[2 * n + node] : p.node_status[at];
+      seq[len++] = here ? nodes[n + node] : p.node_token[at];
+      done = 1;
+      if (node >= p.n_int) break;
+      const int child = tree_first_child(p, node, layer);
+      w.first_cand[layer] = child - 1;
+      w.n_cand[layer] = p.expansion[layer];
+      ++layer;
+      const int slot = here ? nodes[node] : p.node_slot[at];         // -1 unless a child was accepted
+      if (slot >= 0) {
+        node = child + slot;
+        done = 0;
+      }
+    }
+    w.n_passed = layer;
+    w.node = node;
+    w.layer = layer;
+    w.len = len;
+    w.status = st;
+    w.done = done;
+  }
+  __syncthreads();
 }
 // The ratios and rates of the candidates of all other nodes: NaN.
 __device__ __forceinline__ void tree_clear_others(const TreeParams& p, int64_t b, const TreeWalk& w) {
@@ -241,25 +268,19 @@ __device__ __forceinline__ void tree_clear_others(const TreeParams& p, int64_t b
   }
 }
 
-// One wave per tree, after every node has been evaluated.
-__global__ __launch_bounds__(64) void tree_walk_kernel(const TreeParams p) {
+// One workgroup per tree, after every node has been evaluated.
+constexpr int kWalkNodes = 3 * 4000;                                 // words: 47 KB
+__global__ __launch_bounds__(1024) void tree_walk_kernel(const TreeParams p) {
   __shared__ TreeWalk w;
+  extern __shared__ __align__(16) unsigned char dyn_lds[];
   const int64_t b = blockIdx.x;
-  const int lane = threadIdx.x;
-  int st = 0;
-  if (p.all_nodes) {
-    for (int n = lane; n < p.n_nodes; n += 64) st |= p.node_status[b * p.n_nodes + n];
-    st = wave_or_i32(st);
-  }
-  if (lane == 0) {
-    tree_walk(p, b, w);
+  tree_walk(p, b, w, reinterpret_cast<int32_t*>(dyn_lds), 3 * p.n_eval <= kWalkNodes ? kWalkNodes : 0);
+  if (threadIdx.x == 0) {
     p.out_len[b] = w.len;
     for (int i = w.len; i <= p.depth; ++i) p.out_seq[size_t(b) * (p.depth + 1) + i] = -1;
-    if (p.status) p.status[b] = p.all_nodes ? st : w.status;
+    if (p.status) p.status[b] = p.all_nodes ? w.all_status : w.status;
   }
-  if (p.all_nodes) return;
-  __syncthreads();
-  tree_clear_others(p, b, w);
+  if (!p.all_nodes) tree_clear_others(p, b, w);
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -404,8 +425,7 @@ __global__ __launch_bounds__(kRowThreads) void tree_path_kernel(const TreeParams
   const double* items = nullptr;
   if constexpr (kFrom == kFromHead) {
     __shared__ TreeWalk walk;
-    if (tid == 0) tree_walk(p, b, walk);
-    __syncthreads();
+    tree_walk(p, b, walk, reinterpret_cast<int32_t*>(dyn_lds), int(Terms::kBytes / 4));      // (the terms' table comes later)
     tree_clear_others(p, b, walk);
     node = walk.node;
     layer = walk.layer;
@@ -519,7 +539,8 @@ template <typename T, typename Terms> hipError_t launch_verify_tree_with(TreePar
   }
   if (p.n_eval == 0) return walk(tree_path_kernel<T, Terms, kFromRoot>);
   if (p.n_eval_layers <= p.depth) return walk(tree_path_kernel<T, Terms, kFromHead>);
-  hipLaunchKernelGGL(tree_walk_kernel, dim3(unsigned(p.B)), dim3(64), 0, s, p);
+  const int threads = std::min(1024, (p.n_eval + 63) / 64 * 64);
+  hipLaunchKernelGGL(tree_walk_kernel, dim3(unsigned(p.B)), dim3(threads), 3 * p.n_eval <= kWalkNodes ? 12 * p.n_eval : 0, s, p);
   return hipGetLastError();
 }
 template <typename T> hipError_t launch_verify_tree(const TreeParams& p, hipStream_t s) {

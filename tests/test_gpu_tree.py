@@ -298,3 +298,29 @@ def test_tree_path_walked_quickly(tslt, dtype, B, expansion, V, rule):
             # random errors of the terms (2^-24 of an exponent up to 40, over hundreds of terms), the outputs' rounding,
             # and both magnified by what an earlier stage's residual divides by
             np.testing.assert_allclose(path[k][b][on], out[k][b][on], rtol=1e-6, atol=1e-9, err_msg=f"tree {b}")
+
+
+@pytest.mark.parametrize("expansion", [(15, 16, 15), (16, 16, 16), (16, 16, 15)])      # 3856, 4369 and 4113 nodes
+def test_tree_search_through_many_nodes(tslt, expansion):
+    """The search out of LDS and, for the larger trees, out of memory: the sequence and status of the walk node by node."""
+    w = W.scaled(W.WORKLOADS["tree"], B=3, V=260, expansion=expansion, top_k=8, k_cap=8, noise_t=0.3)
+    tree = W.make_tree(w, 11, DEV)
+    n_int = tree["target"].shape[1] - int(np.prod(expansion))
+    sets = tslt.truncate(tree["draft"].reshape(-1, w.V), w.T, w.top_k, w.top_p, w.k_cap)
+    g = torch.Generator(device="cpu").manual_seed(3)
+    n_nodes = tree["target"].shape[1]
+    idx = sets["idx"].view(w.B, n_int, w.k_cap)
+    cand, node = [], 0
+    for layer, k in enumerate(expansion):
+        width = int(np.prod(expansion[:layer], dtype=np.int64))
+        pick = torch.randint(0, 8, (w.B, width, k), generator=g).to(DEV)
+        cand.append(idx[:, node:node + width].gather(2, pick).reshape(w.B, -1))
+        node += width
+    cand = torch.cat(cand, 1).contiguous()
+    args = (tree["target"], w.T, list(expansion), idx.contiguous(), sets["logit"].view(w.B, n_int, w.k_cap),
+            sets["count"].view(w.B, n_int), cand, tree["u_accept"], tree["u_resample"])
+    every, path = tslt.verify_tree(*args, all_nodes=True), tslt.verify_tree(*args, all_nodes=False)
+    torch.cuda.synchronize()
+    assert every["node_token"].shape == (w.B, n_nodes)
+    assert torch.equal(every["seq"], path["seq"]) and torch.equal(every["len"], path["len"])
+    assert int(every["len"].max()) > 1
