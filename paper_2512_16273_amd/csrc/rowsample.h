@@ -334,7 +334,7 @@ template <typename T> __device__ __forceinline__ void row_store_set(const RowWor
 // The masses of the row's items, referenced to 0: of its runs run0 .. run1 - 1, and with `ends` of the elements before and
 // after its aligned body; and sh.flags, as of run_sum.  A wave takes run run0 + `wave` first and then whichever run is next (a counter in
 // LDS), so that the waves end together.  Every request of the loop is unconditional (a vector past the row's end
-// is read from the row's last vector and its sum dropped; a run past the last is the last one again, to no
+// is read from the row's last vector, or as zeros, and its sum dropped; a run past the last likewise, to no
 // effect): with requests inside branches the number in flight is not known where a wait is placed, and the wait
 // for the current run would wait for the run requested ahead as well.  While the first requests travel the terms'
 // table is made: all of it (half -1), its second half (1) or nothing (-2).
@@ -363,12 +363,22 @@ __device__ __forceinline__ void row_pass(RowWork<T>& w, double* table, int half,
   }
   if (run0 < run1) {
     const uint32_t last_vec = uint32_t(rs.nvec - 1), nvec = uint32_t(rs.nvec);
+    // (PowTerms: through a buffer, which takes the addresses out of the vector registers, streams past the caches and gives
+    // zeros past the row's end; with 64 registers a thread the sweep spills less.  Two fp32 trees of 1365 nodes, V = 151936,
+    // every node: 319 us by plain loads, 291 so; 60 binary16 trees <4,2,2,1> of 32000 94 and 86; 24 x 5 binary16 rows of 55257
+    // 19.4 and 18.5.  BitTerms, bound by the LDS, gain nothing: 64 bfloat16 trees <2,2,2> of 128256 57 and 63.)
+    const __amdgpu_buffer_rsrc_t body = row_buffer(rs.body, nvec);
     auto request = [&](int run, uint4 (&q)[kSegVecs]) {
-      const uint32_t vbase = uint32_t(run < run1 ? run : run1 - 1) * kRunVecs + lane;
+      if constexpr (!Terms::kBits) {
 #pragma unroll
-      for (int i = 0; i < kSegVecs; ++i) {
-        const uint32_t vi = vbase + i * 64;
-        q[i] = load_vec(&rs.body[vi < last_vec ? vi : last_vec]);
+        for (int i = 0; i < kSegVecs; ++i) q[i] = buffer_load_vec_stream(body, lane * 16u, uint32_t(run) * (kRunVecs * 16u) + i * 1024u);
+      } else {
+        const uint32_t vbase = uint32_t(run < run1 ? run : run1 - 1) * kRunVecs + lane;
+#pragma unroll
+        for (int i = 0; i < kSegVecs; ++i) {
+          const uint32_t vi = vbase + i * 64;
+          q[i] = load_vec(&rs.body[vi < last_vec ? vi : last_vec]);
+        }
       }
     };
     auto consume = [&](int run, const uint4 (&q)[kSegVecs]) {
