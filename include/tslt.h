@@ -58,7 +58,7 @@ enum {
   TSLT_OK = 0,
   TSLT_ERR_INVALID_ARG = -1,
   TSLT_ERR_UNSUPPORTED = -2,  /* a size beyond what the kernels are built for (see TSLT_MAX_K_CAP) */
-  TSLT_ERR_WORKSPACE = -3,    /* workspace missing, misaligned or smaller than tslt_workspace_bytes() */
+  TSLT_ERR_WORKSPACE = -3,    /* workspace missing, misaligned or too small (tslt_workspace_bytes()) */
   TSLT_ERR_HIP = -4           /* a HIP runtime call failed */
 };
 
@@ -94,7 +94,8 @@ const char* tslt_last_error(void);
 
 /* Bytes of workspace an operation needs.  `n_outer` is the number of rows (truncate, sample) or of
  * sequences B (verify, verify_tree); `n_inner` is gamma (verify) or N_nodes (verify_tree), ignored
- * otherwise.  Returns 0 when the operation uses none. */
+ * otherwise.  Returns 0 when the operation uses none.  (verify, and verify_tree for the path alone, run with the
+ * smaller sizes of earlier versions too; they then leave a small batch's rows to one workgroup each.) */
 size_t tslt_workspace_bytes(int op, int64_t n_outer, int64_t n_inner, int64_t V, int32_t k_cap);
 
 /* Truncated sampling on logits (Section 3.1; Solution 1 of Section 3.2), one draft row per position.

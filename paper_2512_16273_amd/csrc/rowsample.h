@@ -5,9 +5,9 @@
 //   row_locate, row_pick   the token at which the cumulative mass of p, or of what the updates made of it, passes
 //                u * total, in ascending token index: the run that holds it, then the element
 // fp64 is needed for the sampling: at V >= 128k the buckets of the inverse CDF are far narrower than fp32 prefix
-// sums can resolve.  One workgroup per row keeps the sums in LDS and one pass serves the test and the sample.  Inside a
-// launch, workgroups that share a row would have to hand their sums over through a device-scope fence each; where a
-// second launch follows anyway its boundary does that (row_fetch; trees only).
+// sums can resolve.  One workgroup per row keeps the sums in LDS and one pass serves the test and the sample.  Where few
+// long rows leave compute units idle several workgroups sweep one and a second launch takes up the sums (row_part,
+// row_fetch): its boundary hands them over, where inside a launch every workgroup would need a device-scope fence.
 #pragma once
 #include <algorithm>
 #include <type_traits>
@@ -499,8 +499,26 @@ __device__ __forceinline__ void row_sweep(RowWork<T>& w, double* table, int half
   }
 }
 
-// The row as row_sweep leaves it, from masses that other workgroups have made of it (row_pass, then stored; NaN where a
-// part met something that asks for a sweep by the row's maximum).  sh.fetched is 0, as published by a barrier.
+// One of `parts` workgroups that share a row: the masses of its runs, and the first one's of the elements outside the aligned
+// body, stored for a launch that takes them up; NaN where it met something that asks for a sweep by the row's maximum.
+template <typename T, typename Terms>
+__device__ __forceinline__ void row_part(RowWork<T>& w, double* table, int part, int parts, double* out, RowShared& sh) {
+  w.count = 0;                                       // no set
+  w.y = -1;
+  w.ql = w.ql0 = 0.0f;
+  const int per = (w.n_runs + parts - 1) / parts;
+  const int run0 = part * per, run1 = run0 + per < w.n_runs ? run0 + per : w.n_runs;
+  row_pass<T, Terms>(w, table, -1, run0, run1, part == 0, sh);
+  const bool broken = (sh.flags & 3) != 0;
+  const double bad = __longlong_as_double(0x7FF8000000000000ll);
+  for (int i = run0 + threadIdx.x; i < run1; i += kRowThreads) out[1 + i] = broken ? bad : sh.items[1 + i];
+  if (part == 0 && threadIdx.x < 2) {
+    const int i = threadIdx.x == 0 ? 0 : w.n_items - 1;
+    out[i] = broken ? bad : sh.items[i];
+  }
+}
+
+// The row as row_sweep leaves it, from masses that other workgroups have made of it (row_part).  sh.fetched is 0, as published by a barrier.
 template <typename T, typename Terms>
 __device__ __forceinline__ void row_fetch(RowWork<T>& w, const double* items, double* table, RowShared& sh) {
   const int tid = threadIdx.x, lane = lane_id();
@@ -513,6 +531,28 @@ __device__ __forceinline__ void row_fetch(RowWork<T>& w, const double* items, do
   if (lane == 0 && seen) atomicOr(&sh.fetched, seen);
   __syncthreads();
   if (__builtin_amdgcn_readfirstlane(sh.fetched) != 2) row_sweep<T, Terms>(w, table, -1, sh);
+}
+
+constexpr int64_t kShareRows = 128;                  // at most, by two workgroups or more
+constexpr int64_t kShareLeastV = 50000;              // of any type
+// Workgroups that share each of `rows` rows (1: none do): as many as fill the chip, a run for every wave at least.  A launch
+// more (two microseconds, and a table made again) against the sweep of a row by one compute unit, so rows from the
+// length on where that is some 6 us (BitTerms' terms are the cheapest, and binary16 has twice fp32's in a run).  us a round by
+// one workgroup a row / shared, 1 x 4 and 8 x 8: fp32 32000 14.1 / 15.0 and 15.3 / 16.9, 64000 18.3 / 15.4 and 19.1 / 17.9,
+// 128256 25.3 / 15.4 and 26.4 / 20.7, 256000 40.1 / 15.6 and 42.2 / 26.7; binary16 64000 19.2 / 18.1 and 19.6 / 19.0, 128256
+// 26.1 / 17.5 and 27.0 / 21.3; bfloat16 64000 15.8 / 17.5 and 16.9 / 18.0, 128256 19.9 / 17.1 and 20.6 / 19.3, 256000 26.4 / 17.1
+// and 27.5 / 21.5.  The sampled rows of larger batches alone: 48 x 5 fp32 V = 151936 53.2 / 43.9, 64 x 8 bfloat16 256000 67.5 / 61.3.
+// By two workgroups a row (more than a third as many rows as compute units) later: 16 x 7 bfloat16 112000 19.9 / 20.5, 128256
+// 20.7 / 20.5; 9 x 13 fp32 60000 22.6 / 23.3, 16 x 7 64000 19.7 / 19.4.
+template <typename T, typename Terms> inline int64_t share_min_V(bool by_two) {
+  if (ElemTraits<T>::kBytes == 4) return by_two ? 64000 : kShareLeastV;
+  if (Terms::kBits) return by_two ? 125000 : 100000;
+  return 60000;
+}
+template <typename T, typename Terms> inline int row_parts(int64_t V, int64_t rows) {
+  if (rows > kShareRows || V < share_min_V<T, Terms>(3 * rows > compute_units())) return 1;
+  const int64_t runs = V / (ElemTraits<T>::kPerVec * kRunVecs) + 1;
+  return int(std::max<int64_t>(1, std::min<int64_t>(compute_units() / rows, (runs + kRowWaves - 1) / kRowWaves)));
 }
 
 // Passes over the set's entries by one wave, four per lane at a time: load(k, i) for all four first, so that their

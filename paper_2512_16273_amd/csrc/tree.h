@@ -48,9 +48,12 @@ struct TreeParams {
   // (path only, tree_quick_kernel first)
   int32_t* walk_node;     // [B] where the quick walk stopped
   int32_t* walk_status;   // [B] status bits of the nodes before it
-  double* items;          // [B, items_stride] masses of that node's row
+  // masses of shared rows' items: of the node where the quick walk stopped [B, items_stride], or of every node evaluated at
+  // once [B, n_eval, items_stride]
+  double* items;
   int64_t items_stride;
-  int parts;              // workgroups that share that row
+  int64_t items_rows;     // there is room for
+  int parts;              // workgroups that share a row
   int all_nodes;
   int n_eval;             // nodes of a tree that tree_node_kernel evaluates: whole layers from the root
   int n_eval_layers;
@@ -58,15 +61,24 @@ struct TreeParams {
 
 // (Evaluating every node uses the node arrays alone.  The rest, two words a tree and the masses of a row's items, is for the
 // path; with node outputs it is still asked for once a node: the size that callers have been told all along, so that a
-// workspace kept from an earlier version and one sized by this one are the same.)
-inline size_t tree_workspace_bytes(int64_t B, int64_t n_nodes, int64_t V, bool all_nodes) {
+// workspace kept from an earlier version and one sized by this one are the same.  For the path a call may be given less
+// than it is told to bring: the rows of a small tree's nodes are then not shared.)
+inline int64_t tree_items_stride(int64_t V) { return int64_t(row_segments(V)) * kSubChunks + 2; }
+inline size_t tree_least_workspace_bytes(int64_t B, int64_t n_nodes, int64_t V, bool all_nodes) {
   const size_t n_seg = size_t(row_segments(V));
   const size_t tasks = all_nodes ? size_t(n_nodes) : 1;
   return align256(size_t(B) * n_nodes * 4) * 4 + align256(size_t(B) * 4) * 2 +
          align256(size_t(B) * tasks * (n_seg + 2) * 16) +
          align256(size_t(B) * tasks * n_seg * kSubChunks * sizeof(double));
 }
-inline void tree_carve_workspace(TreeParams& p, void* ws) {
+inline size_t tree_workspace_bytes(int64_t B, int64_t n_nodes, int64_t V, bool all_nodes) {
+  const size_t least = tree_least_workspace_bytes(B, n_nodes, V, all_nodes);
+  if (V < kShareLeastV) return least;
+  const size_t arrays = align256(size_t(B) * n_nodes * 4) * 4 + align256(size_t(B) * 4) * 2;
+  const size_t rows = arrays + align256(size_t(std::min(B * n_nodes, kShareRows) * tree_items_stride(V)) * sizeof(double));
+  return std::max(least, rows);
+}
+inline void tree_carve_workspace(TreeParams& p, void* ws, size_t ws_bytes) {
   char* w = reinterpret_cast<char*>(ws);
   const size_t per = align256(size_t(p.B) * p.n_nodes * 4);
   p.node_state = reinterpret_cast<int32_t*>(w); w += per;
@@ -76,7 +88,8 @@ inline void tree_carve_workspace(TreeParams& p, void* ws) {
   p.walk_node = reinterpret_cast<int32_t*>(w); w += align256(size_t(p.B) * 4);
   p.walk_status = reinterpret_cast<int32_t*>(w); w += align256(size_t(p.B) * 4);
   p.items = reinterpret_cast<double*>(w);
-  p.items_stride = int64_t(row_segments(p.V)) * kSubChunks + 2;
+  p.items_stride = tree_items_stride(p.V);
+  p.items_rows = int64_t((ws_bytes - size_t(w - reinterpret_cast<char*>(ws))) / (size_t(p.items_stride) * sizeof(double)));
 }
 
 template <typename T> __device__ __forceinline__ const void* tree_row(const TreeParams& p, int64_t b, int node) {
@@ -180,14 +193,21 @@ __device__ __forceinline__ int tree_node(const TreeParams& p, int64_t b, int nod
 // ---------------------------------------------------------------------------------------------
 // Every node of the layers wanted: one workgroup per node.
 // ---------------------------------------------------------------------------------------------
-template <typename T, typename Terms, int kWavesPerSimd>
+// (kItems: their rows' masses have been made by tree_share_kernel.)
+template <typename T, typename Terms, int kWavesPerSimd, bool kItems = false>
 __global__ __launch_bounds__(kRowThreads, kWavesPerSimd) void tree_node_kernel(const TreeParams p) {
   __shared__ RowShared sh;
   extern __shared__ __align__(16) unsigned char dyn_lds[];
   const int64_t b = blockIdx.x / p.n_eval;
   const int node = int(blockIdx.x - b * p.n_eval);
   int slot, token, st;
-  const int state = tree_node<T, Terms, kWavesPerSimd == kAlone>(p, b, node, reinterpret_cast<double*>(dyn_lds), true, sh, slot, token, st);
+  const double* items = nullptr;
+  if constexpr (kItems) {
+    items = p.items + int64_t(blockIdx.x) * p.items_stride;
+    if (threadIdx.x == 0) sh.fetched = 0;
+    __syncthreads();
+  }
+  const int state = tree_node<T, Terms, kWavesPerSimd == kAlone>(p, b, node, reinterpret_cast<double*>(dyn_lds), true, sh, slot, token, st, items);
   if (threadIdx.x == 0) {
     const int64_t n = b * p.n_nodes + node;
     p.node_state[n] = state;
@@ -197,6 +217,18 @@ __global__ __launch_bounds__(kRowThreads, kWavesPerSimd) void tree_node_kernel(c
     if (p.out_node_token) p.out_node_token[n] = token;
     if (p.out_node_slot) p.out_node_slot[n] = slot;
   }
+}
+
+// Those nodes' rows, each shared by p.parts workgroups: the masses of their items.
+template <typename T, typename Terms>
+__global__ __launch_bounds__(kRowThreads, kAlone) void tree_share_kernel(const TreeParams p) {
+  __shared__ RowShared sh;
+  extern __shared__ __align__(16) unsigned char dyn_lds[];
+  const int64_t at = blockIdx.x / p.parts, b = at / p.n_eval;
+  const int part = int(blockIdx.x - at * p.parts);
+  RowWork<T> w;
+  row_open<T>(w, tree_row<T>(p, b, int(at - b * p.n_eval)), p.V, p.rT, sh);
+  row_part<T, Terms>(w, reinterpret_cast<double*>(dyn_lds), part, p.parts, p.items + at * p.items_stride, sh);
 }
 
 // The new-sequence search through the layers that have been evaluated: all threads of the calling workgroup; the first
@@ -390,20 +422,7 @@ __global__ __launch_bounds__(kRowThreads, kAlone) void tree_part_kernel(const Tr
   const int part = int(blockIdx.x - b * p.parts);
   RowWork<T> w;
   row_open<T>(w, tree_row<T>(p, b, p.walk_node[b]), p.V, p.rT, sh);
-  w.count = 0;
-  w.y = -1;
-  w.ql = w.ql0 = 0.0f;
-  const int per = (w.n_runs + p.parts - 1) / p.parts;
-  const int run0 = part * per, run1 = run0 + per < w.n_runs ? run0 + per : w.n_runs;
-  row_pass<T, Terms>(w, reinterpret_cast<double*>(dyn_lds), -1, run0, run1, part == 0, sh);
-  double* out = p.items + b * p.items_stride;
-  const bool broken = (sh.flags & 3) != 0;
-  const double bad = __longlong_as_double(0x7FF8000000000000ll);
-  for (int i = run0 + threadIdx.x; i < run1; i += kRowThreads) out[1 + i] = broken ? bad : sh.items[1 + i];
-  if (part == 0 && threadIdx.x < 2) {
-    const int i = threadIdx.x == 0 ? 0 : w.n_items - 1;
-    out[i] = broken ? bad : sh.items[i];
-  }
+  row_part<T, Terms>(w, reinterpret_cast<double*>(dyn_lds), part, p.parts, p.items + b * p.items_stride, sh);
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -513,9 +532,17 @@ template <typename T, typename Terms> hipError_t launch_verify_tree_with(TreePar
   hipError_t e = hipSuccess;
   if (p.n_eval > 0) {
     // (one binary16 tree of 13 nodes, V = 9728: 18.3 us with 64 registers, 17.5 with 128)
-    const bool alone = p.B * p.n_eval <= compute_units();
-    hipLaunchKernelGGL((alone ? tree_node_kernel<T, Terms, kAlone> : tree_node_kernel<T, Terms, kShared>), dim3(unsigned(p.B * p.n_eval)),
-                       dim3(kRowThreads), Terms::kBytes, s, p);
+    const int64_t rows = p.B * p.n_eval;
+    const bool alone = rows <= compute_units();
+    p.parts = rows <= p.items_rows ? row_parts<T, Terms>(p.V, rows) : 1;
+    if (p.parts > 1) {
+      hipLaunchKernelGGL((tree_share_kernel<T, Terms>), dim3(unsigned(rows * p.parts)), dim3(kRowThreads), Terms::kBytes, s, p);
+      if ((e = hipGetLastError()) != hipSuccess) return e;
+      hipLaunchKernelGGL((tree_node_kernel<T, Terms, kAlone, true>), dim3(unsigned(rows)), dim3(kRowThreads), Terms::kBytes, s, p);
+    } else {
+      hipLaunchKernelGGL((alone ? tree_node_kernel<T, Terms, kAlone> : tree_node_kernel<T, Terms, kShared>), dim3(unsigned(rows)),
+                         dim3(kRowThreads), Terms::kBytes, s, p);
+    }
     if ((e = hipGetLastError()) != hipSuccess) return e;
   }
   auto walk = [&](auto fn) {

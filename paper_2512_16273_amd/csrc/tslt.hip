@@ -328,7 +328,7 @@ static int verify_impl(int phases, int stage0, const char* name, const void* tar
       !out_accept_len || !out_tokens)
     return fail(TSLT_ERR_INVALID_ARG, "%s: null pointer", name);
   if (reinterpret_cast<uintptr_t>(target_logits) % elem_bytes(dt)) return fail(TSLT_ERR_INVALID_ARG, "%s: logits not aligned to their element type", name);
-  const size_t need = tslt::verify_workspace_bytes(B, gamma, V, k_cap);
+  const size_t need = tslt::verify_least_workspace_bytes(B, gamma);
   if (!ws || ws_bytes < need || reinterpret_cast<uintptr_t>(ws) % 256)
     return fail(TSLT_ERR_WORKSPACE, "%s: workspace of %zu bytes, 256-byte aligned, required", name, need);
 
@@ -341,7 +341,7 @@ static int verify_impl(int phases, int stage0, const char* name, const void* tar
   p.out_accept_len = out_accept_len; p.out_tokens = out_tokens; p.out_ratio = out_ratio; p.out_beta = out_beta;
   p.status = status;
   p.stage0 = stage0 >= gamma ? 0 : stage0;
-  tslt::verify_carve_workspace(p, ws);
+  tslt::verify_carve_workspace(p, ws, ws_bytes);
   hipStream_t s = reinterpret_cast<hipStream_t>(stream);
   hipError_t e = dt == TSLT_BF16 ? tslt::launch_verify<tslt::Bf16>(p, s, phases)
                  : dt == TSLT_F16 ? tslt::launch_verify<tslt::F16>(p, s, phases) : tslt::launch_verify<float>(p, s, phases);
@@ -378,7 +378,7 @@ int tslt_verify_static(const void* target_logits, tslt_dtype dt, int64_t B, int3
   if (B > TSLT_STATIC_MAX_POSITIONS || B * int64_t(gamma) > TSLT_STATIC_MAX_POSITIONS)
     return fail(TSLT_ERR_UNSUPPORTED, "%s: B * gamma = %lld positions, the static scratch array holds %d; use tslt_verify "
                 "with a workspace", name, (long long)(B * int64_t(gamma)), TSLT_STATIC_MAX_POSITIONS);
-  if (tslt::verify_workspace_bytes(B, gamma, V, k_cap) > size_t(TSLT_STATIC_SCRATCH_BYTES))
+  if (tslt::verify_least_workspace_bytes(B, gamma) > size_t(TSLT_STATIC_SCRATCH_BYTES))
     return fail(TSLT_ERR_UNSUPPORTED, "%s: the static scratch array is too small for this call", name);
   void* ptr = nullptr;
   const hipError_t e = scratch_on_current_device(&ptr);
@@ -506,7 +506,7 @@ int tslt_verify_tree(const void* target_logits, tslt_dtype dt, int64_t B, int64_
   if (!target_logits || !q_idx || !q_logit || !q_count || !cand_tokens || !u_accept || !u_resample || !out_seq || !out_len)
     return fail(TSLT_ERR_INVALID_ARG, "%s: null pointer", name);
   if (reinterpret_cast<uintptr_t>(target_logits) % elem_bytes(dt)) return fail(TSLT_ERR_INVALID_ARG, "%s: logits not aligned to their element type", name);
-  const size_t need = tslt::tree_workspace_bytes(B, n_nodes, V, all_nodes);
+  const size_t need = tslt::tree_least_workspace_bytes(B, n_nodes, V, all_nodes);
   if (!ws || ws_bytes < need || reinterpret_cast<uintptr_t>(ws) % 256)
     return fail(TSLT_ERR_WORKSPACE, "%s: workspace of %zu bytes, 256-byte aligned, required", name, need);
   p.target = target_logits; p.B = B; p.V = V; p.row_stride = row_stride;
@@ -517,7 +517,7 @@ int tslt_verify_tree(const void* target_logits, tslt_dtype dt, int64_t B, int64_
   p.wor = without_replacement ? 1 : 0;
   p.out_node_token = out_node_token; p.out_node_slot = out_node_slot; p.out_seq = out_seq; p.out_len = out_len;
   p.out_ratio = out_ratio; p.out_beta = out_beta; p.status = status;
-  tslt::tree_carve_workspace(p, ws);
+  tslt::tree_carve_workspace(p, ws, ws_bytes);
   hipStream_t s = reinterpret_cast<hipStream_t>(stream);
   hipError_t e = dt == TSLT_BF16 ? tslt::launch_verify_tree<tslt::Bf16>(p, s)
                  : dt == TSLT_F16 ? tslt::launch_verify_tree<tslt::F16>(p, s) : tslt::launch_verify_tree<float>(p, s);

@@ -9,6 +9,8 @@
 // Kernel B, one workgroup of 1024 threads per sequence: finds the first rejected position j (or the bonus row) from
 // kernel A's decisions, sweeps that one target row in fp64, draws from norm(max(0, p - q_hat)) (or from p for
 // the bonus row) by inverse CDF and writes the sequence's outputs.
+// Where a few long rows leave compute units idle, several workgroups sweep each (verify_part_kernel) and the kernels above take
+// up the masses from memory.
 #pragma once
 #include "rowops.h"
 #include "rowsample.h"
@@ -38,17 +40,32 @@ struct VerifyParams {
   int stage0;            // staged mode: positions in the first stage (0 = all positions in one launch)
   int j_begin, j_count;  // the positions one launch covers (verify_round_kernel with draws: the bonus row too)
   int draws;             // verify_round_kernel draws as well
+  double* items;         // masses of shared rows' items (null: the workspace has no room for them)
+  int64_t items_stride;
+  int parts;             // workgroups that share a row
 };
 constexpr int kFlagSkipped = 3;
 
-inline size_t verify_workspace_bytes(int64_t B, int64_t gamma, int64_t V, int k_cap) {
-  (void)V; (void)k_cap;
-  return align256(size_t(B) * gamma * 4) * 2;
+// Rows that may be shared by workgroups (row_parts): those of a small round, or one for each sequence.
+inline int64_t verify_rows_to_share(int64_t B, int64_t gamma, int64_t V) {
+  if (B <= 0 || gamma <= 0 || V < kShareLeastV) return 0;
+  return B * (gamma + 1) <= kShareRows ? B * (gamma + 1) : (B <= kShareRows ? B : 0);
 }
-inline void verify_carve_workspace(VerifyParams& p, void* ws) {
+inline int64_t verify_items_stride(int64_t V) { return int64_t(row_segments(V)) * kSubChunks + 2; }
+// What a call has to be given: a decision and a status word for every position.  With room for the masses of shared rows'
+// items behind them, the size that callers are told, it may share rows as well.
+inline size_t verify_least_workspace_bytes(int64_t B, int64_t gamma) { return align256(size_t(B) * gamma * 4) * 2; }
+inline size_t verify_workspace_bytes(int64_t B, int64_t gamma, int64_t V, int k_cap) {
+  (void)k_cap;
+  return verify_least_workspace_bytes(B, gamma) + align256(size_t(verify_rows_to_share(B, gamma, V) * verify_items_stride(V)) * sizeof(double));
+}
+inline void verify_carve_workspace(VerifyParams& p, void* ws, size_t ws_bytes) {
   char* w = reinterpret_cast<char*>(ws);
   p.flags = reinterpret_cast<int32_t*>(w); w += align256(size_t(p.B) * p.gamma * 4);
-  p.row_status = reinterpret_cast<int32_t*>(w);
+  p.row_status = reinterpret_cast<int32_t*>(w); w += align256(size_t(p.B) * p.gamma * 4);
+  p.items = ws_bytes >= verify_workspace_bytes(p.B, p.gamma, p.V, p.k_cap) && verify_rows_to_share(p.B, p.gamma, p.V) > 0
+                ? reinterpret_cast<double*>(w) : nullptr;
+  p.items_stride = verify_items_stride(p.V);
 }
 
 template <typename T> __device__ __forceinline__ const void* target_row(const VerifyParams& p, int64_t b, int j) {
@@ -124,10 +141,37 @@ __global__ __launch_bounds__(kBlock, kAccWavesPerSimd) void verify_accept_kernel
 }
 
 // ---------------------------------------------------------------------------------------------
-// Kernel B: one workgroup of 1024 threads per sequence sweeps the row to be sampled and writes the sequence's
-// outputs.
+// Rows shared by p.parts workgroups each: the masses of their items, for a launch that takes them up (row_fetch).
+// kRound: every row of a round; else the one of each sequence that is to be sampled, from kernel A's decisions.
 // ---------------------------------------------------------------------------------------------
-template <typename T, typename Terms, int kWavesPerSimd>
+template <typename T, typename Terms, bool kRound>
+__global__ __launch_bounds__(kRowThreads, kAlone) void verify_part_kernel(const VerifyParams p) {
+  __shared__ RowShared sh;
+  extern __shared__ __align__(16) unsigned char dyn_lds[];
+  const int64_t at = blockIdx.x / p.parts;           // the row, or its sequence
+  const int part = int(blockIdx.x - at * p.parts);
+  int64_t b = at;
+  int j = 0;
+  if constexpr (kRound) {
+    b = at / (p.gamma + 1);
+    j = int(at - b * (p.gamma + 1));
+  } else {
+    const int32_t* fl_b = p.flags + b * p.gamma;
+    int first = p.gamma;
+    for (int i = lane_id(); i < p.gamma; i += 64)
+      if (fl_b[i] != 1) { first = i; break; }
+    j = -wave_max_i32(-first);
+  }
+  RowWork<T> w;
+  row_open<T>(w, target_row<T>(p, b, j), p.V, p.rT, sh);
+  row_part<T, Terms>(w, reinterpret_cast<double*>(dyn_lds), part, p.parts, p.items + at * p.items_stride, sh);
+}
+
+// ---------------------------------------------------------------------------------------------
+// Kernel B: one workgroup of 1024 threads per sequence sweeps the row to be sampled, or takes up its masses (kItems), and
+// writes the sequence's outputs.
+// ---------------------------------------------------------------------------------------------
+template <typename T, typename Terms, int kWavesPerSimd, bool kItems = false>
 __global__ __launch_bounds__(kRowThreads, kWavesPerSimd) void verify_resample_kernel(const VerifyParams p) {
   __shared__ RowShared sh;
   extern __shared__ __align__(16) unsigned char dyn_lds[];
@@ -139,7 +183,7 @@ __global__ __launch_bounds__(kRowThreads, kWavesPerSimd) void verify_resample_ke
   // accepted): the words are few and nothing has to be handed round.
   const int32_t* fl_b = p.flags + b * p.gamma;
   const int f0 = lane < p.gamma ? fl_b[lane] : 1;
-  Terms::build(table, p.rT, kRowThreads, 0);
+  if constexpr (!kItems) Terms::build(table, p.rT, kRowThreads, 0);
   int j0 = f0 != 1 ? lane : p.gamma;
   if (p.gamma > 64 && ballot(f0 != 1) == 0) {
     for (int j = lane + 64; j < p.gamma; j += 64)
@@ -156,11 +200,16 @@ __global__ __launch_bounds__(kRowThreads, kWavesPerSimd) void verify_resample_ke
   const float u_res = p.u_resample[b * (p.gamma + 1) + jstar];
   RowWork<T> w;
   int token = -1;
-  if (tid == 0) sh.cmd = 0;                     // read behind a barrier: 1 when there is something to draw from
+  if (tid == 0) { sh.cmd = 0; sh.fetched = 0; } // read behind a barrier: 1 when there is something to draw from
   if (!unusable) {
     row_open<T>(w, target_row<T>(p, b, jstar), p.V, p.rT, sh);
     row_take_set(w, p.q_idx + size_t(r) * p.k_cap, p.q_logit + size_t(r) * p.k_cap, residual ? p.q_count[r] : 0, p.k_cap);
-    row_sweep<T, Terms, kWavesPerSimd == kAlone>(w, table, 1, sh);
+    if constexpr (kItems) {
+      __syncthreads();
+      row_fetch<T, Terms>(w, p.items + b * p.items_stride, table, sh);
+    } else {
+      row_sweep<T, Terms, kWavesPerSimd == kAlone>(w, table, 1, sh);
+    }
     if (wave_id() == 0) {
       RowState rst;
       row_eval(w, rst, sh);
@@ -205,7 +254,7 @@ __global__ __launch_bounds__(kRowThreads, kWavesPerSimd) void verify_resample_ke
 // Without draws it is kernel A for such batches: the decisions of a batch are made in the same way whether it is
 // verified by one call, by two halves or in stages.
 // ---------------------------------------------------------------------------------------------
-template <typename T, typename Terms, int kWavesPerSimd>
+template <typename T, typename Terms, int kWavesPerSimd, bool kItems = false>
 __global__ __launch_bounds__(kRowThreads, kWavesPerSimd) void verify_round_kernel(const VerifyParams p) {
   __shared__ RowShared sh;
   extern __shared__ __align__(16) unsigned char dyn_lds[];
@@ -220,7 +269,13 @@ __global__ __launch_bounds__(kRowThreads, kWavesPerSimd) void verify_round_kerne
   const int count = p.q_count[r], x = p.draft_tokens[r];
   const float u_acc = p.u_accept[r], u_res = p.u_resample[b * (p.gamma + 1) + j];
   row_take_set(w, p.q_idx + size_t(r) * p.k_cap, p.q_logit + size_t(r) * p.k_cap, bonus ? 0 : count, p.k_cap);
-  row_sweep<T, Terms, kWavesPerSimd == kAlone>(w, table, -1, sh);
+  if constexpr (kItems) {
+    if (threadIdx.x == 0) sh.fetched = 0;
+    __syncthreads();
+    row_fetch<T, Terms>(w, p.items + (b * (p.gamma + 1) + j) * p.items_stride, table, sh);
+  } else {
+    row_sweep<T, Terms, kWavesPerSimd == kAlone>(w, table, -1, sh);
+  }
   // (nothing is stored to memory before the last barrier, which would wait for it)
   int st = 0, flag = 0;
   float ratio = NAN, beta = NAN;
@@ -313,12 +368,26 @@ template <typename T, typename Terms> hipError_t launch_verify_with(VerifyParams
     return by_rows(KernelTag<&verify_round_kernel<T, Terms, kAlone>>{}, KernelTag<&verify_round_kernel<T, Terms, kShared>>{},
                    p.B * p.j_count);
   };
+  auto share = [&](auto fn, int64_t rows) -> hipError_t {
+    if constexpr (kLargeTable<Terms>) {
+      if ((e = allow_dynamic_lds<decltype(fn)::value>(int(Terms::kBytes))) != hipSuccess) return e;
+    }
+    hipLaunchKernelGGL(fn.value, dim3(unsigned(rows * p.parts)), dim3(kRowThreads), Terms::kBytes, s, p);
+    return hipGetLastError();
+  };
   const bool by_row = p.B * (p.gamma + 1) <= round_rows<Terms>();
   if (by_row && phases == 3 && p.stage0 == 0) {
     p.j_begin = 0;
     p.j_count = p.gamma + 1;
     p.draws = 1;
-    if ((e = round()) != hipSuccess) return e;
+    p.parts = p.items != nullptr ? row_parts<T, Terms>(p.V, p.B * p.j_count) : 1;
+    if (p.parts > 1) {
+      if ((e = share(KernelTag<&verify_part_kernel<T, Terms, true>>{}, p.B * p.j_count)) != hipSuccess) return e;
+      const auto fetch = KernelTag<&verify_round_kernel<T, Terms, kAlone, true>>{};
+      if ((e = by_rows(fetch, fetch, p.B * p.j_count)) != hipSuccess) return e;
+    } else if ((e = round()) != hipSuccess) {
+      return e;
+    }
     hipLaunchKernelGGL(verify_select_kernel, dim3(unsigned(p.B)), dim3(64), 0, s, p);
     return hipGetLastError();
   }
@@ -341,6 +410,12 @@ template <typename T, typename Terms> hipError_t launch_verify_with(VerifyParams
     }
   }
   if (phases & 2) {
+    p.parts = p.items != nullptr ? row_parts<T, Terms>(p.V, p.B) : 1;
+    if (p.parts > 1) {
+      if ((e = share(KernelTag<&verify_part_kernel<T, Terms, false>>{}, p.B)) != hipSuccess) return e;
+      const auto fetch = KernelTag<&verify_resample_kernel<T, Terms, kAlone, true>>{};
+      return by_rows(fetch, fetch, p.B);
+    }
     e = by_rows(KernelTag<&verify_resample_kernel<T, Terms, kAlone>>{}, KernelTag<&verify_resample_kernel<T, Terms, kShared>>{},
                 p.B);
   }

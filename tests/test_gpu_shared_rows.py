@@ -1,0 +1,137 @@
+"""Rows of small batches that several workgroups sweep together: with a workspace that has no room for their masses every row
+has one workgroup, and the outputs have to be the same bit for bit; with broken, masked and shifted rows among them, odd
+vocabularies, and captured into a graph over a workspace that holds nothing of an earlier call."""
+import pytest
+import torch
+
+from paper_2512_16273_amd import workloads as W
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda:0"
+
+
+def up256(n):
+    return (n + 255) // 256 * 256
+
+
+def odd_rows(t):
+    """A few rows of t [n, V] (n >= 6) that a sweep referenced to 0 cannot take, or only just."""
+    t[0, 77] = float("nan")
+    t[1] += 650.0
+    t[2, 1000:] = -float("inf")
+    t[3] = -float("inf")
+    t[4, ::3] = torch.finfo(t.dtype).min
+    t[5, -1] = float("inf")
+
+
+def same(a, b):
+    for k, v in a.items():
+        if v is not None:
+            assert torch.equal(v.nan_to_num(nan=-7.0), b[k].nan_to_num(nan=-7.0)) if v.is_floating_point() else torch.equal(v, b[k]), k
+
+
+@pytest.mark.parametrize("dtype,V,B,gamma", [
+    ("f32", 50000, 3, 4), ("f32", 64001, 14, 8), ("f32", 151936, 40, 8),      # three workgroups a row, two, the sampled rows alone
+    ("f16", 60001, 2, 3), ("f16", 131072, 30, 12), ("bf16", 100003, 8, 8), ("bf16", 125000, 16, 7), ("bf16", 250001, 1, 1),
+])
+@pytest.mark.parametrize("broken", [False, True])
+def test_chain_of_shared_rows(tslt, dtype, V, B, gamma, broken):
+    K = 64
+    w = W.scaled(W.WORKLOADS["chain_topk"], B=B, V=V, gamma=gamma, dtype=dtype, top_k=K, k_cap=K, T=0.8)
+    c = W.make_chain(w, 7, DEV)
+    tr = tslt.truncate(c["draft"].view(B * gamma, V), w.T, K, 0.0, K, u=c["u_sample"].view(B * gamma, 1))
+    target = c["target"]
+    if broken:
+        odd_rows(target.view(-1, V)[:: max(1, B * (gamma + 1) // 7)][:6] if B * (gamma + 1) >= 12 else target.view(-1, V).repeat(3, 1)[:6])
+    args = (target, w.T, tr["idx"].view(B, gamma, K), tr["logit"].view(B, gamma, K), tr["count"].view(B, gamma),
+            tr["token"].view(B, gamma), c["u_accept"], c["u_resample"])
+    least = 2 * up256(B * gamma * 4)
+    told = tslt.workspace_bytes(tslt.OP_VERIFY, B, gamma, V, K)
+    assert told > least
+    alone = tslt.verify(*args, workspace=torch.full((least,), 255, dtype=torch.uint8, device=DEV))
+    ws = torch.full((told,), 255, dtype=torch.uint8, device=DEV)          # the items: NaN until they are written
+    shared = tslt.verify(*args, workspace=ws)
+    torch.cuda.synchronize()
+    same(alone, shared)
+    ws.fill_(255)
+    halves = tslt.verify(*args, workspace=ws, phase="accept")
+    tslt.verify(*args, workspace=ws, phase="resample", out=halves)
+    static = {k: v.clone() for k, v in alone.items()}
+    tslt.verify_static(*args, out=static)
+    torch.cuda.synchronize()
+    same(alone, halves)
+    same(alone, static)
+    with pytest.raises(tslt.TsltError):
+        tslt.verify(*args, workspace=ws[:least - 256])
+
+
+@pytest.mark.parametrize("dtype,V,B,expansion", [
+    ("f32", 50001, 2, (2, 2, 2)), ("f32", 128256, 1, (4, 4, 4)), ("f16", 60000, 6, (3, 3)), ("bf16", 125001, 4, (2, 2, 2)),
+    ("f32", 100000, 30, (2, 2, 2)),                                          # of the path, the first layers alone at once
+])
+@pytest.mark.parametrize("broken", [False, True])
+def test_trees_of_shared_rows(tslt, dtype, V, B, expansion, broken):
+    K = 16
+    w = W.scaled(W.WORKLOADS["tree"], B=B, V=V, expansion=expansion, top_k=K, k_cap=K, dtype=dtype, without_replacement=False)
+    tree = W.make_tree(w, 9, DEV)
+    n = tree["target"].shape[1]
+    sets = tslt.truncate(tree["draft"].reshape(-1, V), w.T, K, 0.0, K)
+    n_int = sets["idx"].shape[0] // B
+    g = torch.Generator().manual_seed(5)
+    idx = sets["idx"].view(B, n_int, K)
+    cand, node, width = [], 0, 1
+    for k in expansion:
+        pick = torch.randint(0, 6, (B, width, k), generator=g).to(DEV)
+        cand.append(idx[:, node:node + width].gather(2, pick).reshape(B, -1))
+        node, width = node + width, width * k
+    target = tree["target"].view(-1, V)
+    if broken:
+        odd_rows(target[1::max(1, B * n // 8)][:6])
+    args = (tree["target"], w.T, list(expansion), idx.contiguous(), sets["logit"].view(B, n_int, K), sets["count"].view(B, n_int),
+            torch.cat(cand, 1).contiguous(), tree["u_accept"], tree["u_resample"])
+    n_seg = (V // 4 + 1 + 1023) // 1024
+    least = 4 * up256(B * n * 4) + 2 * up256(B * 4) + up256(B * (n_seg + 2) * 16) + up256(B * n_seg * 32)
+    told = tslt.workspace_bytes(tslt.OP_VERIFY_TREE_PATH, B, n, V, K)
+    assert told >= least
+    alone = tslt.verify_tree(*args, all_nodes=False, workspace=torch.full((least,), 255, dtype=torch.uint8, device=DEV))
+    ws = torch.full((told,), 255, dtype=torch.uint8, device=DEV)
+    shared = tslt.verify_tree(*args, all_nodes=False, workspace=ws)
+    every = tslt.verify_tree(*args, all_nodes=True)
+    torch.cuda.synchronize()
+    same(alone, shared)
+    assert torch.equal(every["seq"], alone["seq"]) and torch.equal(every["len"], alone["len"])
+    tested = ~alone["ratio"].isnan()
+    assert torch.equal(every["ratio"][tested], alone["ratio"][tested])
+
+
+def test_shared_rows_captured(tslt):
+    B, gamma, V, K = 2, 3, 128256, 32
+    w = W.scaled(W.WORKLOADS["chain_topk"], B=B, V=V, gamma=gamma, dtype="f16", top_k=K, k_cap=K)
+    sets = []
+    for seed in (3, 4):
+        c = W.make_chain(w, seed, DEV)
+        tr = tslt.truncate(c["draft"].view(B * gamma, V), w.T, K, 0.0, K, u=c["u_sample"].view(B * gamma, 1))
+        sets.append([c["target"], tr["idx"].view(B, gamma, K), tr["logit"].view(B, gamma, K), tr["count"].view(B, gamma),
+                     tr["token"].view(B, gamma).contiguous(), c["u_accept"], c["u_resample"]])
+    ws = torch.empty(tslt.workspace_bytes(tslt.OP_VERIFY, B, gamma, V, K), dtype=torch.uint8, device=DEV)
+    call = lambda s, out=None: tslt.verify(s[0], w.T, *s[1:], out=out, workspace=ws)  # noqa: E731
+    eager = []
+    for s in sets:
+        out = call(s)
+        torch.cuda.synchronize()
+        eager.append({k: v.clone() for k, v in out.items()})
+    static = [t.clone() for t in sets[0]]
+    out_s = call(static)
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        call(static, out_s)
+    for rep in range(2):
+        for i, s in enumerate(sets):
+            for a, b in zip(static, s):
+                a.copy_(b)
+            ws.fill_(255)
+            torch.cuda.synchronize()
+            graph.replay()
+            torch.cuda.synchronize()
+            same(eager[i], out_s)
