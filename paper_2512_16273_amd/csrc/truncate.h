@@ -18,8 +18,8 @@
 // vector registers without a sign to change (2.7 cycles a wave, 4.4 otherwise), binary16 is tested against the threshold as
 // packed halves and never widened, addresses are a scalar offset into a buffer, the complete stages have a loop without a
 // check for the row's end, and every exchange between waves behind the pass is one barrier (12 in all, 24 before).  us
-// before / now: 1 binary16 row of 32000, k 320 12.3 / 11.5; 64 bfloat16 rows of 128256, k 256 20.7 / 18.7; 19 binary16 rows of
-// 223104 27.6 / 23.6; 600 binary16 rows of 32000 17.7 / 15.8; 4096 bfloat16 rows of 256000, k 1024 407 / 396.
+// before / now: 1 binary16 row of 32000, k 320 12.4 / 10.8; 64 bfloat16 rows of 128256, k 256 20.5 / 17.8; 19 binary16 rows of
+// 223104 27.7 / 23.0; 600 binary16 rows of 32000 17.7 / 15.8; 4096 bfloat16 rows of 256000, k 1024 407 / 396.
 #pragma once
 #include <type_traits>
 #include "common.h"
@@ -38,7 +38,7 @@ constexpr int kGroup = 2;        // tiles (one 16-byte vector per thread each) i
 // then need more requests in flight each to keep the memory busy.
 //   "Tall": 512 threads and four stages, for batches that leave the chip to one or two rows per compute unit, bound by
 // a row's own latency: twice the requests in flight, rows shorter than the sample's distances through the same pipeline
-// (they went pair by pair, a memory latency each), the threshold three bits at a time.  us by 256 / 512 threads: 1 row
+// (they went pair by pair, a memory latency each), the threshold out of a histogram.  us by 256 / 512 threads: 1 row
 // binary16 V = 32000 14.8 / 13.0, 64 bfloat16 V = 128256 27.0 / 21.7, 200 28.1 / 23.2, 384 29.8 / 28.3, 700 42.1 / 46.7;
 // 100 fp32 V = 151936 40.6 / 27.8, 400 51.2 / 51.2.  1024 threads are slower again (14.9, 23.4, 25.6 us).
 constexpr int kTallThreads = 512;
@@ -602,49 +602,108 @@ __global__ __launch_bounds__(NT, kWavesPerSimd) void truncate_kernel(const Trunc
     // compiler would otherwise keep the unpacked values, twice the registers, across the threshold search)
 #pragma unroll
     for (int u = 0; u < kBatch; ++u) asm volatile("" : "+v"(d[u].x), "+v"(d[u].y), "+v"(d[u].z), "+v"(d[u].w));
-    tables[tid] = mono_key(tmax);
-    __syncthreads();
-    // ---- tau0: the jprime-th largest of the per-thread sample maxima
-    uint32_t kq[NW];
-#pragma unroll
-    for (int q = 0; q < NW; ++q) kq[q] = tables[lane + 64 * q];
-    uint32_t top_key = kq[0];                          // the sample's maximum
-#pragma unroll
-    for (int q = 1; q < NW; ++q) top_key = kq[q] > top_key ? kq[q] : top_key;
-    top_key = wave_max_u32(top_key);
-    auto reach = [&](uint32_t trial) {                 // how many of them reach `trial`
-      int cnt = 0;
-#pragma unroll
-      for (int q = 0; q < NW; ++q) cnt += __popcll(ballot(kq[q] >= trial));
-      return cnt;
-    };
-    uint32_t tau_key = 0;
+    // ---- tau0: the jprime-th largest of the per-thread sample maxima, to the leading tau_bits of its key
+    uint32_t tau_key = 0, top_key;                     // top_key: the sample's maximum
     if constexpr (!kTall) {                            // a bit at a time, every wave for itself
+      tables[tid] = mono_key(tmax);
+      __syncthreads();
+      uint32_t kq[NW];
+#pragma unroll
+      for (int q = 0; q < NW; ++q) kq[q] = tables[lane + 64 * q];
       for (int bit = 31; bit >= 32 - p.tau_bits; --bit) {
         const uint32_t trial = tau_key | (1u << bit);
-        if (reach(trial) >= p.jprime) tau_key = trial;
-      }
-    } else {                                           // three bits at a time, every wave tries one of their values
-      static_assert(NW == 8, "a wave per value");
-      // the leading bits that all of them share need no search: half of them where a row's large logits are within a few
-      // powers of two, a barrier for every three
-      uint32_t low_key = kq[0];
+        int reach = 0;
 #pragma unroll
-      for (int q = 1; q < NW; ++q) low_key = kq[q] < low_key ? kq[q] : low_key;
-      low_key = ~wave_max_u32(~low_key);
-      const int first_bit = top_key != low_key ? 31 - __builtin_clz(top_key ^ low_key) : 0;
-      int shift = 32 - 3 * ((31 - first_bit) / 3);     // the groups of three above the first bit
-      tau_key = shift < 32 ? top_key & ~((1u << shift) - 1u) : 0u;
-      const int last = 32 - 3 * ((p.tau_bits + 2) / 3);
-      if (shift < last) { shift = last; tau_key = top_key & ~((1u << last) - 1u); }
-      for (int step = 0; shift > 32 - p.tau_bits; ++step) {
-        shift -= 3;
-        int* reached = step & 1 ? reinterpret_cast<int*>(sh.red.f) : sh.red.i;
-        const int cnt = reach(tau_key | (uint32_t(wave) << shift));
-        if (lane == 0) reached[wave] = cnt;
+        for (int q = 0; q < NW; ++q) reach += __popcll(ballot(kq[q] >= trial));
+        if (reach >= p.jprime) tau_key = trial;
+      }
+      top_key = kq[0];
+#pragma unroll
+      for (int q = 1; q < NW; ++q) top_key = kq[q] > top_key ? kq[q] : top_key;
+      top_key = wave_max_u32(top_key);
+    } else {
+      // By a histogram over 256 value bins and the few maxima in the bin of the jprime-th: three barriers.  Where that does not
+      // tell them apart (masked rows, rows full of ties) four bits of the key at a time, with a barrier for each four.  (Bits
+      // alone, three at a time: 5000 cycles of the 26000 that a binary16 row of 32000 took, 3400 so.)
+      const uint32_t key = mono_key(tmax);
+      const uint32_t hi = wave_max_u32(key), lo = ~wave_max_u32(~key);
+      if (lane == 0) { sh.red.i[wave] = int(hi); sh.red.f[wave] = as_f32(lo); }
+      uint32_t* counts = tables + NT;                  // the bins; eight steps of sixteen; the list's length, the list
+      uint32_t* list_n = counts + 256 + 8 * 16;
+      uint32_t* list = list_n + 4;
+      tables[tid] = key;                               // (read by its own wave)
+      if (tid < 256 + 8 * 16 + 4) counts[tid] = 0;
+      __syncthreads();
+      top_key = uint32_t(sh.red.i[0]);
+      uint32_t low_key = as_u32(sh.red.f[0]);
+#pragma unroll
+      for (int w = 1; w < NW; ++w) {
+        top_key = uint32_t(sh.red.i[w]) > top_key ? uint32_t(sh.red.i[w]) : top_key;
+        low_key = as_u32(sh.red.f[w]) < low_key ? as_u32(sh.red.f[w]) : low_key;
+      }
+      const int last = 32 - 3 * ((p.tau_bits + 2) / 3);                      // the lowest bit that counts
+      const float vmin = key_to_f32(low_key), span = key_to_f32(top_key) - vmin;
+      int n_list = 65;
+      if (span > 0.0f && span < 3.0e38f) {
+        const int in_bin = int((key_to_f32(key) - vmin) * (255.0f / span)), bin = in_bin > 255 ? 255 : in_bin;
+        atomicAdd(&counts[bin], 1u);
         __syncthreads();
-        const int of_lane = lane < NW ? reached[lane] : 0;                   // falls with the value
-        tau_key |= uint32_t(__popcll(ballot(lane > 0 && of_lane >= p.jprime))) << shift;
+        // every wave: the bin in which the count from the top passes jprime; lane l has bins 255 - 4 l downwards
+        const uint4 h = reinterpret_cast<const uint4*>(counts)[63 - lane];
+        const int h4[4] = {int(h.w), int(h.z), int(h.y), int(h.x)};
+        const int mine = (h4[0] + h4[1]) + (h4[2] + h4[3]);
+        int run = wave_incl_scan_i32(mine) - mine, at = -1, before = 0;
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+          const bool here = run < p.jprime && run + h4[j] >= p.jprime;
+          at = here ? 255 - 4 * lane - j : at;
+          before = here ? run : before;
+          run += h4[j];
+        }
+        const int src = __ffsll((long long)ballot(at >= 0)) - 1;             // (jprime is not more than the maxima)
+        at = __builtin_amdgcn_readlane(at, src);
+        const int rank = p.jprime - __builtin_amdgcn_readlane(before, src);  // among the bin's
+        if (bin == at) {
+          const uint32_t pos = atomicAdd(list_n, 1u);
+          if (pos < 64) list[pos] = key;
+        }
+        __syncthreads();
+        n_list = __builtin_amdgcn_readfirstlane(int(*list_n));
+        if (n_list <= 64) {
+          const uint32_t k = lane < n_list ? list[lane] : 0u;
+          int above = 0, reach = 0;                                           // of the list: larger, no smaller
+          for (int i = 0; i < n_list; ++i) {
+            const uint32_t x = uint32_t(__builtin_amdgcn_readlane(int(k), i));
+            above += x > k ? 1 : 0;
+            reach += x >= k ? 1 : 0;
+          }
+          const int of = __ffsll((long long)ballot(lane < n_list && above < rank && reach >= rank)) - 1;
+          tau_key = (uint32_t(__builtin_amdgcn_readlane(int(k), of)) >> last) << last;
+        }
+      }
+      if (n_list > 64) {                                                      // the same in all waves
+        uint4 kq[4];
+#pragma unroll
+        for (int q = 0; q < 4; ++q) kq[q] = reinterpret_cast<const uint4*>(tables)[wave * 16 + (lane >> 4) * 4 + q];
+        uint32_t* step = counts + 256;
+        int above = 32;
+        for (tau_key = 0u; above > last; step += 16) {
+          const int bits = above - last < 4 ? above - last : 4, value = lane & 15;
+          above -= bits;
+          const uint32_t trial = tau_key | (uint32_t(value) << above);
+          uint32_t reach = 0;
+#pragma unroll
+          for (int q = 0; q < 4; ++q) {
+            reach += kq[q].x >= trial ? 1u : 0u;
+            reach += kq[q].y >= trial ? 1u : 0u;
+            reach += kq[q].z >= trial ? 1u : 0u;
+            reach += kq[q].w >= trial ? 1u : 0u;
+          }
+          atomicAdd(&step[value], reach);
+          __syncthreads();
+          const bool tries = lane > 0 && lane < (1 << bits);                 // falls with the value
+          tau_key |= uint32_t(__popcll(ballot(tries && int(step[value]) >= p.jprime))) << above;
+        }
       }
     }
     const float smax = key_to_f32(top_key);
