@@ -367,11 +367,17 @@ __device__ __forceinline__ void row_pass(RowWork<T>& w, double* table, int half,
     // zeros past the row's end; with 64 registers a thread the sweep spills less.  Two fp32 trees of 1365 nodes, V = 151936,
     // every node: 319 us by plain loads, 291 so; 60 binary16 trees <4,2,2,1> of 32000 94 and 86; 24 x 5 binary16 rows of 55257
     // 19.4 and 18.5.  BitTerms, bound by the LDS, gain nothing: 64 bfloat16 trees <2,2,2> of 128256 57 and 63.)
-    const __amdgpu_buffer_rsrc_t body = row_buffer(rs.body, nvec);
+    // (A workgroup's row, a wave's run: said so, where the compiler cannot tell and would put a loop around each load.  64
+    // binary16 trees <2,2,2> of 32000, the path: 40.3 us with the loops, 39.5 without.)
+    const uint64_t row_at = reinterpret_cast<uint64_t>(rs.body);
+    const uint32_t row_lo = __builtin_amdgcn_readfirstlane(uint32_t(row_at)), row_hi = __builtin_amdgcn_readfirstlane(uint32_t(row_at >> 32));
+    const __amdgpu_buffer_rsrc_t body =
+        row_buffer(reinterpret_cast<const uint4*>((uint64_t(row_hi) << 32) | row_lo), uint32_t(__builtin_amdgcn_readfirstlane(nvec)));
     auto request = [&](int run, uint4 (&q)[kSegVecs]) {
       if constexpr (!Terms::kBits) {
+        const uint32_t at = uint32_t(__builtin_amdgcn_readfirstlane(run)) * (kRunVecs * 16u);
 #pragma unroll
-        for (int i = 0; i < kSegVecs; ++i) q[i] = buffer_load_vec_stream(body, lane * 16u, uint32_t(run) * (kRunVecs * 16u) + i * 1024u);
+        for (int i = 0; i < kSegVecs; ++i) q[i] = buffer_load_vec_stream(body, lane * 16u, at + i * 1024u);
       } else {
         const uint32_t vbase = uint32_t(run < run1 ? run : run1 - 1) * kRunVecs + lane;
 #pragma unroll

@@ -52,11 +52,11 @@ struct TreeParams {
   // once [B, n_eval, items_stride]
   double* items;
   int64_t items_stride;
-  int64_t items_rows;     // there is room for
   int parts;              // workgroups that share a row
   int all_nodes;
   int n_eval;             // nodes of a tree that tree_node_kernel evaluates: whole layers from the root
   int n_eval_layers;
+  int64_t items_rows;     // there is room for (read on the host)
 };
 
 // (Evaluating every node uses the node arrays alone.  The rest, two words a tree and the masses of a row's items, is for the
