@@ -365,7 +365,7 @@ __device__ __forceinline__ void row_pass(RowWork<T>& w, double* table, int half,
     const uint32_t last_vec = uint32_t(rs.nvec - 1), nvec = uint32_t(rs.nvec);
     // (PowTerms: through a buffer, which takes the addresses out of the vector registers, streams past the caches and gives
     // zeros past the row's end; with 64 registers a thread the sweep spills less.  Two fp32 trees of 1365 nodes, V = 151936,
-    // every node: 319 us by plain loads, 291 so; 60 binary16 trees <4,2,2,1> of 32000 94 and 86; 24 x 5 binary16 rows of 55257
+    // every node: 322 us by plain loads, 302 so; 60 binary16 trees <4,2,2,1> of 32000 94 and 86; 24 x 5 binary16 rows of 55257
     // 19.4 and 18.5.  BitTerms, bound by the LDS, gain nothing: 64 bfloat16 trees <2,2,2> of 128256 57 and 63.)
     // (A workgroup's row, a wave's run: said so, where the compiler cannot tell and would put a loop around each load.  64
     // binary16 trees <2,2,2> of 32000, the path: 40.3 us with the loops, 39.5 without.)

@@ -5,8 +5,8 @@
 // and the update p^(i+1) = norm(max(0, p^(i) - q_hat)) is a <- max(0, a - q_hat) / Z, c <- c / Z with
 // Z = sum(max(0, a - q_hat)) + c * p_out: one dense pass per node, O(k * K) work for the k candidates, and the
 // sums of that pass serve the draw as well (rowsample.h).  Bound by the vector units (fp32: 19 instructions an element,
-// 5.1 TB/s) or the LDS (bfloat16).  Two fp32 trees of 1365 nodes, V = 151936, every node: 546 us as a pass for the
-// tests, a sweep, a finish and two more launches, 330 so; the path of 64 binary16 trees <2,2,2>, V = 32000: 52 and 39.7.
+// 5.5 TB/s) or the LDS (bfloat16).  Two fp32 trees of 1365 nodes, V = 151936, every node: 546 us as a pass for the
+// tests, a sweep, a finish and two more launches, 302 so; the path of 64 binary16 trees <2,2,2>, V = 32000: 52 and 39.5.
 // Paths over long rows take the tests on the way from an fp32 pass (rowops.h) and sweep the last node alone.
 #pragma once
 #include "rowops.h"

@@ -136,7 +136,7 @@ bool sparse_hits(tslt_dtype dt, int64_t V, int nt, const tslt::TruncateParams& p
 // 12.1 / 11.4 and 10.5 / 10.2),
 // and up to three rows for two compute units if a row is neither short nor very long (us by 256 / 512 threads, 306
 // rows: bfloat16 16000 11.3 / 12.2, 60000 19.0 / 20.4, 128256 28.0 / 27.5, 213696 39.8 / 38.3; fp32 25240 16.3 / 17.4, 60000
-// 24.2 / 22.6, 128256 39.9 / 38.2, 213696 55.8 / 58.9).
+// 24.2 / 22.6, 128256 39.9 / 38.2, 213696 55.8 / 58.9; both have since become 3 to 17 % faster, and the lines stay).
 bool tall_rows(tslt_dtype dt, int64_t V, int64_t rows) {
   const int64_t cus = tslt::compute_units(), kb = V * elem_bytes(dt) >> 10;
   if (rows <= cus) return V >= 10240;
