@@ -473,3 +473,24 @@ def test_large_batches_with_broken_rows_and_sets(tslt, dtype, B, gamma):
     v = {k: x[rest] for k, x in v.items()}
     v["beta_hat"] = v["beta_hat"].astype(np.float32)
     print(P.compare_verify(out, v, seqs=rest, label=f"{dtype} large, broken"), v["status"][:13])
+
+
+@pytest.mark.parametrize("V", [30720, 32765, 32768, 32773, 34816])
+@pytest.mark.parametrize("dtype,T,B,gamma", [("f16", 1.0, 3, 2), ("bf16", 0.15, 3, 2), ("f16", 0.8, 88, 2)])
+def test_verify_rows_of_about_as_many_runs_as_waves(tslt, V, dtype, T, B, gamma):
+    """16-bit rows of 15, 16 and 17 runs of 2048 for the sixteen waves of a row's workgroup (a run for every wave at most is summed
+    without the loop that requests ahead), ragged and shifted off their alignment by odd vocabularies: in one pass, and
+    (88 sequences) in two halves."""
+    w = W.scaled(W.WORKLOADS["chain_topk"], B=B, V=V, gamma=gamma, dtype=dtype, T=T, top_k=40, k_cap=40)
+    if T < 0.5:                               # scaled values as at T = 1
+        w = W.scaled(w, sigma=w.sigma * T, zipf=w.zipf * T, noise_t=w.noise_t * T)
+    chain = W.make_chain(w, 71, DEV)
+    u_acc = chain["u_accept"].clone()
+    u_acc[0] = 0.0                            # the bonus row
+    u_acc[1] = 0.9995
+    chain["u_accept"] = u_acc
+    ref = P.oracle_chain(P.to_np(chain["draft"]), P.to_np(chain["target"]), w.T, w.top_k, w.top_p, w.k_cap,
+                         P.to_np(chain["u_sample"]), P.to_np(u_acc), P.to_np(chain["u_resample"]))
+    out = run_verify_from_oracle_inputs(tslt, w, chain, ref)
+    torch.cuda.synchronize()
+    print(P.compare_verify(out, ref["verify"], label=f"runs {dtype} {V}"), ref["verify"]["accept_len"][:8])
