@@ -334,7 +334,7 @@ template <typename T> __device__ __forceinline__ void row_store_set(const RowWor
 // The masses of the row's items, referenced to 0: of its runs run0 .. run1 - 1, and with `ends` of the elements before and
 // after its aligned body; and sh.flags, as of run_sum.  A wave takes run run0 + `wave` first and then whichever run is next (a counter in
 // LDS), so that the waves end together.  Every request of the loop is unconditional (a vector past the row's end
-// is read from the row's last vector, or as zeros, and its sum dropped; a run past the last likewise, to no
+// is read from the row's last vector, or as zeros, and its sum dropped; a run past the part's last likewise, to no
 // effect): with requests inside branches the number in flight is not known where a wait is placed, and the wait
 // for the current run would wait for the run requested ahead as well.  While the first requests travel the terms'
 // table is made: all of it (half -1), its second half (1) or nothing (-2).
@@ -371,13 +371,16 @@ __device__ __forceinline__ void row_pass(RowWork<T>& w, double* table, int half,
     // binary16 trees <2,2,2> of 32000, the path: 40.3 us with the loops, 39.5 without.)
     const uint64_t row_at = reinterpret_cast<uint64_t>(rs.body);
     const uint32_t row_lo = __builtin_amdgcn_readfirstlane(uint32_t(row_at)), row_hi = __builtin_amdgcn_readfirstlane(uint32_t(row_at >> 32));
-    const __amdgpu_buffer_rsrc_t body =
-        row_buffer(reinterpret_cast<const uint4*>((uint64_t(row_hi) << 32) | row_lo), uint32_t(__builtin_amdgcn_readfirstlane(nvec)));
+    // (The buffer ends where run1 does: in a part of a row what lies behind is the next workgroup's, and the run that a wave
+    // requests ahead of its last one would be fetched to be dropped.  48 x 6 fp32 rows of 151936, five parts of 30 runs each:
+    // verify_part_kernel took 20.5 MB from memory and 10.1 us so, 14.3 and 9.9 now.)
+    const uint32_t end_vec = uint32_t(__builtin_amdgcn_readfirstlane(std::min(nvec, uint32_t(run1) * kRunVecs)));
+    const __amdgpu_buffer_rsrc_t body = row_buffer(reinterpret_cast<const uint4*>((uint64_t(row_hi) << 32) | row_lo), end_vec);
     auto request = [&](int run, uint4 (&q)[kSegVecs]) {
       if constexpr (!Terms::kBits) {
-        const uint32_t at = uint32_t(__builtin_amdgcn_readfirstlane(run)) * (kRunVecs * 16u);
+        const uint32_t at = std::min(uint32_t(__builtin_amdgcn_readfirstlane(run)) * (kRunVecs * 16u), end_vec * 16u);
 #pragma unroll
-        for (int i = 0; i < kSegVecs; ++i) q[i] = buffer_load_vec_stream(body, lane * 16u, at + i * 1024u);
+        for (int i = 0; i < kSegVecs; ++i) q[i] = buffer_load_vec_stream(body, lane * 16u + i * 1024u, at);
       } else {
         const uint32_t vbase = uint32_t(run < run1 ? run : run1 - 1) * kRunVecs + lane;
 #pragma unroll
