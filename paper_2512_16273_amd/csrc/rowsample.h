@@ -551,18 +551,20 @@ __device__ __forceinline__ void row_fetch(RowWork<T>& w, const double* items, do
 constexpr int64_t kShareRows = 128;                  // at most, by two workgroups or more
 constexpr int64_t kShareLeastV = 50000;              // of any type
 // Workgroups that share each of `rows` rows (1: none do): as many as fill the chip, a run for every wave at least.  A launch
-// more (two microseconds, and a table made again) against the sweep of a row by one compute unit, so rows from the
+// more (two microseconds, the terms' table made by every part) against the sweep of a row by one compute unit, so rows from the
 // length on where that is some 6 us (BitTerms' terms are the cheapest, and binary16 has twice fp32's in a run).  us a round by
-// one workgroup a row / shared, 1 x 4 and 8 x 8: fp32 32000 14.1 / 15.0 and 15.3 / 16.9, 64000 18.3 / 15.4 and 19.1 / 17.9,
-// 128256 25.3 / 15.4 and 26.4 / 20.7, 256000 40.1 / 15.6 and 42.2 / 26.7; binary16 64000 19.2 / 18.1 and 19.6 / 19.0, 128256
-// 26.1 / 17.5 and 27.0 / 21.3; bfloat16 64000 15.8 / 17.5 and 16.9 / 18.0, 128256 19.9 / 17.1 and 20.6 / 19.3, 256000 26.4 / 17.1
-// and 27.5 / 21.5.  The sampled rows of larger batches alone: 48 x 5 fp32 V = 151936 53.2 / 43.9, 64 x 8 bfloat16 256000 67.5 / 61.3.
-// By two workgroups a row (more than a third as many rows as compute units) later: 16 x 7 bfloat16 112000 19.9 / 20.5, 128256
-// 20.7 / 20.5; 9 x 13 fp32 60000 22.6 / 23.3, 16 x 7 64000 19.7 / 19.4.
+// one workgroup a row / shared, 1 x 4 and 8 x 8: fp32 50000 15.8 / 14.8 and 16.4 / 16.0, 64000 17.2 / 15.2 and 18.2 / 17.1, 96000
+// 20.6 / 15.2 and 21.7 / 18.8; binary16 60000 18.5 / 17.8 and 19.2 / 18.6, 96000 21.8 / 17.4 and 22.5 / 18.9; bfloat16 100000
+// 17.7 / 17.1 and 18.1 / 18.1, 128256 19.0 / 17.0 and 19.8 / 18.5, 200000 23.2 / 16.9 and 23.6 / 20.5.  The sampled rows of larger
+// batches alone: 48 x 5 fp32 96000 36.9 / 32.8, binary16 by its bit table 152064 46.0 / 42.2 (40 x 7).
+// By two workgroups a row (more than a third as many rows as compute units) later; 16 x 7, trees 8 x <2,2,2> and the sampled rows of
+// 128 x 4: fp32 68000 18.5 / 18.8, 22.0 / 22.0 and 39.8 / 40.8, 76000 21.0 / 20.5, 24.2 / 24.4 and 45.9 / 46.1, 84000 22.0 / 21.0 and
+// 49.4 / 48.8; binary16 72000 20.2 / 20.5, 23.3 / 24.2 and 32.4 / 34.2, 78000 21.1 / 20.6, 24.4 / 24.1 and 34.8 / 35.0; bfloat16 125000
+// 19.7 / 19.9, 22.9 / 23.5 and 41.3 / 42.1, 155000 20.9 / 20.7, 24.4 / 24.3 and 48.1 / 48.3; binary16 by its bit table, 128 x 4 147456
+// 50.7 / 51.2, 170000 56.6 / 56.0.
 template <typename T, typename Terms> inline int64_t share_min_V(bool by_two) {
-  if (ElemTraits<T>::kBytes == 4) return by_two ? 64000 : kShareLeastV;
-  if (Terms::kBits) return by_two ? 125000 : 100000;
-  return 60000;
+  if (Terms::kBits) return by_two ? (kLargeTable<Terms> ? 165000 : 150000) : 100000;
+  return by_two ? 76000 : (ElemTraits<T>::kBytes == 4 ? kShareLeastV : 60000);
 }
 template <typename T, typename Terms> inline int row_parts(int64_t V, int64_t rows) {
   if (rows > kShareRows || V < share_min_V<T, Terms>(3 * rows > compute_units())) return 1;

@@ -31,8 +31,8 @@ def same(a, b):
 
 
 @pytest.mark.parametrize("dtype,V,B,gamma", [
-    ("f32", 50000, 3, 4), ("f32", 64001, 14, 8), ("f32", 151936, 40, 8),      # three workgroups a row, two, the sampled rows alone
-    ("f16", 60001, 2, 3), ("f16", 131072, 30, 12), ("bf16", 100003, 8, 8), ("bf16", 125000, 16, 7), ("bf16", 250001, 1, 1),
+    ("f32", 50000, 3, 4), ("f32", 64001, 14, 8), ("f32", 76001, 14, 8), ("f32", 151936, 40, 8),      # a dozen workgroups a row, none, two, the sampled rows alone
+    ("f16", 60001, 2, 3), ("f16", 131072, 30, 12), ("bf16", 100003, 8, 8), ("bf16", 125000, 16, 7), ("bf16", 150001, 16, 7), ("bf16", 250001, 1, 1),
 ])
 @pytest.mark.parametrize("broken", [False, True])
 def test_chain_of_shared_rows(tslt, dtype, V, B, gamma, broken):
