@@ -14,14 +14,20 @@ def up256(n):
     return (n + 255) // 256 * 256
 
 
-def odd_rows(t):
-    """A few rows of t [n, V] (n >= 6) that a sweep referenced to 0 cannot take, or only just."""
-    t[0, 77] = float("nan")
-    t[1] += 650.0
-    t[2, 1000:] = -float("inf")
-    t[3] = -float("inf")
-    t[4, ::3] = torch.finfo(t.dtype).min
-    t[5, -1] = float("inf")
+def odd_row(t, i):
+    """The i-th of six patterns that a sweep referenced to 0 cannot take, or only just, written into row t [V]."""
+    if i == 0:
+        t[77] = float("nan")
+    elif i == 1:
+        t += 650.0
+    elif i == 2:
+        t[1000:] = -float("inf")
+    elif i == 3:
+        t[:] = -float("inf")
+    elif i == 4:
+        t[::3] = torch.finfo(t.dtype).min
+    else:
+        t[-1] = float("inf")
 
 
 def same(a, b):
@@ -30,21 +36,10 @@ def same(a, b):
             assert torch.equal(v.nan_to_num(nan=-7.0), b[k].nan_to_num(nan=-7.0)) if v.is_floating_point() else torch.equal(v, b[k]), k
 
 
-@pytest.mark.parametrize("dtype,V,B,gamma", [
-    ("f32", 50000, 3, 4), ("f32", 64001, 14, 8), ("f32", 76001, 14, 8), ("f32", 151936, 40, 8),      # a dozen workgroups a row, none, two, the sampled rows alone
-    ("f16", 60001, 2, 3), ("f16", 131072, 30, 12), ("bf16", 100003, 8, 8), ("bf16", 125000, 16, 7), ("bf16", 150001, 16, 7), ("bf16", 250001, 1, 1),
-])
-@pytest.mark.parametrize("broken", [False, True])
-def test_chain_of_shared_rows(tslt, dtype, V, B, gamma, broken):
-    K = 64
-    w = W.scaled(W.WORKLOADS["chain_topk"], B=B, V=V, gamma=gamma, dtype=dtype, top_k=K, k_cap=K, T=0.8)
-    c = W.make_chain(w, 7, DEV)
-    tr = tslt.truncate(c["draft"].view(B * gamma, V), w.T, K, 0.0, K, u=c["u_sample"].view(B * gamma, 1))
-    target = c["target"]
-    if broken:
-        odd_rows(target.view(-1, V)[:: max(1, B * (gamma + 1) // 7)][:6] if B * (gamma + 1) >= 12 else target.view(-1, V).repeat(3, 1)[:6])
+def compare_chain(tslt, w, target, tr, c, u_accept):
+    B, gamma, V, K = w.B, w.gamma, w.V, w.k_cap
     args = (target, w.T, tr["idx"].view(B, gamma, K), tr["logit"].view(B, gamma, K), tr["count"].view(B, gamma),
-            tr["token"].view(B, gamma), c["u_accept"], c["u_resample"])
+            tr["token"].view(B, gamma), u_accept, c["u_resample"])
     least = 2 * up256(B * gamma * 4)
     told = tslt.workspace_bytes(tslt.OP_VERIFY, B, gamma, V, K)
     assert told > least
@@ -63,11 +58,59 @@ def test_chain_of_shared_rows(tslt, dtype, V, B, gamma, broken):
     same(alone, static)
     with pytest.raises(tslt.TsltError):
         tslt.verify(*args, workspace=ws[:least - 256])
+    return alone
+
+
+@pytest.mark.parametrize("dtype,V,B,gamma", [
+    ("f32", 50000, 3, 4), ("f32", 64001, 14, 8), ("f32", 76001, 14, 8),      # a dozen workgroups a row, none, two
+    ("f32", 151936, 40, 8),                                                  # the sampled rows alone, by six
+    ("f16", 60001, 2, 3), ("f16", 131072, 30, 12), ("bf16", 100003, 8, 8), ("bf16", 125000, 16, 7), ("bf16", 150001, 16, 7),
+    ("bf16", 250001, 1, 1),
+    ("f16", 147457, 40, 7), ("f16", 165001, 128, 2),                         # sampled through binary16's bit table, by six and two
+])
+@pytest.mark.parametrize("broken", [False, True])
+def test_chain_of_shared_rows(tslt, dtype, V, B, gamma, broken):
+    K = 64
+    w = W.scaled(W.WORKLOADS["chain_topk"], B=B, V=V, gamma=gamma, dtype=dtype, top_k=K, k_cap=K, T=0.8)
+    c = W.make_chain(w, 7, DEV)
+    tr = tslt.truncate(c["draft"].view(B * gamma, V), w.T, K, 0.0, K, u=c["u_sample"].view(B * gamma, 1))
+    intact, n = c["target"], B * (gamma + 1)
+    if not broken:
+        compare_chain(tslt, w, intact, tr, c, c["u_accept"])
+        return
+    u_accept = c["u_accept"].clone()
+    if n > 128:                    # the sampled rows alone: the patterns on bonus rows that are reached, and on rejected rows
+        target = intact.clone()
+        for i in range(6):
+            odd_row(target[i, gamma], i)
+            odd_row(target[6 + i, 0], i)
+        u_accept[:6] = 0.0
+        u_accept[6:12, 0] = 0.9999
+        out = compare_chain(tslt, w, target, tr, c, u_accept)
+        assert (out["accept_len"][:6] == gamma).all()
+        assert out["status"][:6].tolist() == [1, 0, 0, 2, 0, 1]
+        assert (out["tokens"][:6, gamma] < 0).tolist() == [True, False, False, True, False, True]
+        assert (out["status"][[6, 9, 11]] & 3).tolist() == [1, 2, 1] and out["ratio"][[6, 9, 11], 0].isnan().all()
+        return
+    for first in range(0, 6, min(n, 6)):                                     # (two rows: two patterns at a time)
+        target = intact.clone()
+        rows = target.view(-1, V)
+        at = torch.linspace(0, n - 1, min(n, 6)).long().tolist()
+        for k, r in enumerate(at):
+            odd_row(rows[r], first + k)
+        out = compare_chain(tslt, w, target, tr, c, u_accept)
+        for k, r in enumerate(at):
+            if r % (gamma + 1) < gamma:                                      # (of a bonus row nothing else is told)
+                assert out["ratio"][r // (gamma + 1), r % (gamma + 1)].isnan() == (first + k in (0, 3, 5)), (r, first + k)
+        if first == 0:
+            assert out["status"][0] & 1
 
 
 @pytest.mark.parametrize("dtype,V,B,expansion", [
     ("f32", 50001, 2, (2, 2, 2)), ("f32", 128256, 1, (4, 4, 4)), ("f16", 60000, 6, (3, 3)), ("bf16", 125001, 4, (2, 2, 2)),
-    ("f32", 100000, 30, (2, 2, 2)),                                          # of the path, the first layers alone at once
+    ("f32", 100000, 30, (2, 2, 2)),                                          # all layers at once, too many rows to share
+    # of the path, the first layers alone at once, by two workgroups a row
+    ("bf16", 150001, 40, (2, 2, 2)), ("f16", 100003, 18, (2, 2, 2, 2)), ("f32", 100001, 18, (2, 2, 2, 2)),
 ])
 @pytest.mark.parametrize("broken", [False, True])
 def test_trees_of_shared_rows(tslt, dtype, V, B, expansion, broken):
@@ -86,13 +129,18 @@ def test_trees_of_shared_rows(tslt, dtype, V, B, expansion, broken):
         node, width = node + width, width * k
     target = tree["target"].view(-1, V)
     if broken:
-        odd_rows(target[1::max(1, B * n // 8)][:6])
+        for i in range(6):         # of many trees six roots and a child of six more, else rows all over
+            if B >= 12:
+                odd_row(target[i * n], i)
+                odd_row(target[(6 + i) * n + 1], i)
+            else:
+                odd_row(target[1 + i * max(1, B * n // 8)], i)
     args = (tree["target"], w.T, list(expansion), idx.contiguous(), sets["logit"].view(B, n_int, K), sets["count"].view(B, n_int),
             torch.cat(cand, 1).contiguous(), tree["u_accept"], tree["u_resample"])
     n_seg = (V // 4 + 1 + 1023) // 1024
     least = 4 * up256(B * n * 4) + 2 * up256(B * 4) + up256(B * (n_seg + 2) * 16) + up256(B * n_seg * 32)
     told = tslt.workspace_bytes(tslt.OP_VERIFY_TREE_PATH, B, n, V, K)
-    assert told >= least
+    assert told > least
     alone = tslt.verify_tree(*args, all_nodes=False, workspace=torch.full((least,), 255, dtype=torch.uint8, device=DEV))
     ws = torch.full((told,), 255, dtype=torch.uint8, device=DEV)
     shared = tslt.verify_tree(*args, all_nodes=False, workspace=ws)
@@ -102,6 +150,12 @@ def test_trees_of_shared_rows(tslt, dtype, V, B, expansion, broken):
     assert torch.equal(every["seq"], alone["seq"]) and torch.equal(every["len"], alone["len"])
     tested = ~alone["ratio"].isnan()
     assert torch.equal(every["ratio"][tested], alone["ratio"][tested])
+    if broken and B >= 12:
+        assert (alone["status"][:6] & 3).tolist() == [1, 0, 0, 2, 0, 1]
+        assert (alone["seq"][:6, 0] < 0).tolist() == [True, False, False, True, False, True]
+    elif broken:
+        st = every["status"].tolist()
+        assert any(x & 1 for x in st) and any(x & 2 for x in st)
 
 
 def test_shared_rows_captured(tslt):
