@@ -342,21 +342,7 @@ template <int NW> __device__ __forceinline__ int block_or_i32(int v, BlockScratc
   return t;
 }
 
-// Block-wide exclusive scans in thread order; `total` receives the sum over the block.
-template <int NW> __device__ __forceinline__ double block_excl_scan_f64(double v, BlockScratch& s, double& total) {
-  const double inc = wave_incl_scan_f64(v);
-  __syncthreads();
-  if (lane_id() == 63) s.d[wave_id()] = inc;
-  __syncthreads();
-  double base = 0.0, t = 0.0;
-#pragma unroll
-  for (int w = 0; w < NW; ++w) {
-    if (w < wave_id()) base += s.d[w];
-    t += s.d[w];
-  }
-  total = t;
-  return base + inc - v;
-}
+// Block-wide exclusive scan in thread order; `total` receives the sum over the block.
 template <int NW> __device__ __forceinline__ int block_excl_scan_i32(int v, BlockScratch& s, int& total) {
   const int inc = wave_incl_scan_i32(v);
   __syncthreads();

@@ -41,7 +41,6 @@ struct TreeParams {
   int32_t* status;
   // workspace
   // (every node evaluated only)
-  int32_t* node_state;    // [B, n_nodes] 0 sampled, 1 a child accepted, 2 row unusable
   int32_t* node_slot;     // [B, n_nodes] accepted child number or -1
   int32_t* node_token;    // [B, n_nodes] the node's output
   int32_t* node_status;   // [B, n_nodes]
@@ -79,9 +78,8 @@ inline size_t tree_workspace_bytes(int64_t B, int64_t n_nodes, int64_t V, bool a
   return std::max(least, rows);
 }
 inline void tree_carve_workspace(TreeParams& p, void* ws, size_t ws_bytes) {
-  char* w = reinterpret_cast<char*>(ws);
   const size_t per = align256(size_t(p.B) * p.n_nodes * 4);
-  p.node_state = reinterpret_cast<int32_t*>(w); w += per;
+  char* w = reinterpret_cast<char*>(ws) + per;       // (the first of the four node arrays that are asked for is not used)
   p.node_slot = reinterpret_cast<int32_t*>(w); w += per;
   p.node_token = reinterpret_cast<int32_t*>(w); w += per;
   p.node_status = reinterpret_cast<int32_t*>(w); w += per;
@@ -207,10 +205,9 @@ __global__ __launch_bounds__(kRowThreads, kWavesPerSimd) void tree_node_kernel(c
     if (threadIdx.x == 0) sh.fetched = 0;
     __syncthreads();
   }
-  const int state = tree_node<T, Terms, kWavesPerSimd == kAlone>(p, b, node, reinterpret_cast<double*>(dyn_lds), true, sh, slot, token, st, items);
+  tree_node<T, Terms, kWavesPerSimd == kAlone>(p, b, node, reinterpret_cast<double*>(dyn_lds), true, sh, slot, token, st, items);
   if (threadIdx.x == 0) {
     const int64_t n = b * p.n_nodes + node;
-    p.node_state[n] = state;
     p.node_slot[n] = slot;
     p.node_token[n] = token;
     p.node_status[n] = st;

@@ -558,7 +558,7 @@ __global__ __launch_bounds__(NT, kWavesPerSimd) void truncate_kernel(const Trunc
     load_sample(rs, d);
     // The pass keeps kStages stages of kGroup tiles in flight per thread; the first ones are requested now, so
     // that they travel while the threshold is being worked out.  In a long row a sample tile is the first tile of
-    // its stage and is not read again; in a short one (512 threads) the stages begin behind the sample.  The row's ragged end
+    // its stage and is not read again; in a short one the stages begin behind the sample.  The row's ragged end
     // (the last tile possibly incomplete, the last stage possibly half empty) is the last stage.
     static_assert(kGroup == 2, "a stage is a pair of tiles");
     uint4 pipe[kStages][kGroup];
@@ -989,7 +989,7 @@ __global__ __launch_bounds__(NT, kWavesPerSimd) void truncate_kernel(const Trunc
   // the rounded values (q_hat is the softmax of what the receiver gets)
   double pw[kMaxPer];
   double p_excl = excl, p_total = c_sel;
-  auto scan_again = [&](double v, double& before, double& total) {      // block_excl_scan_f64 with one barrier
+  auto scan_again = [&](double v, double& before, double& total) {      // exclusive scan in thread order, and the sum
     const double inc = wave_incl_scan_f64(v);
     if (lane == 63) sh.red.d[wave] = inc;
     __syncthreads();
