@@ -261,9 +261,11 @@ int tslt_verify_accept_staged(const void* target_logits, tslt_dtype dt, int64_t 
 
 /* tslt_verify for callers that cannot allocate or bring a workspace: code under HIP graph capture, tight serving
  * loops, harnesses that forbid hipMalloc.  Same arguments as tslt_verify without `ws` / `ws_bytes`, same
- * kernels, same results; the per-position decisions and status words (8 bytes per draft position) live in an
+ * kernels, same results; what tslt_verify keeps in its workspace (the per-position decisions and status words, 8 bytes
+ * per draft position, and behind them the masses of the long rows of a small batch, which several workgroups sweep) lives in an
  * array that is part of the library's device image (TSLT_STATIC_MAX_POSITIONS positions, 2 MiB per GPU, held
- * until the process ends).  The call allocates nothing and calls no allocating routine.
+ * until the process ends).  Where the masses do not fit behind the rest, every row is left to one workgroup.  The call
+ * allocates nothing and calls no allocating routine.
  *   - B * gamma above TSLT_STATIC_MAX_POSITIONS returns TSLT_ERR_UNSUPPORTED (use tslt_verify and a workspace).
  *   - The first call on a device looks up the array's address on that device (hipGetSymbolAddress) and keeps
  *     it; make that first call outside a stream capture.

@@ -166,7 +166,8 @@ __device__ __forceinline__ uint4 load_vec(const uint4* p) {
 // from scalar registers, a per-thread byte offset that never changes (lane * 16) from a vector register and
 // the moving part of the address from a scalar one, so that a streaming loop spends no vector instruction on
 // addresses; a load that reaches past the body's end returns zeros instead of faulting (the hardware checks
-// the range), and the loops give such vectors the value they need afterwards.  The body must be below 4 GiB.
+// the range of the whole offset, also where the scalar part alone lies far beyond the size: measured on gfx950), and the
+// loops give such vectors the value they need afterwards.  The body must be below 4 GiB.
 __device__ __forceinline__ __amdgpu_buffer_rsrc_t row_buffer(const uint4* body, uint32_t nvec) {
   // (third dword: raw buffer of 32-bit data, the setting of the GFX9 family)
   return __builtin_amdgcn_make_buffer_rsrc(const_cast<uint4*>(body), 0, int(nvec * 16u), 0x00020000);

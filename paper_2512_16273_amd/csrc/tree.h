@@ -58,10 +58,10 @@ struct TreeParams {
   int64_t items_rows;     // there is room for (read on the host)
 };
 
-// (Evaluating every node uses the node arrays alone.  The rest, two words a tree and the masses of a row's items, is for the
-// path; with node outputs it is still asked for once a node: the size that callers have been told all along, so that a
-// workspace kept from an earlier version and one sized by this one are the same.  For the path a call may be given less
-// than it is told to bring: the rows of a small tree's nodes are then not shared.)
+// (Evaluating every node uses three of the four node arrays and, where the rows of few nodes are shared by workgroups, the masses of
+// their items; the two words a tree are for the path.  With node outputs masses are asked for once a node: the size that
+// callers have been told all along, so that a workspace kept from an earlier version and one sized by this one are the same.
+// For the path a call may be given less than it is told to bring: the rows of a small tree's nodes are then not shared.)
 inline int64_t tree_items_stride(int64_t V) { return int64_t(row_segments(V)) * kSubChunks + 2; }
 inline size_t tree_least_workspace_bytes(int64_t B, int64_t n_nodes, int64_t V, bool all_nodes) {
   const size_t n_seg = size_t(row_segments(V));

@@ -39,9 +39,9 @@ constexpr int kGroup = 2;        // tiles (one 16-byte vector per thread each) i
 //   "Tall": 512 threads and four stages, for batches that leave the chip to one or two rows per compute unit, bound by
 // a row's own latency: twice the requests in flight, rows shorter than the sample's distances through the same pipeline
 // (they went pair by pair, a memory latency each), the threshold out of a histogram.  us by 256 / 512 threads: 1 row
-// binary16 V = 32000 14.8 / 13.0, 64 bfloat16 V = 128256 27.0 / 21.7, 200 28.1 / 23.2, 384 29.8 / 28.3, 700 42.1 / 46.7;
-// 100 fp32 V = 151936 40.6 / 27.8, 400 51.2 / 51.2.  1024 threads are slower again (14.9, 23.4, 25.6 us).
-// (All before the passes and the sort were shortened: by 512 threads the first two take 10.8 and 17.8 now.)
+// binary16 V = 32000 12.7 / 10.0, 64 bfloat16 V = 128256 25.1 / 17.5, 200 28.3 / 18.3, 384 32.4 / 26.0, 700 38.8 / 38.0;
+// 100 fp32 V = 151936 41.9 / 24.4, 400 50.9 / 43.6.  (1024 threads, before the pass and the sort were shortened: slower
+// again, 14.9, 23.4 and 25.6 us for the first three, which took 13.0, 21.7 and 23.2 then.)
 constexpr int kTallThreads = 512;
 constexpr int kStagesWide = 2, kWavesWide = 8;
 constexpr int kStagesDeep = 4, kWavesDeep = 4;

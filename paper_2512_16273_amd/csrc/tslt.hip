@@ -19,8 +19,8 @@
 #include "stats.h"
 #include "calib.h"
 
-// Scratch memory of tslt_verify_static: the per-position decisions and status words that tslt_verify keeps in
-// its caller's workspace.  Every GPU the library runs on holds its own copy until the process ends.  In host
+// Scratch memory of tslt_verify_static: what tslt_verify keeps in its caller's workspace, the per-position decisions and status
+// words and, where there is room behind them, the masses of rows that workgroups share.  Every GPU the library runs on holds its own copy until the process ends.  In host
 // code the name is only a handle for hipGetSymbolAddress; kernels are given the address that call returns.
 #define TSLT_STATIC_SCRATCH_BYTES (2 * 4 * TSLT_STATIC_MAX_POSITIONS)
 static __device__ __align__(256) unsigned char scratch[TSLT_STATIC_SCRATCH_BYTES];
@@ -132,11 +132,12 @@ bool sparse_hits(tslt_dtype dt, int64_t V, int nt, const tslt::TruncateParams& p
   return 128.0 * h + 5.0 * std::sqrt(128.0 * h) <= tslt::kRingSmall - tslt::kRingExpand;
 }
 // Whether 512 threads take a row: where every row has a compute unit to itself (but for the shortest, of few tiles more than
-// the sample or less than that: 70 fp32 rows of 9088 10.2 us by 256 threads, 10.7 by 512; binary16 9.8 / 10.2; 16000
-// 12.1 / 11.4 and 10.5 / 10.2),
+// the sample or less than that, where there is little to gain: 70 fp32 rows of 9088 9.4 us by 256 threads, 9.0 by 512; binary16
+// 9.1 / 8.7; 16000 10.6 / 9.8 and 9.5 / 8.8),
 // and up to three rows for two compute units if a row is neither short nor very long (us by 256 / 512 threads, 306
-// rows: bfloat16 16000 11.3 / 12.2, 60000 19.0 / 20.4, 128256 28.0 / 27.5, 213696 39.8 / 38.3; fp32 25240 16.3 / 17.4, 60000
-// 24.2 / 22.6, 128256 39.9 / 38.2, 213696 55.8 / 58.9; both have since become 3 to 17 % faster, and the lines stay).
+// rows: bfloat16 16000 11.3 / 11.4, 41000 15.6 / 16.4, 82000 22.5 / 20.5, 128256 29.9 / 24.4, 256000 48.9 / 40.2; fp32 16000 12.4 /
+// 12.9, 60000 25.0 / 20.0, 128256 44.3 / 36.2, 213696 54.8 / 55.8, 256000 63.5 / 67.6.  Sets of 64; the lines are on the safe side:
+// 60000 bfloat16 values 18.5 / 18.3, 25240 fp32 ones 16.2 / 15.2, 180000 58.0 / 49.1.)
 bool tall_rows(tslt_dtype dt, int64_t V, int64_t rows) {
   const int64_t cus = tslt::compute_units(), kb = V * elem_bytes(dt) >> 10;
   if (rows <= cus) return V >= 10240;
