@@ -348,7 +348,7 @@ template <typename T> __device__ __forceinline__ void row_edges(const RowWork<T>
   const double head = wave_sum_f64(lane < w.rs.head ? t : 0.0), tail = wave_sum_f64(lane < w.rs.head ? 0.0 : t);
   if (lane == 0) { sh.items[0] = head; sh.items[w.n_items - 1] = tail; }
 }
-template <typename T, typename Terms, bool kOneCopy = false>
+template <typename T, typename Terms, bool kOneCopy = false, bool kPart = false>
 __device__ __forceinline__ void row_pass(RowWork<T>& w, double* table, int half, int run0, int run1, bool ends, RowShared& sh) {
   const int lane = lane_id(), wave = wave_id();
   const RowSplit& rs = w.rs;
@@ -371,16 +371,17 @@ __device__ __forceinline__ void row_pass(RowWork<T>& w, double* table, int half,
     // binary16 trees <2,2,2> of 32000, the path: 40.3 us with the loops, 39.5 without.)
     const uint64_t row_at = reinterpret_cast<uint64_t>(rs.body);
     const uint32_t row_lo = __builtin_amdgcn_readfirstlane(uint32_t(row_at)), row_hi = __builtin_amdgcn_readfirstlane(uint32_t(row_at >> 32));
-    // (The buffer ends where run1 does: in a part of a row what lies behind is the next workgroup's, and the run that a wave
-    // requests ahead of its last one would be fetched to be dropped.  48 x 6 fp32 rows of 151936, five parts of 30 runs each:
+    // (A part's buffer ends where the part does: what lies behind is the next workgroup's, and the run that a wave requests
+    // ahead of its last one would be fetched to be dropped.  48 x 6 fp32 rows of 151936, five parts of 30 runs each:
     // verify_part_kernel took 20.5 MB from memory and 10.1 us so, 14.3 and 9.9 now.)
-    const uint32_t end_vec = uint32_t(__builtin_amdgcn_readfirstlane(std::min(nvec, uint32_t(run1) * kRunVecs)));
-    const __amdgpu_buffer_rsrc_t body = row_buffer(reinterpret_cast<const uint4*>((uint64_t(row_hi) << 32) | row_lo), end_vec);
+    const uint32_t end_vec = kPart ? std::min(nvec, uint32_t(run1) * kRunVecs) : nvec;
+    const __amdgpu_buffer_rsrc_t body =
+        row_buffer(reinterpret_cast<const uint4*>((uint64_t(row_hi) << 32) | row_lo), uint32_t(__builtin_amdgcn_readfirstlane(end_vec)));
     auto request = [&](int run, uint4 (&q)[kSegVecs]) {
       if constexpr (!Terms::kBits) {
-        const uint32_t at = std::min(uint32_t(__builtin_amdgcn_readfirstlane(run)) * (kRunVecs * 16u), end_vec * 16u);
+        const uint32_t at = uint32_t(__builtin_amdgcn_readfirstlane(run)) * (kRunVecs * 16u);
 #pragma unroll
-        for (int i = 0; i < kSegVecs; ++i) q[i] = buffer_load_vec_stream(body, lane * 16u + i * 1024u, at);
+        for (int i = 0; i < kSegVecs; ++i) q[i] = buffer_load_vec_stream(body, lane * 16u, at + i * 1024u);
       } else {
         const uint32_t vbase = uint32_t(run < run1 ? run : run1 - 1) * kRunVecs + lane;
 #pragma unroll
@@ -523,7 +524,7 @@ __device__ __forceinline__ void row_part(RowWork<T>& w, double* table, int part,
   w.ql = w.ql0 = 0.0f;
   const int per = (w.n_runs + parts - 1) / parts;
   const int run0 = part * per, run1 = run0 + per < w.n_runs ? run0 + per : w.n_runs;
-  row_pass<T, Terms>(w, table, -1, run0, run1, part == 0, sh);
+  row_pass<T, Terms, false, true>(w, table, -1, run0, run1, part == 0, sh);
   const bool broken = (sh.flags & 3) != 0;
   const double bad = __longlong_as_double(0x7FF8000000000000ll);
   for (int i = run0 + threadIdx.x; i < run1; i += kRowThreads) out[1 + i] = broken ? bad : sh.items[1 + i];
@@ -557,14 +558,16 @@ constexpr int64_t kShareLeastV = 50000;              // of any type
 // 20.6 / 15.2 and 21.7 / 18.8; binary16 60000 18.5 / 17.8 and 19.2 / 18.6, 96000 21.8 / 17.4 and 22.5 / 18.9; bfloat16 100000
 // 17.7 / 17.1 and 18.1 / 18.1, 128256 19.0 / 17.0 and 19.8 / 18.5, 200000 23.2 / 16.9 and 23.6 / 20.5.  The sampled rows of larger
 // batches alone: 48 x 5 fp32 96000 36.9 / 32.8, binary16 by its bit table 152064 46.0 / 42.2 (40 x 7).
-// By two workgroups a row (more than a third as many rows as compute units) later; 16 x 7, trees 8 x <2,2,2> and the sampled rows of
-// 128 x 4: fp32 68000 18.5 / 18.8, 22.0 / 22.0 and 39.8 / 40.8, 76000 21.0 / 20.5, 24.2 / 24.4 and 45.9 / 46.1, 84000 22.0 / 21.0 and
-// 49.4 / 48.8; binary16 72000 20.2 / 20.5, 23.3 / 24.2 and 32.4 / 34.2, 78000 21.1 / 20.6, 24.4 / 24.1 and 34.8 / 35.0; bfloat16 125000
-// 19.7 / 19.9, 22.9 / 23.5 and 41.3 / 42.1, 155000 20.9 / 20.7, 24.4 / 24.3 and 48.1 / 48.3; binary16 by its bit table, 128 x 4 147456
-// 50.7 / 51.2, 170000 56.6 / 56.0.
+// By two workgroups a row (more than a third as many rows as compute units) fp32 and bfloat16 later; 16 x 7, trees 8 x <2,2,2> and
+// the sampled rows of 128 x 4: fp32 60000 18.4 / 18.8, 21.6 / 21.8 and 37.5 / 39.3, 76000 20.6 / 20.6, 24.0 / 23.8 and 44.5 / 45.1, 84000
+// 22.0 / 21.0 and 49.4 / 48.8 (16 x 7, 128 x 4); bfloat16 125000 19.8 / 20.0, 23.0 / 23.4 and 41.3 / 42.1, 155000 21.1 / 20.6, 24.4 / 24.2
+// and 48.1 / 48.3; binary16 56000 18.7 / 18.0, 21.2 / 21.2 and 29.1 / 29.5, 60000 19.1 / 18.1, 22.4 / 21.4 and 30.4 / 30.2, 72000 (a part
+// is a few runs more than its waves) 20.1 / 20.1, 23.3 / 23.4 and 33.1 / 33.7, 78000 21.6 / 20.2, 24.6 / 23.7 and 35.6 / 35.3; by its bit
+// table 128 x 2 147456 40.8 / 40.6, 160000 42.8 / 42.3.
 template <typename T, typename Terms> inline int64_t share_min_V(bool by_two) {
-  if (Terms::kBits) return by_two ? (kLargeTable<Terms> ? 165000 : 150000) : 100000;
-  return by_two ? 76000 : (ElemTraits<T>::kBytes == 4 ? kShareLeastV : 60000);
+  if (ElemTraits<T>::kBytes == 4) return by_two ? 76000 : kShareLeastV;
+  if (Terms::kBits) return by_two && !kLargeTable<Terms> ? 150000 : 100000;
+  return 60000;
 }
 template <typename T, typename Terms> inline int row_parts(int64_t V, int64_t rows) {
   if (rows > kShareRows || V < share_min_V<T, Terms>(3 * rows > compute_units())) return 1;
