@@ -16,12 +16,11 @@
 // Bound by memory in large batches (2048 bfloat16 rows of 128256: 92 us, of which 81 are the reading), by the instructions a
 // row's waves issue one after the other in small ones.  The pass is written for the second: an fma takes its operands from
 // vector registers without a sign to change (2.7 cycles a wave, 4.4 otherwise), binary16 is tested against the threshold as
-// packed halves and never widened, addresses are a scalar offset into a buffer, the complete stages have a loop without a
+// packed halves and never widened, addresses are a scalar offset into a buffer (but for large batches), the complete stages have a loop without a
 // check for the row's end, and every exchange between waves behind the pass is one barrier (12 in all, 24 before).  us
 // before / now: 1 binary16 row of 32000, k 320 12.4 / 10.8; 64 bfloat16 rows of 128256, k 256 20.5 / 17.8; 19 binary16 rows of
 // 223104 27.7 / 23.0; 600 binary16 rows of 32000 17.7 / 15.8; 4096 bfloat16 rows of 256000, k 1024 407 / 396.
 #pragma once
-#include <type_traits>
 #include "common.h"
 #include "wire.h"
 #include "exp64.h"
@@ -565,9 +564,17 @@ __global__ __launch_bounds__(NT, kWavesPerSimd) void truncate_kernel(const Trunc
     const uint32_t tile0 = long_row ? 0u : uint32_t(kBatch);                    // of the first stage
     const uint32_t n_stage = n_tiles > tile0 ? (n_tiles - tile0 + kGroup - 1) / kGroup : 0u;
     const uint32_t stride_g = s_stride / kGroup;
-    // (the row as a buffer: no vector instruction goes into addresses; what lies past the row's end comes back as zeros)
+    // The row as a buffer: no vector instruction goes into addresses; what lies past the row's end comes back as zeros.  Not
+    // in the wide shape, where other workgroups fill the vector units in any case and requests through a buffer are slower
+    // (us by buffer / by address: 500 rows of 151936, sets of 200 to 256, bfloat16 37.2 / 35.0, binary16 35.5 / 33.9; 450 fp32 rows,
+    // sets of 32, 51.0 / 48.5; 2728 254.9 / 253.0; the deep shape, 1000 fp32 rows of 151936, sets of 1024, 114.8 / 116.5).
+    constexpr bool kBuffer = kWavesPerSimd < kWavesWide;
     const __amdgpu_buffer_rsrc_t body = row_buffer(rs.body, nvec);
-    const uint32_t lane_bytes = uint32_t(tid) * 16u;
+    auto request = [&](uint32_t at) -> uint4 {          // of a tile that begins `at` bytes into the row's body
+      if constexpr (kBuffer) return buffer_load_vec_stream(body, uint32_t(tid) * 16u, at);
+      const uint32_t vi = at / 16u + tid;
+      return load_vec_stream(&rs.body[vi < nvec - 1 ? vi : nvec - 1]);
+    };
     // stages 0, stride_g, 2 stride_g, 3 stride_g begin with a sample tile
     constexpr uint32_t kNever = 0xFFFFFFFFu;
     uint32_t skip_g = long_row ? 0u : kNever, issue_at = tile0 * (NT * 16u);
@@ -582,8 +589,8 @@ __global__ __launch_bounds__(NT, kWavesPerSimd) void truncate_kernel(const Trunc
         skip_g = next_sample(g);
       }
       issue_at = at_b + NT * 16u;
-      q[0] = buffer_load_vec_stream(body, lane_bytes, at_a);
-      q[1] = buffer_load_vec_stream(body, lane_bytes, at_b);
+      q[0] = request(at_a);
+      q[1] = request(at_b);
     };
     // (not yet for the short rows of a large batch, whose sample it would hold up: 2000 fp32 rows of 16000 27.2 and 25.6 us)
     const bool early = kTall || long_row;
@@ -771,13 +778,9 @@ __global__ __launch_bounds__(NT, kWavesPerSimd) void truncate_kernel(const Trunc
           for (int e = 0; e < w; ++e) t[e] += t[e + w];
         return t[0];
       };
-      auto process_pair = [&](uint4 w0, uint4 w1, uint32_t vidx0, uint32_t vidx1, auto packed) -> float {
+      auto process_pair = [&](uint4 w0, uint4 w1, uint32_t vidx0, uint32_t vidx1) -> float {
         float a[E], b[E], t[2 * E];
         const bool hit_a = HitTest<T>::hit(w0, tau), hit_b = HitTest<T>::hit(w1, tau);
-        if constexpr (decltype(packed)::value) {       // registers are short: the vectors wait in their packed form
-          park(hit_a, hit_b, w0, w1, vidx0, vidx1);
-          asm volatile("" : "+v"(w0.x), "+v"(w0.y), "+v"(w0.z), "+v"(w0.w), "+v"(w1.x), "+v"(w1.y), "+v"(w1.z), "+v"(w1.w));
-        }
         unpack<T>(w0, a);
         unpack<T>(w1, b);
 #pragma unroll
@@ -786,7 +789,7 @@ __global__ __launch_bounds__(NT, kWavesPerSimd) void truncate_kernel(const Trunc
           t[E + e] = fast_exp2(__builtin_fmaf(b[e], k2, neg_c));
         }
         const float pair_sum = sum_of(t);
-        if constexpr (!decltype(packed)::value) park(hit_a, hit_b, w0, w1, vidx0, vidx1);
+        park(hit_a, hit_b, w0, w1, vidx0, vidx1);
         return pair_sum;
       };
       // the second vector of a pair whose first is done
@@ -808,7 +811,7 @@ __global__ __launch_bounds__(NT, kWavesPerSimd) void truncate_kernel(const Trunc
         float both = 0.0f;
 #pragma unroll 1
         for (uint32_t t = 0; t <= 2 * t1; t += 2 * t1) {              // (s_stride > 0)
-          both += process_pair(d[0], d[1], t * NT + tid, (t + t1) * NT + tid, std::bool_constant<(kWavesPerSimd >= 8 && std::is_same<T, Bf16>::value)>{});
+          both += process_pair(d[0], d[1], t * NT + tid, (t + t1) * NT + tid);
           d[0] = d[2];
           d[1] = d[3];
         }
@@ -834,7 +837,7 @@ __global__ __launch_bounds__(NT, kWavesPerSimd) void truncate_kernel(const Trunc
           const uint32_t v0 = (tile0 + g * kGroup) * NT + tid;
           // (their distance is a multiple of kUnit tiles)
           const bool seen = s % (kUnit / kGroup) == 0 && sample_stage(g);
-          const float ps = seen ? process_second(pipe[s][1], v0 + NT) : process_pair(pipe[s][0], pipe[s][1], v0, v0 + NT, std::false_type{});
+          const float ps = seen ? process_second(pipe[s][1], v0 + NT) : process_pair(pipe[s][0], pipe[s][1], v0, v0 + NT);
           two = (s & 1) && !apart ? two + ps : ps;
           if ((s & 1) || apart) dacc += double(two);
           issue(g + kStages, pipe[s]);
@@ -848,7 +851,7 @@ __global__ __launch_bounds__(NT, kWavesPerSimd) void truncate_kernel(const Trunc
         if (sample_stage(g)) pipe[0][0] = neg_inf_vec<T>();
         if (v0 >= nvec) pipe[0][0] = neg_inf_vec<T>();
         if (v0 + NT >= nvec) pipe[0][1] = neg_inf_vec<T>();
-        const float ps = process_pair(pipe[0][0], pipe[0][1], v0, v0 + NT, std::false_type{});
+        const float ps = process_pair(pipe[0][0], pipe[0][1], v0, v0 + NT);
         const bool odd = (g - g0) & 1;
         two = odd && !apart ? two + ps : ps;
         if (odd || apart || g + 1 == n_stage) dacc += double(two);    // (a lone last stage's sum is added as it is)
