@@ -176,6 +176,10 @@ __device__ __forceinline__ uint4 buffer_load_vec_stream(__amdgpu_buffer_rsrc_t r
   u32x4_t v = __builtin_amdgcn_raw_buffer_load_b128(r, int(lane_bytes), int(wave_bytes), 2);      // 2: nontemporal
   return make_uint4(v.x, v.y, v.z, v.w);
 }
+__device__ __forceinline__ uint4 buffer_load_vec(__amdgpu_buffer_rsrc_t r, uint32_t lane_bytes, uint32_t wave_bytes) {
+  u32x4_t v = __builtin_amdgcn_raw_buffer_load_b128(r, int(lane_bytes), int(wave_bytes), 0);
+  return make_uint4(v.x, v.y, v.z, v.w);
+}
 // max of three without the NaN-quieting moves the compiler adds around fmaxf (NaNs are found by other means)
 __device__ __forceinline__ float max3f(float a, float b, float c) {
   float r;

@@ -348,7 +348,18 @@ template <typename T> __device__ __forceinline__ void row_edges(const RowWork<T>
   const double head = wave_sum_f64(lane < w.rs.head ? t : 0.0), tail = wave_sum_f64(lane < w.rs.head ? 0.0 : t);
   if (lane == 0) { sh.items[0] = head; sh.items[w.n_items - 1] = tail; }
 }
-template <typename T, typename Terms, bool kOneCopy = false, bool kPart = false>
+// How PowTerms' rows are loaded: streamed past the caches through a buffer; and of fp32 rows, through a buffer into the caches, or by
+// address.  A row that an earlier launch of the call has read may still be in a cache, but streaming keeps room for the ones that
+// wait: the sampled rows of chains are better streamed in batches that fit the Infinity Cache (us streamed / cached: 400 x 4 fp32
+// rows of 16000 30.9 / 32.3, 256 x 5 of 32000 36.5 / 37.8, 200 x 2 of 100000 38.6 / 39.7; 130 x 4 of 151936 70.6 / 69.8, 300 x 3 117.2 /
+// 111.8, 512 x 2 of 100000 80.1 / 76.2) or where they do not fit it themselves (512 x 2 of 256000 175.8 / 181.7), those of quick walks up to more than that (64 trees <4,2> of 152064 61.5 / 62.2, 512 <1,1,1,1> of
+// 32000 79.2 / 80.5; 512 of 64000 119.7 / 116.7, 400 <4,2> of 99968 112.2 / 108.0, 80 <3,3> of 256000 87.9 / 83.5).  A walk over
+// rows of a run or two a wave is faster by address (streamed / so: 400 trees <4,2> of 20000 48.7 / 46.5, 1000 <3> of 32000 83.2 / 82.0, of
+// 64000 118.2 / 121.2).
+enum { kStreamed = 0, kCached = 1, kByAddress = 2 };
+constexpr int64_t kStreamBytes = int64_t(256) << 20, kCachedBytes = int64_t(400) << 20, kStreamTreeBytes = int64_t(600) << 20;
+constexpr int64_t kByAddressV = 48000;
+template <typename T, typename Terms, bool kOneCopy = false, int kLoads = kStreamed, bool kPart = false>
 __device__ __forceinline__ void row_pass(RowWork<T>& w, double* table, int half, int run0, int run1, bool ends, RowShared& sh) {
   const int lane = lane_id(), wave = wave_id();
   const RowSplit& rs = w.rs;
@@ -378,10 +389,11 @@ __device__ __forceinline__ void row_pass(RowWork<T>& w, double* table, int half,
     const __amdgpu_buffer_rsrc_t body =
         row_buffer(reinterpret_cast<const uint4*>((uint64_t(row_hi) << 32) | row_lo), uint32_t(__builtin_amdgcn_readfirstlane(end_vec)));
     auto request = [&](int run, uint4 (&q)[kSegVecs]) {
-      if constexpr (!Terms::kBits) {
+      if constexpr (!Terms::kBits && !(kLoads == kByAddress && ElemTraits<T>::kBytes == 4)) {
         const uint32_t at = uint32_t(__builtin_amdgcn_readfirstlane(run)) * (kRunVecs * 16u);
 #pragma unroll
-        for (int i = 0; i < kSegVecs; ++i) q[i] = buffer_load_vec_stream(body, lane * 16u, at + i * 1024u);
+        for (int i = 0; i < kSegVecs; ++i)
+          q[i] = kLoads == kCached ? buffer_load_vec(body, lane * 16u, at + i * 1024u) : buffer_load_vec_stream(body, lane * 16u, at + i * 1024u);
       } else {
         const uint32_t vbase = uint32_t(run < run1 ? run : run1 - 1) * kRunVecs + lane;
 #pragma unroll
@@ -452,10 +464,10 @@ __device__ __forceinline__ void row_pass(RowWork<T>& w, double* table, int half,
 }
 // The masses of all the row's items, referenced to w.smax (0, or the row's maximum where it needs that), and sh.flags
 // (bit 0: NaN or +inf).
-template <typename T, typename Terms, bool kOneCopy = false>
+template <typename T, typename Terms, bool kOneCopy = false, int kLoads = kStreamed>
 __device__ __forceinline__ void row_sweep(RowWork<T>& w, double* table, int half, RowShared& sh) {
   constexpr int E = ElemTraits<T>::kPerVec;
-  row_pass<T, Terms, kOneCopy>(w, table, half, 0, w.n_runs, true, sh);
+  row_pass<T, Terms, kOneCopy, kLoads>(w, table, half, 0, w.n_runs, true, sh);
   const int tid = threadIdx.x, lane = lane_id(), wave = wave_id();
   const RowSplit& rs = w.rs;
   const int n_runs = w.n_runs;
@@ -517,14 +529,14 @@ __device__ __forceinline__ void row_sweep(RowWork<T>& w, double* table, int half
 
 // One of `parts` workgroups that share a row: the masses of its runs, and the first one's of the elements outside the aligned
 // body, stored for a launch that takes them up; NaN where it met something that asks for a sweep by the row's maximum.
-template <typename T, typename Terms>
+template <typename T, typename Terms, int kLoads>
 __device__ __forceinline__ void row_part(RowWork<T>& w, double* table, int part, int parts, double* out, RowShared& sh) {
   w.count = 0;                                       // no set
   w.y = -1;
   w.ql = w.ql0 = 0.0f;
   const int per = (w.n_runs + parts - 1) / parts;
   const int run0 = part * per, run1 = run0 + per < w.n_runs ? run0 + per : w.n_runs;
-  row_pass<T, Terms, false, true>(w, table, -1, run0, run1, part == 0, sh);
+  row_pass<T, Terms, false, kLoads, true>(w, table, -1, run0, run1, part == 0, sh);
   const bool broken = (sh.flags & 3) != 0;
   const double bad = __longlong_as_double(0x7FF8000000000000ll);
   for (int i = run0 + threadIdx.x; i < run1; i += kRowThreads) out[1 + i] = broken ? bad : sh.items[1 + i];

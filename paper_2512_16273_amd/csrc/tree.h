@@ -111,7 +111,7 @@ __device__ __forceinline__ int tree_first_child(const TreeParams& p, int node, i
 // `slot`, the output in `token` and the status bits in `st` (both as the first wave has them).  Unless a child was
 // accepted the terms' table is used up.  `items`: the row's masses, where they have been made already (else null).
 // ---------------------------------------------------------------------------------------------
-template <typename T, typename Terms, bool kOneCopy = false>
+template <typename T, typename Terms, bool kOneCopy = false, int kLoads = kStreamed>
 __device__ __forceinline__ int tree_node(const TreeParams& p, int64_t b, int node, double* table, bool build, RowShared& sh,
                                          int& slot, int& token, int& st, const double* items = nullptr) {
   const int lane = lane_id();
@@ -128,7 +128,7 @@ __device__ __forceinline__ int tree_node(const TreeParams& p, int64_t b, int nod
   const int my_cand = p.cand_tokens[c0 + (lane < k ? lane : 0)];
   const float my_u = p.u_accept[c0 + (lane < k ? lane : 0)];
   if (items != nullptr) row_fetch<T, Terms>(w, items, table, sh);
-  else row_sweep<T, Terms, kOneCopy>(w, table, build ? -1 : -2, sh);
+  else row_sweep<T, Terms, kOneCopy, kLoads>(w, table, build ? -1 : -2, sh);
   token = -1;
   st = 0;
   float my_ratio = NAN, my_beta = NAN;                              // NaN if the candidate is never tested
@@ -225,7 +225,7 @@ __global__ __launch_bounds__(kRowThreads, kAlone) void tree_share_kernel(const T
   const int part = int(blockIdx.x - at * p.parts);
   RowWork<T> w;
   row_open<T>(w, tree_row<T>(p, b, int(at - b * p.n_eval)), p.V, p.rT, sh);
-  row_part<T, Terms>(w, reinterpret_cast<double*>(dyn_lds), part, p.parts, p.items + at * p.items_stride, sh);
+  row_part<T, Terms, kStreamed>(w, reinterpret_cast<double*>(dyn_lds), part, p.parts, p.items + at * p.items_stride, sh);
 }
 
 // The new-sequence search through the layers that have been evaluated: all threads of the calling workgroup; the first
@@ -411,7 +411,7 @@ __global__ __launch_bounds__(NT) void tree_quick_kernel(const TreeParams p) {
   }
 }
 // The row of the node at which it stopped, shared by p.parts workgroups: the masses of its items.
-template <typename T, typename Terms>
+template <typename T, typename Terms, int kLoads>
 __global__ __launch_bounds__(kRowThreads, kAlone) void tree_part_kernel(const TreeParams p) {
   __shared__ RowShared sh;
   extern __shared__ __align__(16) unsigned char dyn_lds[];
@@ -419,7 +419,7 @@ __global__ __launch_bounds__(kRowThreads, kAlone) void tree_part_kernel(const Tr
   const int part = int(blockIdx.x - b * p.parts);
   RowWork<T> w;
   row_open<T>(w, tree_row<T>(p, b, p.walk_node[b]), p.V, p.rT, sh);
-  row_part<T, Terms>(w, reinterpret_cast<double*>(dyn_lds), part, p.parts, p.items + b * p.items_stride, sh);
+  row_part<T, Terms, kLoads>(w, reinterpret_cast<double*>(dyn_lds), part, p.parts, p.items + b * p.items_stride, sh);
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -430,7 +430,7 @@ __global__ __launch_bounds__(kRowThreads, kAlone) void tree_part_kernel(const Tr
 // whose registers it costs.)
 // ---------------------------------------------------------------------------------------------
 enum { kFromRoot = 0, kFromHead = 1, kFromQuick = 2 };      // nothing done yet; the first layers evaluated; the quick walk
-template <typename T, typename Terms, int kFrom>
+template <typename T, typename Terms, int kFrom, int kLoads = kStreamed>
 __global__ __launch_bounds__(kRowThreads) void tree_path_kernel(const TreeParams p) {
   __shared__ RowShared sh;
   extern __shared__ __align__(16) unsigned char dyn_lds[];
@@ -465,7 +465,7 @@ __global__ __launch_bounds__(kRowThreads) void tree_path_kernel(const TreeParams
   bool build = true;                         // the terms' table is still to be made
   while (!done) {
     int slot, st;
-    const int state = tree_node<T, Terms>(p, b, node, reinterpret_cast<double*>(dyn_lds), build, sh, slot, token, st, items);
+    const int state = tree_node<T, Terms, false, kLoads>(p, b, node, reinterpret_cast<double*>(dyn_lds), build, sh, slot, token, st, items);
     build = items != nullptr;
     items = nullptr;
     st_all |= st;
@@ -554,14 +554,26 @@ template <typename T, typename Terms> hipError_t launch_verify_tree_with(TreePar
       // as many workgroups to a row as fill the chip, a run for every wave at least
       const int64_t runs = p.V / (ElemTraits<T>::kPerVec * kRunVecs) + 1;
       p.parts = int(std::max<int64_t>(1, std::min<int64_t>(compute_units() / p.B, (runs + kRowWaves - 1) / kRowWaves)));
-      if (p.parts > 1) {
-        hipLaunchKernelGGL((tree_part_kernel<T, Terms>), dim3(unsigned(p.B * p.parts)), dim3(kRowThreads), Terms::kBytes, s, p);
-        if ((e = hipGetLastError()) != hipSuccess) return e;
+      auto last_rows = [&](auto loads) -> hipError_t {
+        constexpr int kLoads = decltype(loads)::value;
+        if (p.parts > 1) {
+          hipLaunchKernelGGL((tree_part_kernel<T, Terms, kLoads>), dim3(unsigned(p.B * p.parts)), dim3(kRowThreads), Terms::kBytes, s, p);
+          if ((e = hipGetLastError()) != hipSuccess) return e;
+        }
+        return walk(tree_path_kernel<T, Terms, kFromQuick, kLoads>);
+      };
+      if constexpr (ElemTraits<T>::kBytes == 4) {
+        if (p.B * p.n_nodes * p.V * 4 > kStreamTreeBytes) return last_rows(std::integral_constant<int, kCached>{});
       }
-      return walk(tree_path_kernel<T, Terms, kFromQuick>);
+      return last_rows(std::integral_constant<int, kStreamed>{});
     }
   }
-  if (p.n_eval == 0) return walk(tree_path_kernel<T, Terms, kFromRoot>);
+  if (p.n_eval == 0) {
+    if constexpr (ElemTraits<T>::kBytes == 4) {
+      if (p.V < kByAddressV) return walk(tree_path_kernel<T, Terms, kFromRoot, kByAddress>);
+    }
+    return walk(tree_path_kernel<T, Terms, kFromRoot>);
+  }
   if (p.n_eval_layers <= p.depth) return walk(tree_path_kernel<T, Terms, kFromHead>);
   const int threads = std::min(1024, (p.n_eval + 63) / 64 * 64);
   hipLaunchKernelGGL(tree_walk_kernel, dim3(unsigned(p.B)), dim3(threads), 3 * p.n_eval <= kWalkNodes ? 12 * p.n_eval : 0, s, p);

@@ -144,7 +144,7 @@ __global__ __launch_bounds__(kBlock, kAccWavesPerSimd) void verify_accept_kernel
 // Rows shared by p.parts workgroups each: the masses of their items, for a launch that takes them up (row_fetch).
 // kRound: every row of a round; else the one of each sequence that is to be sampled, from kernel A's decisions.
 // ---------------------------------------------------------------------------------------------
-template <typename T, typename Terms, bool kRound>
+template <typename T, typename Terms, bool kRound, int kLoads = kStreamed>
 __global__ __launch_bounds__(kRowThreads, kAlone) void verify_part_kernel(const VerifyParams p) {
   __shared__ RowShared sh;
   extern __shared__ __align__(16) unsigned char dyn_lds[];
@@ -164,14 +164,14 @@ __global__ __launch_bounds__(kRowThreads, kAlone) void verify_part_kernel(const 
   }
   RowWork<T> w;
   row_open<T>(w, target_row<T>(p, b, j), p.V, p.rT, sh);
-  row_part<T, Terms>(w, reinterpret_cast<double*>(dyn_lds), part, p.parts, p.items + at * p.items_stride, sh);
+  row_part<T, Terms, kLoads>(w, reinterpret_cast<double*>(dyn_lds), part, p.parts, p.items + at * p.items_stride, sh);
 }
 
 // ---------------------------------------------------------------------------------------------
 // Kernel B: one workgroup of 1024 threads per sequence sweeps the row to be sampled, or takes up its masses (kItems), and
 // writes the sequence's outputs.
 // ---------------------------------------------------------------------------------------------
-template <typename T, typename Terms, int kWavesPerSimd, bool kItems = false>
+template <typename T, typename Terms, int kWavesPerSimd, bool kItems = false, int kLoads = kStreamed>
 __global__ __launch_bounds__(kRowThreads, kWavesPerSimd) void verify_resample_kernel(const VerifyParams p) {
   __shared__ RowShared sh;
   extern __shared__ __align__(16) unsigned char dyn_lds[];
@@ -208,7 +208,7 @@ __global__ __launch_bounds__(kRowThreads, kWavesPerSimd) void verify_resample_ke
       __syncthreads();
       row_fetch<T, Terms>(w, p.items + b * p.items_stride, table, sh);
     } else {
-      row_sweep<T, Terms, kWavesPerSimd == kAlone>(w, table, 1, sh);
+      row_sweep<T, Terms, kWavesPerSimd == kAlone, kLoads>(w, table, 1, sh);
     }
     if (wave_id() == 0) {
       RowState rst;
@@ -411,13 +411,20 @@ template <typename T, typename Terms> hipError_t launch_verify_with(VerifyParams
   }
   if (phases & 2) {
     p.parts = p.items != nullptr ? row_parts<T, Terms>(p.V, p.B) : 1;
-    if (p.parts > 1) {
-      if ((e = share(KernelTag<&verify_part_kernel<T, Terms, false>>{}, p.B)) != hipSuccess) return e;
-      const auto fetch = KernelTag<&verify_resample_kernel<T, Terms, kAlone, true>>{};
-      return by_rows(fetch, fetch, p.B);
+    auto resample = [&](auto loads) -> hipError_t {
+      constexpr int kLoads = decltype(loads)::value;
+      if (p.parts > 1) {
+        if ((e = share(KernelTag<&verify_part_kernel<T, Terms, false, kLoads>>{}, p.B)) != hipSuccess) return e;
+        const auto fetch = KernelTag<&verify_resample_kernel<T, Terms, kAlone, true>>{};
+        return by_rows(fetch, fetch, p.B);
+      }
+      return by_rows(KernelTag<&verify_resample_kernel<T, Terms, kAlone, false, kLoads>>{},
+                     KernelTag<&verify_resample_kernel<T, Terms, kShared, false, kLoads>>{}, p.B);
+    };
+    if constexpr (ElemTraits<T>::kBytes == 4) {
+      if (p.B * (p.gamma + 1) * p.V * 4 > kStreamBytes && p.B * p.V * 4 <= kCachedBytes) return resample(std::integral_constant<int, kCached>{});
     }
-    e = by_rows(KernelTag<&verify_resample_kernel<T, Terms, kAlone>>{}, KernelTag<&verify_resample_kernel<T, Terms, kShared>>{},
-                p.B);
+    return resample(std::integral_constant<int, kStreamed>{});
   }
   return e;
 }
