@@ -38,8 +38,8 @@ constexpr int kGroup = 2;        // tiles (one 16-byte vector per thread each) i
 //   "Tall": 512 threads and four stages, for batches that leave the chip to one or two rows per compute unit, bound by
 // a row's own latency: twice the requests in flight, rows shorter than the sample's distances through the same pipeline
 // (they went pair by pair, a memory latency each), the threshold out of a histogram.  us by 256 / 512 threads: 1 row
-// binary16 V = 32000 12.7 / 10.0, 64 bfloat16 V = 128256 25.1 / 17.5, 200 28.3 / 18.3, 384 32.4 / 26.0, 700 38.8 / 38.0;
-// 100 fp32 V = 151936 41.9 / 24.4, 400 50.9 / 43.6.  (1024 threads, before the pass and the sort were shortened: slower
+// binary16 V = 32000 12.8 / 10.4, 64 bfloat16 V = 128256 24.7 / 17.6, 200 26.2 / 19.0, 384 30.5 / 26.2, 700 38.9 / 38.6;
+// 100 fp32 V = 151936 38.1 / 24.4, 400 47.3 / 43.5.  (1024 threads, before the pass and the sort were shortened: slower
 // again, 14.9, 23.4 and 25.6 us for the first three, which took 13.0, 21.7 and 23.2 then.)
 constexpr int kTallThreads = 512;
 constexpr int kStagesWide = 2, kWavesWide = 8;
@@ -570,8 +570,9 @@ __global__ __launch_bounds__(NT, kWavesPerSimd) void truncate_kernel(const Trunc
     // sets of 32, 51.0 / 48.5; 2728 254.9 / 253.0; the deep shape, 1000 fp32 rows of 151936, sets of 1024, 114.8 / 116.5).
     constexpr bool kBuffer = kWavesPerSimd < kWavesWide;
     const __amdgpu_buffer_rsrc_t body = row_buffer(rs.body, nvec);
+    const uint32_t lane_bytes = uint32_t(tid) * 16u;
     auto request = [&](uint32_t at) -> uint4 {          // of a tile that begins `at` bytes into the row's body
-      if constexpr (kBuffer) return buffer_load_vec_stream(body, uint32_t(tid) * 16u, at);
+      if constexpr (kBuffer) return buffer_load_vec_stream(body, lane_bytes, at);
       const uint32_t vi = at / 16u + tid;
       return load_vec_stream(&rs.body[vi < nvec - 1 ? vi : nvec - 1]);
     };

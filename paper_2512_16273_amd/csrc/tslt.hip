@@ -132,12 +132,12 @@ bool sparse_hits(tslt_dtype dt, int64_t V, int nt, const tslt::TruncateParams& p
   return 128.0 * h + 5.0 * std::sqrt(128.0 * h) <= tslt::kRingSmall - tslt::kRingExpand;
 }
 // Whether 512 threads take a row: where every row has a compute unit to itself (but for the shortest, of few tiles more than
-// the sample or less than that, where there is little to gain: 70 fp32 rows of 9088 9.4 us by 256 threads, 9.0 by 512; binary16
-// 9.1 / 8.7; 16000 10.6 / 9.8 and 9.5 / 8.8),
+// the sample or less than that, where there is little to gain: 70 fp32 rows of 9088 9.8 us by 256 threads, 9.4 by 512; binary16
+// 9.6 / 9.5; 16000 10.7 / 10.0 and 10.1 / 9.7),
 // and up to three rows for two compute units if a row is neither short nor very long (us by 256 / 512 threads, 306
-// rows: bfloat16 16000 11.3 / 11.4, 41000 15.6 / 16.4, 82000 22.5 / 20.5, 128256 29.9 / 24.4, 256000 48.9 / 40.2; fp32 16000 12.4 /
-// 12.9, 60000 25.0 / 20.0, 128256 44.3 / 36.2, 213696 54.8 / 55.8, 256000 63.5 / 67.6.  Sets of 64; the lines are on the safe side:
-// 60000 bfloat16 values 18.5 / 18.3, 25240 fp32 ones 16.2 / 15.2, 180000 58.0 / 49.1.)
+// rows: bfloat16 16000 11.1 / 11.5, 41000 15.4 / 16.3, 82000 21.8 / 20.7, 128256 28.9 / 24.4, 256000 46.0 / 40.3; fp32 16000 12.2 /
+// 12.9, 60000 23.9 / 20.1, 128256 41.0 / 36.4, 213696 54.9 / 55.8, 256000 63.5 / 67.4.  Sets of 64; the lines are on the safe side:
+// 25240 fp32 values 15.7 / 15.0, 180000 53.3 / 49.1.)
 bool tall_rows(tslt_dtype dt, int64_t V, int64_t rows) {
   const int64_t cus = tslt::compute_units(), kb = V * elem_bytes(dt) >> 10;
   if (rows <= cus) return V >= 10240;
