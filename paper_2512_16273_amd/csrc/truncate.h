@@ -13,7 +13,7 @@
 // by an exact radix selection that makes several passes.  Either way the kept entries are then
 // evaluated in fp64, which is also where Top-rho and the renormalisation are decided.
 //
-// Bound by memory in large batches (2048 bfloat16 rows of 128256: 92 us, of which 81 are the reading), by the instructions a
+// Bound by memory in large batches (2048 bfloat16 rows of 128256: 91 us, of which 81 are the reading), by the instructions a
 // row's waves issue one after the other in small ones.  The pass is written for the second: an fma takes its operands from
 // vector registers without a sign to change (2.7 cycles a wave, 4.4 otherwise), binary16 is tested against the threshold as
 // packed halves and never widened, addresses are a scalar offset into a buffer (but for large batches), the complete stages have a loop without a

@@ -62,11 +62,11 @@ def compare_chain(tslt, w, target, tr, c, u_accept):
 
 
 @pytest.mark.parametrize("dtype,V,B,gamma", [
-    ("f32", 50000, 3, 4), ("f32", 64001, 14, 8), ("f32", 76001, 14, 8),      # a dozen workgroups a row, none, two
+    ("f32", 50000, 3, 4), ("f32", 64001, 14, 8), ("f32", 76001, 14, 8),      # four workgroups a row, none, two
     ("f32", 151936, 40, 8),                                                  # the sampled rows alone, by six
     ("f16", 60001, 2, 3), ("f16", 131072, 30, 12), ("bf16", 100003, 8, 8), ("bf16", 125000, 16, 7), ("bf16", 150001, 16, 7),
     ("bf16", 250001, 1, 1),
-    ("f16", 147457, 40, 7), ("f16", 147459, 128, 2),                         # sampled through binary16's bit table, by six and two
+    ("f16", 147457, 40, 7), ("f16", 147459, 128, 2),                         # sampled through binary16's bit table, by five and two
 ])
 @pytest.mark.parametrize("broken", [False, True])
 def test_chain_of_shared_rows(tslt, dtype, V, B, gamma, broken):
