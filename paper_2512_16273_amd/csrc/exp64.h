@@ -53,6 +53,40 @@ TSLT_HD double exp64(double x) {
   return p * scale;
 }
 
+// exp(x) and exp(-x), |x| <= 700: the same series, its even and odd parts apart, so that the second value costs four operations
+// more than the first (a table of both signs takes half the time).  Every rounding but the last is of a quantity below 0.42.
+TSLT_HD void exp64_pair(double x, double& plus, double& minus) {
+  const double kMagic = 6755399441055744.0;
+  const double t = __builtin_fma(x, 1.44269504088896338700e+00, kMagic);
+  const double n = t - kMagic;
+  uint64_t tb;
+  memcpy(&tb, &t, 8);
+  const int32_t ni = int32_t(uint32_t(tb));
+  double r = __builtin_fma(n, -6.93147180369123816490e-01, x);
+  r = __builtin_fma(n, -1.90821492927058770002e-10, r);
+  const double r2 = r * r;
+  double odd = 1.6059043836821613e-10;                            // 1/13!
+  odd = __builtin_fma(odd, r2, 2.505210838544172e-08);
+  odd = __builtin_fma(odd, r2, 2.7557319223985893e-06);
+  odd = __builtin_fma(odd, r2, 1.984126984126984e-04);
+  odd = __builtin_fma(odd, r2, 8.333333333333333e-03);
+  odd = __builtin_fma(odd, r2, 1.6666666666666666e-01);
+  odd = __builtin_fma(odd, r2, 1.0);
+  double even = 2.08767569878681e-09;                             // 1/12!
+  even = __builtin_fma(even, r2, 2.755731922398589e-07);
+  even = __builtin_fma(even, r2, 2.48015873015873e-05);
+  even = __builtin_fma(even, r2, 1.388888888888889e-03);
+  even = __builtin_fma(even, r2, 4.1666666666666664e-02);
+  even = __builtin_fma(even, r2, 0.5);
+  even = even * r2;
+  const uint64_t up = uint64_t(uint32_t(1023 + ni)) << 52, down = uint64_t(uint32_t(1023 - ni)) << 52;
+  double scale_up, scale_down;
+  memcpy(&scale_up, &up, 8);
+  memcpy(&scale_down, &down, 8);
+  plus = (1.0 + __builtin_fma(r, odd, even)) * scale_up;
+  minus = (1.0 + __builtin_fma(-r, odd, even)) * scale_down;
+}
+
 // exp(x) for a finite x with |x| <= 700 (in the kernels an fp32 value) through a table of 2^(i/2048):
 // x = n * ln2/2048 + r, |r| <= ln2/4096, exp(x) = 2^(n div 2048) * table[n mod 2048] * (1 + r + r^2/2 + r^3/6) (the
 // series is cut below 2^-54).  Half the fp64 operations of exp64, for one 8-byte read from LDS; within about 1.3

@@ -13,6 +13,7 @@
 #include <type_traits>
 #include "common.h"
 #include "exp64.h"
+#include "handover.h"
 #include "rowops.h"
 
 namespace tslt {
@@ -23,6 +24,7 @@ constexpr int kRowWaves = kRowThreads / 64;
 // spilled value in the chain of steps after the sweep costs a memory latency; 8 (two workgroups on a compute unit)
 // for more rows than that, where one sweeps while the other is in that chain.
 constexpr int kAlone = 4, kShared = 8;
+constexpr int kMaxStages = 16;                      // candidates of a node (TSLT_MAX_BRANCH)
 constexpr int kMaxRuns = (kBlock - 2) * kSubChunks;
 constexpr int kMaxItems = kMaxRuns + 2;             // a row's runs, and the elements before and after its aligned body
 static_assert(kMaxItems <= kRowThreads, "one item per thread");
@@ -80,21 +82,17 @@ template <typename T> inline bool exp_table_usable(float rT) {
   return false;
 }
 
-template <typename T> __device__ __forceinline__ double exp_table_entry(int i, float rT) {
-  using TB = ExpTab<T>;
-  if (i < 1 || i > TB::kEntries) return __longlong_as_double(0x7FF8000000000000ll);
-  const int j = i - 1;
-  const uint32_t bits = (uint32_t(j & 1) << 15) | uint32_t(TB::kLo + (j >> 1));
-  return exp64(double(__fmul_rn(TB::widen(bits), rT)));
-}
 // Fills the table with all `threads` threads of the workgroup; the caller synchronises.  `half` 0 / 1 fills the
 // first / second half only (a kernel that has requests to make between the two does so: the entries are
-// pure arithmetic, a good thing to have while data travels), -1 everything.
+// pure arithmetic, a good thing to have while data travels), -1 everything.  A magnitude's two entries lie side by side and are made
+// together (exp64_pair; one by one bfloat16's table took 3.0 us of a round's kernel, 1.9 so).
 template <typename T> __device__ __forceinline__ void build_exp_table(double* table, float rT, int threads, int half = -1) {
-  constexpr int n = ExpTab<T>::kEntries + 2;
-  const int mid = ((n / 2 + threads - 1) / threads) * threads;
-  const int lo = half == 1 ? mid : 0, hi = half == 0 ? mid : n;
-  for (int i = lo + threadIdx.x; i < hi; i += threads) table[i] = exp_table_entry<T>(i, rT);
+  using TB = ExpTab<T>;
+  const int mid = ((TB::kSpan / 2 + threads - 1) / threads) * threads;
+  const int lo = half == 1 ? mid : 0, hi = half == 0 ? mid : TB::kSpan;
+  for (int j = lo + threadIdx.x; j < hi; j += threads)
+    exp64_pair(double(__fmul_rn(TB::widen(uint32_t(TB::kLo + j)), rT)), table[1 + 2 * j], table[2 + 2 * j]);
+  if (half != 1 && threadIdx.x == 0) table[0] = table[TB::kEntries + 1] = __longlong_as_double(0x7FF8000000000000ll);
 }
 
 // Sum of exp(s) over the 8 elements of a 16-bit vector through the table.  The index arithmetic runs on
@@ -237,22 +235,25 @@ template <> __device__ __forceinline__ float dword_element<F16>(uint32_t w, int 
 // ---------------------------------------------------------------------------------------------
 // The row.  Its mass is held in "items", in row order: the elements before the aligned body, every run of the
 // body, the elements after it.  All sixteen waves sweep; what comes between the sweep and the search for the
-// element is a chain of short dependent steps over a few hundred set entries, which the first wave does alone out
-// of LDS (no barrier, no sum over waves, and the vector units to itself: with the same steps spread over sixteen
-// waves a redundant instruction costs sixteen issue slots; 7 us of the 15 that a row of 32000 took).
+// element is a chain of short dependent steps over a few hundred set entries.  The waves that hold entries, one a lane, make the
+// tests and updates out of registers and leave their sums for each other, a barrier a stage; whatever all of them need they make
+// each for itself.  The others wait, and the search is the first wave's alone (with redundant steps spread over sixteen waves an
+// instruction costs sixteen issue slots).  us of a round's kernel, one binary16 row of 32000 with 320 entries: the tests by the first wave,
+// four entries a lane at a time out of LDS, 1.28, so 0.7.
 // ---------------------------------------------------------------------------------------------
 struct RowShared {
   double items[kMaxItems];
-  // the received set: token index (-1 outside the vocabulary), weight, mass of the row at it, and, once there has been
-  // an update, the distribution at it (row_locate leaves the correction to the row's mass in its place)
-  double set_w[kRowThreads], set_e[kRowThreads], set_a[kRowThreads];
+  // the received set: token index (-1 outside the vocabulary), mass of the row at it, correction to that mass
+  double set_e[kRowThreads], set_a[kRowThreads];
   int set_y[kRowThreads];
-  double w_part[kRowWaves], e_part[kRowWaves];      // their sums over the entries that a wave stored
+  double w_part[kRowWaves], e_part[kRowWaves];      // sums of weights and masses over the entries that a wave holds
+  // what the waves leave of a test (two buffers: a wave may be at the next one), by stage whether one of them has found the candidate
+  double t_part[2][kRowWaves], t_shared[2][kRowWaves], t_ratio[2][kRowWaves], t_q[2][kRowWaves];
+  int found[kMaxStages];
   double wave_sum[kRowWaves];
   float wave_max[kRowWaves];
   double target, before, none;
-  double removed;                       // q_hat of the candidates that have left the proposal
-  int flags, next_run, item, n_corr, pick, last, cmd, st, fetched;
+  int flags, next_run, item, n_corr, pick, last, cmd, st, fetched, stop_at;
 };
 
 template <typename T> struct RowWork {
@@ -262,8 +263,9 @@ template <typename T> struct RowWork {
   float rT;
   int n_runs, n_items;
   int count;            // entries of the received set
-  int y;                // this thread's entry: token index, payload, target logit
+  int y;                // this thread's entry: token index (-1: none), payload, target logit
   float ql, ql0, tv;
+  double wt, e, a;      // ... its weight, the row's mass at it, and after an update the distribution at it
   float smax;           // the reference of the masses
 };
 
@@ -274,12 +276,13 @@ template <typename T> struct RowWork {
 // token of the set leaves is the share 2^-24 of its q_hat.)
 constexpr double kNoResidual = 0x1p-47;
 
-// What the first wave knows of the row (the same in all lanes).
+// What the waves that hold entries know of the row (the same in all of them).
 struct RowState {
   double zp, sum_e;     // total mass, the set's part of it
   double inv_zp;        // 1 / total mass: p is set_e * inv_zp before the first update
   double inv_w;         // 1 / sum of the set's weights: q_hat is set_w * inv_w, a stage's proposal q_hat * qscale
   double p_out, c, sum_a, qscale;
+  double removed;       // q_hat of the candidates that have left the proposal
   int st, stages;
   bool ok;
 };
@@ -292,7 +295,9 @@ __device__ __forceinline__ void row_open(RowWork<T>& w, const void* row, int64_t
   w.rT = rT;
   w.n_runs = int((w.rs.nvec + kRunVecs - 1) / kRunVecs);
   w.n_items = w.n_runs + 2;
-  if (threadIdx.x == 0) { sh.flags = 0; sh.next_run = kRowWaves; }      // published by the sweep's first barrier
+  // (published by the sweep's first barrier)
+  if (threadIdx.x == 0) { sh.flags = 0; sh.next_run = kRowWaves; sh.stop_at = 0; }
+  if (threadIdx.x < kMaxStages) sh.found[threadIdx.x] = 0;
 }
 
 // This thread's entry of a received set; every request is unconditional (a slot beyond the set reads the set's
@@ -312,23 +317,26 @@ template <typename T> __device__ __forceinline__ void row_gather(RowWork<T>& w) 
   w.y = valid ? w.y : -1;
   w.tv = load_elem<T>(w.row, valid ? w.y : 0);
 }
-// The entry as the first wave needs it.  A value that is not finite or an index outside the vocabulary makes the
+// The entry's weight and mass, and their sums.  A value that is not finite or an index outside the vocabulary makes the
 // set unusable: the weight is NaN, which shows in the sum.
-template <typename T> __device__ __forceinline__ void row_store_set(const RowWork<T>& w, float smax, RowShared& sh) {
+template <typename T> __device__ __forceinline__ void row_store_set(RowWork<T>& w, float smax, RowShared& sh) {
   const int tid = threadIdx.x;
+  w.wt = w.e = 0.0;
   if (__builtin_amdgcn_readfirstlane(wave_id() * 64) < w.count) {       // whole waves
-    double wt = 0.0, e = 0.0;
     if (tid < w.count) {
-      wt = fabsf(w.ql) < INFINITY && w.y >= 0 ? exp64(double(w.ql) - double(w.ql0)) : __longlong_as_double(0x7FF8000000000000ll);
-      e = w.y >= 0 && w.tv > -INFINITY ? exp64(double(__fmul_rn(w.tv, w.rT)) - double(smax)) : 0.0;
+      w.wt = fabsf(w.ql) < INFINITY && w.y >= 0 ? exp64(double(w.ql) - double(w.ql0)) : __longlong_as_double(0x7FF8000000000000ll);
+      w.e = w.y >= 0 && w.tv > -INFINITY ? exp64(double(__fmul_rn(w.tv, w.rT)) - double(smax)) : 0.0;
       sh.set_y[tid] = w.y;
-      sh.set_w[tid] = wt;
-      sh.set_e[tid] = e;
+      sh.set_e[tid] = w.e;
     }
-    double sums[2] = {wt, e};
+    double sums[2] = {w.wt, w.e};
     wave_sums_f64(sums);
     if (lane_id() == 0) { sh.w_part[wave_id()] = sums[0]; sh.e_part[wave_id()] = sums[1]; }
   }
+}
+// Waves that hold entries (one, if there are none).
+template <typename T> __device__ __forceinline__ int row_set_waves(const RowWork<T>& w) {
+  return __builtin_amdgcn_readfirstlane(w.count > 64 ? (w.count + 63) / 64 : 1);
 }
 
 // The masses of the row's items, referenced to 0: of its runs run0 .. run1 - 1, and with `ends` of the elements before and
@@ -456,7 +464,7 @@ __device__ __forceinline__ void row_pass(RowWork<T>& w, double* table, int half,
     __syncthreads();
     row_gather(w);
   }
-  row_store_set(w, 0.0f, sh);
+  if constexpr (!kPart) row_store_set(w, 0.0f, sh);
   if (ends && wave == kRowWaves - 1) row_edges(w, edge_v, 0.0f, sh);
   flags = wave_or_i32(flags);
   if (lane == 0 && flags) atomicOr(&sh.flags, flags);
@@ -528,41 +536,53 @@ __device__ __forceinline__ void row_sweep(RowWork<T>& w, double* table, int half
 }
 
 // One of `parts` workgroups that share a row: the masses of its runs, and the first one's of the elements outside the aligned
-// body, stored for a launch that takes them up; NaN where it met something that asks for a sweep by the row's maximum.
+// body, left in memory; NaN where it met something that asks for a sweep by the row's maximum.  (The set's target logits are
+// gathered on the way, as in row_sweep, by each of them: whoever goes on has them.)
 template <typename T, typename Terms, int kLoads>
 __device__ __forceinline__ void row_part(RowWork<T>& w, double* table, int part, int parts, double* out, RowShared& sh) {
-  w.count = 0;                                       // no set
-  w.y = -1;
-  w.ql = w.ql0 = 0.0f;
   const int per = (w.n_runs + parts - 1) / parts;
   const int run0 = part * per, run1 = run0 + per < w.n_runs ? run0 + per : w.n_runs;
   row_pass<T, Terms, false, kLoads, true>(w, table, -1, run0, run1, part == 0, sh);
   const bool broken = (sh.flags & 3) != 0;
   const double bad = __longlong_as_double(0x7FF8000000000000ll);
-  for (int i = run0 + threadIdx.x; i < run1; i += kRowThreads) out[1 + i] = broken ? bad : sh.items[1 + i];
-  if (part == 0 && threadIdx.x < 2) {
-    const int i = threadIdx.x == 0 ? 0 : w.n_items - 1;
-    out[i] = broken ? bad : sh.items[i];
-  }
+  auto leave = [&](int i) {
+    store_through(reinterpret_cast<uint64_t*>(out) + i, uint64_t(__double_as_longlong(broken ? bad : sh.items[i])));
+  };
+  for (int i = run0 + threadIdx.x; i < run1; i += kRowThreads) leave(1 + i);
+  if (part == 0 && threadIdx.x < 2) leave(threadIdx.x == 0 ? 0 : w.n_items - 1);
+  w.smax = 0.0f;
+  row_store_set(w, 0.0f, sh);                        // (while they travel; each for itself)
 }
 
-// The row as row_sweep leaves it, from masses that other workgroups have made of it (row_part).  sh.fetched is 0, as published by a barrier.
+// The row as row_sweep leaves it, from the masses that its workgroups have left.
 template <typename T, typename Terms>
 __device__ __forceinline__ void row_fetch(RowWork<T>& w, const double* items, double* table, RowShared& sh) {
   const int tid = threadIdx.x, lane = lane_id();
-  const double mass = items[tid < w.n_items ? tid : 0];
-  row_gather(w);
+  const double mass = __longlong_as_double((long long)load_through(reinterpret_cast<const uint64_t*>(items) + (tid < w.n_items ? tid : 0)));
   if (tid < w.n_items) sh.items[tid] = mass;
-  w.smax = 0.0f;
-  row_store_set(w, 0.0f, sh);
   const int seen = (ballot(mass != mass) != 0 ? 1 : 0) | (ballot(mass > kSomeMass) != 0 ? 2 : 0);
+  if (tid == 0) sh.flags = 0;                        // (its own part's, looked at before the last barrier)
   if (lane == 0 && seen) atomicOr(&sh.fetched, seen);
   __syncthreads();
-  if (__builtin_amdgcn_readfirstlane(sh.fetched) != 2) row_sweep<T, Terms>(w, table, -1, sh);
+  if (__builtin_amdgcn_readfirstlane(sh.fetched) != 2) {
+    if (tid == 0) sh.next_run = kRowWaves;           // (published by the sweep's first barrier)
+    row_sweep<T, Terms>(w, table, -1, sh);
+  }
+}
+// Both: whether this workgroup goes on with the row.
+template <typename T, typename Terms, int kLoads = kStreamed>
+__device__ __forceinline__ bool row_shared(RowWork<T>& w, double* table, int part, int parts, double* items, uint64_t* words, Tag tag,
+                                           RowShared& sh) {
+  if (threadIdx.x == 0) sh.fetched = 0;
+  row_part<T, Terms, kLoads>(w, table, part, parts, items, sh);
+  if (!all_arrived(words, part, parts, tag, sh.cmd)) return false;
+  row_fetch<T, Terms>(w, items, table, sh);
+  return true;
 }
 
 constexpr int64_t kShareRows = 128;                  // at most, by two workgroups or more
 constexpr int64_t kShareLeastV = 50000;              // of any type
+constexpr int64_t kShareWords = 512;                 // words that the workgroups of all shared rows leave, at most
 // Workgroups that share each of `rows` rows (1: none do): as many as fill the chip, a run for every wave at least.  A launch
 // more (two microseconds, the terms' table made by every part) against the sweep of a row by one compute unit, so rows from the
 // length on where that is some 6 us (BitTerms' terms are the cheapest, and binary16 has twice fp32's in a run).  us a round by
@@ -584,23 +604,11 @@ template <typename T, typename Terms> inline int64_t share_min_V(bool by_two) {
 template <typename T, typename Terms> inline int row_parts(int64_t V, int64_t rows) {
   if (rows > kShareRows || V < share_min_V<T, Terms>(3 * rows > compute_units())) return 1;
   const int64_t runs = V / (ElemTraits<T>::kPerVec * kRunVecs) + 1;
-  return int(std::max<int64_t>(1, std::min<int64_t>(compute_units() / rows, (runs + kRowWaves - 1) / kRowWaves)));
+  return int(std::max<int64_t>(1, std::min<int64_t>(std::min<int64_t>(compute_units(), kShareWords) / rows, (runs + kRowWaves - 1) / kRowWaves)));
 }
 
-// Passes over the set's entries by one wave, four per lane at a time: load(k, i) for all four first, so that their
-// LDS reads are in flight together, then body(k, i, valid).  (An entry beyond the set is read, within the arrays,
-// and not counted.)
-template <typename L, typename F> __device__ __forceinline__ void over_set(int count, L load, F body) {
-  for (int i0 = lane_id(); i0 < count; i0 += 256) {
-#pragma unroll
-    for (int k = 0; k < 4; ++k) load(k, i0 + 64 * k);
-#pragma unroll
-    for (int k = 0; k < 4; ++k) body(k, i0 + 64 * k, i0 + 64 * k < count);
-  }
-}
-
-// First wave: normaliser, and p and q_hat at the set.  A row that holds NaN or +inf, or nothing above -inf, is
-// unusable.
+// The waves that hold entries, each for itself: normaliser, and what p and q_hat at the set are made with.  A row that holds NaN
+// or +inf, or nothing above -inf, is unusable.
 template <typename T> __device__ __forceinline__ void row_eval(const RowWork<T>& w, RowState& r, RowShared& sh) {
   const int lane = lane_id();
   const int n_stored = (w.count + 63) / 64;        // waves that stored entries
@@ -627,133 +635,90 @@ template <typename T> __device__ __forceinline__ void row_eval(const RowWork<T>&
   r.p_out = 1.0 - r.sum_a > 0.0 ? 1.0 - r.sum_a : 0.0;
   r.c = 1.0;
   r.qscale = 1.0;
-  sh.removed = 0.0;
+  r.removed = 0.0;
   r.stages = 0;
 }
 
-// First wave: the test of candidate x against the distribution as it stands and the stage's proposal: its ratio (-1
-// if x is not in the set), the mass the two share (sum of their minima), and what an update needs.
+// The test of candidate x against the distribution as it stands and the stage's proposal: its ratio (-1 if x is not in the
+// set), the mass the two share (sum of their minima), and what an update needs.  The waves that hold entries leave their sums
+// (row_test) and take up the total of all behind a barrier (row_tested).
 struct RowTest {
   double ratio, shared, part, q_x;
   bool found;
 };
-// (q_x, a_x: the lane's, where it holds x)
-__device__ __forceinline__ RowTest row_test_result(double part, double shared, double q_x, double a_x, double qscale) {
-  RowTest t;
-  const double ratio = a_x / (q_x * qscale);
-  double sums[2] = {part, shared};
+template <typename T> __device__ __forceinline__ double row_at(const RowWork<T>& w, const RowState& r) { return r.stages ? w.a : w.e * r.inv_zp; }
+// Returns the thread's max(0, p - q).
+template <typename T>
+__device__ __forceinline__ double row_test(const RowWork<T>& w, const RowState& r, int x, int stage, RowShared& sh) {
+  const int lane = lane_id(), wave = wave_id(), k = stage & 1;
+  const double a = row_at(w, r), qk = w.wt * r.inv_w, q = qk * r.qscale;
+  const double d = a - q > 0.0 ? a - q : 0.0;
+  const bool valid = w.y >= 0;
+  double sums[2] = {valid ? d : 0.0, valid ? a - d : 0.0};      // the second: min(a, q)
   wave_sums_f64(sums);
-  t.part = sums[0];
-  t.shared = sums[1];
-  const uint64_t at = ballot(q_x > 0.0);
-  t.found = at != 0;
-  const int src = t.found ? 63 - __clzll((long long)at) : 0;
-  t.q_x = lane_f64(q_x, src);
-  t.ratio = t.found ? lane_f64(ratio, src) : -1.0;
+  if (lane == 0) { sh.t_part[k][wave] = sums[0]; sh.t_shared[k][wave] = sums[1]; }
+  const bool mine = valid && w.y == x && qk > 0.0;
+  const uint64_t at = ballot(mine);
+  if (at != 0 && lane == 63 - __clzll((long long)at)) {
+    sh.t_ratio[k][wave] = a / q;
+    sh.t_q[k][wave] = qk;
+    atomicOr(&sh.found[stage], 1 << wave);
+  }
+  return d;
+}
+__device__ __forceinline__ RowTest row_tested(int waves, int stage, const RowShared& sh) {
+  const int k = stage & 1, found = sh.found[stage];
+  RowTest t;
+  t.part = sh.t_part[k][0];
+  t.shared = sh.t_shared[k][0];
+  for (int i = 1; i < waves; ++i) {
+    t.part += sh.t_part[k][i];
+    t.shared += sh.t_shared[k][i];
+  }
+  t.found = found != 0;
+  const int by = t.found ? 31 - __clz(found) : 0;
+  t.ratio = t.found ? sh.t_ratio[k][by] : -1.0;
+  t.q_x = t.found ? sh.t_q[k][by] : 0.0;
   return t;
 }
-template <typename T>
-__device__ __forceinline__ RowTest row_test(const RowWork<T>& w, const RowState& r, int x, const RowShared& sh) {
-  double part = 0.0, shared = 0.0, q_x = 0.0, a_x = 0.0;
-  const double* src_a = r.stages ? sh.set_a : sh.set_e;
-  const double a_scale = r.stages ? 1.0 : r.inv_zp;
-  int y[4];
-  double a[4], q0[4];
-  over_set(w.count, [&](int k, int i) { y[k] = sh.set_y[i]; a[k] = src_a[i]; q0[k] = sh.set_w[i]; },
-           [&](int k, int, bool valid) {
-    const double ak = a[k] * a_scale, qk = q0[k] * r.inv_w;
-    const double d = ak - qk * r.qscale > 0.0 ? ak - qk * r.qscale : 0.0;
-    valid = valid && y[k] >= 0;
-    part += valid ? d : 0.0;
-    shared += valid ? ak - d : 0.0;                // min(a, q)
-    const bool mine = valid && y[k] == x && qk > 0.0;
-    q_x = mine ? qk : q_x;
-    a_x = mine ? ak : a_x;
-  });
-  return row_test_result(part, shared, q_x, a_x, r.qscale);
-}
-// First wave, before any update: row_test, and in the same pass what row_locate would do to the masses if the
-// candidate were rejected: a becomes max(0, p - q) / Z and the mass off the set e / (zp Z), so that Z drops out of
-// an entry's mass in units of the row's terms.  (An accepted candidate's row is not looked at again.)
 template <typename T>
 __device__ __forceinline__ int item_of(const RowWork<T>& w, int y) {
   if (y < w.rs.head) return 0;
   const int v = (y - w.rs.head) / ElemTraits<T>::kPerVec;
   return v >= w.rs.nvec ? w.n_items - 1 : 1 + v / kRunVecs;
 }
-template <typename T>
-__device__ __forceinline__ RowTest row_test_first(const RowWork<T>& w, const RowState& r, int x, RowShared& sh) {
-  double part = 0.0, shared = 0.0, q_x = 0.0, a_x = 0.0;
-  int y[4];
-  double e[4], q[4];
-  over_set(w.count, [&](int k, int i) { y[k] = sh.set_y[i]; e[k] = sh.set_e[i]; q[k] = sh.set_w[i]; },
-           [&](int k, int i, bool valid) {
-    const double a = e[k] * r.inv_zp, qk = q[k] * r.inv_w;
-    const double d = a - qk > 0.0 ? a - qk : 0.0;
-    valid = valid && y[k] >= 0;
-    part += valid ? d : 0.0;
-    shared += valid ? a - d : 0.0;                 // min(a, q)
-    const bool mine = valid && y[k] == x && qk > 0.0;
-    q_x = mine ? qk : q_x;
-    a_x = mine ? a : a_x;
-    if (valid) {
-      const double corr = d * r.zp - e[k];
-      sh.set_a[i] = corr;
-      atomicAdd(&sh.items[item_of(w, y[k])], corr);
-    }
-  });
-  return row_test_result(part, shared, q_x, a_x, 1.0);
+// The mass at the thread's entry becomes `mass`, in units of the row's terms: the item it falls into is corrected by the difference.
+template <typename T> __device__ __forceinline__ void row_set_mass(const RowWork<T>& w, double mass, RowShared& sh) {
+  if (w.y < 0) return;
+  const double corr = mass - w.e;
+  sh.set_a[threadIdx.x] = corr;
+  atomicAdd(&sh.items[item_of(w, w.y)], corr);
 }
-// First wave: whether max(0, p - proposal), with the sum over the set that row_test returned, holds any mass.
+// Whether max(0, p - proposal), with the sum over the set that a test returned, holds any mass.
 __device__ __forceinline__ bool row_has_residual(const RowState& r, double part) {
   return same_in_wave(part + r.c * r.p_out > kNoResidual * r.c);
 }
-// First wave: p <- norm(max(0, p - proposal)), or p if that holds none; `gone` leaves the proposal (a candidate drawn
-// without replacement; -1: none).
+// p <- norm(max(0, p - proposal)), or p if that holds none; `gone` leaves the proposal (a candidate drawn without
+// replacement; -1: none).
 template <typename T>
-__device__ __forceinline__ void row_update(const RowWork<T>& w, RowState& r, double part, int gone, RowShared& sh) {
+__device__ __forceinline__ void row_update(RowWork<T>& w, RowState& r, double part, int gone) {
   const bool holds = row_has_residual(r, part);
   const double inv_Z = holds ? 1.0 / (part + r.c * r.p_out) : 1.0;
-  const double q_scale = holds ? r.inv_w * r.qscale : 0.0;
-  const double* src_a = r.stages ? sh.set_a : sh.set_e;
-  const double a_scale = r.stages ? 1.0 : r.inv_zp;
-  int y[4];
-  double a[4], wt[4];
-  over_set(w.count, [&](int k, int i) { y[k] = sh.set_y[i]; a[k] = src_a[i]; wt[k] = sh.set_w[i]; },
-           [&](int k, int i, bool valid) {
-    const double d = a[k] * a_scale - wt[k] * q_scale;
-    if (valid) {
-      sh.set_a[i] = y[k] >= 0 && d > 0.0 ? d * inv_Z : 0.0;
-      if (y[k] == gone && y[k] >= 0) sh.set_w[i] = 0.0;
-    }
-  });
+  const double d = row_at(w, r) - w.wt * (holds ? r.inv_w * r.qscale : 0.0);
+  w.a = w.y >= 0 && d > 0.0 ? d * inv_Z : 0.0;
+  if (w.y == gone && w.y >= 0) w.wt = 0.0;
   r.c *= inv_Z;
   r.sum_a = holds ? part * inv_Z : r.sum_a;
   ++r.stages;
 }
-
-// First wave: the masses after the updates made so far, and after one more with the sum `part` if it is pending: e_y off
-// the set and a * z_p / c on it, in units of the row's terms.  The set's corrections are added to the items they fall into;
-// returns their total.
+// The masses after the updates made so far, and after one more with the sum `part` if it is pending: e_y off the set and
+// a * z_p / c on it, in units of the row's terms.  Returns the total of the set's corrections.
 template <typename T>
 __device__ __forceinline__ double row_correct(const RowWork<T>& w, const RowState& r, bool pending, double part, RowShared& sh) {
   // with one more update a becomes max(0, a - q) / Z and c becomes c / Z: Z drops out of a * z_p / c
   const double zp_over_c = r.zp / r.c;
-  const double* src_a = r.stages ? sh.set_a : sh.set_e;
-  const double a_scale = r.stages ? 1.0 : r.inv_zp;
-  const double q_scale = pending ? r.inv_w * r.qscale : 0.0;
-  int y[4];
-  double a[4], e[4], wt[4];
-  over_set(w.count, [&](int k, int i) { y[k] = sh.set_y[i]; a[k] = src_a[i]; e[k] = sh.set_e[i]; wt[k] = sh.set_w[i]; },
-           [&](int k, int i, bool valid) {
-    double ak = a[k] * a_scale - wt[k] * q_scale;
-    ak = ak > 0.0 ? ak : 0.0;
-    if (valid && y[k] >= 0) {
-      const double corr = ak * zp_over_c - e[k];
-      sh.set_a[i] = corr;
-      atomicAdd(&sh.items[item_of(w, y[k])], corr);
-    }
-  });
+  const double a = row_at(w, r) - w.wt * (pending ? r.inv_w * r.qscale : 0.0);
+  row_set_mass(w, (a > 0.0 ? a : 0.0) * zp_over_c, sh);
   return (pending ? part : r.sum_a) * zp_over_c - r.sum_e;
 }
 // First wave: the item in which the cumulative mass passes u * total, in row order, and what row_pick needs (item -1:
@@ -780,30 +745,34 @@ __device__ __forceinline__ void row_locate(const RowWork<T>& w, const RowState& 
   }
   const int per = (n_items + 63) / 64;               // consecutive items per lane, four at a time
   for (;;) {
-    double lsum = 0.0;
-    for (int q = 0; q < per; q += 4) {
+    double lsum = 0.0, t[4];
+    auto four = [&](int q) {
 #pragma unroll
       for (int k = 0; k < 4; ++k) {
         const int it = lane * per + q + k;
-        const double t = q + k < per && it < n_items ? sh.items[it] : 0.0;
-        lsum += t > 0.0 ? t : 0.0;
+        t[k] = q + k < per && it < n_items ? sh.items[it] : 0.0;
       }
+    };
+    for (int q = 0; q < per; q += 4) {
+      four(q);
+#pragma unroll
+      for (int k = 0; k < 4; ++k) lsum += t[k] > 0.0 ? t[k] : 0.0;
     }
     double run = wave_incl_scan_f64(lsum) - lsum;
     int found = -1, last_pos = -1;
     double found_before = 0.0, last_before = 0.0;
     for (int q = 0; q < per; q += 4) {
+      if (per > 4) four(q);                          // (else they are at hand)
 #pragma unroll
       for (int k = 0; k < 4; ++k) {
         const int it = lane * per + q + k;
-        const double t = q + k < per && it < n_items ? sh.items[it] : 0.0;
-        const bool pos = t > 0.0;
-        const bool hit = pos && run + t > target && found < 0;
+        const bool pos = t[k] > 0.0;
+        const bool hit = pos && run + t[k] > target && found < 0;
         last_pos = pos ? it : last_pos;
         last_before = pos ? run : last_before;
         found = hit ? it : found;
         found_before = hit ? run : found_before;
-        run += pos ? t : 0.0;
+        run += pos ? t[k] : 0.0;
       }
     }
     // the first lane that saw the target passed, else the last one that holds an item with mass

@@ -16,6 +16,7 @@ namespace tslt {
 
 constexpr int kMaxTreeDepth = 16;
 constexpr int kMaxBranch = 16;
+static_assert(kMaxBranch <= kMaxStages, "a stage to a candidate");
 
 struct TreeParams {
   const void* target;
@@ -52,6 +53,9 @@ struct TreeParams {
   double* items;
   int64_t items_stride;
   int parts;              // workgroups that share a row
+  uint64_t* part_words;   // [rows, parts]: theirs (handover.h)
+  uint64_t* words;        // [B, n_nodes, 2]: what the workgroups of a tree's nodes leave, in place of the node arrays (else null)
+  Tag tag;
   int all_nodes;
   int n_eval;             // nodes of a tree that tree_node_kernel evaluates: whole layers from the root
   int n_eval_layers;
@@ -74,20 +78,23 @@ inline size_t tree_workspace_bytes(int64_t B, int64_t n_nodes, int64_t V, bool a
   const size_t least = tree_least_workspace_bytes(B, n_nodes, V, all_nodes);
   if (V < kShareLeastV) return least;
   const size_t arrays = align256(size_t(B) * n_nodes * 4) * 4 + align256(size_t(B) * 4) * 2;
-  const size_t rows = arrays + align256(size_t(std::min(B * n_nodes, kShareRows) * tree_items_stride(V)) * sizeof(double));
+  const size_t rows = arrays + size_t(kShareWords) * 8 + align256(size_t(std::min(B * n_nodes, kShareRows) * tree_items_stride(V)) * sizeof(double));
   return std::max(least, rows);
 }
 inline void tree_carve_workspace(TreeParams& p, void* ws, size_t ws_bytes) {
   const size_t per = align256(size_t(p.B) * p.n_nodes * 4);
-  char* w = reinterpret_cast<char*>(ws) + per;       // (the first of the four node arrays that are asked for is not used)
+  char* w = reinterpret_cast<char*>(ws) + per;       // (the first of the four node arrays that are asked for is not used ...)
+  p.words = reinterpret_cast<uint64_t*>(ws);         // (... but where these words take their place, 16 bytes a node)
   p.node_slot = reinterpret_cast<int32_t*>(w); w += per;
   p.node_token = reinterpret_cast<int32_t*>(w); w += per;
   p.node_status = reinterpret_cast<int32_t*>(w); w += per;
   p.walk_node = reinterpret_cast<int32_t*>(w); w += align256(size_t(p.B) * 4);
   p.walk_status = reinterpret_cast<int32_t*>(w); w += align256(size_t(p.B) * 4);
+  p.part_words = reinterpret_cast<uint64_t*>(w); w += size_t(kShareWords) * 8;
   p.items = reinterpret_cast<double*>(w);
   p.items_stride = tree_items_stride(p.V);
-  p.items_rows = int64_t((ws_bytes - size_t(w - reinterpret_cast<char*>(ws))) / (size_t(p.items_stride) * sizeof(double)));
+  const int64_t left = int64_t(ws_bytes) - int64_t(w - reinterpret_cast<char*>(ws));
+  p.items_rows = left > 0 ? left / (p.items_stride * int64_t(sizeof(double))) : 0;
 }
 
 template <typename T> __device__ __forceinline__ const void* tree_row(const TreeParams& p, int64_t b, int node) {
@@ -109,11 +116,17 @@ __device__ __forceinline__ int tree_first_child(const TreeParams& p, int node, i
 // accepted, the draw of its output (a leaf: of its target distribution).  Writes the ratios and rates of the
 // candidates it tested; returns the state (0 sampled, 1 a child accepted, 2 row unusable), the accepted child in
 // `slot`, the output in `token` and the status bits in `st` (both as the first wave has them).  Unless a child was
-// accepted the terms' table is used up.  `items`: the row's masses, where they have been made already (else null).
+// accepted the terms' table is used up.  kParts: p.parts workgroups share the row, `row_at` in order, of which this one is
+// `part`; state 3 where it leaves the node to another.  kOnce: the workgroup has no other row to sweep.
 // ---------------------------------------------------------------------------------------------
-template <typename T, typename Terms, bool kOneCopy = false, int kLoads = kStreamed>
+// (A candidate's ratio and rate go straight to memory where another workgroup may write over them.)
+__device__ __forceinline__ void store_rate(float* to, float v, bool through) {
+  if (through) __hip_atomic_store(to, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  else *to = v;
+}
+template <typename T, typename Terms, bool kOneCopy = false, int kLoads = kStreamed, bool kParts = false, bool kOnce = false>
 __device__ __forceinline__ int tree_node(const TreeParams& p, int64_t b, int node, double* table, bool build, RowShared& sh,
-                                         int& slot, int& token, int& st, const double* items = nullptr) {
+                                         int& slot, int& token, int& st, int64_t row_at = 0, int part = 0) {
   const int lane = lane_id();
   const bool leaf = node >= p.n_int;
   const int64_t row = b * p.n_int + (leaf ? 0 : node);
@@ -127,15 +140,21 @@ __device__ __forceinline__ int tree_node(const TreeParams& p, int64_t b, int nod
   const int64_t c0 = leaf ? 0 : b * (p.n_nodes - 1) + tree_first_child(p, node, layer) - 1;
   const int my_cand = p.cand_tokens[c0 + (lane < k ? lane : 0)];
   const float my_u = p.u_accept[c0 + (lane < k ? lane : 0)];
-  if (items != nullptr) row_fetch<T, Terms>(w, items, table, sh);
-  else row_sweep<T, Terms, kOneCopy, kLoads>(w, table, build ? -1 : -2, sh);
+  if constexpr (kParts) {
+    if (!row_shared<T, Terms, kLoads>(w, table, part, p.parts, p.items + row_at * p.items_stride, p.part_words + row_at * p.parts, p.tag, sh))
+      return 3;
+  } else {
+    row_sweep<T, Terms, kOneCopy, kLoads>(w, table, build ? -1 : -2, sh);
+  }
+  if (kOnce) row_clear<T>(table);                                   // (the table is not needed for another row)
   token = -1;
   st = 0;
   float my_ratio = NAN, my_beta = NAN;                              // NaN if the candidate is never tested
-  if (wave_id() == 0) {
+  const int waves = row_set_waves(w), wave = __builtin_amdgcn_readfirstlane(wave_id());
+  if (wave < waves) {
     RowState r;
     row_eval(w, r, sh);
-    int accepted = -1;
+    int accepted = -1, barriers = 0;
     double part = -1.0;                                             // of the last rejection, whose update is still to be made
     if (!leaf) {
       int gone = -1;
@@ -144,88 +163,66 @@ __device__ __forceinline__ int tree_node(const TreeParams& p, int64_t b, int nod
           const int x = __builtin_amdgcn_readlane(my_cand, i);
           if (x < 0) continue;                                      // absent candidate
           if (part >= 0.0) {                                        // the candidate before was rejected
-            row_update(w, r, part, gone, sh);
+            row_update(w, r, part, gone);
             if (p.wor) {
-              const double rest = 1.0 - sh.removed;
+              const double rest = 1.0 - r.removed;
               r.qscale = rest > 0.0 ? 1.0 / rest : 0.0;
             }
           }
-          const RowTest t = row_test(w, r, x, sh);
+          row_test(w, r, x, barriers, sh);
+          __syncthreads();
+          const RowTest t = row_tested(waves, barriers, sh);
+          ++barriers;
           if (!t.found) r.st |= 4;
           if (lane == i) { my_ratio = float(t.ratio); my_beta = float(t.shared); }   // Section 4.3's beta^(i)
           const double bound = t.ratio < 1.0 ? t.ratio : 1.0;
           const float u = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(my_u), i));
-          if (t.found && double(u) < bound) { accepted = i; token = x; break; }
+          if (same_in_wave(t.found && double(u) < bound)) { accepted = i; token = x; break; }
           part = t.part;
           // drawn without replacement: x leaves the urn and what is left is renormalised
           gone = p.wor && t.found ? x : -1;
-          if (gone >= 0) sh.removed += t.q_x;
+          if (gone >= 0) r.removed += t.q_x;
         }
       }
     }
-    if (accepted < 0 && r.ok) {
-      const bool pending = part >= 0.0 && row_has_residual(r, part);
-      const bool updated = r.stages > 0 || pending;                 // not at a leaf or where every candidate is absent
-      row_locate(w, r, u_res, updated, updated ? row_correct(w, r, pending, part, sh) : 0.0, sh);
+    const bool draw = accepted < 0 && r.ok;
+    const bool pending = draw && part >= 0.0 && row_has_residual(r, part);
+    const bool updated = draw && (r.stages > 0 || pending);         // not at a leaf or where every candidate is absent
+    // (where there is an update there has been a test, and a barrier behind every wave's look at the masses)
+    const double corr = updated ? row_correct(w, r, pending, part, sh) : 0.0;
+    if (wave == 0 && lane == 0) sh.stop_at = barriers + 1;
+    __syncthreads();
+    if (wave == 0) {
+      if (draw) row_locate(w, r, u_res, updated, corr, sh);
+      st = r.st;
+      if (lane == 0) sh.cmd = accepted >= 0 ? accepted : (r.ok ? -1 : -2);
     }
-    st = r.st;
-    if (lane == 0) sh.cmd = accepted >= 0 ? accepted : (r.ok ? -1 : -2);
+  } else {
+    // the others pass as many barriers, whose number they learn at the last of them
+    int barriers = 0;
+    do {
+      __syncthreads();
+      ++barriers;
+    } while (__builtin_amdgcn_readfirstlane(sh.stop_at) != barriers);
   }
   __syncthreads();
   slot = sh.cmd;
   if (threadIdx.x < k) {
-    if (p.out_ratio) p.out_ratio[c0 + lane] = my_ratio;
-    if (p.out_beta) p.out_beta[c0 + lane] = my_beta;
+    const bool through = p.words != nullptr && !p.all_nodes;
+    if (p.out_ratio) store_rate(&p.out_ratio[c0 + lane], my_ratio, through);
+    if (p.out_beta) store_rate(&p.out_beta[c0 + lane], my_beta, through);
   }
   if (slot >= 0) return 1;
   const int state = slot == -1 ? 0 : 2;
   slot = -1;
   if (state == 0) {
-    row_clear<T>(table);
-    __syncthreads();
+    if (!kOnce) {
+      row_clear<T>(table);
+      __syncthreads();
+    }
     if (wave_id() < kPickWaves) token = row_pick(w, table, sh);     // (nothing follows for the other waves)
   }
   return state;
-}
-
-// ---------------------------------------------------------------------------------------------
-// Every node of the layers wanted: one workgroup per node.
-// ---------------------------------------------------------------------------------------------
-// (kItems: their rows' masses have been made by tree_share_kernel.)
-template <typename T, typename Terms, int kWavesPerSimd, bool kItems = false>
-__global__ __launch_bounds__(kRowThreads, kWavesPerSimd) void tree_node_kernel(const TreeParams p) {
-  __shared__ RowShared sh;
-  extern __shared__ __align__(16) unsigned char dyn_lds[];
-  const int64_t b = blockIdx.x / p.n_eval;
-  const int node = int(blockIdx.x - b * p.n_eval);
-  int slot, token, st;
-  const double* items = nullptr;
-  if constexpr (kItems) {
-    items = p.items + int64_t(blockIdx.x) * p.items_stride;
-    if (threadIdx.x == 0) sh.fetched = 0;
-    __syncthreads();
-  }
-  tree_node<T, Terms, kWavesPerSimd == kAlone>(p, b, node, reinterpret_cast<double*>(dyn_lds), true, sh, slot, token, st, items);
-  if (threadIdx.x == 0) {
-    const int64_t n = b * p.n_nodes + node;
-    p.node_slot[n] = slot;
-    p.node_token[n] = token;
-    p.node_status[n] = st;
-    if (p.out_node_token) p.out_node_token[n] = token;
-    if (p.out_node_slot) p.out_node_slot[n] = slot;
-  }
-}
-
-// Those nodes' rows, each shared by p.parts workgroups: the masses of their items.
-template <typename T, typename Terms>
-__global__ __launch_bounds__(kRowThreads, kAlone) void tree_share_kernel(const TreeParams p) {
-  __shared__ RowShared sh;
-  extern __shared__ __align__(16) unsigned char dyn_lds[];
-  const int64_t at = blockIdx.x / p.parts, b = at / p.n_eval;
-  const int part = int(blockIdx.x - at * p.parts);
-  RowWork<T> w;
-  row_open<T>(w, tree_row<T>(p, b, int(at - b * p.n_eval)), p.V, p.rT, sh);
-  row_part<T, Terms, kStreamed>(w, reinterpret_cast<double*>(dyn_lds), part, p.parts, p.items + at * p.items_stride, sh);
 }
 
 // The new-sequence search through the layers that have been evaluated: all threads of the calling workgroup; the first
@@ -237,6 +234,33 @@ struct TreeWalk {
   int n_passed, node, layer, len, status, done;
   int all_status;                                                    // of every node evaluated (if they were looked at)
 };
+// One thread: at(node) gives a node's accepted child (-1: none), output and status bits.
+template <typename F> __device__ __forceinline__ void tree_search(const TreeParams& p, int64_t b, TreeWalk& w, F at) {
+  int32_t* seq = p.out_seq + size_t(b) * (p.depth + 1);
+  int node = 0, layer = 0, len = 0, st = 0, done = 0;
+  while (!done && layer < p.n_eval_layers) {
+    int slot, token, status;
+    at(node, slot, token, status);
+    st |= status;
+    seq[len++] = token;
+    done = 1;
+    if (node >= p.n_int) break;
+    const int child = tree_first_child(p, node, layer);
+    w.first_cand[layer] = child - 1;
+    w.n_cand[layer] = p.expansion[layer];
+    ++layer;
+    if (slot >= 0) {
+      node = child + slot;
+      done = 0;
+    }
+  }
+  w.n_passed = layer;
+  w.node = node;
+  w.layer = layer;
+  w.len = len;
+  w.status = st;
+  w.done = done;
+}
 __device__ __forceinline__ void tree_walk(const TreeParams& p, int64_t b, TreeWalk& w, int32_t* nodes, int room) {
   const int tid = threadIdx.x, n = p.n_eval;
   const bool here = 3 * n <= room;
@@ -259,42 +283,83 @@ __device__ __forceinline__ void tree_walk(const TreeParams& p, int64_t b, TreeWa
   }
   __syncthreads();
   if (tid == 0) {
-    int32_t* seq = p.out_seq + size_t(b) * (p.depth + 1);
-    int node = 0, layer = 0, len = 0, st = 0, done = 0;
-    while (!done && layer < p.n_eval_layers) {
+    tree_search(p, b, w, [&](int node, int& slot, int& token, int& status) {
       const int64_t at = b * p.n_nodes + node;
-      st |= here ? nodes[2 * n + node] : p.node_status[at];
-      seq[len++] = here ? nodes[n + node] : p.node_token[at];
-      done = 1;
-      if (node >= p.n_int) break;
-      const int child = tree_first_child(p, node, layer);
-      w.first_cand[layer] = child - 1;
-      w.n_cand[layer] = p.expansion[layer];
-      ++layer;
-      const int slot = here ? nodes[node] : p.node_slot[at];         // -1 unless a child was accepted
-      if (slot >= 0) {
-        node = child + slot;
-        done = 0;
-      }
-    }
-    w.n_passed = layer;
-    w.node = node;
-    w.layer = layer;
-    w.len = len;
-    w.status = st;
-    w.done = done;
+      slot = here ? nodes[node] : p.node_slot[at];
+      token = here ? nodes[n + node] : p.node_token[at];
+      status = here ? nodes[2 * n + node] : p.node_status[at];
+    });
   }
   __syncthreads();
 }
 // The ratios and rates of the candidates of all other nodes: NaN.
-__device__ __forceinline__ void tree_clear_others(const TreeParams& p, int64_t b, const TreeWalk& w) {
-  for (int i = threadIdx.x; i < p.n_nodes - 1; i += blockDim.x) {
+__device__ __forceinline__ void tree_clear_others(const TreeParams& p, int64_t b, const TreeWalk& w, int threads) {
+  for (int i = threadIdx.x; i < p.n_nodes - 1; i += threads) {
     bool tested = false;
     for (int l = 0; l < w.n_passed; ++l) tested |= i >= w.first_cand[l] && i < w.first_cand[l] + w.n_cand[l];
     if (tested) continue;
     if (p.out_ratio) p.out_ratio[size_t(b) * (p.n_nodes - 1) + i] = NAN;
     if (p.out_beta) p.out_beta[size_t(b) * (p.n_nodes - 1) + i] = NAN;
   }
+}
+
+// What every node evaluated gives as a tree's outputs.
+__device__ __forceinline__ void tree_write(const TreeParams& p, int64_t b, const TreeWalk& w, int threads) {
+  if (threadIdx.x == 0) {
+    p.out_len[b] = w.len;
+    for (int i = w.len; i <= p.depth; ++i) p.out_seq[size_t(b) * (p.depth + 1) + i] = -1;
+    if (p.status) p.status[b] = p.all_nodes ? w.all_status : w.status;
+  }
+  if (!p.all_nodes) tree_clear_others(p, b, w, threads);
+}
+
+// ---------------------------------------------------------------------------------------------
+// Every node of the layers wanted: one workgroup per node, or p.parts of them (kParts).  Where those are the whole of a tree of no
+// more than kHandNodes, what a node came to is left in memory (handover.h) and the workgroup that finds all of its tree's
+// searches the new sequence at once; else tree_walk_kernel or tree_path_kernel does, from the node arrays.
+// ---------------------------------------------------------------------------------------------
+constexpr int kHandNodes = 256;
+template <typename T, typename Terms, int kWavesPerSimd, bool kParts = false>
+__global__ __launch_bounds__(kRowThreads, kWavesPerSimd) void tree_node_kernel(const TreeParams p) {
+  __shared__ RowShared sh;
+  extern __shared__ __align__(16) unsigned char dyn_lds[];
+  const uint32_t at = kParts ? blockIdx.x / uint32_t(p.parts) : blockIdx.x;      // (a division by 64 bits takes half a microsecond)
+  const int64_t b = at / uint32_t(p.n_eval);
+  const int node = int(at - uint32_t(b) * p.n_eval);
+  int slot, token, st;
+  if (tree_node<T, Terms, kWavesPerSimd == kAlone, kStreamed, kParts, true>(p, b, node, reinterpret_cast<double*>(dyn_lds), true, sh, slot, token, st,
+                                                                      at, int(blockIdx.x - at * p.parts)) == 3) return;
+  if (wave_id() != 0) return;
+  const int64_t n = b * p.n_nodes + node;
+  if (threadIdx.x == 0) {
+    if (p.out_node_token) p.out_node_token[n] = token;
+    if (p.out_node_slot) p.out_node_slot[n] = slot;
+    if (p.words == nullptr) {
+      p.node_slot[n] = slot;
+      p.node_token[n] = token;
+      p.node_status[n] = st;
+    }
+  }
+  if (p.words == nullptr) return;
+  // (nothing of the row is needed any more)
+  int* tokens = sh.set_y;
+  int* state = reinterpret_cast<int*>(sh.set_e);
+  TreeWalk& walk = *reinterpret_cast<TreeWalk*>(sh.set_a);
+  static_assert(sizeof(TreeWalk) <= sizeof(sh.set_a) && kHandNodes <= kRowThreads, "room in LDS");
+  if (!hand_over(p.words + 2 * size_t(b) * p.n_nodes, node, p.n_nodes, uint32_t(token), uint32_t((slot + 1) | st << 8), p.tag, tokens, state)) return;
+  int all = 0;
+  for (int i = lane_id(); i < p.n_nodes; i += 64) all |= state[i] >> 8;
+  all = wave_or_i32(all);
+  if (threadIdx.x == 0) {
+    walk.all_status = all;
+    tree_search(p, b, walk, [&](int i, int& s, int& t, int& status) {
+      s = (state[i] & 255) - 1;
+      t = tokens[i];
+      status = state[i] >> 8;
+    });
+  }
+  wave_sync();
+  tree_write(p, b, walk, 64);
 }
 
 // One workgroup per tree, after every node has been evaluated.
@@ -304,12 +369,7 @@ __global__ __launch_bounds__(1024) void tree_walk_kernel(const TreeParams p) {
   extern __shared__ __align__(16) unsigned char dyn_lds[];
   const int64_t b = blockIdx.x;
   tree_walk(p, b, w, reinterpret_cast<int32_t*>(dyn_lds), 3 * p.n_eval <= kWalkNodes ? kWalkNodes : 0);
-  if (threadIdx.x == 0) {
-    p.out_len[b] = w.len;
-    for (int i = w.len; i <= p.depth; ++i) p.out_seq[size_t(b) * (p.depth + 1) + i] = -1;
-    if (p.status) p.status[b] = p.all_nodes ? w.all_status : w.status;
-  }
-  if (!p.all_nodes) tree_clear_others(p, b, w);
+  tree_write(p, b, w, blockDim.x);
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -410,39 +470,28 @@ __global__ __launch_bounds__(NT) void tree_quick_kernel(const TreeParams p) {
     p.walk_status[b] = st_all;
   }
 }
-// The row of the node at which it stopped, shared by p.parts workgroups: the masses of its items.
-template <typename T, typename Terms, int kLoads>
-__global__ __launch_bounds__(kRowThreads, kAlone) void tree_part_kernel(const TreeParams p) {
-  __shared__ RowShared sh;
-  extern __shared__ __align__(16) unsigned char dyn_lds[];
-  const int64_t b = blockIdx.x / p.parts;
-  const int part = int(blockIdx.x - b * p.parts);
-  RowWork<T> w;
-  row_open<T>(w, tree_row<T>(p, b, p.walk_node[b]), p.V, p.rT, sh);
-  row_part<T, Terms, kLoads>(w, reinterpret_cast<double*>(dyn_lds), part, p.parts, p.items + b * p.items_stride, sh);
-}
 
 // ---------------------------------------------------------------------------------------------
 // Only the verified path is wanted: one workgroup per tree takes up the walk where it has got to, then goes from node to
 // node, running Algorithm 5 at each node it reaches, descending into the accepted child and drawing the output of the
 // node it stops at, so that a target row is read only where it counts.  Uniforms are indexed by node, so the result is
-// the one that evaluating every node gives.  (The walk through evaluated layers is not compiled into the other forms,
+// the one that evaluating every node gives.  The node at which the quick walk stopped may be shared by p.parts workgroups; the one that
+// finds its masses complete goes on alone.  (The walk through evaluated layers is not compiled into the other forms,
 // whose registers it costs.)
 // ---------------------------------------------------------------------------------------------
 enum { kFromRoot = 0, kFromHead = 1, kFromQuick = 2 };      // nothing done yet; the first layers evaluated; the quick walk
-template <typename T, typename Terms, int kFrom, int kLoads = kStreamed>
+template <typename T, typename Terms, int kFrom, int kLoads = kStreamed, bool kParts = false>
 __global__ __launch_bounds__(kRowThreads) void tree_path_kernel(const TreeParams p) {
   __shared__ RowShared sh;
   extern __shared__ __align__(16) unsigned char dyn_lds[];
   const int tid = threadIdx.x;
-  const int64_t b = blockIdx.x;
+  const int64_t b = kParts ? blockIdx.x / uint32_t(p.parts) : blockIdx.x;
   int node = 0, layer = 0, len = 0, st_all = 0, token = -1;
   bool done = false;
-  const double* items = nullptr;
   if constexpr (kFrom == kFromHead) {
     __shared__ TreeWalk walk;
     tree_walk(p, b, walk, reinterpret_cast<int32_t*>(dyn_lds), int(Terms::kBytes / 4));      // (the terms' table comes later)
-    tree_clear_others(p, b, walk);
+    tree_clear_others(p, b, walk, kRowThreads);
     node = walk.node;
     layer = walk.layer;
     len = walk.len;
@@ -452,8 +501,6 @@ __global__ __launch_bounds__(kRowThreads) void tree_path_kernel(const TreeParams
     node = p.walk_node[b];
     layer = len = tree_layer(p, node);
     st_all = p.walk_status[b];
-    if (p.parts > 1) items = p.items + b * p.items_stride;
-    if (tid == 0) sh.fetched = 0;
   } else {
     for (int i = tid; i < p.n_nodes - 1; i += kRowThreads) {
       if (p.out_ratio) p.out_ratio[size_t(b) * (p.n_nodes - 1) + i] = NAN;
@@ -463,11 +510,18 @@ __global__ __launch_bounds__(kRowThreads) void tree_path_kernel(const TreeParams
   __syncthreads();
   int32_t* seq = p.out_seq + size_t(b) * (p.depth + 1);
   bool build = true;                         // the terms' table is still to be made
+  bool shared = kParts;
   while (!done) {
-    int slot, st;
-    const int state = tree_node<T, Terms, false, kLoads>(p, b, node, reinterpret_cast<double*>(dyn_lds), build, sh, slot, token, st, items);
-    build = items != nullptr;
-    items = nullptr;
+    int slot, st, state;
+    if (kParts && shared) {
+      state = tree_node<T, Terms, false, kLoads, kParts>(p, b, node, reinterpret_cast<double*>(dyn_lds), true, sh, slot, token, st, b,
+                                                         int(blockIdx.x - b * p.parts));
+      if (state == 3) return;
+      shared = false;
+    } else {
+      state = tree_node<T, Terms, false, kLoads>(p, b, node, reinterpret_cast<double*>(dyn_lds), build, sh, slot, token, st);
+      build = false;
+    }
     st_all |= st;
     if (tid == 0) seq[len] = token;
     ++len;
@@ -532,16 +586,13 @@ template <typename T, typename Terms> hipError_t launch_verify_tree_with(TreePar
     const int64_t rows = p.B * p.n_eval;
     const bool alone = rows <= compute_units();
     p.parts = rows <= p.items_rows ? row_parts<T, Terms>(p.V, rows) : 1;
-    if (p.parts > 1) {
-      hipLaunchKernelGGL((tree_share_kernel<T, Terms>), dim3(unsigned(rows * p.parts)), dim3(kRowThreads), Terms::kBytes, s, p);
-      if ((e = hipGetLastError()) != hipSuccess) return e;
-      hipLaunchKernelGGL((tree_node_kernel<T, Terms, kAlone, true>), dim3(unsigned(rows)), dim3(kRowThreads), Terms::kBytes, s, p);
-    } else {
-      hipLaunchKernelGGL((alone ? tree_node_kernel<T, Terms, kAlone> : tree_node_kernel<T, Terms, kShared>), dim3(unsigned(rows)),
-                         dim3(kRowThreads), Terms::kBytes, s, p);
-    }
-    if ((e = hipGetLastError()) != hipSuccess) return e;
+    if (p.n_eval_layers <= p.depth || p.n_nodes > kHandNodes) p.words = nullptr;
+    p.tag = next_tag();
+    hipLaunchKernelGGL((p.parts > 1 ? tree_node_kernel<T, Terms, kAlone, true> : alone ? tree_node_kernel<T, Terms, kAlone> : tree_node_kernel<T, Terms, kShared>),
+                       dim3(unsigned(rows * p.parts)), dim3(kRowThreads), Terms::kBytes, s, p);
+    if ((e = hipGetLastError()) != hipSuccess || p.words != nullptr) return e;
   }
+  p.words = nullptr;
   auto walk = [&](auto fn) {
     hipLaunchKernelGGL(fn, dim3(unsigned(p.B)), dim3(kRowThreads), Terms::kBytes, s, p);
     return hipGetLastError();
@@ -553,14 +604,13 @@ template <typename T, typename Terms> hipError_t launch_verify_tree_with(TreePar
       if ((e = hipGetLastError()) != hipSuccess) return e;
       // as many workgroups to a row as fill the chip, a run for every wave at least
       const int64_t runs = p.V / (ElemTraits<T>::kPerVec * kRunVecs) + 1;
-      p.parts = int(std::max<int64_t>(1, std::min<int64_t>(compute_units() / p.B, (runs + kRowWaves - 1) / kRowWaves)));
+      p.parts = p.B <= p.items_rows ? int(std::max<int64_t>(1, std::min<int64_t>(std::min<int64_t>(compute_units(), kShareWords) / p.B, (runs + kRowWaves - 1) / kRowWaves))) : 1;
       auto last_rows = [&](auto loads) -> hipError_t {
         constexpr int kLoads = decltype(loads)::value;
-        if (p.parts > 1) {
-          hipLaunchKernelGGL((tree_part_kernel<T, Terms, kLoads>), dim3(unsigned(p.B * p.parts)), dim3(kRowThreads), Terms::kBytes, s, p);
-          if ((e = hipGetLastError()) != hipSuccess) return e;
-        }
-        return walk(tree_path_kernel<T, Terms, kFromQuick, kLoads>);
+        if (p.parts == 1) return walk(tree_path_kernel<T, Terms, kFromQuick, kLoads>);
+        p.tag = next_tag();
+        hipLaunchKernelGGL((tree_path_kernel<T, Terms, kFromQuick, kLoads, true>), dim3(unsigned(p.B * p.parts)), dim3(kRowThreads), Terms::kBytes, s, p);
+        return hipGetLastError();
       };
       if constexpr (ElemTraits<T>::kBytes == 4) {
         if (p.B * p.n_nodes * p.V * 4 > kStreamTreeBytes) return last_rows(std::integral_constant<int, kCached>{});

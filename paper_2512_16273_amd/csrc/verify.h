@@ -40,9 +40,12 @@ struct VerifyParams {
   int stage0;            // staged mode: positions in the first stage (0 = all positions in one launch)
   int j_begin, j_count;  // the positions one launch covers (verify_round_kernel with draws: the bonus row too)
   int draws;             // verify_round_kernel draws as well
-  double* items;         // masses of shared rows' items (null: the workspace has no room for them)
+  double* items;         // masses of shared rows' items
   int64_t items_stride;
   int parts;             // workgroups that share a row
+  uint64_t* part_words;  // [rows, parts]: theirs (handover.h)
+  uint64_t* words;       // [B, gamma + 1, 2]: what a round's workgroups leave (null: the workspace has no room; nothing is shared)
+  Tag tag;
 };
 constexpr int kFlagSkipped = 3;
 
@@ -52,20 +55,38 @@ inline int64_t verify_rows_to_share(int64_t B, int64_t gamma, int64_t V) {
   return B * (gamma + 1) <= kShareRows ? B * (gamma + 1) : (B <= kShareRows ? B : 0);
 }
 inline int64_t verify_items_stride(int64_t V) { return int64_t(row_segments(V)) * kSubChunks + 2; }
-// What a call has to be given: a decision and a status word for every position.  With room for the masses of shared rows'
-// items behind them, the size that callers are told, it may share rows as well.
+// Rows of a round whose workgroups leave their results in memory for the last of each sequence.  (Where there is little to
+// gain, in rows as short as this, callers are told the size that they have always been told.)
+constexpr int64_t kHandRows = 1024, kHandLeastV = 2048;
+inline int64_t verify_rows_handed(int64_t B, int64_t gamma, int64_t V) {
+  return V >= kHandLeastV && B * (gamma + 1) <= kHandRows ? B * (gamma + 1) : 0;
+}
+// What a call has to be given: a decision and a status word for every position.  With room behind them for what workgroups
+// hand over, the size that callers are told, rows are shared and a round takes one launch.
 inline size_t verify_least_workspace_bytes(int64_t B, int64_t gamma) { return align256(size_t(B) * gamma * 4) * 2; }
+inline size_t verify_words_bytes(int64_t B, int64_t gamma, int64_t V) { return align256(size_t(verify_rows_handed(B, gamma, V)) * 16); }
+inline size_t verify_part_words_bytes(int64_t B, int64_t gamma, int64_t V) {
+  return verify_rows_to_share(B, gamma, V) > 0 ? align256(size_t(kShareWords) * 8) : 0;
+}
 inline size_t verify_workspace_bytes(int64_t B, int64_t gamma, int64_t V, int k_cap) {
   (void)k_cap;
-  return verify_least_workspace_bytes(B, gamma) + align256(size_t(verify_rows_to_share(B, gamma, V) * verify_items_stride(V)) * sizeof(double));
+  return verify_least_workspace_bytes(B, gamma) + verify_words_bytes(B, gamma, V) + verify_part_words_bytes(B, gamma, V) +
+         align256(size_t(verify_rows_to_share(B, gamma, V) * verify_items_stride(V)) * sizeof(double));
 }
 inline void verify_carve_workspace(VerifyParams& p, void* ws, size_t ws_bytes) {
   char* w = reinterpret_cast<char*>(ws);
   p.flags = reinterpret_cast<int32_t*>(w); w += align256(size_t(p.B) * p.gamma * 4);
   p.row_status = reinterpret_cast<int32_t*>(w); w += align256(size_t(p.B) * p.gamma * 4);
-  p.items = ws_bytes >= verify_workspace_bytes(p.B, p.gamma, p.V, p.k_cap) && verify_rows_to_share(p.B, p.gamma, p.V) > 0
-                ? reinterpret_cast<double*>(w) : nullptr;
   p.items_stride = verify_items_stride(p.V);
+  p.words = p.part_words = nullptr;
+  p.items = nullptr;
+  if (ws_bytes < verify_workspace_bytes(p.B, p.gamma, p.V, p.k_cap)) return;
+  if (verify_rows_handed(p.B, p.gamma, p.V) > 0) p.words = reinterpret_cast<uint64_t*>(w);
+  w += verify_words_bytes(p.B, p.gamma, p.V);
+  if (verify_rows_to_share(p.B, p.gamma, p.V) > 0) {
+    p.part_words = reinterpret_cast<uint64_t*>(w);
+    p.items = reinterpret_cast<double*>(w + verify_part_words_bytes(p.B, p.gamma, p.V));
+  }
 }
 
 template <typename T> __device__ __forceinline__ const void* target_row(const VerifyParams& p, int64_t b, int j) {
@@ -141,49 +162,24 @@ __global__ __launch_bounds__(kBlock, kAccWavesPerSimd) void verify_accept_kernel
 }
 
 // ---------------------------------------------------------------------------------------------
-// Rows shared by p.parts workgroups each: the masses of their items, for a launch that takes them up (row_fetch).
-// kRound: every row of a round; else the one of each sequence that is to be sampled, from kernel A's decisions.
+// Kernel B: one workgroup of 1024 threads per sequence, or p.parts of them (kParts), sweeps the row to be sampled and writes
+// the sequence's outputs.
 // ---------------------------------------------------------------------------------------------
-template <typename T, typename Terms, bool kRound, int kLoads = kStreamed>
-__global__ __launch_bounds__(kRowThreads, kAlone) void verify_part_kernel(const VerifyParams p) {
-  __shared__ RowShared sh;
-  extern __shared__ __align__(16) unsigned char dyn_lds[];
-  const int64_t at = blockIdx.x / p.parts;           // the row, or its sequence
-  const int part = int(blockIdx.x - at * p.parts);
-  int64_t b = at;
-  int j = 0;
-  if constexpr (kRound) {
-    b = at / (p.gamma + 1);
-    j = int(at - b * (p.gamma + 1));
-  } else {
-    const int32_t* fl_b = p.flags + b * p.gamma;
-    int first = p.gamma;
-    for (int i = lane_id(); i < p.gamma; i += 64)
-      if (fl_b[i] != 1) { first = i; break; }
-    j = -wave_max_i32(-first);
-  }
-  RowWork<T> w;
-  row_open<T>(w, target_row<T>(p, b, j), p.V, p.rT, sh);
-  row_part<T, Terms, kLoads>(w, reinterpret_cast<double*>(dyn_lds), part, p.parts, p.items + at * p.items_stride, sh);
-}
-
-// ---------------------------------------------------------------------------------------------
-// Kernel B: one workgroup of 1024 threads per sequence sweeps the row to be sampled, or takes up its masses (kItems), and
-// writes the sequence's outputs.
-// ---------------------------------------------------------------------------------------------
-template <typename T, typename Terms, int kWavesPerSimd, bool kItems = false, int kLoads = kStreamed>
+template <typename T, typename Terms, int kWavesPerSimd, bool kParts = false, int kLoads = kStreamed>
 __global__ __launch_bounds__(kRowThreads, kWavesPerSimd) void verify_resample_kernel(const VerifyParams p) {
   __shared__ RowShared sh;
   extern __shared__ __align__(16) unsigned char dyn_lds[];
   double* table = reinterpret_cast<double*>(dyn_lds);
   const int tid = threadIdx.x, lane = lane_id();
-  const int64_t b = blockIdx.x;
+  const uint32_t at = kParts ? blockIdx.x / uint32_t(p.parts) : blockIdx.x;      // (a division by 64 bits takes half a microsecond)
+  const int64_t b = at;
+  const int part = kParts ? int(blockIdx.x - at * p.parts) : 0;
   // The decisions of the sequence's first 64 positions are requested first; half of the table is built while they
   // travel.  Every wave then finds the first rejected position by itself (gamma when every draft token was
   // accepted): the words are few and nothing has to be handed round.
   const int32_t* fl_b = p.flags + b * p.gamma;
   const int f0 = lane < p.gamma ? fl_b[lane] : 1;
-  if constexpr (!kItems) Terms::build(table, p.rT, kRowThreads, 0);
+  if constexpr (!kParts) Terms::build(table, p.rT, kRowThreads, 0);
   int j0 = f0 != 1 ? lane : p.gamma;
   if (p.gamma > 64 && ballot(f0 != 1) == 0) {
     for (int j = lane + 64; j < p.gamma; j += 64)
@@ -200,29 +196,36 @@ __global__ __launch_bounds__(kRowThreads, kWavesPerSimd) void verify_resample_ke
   const float u_res = p.u_resample[b * (p.gamma + 1) + jstar];
   RowWork<T> w;
   int token = -1;
-  if (tid == 0) { sh.cmd = 0; sh.fetched = 0; } // read behind a barrier: 1 when there is something to draw from
+  if (tid == 0) sh.cmd = 0;                    // read behind a barrier: 1 when there is something to draw from
   if (!unusable) {
     row_open<T>(w, target_row<T>(p, b, jstar), p.V, p.rT, sh);
     row_take_set(w, p.q_idx + size_t(r) * p.k_cap, p.q_logit + size_t(r) * p.k_cap, residual ? p.q_count[r] : 0, p.k_cap);
-    if constexpr (kItems) {
-      __syncthreads();
-      row_fetch<T, Terms>(w, p.items + b * p.items_stride, table, sh);
+    if constexpr (kParts) {
+      if (!row_shared<T, Terms, kLoads>(w, table, part, p.parts, p.items + b * p.items_stride, p.part_words + b * p.parts, p.tag, sh)) return;
     } else {
       row_sweep<T, Terms, kWavesPerSimd == kAlone, kLoads>(w, table, 1, sh);
     }
-    if (wave_id() == 0) {
-      RowState rst;
+    row_clear<T>(table);
+    const int waves = row_set_waves(w), wave = __builtin_amdgcn_readfirstlane(wave_id());
+    RowState rst;
+    double left = 0.0;                             // max(0, p - q) at this thread's entry
+    if (wave < waves) {
       row_eval(w, rst, sh);
-      if (rst.ok) {
-        row_locate(w, rst, u_res, residual, residual ? row_test_first(w, rst, -1, sh).part * rst.zp - rst.sum_e : 0.0, sh);
-      }
+      if (residual && rst.ok) left = row_test(w, rst, -1, 0, sh);
+    }
+    __syncthreads();
+    if (wave >= waves && wave >= kPickWaves) return;
+    if (wave < waves && residual && rst.ok) row_set_mass(w, left * rst.zp, sh);
+    __syncthreads();
+    if (wave == 0) {
+      if (rst.ok) row_locate(w, rst, u_res, residual, residual ? row_tested(waves, 0, sh).part * rst.zp - rst.sum_e : 0.0, sh);
       if (lane == 0) { sh.cmd = rst.ok ? 1 : 0; sh.st = rst.st; }      // (another wave may still look at sh.flags)
     }
-    row_clear<T>(table);
     __syncthreads();
-    if (wave_id() >= kPickWaves) return;
+    if (wave >= kPickWaves) return;
     if (sh.cmd) token = row_pick(w, table, sh);
   } else {
+    if (part != 0) return;
     if (tid == 0) sh.st = 0;
     __syncthreads();
   }
@@ -246,21 +249,56 @@ __global__ __launch_bounds__(kRowThreads, kWavesPerSimd) void verify_resample_ke
 
 // ---------------------------------------------------------------------------------------------
 // A round in one pass over the rows, for batches that do not fill the chip (bound there by one row's own latency: the
-// sweep by sixteen waves, then the chain of steps after it; one sequence x 4, V = 32000: 26 us by kernels A and B,
-// 15 so; 8 x 8, V = 128256: 30.6 and 19.3): one workgroup of 1024 threads per (sequence, row) sweeps its row once, takes the acceptance test from the sums and, if the token is rejected (or
+// sweep by sixteen waves, then the chain of steps after it): one workgroup of 1024 threads per (sequence, row), or p.parts of them
+// (kParts), sweeps its row once, takes the acceptance test from the sums and, if the token is rejected (or
 // the row is the bonus row), draws the replacement at once, whether or not an earlier position will turn out to
-// have been rejected.  A second launch, one wave per sequence, keeps the draw of the first rejected position.
-// Until then a position's draw waits in its place in out_tokens, and the bonus row's status in out_accept_len.
+// have been rejected.  What a position came to it leaves in memory (handover.h); the workgroup that finds those of all its
+// sequence keeps the draw of the first rejected position and writes the sequence's outputs.  With a workspace that has no room
+// for that a second launch does, one wave per sequence; until then a position's draw waits in its place in out_tokens, and
+// the bonus row's status in out_accept_len.
 // Without draws it is kernel A for such batches: the decisions of a batch are made in the same way whether it is
 // verified by one call, by two halves or in stages.
 // ---------------------------------------------------------------------------------------------
-template <typename T, typename Terms, int kWavesPerSimd, bool kItems = false>
+// One wave: the outputs of a sequence, from position j's decision, status bits and draw on: at(j) gives them for the positions of a
+// lane, four words of gamma + 1 of them.  x_first: the lane's draft token.
+template <typename F>
+__device__ __forceinline__ void write_sequence(const VerifyParams& p, int64_t b, int x_first, F at) {
+  const int lane = lane_id();
+  int jstar = p.gamma, st = 0, token = -1;
+  for (int j0 = 0; j0 <= p.gamma; j0 += 64) {
+    const int j = j0 + lane;
+    int flag = 1, s = 0, t = -1;
+    if (j <= p.gamma) at(j, flag, s, t);
+    const uint64_t stop = ballot(j == p.gamma || (j < p.gamma && flag != 1));
+    st |= stop == 0 || lane <= __ffsll((long long)stop) - 1 ? s : 0;
+    if (stop != 0) {
+      const int src = __ffsll((long long)stop) - 1;
+      jstar = j0 + src;
+      token = __builtin_amdgcn_readlane(t, src);
+      break;
+    }
+  }
+  st = wave_or_i32(st);
+  int32_t* ot = p.out_tokens + size_t(b) * (p.gamma + 1);
+  for (int j = lane; j <= p.gamma; j += 64) {
+    int v = -1;
+    if (j < jstar) v = j == lane ? x_first : p.draft_tokens[b * p.gamma + j];
+    else if (j == jstar) v = token;
+    ot[j] = v;
+  }
+  if (lane == 0) {
+    p.out_accept_len[b] = jstar;
+    if (p.status) p.status[b] = st;
+  }
+}
+template <typename T, typename Terms, int kWavesPerSimd, bool kParts = false>
 __global__ __launch_bounds__(kRowThreads, kWavesPerSimd) void verify_round_kernel(const VerifyParams p) {
   __shared__ RowShared sh;
   extern __shared__ __align__(16) unsigned char dyn_lds[];
   double* table = reinterpret_cast<double*>(dyn_lds);
-  const int64_t b = blockIdx.x / p.j_count;
-  const int j = p.j_begin + int(blockIdx.x - b * p.j_count);
+  const uint32_t at = kParts ? blockIdx.x / uint32_t(p.parts) : blockIdx.x;      // (a division by 64 bits takes half a microsecond)
+  const int64_t b = at / uint32_t(p.j_count);
+  const int j = p.j_begin + int(at - uint32_t(b) * p.j_count);
   const bool bonus = j == p.gamma;
   const int64_t r = b * p.gamma + (bonus ? 0 : j);
   if (p.j_begin > 0 && skip_position(p, b, r)) return;
@@ -269,79 +307,85 @@ __global__ __launch_bounds__(kRowThreads, kWavesPerSimd) void verify_round_kerne
   const int count = p.q_count[r], x = p.draft_tokens[r];
   const float u_acc = p.u_accept[r], u_res = p.u_resample[b * (p.gamma + 1) + j];
   row_take_set(w, p.q_idx + size_t(r) * p.k_cap, p.q_logit + size_t(r) * p.k_cap, bonus ? 0 : count, p.k_cap);
-  if constexpr (kItems) {
-    if (threadIdx.x == 0) sh.fetched = 0;
-    __syncthreads();
-    row_fetch<T, Terms>(w, p.items + (b * (p.gamma + 1) + j) * p.items_stride, table, sh);
+  if constexpr (kParts) {
+    const int part = int(blockIdx.x - at * p.parts);
+    if (!row_shared<T, Terms>(w, table, part, p.parts, p.items + at * p.items_stride, p.part_words + at * p.parts, p.tag, sh)) return;
   } else {
     row_sweep<T, Terms, kWavesPerSimd == kAlone>(w, table, -1, sh);
   }
   // (nothing is stored to memory before the last barrier, which would wait for it)
+  row_clear<T>(table);
+  const int waves = row_set_waves(w), wave = __builtin_amdgcn_readfirstlane(wave_id());
   int st = 0, flag = 0;
   float ratio = NAN, beta = NAN;
-  if (wave_id() == 0) {
-    RowState rst;
+  RowState rst;
+  double left = 0.0;                               // max(0, p - q) at this thread's entry
+  if (wave < waves) {
     row_eval(w, rst, sh);
+    if (!bonus && rst.ok) left = row_test(w, rst, x, 0, sh);
+  }
+  __syncthreads();
+  if (wave >= waves && wave >= kPickWaves) return;
+  double corr = 0.0;
+  if (wave < waves) {
     flag = rst.ok ? 0 : 2;
-    double corr = 0.0;
     if (!bonus && rst.ok) {
-      const RowTest t = row_test_first(w, rst, x, sh);
+      const RowTest t = row_tested(waves, 0, sh);
       ratio = float(t.ratio);
       beta = float(t.shared);
       if (!t.found) rst.st |= 4;
       const double bound = t.ratio < 1.0 ? t.ratio : 1.0;
       flag = t.found && double(u_acc) < bound ? 1 : 0;
       corr = t.part * rst.zp - rst.sum_e;
+      if (flag == 0 && p.draws) row_set_mass(w, left * rst.zp, sh);
     }
+  }
+  __syncthreads();
+  if (wave == 0) {
     if (flag == 0 && p.draws) row_locate(w, rst, u_res, !bonus, corr, sh);
     st = rst.st;
     if (lane_id() == 0) sh.cmd = flag;
   }
-  row_clear<T>(table);
   __syncthreads();
-  if (wave_id() >= kPickWaves) return;
+  if (wave >= kPickWaves) return;
   const int token = sh.cmd == 0 && p.draws ? row_pick(w, table, sh) : -1;
-  if (threadIdx.x == 0) {
+  if (threadIdx.x == 0 && !bonus) {
+    if (p.out_ratio) p.out_ratio[r] = ratio;
+    if (p.out_beta) p.out_beta[r] = beta;
+  }
+  if (p.words == nullptr || !p.draws) {
+    if (threadIdx.x != 0) return;
     if (!bonus) {
       p.flags[r] = flag;
       p.row_status[r] = st;
-      if (p.out_ratio) p.out_ratio[r] = ratio;
-      if (p.out_beta) p.out_beta[r] = beta;
     } else {
       p.out_accept_len[b] = st;
     }
     if (p.draws) p.out_tokens[size_t(b) * (p.gamma + 1) + j] = token;
+    return;
   }
+  if (wave_id() != 0) return;
+  const int lane = lane_id();
+  const int x_first = p.draft_tokens[b * p.gamma + (lane < p.gamma ? lane : p.gamma - 1)];      // (travels meanwhile)
+  // (nothing in LDS is needed any more)
+  int* tokens = sh.set_y;
+  int* state = reinterpret_cast<int*>(sh.set_e);
+  if (!hand_over(p.words + 2 * size_t(b) * (p.gamma + 1), j, p.gamma + 1, uint32_t(token), uint32_t(flag | st << 8), p.tag, tokens, state)) return;
+  write_sequence(p, b, x_first, [&](int i, int& f, int& s, int& t) {
+    t = tokens[i];
+    f = state[i] & 255;
+    s = state[i] >> 8;
+  });
 }
 __global__ __launch_bounds__(64) void verify_select_kernel(const VerifyParams p) {
   const int64_t b = blockIdx.x;
   const int lane = threadIdx.x;
-  // (everything that the first 64 positions need is requested at once)
-  const int j_lane = lane < p.gamma ? lane : p.gamma - 1;
-  const int flag_first = p.flags[b * p.gamma + j_lane], st_first = p.row_status[b * p.gamma + j_lane];
-  const int x_first = p.draft_tokens[b * p.gamma + j_lane], st_bonus = p.out_accept_len[b];
-  int jstar = p.gamma, st = 0;
-  for (int j0 = 0; j0 < p.gamma && jstar == p.gamma; j0 += 64) {
-    const int j = j0 + lane;
-    const int flag = j0 == 0 ? flag_first : (j < p.gamma ? p.flags[b * p.gamma + j] : 1);
-    const int s = j0 == 0 ? st_first : (j < p.gamma ? p.row_status[b * p.gamma + j] : 0);
-    const uint64_t stop = ballot(j < p.gamma && flag != 1);
-    if (stop != 0) jstar = j0 + __ffsll((long long)stop) - 1;
-    st |= j <= jstar && j < p.gamma ? s : 0;
-  }
-  st = wave_or_i32(st);
-  if (jstar == p.gamma) st |= st_bonus;
-  int32_t* ot = p.out_tokens + size_t(b) * (p.gamma + 1);
-  for (int j = lane; j <= p.gamma; j += 64) {
-    if (j == jstar) continue;
-    int v = -1;
-    if (j < jstar) v = j == lane ? x_first : p.draft_tokens[b * p.gamma + j];
-    ot[j] = v;
-  }
-  if (lane == 0) {
-    p.out_accept_len[b] = jstar;
-    if (p.status) p.status[b] = st;
-  }
+  const int x_first = p.draft_tokens[b * p.gamma + (lane < p.gamma ? lane : p.gamma - 1)];
+  write_sequence(p, b, x_first, [&](int j, int& flag, int& s, int& t) {
+    t = p.out_tokens[size_t(b) * (p.gamma + 1) + j];
+    if (j < p.gamma) { flag = p.flags[b * p.gamma + j]; s = p.row_status[b * p.gamma + j]; }
+    else s = p.out_accept_len[b];
+  });
 }
 
 // Largest batch, in rows B * (gamma + 1), that is verified by verify_round_kernel: one row per compute unit, and two
@@ -368,7 +412,7 @@ template <typename T, typename Terms> hipError_t launch_verify_with(VerifyParams
     return by_rows(KernelTag<&verify_round_kernel<T, Terms, kAlone>>{}, KernelTag<&verify_round_kernel<T, Terms, kShared>>{},
                    p.B * p.j_count);
   };
-  auto share = [&](auto fn, int64_t rows) -> hipError_t {
+  auto share = [&](auto fn, int64_t rows) -> hipError_t {                        // p.parts workgroups per row
     if constexpr (kLargeTable<Terms>) {
       if ((e = allow_dynamic_lds<decltype(fn)::value>(int(Terms::kBytes))) != hipSuccess) return e;
     }
@@ -380,14 +424,10 @@ template <typename T, typename Terms> hipError_t launch_verify_with(VerifyParams
     p.j_begin = 0;
     p.j_count = p.gamma + 1;
     p.draws = 1;
-    p.parts = p.items != nullptr ? row_parts<T, Terms>(p.V, p.B * p.j_count) : 1;
-    if (p.parts > 1) {
-      if ((e = share(KernelTag<&verify_part_kernel<T, Terms, true>>{}, p.B * p.j_count)) != hipSuccess) return e;
-      const auto fetch = KernelTag<&verify_round_kernel<T, Terms, kAlone, true>>{};
-      if ((e = by_rows(fetch, fetch, p.B * p.j_count)) != hipSuccess) return e;
-    } else if ((e = round()) != hipSuccess) {
-      return e;
-    }
+    p.parts = p.words != nullptr && p.items != nullptr ? row_parts<T, Terms>(p.V, p.B * p.j_count) : 1;
+    if (p.words != nullptr) p.tag = next_tag();
+    e = p.parts > 1 ? share(KernelTag<&verify_round_kernel<T, Terms, kAlone, true>>{}, p.B * p.j_count) : round();
+    if (e != hipSuccess || p.words != nullptr) return e;
     hipLaunchKernelGGL(verify_select_kernel, dim3(unsigned(p.B)), dim3(64), 0, s, p);
     return hipGetLastError();
   }
@@ -414,9 +454,8 @@ template <typename T, typename Terms> hipError_t launch_verify_with(VerifyParams
     auto resample = [&](auto loads) -> hipError_t {
       constexpr int kLoads = decltype(loads)::value;
       if (p.parts > 1) {
-        if ((e = share(KernelTag<&verify_part_kernel<T, Terms, false, kLoads>>{}, p.B)) != hipSuccess) return e;
-        const auto fetch = KernelTag<&verify_resample_kernel<T, Terms, kAlone, true>>{};
-        return by_rows(fetch, fetch, p.B);
+        p.tag = next_tag();
+        return share(KernelTag<&verify_resample_kernel<T, Terms, kAlone, true, kLoads>>{}, p.B);
       }
       return by_rows(KernelTag<&verify_resample_kernel<T, Terms, kAlone, false, kLoads>>{},
                      KernelTag<&verify_resample_kernel<T, Terms, kShared, false, kLoads>>{}, p.B);
