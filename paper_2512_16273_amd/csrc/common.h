@@ -258,6 +258,14 @@ template <int N> __device__ __forceinline__ void wave_incl_scan_f64(double (&v)[
 #pragma unroll
   for (int i = 0; i < N; ++i) v[i] += dpp_f64<0x143, 0xC>(0.0, v[i]);
 }
+// Inclusive scan within each row of 16 lanes.
+__device__ __forceinline__ double scan16_f64(double v) {
+  v += dpp_or_zero_f64<0x111>(v);
+  v += dpp_or_zero_f64<0x112>(v);
+  v += dpp_or_zero_f64<0x114>(v);
+  v += dpp_or_zero_f64<0x118>(v);
+  return v;
+}
 __device__ __forceinline__ double wave_incl_scan_f64(double v) {
   double t[1] = {v};
   wave_incl_scan_f64<1>(t);

@@ -252,8 +252,8 @@ struct RowShared {
   int found[kMaxStages];
   double wave_sum[kRowWaves];
   float wave_max[kRowWaves];
-  double target, before, none;
-  int flags, next_run, item, n_corr, pick, last, cmd, st, fetched, stop_at;
+  double target, before;
+  int flags, next_run, item, n_corr, pick, cmd, st, fetched, stop_at;
 };
 
 template <typename T> struct RowWork {
@@ -683,9 +683,8 @@ __device__ __forceinline__ RowTest row_tested(int waves, int stage, const RowSha
 }
 template <typename T>
 __device__ __forceinline__ int item_of(const RowWork<T>& w, int y) {
-  if (y < w.rs.head) return 0;
-  const int v = (y - w.rs.head) / ElemTraits<T>::kPerVec;
-  return v >= w.rs.nvec ? w.n_items - 1 : 1 + v / kRunVecs;
+  const uint32_t v = uint32_t(y - w.rs.head) / ElemTraits<T>::kPerVec;
+  return y < w.rs.head ? 0 : (v >= uint32_t(w.rs.nvec) ? w.n_items - 1 : int(1 + v / kRunVecs));
 }
 // The mass at the thread's entry becomes `mass`, in units of the row's terms: the item it falls into is corrected by the difference.
 template <typename T> __device__ __forceinline__ void row_set_mass(const RowWork<T>& w, double mass, RowShared& sh) {
@@ -738,41 +737,54 @@ __device__ __forceinline__ void row_locate(const RowWork<T>& w, const RowState& 
     corrected = false;
     total = r.zp;
   }
-  const double target = double(u) * total;
-  if (lane == 0) {                                   // (what is seldom looked at again waits in LDS, not in registers)
-    sh.target = target; sh.none = kNoResidual * r.zp; sh.n_corr = corrected ? w.count : 0;
-    sh.item = sh.last = -1; sh.pick = 0x7FFFFFFF;
+  const double target = double(u) * total, none = kNoResidual * r.zp;
+  if (lane == 0) {
+    sh.target = target; sh.n_corr = corrected ? w.count : 0;
+    sh.item = sh.pick = -1;
   }
   const int per = (n_items + 63) / 64;               // consecutive items per lane, four at a time
   for (;;) {
-    double lsum = 0.0, t[4];
+    double lsum = 0.0, t0, t1, t2, t3;               // (uniform branches: a row of 64 items or fewer has one a lane)
     auto four = [&](int q) {
-#pragma unroll
-      for (int k = 0; k < 4; ++k) {
-        const int it = lane * per + q + k;
-        t[k] = q + k < per && it < n_items ? sh.items[it] : 0.0;
+      const int it = lane * per + q;
+      t0 = it < n_items ? sh.items[it] : 0.0;
+      t1 = t2 = t3 = 0.0;
+      if (per > 1) {
+        t1 = q + 1 < per && it + 1 < n_items ? sh.items[it + 1] : 0.0;
+        t2 = q + 2 < per && it + 2 < n_items ? sh.items[it + 2] : 0.0;
+        t3 = q + 3 < per && it + 3 < n_items ? sh.items[it + 3] : 0.0;
       }
     };
     for (int q = 0; q < per; q += 4) {
       four(q);
-#pragma unroll
-      for (int k = 0; k < 4; ++k) lsum += t[k] > 0.0 ? t[k] : 0.0;
+      lsum += t0 > 0.0 ? t0 : 0.0;
+      if (per > 1) {
+        lsum += t1 > 0.0 ? t1 : 0.0;
+        lsum += t2 > 0.0 ? t2 : 0.0;
+        lsum += t3 > 0.0 ? t3 : 0.0;
+      }
     }
     double run = wave_incl_scan_f64(lsum) - lsum;
     int found = -1, last_pos = -1;
     double found_before = 0.0, last_before = 0.0;
+    double found_mass = 0.0, last_mass = 0.0;
+    auto look = [&](int it, double t) {
+      const bool pos = t > 0.0, hit = pos && run + t > target && found < 0;
+      last_pos = pos ? it : last_pos;
+      last_before = pos ? run : last_before;
+      last_mass = pos ? t : last_mass;
+      found = hit ? it : found;
+      found_before = hit ? run : found_before;
+      found_mass = hit ? t : found_mass;
+      run += pos ? t : 0.0;
+    };
     for (int q = 0; q < per; q += 4) {
       if (per > 4) four(q);                          // (else they are at hand)
-#pragma unroll
-      for (int k = 0; k < 4; ++k) {
-        const int it = lane * per + q + k;
-        const bool pos = t[k] > 0.0;
-        const bool hit = pos && run + t[k] > target && found < 0;
-        last_pos = pos ? it : last_pos;
-        last_before = pos ? run : last_before;
-        found = hit ? it : found;
-        found_before = hit ? run : found_before;
-        run += pos ? t[k] : 0.0;
+      look(lane * per + q, t0);
+      if (per > 1) {
+        look(lane * per + q + 1, t1);
+        look(lane * per + q + 2, t2);
+        look(lane * per + q + 3, t3);
       }
     }
     // the first lane that saw the target passed, else the last one that holds an item with mass
@@ -784,8 +796,8 @@ __device__ __forceinline__ void row_locate(const RowWork<T>& w, const RowState& 
       return;
     }
     if (lane == src) { sh.item = item; sh.before = hit != 0 ? found_before : last_before; }
-    const double mass = sh.items[item];
-    if (same_in_wave(sh.n_corr == 0 || mass > sh.none)) return;
+    const double mass = lane_f64(hit != 0 ? found_mass : last_mass, src);
+    if (same_in_wave(!corrected || mass > none)) return;
     // so little: is it more than what rounding leaves where the corrections take an item's whole mass away?
     double e = 0.0;
     for (int i = lane; i < w.count; i += 64) e += sh.set_y[i] >= 0 && item_of(w, sh.set_y[i]) == item ? sh.set_e[i] : 0.0;
@@ -794,10 +806,9 @@ __device__ __forceinline__ void row_locate(const RowWork<T>& w, const RowState& 
   }
 }
 
-// The first four waves: the token, from what row_locate left (behind a barrier; the other waves have ended): every
-// thread takes one vector of the run.  `elem_corr`: LDS scratch of one double per element of a run (the terms'
-// table, which is not needed any more), set to zero by all threads since (row_clear).
-constexpr int kPickWaves = kRunVecs / 64;
+// All waves: the token, from what row_locate left (behind a barrier): every thread takes one 32-bit word of the run.  (Bound by the fp64
+// exponentials' issue: by four waves, a vector a thread, one on each SIMD, 1.25 us; so 0.5.)  `elem_corr`: LDS scratch of one double per
+// element of a run (the terms' table, which is not needed any more), set to zero by all threads since (row_clear).
 template <typename T> __device__ __forceinline__ void row_clear(double* elem_corr) {
   constexpr int kRun = kRunVecs * ElemTraits<T>::kPerVec;
 #pragma unroll
@@ -807,8 +818,8 @@ template <typename T>
 __device__ __forceinline__ int row_pick(const RowWork<T>& w, double* elem_corr, RowShared& sh) {
   constexpr int E = ElemTraits<T>::kPerVec;
   constexpr int kRun = kRunVecs * E;               // elements in a run
-  constexpr int kThreads = kPickWaves * 64;
-  static_assert(kThreads == kRunVecs, "a thread's share of a run is one vector");
+  constexpr int kOwn = kRun / kRowThreads;         // a thread's, in one word
+  static_assert(kOwn * ElemTraits<T>::kBytes == 4, "a thread's share of a run is one word");
   const int tid = threadIdx.x, lane = lane_id(), wave = wave_id();
   const RowSplit& rs = w.rs;
   const double smax = double(w.smax), target = sh.target, before = sh.before;
@@ -819,14 +830,13 @@ __device__ __forceinline__ int row_pick(const RowWork<T>& w, double* elem_corr, 
   const int e0 = item == 0 ? 0 : rs.head, e1 = item == 0 ? rs.head : rs.head + rs.tail;
   const int64_t first = edge ? edge_index<T>(rs, e0) : rs.head + int64_t(item - 1) * kRun;
   const int64_t end = edge ? first + (e1 - e0) : first + kRun;
-  const int64_t my_vec = int64_t(item - 1) * kRunVecs + tid;
-  const bool inside = !edge && my_vec < rs.nvec;
-  uint4 dv = neg_inf_vec<T>();
-  if (inside) dv = load_vec(&rs.body[my_vec]);     // travels while the corrections are laid out
-  const int n_corr = sh.n_corr;
-  for (int i = tid; i < n_corr; i += kThreads) {
-    const int y = sh.set_y[i];
-    if (y >= first && y < end) elem_corr[y - first] = sh.set_a[i];
+  const int64_t word = int64_t(item - 1) * (kRunVecs * 4) + tid;
+  const bool inside = !edge && word < rs.nvec * 4;
+  uint32_t bits = 0;
+  if (inside) bits = as_global(reinterpret_cast<const uint32_t*>(rs.body))[word];      // travels while the corrections are laid out
+  if (tid < sh.n_corr) {
+    const int y = sh.set_y[tid];
+    if (y >= first && y < end) elem_corr[y - first] = sh.set_a[tid];
   }
   __syncthreads();
   if (edge) {
@@ -836,46 +846,47 @@ __device__ __forceinline__ int row_pick(const RowWork<T>& w, double* elem_corr, 
         const int64_t y = edge_index<T>(rs, e);
         const double v = exp64(double(__fmul_rn(load_elem<T>(w.row, y), w.rT)) - smax) + elem_corr[e - e0];
         if (v > 0.0) {
-          sh.last = int(y);
+          sh.pick = int(y);
           run_e += v;
           if (run_e > target) break;
         }
       }
     }
     __syncthreads();
-    return sh.last;
+    return sh.pick;
   }
-  float t[E];
-  unpack<T>(dv, t);
-  double v[E], mine = 0.0;
+  double v[kOwn], mine = 0.0;
 #pragma unroll
-  for (int i = 0; i < E; ++i) {
-    v[i] = exp64(double(__fmul_rn(t[i], w.rT)) - smax) + elem_corr[tid * E + i];      // -inf gives exactly 0
+  for (int i = 0; i < kOwn; ++i) {
+    v[i] = exp64(double(__fmul_rn(dword_element<T>(bits, i), w.rT)) - smax) + elem_corr[tid * kOwn + i];      // -inf gives exactly 0
     v[i] = v[i] > 0.0 && inside ? v[i] : 0.0;
     mine += v[i];
   }
   const double inc = wave_incl_scan_f64(mine);
   if (lane == 63) sh.wave_sum[wave] = inc;
   __syncthreads();
-  double base = before;
+  // the wave in which the cumulative mass passes the target, else the last one with mass, finds the element: the first that passes it,
+  // else the last with mass
+  const double sum = lane < kRowWaves ? sh.wave_sum[lane & (kRowWaves - 1)] : 0.0;
+  const double upto = scan16_f64(sum);
+  const uint64_t passes = ballot(sum > 0.0 && before + upto > target), holds = ballot(sum > 0.0);
+  if (holds == 0) return -1;
+  const int by = passes != 0 ? __ffsll((long long)passes) - 1 : 63 - __clzll((long long)holds);
+  if (wave == by) {
+    double run_e = before + lane_f64(upto - sum, by) + (inc - mine);
+    int first_pass = -1, last_mass = -1;
 #pragma unroll
-  for (int k = 0; k < kPickWaves - 1; ++k) base += k < wave ? sh.wave_sum[k] : 0.0;
-  // the element at which the cumulative mass passes the target, else the last one with mass
-  int first_pass = 0x7FFFFFFF, last_mass = -1;
-  double run_e = base + (inc - mine);
-#pragma unroll
-  for (int i = 0; i < E; ++i) {
-    run_e += v[i];
-    last_mass = v[i] > 0.0 ? tid * E + i : last_mass;
-    first_pass = v[i] > 0.0 && run_e > target && first_pass == 0x7FFFFFFF ? tid * E + i : first_pass;
+    for (int i = 0; i < kOwn; ++i) {
+      run_e += v[i];
+      last_mass = v[i] > 0.0 ? tid * kOwn + i : last_mass;
+      first_pass = v[i] > 0.0 && run_e > target && first_pass < 0 ? tid * kOwn + i : first_pass;
+    }
+    // (elements ascend with the lane)
+    const uint64_t pass = ballot(first_pass >= 0), mass = ballot(last_mass >= 0);
+    if (pass != 0 ? lane == __ffsll((long long)pass) - 1 : lane == 63 - __clzll((long long)mass)) sh.pick = pass != 0 ? first_pass : last_mass;
   }
-  // (elements ascend with the lane: the first and the last lane that have one)
-  const uint64_t pass = ballot(first_pass != 0x7FFFFFFF), mass = ballot(last_mass >= 0);
-  if (pass != 0 && lane == __ffsll((long long)pass) - 1) atomicMin(&sh.pick, first_pass);
-  if (mass != 0 && lane == 63 - __clzll((long long)mass)) atomicMax(&sh.last, last_mass);
   __syncthreads();
-  const int pick = sh.pick != 0x7FFFFFFF ? sh.pick : sh.last;
-  return pick >= 0 ? int(first + pick) : -1;
+  return int(first + sh.pick);
 }
 
 }  // namespace tslt

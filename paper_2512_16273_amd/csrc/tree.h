@@ -220,7 +220,7 @@ __device__ __forceinline__ int tree_node(const TreeParams& p, int64_t b, int nod
       row_clear<T>(table);
       __syncthreads();
     }
-    if (wave_id() < kPickWaves) token = row_pick(w, table, sh);     // (nothing follows for the other waves)
+    token = row_pick(w, table, sh);
   }
   return state;
 }

@@ -214,7 +214,6 @@ __global__ __launch_bounds__(kRowThreads, kWavesPerSimd) void verify_resample_ke
       if (residual && rst.ok) left = row_test(w, rst, -1, 0, sh);
     }
     __syncthreads();
-    if (wave >= waves && wave >= kPickWaves) return;
     if (wave < waves && residual && rst.ok) row_set_mass(w, left * rst.zp, sh);
     __syncthreads();
     if (wave == 0) {
@@ -222,7 +221,6 @@ __global__ __launch_bounds__(kRowThreads, kWavesPerSimd) void verify_resample_ke
       if (lane == 0) { sh.cmd = rst.ok ? 1 : 0; sh.st = rst.st; }      // (another wave may still look at sh.flags)
     }
     __syncthreads();
-    if (wave >= kPickWaves) return;
     if (sh.cmd) token = row_pick(w, table, sh);
   } else {
     if (part != 0) return;
@@ -325,7 +323,6 @@ __global__ __launch_bounds__(kRowThreads, kWavesPerSimd) void verify_round_kerne
     if (!bonus && rst.ok) left = row_test(w, rst, x, 0, sh);
   }
   __syncthreads();
-  if (wave >= waves && wave >= kPickWaves) return;
   double corr = 0.0;
   if (wave < waves) {
     flag = rst.ok ? 0 : 2;
@@ -347,7 +344,6 @@ __global__ __launch_bounds__(kRowThreads, kWavesPerSimd) void verify_round_kerne
     if (lane_id() == 0) sh.cmd = flag;
   }
   __syncthreads();
-  if (wave >= kPickWaves) return;
   const int token = sh.cmd == 0 && p.draws ? row_pick(w, table, sh) : -1;
   if (threadIdx.x == 0 && !bonus) {
     if (p.out_ratio) p.out_ratio[r] = ratio;
