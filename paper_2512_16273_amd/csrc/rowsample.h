@@ -581,30 +581,36 @@ __device__ __forceinline__ bool row_shared(RowWork<T>& w, double* table, int par
 }
 
 constexpr int64_t kShareRows = 128;                  // at most, by two workgroups or more
-constexpr int64_t kShareLeastV = 50000;              // of any type
+constexpr int64_t kShareLeastV = 40000;              // of any type
 constexpr int64_t kShareWords = 512;                 // words that the workgroups of all shared rows leave, at most
-// Workgroups that share each of `rows` rows (1: none do): as many as fill the chip, a run for every wave at least.  A launch
-// more (two microseconds, the terms' table made by every part) against the sweep of a row by one compute unit, so rows from the
-// length on where that is some 6 us (BitTerms' terms are the cheapest, and binary16 has twice fp32's in a run).  us a round by
-// one workgroup a row / shared, 1 x 4 and 8 x 8: fp32 50000 15.8 / 14.8 and 16.4 / 16.0, 64000 17.2 / 15.2 and 18.2 / 17.1, 96000
-// 20.6 / 15.2 and 21.7 / 18.8; binary16 60000 18.5 / 17.8 and 19.2 / 18.6, 96000 21.8 / 17.4 and 22.5 / 18.9; bfloat16 100000
-// 17.7 / 17.1 and 18.1 / 18.1, 128256 19.0 / 17.0 and 19.8 / 18.5, 200000 23.2 / 16.9 and 23.6 / 20.5.  The sampled rows of larger
-// batches alone: 48 x 5 fp32 96000 36.9 / 32.8, binary16 by its bit table 152064 46.0 / 42.2 (40 x 7).
-// By two workgroups a row (more than a third as many rows as compute units) fp32 and bfloat16 later; 16 x 7, trees 8 x <2,2,2> and
-// the sampled rows of 128 x 4: fp32 60000 18.4 / 18.8, 21.6 / 21.8 and 37.5 / 39.3, 76000 20.6 / 20.6, 24.0 / 23.8 and 44.5 / 45.1, 84000
-// 22.0 / 21.0 and 49.4 / 48.8 (16 x 7, 128 x 4); bfloat16 125000 19.8 / 20.0, 23.0 / 23.4 and 41.3 / 42.1, 155000 21.1 / 20.6, 24.4 / 24.2
-// and 48.1 / 48.3; binary16 56000 18.7 / 18.0, 21.2 / 21.2 and 29.1 / 29.5, 60000 19.1 / 18.1, 22.4 / 21.4 and 30.4 / 30.2, 72000 (a part
-// is a few runs more than its waves) 20.1 / 20.1, 23.3 / 23.4 and 33.1 / 33.7, 78000 21.6 / 20.2, 24.6 / 23.7 and 35.6 / 35.3; by its bit
-// table 128 x 2 147456 40.8 / 40.6, 160000 42.8 / 42.3.
-template <typename T, typename Terms> inline int64_t share_min_V(bool by_two) {
-  if (ElemTraits<T>::kBytes == 4) return by_two ? 76000 : kShareLeastV;
-  if (Terms::kBits) return by_two && !kLargeTable<Terms> ? 150000 : 100000;
-  return 60000;
+// Workgroups that share each of `rows` rows (1: none do): as many as fill the chip, with eight runs each at least (a wave alone on its
+// SIMD is done with a run in a third of the time that four of them take; fp32 and BitTerms, whose runs cost less: sixteen where eight
+// would make more workgroups than half the chip).  Two trips to memory and the terms' table made by every part (some 2 us) against the
+// sweep of a row by one compute unit, so rows from the length on where that is more: BitTerms' terms are the cheapest, and
+// binary16 has twice fp32's in a run.  us a call by one workgroup a row / shared, chains 1 x 4, 4 x 4, 8 x 8 and two trees <2,2,2>, sets of 256:
+//   binary16  32000 12.9 / 13.3, 13.0 / 14.1, 13.4 / 14.4, 15.9 / 16.6;  44000 14.7 / 13.7, 15.2 / 14.3, 15.2 / 14.9, 18.0 / 16.7
+//   fp32      32000 12.9 / 12.4, 13.3 / 13.2, 13.5 / 14.4, 15.7 / 15.2;  44000 14.1 / 12.8, 14.8 / 13.5, 14.9 / 14.8, 16.9 / 15.4
+//   bfloat16  44000 12.0 / 13.4, 12.5 / 13.6, 12.6 / 14.4, 15.1 / 15.8;  64000 13.1 / 12.6, 13.6 / 13.7, 13.6 / 14.9, 16.4 / 15.8;
+//             90000 13.6 / 12.6, 14.7 / 14.1, 14.8 / 15.2, 17.9 / 16.2
+// By sixteen runs a part / eight: binary16 64000 15.0 / 13.2, 16.3 / 14.0, 16.5 / 15.8; fp32 64000 13.3 / 12.6, 14.1 / 14.5, 90000 (4 x 4)
+// 14.7 / 15.6, bfloat16 200000 15.7 / 16.3.  By two workgroups a row (more than a third as many rows as compute units) later, with a launch between them: fp32 60000 18.4 / 18.8,
+// 76000 20.6 / 20.6, 84000 22.0 / 21.0; bfloat16 125000 19.8 / 20.0, 155000 21.1 / 20.6; binary16 56000 18.7 / 18.0; the sampled rows of 128 x 4
+// fp32 76000 44.5 / 45.1, 84000 49.4 / 48.8; by binary16's bit table 128 x 2 147456 40.8 / 40.6.
+template <typename T, typename Terms> inline int64_t share_min_V(int64_t rows) {
+  const int64_t cus = compute_units();
+  const bool by_two = 3 * rows > cus;
+  if (ElemTraits<T>::kBytes == 4) return by_two ? 76000 : (4 * rows > cus ? 50000 : kShareLeastV);
+  if (kLargeTable<Terms>) return 100000;
+  if (Terms::kBits) return by_two ? 150000 : (8 * rows > cus ? 100000 : 64000);
+  return by_two ? 60000 : kShareLeastV;
 }
 template <typename T, typename Terms> inline int row_parts(int64_t V, int64_t rows) {
-  if (rows > kShareRows || V < share_min_V<T, Terms>(3 * rows > compute_units())) return 1;
+  if (rows > kShareRows || V < share_min_V<T, Terms>(rows)) return 1;
+  const int64_t cus = std::min<int64_t>(compute_units(), kShareWords);
   const int64_t runs = V / (ElemTraits<T>::kPerVec * kRunVecs) + 1;
-  return int(std::max<int64_t>(1, std::min<int64_t>(std::min<int64_t>(compute_units(), kShareWords) / rows, (runs + kRowWaves - 1) / kRowWaves)));
+  int64_t parts = (runs + 7) / 8;
+  if ((ElemTraits<T>::kBytes == 4 || Terms::kBits) && 2 * rows * parts > cus) parts = (runs + kRowWaves - 1) / kRowWaves;
+  return int(std::max<int64_t>(1, std::min(cus / rows, std::min<int64_t>(parts, 64))));
 }
 
 // The waves that hold entries, each for itself: normaliser, and what p and q_hat at the set are made with.  A row that holds NaN
