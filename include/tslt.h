@@ -78,7 +78,8 @@ enum {
   TSLT_OP_SAMPLE = 1,
   TSLT_OP_VERIFY = 2,
   TSLT_OP_VERIFY_TREE = 3,      /* tslt_verify_tree with node outputs: every node is evaluated */
-  TSLT_OP_VERIFY_TREE_PATH = 4  /* tslt_verify_tree without node outputs: only the verified path is sampled */
+  TSLT_OP_VERIFY_TREE_PATH = 4, /* tslt_verify_tree without node outputs: only the verified path is sampled */
+  TSLT_OP_TRUNCATE_SHARED = 5   /* tslt_truncate, tslt_truncate_sample: workspace that they can do without, see there */
 };
 
 #define TSLT_MAX_K_CAP 1024   /* largest width of a sparse set */
@@ -121,7 +122,9 @@ size_t tslt_workspace_bytes(int op, int64_t n_outer, int64_t n_inner, int64_t V,
  *   out_mass    [rows] fp32 rho-mass of the kept set, sum_{kept} q (sigma of Theorem 1 = 1 - mass);
  *               may be NULL
  *   status      [rows] int32 TSLT_ROW_* bits (written, not accumulated); may be NULL
- * Workspace: none (ws may be NULL).
+ * Workspace: none is needed (ws may be NULL).  With tslt_workspace_bytes(TSLT_OP_TRUNCATE_SHARED, rows, 0, V, k_cap) bytes,
+ * 256-byte aligned, the rows of a small batch of long rows are shared by several workgroups each; that size is 0 where
+ * they never are.  Same sets; the normaliser's fp32 terms are added up in another order.
  */
 int tslt_truncate(const void* logits, tslt_dtype dt, int64_t rows, int64_t V, int64_t row_stride,
                   float temperature, int32_t top_k, float top_p, int32_t k_cap, tslt_dtype payload,

@@ -24,6 +24,7 @@
 #include "common.h"
 #include "wire.h"
 #include "exp64.h"
+#include "handover.h"
 
 namespace tslt {
 
@@ -74,7 +75,17 @@ struct TruncateParams {
   int n_samples;
   int32_t* out_token;
   int32_t* out_slot;
+  // rows shared by workgroups (handover.h)
+  int parts;                 // of a row
+  uint64_t* part_words;      // [rows, parts]
+  uint64_t* part_found;      // [rows, parts, 2 + sort_cap]: the sum of its terms, the number of its candidates, those
+  Tag tag;
 };
+// Memory for them: a word and a region of candidates for each workgroup.
+constexpr int kTruncMaxParts = 4;
+inline size_t truncate_part_bytes(int64_t rows, int64_t parts, int sort_cap) {
+  return size_t(rows) * size_t(parts) * (8 + 8 * (2 + size_t(sort_cap))) + 256;
+}
 
 // Dynamic LDS: [ rings ] [ candidates ].  The ring space is reused for the sort's table and its scratch records behind it
 // and, before the pass, for the per-thread sample maxima.
@@ -495,7 +506,10 @@ template <> struct HitTest<F16> {
   }
 };
 
-template <typename T, int NT, int kStages, int kWavesPerSimd>
+// kParts: p.parts workgroups share a row.  Each makes the same sample and the same threshold, walks its part of the stages
+// (with the sample tiles that lie there) and leaves the sum of its terms and its candidates in memory; the one that finds those of
+// all goes on as if it had found them itself.
+template <typename T, int NT, int kStages, int kWavesPerSimd, bool kParts = false>
 __global__ __launch_bounds__(NT, kWavesPerSimd) void truncate_kernel(const TruncateParams p) {
   constexpr int E = ElemTraits<T>::kPerVec;
   constexpr int NW = NT / 64;
@@ -514,7 +528,9 @@ __global__ __launch_bounds__(NT, kWavesPerSimd) void truncate_kernel(const Trunc
   const int tid = threadIdx.x;
   const int lane = lane_id();
   const int wave = wave_id();
-  const int64_t row_i = blockIdx.x;
+  const uint32_t row_u = kParts ? blockIdx.x / uint32_t(p.parts) : blockIdx.x;
+  const int part = kParts ? int(blockIdx.x - row_u * p.parts) : 0;
+  const int64_t row_i = row_u;
   const void* row = reinterpret_cast<const char*>(p.logits) + size_t(row_i) * size_t(p.row_stride) * ElemTraits<T>::kBytes;
   const RowSplit rs = split_row<T>(row, p.V);
   const int n_edge = rs.head + rs.tail;
@@ -562,14 +578,20 @@ __global__ __launch_bounds__(NT, kWavesPerSimd) void truncate_kernel(const Trunc
     static_assert(kGroup == 2, "a stage is a pair of tiles");
     uint4 pipe[kStages][kGroup];
     const uint32_t tile0 = long_row ? 0u : uint32_t(kBatch);                    // of the first stage
-    const uint32_t n_stage = n_tiles > tile0 ? (n_tiles - tile0 + kGroup - 1) / kGroup : 0u;
+    const uint32_t all_stages = n_tiles > tile0 ? (n_tiles - tile0 + kGroup - 1) / kGroup : 0u;
     const uint32_t stride_g = s_stride / kGroup;
+    // this workgroup's stages (kParts: rows long enough that each has some)
+    const uint32_t per_part = kParts ? (all_stages + uint32_t(p.parts) - 1) / uint32_t(p.parts) : 0u;
+    const uint32_t first_g = kParts ? min(per_part * uint32_t(part), all_stages) : 0u;
+    const uint32_t n_stage = kParts ? min(first_g + per_part, all_stages) : all_stages;
     // The row as a buffer: no vector instruction goes into addresses; what lies past the row's end comes back as zeros.  Not
     // in the wide shape, where other workgroups fill the vector units in any case and requests through a buffer are slower
     // (us by buffer / by address: 500 rows of 151936, sets of 200 to 256, bfloat16 37.2 / 35.0, binary16 35.5 / 33.9; 450 fp32 rows,
     // sets of 32, 51.0 / 48.5; 2728 254.9 / 253.0; the deep shape, 1000 fp32 rows of 151936, sets of 1024, 114.8 / 116.5).
     constexpr bool kBuffer = kWavesPerSimd < kWavesWide;
-    const __amdgpu_buffer_rsrc_t body = row_buffer(rs.body, nvec);
+    // (A part's buffer ends where the part does: what its last requests ahead reach is the next workgroup's.)
+    const uint32_t end_vec = kParts && (tile0 + n_stage * kGroup) * NT < nvec ? (tile0 + n_stage * kGroup) * NT : nvec;
+    const __amdgpu_buffer_rsrc_t body = row_buffer(rs.body, end_vec);
     const uint32_t lane_bytes = uint32_t(tid) * 16u;
     auto request = [&](uint32_t at) -> uint4 {          // of a tile that begins `at` bytes into the row's body
       if constexpr (kBuffer) return buffer_load_vec_stream(body, lane_bytes, at);
@@ -578,8 +600,15 @@ __global__ __launch_bounds__(NT, kWavesPerSimd) void truncate_kernel(const Trunc
     };
     // stages 0, stride_g, 2 stride_g, 3 stride_g begin with a sample tile
     constexpr uint32_t kNever = 0xFFFFFFFFu;
-    uint32_t skip_g = long_row ? 0u : kNever, issue_at = tile0 * (NT * 16u);
     auto next_sample = [&](uint32_t g) { return g == (kBatch - 1) * stride_g ? kNever : g + stride_g; };
+    uint32_t first_sample = long_row ? 0u : kNever;                  // the first stage from first_g on that begins with one
+    if constexpr (kParts) {
+#pragma unroll
+      for (int u = 1; u < kBatch; ++u)
+        if (first_sample < first_g) first_sample = u * stride_g;
+      if (first_sample < first_g || !long_row) first_sample = kNever;
+    }
+    uint32_t skip_g = first_sample, issue_at = (tile0 + first_g * kGroup) * (NT * 16u);
     // (called with g = 0, 1, 2, ...: its scalar instructions count where a pair of fp32 vectors has eight logits)
     auto issue = [&](uint32_t g, uint4 (&q)[kGroup]) {
       // the first tile of a sample stage is in registers already: its slot repeats the second tile's load
@@ -597,9 +626,9 @@ __global__ __launch_bounds__(NT, kWavesPerSimd) void truncate_kernel(const Trunc
     const bool early = kTall || long_row;
     auto issue_first = [&]() {
 #pragma unroll
-      for (int s = 0; s < kStages; ++s) issue(uint32_t(s), pipe[s]);
+      for (int s = 0; s < kStages; ++s) issue(first_g + uint32_t(s), pipe[s]);
     };
-    if (n_stage > 0 && early) issue_first();
+    if (n_stage > first_g && early) issue_first();
     float tmax = -INFINITY;
 #pragma unroll
     for (int u = 0; u < kBatch; ++u) {
@@ -721,6 +750,7 @@ __global__ __launch_bounds__(NT, kWavesPerSimd) void truncate_kernel(const Trunc
     c_ref = __fmul_rn(smax, p.k2);
     __syncthreads();                                  // the maxima are read; the space becomes the rings
 
+    if (kParts && !fast_ok && part != 0) return;      // (the same for all of them)
     if (fast_ok) {
       // ---- the pass -------------------------------------------------------------------------
       // (The two operands that every term's fma shares stand in vector registers, without a sign to change: from a scalar
@@ -807,7 +837,13 @@ __global__ __launch_bounds__(NT, kWavesPerSimd) void truncate_kernel(const Trunc
 
       if (n_stage > 0 && !early) issue_first();
       // the sample tiles, already in registers
-      {
+      if constexpr (kParts) {
+#pragma unroll
+        for (int u = 0; u < kBatch; ++u) {
+          const uint32_t g = u * stride_g;
+          if (long_row ? g >= first_g && g < n_stage : part == 0) dacc += double(process_second(d[u], u * s_stride * NT + tid));
+        }
+      } else {
         const uint32_t t1 = s_stride;
         float both = 0.0f;
 #pragma unroll 1
@@ -818,9 +854,10 @@ __global__ __launch_bounds__(NT, kWavesPerSimd) void truncate_kernel(const Trunc
         }
         dacc += double(both);
       }
-      uint32_t seen_g = long_row ? 0u : kNever;
+      uint32_t seen_g = first_sample;
       // stages before this one are complete
-      const uint32_t ragged_g = nvec / NT > tile0 ? (nvec / NT - tile0) / kGroup : 0u;
+      uint32_t ragged_g = nvec / NT > tile0 ? (nvec / NT - tile0) / kGroup : 0u;
+      if (kParts && n_stage < ragged_g) ragged_g = n_stage;
       // (a short row's stages go to the fp64 total one by one where 256 threads take it)
       const bool apart = !kTall && !long_row;
       static_assert(kStages % 2 == 0, "the fp32 sums of two stages are added up before they go to the fp64 total");
@@ -829,7 +866,7 @@ __global__ __launch_bounds__(NT, kWavesPerSimd) void truncate_kernel(const Trunc
         if (seen) seen_g = next_sample(g);
         return seen;
       };
-      uint32_t g0 = 0;
+      uint32_t g0 = first_g;
       for (; g0 + kStages <= ragged_g; g0 += kStages) {
         float two = 0.0f;
 #pragma unroll
@@ -837,7 +874,7 @@ __global__ __launch_bounds__(NT, kWavesPerSimd) void truncate_kernel(const Trunc
           const uint32_t g = g0 + s;
           const uint32_t v0 = (tile0 + g * kGroup) * NT + tid;
           // (their distance is a multiple of kUnit tiles)
-          const bool seen = s % (kUnit / kGroup) == 0 && sample_stage(g);
+          const bool seen = (kParts || s % (kUnit / kGroup) == 0) && sample_stage(g);
           const float ps = seen ? process_second(pipe[s][1], v0 + NT) : process_pair(pipe[s][0], pipe[s][1], v0, v0 + NT);
           two = (s & 1) && !apart ? two + ps : ps;
           if ((s & 1) || apart) dacc += double(two);
@@ -862,7 +899,7 @@ __global__ __launch_bounds__(NT, kWavesPerSimd) void truncate_kernel(const Trunc
       expand();
       if (lost && lane == 0) sh.overflow = 1;
       // edge elements (row not 16-byte aligned, or V not a whole number of vectors)
-      if (tid < n_edge) {
+      if (tid < n_edge && part == 0) {
         const int64_t edge_i = edge_index<T>(rs, tid);
         const float edge_v = load_elem<T>(row, edge_i);
         dacc += double(fast_exp2(__builtin_fmaf(edge_v, k2, neg_c)));
@@ -877,6 +914,44 @@ __global__ __launch_bounds__(NT, kWavesPerSimd) void truncate_kernel(const Trunc
 #pragma unroll
       for (int w = 0; w < NW; ++w) z_c += sh.red.d[w];
       n_cand = sh.cand_count;
+      if constexpr (kParts) {
+        uint64_t* found = p.part_found + (size_t(row_i) * p.parts) * (2 + p.sort_cap);
+        {
+          uint64_t* mine = found + size_t(part) * (2 + p.sort_cap);
+          const int n = n_cand < p.sort_cap ? n_cand : p.sort_cap;
+          for (int i = tid; i < n; i += NT) store_through(&mine[2 + i], cand[i]);
+          if (tid == 0) {
+            store_through(&mine[0], uint64_t(__double_as_longlong(z_c)));
+            store_through(&mine[1], uint64_t(n_cand));
+          }
+        }
+        if (!all_arrived(p.part_words + size_t(row_i) * p.parts, part, p.parts, p.tag, sh.bcast_i[0])) return;
+        // (a part's first candidates are asked for with its numbers, the others behind them)
+        z_c = 0.0;
+        n_cand = 0;
+        uint64_t sum[kTruncMaxParts], count[kTruncMaxParts], rec[kTruncMaxParts];
+#pragma unroll
+        for (int k = 0; k < kTruncMaxParts; ++k) {
+          if (k >= p.parts) break;
+          const uint64_t* from = found + size_t(k) * (2 + p.sort_cap);
+          sum[k] = load_through(&from[0]);
+          count[k] = load_through(&from[1]);
+          rec[k] = load_through(&from[2 + tid]);       // (sort_cap is more than NT)
+        }
+#pragma unroll
+        for (int k = 0; k < kTruncMaxParts; ++k) {
+          if (k >= p.parts) break;
+          const uint64_t* from = found + size_t(k) * (2 + p.sort_cap);
+          const int n = int(count[k]);
+          z_c += __longlong_as_double((long long)sum[k]);
+          if (n_cand + n <= p.sort_cap) {              // (more than that do not fit: the row is redone)
+            if (tid < n) cand[n_cand + tid] = rec[k];
+            for (int i = NT + tid; i < n; i += NT) cand[n_cand + i] = load_through(&from[2 + i]);
+          }
+          n_cand += n;
+        }
+        __syncthreads();
+      }
       fast_ok = !sh.overflow && n_cand <= p.sort_cap && n_cand >= p.k_sel && z_c > 0.0 && z_c < INFINITY;
     }
   }

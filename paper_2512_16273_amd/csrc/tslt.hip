@@ -112,15 +112,28 @@ hipError_t scratch_on_current_device(void** out) {
 constexpr int kLargeLds = int(kMaxLds - 4096);
 
 // One shape of the truncation kernel (see truncate.h): NT threads to a row.
-template <typename T, int NT, int kStages, int kWavesPerSimd>
+template <typename T, int NT, int kStages, int kWavesPerSimd, bool kParts = false>
 hipError_t launch_truncate_shape(const tslt::TruncateParams& p, size_t lds, hipStream_t s) {
-  constexpr auto fn = &tslt::truncate_kernel<T, NT, kStages, kWavesPerSimd>;
+  constexpr auto fn = &tslt::truncate_kernel<T, NT, kStages, kWavesPerSimd, kParts>;
   if (lds + sizeof(tslt::TruncateShared) > 48 * 1024) {
     const hipError_t e = tslt::allow_dynamic_lds<fn>(kLargeLds);
     if (e != hipSuccess) return e;
   }
-  hipLaunchKernelGGL(fn, dim3(unsigned(p.rows)), dim3(NT), lds, s, p);
+  hipLaunchKernelGGL(fn, dim3(unsigned(kParts ? p.rows * p.parts : p.rows)), dim3(NT), lds, s, p);
   return hipSuccess;
+}
+// Workgroups that share each row of a small batch (1: none do): four where that makes no more of them than compute units, else
+// two, for rows long enough that the walk saved is worth two trips to memory (some 3 us).  us by one workgroup a row / two / four,
+// 1, 32, 64 and 128 rows, sets of 256: bfloat16 64000 12.2 / 12.4 / 12.6, 14.0 / 14.6 / 14.2, 14.0 / 14.6 / 14.6, 14.3 / 15.3 / 18.1;
+// 90000 14.4 / 13.8 / 13.2, 15.4 / 15.5 / 14.9, 15.6 / 15.7 / 15.7, 16.0 / 16.6; 128256 16.8 / 15.2 / 14.0, 17.6 / 16.4 / 15.3,
+// 17.9 / 16.7 / 16.1, 18.2 / 17.5 / 20.5; 256000 23.4 / 18.6 / 15.9, 24.4 / 19.8 / 17.2, 24.8 / 20.2 / 18.3, 25.1 / 22.3 / 25.0; fp32
+// 64000 14.2 / 14.1 / 13.4, 15.3 / 15.1 / 14.6, 15.6 / 15.4 / 15.4, 16.1 / 16.7; 90000 (128 rows) 18.8 / 18.7; 128256 19.1 / 16.6 / 14.9,
+// 20.1 / 17.6 / 16.0, 20.4 / 18.1 / 17.4, 21.8 / 21.4.  (Eight: 16 rows of half a megabyte 2 % faster than four, the others slower.)
+int truncate_parts(tslt_dtype dt, int64_t V, int64_t rows) {
+  const int64_t cus = tslt::compute_units(), kb = V * elem_bytes(dt) >> 10;
+  if (4 * rows <= cus && kb >= (8 * rows <= cus ? 170 : 220)) return 4;
+  if (2 * rows <= cus && kb >= (dt == TSLT_F32 ? 350 : 240)) return 2;
+  return 1;
 }
 // Whether a row's vectors with an element above the threshold come so thinly that a ring of kRingSmall slots, expanded
 // beyond kRingExpand, loses one less than once in a million rows.
@@ -143,17 +156,36 @@ bool tall_rows(tslt_dtype dt, int64_t V, int64_t rows) {
   if (rows <= cus) return V >= 10240;
   return 2 * rows <= 3 * cus && kb >= 160 && kb < 700;
 }
+// What a call whose rows are shared has to be given, whatever is selected (a smaller selection has fewer candidates).
+size_t truncate_share_bytes(tslt_dtype dt, int64_t rows, int64_t V, int32_t k_cap) {
+  const int parts = truncate_parts(dt, V, rows);
+  if (parts == 1 || k_cap < 1 || k_cap > TSLT_MAX_K_CAP) return 0;
+  tslt::TruncateParams p{};
+  p.k_sel = k_cap;
+  plan_truncate(dt, V, tslt::kTallThreads, p);
+  return p.jprime > 0 ? tslt::truncate_part_bytes(rows, parts, p.sort_cap) : 0;
+}
 // The shapes of the truncation kernel (see truncate.h): 512 threads for such rows, but not where a row may be redone under
 // 256 threads because its large logits are many (sets of more than a few per cent of the row: its status tells, and does
 // not depend on the batch.  A row whose large logits are crowded together may still lose ring slots under 256 threads
 // alone, and say so).  Else 256: eight workgroups of this footprint on a compute unit, the wide shape; else the deep one.
-template <typename T> hipError_t launch_truncate(tslt_dtype dt, tslt::TruncateParams& p, hipStream_t s) {
+template <typename T> hipError_t launch_truncate(tslt_dtype dt, tslt::TruncateParams& p, void* ws, size_t ws_bytes, hipStream_t s) {
   constexpr int NT = tslt::kTruncThreads, TT = tslt::kTallThreads;
   const size_t lds = plan_truncate(dt, p.V, NT, p);
   if (tall_rows(dt, p.V, p.rows) && p.jprime > 0 && sparse_hits(dt, p.V, NT, p)) {
     tslt::TruncateParams tall = p;
     const size_t tall_lds = plan_truncate(dt, p.V, TT, tall);
-    if (tall.jprime > 0) return launch_truncate_shape<T, TT, tslt::kStagesDeep, tslt::kWavesDeep>(tall, tall_lds, s);
+    if (tall.jprime > 0) {
+      tall.parts = truncate_parts(dt, p.V, p.rows);
+      if (tall.parts > 1 && ws != nullptr && reinterpret_cast<uintptr_t>(ws) % 256 == 0 &&
+          ws_bytes >= tslt::truncate_part_bytes(p.rows, tall.parts, tall.sort_cap)) {
+        tall.part_words = reinterpret_cast<uint64_t*>(ws);
+        tall.part_found = tall.part_words + p.rows * tall.parts;
+        tall.tag = tslt::next_tag();
+        return launch_truncate_shape<T, TT, tslt::kStagesDeep, tslt::kWavesDeep, true>(tall, tall_lds, s);
+      }
+      return launch_truncate_shape<T, TT, tslt::kStagesDeep, tslt::kWavesDeep>(tall, tall_lds, s);
+    }
   }
   if (8 * (lds + sizeof(tslt::TruncateShared) + 256) <= kMaxLds)
     return launch_truncate_shape<T, NT, tslt::kStagesWide, tslt::kWavesWide>(p, lds, s);
@@ -173,6 +205,9 @@ size_t tslt_workspace_bytes(int op, int64_t n_outer, int64_t n_inner, int64_t V,
   switch (op) {
     case TSLT_OP_VERIFY:
       return tslt::verify_workspace_bytes(n_outer, n_inner, V, k_cap);
+    case TSLT_OP_TRUNCATE_SHARED:
+      return std::max({truncate_share_bytes(TSLT_F32, n_outer, V, k_cap), truncate_share_bytes(TSLT_BF16, n_outer, V, k_cap),
+                       truncate_share_bytes(TSLT_F16, n_outer, V, k_cap)});
     case TSLT_OP_VERIFY_TREE:
       return n_inner > 0 ? tslt::tree_workspace_bytes(n_outer, n_inner, V, true) : 0;
     case TSLT_OP_VERIFY_TREE_PATH:
@@ -212,8 +247,8 @@ static int truncate_impl(const void* logits, tslt_dtype dt, int64_t rows, int64_
   p.u = u; p.n_samples = n_samples; p.without_replacement = without_replacement ? 1 : 0;
   p.out_token = out_token; p.out_slot = out_slot;
   hipStream_t s = reinterpret_cast<hipStream_t>(stream);
-  hipError_t e = dt == TSLT_BF16 ? launch_truncate<tslt::Bf16>(dt, p, s)
-                 : dt == TSLT_F16 ? launch_truncate<tslt::F16>(dt, p, s) : launch_truncate<float>(dt, p, s);
+  hipError_t e = dt == TSLT_BF16 ? launch_truncate<tslt::Bf16>(dt, p, ws, ws_bytes, s)
+                 : dt == TSLT_F16 ? launch_truncate<tslt::F16>(dt, p, ws, ws_bytes, s) : launch_truncate<float>(dt, p, ws, ws_bytes, s);
   if (e != hipSuccess) return hip_fail(e, "hipFuncSetAttribute");
   if ((e = hipGetLastError()) != hipSuccess) return hip_fail(e, "tslt_truncate launch");
   return TSLT_OK;

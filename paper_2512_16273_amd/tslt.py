@@ -8,6 +8,7 @@ fallback: if the library is missing, or a tensor is not on a GPU, the call raise
 from __future__ import annotations
 
 import ctypes
+import functools
 import os
 from typing import Optional, Sequence
 
@@ -17,7 +18,7 @@ _HERE = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(_HERE, "libtslt.so")
 
 F32, BF16, F16 = 0, 1, 2
-OP_TRUNCATE, OP_SAMPLE, OP_VERIFY, OP_VERIFY_TREE, OP_VERIFY_TREE_PATH = 0, 1, 2, 3, 4
+OP_TRUNCATE, OP_SAMPLE, OP_VERIFY, OP_VERIFY_TREE, OP_VERIFY_TREE_PATH, OP_TRUNCATE_SHARED = 0, 1, 2, 3, 4, 5
 ROW_NONFINITE, ROW_EMPTY, ROW_TOKEN_NOT_IN_SET, ROW_BAD_SET, ROW_EXACT_PATH = 1, 2, 4, 8, 256
 MAX_K_CAP = 1024
 PAYLOAD = {"f32": 0, "bf16": 1, "f16": 2}       # tslt_dtype codes of the formats a payload can travel in
@@ -150,6 +151,11 @@ def _workspace(nbytes: int, device) -> Optional[torch.Tensor]:
     return torch.empty(nbytes, dtype=torch.uint8, device=device)   # torch aligns to >= 256 bytes
 
 
+@functools.lru_cache(maxsize=256)
+def _truncate_workspace_bytes(rows: int, V: int, k_cap: int) -> int:
+    return workspace_bytes(OP_TRUNCATE_SHARED, rows, 0, V, k_cap)
+
+
 def truncate(logits: torch.Tensor, temperature: float, top_k: int, top_p: float, k_cap: int,
              want_prob: bool = True, out: Optional[dict] = None, u: Optional[torch.Tensor] = None,
              payload: str = "f32", without_replacement: bool = False) -> dict:
@@ -170,10 +176,14 @@ def truncate(logits: torch.Tensor, temperature: float, top_k: int, top_p: float,
             "mass": torch.empty(rows, dtype=torch.float32, device=dev),
             "status": torch.empty(rows, dtype=torch.int32, device=dev),
         }
+    # (a few long rows: memory in which the workgroups that share each of them hand over what they have found)
+    ws_bytes = _truncate_workspace_bytes(rows, V, int(k_cap)) if 0 < rows <= 128 else 0
+    held = torch.empty(ws_bytes, dtype=torch.uint8, device=dev) if ws_bytes else None
+    ws = _ptr(held)
     if u is None:
         _check(lib.tslt_truncate(_ptr(logits), _dtype_code(logits), rows, V, stride, float(temperature), int(top_k),
                                  float(top_p), int(k_cap), PAYLOAD[payload], _ptr(out["idx"]), _ptr(out["logit"]), _ptr(out.get("prob")),
-                                 _ptr(out["count"]), _ptr(out.get("mass")), _ptr(out.get("status")), None, 0, _stream()))
+                                 _ptr(out["count"]), _ptr(out.get("mass")), _ptr(out.get("status")), ws, ws_bytes, _stream()))
         return out
     _dev(u, torch.float32, "u")
     u2 = u.reshape(rows, -1)
@@ -186,7 +196,7 @@ def truncate(logits: torch.Tensor, temperature: float, top_k: int, top_p: float,
                                     _ptr(out.get("prob")), _ptr(out["count"]), _ptr(out.get("mass")),
                                     _ptr(out.get("status")), _ptr(u2), n, 1 if without_replacement else 0,
                                     _ptr(out["token"]), _ptr(out.get("slot")),
-                                    None, 0, _stream()))
+                                    ws, ws_bytes, _stream()))
     return out
 
 

@@ -189,3 +189,59 @@ def test_shared_rows_captured(tslt):
             graph.replay()
             torch.cuda.synchronize()
             same(eager[i], out_s)
+
+
+@pytest.mark.parametrize("dtype,V,rows,K,top_p,stride_pad", [
+    ("bf16", 128256, 64, 256, 0.9, 0), ("bf16", 122880, 128, 64, 0.0, 0), ("f16", 223105, 3, 1024, 0.99, 7), ("f16", 90001, 31, 320, 0.0, 1),
+    ("f32", 89601, 100, 32, 0.95, 3), ("f32", 151936, 1, 512, 0.0, 0), ("f32", 100003, 32, 1, 0.0, 0), ("bf16", 255999, 127, 100, 0.95, 1),
+    ("f16", 87047, 2, 16, 0.9, 5), ("f32", 56325, 33, 700, 0.0, 0),      # from an odd start, the last stage half empty
+])
+def test_drafts_of_shared_rows(tslt, monkeypatch, dtype, V, rows, K, top_p, stride_pad):
+    """A row's workgroups make the same threshold and so find the same candidates: sets, counts, draws and status are those of
+    one workgroup, bit for bit; the normaliser is added up in another order (fp32 terms, sums of a vector to the fp64 total: 1e-6)."""
+    dt = {"f32": torch.float32, "bf16": torch.bfloat16, "f16": torch.float16}[dtype]
+    assert tslt.workspace_bytes(tslt.OP_TRUNCATE_SHARED, rows, 0, V, K) > 0
+    g = torch.Generator(device=DEV).manual_seed(11)
+    z = torch.randn(rows, V + stride_pad, generator=g, device=DEV).mul_(2.5)
+    z -= torch.rand(rows, V + stride_pad, generator=g, device=DEV).mul_(V).add_(1.0).log_()
+    z = z.to(dt)[:, :V] if stride_pad else z.to(dt)
+    u = torch.rand(rows, 2, generator=g, device=DEV)
+    for broken in (False, True):
+        if broken:                                 # NaN, shifted, nearly empty, empty, masked, +inf, ties all over
+            for i in range(min(rows, 6)):
+                odd_row(z[i], i)
+            if rows > 7:
+                z[6] = 0.5
+                z[7, V // 2:] = 3.0
+        shared = tslt.truncate(z, 0.8, 0, top_p, K, u=u, payload="bf16", without_replacement=True)
+        with monkeypatch.context() as m:
+            m.setattr(tslt, "_truncate_workspace_bytes", lambda *a: 0)
+            alone = tslt.truncate(z, 0.8, 0, top_p, K, u=u, payload="bf16", without_replacement=True)
+        torch.cuda.synchronize()
+        for k in ("idx", "count", "status", "token", "slot", "logit"):
+            assert torch.equal(shared[k], alone[k]), (k, broken)
+        for k in ("prob", "mass"):
+            assert torch.allclose(shared[k], alone[k], rtol=1e-6, atol=0.0, equal_nan=True), (k, broken)
+
+
+def test_shared_drafts_captured(tslt):
+    rows, V, K = 8, 128256, 64
+    g = torch.Generator(device=DEV).manual_seed(3)
+    z = [torch.randn(rows, V, generator=g, device=DEV).mul_(3.0).half() for _ in range(3)]
+    u = torch.rand(rows, 1, generator=g, device=DEV)
+    call = lambda t, out=None: tslt.truncate(t, 1.0, K, 0.0, K, u=u, out=out)  # noqa: E731
+    eager = [{k: v.clone() for k, v in call(t).items()} for t in z]
+    static = z[0].clone()
+    out = call(static)
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        call(static, out)
+    for rep in range(6):
+        static.copy_(z[rep % 3])
+        for v in out.values():
+            v.zero_()
+        call(z[(rep + 1) % 3])                     # the program's own eager work between the replays
+        graph.replay()
+        torch.cuda.synchronize()
+        same(eager[rep % 3], out)
