@@ -190,10 +190,11 @@ __global__ __launch_bounds__(kRowThreads, kWavesPerSimd) void verify_resample_ke
   // the decision at that position, from the lane that holds it (a position beyond the first 64 is read again)
   const bool unusable = residual && (jstar < 64 ? __shfl(f0, jstar, 64) : fl_b[jstar]) == 2;
   const int64_t r = b * p.gamma + (residual ? jstar : 0);
-  // what the end needs is requested now and travels during the sweep
-  const int j_lane = lane < p.gamma ? lane : p.gamma - 1;
-  const int st_first = p.row_status[b * p.gamma + j_lane], x_first = p.draft_tokens[b * p.gamma + j_lane];
   const float u_res = p.u_resample[b * (p.gamma + 1) + jstar];
+  // (what the end needs is requested behind the sweep, whose registers are short, and travels during the search)
+  const int j_lane = lane < p.gamma ? lane : p.gamma - 1;
+  int st_first, x_first;
+  auto request_end = [&]() { st_first = p.row_status[b * p.gamma + j_lane]; x_first = p.draft_tokens[b * p.gamma + j_lane]; };
   RowWork<T> w;
   int token = -1;
   if (tid == 0) sh.cmd = 0;                    // read behind a barrier: 1 when there is something to draw from
@@ -205,6 +206,7 @@ __global__ __launch_bounds__(kRowThreads, kWavesPerSimd) void verify_resample_ke
     } else {
       row_sweep<T, Terms, kWavesPerSimd == kAlone, kLoads>(w, table, 1, sh);
     }
+    request_end();
     row_clear<T>(table);
     const int waves = row_set_waves(w), wave = __builtin_amdgcn_readfirstlane(wave_id());
     RowState rst;
@@ -224,6 +226,7 @@ __global__ __launch_bounds__(kRowThreads, kWavesPerSimd) void verify_resample_ke
     if (sh.cmd) token = row_pick(w, table, sh);
   } else {
     if (part != 0) return;
+    request_end();
     if (tid == 0) sh.st = 0;
     __syncthreads();
   }
