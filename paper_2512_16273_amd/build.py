@@ -1,13 +1,17 @@
-"""Builds the C-ABI library `libtslt.so` for gfx950 with hipcc (cross-compiles without a GPU)."""
+"""Builds the C-ABI library `libtslt.so` for gfx950 with hipcc (cross-compiles without a GPU), and `_binding.so`, the fast
+path of the Python binding, with the host compiler against torch's headers."""
 from __future__ import annotations
 
 import os
 import subprocess
 import sys
+import sysconfig
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
 LIB_PATH = os.path.join(HERE, "libtslt.so")
+BINDING_PATH = os.path.join(HERE, "_binding.so")
+BINDING_SOURCE = os.path.join(HERE, "csrc", "binding.cpp")
 SOURCES = [os.path.join(HERE, "csrc", "tslt.hip")]
 HEADERS = [os.path.join(HERE, "csrc", n) for n in ("common.h", "handover.h", "truncate.h", "sample.h", "verify.h", "rowops.h", "rowsample.h", "exp64.h", "tree.h", "wire.h", "stats.h", "calib.h")] + \
           [os.path.join(ROOT, "include", "tslt.h")]
@@ -27,19 +31,28 @@ def hipcc_command(out: str = LIB_PATH) -> list:
             "-o", out] + SOURCES
 
 
+def binding_command(out: str = BINDING_PATH) -> list:
+    import torch
+    base = os.path.dirname(torch.__file__)
+    return [os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-shared",
+            f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}",
+            "-I", os.path.join(ROOT, "include"), "-isystem", os.path.join(base, "include"),
+            "-isystem", os.path.join(base, "include", "torch", "csrc", "api", "include"), "-isystem", sysconfig.get_paths()["include"],
+            "-o", out, BINDING_SOURCE, "-L", os.path.join(base, "lib"), "-ltorch_python", "-ltorch_cpu", "-lc10"]
+
+
 def build_library(verbose: bool = True) -> str:
-    cmd = hipcc_command()
-    if verbose:
-        print(" ".join(cmd), flush=True)
-    subprocess.run(cmd, check=True)
+    for cmd in (hipcc_command(), binding_command()):
+        if verbose:
+            print(" ".join(cmd), flush=True)
+        subprocess.run(cmd, check=True)
     return LIB_PATH
 
 
 def is_stale() -> bool:
-    if not os.path.exists(LIB_PATH):
-        return True
-    t = os.path.getmtime(LIB_PATH)
-    return any(os.path.exists(s) and os.path.getmtime(s) > t for s in SOURCES + HEADERS)
+    def older(out, sources):
+        return not os.path.exists(out) or any(os.path.exists(s) and os.path.getmtime(s) > os.path.getmtime(out) for s in sources)
+    return older(LIB_PATH, SOURCES + HEADERS) or older(BINDING_PATH, [BINDING_SOURCE, HEADERS[-1]])
 
 
 if __name__ == "__main__":

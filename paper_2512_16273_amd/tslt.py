@@ -4,6 +4,10 @@ Every function takes torch tensors that live on the GPU, allocates the outputs a
 with torch (device memory and streams are torch's job here, nothing else), passes raw device
 pointers and the current HIP stream to the library and returns the output tensors.  There is no
 fallback: if the library is missing, or a tensor is not on a GPU, the call raises.
+
+The calls of a serving loop (with the caller's outputs and workspace; pack and unpack) go through `_binding`
+(csrc/binding.cpp), which makes the same checks natively; where one does not hold it returns None and the
+function here goes through them one by one and says which.
 """
 from __future__ import annotations
 
@@ -29,6 +33,7 @@ EXPORTS = ("tslt_version", "tslt_last_error", "tslt_workspace_bytes", "tslt_trun
            "tslt_verify_static", "tslt_truncation_stats", "tslt_multicandidate_stats", "tslt_calibrate_read", "tslt_verify_tree")
 
 _lib = None
+_fast = None                                    # the module _binding, bound to the library that is loaded
 
 
 class TsltError(RuntimeError):
@@ -37,7 +42,7 @@ class TsltError(RuntimeError):
 
 def load(path: Optional[str] = None):
     """Open the library; raises if it has not been built (python -m paper_2512_16273_amd.build)."""
-    global _lib
+    global _lib, _fast
     if _lib is not None and path is None:
         return _lib
     path = path or os.environ.get("TSLT_LIBRARY") or LIB_PATH      # TSLT_LIBRARY: another build of the same ABI
@@ -84,6 +89,14 @@ def load(path: Optional[str] = None):
     lib.tslt_verify_tree.restype = c.c_int
     lib.tslt_verify_tree.argtypes = [vp, c.c_int, i64, i64, i64, f32, i32, c.POINTER(i32), vp, vp, vp, i32, vp, vp,
                                      vp, i32, vp, vp, vp, vp, vp, vp, vp, vp, sz, vp]
+    try:
+        from . import _binding
+    except ImportError as e:
+        raise TsltError(f"_binding.so: {e}; build it with `python -m paper_2512_16273_amd.build`") from e
+    _binding.bind(*[c.cast(getattr(lib, fn), vp).value for fn in (
+        "tslt_workspace_bytes", "tslt_truncate_sample", "tslt_verify", "tslt_verify_accept", "tslt_verify_resample", "tslt_verify_tree",
+        "tslt_pack_bound_words", "tslt_pack_cleared", "tslt_unpack")])
+    _fast = _binding
     _lib = lib
     return lib
 
@@ -115,10 +128,7 @@ def _dev(t: torch.Tensor, dtype=None, name="tensor", contiguous=True) -> torch.T
     return t
 
 
-# (Pointers and streams go to ctypes as plain integers, without a c_void_p for each of the twenty arguments of a call:
-# pack and unpack 23.4 -> 18.2 us, bound by the host.  A tensor that is as wanted passes after one
-# test, one that has been seen is asked for its pointer at once, and the workspace's size is worked out only where no
-# workspace is given: 2048 rows packed and unpacked 18.1 -> 17.7 us.)
+# (Pointers and streams go to ctypes as plain integers, without a c_void_p for each of the twenty arguments of a call.)
 def _ptr(t: Optional[torch.Tensor]) -> Optional[int]:
     return None if t is None else t.data_ptr()
 
@@ -164,6 +174,13 @@ def truncate(logits: torch.Tensor, temperature: float, top_k: int, top_p: float,
     [rows, n], n draws from each row's q_hat (i.i.d., or without replacement).  payload = "bf16" / "f16" rounds the kept values to the
     format in which they will travel before q_hat and the draws are computed."""
     lib = load()
+    if out is not None and u is not None and logits.is_cuda:
+        code = _fast.truncate(logits, float(temperature), int(top_k), float(top_p), int(k_cap), PAYLOAD[payload], without_replacement,
+                              out, u, _stream())
+        if code is not None:
+            if code:
+                _check(code)
+            return out
     _dev(logits, name="logits", contiguous=False)
     rows, V, stride = _rows_2d(logits)
     dev = logits.device
@@ -203,6 +220,12 @@ def truncate(logits: torch.Tensor, temperature: float, top_k: int, top_p: float,
 def pack(idx: torch.Tensor, logit: torch.Tensor, count: torch.Tensor, V: int, payload: str) -> dict:
     """tslt_pack: truncated sets [rows, k_cap] -> words (uint32, as int32 storage), row_offset [rows + 1] int64."""
     lib = load()
+    if idx.is_cuda:
+        made = _fast.pack(idx, logit, count, int(V), PAYLOAD[payload], _stream())
+        if made is not None:
+            if made[0]:
+                _check(made[0])
+            return made[1]
     _dev(idx, torch.int32, "idx"); _dev(logit, torch.float32, "logit"); _dev(count, torch.int32, "count")
     rows, k_cap = idx.shape
     cap = int(lib.tslt_pack_bound_words(rows, k_cap, V))
@@ -217,6 +240,12 @@ def pack(idx: torch.Tensor, logit: torch.Tensor, count: torch.Tensor, V: int, pa
 def unpack(words: torch.Tensor, row_offset: torch.Tensor, rows: int, k_cap: int, V: int, payload: str) -> dict:
     """tslt_unpack: the inverse of pack -> idx, logit [rows, k_cap], count [rows]."""
     lib = load()
+    if words.is_cuda:
+        made = _fast.unpack(words, row_offset, rows, k_cap, int(V), PAYLOAD[payload], _stream())
+        if made is not None:
+            if made[0]:
+                _check(made[0])
+            return made[1]
     _dev(words, torch.int32, "words"); _dev(row_offset, torch.int64, "row_offset")
     dev = words.device
     out = {"idx": torch.empty(rows, k_cap, dtype=torch.int32, device=dev),
@@ -244,6 +273,9 @@ def sample(idx: torch.Tensor, logit: torch.Tensor, count: torch.Tensor, u: torch
     return out
 
 
+_PHASES = {"both": 0, "accept": 1, "resample": 2}
+
+
 def verify(target: torch.Tensor, temperature: float, q_idx: torch.Tensor, q_logit: torch.Tensor,
            q_count: torch.Tensor, draft_tokens: torch.Tensor, u_accept: torch.Tensor, u_resample: torch.Tensor,
            out: Optional[dict] = None, workspace: Optional[torch.Tensor] = None, phase: str = "both",
@@ -253,6 +285,13 @@ def verify(target: torch.Tensor, temperature: float, q_idx: torch.Tensor, q_logi
     tslt_verify_accept / tslt_verify_resample (then `out` and `workspace` must be passed to both).
     first_stage > 0 calls tslt_verify_staged / tslt_verify_accept_staged."""
     lib = load()
+    if out is not None and workspace is not None and not first_stage and target.is_cuda:
+        code = _fast.verify(_PHASES[phase], target, float(temperature), q_idx, q_logit, q_count, draft_tokens, u_accept, u_resample, out,
+                            workspace, _stream())
+        if code is not None:
+            if code:
+                _check(code)
+            return out
     fn = {"both": lib.tslt_verify, "accept": lib.tslt_verify_accept, "resample": lib.tslt_verify_resample}[phase]
     extra = ()
     if first_stage and phase != "resample":
@@ -377,6 +416,13 @@ def verify_tree(target: torch.Tensor, temperature: float, expansion: Sequence[in
     [B, N_nodes] (when all_nodes), ratio and beta [B, N_nodes-1], status [B].  without_replacement selects the rule
     for candidates that were drawn without replacement."""
     lib = load()
+    if out is not None and workspace is not None and target.is_cuda:
+        code = _fast.verify_tree(target, float(temperature), expansion, q_idx, q_logit, q_count, cand_tokens, u_accept, u_resample,
+                                 without_replacement, out, workspace, _stream())
+        if code is not None:
+            if code:
+                _check(code)
+            return out
     _dev(target, name="target")
     if target.dim() != 3:
         raise TsltError("target must be [B, N_nodes, V]")
