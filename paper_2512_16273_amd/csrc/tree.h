@@ -586,7 +586,9 @@ template <typename T, typename Terms> hipError_t launch_verify_tree_with(TreePar
     const int64_t rows = p.B * p.n_eval;
     const bool alone = rows <= compute_units();
     p.parts = rows <= p.items_rows ? row_parts<T, Terms>(p.V, rows) : 1;
-    if (p.n_eval_layers <= p.depth || p.n_nodes > kHandNodes) p.words = nullptr;
+    // (handing over keeps a workgroup a microsecond longer: of many times what the chip holds at once, more than the launch that it saves.
+    // 117 trees <4,4,4> of fp32 rows of 17296, 9945 rows, 220 us by a second launch, 239 so; 14 such trees of bfloat16 9083 37.4 / 34.3.)
+    if (p.n_eval_layers <= p.depth || p.n_nodes > kHandNodes || rows > 4 * compute_units()) p.words = nullptr;
     p.tag = next_tag();
     hipLaunchKernelGGL((p.parts > 1 ? tree_node_kernel<T, Terms, kAlone, true> : alone ? tree_node_kernel<T, Terms, kAlone> : tree_node_kernel<T, Terms, kShared>),
                        dim3(unsigned(rows * p.parts)), dim3(kRowThreads), Terms::kBytes, s, p);
