@@ -386,35 +386,44 @@ template <int kBins> __device__ __forceinline__ int value_bin(uint64_t c, float 
   const int b = int((cand_value(c) - vmin) * scale);
   return b > kBins - 1 ? kBins - 1 : (b < 0 ? 0 : b);
 }
-template <int NT>
+// kRange: the bins divide [lo, hi] instead, whatever lies outside in the first and the last of them, and `bins` has been set to zero:
+// the step that looks for the extremes, a third of the whole, and its barrier fall away.  (False where that makes a bin too
+// crowded; nothing has been moved then.)
+template <int NT, bool kRange = false>
 __device__ __forceinline__ bool bucket_sort_desc(const uint64_t* in, int n, uint64_t* tmp, int tmp_cap, uint64_t* out,
-                                                 int k_keep, uint32_t* bins, BlockScratch& red) {
+                                                 int k_keep, uint32_t* bins, BlockScratch& red, float lo = 0.0f, float hi = 0.0f) {
   constexpr int NW = NT / 64;
   static_assert(NW + 2 <= 16, "room in the scratch");
   if (n <= 0) return true;
   const int tid = threadIdx.x;
-  uint32_t kmin = 0xFFFFFFFFu, kmax = 0u;
-  const uint32_t* key = reinterpret_cast<const uint32_t*>(in) + 1;      // the high word of a record
+  float vmin = lo, span = hi - lo;                       // may overflow to +inf: then one bin
+  if constexpr (!kRange) {
+    uint32_t kmin = 0xFFFFFFFFu, kmax = 0u;
+    const uint32_t* key = reinterpret_cast<const uint32_t*>(in) + 1;      // the high word of a record
 #pragma unroll 4
-  for (int i = tid; i < n; i += NT) {
-    const uint32_t k = key[2 * i];
-    kmin = k < kmin ? k : kmin;
-    kmax = k > kmax ? k : kmax;
-  }
-  kmax = wave_max_u32(kmax);
-  kmin = ~wave_max_u32(~kmin);
-  bins[tid] = 0;
-  if (lane_id() == 0) { red.i[wave_id()] = int(kmin); red.f[wave_id()] = as_f32(kmax); }
-  __syncthreads();
-  kmin = uint32_t(red.i[0]); kmax = as_u32(red.f[0]);
+    for (int i = tid; i < n; i += NT) {
+      const uint32_t k = key[2 * i];
+      kmin = k < kmin ? k : kmin;
+      kmax = k > kmax ? k : kmax;
+    }
+    kmax = wave_max_u32(kmax);
+    kmin = ~wave_max_u32(~kmin);
+    bins[tid] = 0;
+    if (lane_id() == 0) { red.i[wave_id()] = int(kmin); red.f[wave_id()] = as_f32(kmax); }
+    __syncthreads();
+    kmin = uint32_t(red.i[0]); kmax = as_u32(red.f[0]);
 #pragma unroll
-  for (int w = 1; w < NW; ++w) {
-    kmin = uint32_t(red.i[w]) < kmin ? uint32_t(red.i[w]) : kmin;
-    kmax = as_u32(red.f[w]) > kmax ? as_u32(red.f[w]) : kmax;
+    for (int w = 1; w < NW; ++w) {
+      kmin = uint32_t(red.i[w]) < kmin ? uint32_t(red.i[w]) : kmin;
+      kmax = as_u32(red.f[w]) > kmax ? as_u32(red.f[w]) : kmax;
+    }
+    vmin = key_to_f32(kmin);
+    span = key_to_f32(kmax) - vmin;
   }
-  const float vmin = key_to_f32(kmin);
-  const float span = key_to_f32(kmax) - vmin;            // may overflow to +inf: then one bin
   const float scale = (span > 0.0f && span < 3.0e38f) ? float(NT - 1) / span : 0.0f;
+  if constexpr (kRange) {
+    if (scale == 0.0f) return false;
+  }
   for (int i = tid; i < n; i += NT) atomicAdd(&bins[value_bin<NT>(in[i], vmin, scale)], 1u);
   __syncthreads();
   // where each bin begins, in descending order; the one that holds place k_keep (the last, if there are fewer records)
@@ -455,6 +464,28 @@ __device__ __forceinline__ bool bucket_sort_desc(const uint64_t* in, int n, uint
   }
   __syncthreads();
   return true;
+}
+
+// The same for a few records, a quarter of the workgroup's threads at most: four lanes count the larger ones for each.  out is
+// another array; behind a barrier on both sides.
+template <int NT>
+__device__ __forceinline__ void rank_sort_desc(const uint64_t* in, int n, uint64_t* out, int k_keep) {
+  const int c = threadIdx.x >> 2, q = threadIdx.x & 3;
+  if (__builtin_amdgcn_readfirstlane(wave_id() * 16) < n) {      // whole waves
+    const uint64_t mine = in[c < n ? c : n - 1];
+    int r = 0;
+    for (int j = q; j < n; j += 16) {
+      uint64_t t[4];
+#pragma unroll
+      for (int u = 0; u < 4; ++u) t[u] = in[j + 4 * u < n ? j + 4 * u : n - 1];
+#pragma unroll
+      for (int u = 0; u < 4; ++u) r += t[u] > mine && j + 4 * u < n ? 1 : 0;
+    }
+    r += dpp_i32<0xB1>(0, r);                                    // quad_perm 1 0 3 2, then 2 3 0 1
+    r += dpp_i32<0x4E>(0, r);
+    if (q == 0 && c < n && r < k_keep) out[r] = mine;
+  }
+  __syncthreads();
 }
 
 // How a row of V elements splits into a 16-byte aligned body of whole vectors plus at most

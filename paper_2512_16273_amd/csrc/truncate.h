@@ -97,7 +97,10 @@ inline int truncate_ring_bytes(int n_waves, int k_sel) {
   const int rings = n_waves * (kRingSmall * 20), sort = (kTablesBytes + 8 * truncate_sort_scratch(k_sel) + 15) & ~15;
   return rings > sort ? rings : sort;                                            // per ring slot a vector and its index
 }
-inline size_t truncate_lds_bytes(int ring_bytes, int sort_cap) { return size_t(ring_bytes) + size_t(8) * sort_cap; }
+// (512 threads: the sort's bins behind them, which are cleared before the rings are needed)
+inline size_t truncate_lds_bytes(int ring_bytes, int sort_cap, int nt) {
+  return size_t(ring_bytes) + size_t(8) * sort_cap + (nt > kTruncThreads ? size_t(4) * nt : 0);
+}
 
 struct TruncateShared {
   BlockScratch red;
@@ -549,7 +552,9 @@ __global__ __launch_bounds__(NT, kWavesPerSimd) void truncate_kernel(const Trunc
 
   int st = 0;
   int n_cand = 0;
-  float c_ref = 0.0f;
+  float c_ref = 0.0f, from = 0.0f, upto = 0.0f;        // (the last two: the threshold, the sample's maximum)
+  uint32_t* bins = reinterpret_cast<uint32_t*>(cand + p.sort_cap);
+  if constexpr (kTall) bins[tid] = 0;
   double z_c = 0.0;
   bool fast_ok = p.jprime > 0 && n_tiles > 0;
   if (tid == 0) { sh.cand_count = 0; sh.overflow = 0; }
@@ -747,6 +752,8 @@ __global__ __launch_bounds__(NT, kWavesPerSimd) void truncate_kernel(const Trunc
     const float smax = key_to_f32(top_key);
     const float tau0 = tau_key <= kKeyNegInf ? -INFINITY : key_to_f32(tau_key);
     fast_ok = smax > -INFINITY && smax < INFINITY;   // false for NaN too
+    from = tau0;
+    upto = smax;
     c_ref = __fmul_rn(smax, p.k2);
     __syncthreads();                                  // the maxima are read; the space becomes the rings
 
@@ -969,7 +976,22 @@ __global__ __launch_bounds__(NT, kWavesPerSimd) void truncate_kernel(const Trunc
 
   // ---- sort the candidates into canonical order ------------------------------------------------
   // (behind a barrier since the candidates were written; what the sort writes first is not what was read since)
-  for (;;) {
+  // 512 threads, out of the pass: few candidates are counted directly; of many the bins lie between the threshold and the sample's
+  // maximum, beyond which there are few more than the sample has been thinned.  us of a kernel's sort: 2.1 by its extremes, 1.5 so; 130
+  // candidates 0.6.
+  const uint64_t* sorted = cand;
+  bool done = false;
+  if constexpr (kTall) {
+    if (fast_ok && n_cand <= NT / 4) {
+      rank_sort_desc<NT>(cand, n_cand, sort_tmp, p.k_sel);
+      sorted = sort_tmp;
+      done = true;
+    } else if (fast_ok) {
+      done = bucket_sort_desc<NT, true>(cand, n_cand, sort_tmp, sort_tmp_cap, cand, p.k_sel, bins, sh.red, from, upto);
+      if (!done) __syncthreads();
+    }
+  }
+  while (!done) {
     if (n_cand < 0) n_cand = exact_select<T, NT>(row, p.V, p.k_sel, p.k2, cand, tables, sh, c_ref, z_c, st);
     if (bucket_sort_desc<NT>(cand, n_cand, sort_tmp, sort_tmp_cap, cand, p.k_sel, tables, sh.red)) break;
     // the bin at the k-th place is too crowded for the scratch space (a row full of ties): radix selection
@@ -991,7 +1013,7 @@ __global__ __launch_bounds__(NT, kWavesPerSimd) void truncate_kernel(const Trunc
   double local = 0.0, head32 = 0.0;
   float v0 = 0.0f, m_s = 0.0f;
   if (k_eff > 0) {
-    v0 = cand_value(cand[0]);
+    v0 = cand_value(sorted[0]);
     m_s = __fmul_rn(v0, p.rT);
   }
 #pragma unroll
@@ -999,7 +1021,7 @@ __global__ __launch_bounds__(NT, kWavesPerSimd) void truncate_kernel(const Trunc
     e64[r] = 0.0; s32[r] = 0.0f; idx[r] = 0;
     const int i = tid * per + r;
     if (r < per && i < k_eff) {
-      const uint64_t c = cand[i];
+      const uint64_t c = sorted[i];
       const float v = cand_value(c);
       idx[r] = cand_index(c);
       s32[r] = __fmul_rn(v, p.rT);

@@ -80,12 +80,12 @@ size_t plan_truncate(tslt_dtype dt, int64_t V, int nt, tslt::TruncateParams& p) 
     const double j_eff = -G * std::log(1.0 - double(jprime) / G);
     int sort_cap = int((j_eff + 5.0 * std::sqrt(j_eff) + 4.0) / f) + 16;   // mean + 5 sigma of the hits
     if (sort_cap < min_cap) sort_cap = min_cap;
-    if (tslt::truncate_lds_bytes(p.ring_bytes, sort_cap) + sizeof(tslt::TruncateShared) + 256 <= kMaxLds) {
+    if (tslt::truncate_lds_bytes(p.ring_bytes, sort_cap, nt) + sizeof(tslt::TruncateShared) + 256 <= kMaxLds) {
       p.jprime = jprime;
       p.sort_cap = sort_cap;
     }
   }
-  return tslt::truncate_lds_bytes(p.ring_bytes, p.sort_cap);
+  return tslt::truncate_lds_bytes(p.ring_bytes, p.sort_cap, nt);
 }
 
 // Device address of `scratch` on the current device, looked up once per device.
