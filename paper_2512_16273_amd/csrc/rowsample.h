@@ -14,6 +14,7 @@
 #include "common.h"
 #include "exp64.h"
 #include "handover.h"
+#include "pow_table.h"
 #include "rowops.h"
 
 namespace tslt {
@@ -154,17 +155,19 @@ __device__ __forceinline__ float max3_nan(float a, float b, float c) {      // v
   return __builtin_elementwise_maximum(__builtin_elementwise_maximum(a, b), c);
 }
 
-// How a sweep makes its terms.  build() fills the LDS table (all `threads` threads of the workgroup, the caller
-// synchronises; `half` as for build_exp_table); run_sum() gives the sum over a wave's run, of which every lane
+// How a sweep makes its terms.  begin() asks for what comes from memory and finish() fills the LDS table (all threads of the
+// workgroup, the caller synchronises; `half` as for build_exp_table, where a table is made in two); run_sum() gives the sum over a wave's run, of which every lane
 // holds kSegVecs vectors (vector i is vector vbase + 64 i of the row and counts if that is below nvec), and
 // raises flags: 1 = NaN or +inf among the elements, 2 = the row has to be swept by its maxima (which finds NaN
 // and +inf for itself), 4 = so it has if the row turns out to hold nothing above the range's lower end.
 template <typename T> struct BitTerms {
+  using Walked = BitTerms<T>;
   static constexpr bool kBits = true;
   static constexpr size_t kBytes = ExpTab<T>::kBytes;
-  static __device__ __forceinline__ void build(double* table, float rT, int threads, int half = -1) {
-    build_exp_table<T>(table, rT, threads, half);
-  }
+  struct Early {};
+  static __device__ __forceinline__ Early begin() { return {}; }
+  static __device__ __forceinline__ void first_half(double* table, float rT) { build_exp_table<T>(table, rT, kRowThreads, 0); }
+  static __device__ __forceinline__ void finish(double* table, Early, float rT, int half) { build_exp_table<T>(table, rT, kRowThreads, half); }
   // (the four vectors' look-ups go out together and one look at their total says whether a value was outside
   // the table)
   static __device__ __forceinline__ double run_sum(const uint4 (&q)[kSegVecs], uint32_t vbase, uint32_t nvec,
@@ -184,13 +187,27 @@ template <typename T> struct BitTerms {
     return wave_sum_f64(acc);
   }
 };
-template <typename T> struct PowTerms {
+template <typename T, bool kCopied = true> struct PowTerms {
+  using Walked = PowTerms<T, false>;      // for kernels that go from row to row
   static constexpr bool kBits = false;
   static constexpr size_t kBytes = size_t(kPowEntries) * sizeof(uint64_t);
-  static __device__ __forceinline__ void build(double* table, float, int threads, int half = -1) {
-    uint64_t* t = reinterpret_cast<uint64_t*>(table);
-    const int lo = half == 1 ? kPowEntries / 2 : 0, hi = half == 0 ? kPowEntries / 2 : kPowEntries;
-    for (int i = lo + threadIdx.x; i < hi; i += threads) t[i] = pow_entry(i);
+  // (Copied: made by each workgroup for itself, two entries a thread, the table took 1.0 us of a round's kernel and a fifth of the vector
+  // instructions of a row of 20000.)
+  // Not where a kernel goes from row to row, with the table made once: 64 binary16 trees <2,2,2> of 32000, the path, 38.5 us made, 39.5 copied.
+  struct Early { uint4 two; };
+  static_assert(kPowEntries == 2 * kRowThreads, "two entries a thread");
+  static __device__ __forceinline__ Early begin() {
+    if constexpr (kCopied) return {load_vec(reinterpret_cast<const uint4*>(kPowTable) + threadIdx.x)};
+    return {};
+  }
+  static __device__ __forceinline__ void first_half(double*, float) {}
+  static __device__ __forceinline__ void finish(double* table, const Early& e, float, int) {
+    if constexpr (kCopied) {
+      reinterpret_cast<uint4*>(table)[threadIdx.x] = e.two;
+    } else {
+      uint64_t* t = reinterpret_cast<uint64_t*>(table);
+      for (int i = threadIdx.x; i < kPowEntries; i += kRowThreads) t[i] = pow_entry(i);
+    }
   }
   // A term is made of max(s, -690), so that masked elements (-inf) need no branch: what they and other far ones
   // add, 2e-300 each, is nothing beside any s >= -kTabMaxS.  A run without such an s counts as 0.
@@ -422,8 +439,10 @@ __device__ __forceinline__ void row_pass(RowWork<T>& w, double* table, int half,
     };
     uint4 d[kSegVecs], dn[kSegVecs];
     int cur = run0 + wave;
+    typename Terms::Early early;
+    if (half > -2) early = Terms::begin();             // (before the row: loads are waited for in order)
     request(cur, d);
-    if (half > -2) Terms::build(table, rT, kRowThreads, half);
+    if (half > -2) Terms::finish(table, early, rT, half);
     __syncthreads();                    // the table is complete
     // Behind the first run the set entry's target logit is requested, whose index has arrived by then.  kOneCopy: that run is
     // not apart, so that the code of a run (PowTerms of 16-bit rows: 700 instructions) is there once; a second copy, first met by the few
@@ -460,7 +479,7 @@ __device__ __forceinline__ void row_pass(RowWork<T>& w, double* table, int half,
       } while (cur < run1);
     }
   } else {
-    if (half > -2) Terms::build(table, rT, kRowThreads, half);      // (the next row of a walk may have runs)
+    if (half > -2) Terms::finish(table, Terms::begin(), rT, half);      // (the next row of a walk may have runs)
     __syncthreads();
     row_gather(w);
   }

@@ -609,9 +609,9 @@ template <typename T, typename Terms> hipError_t launch_verify_tree_with(TreePar
       p.parts = p.B <= p.items_rows ? int(std::max<int64_t>(1, std::min<int64_t>(std::min<int64_t>(compute_units(), kShareWords) / p.B, (runs + kRowWaves - 1) / kRowWaves))) : 1;
       auto last_rows = [&](auto loads) -> hipError_t {
         constexpr int kLoads = decltype(loads)::value;
-        if (p.parts == 1) return walk(tree_path_kernel<T, Terms, kFromQuick, kLoads>);
+        if (p.parts == 1) return walk(tree_path_kernel<T, typename Terms::Walked, kFromQuick, kLoads>);
         p.tag = next_tag();
-        hipLaunchKernelGGL((tree_path_kernel<T, Terms, kFromQuick, kLoads, true>), dim3(unsigned(p.B * p.parts)), dim3(kRowThreads), Terms::kBytes, s, p);
+        hipLaunchKernelGGL((tree_path_kernel<T, typename Terms::Walked, kFromQuick, kLoads, true>), dim3(unsigned(p.B * p.parts)), dim3(kRowThreads), Terms::kBytes, s, p);
         return hipGetLastError();
       };
       if constexpr (ElemTraits<T>::kBytes == 4) {
@@ -622,11 +622,11 @@ template <typename T, typename Terms> hipError_t launch_verify_tree_with(TreePar
   }
   if (p.n_eval == 0) {
     if constexpr (ElemTraits<T>::kBytes == 4) {
-      if (p.V < kByAddressV) return walk(tree_path_kernel<T, Terms, kFromRoot, kByAddress>);
+      if (p.V < kByAddressV) return walk(tree_path_kernel<T, typename Terms::Walked, kFromRoot, kByAddress>);
     }
-    return walk(tree_path_kernel<T, Terms, kFromRoot>);
+    return walk(tree_path_kernel<T, typename Terms::Walked, kFromRoot>);
   }
-  if (p.n_eval_layers <= p.depth) return walk(tree_path_kernel<T, Terms, kFromHead>);
+  if (p.n_eval_layers <= p.depth) return walk(tree_path_kernel<T, typename Terms::Walked, kFromHead>);
   const int threads = std::min(1024, (p.n_eval + 63) / 64 * 64);
   hipLaunchKernelGGL(tree_walk_kernel, dim3(unsigned(p.B)), dim3(threads), 3 * p.n_eval <= kWalkNodes ? 12 * p.n_eval : 0, s, p);
   return hipGetLastError();

@@ -179,7 +179,7 @@ __global__ __launch_bounds__(kRowThreads, kWavesPerSimd) void verify_resample_ke
   // accepted): the words are few and nothing has to be handed round.
   const int32_t* fl_b = p.flags + b * p.gamma;
   const int f0 = lane < p.gamma ? fl_b[lane] : 1;
-  if constexpr (!kParts) Terms::build(table, p.rT, kRowThreads, 0);
+  if constexpr (!kParts) Terms::first_half(table, p.rT);
   int j0 = f0 != 1 ? lane : p.gamma;
   if (p.gamma > 64 && ballot(f0 != 1) == 0) {
     for (int j = lane + 64; j < p.gamma; j += 64)
