@@ -106,6 +106,7 @@ struct TruncateShared {
   BlockScratch red;
   int cand_count;
   int overflow;
+  float from, upto;      // the threshold, the sample's maximum
   int bcast_i[4];
   double bcast_d[2];
 };
@@ -552,9 +553,8 @@ __global__ __launch_bounds__(NT, kWavesPerSimd) void truncate_kernel(const Trunc
 
   int st = 0;
   int n_cand = 0;
-  float c_ref = 0.0f, from = 0.0f, upto = 0.0f;        // (the last two: the threshold, the sample's maximum)
-  uint32_t* bins = reinterpret_cast<uint32_t*>(cand + p.sort_cap);
-  if constexpr (kTall) bins[tid] = 0;
+  float c_ref = 0.0f;
+  if constexpr (kTall) reinterpret_cast<uint32_t*>(cand + p.sort_cap)[tid] = 0;
   double z_c = 0.0;
   bool fast_ok = p.jprime > 0 && n_tiles > 0;
   if (tid == 0) { sh.cand_count = 0; sh.overflow = 0; }
@@ -752,8 +752,7 @@ __global__ __launch_bounds__(NT, kWavesPerSimd) void truncate_kernel(const Trunc
     const float smax = key_to_f32(top_key);
     const float tau0 = tau_key <= kKeyNegInf ? -INFINITY : key_to_f32(tau_key);
     fast_ok = smax > -INFINITY && smax < INFINITY;   // false for NaN too
-    from = tau0;
-    upto = smax;
+    if (tid == 0) { sh.from = tau0; sh.upto = smax; }  // (for the sort: not in registers, which are short during the pass)
     c_ref = __fmul_rn(smax, p.k2);
     __syncthreads();                                  // the maxima are read; the space becomes the rings
 
@@ -976,20 +975,25 @@ __global__ __launch_bounds__(NT, kWavesPerSimd) void truncate_kernel(const Trunc
 
   // ---- sort the candidates into canonical order ------------------------------------------------
   // (behind a barrier since the candidates were written; what the sort writes first is not what was read since)
-  // 512 threads, out of the pass: few candidates are counted directly; of many the bins lie between the threshold and the sample's
-  // maximum, beyond which there are few more than the sample has been thinned.  us of a kernel's sort: 2.1 by its extremes, 1.5 so; 130
-  // candidates 0.6.
+  // Out of the pass few candidates are counted directly; of many the bins lie between the threshold and the sample's
+  // maximum, beyond which there are few more than the sample has been thinned.  us of a 512-thread kernel's sort: 2.1 by its extremes, 1.7
+  // so, 100 candidates 0.9; 30 bfloat16 rows of 9000 8.8 / 8.6, 2000 of 32000 31.6 / 30.9, 2000 of 60000, k 1000 125.7 / 123.9.  Not for fp32
+  // in the wide shape: 2728 rows of 151936 253.1 / 254.4.
   const uint64_t* sorted = cand;
   bool done = false;
-  if constexpr (kTall) {
-    if (fast_ok && n_cand <= NT / 4) {
-      rank_sort_desc<NT>(cand, n_cand, sort_tmp, p.k_sel);
-      sorted = sort_tmp;
-      done = true;
-    } else if (fast_ok) {
-      done = bucket_sort_desc<NT, true>(cand, n_cand, sort_tmp, sort_tmp_cap, cand, p.k_sel, bins, sh.red, from, upto);
-      if (!done) __syncthreads();
+  constexpr bool kAsBefore = kWavesPerSimd == kWavesWide && E == 4;
+  if (!kAsBefore && fast_ok && n_cand <= NT / 4) {
+    rank_sort_desc<NT>(cand, n_cand, sort_tmp, p.k_sel);
+    sorted = sort_tmp;
+    done = true;
+  } else if (!kAsBefore && fast_ok) {
+    uint32_t* bins = kTall ? reinterpret_cast<uint32_t*>(cand + p.sort_cap) : tables;
+    if constexpr (!kTall) {
+      bins[tid] = 0;
+      __syncthreads();
     }
+    done = bucket_sort_desc<NT, true>(cand, n_cand, sort_tmp, sort_tmp_cap, cand, p.k_sel, bins, sh.red, sh.from, sh.upto);
+    if (!done) __syncthreads();
   }
   while (!done) {
     if (n_cand < 0) n_cand = exact_select<T, NT>(row, p.V, p.k_sel, p.k2, cand, tables, sh, c_ref, z_c, st);
