@@ -72,9 +72,9 @@ __device__ __forceinline__ int wire_clamped_count(int c, int k_cap) { return c <
 // them (their counts come out of the L2: 4 bytes a row), scans its own and packs a row per wave at a time.  A lane makes
 // a whole word out of the entries that lie in it (three at most, two from 31 bits an entry on), so that nothing is assembled in LDS and
 // every store is a full line.  With `clear`, a row zeroes as many words as it falls short of a full row's, counted from
-// the end of out_words: together all those behind the stream.  Bound by its launch at the sizes of a round: packing
-// and unpacking 2048 rows of k_cap 256 took 30.8 us a call through the binding with a launch for the offsets, one for the
-// rows and a fill before them, 23.4 so (and 18.2 since the binding hands plain integers over); 14 rows 31.9 and 18.2.
+// the end of out_words: together all those behind the stream.  Bound by its launch at the sizes of a round (2048 rows of k_cap 256: 6.4 us
+// the kernel, 4.7 unpacking, beside 11 of the host's), by trips to memory one after the other in wide rows: 16384 rows of k_cap 1024, packed
+// and unpacked, 104.7 us with a word and an entry at a time, 82.8 with four; 8192 of 1000 49.8 and 47.6; 16384 of 16 21.9 and 22.4.
 constexpr int kPackThreads = 256, kPackWaves = kPackThreads / 64;
 // Workgroups beyond which they take more than one row per wave: what fills the chip (each adds up all counts before its
 // rows, so that more cost: 4 million rows of 2 entries 5.2 ms, 7.8 with 4096).  With 1024 and three entries to every word
@@ -98,7 +98,14 @@ __global__ __launch_bounds__(kPackThreads) void wire_pack_kernel(const WireParam
   const int E = p.b_idx + 16;
   const int row_max = (16 + p.k_cap * E + 31) >> 5;
   long long base = 0;
-  for (int64_t r = tid; r < r0; r += kPackThreads) base += wire_words_of(p.count[r], p);
+  // (eight counts at a time, as many in flight; a row beyond the group's first reads row 0's and counts as nothing)
+  for (int64_t r = tid; r < r0; r += 8 * kPackThreads) {
+    int c[8];
+#pragma unroll
+    for (int u = 0; u < 8; ++u) c[u] = p.count[r + u * kPackThreads < r0 ? r + u * kPackThreads : 0];
+#pragma unroll
+    for (int u = 0; u < 8; ++u) base += r + u * kPackThreads < r0 ? wire_words_of(c[u], p) : 0;
+  }
 #pragma unroll
   for (int d = 32; d >= 1; d >>= 1) base += __shfl_xor(base, d, 64);
   if (lane == 0) before_s[wave] = base;
@@ -137,22 +144,43 @@ __global__ __launch_bounds__(kPackThreads) void wire_pack_kernel(const WireParam
       const int32_t* ix = p.idx + size_t(r) * p.k_cap;
       const float* lg = p.logit + size_t(r) * p.k_cap;
       uint32_t* out = p.words + off;
-      for (int w = lane; w < n_words; w += 64) {
-        const int b0 = w * 32 - 16;                                     // of the entries' own bit stream
-        const int first = b0 > 0 ? int(__umulhi(uint32_t(b0), inv_E)) : 0;
-        uint32_t word = w == 0 ? uint32_t(c) : 0u;
+      // (four words a lane at a time: what they are made of is requested for all of them first)
+      for (int w0 = 0; w0 < n_words; w0 += 4 * 64) {
+        int id[4][3];
+        float value[4][3];
+        auto first_of = [&](int w) {                                    // the first entry that reaches into word w
+          const int b0 = w * 32 - 16;                                   // of the entries' own bit stream
+          return b0 > 0 ? int(__umulhi(uint32_t(b0), inv_E)) : 0;
+        };
 #pragma unroll
-        for (int t = 0; t < 3; ++t) {
-          if (t == 2 && E >= 31) break;                                 // two cover 32 bits wherever they begin
-          const int i = first + t;
-          const int at = i < c ? i : 0;
-          const uint64_t entry = (uint64_t(uint32_t(ix[at])) & ((uint64_t(1) << p.b_idx) - 1)) |
-                                 (uint64_t(payload_bits16(lg[at], p.payload)) << p.b_idx);
-          const int sh = i * E - b0;                                    // where the entry begins in the word
-          const uint32_t piece = sh >= 0 ? uint32_t(entry << (sh & 31)) : uint32_t(entry >> (-sh & 63));
-          word |= i < c && sh < 32 ? piece : 0u;
+        for (int u = 0; u < 4; ++u) {
+          if (w0 + 64 * u >= n_words) break;
+          const int first = first_of(w0 + 64 * u + lane);
+#pragma unroll
+          for (int t = 0; t < 3; ++t) {
+            if (t == 2 && E >= 31) break;                               // two cover 32 bits wherever they begin
+            const int at = first + t < c ? first + t : 0;
+            id[u][t] = ix[at];
+            value[u][t] = lg[at];
+          }
         }
-        out[w] = word;
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+          if (w0 + 64 * u >= n_words) break;
+          const int w = w0 + 64 * u + lane, b0 = w * 32 - 16, first = first_of(w);
+          uint32_t word = w == 0 ? uint32_t(c) : 0u;
+#pragma unroll
+          for (int t = 0; t < 3; ++t) {
+            if (t == 2 && E >= 31) break;
+            const int i = first + t;
+            const uint64_t entry = (uint64_t(uint32_t(id[u][t])) & ((uint64_t(1) << p.b_idx) - 1)) |
+                                   (uint64_t(payload_bits16(value[u][t], p.payload)) << p.b_idx);
+            const int sh = i * E - b0;                                  // where the entry begins in the word
+            const uint32_t piece = sh >= 0 ? uint32_t(entry << (sh & 31)) : uint32_t(entry >> (-sh & 63));
+            word |= i < c && sh < 32 ? piece : 0u;
+          }
+          if (w < n_words) out[w] = word;
+        }
       }
       if (p.clear) {
         uint32_t* tail = p.words + (p.rows * row_max - ((r + 1) * row_max - (off + n_words)));
@@ -163,37 +191,58 @@ __global__ __launch_bounds__(kPackThreads) void wire_pack_kernel(const WireParam
   }
 }
 
+// One wave per row, four entries a lane at a time: their words are requested as soon as the row's place is known, its count with
+// them, so that a row is two trips to memory.
 __global__ __launch_bounds__(64) void wire_unpack_kernel(const WireParams p) {
   const int64_t r = blockIdx.x;
   const int lane = threadIdx.x;
-  const uint32_t* in = p.in_words + p.in_row_offset[r];
-  const int64_t n_words = p.in_row_offset[r + 1] - p.in_row_offset[r];
+  const int64_t from = p.in_row_offset[r];
+  const uint32_t* in = p.in_words + from;
+  const int64_t n_words = p.in_row_offset[r + 1] - from;
   const int E = p.b_idx + 16;
-  int c = n_words > 0 ? int(in[0] & 0xFFFFu) : 0;
-  // a count that its row's words cannot hold is cut to what they do hold
-  const long long fits = n_words > 0 ? (n_words * 32 - 16) / E : 0;
-  if (c > fits) c = int(fits);
-  c = wire_clamped_count(c, p.k_cap);
+  const int64_t last = n_words > 0 ? n_words - 1 : 0;
+  const int head = n_words > 0 ? int(in[0] & 0xFFFFu) : 0;
   int32_t* ix = p.out_idx + size_t(r) * p.k_cap;
   float* lg = p.out_logit + size_t(r) * p.k_cap;
-  for (int i = lane; i < p.k_cap; i += 64) {
-    int id = -1;
-    float v = -INFINITY;
-    if (i < c) {
-      const long long bit = 16 + (long long)i * E;
-      const int64_t w = bit >> 5;
-      const int sh = int(bit & 31);
-      uint64_t lo = uint64_t(in[w]) | (w + 1 < n_words ? uint64_t(in[w + 1]) << 32 : 0);
-      uint64_t entry = lo >> sh;
-      if (sh + E > 64 && w + 2 < n_words) entry |= uint64_t(in[w + 2]) << (64 - sh);
-      entry &= (uint64_t(1) << E) - 1;
-      id = int(entry & ((uint64_t(1) << p.b_idx) - 1));
-      v = payload_from_bits16(uint32_t(entry >> p.b_idx) & 0xFFFFu, p.payload);
+  // a count that its row's words cannot hold is cut to what they do hold
+  const long long fits = n_words > 0 ? (n_words * 32 - 16) / E : 0;
+  for (int i0 = 0; i0 < p.k_cap; i0 += 4 * 64) {
+    uint32_t x[4][3];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      if (i0 + 64 * u >= p.k_cap) break;
+      const int64_t w = (16 + (i0 + 64 * u + lane) * E) >> 5;
+#pragma unroll
+      for (int t = 0; t < 3; ++t) {
+        if (t == 2 && E <= 33) break;                                   // two words hold 33 bits wherever they begin
+        x[u][t] = n_words > 0 ? in[w + t < last ? w + t : last] : 0u;
+      }
     }
-    ix[i] = id;
-    lg[i] = v;
+    int c = head;
+    if (c > fits) c = int(fits);
+    c = wire_clamped_count(c, p.k_cap);
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      if (i0 + 64 * u >= p.k_cap) break;
+      const int i = i0 + 64 * u + lane;
+      int id = -1;
+      float v = -INFINITY;
+      if (i < c) {
+        const int bit = 16 + i * E, sh = bit & 31;
+        const int64_t w = bit >> 5;
+        uint64_t entry = (uint64_t(x[u][0]) | (w + 1 < n_words ? uint64_t(x[u][1]) << 32 : 0)) >> sh;
+        if (E > 33 && sh + E > 64 && w + 2 < n_words) entry |= uint64_t(x[u][2]) << (64 - sh);
+        entry &= (uint64_t(1) << E) - 1;
+        id = int(entry & ((uint64_t(1) << p.b_idx) - 1));
+        v = payload_from_bits16(uint32_t(entry >> p.b_idx) & 0xFFFFu, p.payload);
+      }
+      if (i < p.k_cap) {
+        ix[i] = id;
+        lg[i] = v;
+      }
+    }
+    if (i0 == 0 && lane == 0) p.out_count[r] = c;
   }
-  if (lane == 0) p.out_count[r] = c;
 }
 
 }  // namespace tslt
