@@ -3,9 +3,10 @@
 //
 // Nobody waits for anybody and nothing has to be cleared first.  Every workgroup stores its results, and when they have
 // arrived at memory a word with the launch's tag; when that has arrived too it looks at the words of all.  Whoever finds them
-// complete goes on: the last to arrive does, and perhaps another that arrived at the same time, with the same results to the
-// same places.  It also takes the words away again, so that a captured launch, whose tag is the same every time, finds
-// none of its own from the replay before.  A tag is 62 bits that no earlier launch of the process has had, so that whatever a
+// complete goes on: the last to arrive does, and perhaps another that arrived at the same time.  Where what follows may be done
+// twice, with the same results to the same places and nothing else in between, both do (hand_over: each workgroup leaves its words once);
+// where more is left for others afterwards one of them claims it (all_arrived, claimed).  The words are taken away again, so that a
+// captured launch, whose tag is the same every time, finds none of its own from the replay before.  A tag is 62 bits that no earlier launch of the process has had, so that whatever a
 // workspace holds from before is not taken for one.
 //
 // All of it goes past the caches of the XCDs (relaxed atomics at device scope: each of the eight has an L2 of its own), so that
@@ -46,7 +47,8 @@ __device__ __forceinline__ void wave_sync() {
 }
 
 // All threads of a workgroup, one of `n` (64 at most) that share something: everything that any of its waves stored with
-// store_through is at memory, it says so in words[i], and returns whether all the others have too.  `told` is a word of LDS.
+// store_through is at memory, it says so in words[i], and returns whether all the others have too.  `told` is a word of LDS.  What they
+// have left may be asked for then; which workgroup goes on with it claimed() says.
 __device__ __forceinline__ bool all_arrived(uint64_t* words, int i, int n, Tag tag, int& told) {
   stores_arrived();
   __syncthreads();
@@ -55,12 +57,22 @@ __device__ __forceinline__ bool all_arrived(uint64_t* words, int i, int n, Tag t
     if (lane == 0) store_through(&words[i], tag_word(tag));
     stores_arrived();
     const bool missing = lane < n && load_through(&words[lane]) != tag_word(tag);
-    const bool all = ballot(missing) == 0;
-    if (all && lane < n) store_through(&words[lane], 0);
-    if (lane == 0) told = all ? 1 : 0;
+    if (ballot(missing) != 0) { if (lane == 0) told = 0; }
+    else if (lane == 0) told = 1;
   }
   __syncthreads();
   return __builtin_amdgcn_readfirstlane(told) != 0;
+}
+
+// One wave of a workgroup that has found all words: whether it is the one that goes on; it takes them away.
+__device__ __forceinline__ bool claimed(uint64_t* words, int n, Tag tag) {
+  const int lane = lane_id();
+  uint64_t word = tag_word(tag);
+  bool mine = false;
+  if (lane == 0) mine = __hip_atomic_compare_exchange_strong(&words[0], &word, 0ull, __ATOMIC_RELAXED, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  mine = ballot(mine) != 0;
+  if (mine && lane > 0 && lane < n) store_through(&words[lane], 0);
+  return mine;
 }
 
 // The same where what is left fits beside the tag, two words of 32 bits for each of `n`: one wave leaves its own, and returns

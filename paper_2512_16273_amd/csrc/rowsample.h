@@ -6,8 +6,8 @@
 //                u * total, in ascending token index: the run that holds it, then the element
 // fp64 is needed for the sampling: at V >= 128k the buckets of the inverse CDF are far narrower than fp32 prefix
 // sums can resolve.  One workgroup per row keeps the sums in LDS and one pass serves the test and the sample.  Where few
-// long rows leave compute units idle several workgroups sweep one and a second launch takes up the sums (row_part,
-// row_fetch): its boundary hands them over, where inside a launch every workgroup would need a device-scope fence.
+// long rows leave compute units idle several workgroups sweep one, leave the sums in memory, and the one that finds those of all goes
+// on with the row (row_shared; handover.h).
 #pragma once
 #include <algorithm>
 #include <type_traits>
@@ -86,7 +86,7 @@ template <typename T> inline bool exp_table_usable(float rT) {
 // Fills the table with all `threads` threads of the workgroup; the caller synchronises.  `half` 0 / 1 fills the
 // first / second half only (a kernel that has requests to make between the two does so: the entries are
 // pure arithmetic, a good thing to have while data travels), -1 everything.  A magnitude's two entries lie side by side and are made
-// together (exp64_pair; one by one bfloat16's table took 3.0 us of a round's kernel, 1.9 so).
+// together (exp64_pair; one by one bfloat16's table took 3.0 us of a round's kernel, 1.7 so).
 template <typename T> __device__ __forceinline__ void build_exp_table(double* table, float rT, int threads, int half = -1) {
   using TB = ExpTab<T>;
   const int mid = ((TB::kSpan / 2 + threads - 1) / threads) * threads;
@@ -270,7 +270,7 @@ struct RowShared {
   double wave_sum[kRowWaves];
   float wave_max[kRowWaves];
   double target, before;
-  int flags, next_run, item, n_corr, pick, cmd, st, fetched, stop_at;
+  int flags, next_run, item, n_corr, pick, cmd, st, fetched, claim, stop_at;
 };
 
 template <typename T> struct RowWork {
@@ -409,7 +409,7 @@ __device__ __forceinline__ void row_pass(RowWork<T>& w, double* table, int half,
     const uint32_t row_lo = __builtin_amdgcn_readfirstlane(uint32_t(row_at)), row_hi = __builtin_amdgcn_readfirstlane(uint32_t(row_at >> 32));
     // (A part's buffer ends where the part does: what lies behind is the next workgroup's, and the run that a wave requests
     // ahead of its last one would be fetched to be dropped.  48 x 6 fp32 rows of 151936, five parts of 30 runs each:
-    // verify_part_kernel took 20.5 MB from memory and 10.1 us so, 14.3 and 9.9 now.)
+    // the sampled rows took 20.5 MB from memory and 10.1 us so, 14.3 and 9.9 now.)
     const uint32_t end_vec = kPart ? std::min(nvec, uint32_t(run1) * kRunVecs) : nvec;
     const __amdgpu_buffer_rsrc_t body =
         row_buffer(reinterpret_cast<const uint4*>((uint64_t(row_hi) << 32) | row_lo), uint32_t(__builtin_amdgcn_readfirstlane(end_vec)));
@@ -573,20 +573,27 @@ __device__ __forceinline__ void row_part(RowWork<T>& w, double* table, int part,
   row_store_set(w, 0.0f, sh);                        // (while they travel; each for itself)
 }
 
-// The row as row_sweep leaves it, from the masses that its workgroups have left.
+// The row as row_sweep leaves it, from the masses that its workgroups have left, in the one of them that claims it (which travels with
+// the masses).
 template <typename T, typename Terms>
-__device__ __forceinline__ void row_fetch(RowWork<T>& w, const double* items, double* table, RowShared& sh) {
+__device__ __forceinline__ bool row_fetch(RowWork<T>& w, const double* items, double* table, uint64_t* words, int parts, Tag tag, RowShared& sh) {
   const int tid = threadIdx.x, lane = lane_id();
   const double mass = __longlong_as_double((long long)load_through(reinterpret_cast<const uint64_t*>(items) + (tid < w.n_items ? tid : 0)));
+  if (wave_id() == 0) {
+    const bool mine = claimed(words, parts, tag);
+    if (lane == 0) sh.claim = mine ? 1 : 0;
+  }
   if (tid < w.n_items) sh.items[tid] = mass;
   const int seen = (ballot(mass != mass) != 0 ? 1 : 0) | (ballot(mass > kSomeMass) != 0 ? 2 : 0);
   if (tid == 0) sh.flags = 0;                        // (its own part's, looked at before the last barrier)
   if (lane == 0 && seen) atomicOr(&sh.fetched, seen);
   __syncthreads();
+  if (__builtin_amdgcn_readfirstlane(sh.claim) == 0) return false;
   if (__builtin_amdgcn_readfirstlane(sh.fetched) != 2) {
     if (tid == 0) sh.next_run = kRowWaves;           // (published by the sweep's first barrier)
     row_sweep<T, Terms>(w, table, -1, sh);
   }
+  return true;
 }
 // Both: whether this workgroup goes on with the row.
 template <typename T, typename Terms, int kLoads = kStreamed>
@@ -595,8 +602,7 @@ __device__ __forceinline__ bool row_shared(RowWork<T>& w, double* table, int par
   if (threadIdx.x == 0) sh.fetched = 0;
   row_part<T, Terms, kLoads>(w, table, part, parts, items, sh);
   if (!all_arrived(words, part, parts, tag, sh.cmd)) return false;
-  row_fetch<T, Terms>(w, items, table, sh);
-  return true;
+  return row_fetch<T, Terms>(w, items, table, words, parts, tag, sh);
 }
 
 constexpr int64_t kShareRows = 128;                  // at most, by two workgroups or more

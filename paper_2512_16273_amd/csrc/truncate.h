@@ -17,7 +17,8 @@
 // row's waves issue one after the other in small ones.  The pass is written for the second: an fma takes its operands from
 // vector registers without a sign to change (2.7 cycles a wave, 4.4 otherwise), binary16 is tested against the threshold as
 // packed halves and never widened, addresses are a scalar offset into a buffer (but for large batches), the complete stages have a loop without a
-// check for the row's end, and every exchange between waves behind the pass is one barrier (12 in all, 24 before).  us
+// check for the row's end, and every exchange between waves behind the pass is one barrier (12 in all, 24 before).  Few long rows
+// are shared by workgroups (64 bfloat16 rows of 128256 18.0 us by one each, 16.2 by four).  us
 // before / now: 1 binary16 row of 32000, k 320 12.4 / 10.8; 64 bfloat16 rows of 128256, k 256 20.5 / 17.8; 19 binary16 rows of
 // 223104 27.7 / 23.0; 600 binary16 rows of 32000 17.7 / 15.8; 4096 bfloat16 rows of 256000, k 1024 407 / 396.
 #pragma once
@@ -944,6 +945,10 @@ __global__ __launch_bounds__(NT, kWavesPerSimd) void truncate_kernel(const Trunc
           count[k] = load_through(&from[1]);
           rec[k] = load_through(&from[2 + tid]);       // (sort_cap is more than NT)
         }
+        if (wave == 0) {                               // (travels with them)
+          const bool mine = claimed(p.part_words + size_t(row_i) * p.parts, p.parts, p.tag);
+          if (lane == 0) sh.bcast_i[1] = mine ? 1 : 0;
+        }
 #pragma unroll
         for (int k = 0; k < kTruncMaxParts; ++k) {
           if (k >= p.parts) break;
@@ -957,6 +962,7 @@ __global__ __launch_bounds__(NT, kWavesPerSimd) void truncate_kernel(const Trunc
           n_cand += n;
         }
         __syncthreads();
+        if (__builtin_amdgcn_readfirstlane(sh.bcast_i[1]) == 0) return;
       }
       fast_ok = !sh.overflow && n_cand <= p.sort_cap && n_cand >= p.k_sel && z_c > 0.0 && z_c < INFINITY;
     }
