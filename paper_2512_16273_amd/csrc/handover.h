@@ -6,8 +6,8 @@
 // complete goes on: the last to arrive does, and perhaps another that arrived at the same time.  Where what follows may be done
 // twice, with the same results to the same places and nothing else in between, both do (hand_over: each workgroup leaves its words once);
 // where more is left for others afterwards one of them claims it (all_arrived, claimed).  The words are taken away again, so that a
-// captured launch, whose tag is the same every time, finds none of its own from the replay before.  A tag is 62 bits that no earlier launch of the process has had, so that whatever a
-// workspace holds from before is not taken for one.
+// captured launch, whose tag is the same every time, finds none of its own from the replay before.  A tag
+// is 62 bits mixed from a count of the process's launches, so that whatever a workspace holds from before is not taken for one.
 //
 // All of it goes past the caches of the XCDs (relaxed atomics at device scope: each of the eight has an L2 of its own), so that
 // no cache has to be written back or invalidated.
