@@ -76,7 +76,8 @@ __device__ __forceinline__ bool claimed(uint64_t* words, int n, Tag tag) {
 }
 
 // The same where what is left fits beside the tag, two words of 32 bits for each of `n`: one wave leaves its own, and returns
-// whether it has found those of all, which are then in LDS at a and c.
+// whether it has found those of all, which are then in LDS at a and c.  (It does not wait for what the workgroup stored before:
+// where whoever goes on writes to the same places, the caller does, stores_arrived.)
 __device__ __forceinline__ bool hand_over(uint64_t* words, int i, int n, uint32_t mine_a, uint32_t mine_c, Tag tag, int* a, int* c) {
   const int lane = lane_id();
   if (lane == 0) {

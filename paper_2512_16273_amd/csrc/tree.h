@@ -331,16 +331,23 @@ __global__ __launch_bounds__(kRowThreads, kWavesPerSimd) void tree_node_kernel(c
                                                                       at, int(blockIdx.x - at * p.parts)) == 3) return;
   if (wave_id() != 0) return;
   const int64_t n = b * p.n_nodes + node;
-  if (threadIdx.x == 0) {
+  auto node_outputs = [&]() {
     if (p.out_node_token) p.out_node_token[n] = token;
     if (p.out_node_slot) p.out_node_slot[n] = slot;
-    if (p.words == nullptr) {
+  };
+  if (p.words == nullptr) {
+    if (threadIdx.x == 0) {
+      node_outputs();
       p.node_slot[n] = slot;
       p.node_token[n] = token;
       p.node_status[n] = st;
     }
+    return;
   }
-  if (p.words == nullptr) return;
+  // The candidates' ratios and rates are at memory before the words, for whoever finds these may write NaN over them.  (A node that
+  // draws has had them there since its search.)
+  stores_arrived();
+  if (threadIdx.x == 0) node_outputs();
   // (nothing of the row is needed any more)
   int* tokens = sh.set_y;
   int* state = reinterpret_cast<int*>(sh.set_e);
