@@ -78,6 +78,7 @@ struct TruncateParams {
   int32_t* out_slot;
   // rows shared by workgroups (handover.h)
   int parts;                 // of a row
+  float reach;       // the row's maximum, expected, above the threshold, in units of the sample's
   uint64_t* part_words;      // [rows, parts]
   uint64_t* part_found;      // [rows, parts, 2 + sort_cap]: the sum of its terms, the number of its candidates, those
   Tag tag;
@@ -981,9 +982,11 @@ __global__ __launch_bounds__(NT, kWavesPerSimd) void truncate_kernel(const Trunc
 
   // ---- sort the candidates into canonical order ------------------------------------------------
   // (behind a barrier since the candidates were written; what the sort writes first is not what was read since)
-  // Out of the pass few candidates are counted directly; of many the bins lie between the threshold and the sample's
-  // maximum, beyond which there are few more than the sample has been thinned.  us of a 512-thread kernel's sort: 2.1 by its extremes, 1.7
-  // so, 100 candidates 0.9; 30 bfloat16 rows of 9000 8.8 / 8.6, 2000 of 32000 31.6 / 30.9, 2000 of 60000, k 1000 125.7 / 123.9.  Not for fp32
+  // Out of the pass few candidates are counted directly; of many the bins lie between the threshold and where the row's maximum is
+  // to be expected (p.reach).  us of a 512-thread kernel's sort: 2.1 by its extremes, 1.7
+  // so, 100 candidates 0.9; 30 bfloat16 rows of 9000 8.8 / 8.5, 2000 of 32000 34.5 / 33.9, 2000 of 60000, k 1000 127.3 / 126.3.  (With the bins up
+  // to the sample's maximum as many candidates crowd the top one as the sample is smaller than the row: 464 binary16 rows of 180544, sets
+  // of 59, 38.2 by the extremes, 39.1 so, 38.1 as it is; 464 bfloat16 of 256000, sets of 32, 46.7 / 48.8 / 46.3.)  Not for fp32
   // in the wide shape: 2728 rows of 151936 253.1 / 254.4.
   const uint64_t* sorted = cand;
   bool done = false;
@@ -998,7 +1001,7 @@ __global__ __launch_bounds__(NT, kWavesPerSimd) void truncate_kernel(const Trunc
       bins[tid] = 0;
       __syncthreads();
     }
-    done = bucket_sort_desc<NT, true>(cand, n_cand, sort_tmp, sort_tmp_cap, cand, p.k_sel, bins, sh.red, sh.from, sh.upto);
+    done = bucket_sort_desc<NT, true>(cand, n_cand, sort_tmp, sort_tmp_cap, cand, p.k_sel, bins, sh.red, sh.from, sh.from + (sh.upto - sh.from) * p.reach);
     if (!done) __syncthreads();
   }
   while (!done) {

@@ -83,6 +83,8 @@ size_t plan_truncate(tslt_dtype dt, int64_t V, int nt, tslt::TruncateParams& p) 
     if (tslt::truncate_lds_bytes(p.ring_bytes, sort_cap, nt) + sizeof(tslt::TruncateShared) + 256 <= kMaxLds) {
       p.jprime = jprime;
       p.sort_cap = sort_cap;
+      // (of n values above a threshold, in a tail that falls exponentially, the largest is ln n + 0.577 scales above it)
+      p.reach = float((std::log(j_eff / f) + 0.577) / (std::log(j_eff) + 0.577));
     }
   }
   return tslt::truncate_lds_bytes(p.ring_bytes, p.sort_cap, nt);
