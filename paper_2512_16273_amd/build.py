@@ -13,7 +13,7 @@ LIB_PATH = os.path.join(HERE, "libtslt.so")
 BINDING_PATH = os.path.join(HERE, "_binding.so")
 BINDING_SOURCE = os.path.join(HERE, "csrc", "binding.cpp")
 SOURCES = [os.path.join(HERE, "csrc", "tslt.hip")]
-HEADERS = [os.path.join(HERE, "csrc", n) for n in ("common.h", "handover.h", "pow_table.h", "truncate.h", "sample.h", "verify.h", "rowops.h", "rowsample.h", "exp64.h", "tree.h", "wire.h", "stats.h", "calib.h")] + \
+HEADERS = [os.path.join(HERE, "csrc", n) for n in ("common.h", "bins.h", "handover.h", "pow_table.h", "truncate.h", "sample.h", "verify.h", "rowops.h", "rowsample.h", "exp64.h", "tree.h", "wire.h", "stats.h", "calib.h")] + \
           [os.path.join(ROOT, "include", "tslt.h")]
 
 

@@ -5,6 +5,8 @@
 
 #include <atomic>
 
+#include "bins.h"
+
 namespace tslt {
 
 // ---- host side: what is looked up or set once per device, so that a call after the first on a device is
@@ -382,9 +384,7 @@ template <int NW> __device__ __forceinline__ int block_excl_scan_i32(int v, Bloc
 // values apart), which is therefore read kRankAhead records at a time.
 constexpr int kRankAhead = 4;
 template <int kBins> __device__ __forceinline__ int value_bin(uint64_t c, float vmin, float scale) {
-  // fp32 subtraction and multiplication are monotone, which is all the binning has to be
-  const int b = int((cand_value(c) - vmin) * scale);
-  return b > kBins - 1 ? kBins - 1 : (b < 0 ? 0 : b);
+  return value_bin_of(cand_value(c) - vmin, scale, kBins);
 }
 // kRange: the bins divide [lo, hi] instead, whatever lies outside in the first and the last of them, and `bins` has been set to zero:
 // the step that looks for the extremes, a third of the whole, and its barrier fall away.  (False where that makes a bin too

@@ -77,6 +77,25 @@ def test_truncate_degenerate_rows(tslt):
             assert res["exact_path_rows"] >= 4
 
 
+@pytest.mark.parametrize("dtype,rows", [("bf16", 2), ("bf16", 150), ("bf16", 400), ("f16", 400), ("f32", 150), ("f32", 400)])
+def test_large_logits_that_no_sample_holds(tslt, dtype, rows):
+    """The largest logits stand between the tiles that the threshold's sample takes, of a nearly flat rest: all of them are beyond
+    what the sort's bins were laid out for, the farthest a million bins and more.  Shared rows, 512 and 256 threads."""
+    V = 200001
+    dt = {"f32": torch.float32, "bf16": torch.bfloat16, "f16": torch.float16}[dtype]
+    g = torch.Generator(device=DEV).manual_seed(3)
+    z = torch.randn(rows, V, generator=g, device=DEV).mul_(1e-3).to(dt)
+    where = torch.arange(22000, 22000 + 29 * 300, 29, device=DEV)              # of the sample's tiles only the first starts below
+    z[:, where] = torch.linspace(1.0, 30.0, 300, device=DEV).to(dt)
+    z[:, 30000:30040] = 17.0
+    z[1::2, 31007] = 60000.0
+    out = tslt.truncate(z, 0.8, 200, 0.0, 200, u=torch.full((rows, 1), 0.5, device=DEV))
+    torch.cuda.synchronize()
+    at = torch.tensor([0, 1, rows - 2, rows - 1], device=DEV)
+    P.compare_truncate({k: v[at] for k, v in out.items()}, z[at], 0.8, 200, 0.0, 200, label=f"{dtype} {rows}")
+    assert torch.equal(out["idx"], out["idx"][:2].repeat(rows // 2, 1)) and torch.equal(out["count"], out["count"][:2].repeat(rows // 2))
+
+
 def test_truncate_argument_errors(tslt):
     z = torch.zeros(2, 100, device=DEV)
     for bad in (dict(temperature=0.0), dict(temperature=-1.0), dict(k_cap=0), dict(k_cap=2000), dict(top_k=-1)):
