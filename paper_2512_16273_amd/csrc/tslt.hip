@@ -298,7 +298,9 @@ static int pack_impl(bool clear, const int32_t* idx, const float* logit, const i
   p.clear = clear ? 1 : 0;
   p.rows_per = tslt::wire_rows_per_group(rows);
   const int64_t groups = rows > 0 ? (rows + p.rows_per - 1) / p.rows_per : 1;      // (no rows: the total alone)
-  hipLaunchKernelGGL(tslt::wire_pack_kernel, dim3(unsigned(groups)), dim3(tslt::kPackThreads), 0, reinterpret_cast<hipStream_t>(stream), p);
+  const bool narrow = tslt::wire_row_words(k_cap, p.b_idx) <= 64;                  // a word a lane
+  hipLaunchKernelGGL((narrow ? tslt::wire_pack_kernel<1> : tslt::wire_pack_kernel<4>), dim3(unsigned(groups)), dim3(tslt::kPackThreads), 0,
+                     reinterpret_cast<hipStream_t>(stream), p);
   const hipError_t e = hipGetLastError();
   if (e != hipSuccess) return hip_fail(e, "tslt_pack launch");
   return TSLT_OK;

@@ -73,8 +73,9 @@ __device__ __forceinline__ int wire_clamped_count(int c, int k_cap) { return c <
 // a whole word out of the entries that lie in it (three at most, two from 31 bits an entry on), so that nothing is assembled in LDS and
 // every store is a full line.  With `clear`, a row zeroes as many words as it falls short of a full row's, counted from
 // the end of out_words: together all those behind the stream.  Bound by its launch at the sizes of a round (2048 rows of k_cap 256: 6.4 us
-// the kernel, 4.7 unpacking, beside 11 of the host's), by trips to memory one after the other in wide rows: 16384 rows of k_cap 1024, packed
-// and unpacked, 104.7 us with a word and an entry at a time, 82.8 with four; 8192 of 1000 49.8 and 47.6; 16384 of 16 21.9 and 22.4.
+// the kernel, 4.7 unpacking, beside 11 of the host's), by trips to memory one after the other in wide rows: us of the kernel a word at a
+// time / four, 16384 rows of k_cap 1024 76.3 / 52.4, 8192 of 1000 28.6 / 25.8, 2048 of 256 6.5 / 6.1.  A row that has no more than a word a lane
+// takes them one at a time: 16384 of 16 16.8, by four 17.3.
 constexpr int kPackThreads = 256, kPackWaves = kPackThreads / 64;
 // Workgroups beyond which they take more than one row per wave: what fills the chip (each adds up all counts before its
 // rows, so that more cost: 4 million rows of 2 entries 5.2 ms, 7.8 with 4096).  With 1024 and three entries to every word
@@ -88,6 +89,7 @@ inline int64_t wire_rows_per_group(int64_t rows) {
 __device__ __forceinline__ int wire_words_of(int count, const WireParams& p) {
   return (16 + wire_clamped_count(count, p.k_cap) * (p.b_idx + 16) + 31) >> 5;
 }
+template <int kAt>
 __global__ __launch_bounds__(kPackThreads) void wire_pack_kernel(const WireParams p) {
   __shared__ long long before_s[kPackWaves];
   __shared__ int wave_tot[kPackWaves], count_s[kPackThreads], off_s[kPackThreads];
@@ -144,16 +146,16 @@ __global__ __launch_bounds__(kPackThreads) void wire_pack_kernel(const WireParam
       const int32_t* ix = p.idx + size_t(r) * p.k_cap;
       const float* lg = p.logit + size_t(r) * p.k_cap;
       uint32_t* out = p.words + off;
-      // (four words a lane at a time: what they are made of is requested for all of them first)
-      for (int w0 = 0; w0 < n_words; w0 += 4 * 64) {
-        int id[4][3];
-        float value[4][3];
+      // (kAt words a lane at a time: what they are made of is requested for all of them first)
+      for (int w0 = 0; w0 < n_words; w0 += kAt * 64) {
+        int id[kAt][3];
+        float value[kAt][3];
         auto first_of = [&](int w) {                                    // the first entry that reaches into word w
           const int b0 = w * 32 - 16;                                   // of the entries' own bit stream
           return b0 > 0 ? int(__umulhi(uint32_t(b0), inv_E)) : 0;
         };
 #pragma unroll
-        for (int u = 0; u < 4; ++u) {
+        for (int u = 0; u < kAt; ++u) {
           if (w0 + 64 * u >= n_words) break;
           const int first = first_of(w0 + 64 * u + lane);
 #pragma unroll
@@ -165,7 +167,7 @@ __global__ __launch_bounds__(kPackThreads) void wire_pack_kernel(const WireParam
           }
         }
 #pragma unroll
-        for (int u = 0; u < 4; ++u) {
+        for (int u = 0; u < kAt; ++u) {
           if (w0 + 64 * u >= n_words) break;
           const int w = w0 + 64 * u + lane, b0 = w * 32 - 16, first = first_of(w);
           uint32_t word = w == 0 ? uint32_t(c) : 0u;
@@ -191,58 +193,40 @@ __global__ __launch_bounds__(kPackThreads) void wire_pack_kernel(const WireParam
   }
 }
 
-// One wave per row, four entries a lane at a time: their words are requested as soon as the row's place is known, its count with
-// them, so that a row is two trips to memory.
+// One wave per row, an entry a lane at a time.  (Four entries a lane, their words requested before the count is known, take a trip to
+// memory less and more instructions: 14 rows of k_cap 256 4.1 us the kernel so, 3.8 by four, beside 11 of the host's; 16384 of 16 5.7 / 6.0, of 64
+// 6.4 / 7.0, of 1024 29.2 / 30.2, 4000 of 40 3.7 / 4.0, 2048 of 256 4.7 / 4.6.)
 __global__ __launch_bounds__(64) void wire_unpack_kernel(const WireParams p) {
   const int64_t r = blockIdx.x;
   const int lane = threadIdx.x;
-  const int64_t from = p.in_row_offset[r];
-  const uint32_t* in = p.in_words + from;
-  const int64_t n_words = p.in_row_offset[r + 1] - from;
+  const uint32_t* in = p.in_words + p.in_row_offset[r];
+  const int64_t n_words = p.in_row_offset[r + 1] - p.in_row_offset[r];
   const int E = p.b_idx + 16;
-  const int64_t last = n_words > 0 ? n_words - 1 : 0;
-  const int head = n_words > 0 ? int(in[0] & 0xFFFFu) : 0;
-  int32_t* ix = p.out_idx + size_t(r) * p.k_cap;
-  float* lg = p.out_logit + size_t(r) * p.k_cap;
+  int c = n_words > 0 ? int(in[0] & 0xFFFFu) : 0;
   // a count that its row's words cannot hold is cut to what they do hold
   const long long fits = n_words > 0 ? (n_words * 32 - 16) / E : 0;
-  for (int i0 = 0; i0 < p.k_cap; i0 += 4 * 64) {
-    uint32_t x[4][3];
-#pragma unroll
-    for (int u = 0; u < 4; ++u) {
-      if (i0 + 64 * u >= p.k_cap) break;
-      const int64_t w = (16 + (i0 + 64 * u + lane) * E) >> 5;
-#pragma unroll
-      for (int t = 0; t < 3; ++t) {
-        if (t == 2 && E <= 33) break;                                   // two words hold 33 bits wherever they begin
-        x[u][t] = n_words > 0 ? in[w + t < last ? w + t : last] : 0u;
-      }
+  if (c > fits) c = int(fits);
+  c = wire_clamped_count(c, p.k_cap);
+  int32_t* ix = p.out_idx + size_t(r) * p.k_cap;
+  float* lg = p.out_logit + size_t(r) * p.k_cap;
+  for (int i = lane; i < p.k_cap; i += 64) {
+    int id = -1;
+    float v = -INFINITY;
+    if (i < c) {
+      const long long bit = 16 + (long long)i * E;
+      const int64_t w = bit >> 5;
+      const int sh = int(bit & 31);
+      uint64_t lo = uint64_t(in[w]) | (w + 1 < n_words ? uint64_t(in[w + 1]) << 32 : 0);
+      uint64_t entry = lo >> sh;
+      if (sh + E > 64 && w + 2 < n_words) entry |= uint64_t(in[w + 2]) << (64 - sh);
+      entry &= (uint64_t(1) << E) - 1;
+      id = int(entry & ((uint64_t(1) << p.b_idx) - 1));
+      v = payload_from_bits16(uint32_t(entry >> p.b_idx) & 0xFFFFu, p.payload);
     }
-    int c = head;
-    if (c > fits) c = int(fits);
-    c = wire_clamped_count(c, p.k_cap);
-#pragma unroll
-    for (int u = 0; u < 4; ++u) {
-      if (i0 + 64 * u >= p.k_cap) break;
-      const int i = i0 + 64 * u + lane;
-      int id = -1;
-      float v = -INFINITY;
-      if (i < c) {
-        const int bit = 16 + i * E, sh = bit & 31;
-        const int64_t w = bit >> 5;
-        uint64_t entry = (uint64_t(x[u][0]) | (w + 1 < n_words ? uint64_t(x[u][1]) << 32 : 0)) >> sh;
-        if (E > 33 && sh + E > 64 && w + 2 < n_words) entry |= uint64_t(x[u][2]) << (64 - sh);
-        entry &= (uint64_t(1) << E) - 1;
-        id = int(entry & ((uint64_t(1) << p.b_idx) - 1));
-        v = payload_from_bits16(uint32_t(entry >> p.b_idx) & 0xFFFFu, p.payload);
-      }
-      if (i < p.k_cap) {
-        ix[i] = id;
-        lg[i] = v;
-      }
-    }
-    if (i0 == 0 && lane == 0) p.out_count[r] = c;
+    ix[i] = id;
+    lg[i] = v;
   }
+  if (lane == 0) p.out_count[r] = c;
 }
 
 }  // namespace tslt

@@ -149,3 +149,10 @@ def test_pack_over_the_workgroups(tslt, rows, k_cap, V):
 def test_pack_entries_of_every_width(tslt, rows, k_cap, V):
     """Entries of 18, 30, 31 and 33 bits, at whole rows' width: three of them in a word, or two."""
     test_pack_over_the_workgroups(tslt, rows, k_cap, V)
+
+
+@pytest.mark.parametrize("rows,k_cap,V", [(300, 61, 128256), (300, 62, 128256), (37, 119, 2), (37, 120, 2)])
+def test_pack_a_word_a_lane(tslt, rows, k_cap, V):
+    """Rows of at most 64 words take one a lane at a time, longer ones four: both sides of that line."""
+    assert ((16 + k_cap * (O.index_bits(V) + 16) + 31) // 32 <= 64) == (k_cap in (61, 119))
+    test_pack_over_the_workgroups(tslt, rows, k_cap, V)
