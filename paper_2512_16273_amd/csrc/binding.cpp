@@ -273,5 +273,7 @@ PyMODINIT_FUNC PyInit__binding() {
       {&k_seq, "seq"}, {&k_len, "len"}, {&k_node_token, "node_token"}, {&k_node_slot, "node_slot"}, {&k_words, "words"}, {&k_row_offset, "row_offset"}};
   for (const auto& k : keys)
     if ((*k.first = PyUnicode_InternFromString(k.second)) == nullptr) return nullptr;
-  return PyModule_Create(&module);
+  PyObject* m = PyModule_Create(&module);
+  if (m != nullptr && PyModule_AddStringConstant(m, "built_for", TSLT_BUILT_FOR) != 0) Py_CLEAR(m);
+  return m;
 }

@@ -7,7 +7,8 @@ fallback: if the library is missing, or a tensor is not on a GPU, the call raise
 
 The calls of a serving loop (with the caller's outputs and workspace; pack and unpack) go through `_binding`
 (csrc/binding.cpp), which makes the same checks natively; where one does not hold it returns None and the
-function here goes through them one by one and says which.
+function here goes through them one by one and says which.  Without a `_binding` built for this torch and this
+Python every call takes the functions here, which cost the host 7 us more.
 """
 from __future__ import annotations
 
@@ -17,6 +18,8 @@ import os
 from typing import Optional, Sequence
 
 import torch
+
+from .build import built_for
 
 _HERE = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(_HERE, "libtslt.so")
@@ -33,7 +36,7 @@ EXPORTS = ("tslt_version", "tslt_last_error", "tslt_workspace_bytes", "tslt_trun
            "tslt_verify_static", "tslt_truncation_stats", "tslt_multicandidate_stats", "tslt_calibrate_read", "tslt_verify_tree")
 
 _lib = None
-_fast = None                                    # the module _binding, bound to the library that is loaded
+_fast = None                                    # the module _binding, bound to the library that is loaded (None: there is none to use)
 
 
 class TsltError(RuntimeError):
@@ -89,16 +92,22 @@ def load(path: Optional[str] = None):
     lib.tslt_verify_tree.restype = c.c_int
     lib.tslt_verify_tree.argtypes = [vp, c.c_int, i64, i64, i64, f32, i32, c.POINTER(i32), vp, vp, vp, i32, vp, vp,
                                      vp, i32, vp, vp, vp, vp, vp, vp, vp, vp, sz, vp]
-    try:
-        from . import _binding
-    except ImportError as e:
-        raise TsltError(f"_binding.so: {e}; build it with `python -m paper_2512_16273_amd.build`") from e
-    _binding.bind(*[c.cast(getattr(lib, fn), vp).value for fn in (
-        "tslt_workspace_bytes", "tslt_truncate_sample", "tslt_verify", "tslt_verify_accept", "tslt_verify_resample", "tslt_verify_tree",
-        "tslt_pack_bound_words", "tslt_pack_cleared", "tslt_unpack")])
-    _fast = _binding
+    _fast = _native_binding()
+    if _fast is not None:
+        _fast.bind(*[c.cast(getattr(lib, fn), vp).value for fn in (
+            "tslt_workspace_bytes", "tslt_truncate_sample", "tslt_verify", "tslt_verify_accept", "tslt_verify_resample", "tslt_verify_tree",
+            "tslt_pack_bound_words", "tslt_pack_cleared", "tslt_unpack")])
     _lib = lib
     return lib
+
+
+def _native_binding():
+    """The module `_binding` where it is there, imports, and was built for this torch and this Python; else None."""
+    try:
+        from . import _binding
+    except ImportError:
+        return None
+    return _binding if getattr(_binding, "built_for", "") == built_for() else None
 
 
 def _check(code: int):
@@ -174,7 +183,7 @@ def truncate(logits: torch.Tensor, temperature: float, top_k: int, top_p: float,
     [rows, n], n draws from each row's q_hat (i.i.d., or without replacement).  payload = "bf16" / "f16" rounds the kept values to the
     format in which they will travel before q_hat and the draws are computed."""
     lib = load()
-    if out is not None and u is not None and logits.is_cuda:
+    if _fast is not None and out is not None and u is not None and logits.is_cuda:
         code = _fast.truncate(logits, float(temperature), int(top_k), float(top_p), int(k_cap), PAYLOAD[payload], without_replacement,
                               out, u, _stream())
         if code is not None:
@@ -220,7 +229,7 @@ def truncate(logits: torch.Tensor, temperature: float, top_k: int, top_p: float,
 def pack(idx: torch.Tensor, logit: torch.Tensor, count: torch.Tensor, V: int, payload: str) -> dict:
     """tslt_pack: truncated sets [rows, k_cap] -> words (uint32, as int32 storage), row_offset [rows + 1] int64."""
     lib = load()
-    if idx.is_cuda:
+    if _fast is not None and idx.is_cuda:
         made = _fast.pack(idx, logit, count, int(V), PAYLOAD[payload], _stream())
         if made is not None:
             if made[0]:
@@ -240,7 +249,7 @@ def pack(idx: torch.Tensor, logit: torch.Tensor, count: torch.Tensor, V: int, pa
 def unpack(words: torch.Tensor, row_offset: torch.Tensor, rows: int, k_cap: int, V: int, payload: str) -> dict:
     """tslt_unpack: the inverse of pack -> idx, logit [rows, k_cap], count [rows]."""
     lib = load()
-    if words.is_cuda:
+    if _fast is not None and words.is_cuda:
         made = _fast.unpack(words, row_offset, rows, k_cap, int(V), PAYLOAD[payload], _stream())
         if made is not None:
             if made[0]:
@@ -285,7 +294,7 @@ def verify(target: torch.Tensor, temperature: float, q_idx: torch.Tensor, q_logi
     tslt_verify_accept / tslt_verify_resample (then `out` and `workspace` must be passed to both).
     first_stage > 0 calls tslt_verify_staged / tslt_verify_accept_staged."""
     lib = load()
-    if out is not None and workspace is not None and not first_stage and target.is_cuda:
+    if _fast is not None and out is not None and workspace is not None and not first_stage and target.is_cuda:
         code = _fast.verify(_PHASES[phase], target, float(temperature), q_idx, q_logit, q_count, draft_tokens, u_accept, u_resample, out,
                             workspace, _stream())
         if code is not None:
@@ -416,7 +425,7 @@ def verify_tree(target: torch.Tensor, temperature: float, expansion: Sequence[in
     [B, N_nodes] (when all_nodes), ratio and beta [B, N_nodes-1], status [B].  without_replacement selects the rule
     for candidates that were drawn without replacement."""
     lib = load()
-    if out is not None and workspace is not None and target.is_cuda:
+    if _fast is not None and out is not None and workspace is not None and target.is_cuda:
         code = _fast.verify_tree(target, float(temperature), expansion, q_idx, q_logit, q_count, cand_tokens, u_accept, u_resample,
                                  without_replacement, out, workspace, _stream())
         if code is not None:

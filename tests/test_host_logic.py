@@ -122,3 +122,29 @@ def test_bench_refuses_more_than_one_gpu():
     r = subprocess.run([sys.executable, os.path.join(ROOT, "bench.py"), "--gpus", "2"], capture_output=True, text=True, timeout=60)
     assert r.returncode == 2
     assert "ONE GPU" in r.stderr and r.stdout.strip() == ""
+
+
+@pytest.mark.parametrize("binding", ["absent", "broken", "for another torch", "built"])
+def test_library_loads_with_and_without_its_native_binding(tmp_path, binding):
+    """The library alone is enough: `_binding` is used where it was built for this torch and this Python, and else not asked for."""
+    import shutil
+    from paper_2512_16273_amd import build
+    if not build.binding_possible():
+        pytest.skip("no host compiler, or no headers")
+    if not os.path.exists(LIB) or not os.path.exists(build.BINDING_PATH):
+        build.build_library(verbose=False)
+    pkg = tmp_path / "paper_2512_16273_amd"
+    pkg.mkdir()
+    for name in ("__init__.py", "build.py", "tslt.py"):
+        shutil.copy(os.path.join(build.HERE, name), pkg / name)
+    os.symlink(LIB, pkg / "libtslt.so")
+    if binding == "built":
+        shutil.copy(build.BINDING_PATH, pkg / "_binding.so")
+    elif binding == "broken":
+        (pkg / "_binding.so").write_bytes(b"\x7fELF of something else")
+    elif binding == "for another torch":
+        (pkg / "_binding.py").write_text("built_for = 'torch 1.0'\ndef bind(*a):\n    raise AssertionError('bound')\n")
+    code = "from paper_2512_16273_amd import tslt\nlib = tslt.load()\nprint(lib.tslt_version() >= 100, tslt._fast is not None)"
+    env = {k: v for k, v in os.environ.items() if k not in ("PYTHONPATH", "TSLT_LIBRARY")}
+    out = subprocess.run([sys.executable, "-c", code], cwd=tmp_path, env=env, check=True, capture_output=True, text=True).stdout
+    assert out.split() == ["True", str(binding == "built")]
