@@ -109,7 +109,7 @@ PyObject* py_truncate(PyObject*, PyObject* const* a, Py_ssize_t n) {
   if (!there) Py_RETURN_NONE;
   const int64_t samples = u->numel() / rows;
   // (a few long rows: memory in which the workgroups that share each of them hand over what they have found)
-  const size_t ws_bytes = rows <= 128 ? lib.workspace_bytes(TSLT_OP_TRUNCATE_SHARED, rows, 0, V, int32_t(k_cap)) : 0;
+  const size_t ws_bytes = lib.workspace_bytes(TSLT_OP_TRUNCATE_SHARED, rows, 0, V, int32_t(k_cap));
   at::Tensor ws;
   if (ws_bytes > 0) ws = at::empty({int64_t(ws_bytes)}, at::TensorOptions().dtype(at::kByte).device(z->device()));
   int code;

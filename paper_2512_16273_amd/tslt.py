@@ -170,9 +170,13 @@ def _workspace(nbytes: int, device) -> Optional[torch.Tensor]:
     return torch.empty(nbytes, dtype=torch.uint8, device=device)   # torch aligns to >= 256 bytes
 
 
-@functools.lru_cache(maxsize=256)
 def _truncate_workspace_bytes(rows: int, V: int, k_cap: int) -> int:
-    return workspace_bytes(OP_TRUNCATE_SHARED, rows, 0, V, k_cap)
+    return _memoised_workspace_bytes(load(), torch.cuda.current_device(), OP_TRUNCATE_SHARED, rows, V, k_cap)
+
+
+@functools.lru_cache(maxsize=256)               # (the device: how many rows are shared goes by its compute units)
+def _memoised_workspace_bytes(lib, device: int, op: int, rows: int, V: int, k_cap: int) -> int:
+    return int(lib.tslt_workspace_bytes(op, rows, 0, V, k_cap))
 
 
 def truncate(logits: torch.Tensor, temperature: float, top_k: int, top_p: float, k_cap: int,
@@ -203,7 +207,7 @@ def truncate(logits: torch.Tensor, temperature: float, top_k: int, top_p: float,
             "status": torch.empty(rows, dtype=torch.int32, device=dev),
         }
     # (a few long rows: memory in which the workgroups that share each of them hand over what they have found)
-    ws_bytes = _truncate_workspace_bytes(rows, V, int(k_cap)) if 0 < rows <= 128 else 0
+    ws_bytes = _truncate_workspace_bytes(rows, V, int(k_cap)) if rows else 0
     held = torch.empty(ws_bytes, dtype=torch.uint8, device=dev) if ws_bytes else None
     ws = _ptr(held)
     if u is None:

@@ -148,3 +148,23 @@ def test_library_loads_with_and_without_its_native_binding(tmp_path, binding):
     env = {k: v for k, v in os.environ.items() if k not in ("PYTHONPATH", "TSLT_LIBRARY")}
     out = subprocess.run([sys.executable, "-c", code], cwd=tmp_path, env=env, check=True, capture_output=True, text=True).stdout
     assert out.split() == ["True", str(binding == "built")]
+
+
+def test_shared_draft_rows_workspace_follows_the_library_and_the_device(monkeypatch):
+    """Its size is asked of the library that is loaded, for the device that is current, whatever has been asked before."""
+    import torch
+    from paper_2512_16273_amd import tslt
+
+    class Library:
+        def __init__(self, scale):
+            self.scale = scale
+
+        def tslt_workspace_bytes(self, op, rows, inner, V, k_cap):
+            assert op == tslt.OP_TRUNCATE_SHARED
+            return self.scale * rows + 1000 * torch.cuda.current_device()
+
+    for device in (0, 1, 0):
+        monkeypatch.setattr(torch.cuda, "current_device", lambda: device)
+        for scale in (3, 5):
+            monkeypatch.setattr(tslt, "_lib", Library(scale))
+            assert tslt._truncate_workspace_bytes(200, 128256, 64) == scale * 200 + 1000 * device
