@@ -249,6 +249,13 @@ template <> __device__ __forceinline__ float dword_element<float>(uint32_t w, in
 template <> __device__ __forceinline__ float dword_element<Bf16>(uint32_t w, int i) { return as_f32(i ? w & 0xFFFF0000u : w << 16); }
 template <> __device__ __forceinline__ float dword_element<F16>(uint32_t w, int i) { return i ? f16_hi(w) : f16_lo(w); }
 
+// What a sweep is handed of the table: that it has been asked for (Terms::Early), or this, to ask for it with the row.  (fp32's kernels of
+// 64 registers spill where it waits through what comes before the sweep: 24 trees <2,2,2> of 151936, sets of 1024, 65.4 us asked for with the
+// row, 67.2 before it.)
+struct AskWithRow {};
+template <typename Terms> __device__ __forceinline__ typename Terms::Early table_asked(const typename Terms::Early& asked) { return asked; }
+template <typename Terms> __device__ __forceinline__ typename Terms::Early table_asked(AskWithRow) { return Terms::begin(); }
+
 // ---------------------------------------------------------------------------------------------
 // The row.  Its mass is held in "items", in row order: the elements before the aligned body, every run of the
 // body, the elements after it.  All sixteen waves sweep; what comes between the sweep and the search for the
@@ -384,9 +391,8 @@ template <typename T> __device__ __forceinline__ void row_edges(const RowWork<T>
 enum { kStreamed = 0, kCached = 1, kByAddress = 2 };
 constexpr int64_t kStreamBytes = int64_t(256) << 20, kCachedBytes = int64_t(400) << 20, kStreamTreeBytes = int64_t(600) << 20;
 constexpr int64_t kByAddressV = 48000;
-template <typename T, typename Terms, bool kOneCopy = false, int kLoads = kStreamed, bool kPart = false>
-__device__ __forceinline__ void row_pass(RowWork<T>& w, double* table, int half, const typename Terms::Early& early, int run0, int run1, bool ends,
-                                         RowShared& sh) {
+template <typename T, typename Terms, bool kOneCopy = false, int kLoads = kStreamed, bool kPart = false, typename Asked>
+__device__ __forceinline__ void row_pass(RowWork<T>& w, double* table, int half, const Asked& asked, int run0, int run1, bool ends, RowShared& sh) {
   const int lane = lane_id(), wave = wave_id();
   const RowSplit& rs = w.rs;
   const float rT = w.rT;
@@ -440,6 +446,8 @@ __device__ __forceinline__ void row_pass(RowWork<T>& w, double* table, int half,
     };
     uint4 d[kSegVecs], dn[kSegVecs];
     int cur = run0 + wave;
+    typename Terms::Early early;
+    if (half > -2) early = table_asked<Terms>(asked);  // (before the row: loads are waited for in order)
     request(cur, d);
     if (half > -2) Terms::finish(table, early, rT, half);
     __syncthreads();                    // the table is complete
@@ -478,7 +486,7 @@ __device__ __forceinline__ void row_pass(RowWork<T>& w, double* table, int half,
       } while (cur < run1);
     }
   } else {
-    if (half > -2) Terms::finish(table, early, rT, half);      // (the next row of a walk may have runs)
+    if (half > -2) Terms::finish(table, table_asked<Terms>(asked), rT, half);      // (the next row of a walk may have runs)
     __syncthreads();
     row_gather(w);
   }
@@ -490,10 +498,10 @@ __device__ __forceinline__ void row_pass(RowWork<T>& w, double* table, int half,
 }
 // The masses of all the row's items, referenced to w.smax (0, or the row's maximum where it needs that), and sh.flags
 // (bit 0: NaN or +inf).
-template <typename T, typename Terms, bool kOneCopy = false, int kLoads = kStreamed>
-__device__ __forceinline__ void row_sweep(RowWork<T>& w, double* table, int half, const typename Terms::Early& early, RowShared& sh) {
+template <typename T, typename Terms, bool kOneCopy = false, int kLoads = kStreamed, typename Asked>
+__device__ __forceinline__ void row_sweep(RowWork<T>& w, double* table, int half, const Asked& asked, RowShared& sh) {
   constexpr int E = ElemTraits<T>::kPerVec;
-  row_pass<T, Terms, kOneCopy, kLoads>(w, table, half, early, 0, w.n_runs, true, sh);
+  row_pass<T, Terms, kOneCopy, kLoads>(w, table, half, asked, 0, w.n_runs, true, sh);
   const int tid = threadIdx.x, lane = lane_id(), wave = wave_id();
   const RowSplit& rs = w.rs;
   const int n_runs = w.n_runs;
@@ -556,11 +564,11 @@ __device__ __forceinline__ void row_sweep(RowWork<T>& w, double* table, int half
 // One of `parts` workgroups that share a row: the masses of its runs, and the first one's of the elements outside the aligned
 // body, left in memory; NaN where it met something that asks for a sweep by the row's maximum.  (The set's target logits are
 // gathered on the way, as in row_sweep, by each of them: whoever goes on has them.)
-template <typename T, typename Terms, int kLoads>
-__device__ __forceinline__ void row_part(RowWork<T>& w, double* table, const typename Terms::Early& early, int part, int parts, double* out, RowShared& sh) {
+template <typename T, typename Terms, int kLoads, typename Asked>
+__device__ __forceinline__ void row_part(RowWork<T>& w, double* table, const Asked& asked, int part, int parts, double* out, RowShared& sh) {
   const int per = (w.n_runs + parts - 1) / parts;
   const int run0 = part * per, run1 = run0 + per < w.n_runs ? run0 + per : w.n_runs;
-  row_pass<T, Terms, false, kLoads, true>(w, table, -1, early, run0, run1, part == 0, sh);
+  row_pass<T, Terms, false, kLoads, true>(w, table, -1, asked, run0, run1, part == 0, sh);
   const bool broken = (sh.flags & 3) != 0;
   const double bad = __longlong_as_double(0x7FF8000000000000ll);
   auto leave = [&](int i) {
@@ -590,16 +598,16 @@ __device__ __forceinline__ bool row_fetch(RowWork<T>& w, const double* items, do
   if (__builtin_amdgcn_readfirstlane(sh.claim) == 0) return false;
   if (__builtin_amdgcn_readfirstlane(sh.fetched) != 2) {
     if (tid == 0) sh.next_run = kRowWaves;           // (published by the sweep's first barrier)
-    row_sweep<T, Terms>(w, table, -1, Terms::begin(), sh);
+    row_sweep<T, Terms>(w, table, -1, AskWithRow{}, sh);
   }
   return true;
 }
 // Both: whether this workgroup goes on with the row.
-template <typename T, typename Terms, int kLoads = kStreamed>
-__device__ __forceinline__ bool row_shared(RowWork<T>& w, double* table, const typename Terms::Early& early, int part, int parts, double* items,
-                                           uint64_t* words, Tag tag, RowShared& sh) {
+template <typename T, typename Terms, int kLoads = kStreamed, typename Asked>
+__device__ __forceinline__ bool row_shared(RowWork<T>& w, double* table, const Asked& asked, int part, int parts, double* items, uint64_t* words,
+                                           Tag tag, RowShared& sh) {
   if (threadIdx.x == 0) sh.fetched = 0;
-  row_part<T, Terms, kLoads>(w, table, early, part, parts, items, sh);
+  row_part<T, Terms, kLoads>(w, table, asked, part, parts, items, sh);
   if (!all_arrived(words, part, parts, tag, sh.cmd)) return false;
   return row_fetch<T, Terms>(w, items, table, words, parts, tag, sh);
 }

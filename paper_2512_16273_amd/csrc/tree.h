@@ -141,10 +141,10 @@ __device__ __forceinline__ int tree_node(const TreeParams& p, int64_t b, int nod
   const int my_cand = p.cand_tokens[c0 + (lane < k ? lane : 0)];
   const float my_u = p.u_accept[c0 + (lane < k ? lane : 0)];
   if constexpr (kParts) {
-    if (!row_shared<T, Terms, kLoads>(w, table, Terms::begin(), part, p.parts, p.items + row_at * p.items_stride, p.part_words + row_at * p.parts, p.tag, sh))
+    if (!row_shared<T, Terms, kLoads>(w, table, AskWithRow{}, part, p.parts, p.items + row_at * p.items_stride, p.part_words + row_at * p.parts, p.tag, sh))
       return 3;
   } else {
-    row_sweep<T, Terms, kOneCopy, kLoads>(w, table, build ? -1 : -2, Terms::begin(), sh);
+    row_sweep<T, Terms, kOneCopy, kLoads>(w, table, build ? -1 : -2, AskWithRow{}, sh);
   }
   if (kOnce) row_clear<T>(table);                                   // (the table is not needed for another row)
   token = -1;

@@ -174,12 +174,16 @@ __global__ __launch_bounds__(kRowThreads, kWavesPerSimd) void verify_resample_ke
   const int64_t b = at;
   const int part = kParts ? int(blockIdx.x - at * p.parts) : 0;
   // The decisions of the sequence's first 64 positions are requested first, and with them the table where it is copied (asked for with
-  // the row, behind them: 48 x 5 fp32 rows of 151936 43.6 us, 43.1 so; 128 x 4 binary16 rows of 32000 24.7 and 23.8), else half of it is built while they
+  // the row, behind them: 48 x 5 fp32 rows of 151936 43.6 us, 43.1 so; 128 x 4 binary16 rows of 32000 24.7 and 23.8; 400 x 4 of 60000 66.4 and 64.9;
+  // not in fp32's form of 64 registers, which then spills), else half of it is built while they
   // travel.  Every wave then finds the first rejected position by itself (gamma when every draft token was
   // accepted): the words are few and nothing has to be handed round.
   const int32_t* fl_b = p.flags + b * p.gamma;
   const int f0 = lane < p.gamma ? fl_b[lane] : 1;
-  const typename Terms::Early early = Terms::begin();
+  const auto asked = [] {
+    if constexpr (kWavesPerSimd == kShared && ElemTraits<T>::kBytes == 4) return AskWithRow{};
+    else return Terms::begin();
+  }();
   if constexpr (!kParts) Terms::first_half(table, p.rT);
   int j0 = f0 != 1 ? lane : p.gamma;
   if (p.gamma > 64 && ballot(f0 != 1) == 0) {
@@ -203,9 +207,9 @@ __global__ __launch_bounds__(kRowThreads, kWavesPerSimd) void verify_resample_ke
     row_open<T>(w, target_row<T>(p, b, jstar), p.V, p.rT, sh);
     row_take_set(w, p.q_idx + size_t(r) * p.k_cap, p.q_logit + size_t(r) * p.k_cap, residual ? p.q_count[r] : 0, p.k_cap);
     if constexpr (kParts) {
-      if (!row_shared<T, Terms, kLoads>(w, table, early, part, p.parts, p.items + b * p.items_stride, p.part_words + b * p.parts, p.tag, sh)) return;
+      if (!row_shared<T, Terms, kLoads>(w, table, asked, part, p.parts, p.items + b * p.items_stride, p.part_words + b * p.parts, p.tag, sh)) return;
     } else {
-      row_sweep<T, Terms, kWavesPerSimd == kAlone, kLoads>(w, table, 1, early, sh);
+      row_sweep<T, Terms, kWavesPerSimd == kAlone, kLoads>(w, table, 1, asked, sh);
     }
     request_end();
     row_clear<T>(table);
@@ -312,9 +316,9 @@ __global__ __launch_bounds__(kRowThreads, kWavesPerSimd) void verify_round_kerne
   row_take_set(w, p.q_idx + size_t(r) * p.k_cap, p.q_logit + size_t(r) * p.k_cap, bonus ? 0 : count, p.k_cap);
   if constexpr (kParts) {
     const int part = int(blockIdx.x - at * p.parts);
-    if (!row_shared<T, Terms>(w, table, Terms::begin(), part, p.parts, p.items + at * p.items_stride, p.part_words + at * p.parts, p.tag, sh)) return;
+    if (!row_shared<T, Terms>(w, table, AskWithRow{}, part, p.parts, p.items + at * p.items_stride, p.part_words + at * p.parts, p.tag, sh)) return;
   } else {
-    row_sweep<T, Terms, kWavesPerSimd == kAlone>(w, table, -1, Terms::begin(), sh);
+    row_sweep<T, Terms, kWavesPerSimd == kAlone>(w, table, -1, AskWithRow{}, sh);
   }
   // (nothing is stored to memory before the last barrier, which would wait for it)
   row_clear<T>(table);
