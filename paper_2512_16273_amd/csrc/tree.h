@@ -16,6 +16,7 @@ namespace tslt {
 
 constexpr int kMaxTreeDepth = 16;
 constexpr int kMaxBranch = 16;
+constexpr int64_t kXcds = 8;             // consecutive workgroups go to one after the other of them
 static_assert(kMaxBranch <= kMaxStages, "a stage to a candidate");
 
 struct TreeParams {
@@ -53,6 +54,7 @@ struct TreeParams {
   double* items;
   int64_t items_stride;
   int parts;              // workgroups that share a row
+  int turn;               // a path's workgroups are this many apart
   uint64_t* part_words;   // [rows, parts]: theirs (handover.h)
   uint64_t* words;        // [B, n_nodes, 2]: what the workgroups of a tree's nodes leave, in place of the node arrays (else null)
   Tag tag;
@@ -492,7 +494,9 @@ __global__ __launch_bounds__(kRowThreads) void tree_path_kernel(const TreeParams
   __shared__ RowShared sh;
   extern __shared__ __align__(16) unsigned char dyn_lds[];
   const int tid = threadIdx.x;
-  const int64_t b = kParts ? blockIdx.x / uint32_t(p.parts) : blockIdx.x;
+  const uint32_t part = kParts ? blockIdx.x / uint32_t(p.turn) : 0u, tree = kParts ? blockIdx.x - part * uint32_t(p.turn) : blockIdx.x;
+  if (kParts && tree >= uint32_t(p.B)) return;
+  const int64_t b = tree;
   int node = 0, layer = 0, len = 0, st_all = 0, token = -1;
   bool done = false;
   if constexpr (kFrom == kFromHead) {
@@ -522,7 +526,7 @@ __global__ __launch_bounds__(kRowThreads) void tree_path_kernel(const TreeParams
     int slot, st, state;
     if (kParts && shared) {
       state = tree_node<T, Terms, false, kLoads, kParts>(p, b, node, reinterpret_cast<double*>(dyn_lds), true, sh, slot, token, st, b,
-                                                         int(blockIdx.x - b * p.parts));
+                                                         int(part));
       if (state == 3) return;
       shared = false;
     } else {
@@ -618,7 +622,13 @@ template <typename T, typename Terms> hipError_t launch_verify_tree_with(TreePar
         constexpr int kLoads = decltype(loads)::value;
         if (p.parts == 1) return walk(tree_path_kernel<T, typename Terms::Walked, kFromQuick, kLoads>);
         p.tag = next_tag();
-        hipLaunchKernelGGL((tree_path_kernel<T, typename Terms::Walked, kFromQuick, kLoads, true>), dim3(unsigned(p.B * p.parts)), dim3(kRowThreads), Terms::kBytes, s, p);
+        // On the XCD on which the tree has been walked, where that leaves a compute unit to each: every part reads the set and gathers the row at
+        // it, and eight L2s full of that had the quick walk fetch its sets again.  us in a launch each / side by side / so, 40 binary16 trees
+        // <2,2,2> of 64000, sets of 16 49.3 / 49.2 / 49.5, of 400 52.5 / 51.8 / 51.7, of 1024 58.6 / 60.1 / 55.9; of 100000, sets of 400 59.4 / 60.3 /
+        // 58.4; 64 fp32 of 151936, sets of 400 79.7 / 80.2 / 78.3.  50 fp32 of 151936, sets of 32, 7 trees of 5 parts on one XCD: 73.4 / 73.2 / 82.4.
+        const int64_t per_xcd = (p.B + kXcds - 1) / kXcds;
+        p.turn = int(per_xcd * p.parts * kXcds <= compute_units() ? per_xcd * kXcds : p.B);
+        hipLaunchKernelGGL((tree_path_kernel<T, typename Terms::Walked, kFromQuick, kLoads, true>), dim3(unsigned(p.turn * p.parts)), dim3(kRowThreads), Terms::kBytes, s, p);
         return hipGetLastError();
       };
       if constexpr (ElemTraits<T>::kBytes == 4) {

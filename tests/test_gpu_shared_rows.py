@@ -111,6 +111,8 @@ def test_chain_of_shared_rows(tslt, dtype, V, B, gamma, broken):
     ("f32", 100000, 30, (2, 2, 2)),                                          # all layers at once, too many rows to share
     # of the path, the first layers alone at once, by two workgroups a row
     ("bf16", 150001, 40, (2, 2, 2)), ("f16", 100003, 18, (2, 2, 2, 2)), ("f32", 100001, 18, (2, 2, 2, 2)),
+    # walked quickly first: a tree's workgroups on one XCD (45 trees in turns of 48), and where they would not have a compute unit each
+    ("f16", 64001, 45, (2, 2, 2)), ("f16", 150001, 50, (2, 2, 2)),
 ])
 @pytest.mark.parametrize("broken", [False, True])
 def test_trees_of_shared_rows(tslt, dtype, V, B, expansion, broken):
