@@ -96,8 +96,8 @@ const char* tslt_last_error(void);
 /* Bytes of workspace an operation needs.  `n_outer` is the number of rows (truncate, sample) or of
  * sequences B (verify, verify_tree); `n_inner` is gamma (verify) or N_nodes (verify_tree), ignored
  * otherwise.  Returns 0 when the operation uses none.  (verify, and verify_tree for the path alone, run with the
- * smaller sizes of earlier versions too; they then leave a small batch's rows to one workgroup each, and verify takes a
- * second launch.)  A workspace belongs to one call at a time, also between the replays of a captured one; it need not be
+ * smaller sizes of earlier versions too; they share a small batch's rows between workgroups as far as there is room for that,
+ * and verify takes a second launch where there is none.)  A workspace belongs to one call at a time, also between the replays of a captured one; it need not be
  * cleared. */
 size_t tslt_workspace_bytes(int op, int64_t n_outer, int64_t n_inner, int64_t V, int32_t k_cap);
 

@@ -68,7 +68,6 @@ struct TreeParams {
 // their items; the two words a tree are for the path.  With node outputs masses are asked for once a node: the size that
 // callers have been told all along, so that a workspace kept from an earlier version and one sized by this one are the same.
 // For the path a call may be given less than it is told to bring: the rows of a small tree's nodes are then not shared.)
-inline int64_t tree_items_stride(int64_t V) { return int64_t(row_segments(V)) * kSubChunks + 2; }
 inline size_t tree_least_workspace_bytes(int64_t B, int64_t n_nodes, int64_t V, bool all_nodes) {
   const size_t n_seg = size_t(row_segments(V));
   const size_t tasks = all_nodes ? size_t(n_nodes) : 1;
@@ -80,10 +79,10 @@ inline size_t tree_workspace_bytes(int64_t B, int64_t n_nodes, int64_t V, bool a
   const size_t least = tree_least_workspace_bytes(B, n_nodes, V, all_nodes);
   if (V < kShareLeastV) return least;
   const size_t arrays = align256(size_t(B) * n_nodes * 4) * 4 + align256(size_t(B) * 4) * 2;
-  const size_t rows = arrays + size_t(kShareWords) * 8 + align256(size_t(std::min(B * n_nodes, kShareRows) * tree_items_stride(V)) * sizeof(double));
+  const size_t rows = arrays + size_t(kShareWords) * 8 + align256(size_t(std::min(B * n_nodes, kShareRows) * items_stride(V)) * sizeof(double));
   return std::max(least, rows);
 }
-inline void tree_carve_workspace(TreeParams& p, void* ws, size_t ws_bytes) {
+inline void tree_carve_workspace(TreeParams& p, void* ws, size_t ws_bytes, int per_vec) {
   const size_t per = align256(size_t(p.B) * p.n_nodes * 4);
   char* w = reinterpret_cast<char*>(ws) + per;       // (the first of the four node arrays that are asked for is not used ...)
   p.words = reinterpret_cast<uint64_t*>(ws);         // (... but where these words take their place, 16 bytes a node)
@@ -94,7 +93,7 @@ inline void tree_carve_workspace(TreeParams& p, void* ws, size_t ws_bytes) {
   p.walk_status = reinterpret_cast<int32_t*>(w); w += align256(size_t(p.B) * 4);
   p.part_words = reinterpret_cast<uint64_t*>(w); w += size_t(kShareWords) * 8;
   p.items = reinterpret_cast<double*>(w);
-  p.items_stride = tree_items_stride(p.V);
+  p.items_stride = items_stride(p.V, per_vec);
   const int64_t left = int64_t(ws_bytes) - int64_t(w - reinterpret_cast<char*>(ws));
   p.items_rows = left > 0 ? left / (p.items_stride * int64_t(sizeof(double))) : 0;
 }

@@ -381,7 +381,7 @@ static int verify_impl(int phases, int stage0, const char* name, const void* tar
   p.out_accept_len = out_accept_len; p.out_tokens = out_tokens; p.out_ratio = out_ratio; p.out_beta = out_beta;
   p.status = status;
   p.stage0 = stage0 >= gamma ? 0 : stage0;
-  tslt::verify_carve_workspace(p, ws, ws_bytes);
+  tslt::verify_carve_workspace(p, ws, ws_bytes, 16 / elem_bytes(dt));
   hipStream_t s = reinterpret_cast<hipStream_t>(stream);
   hipError_t e = dt == TSLT_BF16 ? tslt::launch_verify<tslt::Bf16>(p, s, phases)
                  : dt == TSLT_F16 ? tslt::launch_verify<tslt::F16>(p, s, phases) : tslt::launch_verify<float>(p, s, phases);
@@ -557,7 +557,7 @@ int tslt_verify_tree(const void* target_logits, tslt_dtype dt, int64_t B, int64_
   p.wor = without_replacement ? 1 : 0;
   p.out_node_token = out_node_token; p.out_node_slot = out_node_slot; p.out_seq = out_seq; p.out_len = out_len;
   p.out_ratio = out_ratio; p.out_beta = out_beta; p.status = status;
-  tslt::tree_carve_workspace(p, ws, ws_bytes);
+  tslt::tree_carve_workspace(p, ws, ws_bytes, 16 / elem_bytes(dt));
   hipStream_t s = reinterpret_cast<hipStream_t>(stream);
   hipError_t e = dt == TSLT_BF16 ? tslt::launch_verify_tree<tslt::Bf16>(p, s)
                  : dt == TSLT_F16 ? tslt::launch_verify_tree<tslt::F16>(p, s) : tslt::launch_verify_tree<float>(p, s);

@@ -41,9 +41,10 @@ struct VerifyParams {
   int draws;             // verify_round_kernel draws as well
   double* items;         // masses of shared rows' items
   int64_t items_stride;
+  int64_t items_rows;    // there is room for (read on the host)
   int parts;             // workgroups that share a row
   uint64_t* part_words;  // [rows, parts]: theirs (handover.h)
-  uint64_t* words;       // [B, gamma + 1, 2]: what a round's workgroups leave (null: the workspace has no room; nothing is shared)
+  uint64_t* words;       // [B, gamma + 1, 2]: what a round's workgroups leave (null: the workspace has no room; its rows are not shared)
   Tag tag;
 };
 constexpr int kFlagSkipped = 3;
@@ -53,7 +54,6 @@ inline int64_t verify_rows_to_share(int64_t B, int64_t gamma, int64_t V) {
   if (B <= 0 || gamma <= 0 || V < kShareLeastV) return 0;
   return B * (gamma + 1) <= kShareRows ? B * (gamma + 1) : (B <= kShareRows ? B : 0);
 }
-inline int64_t verify_items_stride(int64_t V) { return int64_t(row_segments(V)) * kSubChunks + 2; }
 // Rows of a round whose workgroups leave their results in memory for the last of each sequence.  (Where there is little to
 // gain, in rows as short as this, callers are told the size that they have always been told.)
 constexpr int64_t kHandRows = 1024, kHandLeastV = 2048;
@@ -70,21 +70,29 @@ inline size_t verify_part_words_bytes(int64_t B, int64_t gamma, int64_t V) {
 inline size_t verify_workspace_bytes(int64_t B, int64_t gamma, int64_t V, int k_cap) {
   (void)k_cap;
   return verify_least_workspace_bytes(B, gamma) + verify_words_bytes(B, gamma, V) + verify_part_words_bytes(B, gamma, V) +
-         align256(size_t(verify_rows_to_share(B, gamma, V) * verify_items_stride(V)) * sizeof(double));
+         align256(size_t(verify_rows_to_share(B, gamma, V) * items_stride(V)) * sizeof(double));
 }
-inline void verify_carve_workspace(VerifyParams& p, void* ws, size_t ws_bytes) {
+// (Of less than that, an earlier version's size say, what fits: that version's has room for the masses alone, of which a 16-bit row has half
+// as many as it is asked for.  per_vec: the type's elements in a vector.)
+inline void verify_carve_workspace(VerifyParams& p, void* ws, size_t ws_bytes, int per_vec) {
   char* w = reinterpret_cast<char*>(ws);
   p.flags = reinterpret_cast<int32_t*>(w); w += align256(size_t(p.B) * p.gamma * 4);
   p.row_status = reinterpret_cast<int32_t*>(w); w += align256(size_t(p.B) * p.gamma * 4);
-  p.items_stride = verify_items_stride(p.V);
+  p.items_stride = items_stride(p.V, per_vec);
   p.words = p.part_words = nullptr;
   p.items = nullptr;
-  if (ws_bytes < verify_workspace_bytes(p.B, p.gamma, p.V, p.k_cap)) return;
-  if (verify_rows_handed(p.B, p.gamma, p.V) > 0) p.words = reinterpret_cast<uint64_t*>(w);
-  w += verify_words_bytes(p.B, p.gamma, p.V);
-  if (verify_rows_to_share(p.B, p.gamma, p.V) > 0) {
+  p.items_rows = 0;
+  int64_t left = int64_t(ws_bytes) - int64_t(w - reinterpret_cast<char*>(ws));
+  const int64_t handed = int64_t(verify_words_bytes(p.B, p.gamma, p.V)), parts = int64_t(verify_part_words_bytes(p.B, p.gamma, p.V));
+  if (handed > 0 && left >= handed) {
+    p.words = reinterpret_cast<uint64_t*>(w);
+    w += handed;
+    left -= handed;
+  }
+  if (parts > 0 && left > parts) {
     p.part_words = reinterpret_cast<uint64_t*>(w);
-    p.items = reinterpret_cast<double*>(w + verify_part_words_bytes(p.B, p.gamma, p.V));
+    p.items = reinterpret_cast<double*>(w + parts);
+    p.items_rows = (left - parts) / (p.items_stride * int64_t(sizeof(double)));
   }
 }
 
@@ -429,7 +437,7 @@ template <typename T, typename Terms> hipError_t launch_verify_with(VerifyParams
     p.j_begin = 0;
     p.j_count = p.gamma + 1;
     p.draws = 1;
-    p.parts = p.words != nullptr && p.items != nullptr ? row_parts<T, Terms>(p.V, p.B * p.j_count) : 1;
+    p.parts = p.words != nullptr && p.B * p.j_count <= p.items_rows ? row_parts<T, Terms>(p.V, p.B * p.j_count) : 1;
     if (p.words != nullptr) p.tag = next_tag();
     e = p.parts > 1 ? share(KernelTag<&verify_round_kernel<T, Terms, kAlone, true>>{}, p.B * p.j_count) : round();
     if (e != hipSuccess || p.words != nullptr) return e;
@@ -455,7 +463,7 @@ template <typename T, typename Terms> hipError_t launch_verify_with(VerifyParams
     }
   }
   if (phases & 2) {
-    p.parts = p.items != nullptr ? row_parts<T, Terms>(p.V, p.B) : 1;
+    p.parts = p.B <= p.items_rows ? row_parts<T, Terms>(p.V, p.B) : 1;
     auto resample = [&](auto loads) -> hipError_t {
       constexpr int kLoads = decltype(loads)::value;
       if (p.parts > 1) {

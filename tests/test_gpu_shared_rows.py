@@ -106,6 +106,52 @@ def test_chain_of_shared_rows(tslt, dtype, V, B, gamma, broken):
             assert out["status"][0] & 1
 
 
+@pytest.mark.parametrize("dtype,V,B,gamma,phases,tree", [
+    ("f16", 100001, 8, 4, ("both",), None), ("bf16", 200000, 4, 4, ("both",), None), ("f16", 151936, 48, 5, ("both",), None),
+    ("f32", 100000, 8, 4, ("accept", "resample"), None), ("f16", 100001, 2, 0, (), (2, 2, 2)),
+])
+def test_rows_are_shared_in_the_workspace_of_earlier_versions(tslt, dtype, V, B, gamma, phases, tree):
+    """Those told callers of room for the masses alone, as many as an fp32 row has; what the workgroups say to each other fits beside a 16-bit
+    row's, or where one row of each sequence is swept."""
+    K, stride = 32, (V // 4 + 1 + 1023) // 1024 * 4 + 2
+    if tree:
+        w = W.scaled(W.WORKLOADS["tree"], B=B, V=V, expansion=tree, top_k=K, k_cap=K, dtype=dtype, without_replacement=False)
+        t = W.make_tree(w, 9, DEV)
+        n = t["target"].shape[1]
+        sets = tslt.truncate(t["draft"].reshape(-1, V), w.T, K, 0.0, K)
+        n_int = sets["idx"].shape[0] // B
+        cand = sets["idx"].view(B, n_int, K)[:, :, :2].reshape(B, -1).contiguous()
+        args = (t["target"], w.T, list(tree), sets["idx"].view(B, n_int, K), sets["logit"].view(B, n_int, K), sets["count"].view(B, n_int), cand,
+                t["u_accept"], t["u_resample"])
+        masses = 4 * up256(B * n * 4) + 2 * up256(B * 4)
+        size = masses + up256(min(B * n, 128) * stride * 8)
+        run = lambda ws: tslt.verify_tree(*args, all_nodes=False, workspace=ws)  # noqa: E731
+        told = tslt.workspace_bytes(tslt.OP_VERIFY_TREE_PATH, B, n, V, K)
+    else:
+        w = W.scaled(W.WORKLOADS["chain_topk"], B=B, V=V, gamma=gamma, dtype=dtype, top_k=K, k_cap=K)
+        c = W.make_chain(w, 3, DEV)
+        tr = tslt.truncate(c["draft"].view(B * gamma, V), w.T, K, 0.0, K, u=c["u_sample"].view(B * gamma, 1))
+        args = (c["target"], w.T, tr["idx"].view(B, gamma, K), tr["logit"].view(B, gamma, K), tr["count"].view(B, gamma),
+                tr["token"].view(B, gamma), c["u_accept"], c["u_resample"])
+        rows = B * (gamma + 1)
+        size = 2 * up256(B * gamma * 4) + up256((rows if rows <= 128 else B) * stride * 8)
+        masses = 2 * up256(B * gamma * 4) + up256(rows * 16)                     # (behind the words that a round's workgroups leave)
+        told = tslt.workspace_bytes(tslt.OP_VERIFY, B, gamma, V, K)
+
+        def run(ws):
+            out = None
+            for phase in phases:
+                out = tslt.verify(*args, workspace=ws, phase=phase, out=out)
+            return out
+    assert size < told
+    everything = run(torch.full((told,), 255, dtype=torch.uint8, device=DEV))
+    ws = torch.full((size,), 255, dtype=torch.uint8, device=DEV)
+    out = run(ws)
+    torch.cuda.synchronize()
+    same(everything, out)
+    assert (ws[masses:] != 255).any(), "no masses have been left there"
+
+
 @pytest.mark.parametrize("dtype,V,B,expansion", [
     ("f32", 50001, 2, (2, 2, 2)), ("f32", 128256, 1, (4, 4, 4)), ("f16", 60000, 6, (3, 3)), ("bf16", 125001, 4, (2, 2, 2)),
     ("f32", 100000, 30, (2, 2, 2)),                                          # all layers at once, too many rows to share
