@@ -61,6 +61,12 @@ template <typename T> T* out_ptr(PyObject* dict, PyObject* key, bool optional, b
   return reinterpret_cast<T*>(t->data_ptr());
 }
 template <typename T> T* ptr(const at::Tensor* t) { return reinterpret_cast<T*>(t->data_ptr()); }
+// An argument that is no such number, or too large for its type: ctypes may know what to do with it.
+bool unread() {
+  if (PyErr_Occurred() == nullptr) return false;
+  PyErr_Clear();
+  return true;
+}
 PyObject* result(int code) { return PyLong_FromLong(code); }
 
 PyObject* py_bind(PyObject*, PyObject* args) {
@@ -87,7 +93,7 @@ PyObject* py_truncate(PyObject*, PyObject* const* a, Py_ssize_t n) {
   const long long top_k = PyLong_AsLongLong(a[2]), k_cap = PyLong_AsLongLong(a[4]), payload = PyLong_AsLongLong(a[5]);
   const int wor = PyObject_IsTrue(a[6]);
   void* stream = PyLong_AsVoidPtr(a[9]);
-  if (PyErr_Occurred()) return nullptr;
+  if (unread()) Py_RETURN_NONE;
   if (z == nullptr || u == nullptr || !PyDict_CheckExact(a[7]) || z->dim() < 1) Py_RETURN_NONE;
   const int dt = dtype_code(*z);
   const int64_t V = z->size(-1);
@@ -127,7 +133,7 @@ PyObject* py_verify(PyObject*, PyObject* const* a, Py_ssize_t n) {
   const long phase = PyLong_AsLong(a[0]);
   const double T = PyFloat_AsDouble(a[2]);
   void* stream = PyLong_AsVoidPtr(a[11]);
-  if (PyErr_Occurred()) return nullptr;
+  if (unread()) Py_RETURN_NONE;
   const at::Tensor *t = plain(a[1]), *qi = dense(a[3], at::kInt), *ql = dense(a[4], at::kFloat), *qc = dense(a[5], at::kInt),
                    *x = dense(a[6], at::kInt), *ua = dense(a[7], at::kFloat), *ur = dense(a[8], at::kFloat), *ws = plain(a[10]);
   if (!t || !qi || !ql || !qc || !x || !ua || !ur || !ws || !PyDict_CheckExact(a[9])) Py_RETURN_NONE;
@@ -159,7 +165,7 @@ PyObject* py_verify_tree(PyObject*, PyObject* const* a, Py_ssize_t n) {
   const double T = PyFloat_AsDouble(a[1]);
   const int wor = PyObject_IsTrue(a[9]);
   void* stream = PyLong_AsVoidPtr(a[12]);
-  if (PyErr_Occurred()) return nullptr;
+  if (unread()) Py_RETURN_NONE;
   if (!PyList_CheckExact(a[2]) && !PyTuple_CheckExact(a[2])) Py_RETURN_NONE;
   int32_t expansion[64];
   const Py_ssize_t depth = PySequence_Fast_GET_SIZE(a[2]);
@@ -168,7 +174,7 @@ PyObject* py_verify_tree(PyObject*, PyObject* const* a, Py_ssize_t n) {
     PyObject* k = PySequence_Fast_GET_ITEM(a[2], i);
     if (!PyLong_CheckExact(k)) Py_RETURN_NONE;
     const long long v = PyLong_AsLongLong(k);
-    if (PyErr_Occurred()) return nullptr;
+    if (unread()) Py_RETURN_NONE;
     expansion[i] = int32_t(v);
   }
   const at::Tensor *t = plain(a[0]), *qi = dense(a[3], at::kInt), *ql = dense(a[4], at::kFloat), *qc = dense(a[5], at::kInt),
@@ -215,7 +221,7 @@ PyObject* py_pack(PyObject*, PyObject* const* a, Py_ssize_t n) {
   if (n != 6 || !bound) Py_RETURN_NONE;
   const long long V = PyLong_AsLongLong(a[3]), payload = PyLong_AsLongLong(a[4]);
   void* stream = PyLong_AsVoidPtr(a[5]);
-  if (PyErr_Occurred()) return nullptr;
+  if (unread()) Py_RETURN_NONE;
   const at::Tensor *idx = dense(a[0], at::kInt), *logit = dense(a[1], at::kFloat), *count = dense(a[2], at::kInt);
   if (!idx || !logit || !count || idx->dim() != 2) Py_RETURN_NONE;
   const int64_t rows = idx->size(0), k_cap = idx->size(1);
@@ -236,7 +242,7 @@ PyObject* py_unpack(PyObject*, PyObject* const* a, Py_ssize_t n) {
   if (n != 7 || !bound) Py_RETURN_NONE;
   const long long rows = PyLong_AsLongLong(a[2]), k_cap = PyLong_AsLongLong(a[3]), V = PyLong_AsLongLong(a[4]), payload = PyLong_AsLongLong(a[5]);
   void* stream = PyLong_AsVoidPtr(a[6]);
-  if (PyErr_Occurred()) return nullptr;
+  if (unread()) Py_RETURN_NONE;
   const at::Tensor *words = dense(a[0], at::kInt), *offs = dense(a[1], at::kLong);
   if (!words || !offs || rows <= 0 || k_cap <= 0 || k_cap > TSLT_MAX_K_CAP) Py_RETURN_NONE;
   const auto on = at::TensorOptions().device(words->device());

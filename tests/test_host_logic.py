@@ -168,3 +168,16 @@ def test_shared_draft_rows_workspace_follows_the_library_and_the_device(monkeypa
         for scale in (3, 5):
             monkeypatch.setattr(tslt, "_lib", Library(scale))
             assert tslt._truncate_workspace_bytes(200, 128256, 64) == scale * 200 + 1000 * device
+
+
+def test_native_binding_declines_numbers_it_cannot_hold():
+    """What ctypes cuts to 32 bits is not the native module's to refuse: it hands the call back."""
+    from paper_2512_16273_amd import build, tslt
+    if not build.binding_possible():
+        pytest.skip("no host compiler, or no headers")
+    tslt.load(LIB)
+    big = (1 << 64) + 16
+    assert tslt._fast.truncate(None, 0.7, big, 0.0, 16, 0, False, {}, None, 0) is None
+    assert tslt._fast.verify_tree(None, 0.7, [2, big], *[None] * 6, False, {}, None, 0) is None
+    assert tslt._fast.pack(None, None, None, big, 1, 0) is None
+    assert tslt._fast.unpack(None, None, big, 16, 1000, 1, 0) is None
