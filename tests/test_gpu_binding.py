@@ -14,16 +14,31 @@ class Declines:
         return lambda *a: None
 
 
-def both(tslt, monkeypatch, call):
-    """The call's outcome by either path: its outputs, or the error's type and text."""
-    got = []
-    for fast in (tslt._fast, Declines()):
+class Recorder:
+    """The native module, and which calls it has taken."""
+    def __init__(self, native):
+        self.native, self.taken = native, []
+
+    def __getattr__(self, name):
+        def call(*a):
+            made = getattr(self.native, name)(*a)
+            self.taken.append(made is not None)
+            return made
+        return call
+
+
+def both(tslt, monkeypatch, call, taken=True):
+    """The call's outcome by either path: its outputs, or the error's type and text.  `taken`: whether the native module takes it."""
+    assert tslt._fast is not None
+    native, got = Recorder(tslt._fast), []
+    for fast in (native, Declines()):
         with monkeypatch.context() as m:
             m.setattr(tslt, "_fast", fast)
             try:
                 got.append({k: None if v is None else v.clone() for k, v in call().items()})
             except Exception as e:  # noqa: BLE001  (whatever it is, it has to be the same)
                 got.append((type(e), str(e)))
+    assert native.taken and set(native.taken) == {taken}
     a, b = got
     if isinstance(a, tuple) or isinstance(b, tuple):
         assert a == b
@@ -38,6 +53,11 @@ def both(tslt, monkeypatch, call):
     return a
 
 
+def unwritten(out):
+    """Outputs as they are handed over, with what no call writes in them."""
+    return {k: None if v is None else torch.full_like(v, 77) for k, v in out.items()}
+
+
 def test_calls_by_either_path(tslt, monkeypatch):
     B, G, V, K = 3, 4, 4099, 16
     w = W.scaled(W.WORKLOADS["chain_topk"], B=B, V=V, gamma=G, dtype="bf16", top_k=K, k_cap=K)
@@ -47,37 +67,48 @@ def test_calls_by_either_path(tslt, monkeypatch):
     wide[:, :V] = rows
     u = c["u_sample"].view(B * G, 1)
     made = tslt.truncate(rows, 0.7, K, 0.0, K, u=u)
-    fresh = lambda: {k: torch.full_like(v, 1) for k, v in made.items()}  # noqa: E731
-    def draft(z, top_k=K, u=u, out=None):
-        return both(tslt, monkeypatch, lambda: tslt.truncate(z, 0.7, top_k, 0.0, K, u=u, out=dict(out or fresh())))
+    fresh = lambda: unwritten(made)  # noqa: E731
+    def draft(z, top_k=K, u=u, out=None, taken=True):
+        return both(tslt, monkeypatch, lambda: tslt.truncate(z, 0.7, top_k, 0.0, K, u=u, out=dict(out) if out else fresh()), taken)
     out = draft(rows)
+    assert torch.equal(out["idx"], made["idx"]) and torch.equal(out["token"], made["token"])
     draft(wide[:, :V])                                                   # a stride
     draft(rows.view(B, G, V))
     draft(rows, out={**fresh(), "prob": None, "mass": None, "status": None, "slot": None})
-    draft(rows, out={k: v for k, v in fresh().items() if k not in ("token", "slot")})
-    assert draft(rows, out={k: v for k, v in fresh().items() if k != "idx"})[0] is KeyError
-    for bad in (dict(u=u.cpu()), dict(u=u.double()), dict(top_k=-1)):
-        assert draft(rows, **bad)[0] is tslt.TsltError
-    assert draft(wide.view(B, G, V + 5)[:, :, :V])[0] is tslt.TsltError
-    assert draft(rows.int())[0] is tslt.TsltError and draft(rows.t())[0] is tslt.TsltError
+    draft(rows, out={k: v for k, v in fresh().items() if k not in ("token", "slot")}, taken=False)
+    assert torch.equal(draft(rows, top_k=(1 << 64) + K, taken=False)["idx"], made["idx"])      # (cut to 32 bits, as ctypes does)
+    assert draft(rows, out={k: v for k, v in fresh().items() if k != "idx"}, taken=False)[0] is KeyError
+    assert draft(rows, top_k=-1)[0] is tslt.TsltError
+    for z, bad in ((rows, dict(u=u.cpu())), (rows, dict(u=u.double())), (wide.view(B, G, V + 5)[:, :, :V], {}), (rows.int(), {}), (rows.t(), {})):
+        assert draft(z, taken=False, **bad)[0] is tslt.TsltError
 
     sets = (out["idx"].view(B, G, K), out["logit"].view(B, G, K), out["count"].view(B, G))
     ws = torch.empty(tslt.workspace_bytes(tslt.OP_VERIFY, B, G, V, K), dtype=torch.uint8, device=DEV)
     vf = tslt.verify(c["target"], 0.7, *sets, out["token"].view(B, G), c["u_accept"], c["u_resample"])
-    chain = lambda target, s=sets, ws=ws, T=0.7, **o: both(tslt, monkeypatch, lambda: tslt.verify(  # noqa: E731
-        target, T, *s, out["token"].view(B, G), c["u_accept"], c["u_resample"], out={**{k: v.clone() for k, v in vf.items()}, **o}, workspace=ws))
-    assert torch.equal(chain(c["target"])["tokens"], vf["tokens"])
+    def chain(target, s=sets, ws=ws, T=0.7, taken=True, phases=("both",), **o):
+        def call():
+            got = {**unwritten(vf), **o}
+            for phase in phases:
+                tslt.verify(target, T, *s, out["token"].view(B, G), c["u_accept"], c["u_resample"], out=got, workspace=ws, phase=phase)
+            return got
+        return both(tslt, monkeypatch, call, taken)
+    for phases in (("both",), ("accept", "resample")):
+        got = chain(c["target"], phases=phases)
+        assert torch.equal(got["tokens"], vf["tokens"]) and torch.equal(got["accept_len"], vf["accept_len"])
+        assert torch.equal(got["ratio"], vf["ratio"])
     chain(c["target"], ratio=None, beta=None, status=None)
-    for bad in (dict(ws=ws[:64]), dict(T=0.0), dict(s=(sets[0].long(), *sets[1:])), dict(s=(sets[0][:2], *sets[1:]))):
+    for bad in (dict(ws=ws[:64]), dict(T=0.0)):
         assert chain(c["target"], **bad)[0] is tslt.TsltError
-    assert chain(c["target"][:, :, ::2])[0] is tslt.TsltError and chain(c["target"].view(-1, V))[0] is tslt.TsltError
+    for target, bad in ((c["target"], dict(s=(sets[0].long(), *sets[1:]))), (c["target"], dict(s=(sets[0][:2], *sets[1:]))),
+                        (c["target"][:, :, ::2], {}), (c["target"].view(-1, V), {})):
+        assert chain(target, taken=False, **bad)[0] is tslt.TsltError
 
-    pack = lambda i, pay="bf16": both(tslt, monkeypatch, lambda: tslt.pack(i, out["logit"], out["count"], V, pay))  # noqa: E731
+    pack = lambda i, pay="bf16", taken=True: both(tslt, monkeypatch, lambda: tslt.pack(i, out["logit"], out["count"], V, pay), taken)  # noqa: E731
     sent = pack(out["idx"])
-    assert pack(out["idx"], "f32")[0] is tslt.TsltError and pack(out["idx"].t())[0] is tslt.TsltError
-    pack(out["idx"][:0])
+    assert pack(out["idx"], "f32")[0] is tslt.TsltError and pack(out["idx"].t(), taken=False)[0] is tslt.TsltError
+    pack(out["idx"][:0], taken=False)
     for rows_in, cap in ((B * G, K), (0, K), (B * G, 0)):
-        both(tslt, monkeypatch, lambda: tslt.unpack(sent["words"], sent["row_offset"], rows_in, cap, V, "bf16"))
+        both(tslt, monkeypatch, lambda: tslt.unpack(sent["words"], sent["row_offset"], rows_in, cap, V, "bf16"), rows_in > 0 and cap > 0)
 
 
 def test_trees_by_either_path(tslt, monkeypatch):
@@ -94,11 +125,12 @@ def test_trees_by_either_path(tslt, monkeypatch):
         first = tslt.verify_tree(t["target"], w.T, expansion, *args, all_nodes=every, without_replacement=True)
         op = tslt.OP_VERIFY_TREE if every else tslt.OP_VERIFY_TREE_PATH
         ws = torch.empty(tslt.workspace_bytes(op, B, n, V, K), dtype=torch.uint8, device=DEV)
-        call = lambda e, target=t["target"], ws=ws: both(tslt, monkeypatch, lambda: tslt.verify_tree(  # noqa: E731
-            target, w.T, e, *args, all_nodes=every, out={k: None if v is None else v.clone() for k, v in first.items()}, workspace=ws,
-            without_replacement=True))
-        assert torch.equal(call(expansion)["seq"], first["seq"])
-        call(list(expansion))
+        call = lambda e, target=t["target"], ws=ws, taken=True: both(tslt, monkeypatch, lambda: tslt.verify_tree(  # noqa: E731
+            target, w.T, e, *args, all_nodes=every, out=unwritten(first), workspace=ws, without_replacement=True), taken)
+        for e in (expansion, list(expansion)):
+            got = call(e)
+            assert torch.equal(got["seq"], first["seq"]) and torch.equal(got["len"], first["len"])
+            assert torch.equal(got["ratio"].nan_to_num(nan=-7.0), first["ratio"].nan_to_num(nan=-7.0))
         for bad in ((2, 99), [], (0, 2)):
             assert call(bad)[0] is tslt.TsltError
-        assert call(expansion, ws=ws[:64])[0] is tslt.TsltError and call(expansion, t["target"][0])[0] is tslt.TsltError
+        assert call(expansion, ws=ws[:64])[0] is tslt.TsltError and call(expansion, t["target"][0], taken=False)[0] is tslt.TsltError
