@@ -239,16 +239,34 @@ def test_shared_rows_captured(tslt):
             same(eager[i], out_s)
 
 
+def workgroups_of_a_row(tslt, z, K, top_p, u):
+    """As many as have said in the call's workspace that they are done: each in a word of its own, taken away by the one that goes on."""
+    rows, V = z.shape
+    out = tslt.truncate(z, 0.8, 0, top_p, K, u=u)
+    ws = torch.full((tslt.workspace_bytes(tslt.OP_TRUNCATE_SHARED, rows, 0, V, K),), 255, dtype=torch.uint8, device=DEV)
+    dt = {torch.float32: tslt.F32, torch.bfloat16: tslt.BF16, torch.float16: tslt.F16}[z.dtype]
+    p = {k: v.data_ptr() for k, v in out.items()}
+    assert tslt.load().tslt_truncate_sample(
+        z.data_ptr(), dt, rows, V, z.stride(0), 0.8, 0, top_p, K, tslt.F32, p["idx"], p["logit"], p["prob"], p["count"], p["mass"], p["status"],
+        u.data_ptr(), u.shape[1], 0, p["token"], p["slot"], ws.data_ptr(), ws.numel(), torch.cuda.current_stream().cuda_stream) == 0
+    torch.cuda.synchronize()
+    words = ws[:ws.numel() // 8 * 8].view(torch.int64)
+    left = (words[:4 * rows] != 0).nonzero()                               # behind them the sums that the workgroups have found
+    return (int(left[0]) if len(left) else 4 * rows) // rows
+
+
 @pytest.mark.parametrize("dtype,V,rows,K,top_p,stride_pad", [
     ("bf16", 128256, 64, 256, 0.9, 0), ("bf16", 122880, 128, 64, 0.0, 0), ("f16", 223105, 3, 1024, 0.99, 7), ("f16", 90001, 31, 320, 0.0, 1),
     ("f32", 89601, 100, 32, 0.95, 3), ("f32", 151936, 1, 512, 0.0, 0), ("f32", 100003, 32, 1, 0.0, 0), ("bf16", 255999, 127, 100, 0.95, 1),
     ("f16", 87047, 2, 16, 0.9, 5), ("f32", 56325, 33, 700, 0.0, 0),      # from an odd start, the last stage half empty
+    # well inside the lines: by two workgroups, by four
+    ("bf16", 200000, 100, 64, 0.9, 0), ("f16", 180001, 110, 200, 0.0, 1), ("f32", 140000, 100, 32, 0.9, 0),
+    ("bf16", 200000, 20, 256, 0.0, 0), ("f16", 150000, 25, 100, 0.9, 0), ("f32", 120001, 24, 64, 0.0, 2),
 ])
 def test_drafts_of_shared_rows(tslt, monkeypatch, dtype, V, rows, K, top_p, stride_pad):
     """A row's workgroups make the same threshold and so find the same candidates: sets, counts, draws and status are those of
     one workgroup, bit for bit; the normaliser is added up in another order (fp32 terms, sums of a vector to the fp64 total: 1e-6)."""
     dt = {"f32": torch.float32, "bf16": torch.bfloat16, "f16": torch.float16}[dtype]
-    assert tslt.workspace_bytes(tslt.OP_TRUNCATE_SHARED, rows, 0, V, K) > 0
     g = torch.Generator(device=DEV).manual_seed(11)
     z = torch.randn(rows, V + stride_pad, generator=g, device=DEV).mul_(2.5)
     z -= torch.rand(rows, V + stride_pad, generator=g, device=DEV).mul_(V).add_(1.0).log_()
@@ -262,6 +280,8 @@ def test_drafts_of_shared_rows(tslt, monkeypatch, dtype, V, rows, K, top_p, stri
                 z[6] = 0.5
                 z[7, V // 2:] = 3.0
         shared = tslt.truncate(z, 0.8, 0, top_p, K, u=u, payload="bf16", without_replacement=True)
+        if not broken:
+            assert workgroups_of_a_row(tslt, z, K, top_p, u) >= 2
         with monkeypatch.context() as m:
             m.setattr(tslt, "_truncate_workspace_bytes", lambda *a: 0)
             alone = tslt.truncate(z, 0.8, 0, top_p, K, u=u, payload="bf16", without_replacement=True)
