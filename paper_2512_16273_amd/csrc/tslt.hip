@@ -125,17 +125,32 @@ hipError_t launch_truncate_shape(const tslt::TruncateParams& p, size_t lds, hipS
   return hipSuccess;
 }
 // Workgroups that share each row of a small batch (1: none do): four where that makes no more of them than compute units, else
-// two, for rows long enough that the walk saved is worth two trips to memory (some 3 us).  us by one workgroup a row / two / four,
-// 1, 32, 64 and 128 rows, sets of 256: bfloat16 64000 12.2 / 12.4 / 12.6, 14.0 / 14.6 / 14.2, 14.0 / 14.6 / 14.6, 14.3 / 15.3 / 18.1;
-// 90000 14.4 / 13.8 / 13.2, 15.4 / 15.5 / 14.9, 15.6 / 15.7 / 15.7, 16.0 / 16.6; 128256 16.8 / 15.2 / 14.0, 17.6 / 16.4 / 15.3,
-// 17.9 / 16.7 / 16.1, 18.2 / 17.5 / 20.5; 256000 23.4 / 18.6 / 15.9, 24.4 / 19.8 / 17.2, 24.8 / 20.2 / 18.3, 25.1 / 22.3 / 25.0; fp32
-// 64000 14.2 / 14.1 / 13.4, 15.3 / 15.1 / 14.6, 15.6 / 15.4 / 15.4, 16.1 / 16.7; 90000 (128 rows) 18.8 / 18.7; 128256 19.1 / 16.6 / 14.9,
-// 20.1 / 17.6 / 16.0, 20.4 / 18.1 / 17.4, 21.8 / 21.4.  (Eight: 16 rows of half a megabyte 2 % faster than four, the others slower.)
-int truncate_parts(tslt_dtype dt, int64_t V, int64_t rows) {
+// two, for rows long enough that the walk saved is worth two trips to memory (some 3 us).  What follows the walk is the smaller, and with it
+// the other workgroups' part in the time, the smaller the set: so rows of narrow sets from a greater length on (k_sel: the most that are selected).
+// us by one workgroup a row / four, sets of 32, 256 and 1024:
+//   1 row     binary16 64000 10.9 / 12.2, 11.8 / 12.8; 90000 11.9 / 12.4, 13.4 / 13.3; 110000 12.9 / 12.3, 14.0 / 12.9, 17.4 / 15.4;
+//             bfloat16 90000 12.4 / 12.5, 13.6 / 13.1; 128256 14.4 / 12.4, 15.5 / 13.0, 19.5 / 15.4
+//             fp32 45000 10.5 / 11.9, 11.1 / 12.2; 56000 11.1 / 11.9, 12.5 / 12.5; 64000 11.7 / 11.8, 13.0 / 12.5, 16.2 / 14.3
+//   32 rows   binary16 90000 13.7 / 14.4, 14.9 / 14.8; 110000 14.5 / 14.8, 16.0 / 15.3, 19.5 / 17.1; 128256 15.4 / 14.7
+//             bfloat16 90000 14.0 / 14.5, 15.1 / 14.8; fp32 45000 12.6 / 13.9, 13.5 / 14.2; 56000 12.9 / 14.0, 14.2 / 14.5;
+//             64000 14.0 / 14.2, 15.0 / 14.5; 72000 14.2 / 14.3, 15.5 / 14.9; 90000 15.9 / 14.9
+//             (sets of 100: binary16 95000 14.5 / 14.8, 103000 14.6 / 15.0, 112000 14.9 / 14.7; fp32 64000 14.2 / 14.2)
+//   64 rows   binary16 128256 15.7 / 15.5, 17.1 / 15.6; fp32 64000 14.2 / 15.0, 15.2 / 15.0, 18.2 / 17.2; 72000 14.6 / 15.1, 15.6 / 15.7;
+//             90000 16.4 / 15.8, 17.4 / 16.1
+// and by one / two: 128 rows, binary16 128256 16.0 / 16.8, 17.4 / 17.1; 200000 19.1 / 19.4 (sets of 16), 19.9 / 19.4 (of 100); 256000 22.0 / 21.4,
+// 23.8 / 21.8; bfloat16 128256 16.3 / 16.9, 17.9 / 17.2, 21.5 / 20.9; fp32 90000 17.5 / 18.2, 18.4 / 18.5, 21.0 / 21.7; 100000 17.7 / 18.8, 18.6 / 19.0;
+// 115000 20.4 / 20.2, 21.2 / 20.5; 80 rows, binary16 150000 16.8 / 16.7 (sets of 16); fp32 100000 16.9 / 16.8, 17.9 / 17.2.
+// (Eight: 16 rows of half a megabyte 2 % faster than four, the others slower.)
+int truncate_parts(tslt_dtype dt, int64_t V, int64_t rows, int k_sel) {
   const int64_t cus = tslt::compute_units(), kb = V * elem_bytes(dt) >> 10;
-  if (4 * rows <= cus && kb >= (8 * rows <= cus ? 170 : 220)) return 4;
-  if (2 * rows <= cus && kb >= (dt == TSLT_F32 ? 350 : 240)) return 2;
-  return 1;
+  const bool f32 = dt == TSLT_F32;
+  if (8 * rows <= cus) {
+    if (kb >= (k_sel < 64 ? (f32 ? 300 : 210) : k_sel < 160 ? (f32 ? 270 : 190) : (f32 ? 240 : 170))) return 4;
+  } else if (4 * rows <= cus) {
+    if (kb >= (f32 && k_sel < 512 ? 310 : 220)) return 4;
+  }
+  if (5 * rows <= 2 * cus) return kb >= (f32 ? 350 : 240) ? 2 : 1;
+  return 2 * rows <= cus && kb >= (f32 ? 440 : k_sel < 64 ? 400 : 240) ? 2 : 1;
 }
 // Whether a row's vectors with an element above the threshold come so thinly that a ring of kRingSmall slots, expanded
 // beyond kRingExpand, loses one less than once in a million rows.
@@ -158,9 +173,9 @@ bool tall_rows(tslt_dtype dt, int64_t V, int64_t rows) {
   if (rows <= cus) return V >= 10240;
   return 2 * rows <= 3 * cus && kb >= 160 && kb < 700;
 }
-// What a call whose rows are shared has to be given, whatever is selected (a smaller selection has fewer candidates).
+// What a call whose rows are shared has to be given, whatever is selected (a smaller selection has fewer candidates, and no more workgroups).
 size_t truncate_share_bytes(tslt_dtype dt, int64_t rows, int64_t V, int32_t k_cap) {
-  const int parts = truncate_parts(dt, V, rows);
+  const int parts = truncate_parts(dt, V, rows, k_cap);
   if (parts == 1 || k_cap < 1 || k_cap > TSLT_MAX_K_CAP) return 0;
   tslt::TruncateParams p{};
   p.k_sel = k_cap;
@@ -178,7 +193,7 @@ template <typename T> hipError_t launch_truncate(tslt_dtype dt, tslt::TruncatePa
     tslt::TruncateParams tall = p;
     const size_t tall_lds = plan_truncate(dt, p.V, TT, tall);
     if (tall.jprime > 0) {
-      tall.parts = truncate_parts(dt, p.V, p.rows);
+      tall.parts = truncate_parts(dt, p.V, p.rows, p.k_sel);
       if (tall.parts > 1 && ws != nullptr && reinterpret_cast<uintptr_t>(ws) % 256 == 0 &&
           ws_bytes >= tslt::truncate_part_bytes(p.rows, tall.parts, tall.sort_cap)) {
         tall.part_words = reinterpret_cast<uint64_t*>(ws);

@@ -258,7 +258,7 @@ def workgroups_of_a_row(tslt, z, K, top_p, u):
 @pytest.mark.parametrize("dtype,V,rows,K,top_p,stride_pad", [
     ("bf16", 128256, 64, 256, 0.9, 0), ("bf16", 122880, 128, 64, 0.0, 0), ("f16", 223105, 3, 1024, 0.99, 7), ("f16", 90001, 31, 320, 0.0, 1),
     ("f32", 89601, 100, 32, 0.95, 3), ("f32", 151936, 1, 512, 0.0, 0), ("f32", 100003, 32, 1, 0.0, 0), ("bf16", 255999, 127, 100, 0.95, 1),
-    ("f16", 87047, 2, 16, 0.9, 5), ("f32", 56325, 33, 700, 0.0, 0),      # from an odd start, the last stage half empty
+    ("f16", 111623, 2, 16, 0.9, 5), ("f32", 56325, 33, 700, 0.0, 0),      # from an odd start, the last stage half empty
     # well inside the lines: by two workgroups, by four
     ("bf16", 200000, 100, 64, 0.9, 0), ("f16", 180001, 110, 200, 0.0, 1), ("f32", 140000, 100, 32, 0.9, 0),
     ("bf16", 200000, 20, 256, 0.0, 0), ("f16", 150000, 25, 100, 0.9, 0), ("f32", 120001, 24, 64, 0.0, 2),

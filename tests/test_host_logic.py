@@ -47,6 +47,16 @@ def test_workspace_sizes_and_version(lib):
     assert lib.tslt_workspace_bytes(2, 0, 8, 32000, 64) == 0
 
 
+def test_draft_rows_are_shared_where_that_is_faster(lib):
+    """Rows of narrow sets from a greater length on than those of wide ones: (rows, V, k_cap), the longer of each pair is shared."""
+    lib.tslt_workspace_bytes.restype = ctypes.c_size_t
+    lib.tslt_workspace_bytes.argtypes = [ctypes.c_int, ctypes.c_int64, ctypes.c_int64, ctypes.c_int64, ctypes.c_int32]
+    for rows, k_cap, alone, shared in ((1, 32, 64000, 80000), (32, 32, 72000, 80000), (32, 100, 64000, 72000), (1, 256, 56000, 64000),
+                                       (64, 256, 72000, 80000), (64, 1024, 56000, 64000), (100, 256, 85000, 95000), (128, 32, 105000, 120000)):
+        assert lib.tslt_workspace_bytes(5, rows, 0, alone, k_cap) == 0, (rows, k_cap)
+        assert lib.tslt_workspace_bytes(5, rows, 0, shared, k_cap) > 0, (rows, k_cap)
+
+
 def test_argument_errors_are_found_on_the_host(lib):
     """Bad arguments return a negative code and a message; nothing touches the (absent) GPU."""
     lib.tslt_last_error.restype = ctypes.c_char_p
