@@ -597,8 +597,10 @@ template <typename T, typename Terms> hipError_t launch_verify_tree_with(TreePar
     const bool alone = rows <= compute_units();
     p.parts = rows <= p.items_rows ? row_parts<T, Terms>(p.V, rows) : 1;
     // (handing over keeps a workgroup a microsecond longer: of many times what the chip holds at once, more than the launch that it saves.
-    // 117 trees <4,4,4> of fp32 rows of 17296, 9945 rows, 220 us by a second launch, 239 so; 14 such trees of bfloat16 9083 37.4 / 34.3.)
-    if (p.n_eval_layers <= p.depth || p.n_nodes > kHandNodes || rows > 4 * compute_units()) p.words = nullptr;
+    // 117 trees <4,4,4> of fp32 rows of 17296, 9945 rows, 220 us by a second launch, 239 so; 14 such trees of bfloat16 9083 37.4 / 34.3.
+    // And where each looks at many words: trees of 255 nodes, 3 binary16 of rows of 8000 26.3 / 27.6, 3 fp32 of 30000 34.0 / 36.8, 2 binary16 18.9 / 19.0,
+    // 2 fp32 25.4 / 24.7; of 85, 12 binary16 of 8000 30.0 / 31.1, 9 fp32 35.8 / 35.8, 6 binary16 19.8 / 18.8; of 15, 50 binary16 26.3 / 25.6.)
+    if (p.n_eval_layers <= p.depth || p.n_nodes > kHandNodes || rows > (p.n_nodes > 128 ? 2 : 4) * compute_units()) p.words = nullptr;
     p.tag = next_tag();
     hipLaunchKernelGGL((p.parts > 1 ? tree_node_kernel<T, Terms, kAlone, true> : alone ? tree_node_kernel<T, Terms, kAlone> : tree_node_kernel<T, Terms, kShared>),
                        dim3(unsigned(rows * p.parts)), dim3(kRowThreads), Terms::kBytes, s, p);

@@ -54,8 +54,9 @@ inline int64_t verify_rows_to_share(int64_t B, int64_t gamma, int64_t V) {
   if (B <= 0 || gamma <= 0 || V < kShareLeastV) return 0;
   return B * (gamma + 1) <= kShareRows ? B * (gamma + 1) : (B <= kShareRows ? B : 0);
 }
-// Rows of a round whose workgroups leave their results in memory for the last of each sequence.  (Where there is little to
-// gain, in rows as short as this, callers are told the size that they have always been told.)
+// Rows of a round whose workgroups leave their results in memory for the last of each sequence (more than a round has: round_rows).  (Rows
+// shorter than kHandLeastV would gain as much, 16 x 8 binary16 rows of 1000 11.0 us by a launch more, 9.5 so; their callers are told the
+// size that they have always been told, and no call is refused what it was given before.)
 constexpr int64_t kHandRows = 1024, kHandLeastV = 2048;
 inline int64_t verify_rows_handed(int64_t B, int64_t gamma, int64_t V) {
   return V >= kHandLeastV && B * (gamma + 1) <= kHandRows ? B * (gamma + 1) : 0;
@@ -438,6 +439,9 @@ template <typename T, typename Terms> hipError_t launch_verify_with(VerifyParams
     p.j_count = p.gamma + 1;
     p.draws = 1;
     p.parts = p.words != nullptr && p.B * p.j_count <= p.items_rows ? row_parts<T, Terms>(p.V, p.B * p.j_count) : 1;
+    // (a sequence of more positions than a wave has lanes: more words than one trip to memory brings.  1 x 200 bfloat16 rows of 8000 11.3 us by a
+    // launch more, 12.4 so; 2 x 100 11.3 / 12.3, 1 x 127 11.2 / 10.6, 2 x 63 11.2 / 10.1)
+    if (p.gamma >= 64 && p.parts == 1) p.words = nullptr;
     if (p.words != nullptr) p.tag = next_tag();
     e = p.parts > 1 ? share(KernelTag<&verify_round_kernel<T, Terms, kAlone, true>>{}, p.B * p.j_count) : round();
     if (e != hipSuccess || p.words != nullptr) return e;
