@@ -83,8 +83,11 @@ size_t plan_truncate(tslt_dtype dt, int64_t V, int nt, tslt::TruncateParams& p) 
     if (tslt::truncate_lds_bytes(p.ring_bytes, sort_cap, nt) + sizeof(tslt::TruncateShared) + 256 <= kMaxLds) {
       p.jprime = jprime;
       p.sort_cap = sort_cap;
-      // (of n values above a threshold, in a tail that falls exponentially, the largest is ln n + 0.577 scales above it)
-      p.reach = float((std::log(j_eff / f) + 0.577) / (std::log(j_eff) + 0.577));
+      // (of n values above a threshold, in a tail that falls exponentially, the largest is ln n + 0.577 scales above it.  Not where the sample
+      // itself has many: few are beyond it, and wider bins crowd the first ones.  us so / up to the sample's maximum: j_eff 130 to 220, 1 binary16
+      // row of 90000, sets of 1024, 24.8 / 24.1, 1 bfloat16 of 60000 of 1000 22.6 / 22.2, 500 fp32 of 30000 of 700 23.2 / 23.0; 78, 2000
+      // bfloat16 of 32000 of 200 33.2 / 33.5; 40, 200 fp32 of 100000 of 256 20.7 / 21.0; less, 1064 bfloat16 of 242880 of 356 98.8 / 100.5)
+      p.reach = j_eff >= 100.0 ? 1.0f : float((std::log(j_eff / f) + 0.577) / (std::log(j_eff) + 0.577));
     }
   }
   return tslt::truncate_lds_bytes(p.ring_bytes, p.sort_cap, nt);
@@ -130,7 +133,8 @@ hipError_t launch_truncate_shape(const tslt::TruncateParams& p, size_t lds, hipS
 // us by one workgroup a row / four, sets of 32, 256 and 1024:
 //   1 row     binary16 64000 10.9 / 12.2, 11.8 / 12.8; 90000 11.9 / 12.4, 13.4 / 13.3; 110000 12.9 / 12.3, 14.0 / 12.9, 17.4 / 15.4;
 //             bfloat16 90000 12.4 / 12.5, 13.6 / 13.1; 128256 14.4 / 12.4, 15.5 / 13.0, 19.5 / 15.4
-//             fp32 45000 10.5 / 11.9, 11.1 / 12.2; 56000 11.1 / 11.9, 12.5 / 12.5; 64000 11.7 / 11.8, 13.0 / 12.5, 16.2 / 14.3
+//             fp32 45000 10.5 / 11.9, 11.1 / 12.2; 56000 11.1 / 11.9, 12.5 / 12.5; 64000 11.7 / 11.8, 13.0 / 12.5, 16.2 / 14.3;
+//             50000, 60000 sets of 1024 and 900 14.6 / 14.4, 15.2 / 13.1
 //   32 rows   binary16 90000 13.7 / 14.4, 14.9 / 14.8; 110000 14.5 / 14.8, 16.0 / 15.3, 19.5 / 17.1; 128256 15.4 / 14.7
 //             bfloat16 90000 14.0 / 14.5, 15.1 / 14.8; fp32 45000 12.6 / 13.9, 13.5 / 14.2; 56000 12.9 / 14.0, 14.2 / 14.5;
 //             64000 14.0 / 14.2, 15.0 / 14.5; 72000 14.2 / 14.3, 15.5 / 14.9; 90000 15.9 / 14.9
@@ -145,7 +149,7 @@ int truncate_parts(tslt_dtype dt, int64_t V, int64_t rows, int k_sel) {
   const int64_t cus = tslt::compute_units(), kb = V * elem_bytes(dt) >> 10;
   const bool f32 = dt == TSLT_F32;
   if (8 * rows <= cus) {
-    if (kb >= (k_sel < 64 ? (f32 ? 300 : 210) : k_sel < 160 ? (f32 ? 270 : 190) : (f32 ? 240 : 170))) return 4;
+    if (kb >= (k_sel < 64 ? (f32 ? 300 : 210) : k_sel < 160 ? (f32 ? 270 : 190) : (!f32 ? 170 : k_sel < 512 ? 240 : 200))) return 4;
   } else if (4 * rows <= cus) {
     if (kb >= (f32 && k_sel < 512 ? 310 : 220)) return 4;
   }

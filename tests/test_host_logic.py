@@ -52,7 +52,7 @@ def test_draft_rows_are_shared_where_that_is_faster(lib):
     lib.tslt_workspace_bytes.restype = ctypes.c_size_t
     lib.tslt_workspace_bytes.argtypes = [ctypes.c_int, ctypes.c_int64, ctypes.c_int64, ctypes.c_int64, ctypes.c_int32]
     for rows, k_cap, alone, shared in ((1, 32, 64000, 80000), (32, 32, 72000, 80000), (32, 100, 64000, 72000), (1, 256, 56000, 64000),
-                                       (64, 256, 72000, 80000), (64, 1024, 56000, 64000), (100, 256, 85000, 95000), (128, 32, 105000, 120000)):
+                                       (64, 256, 72000, 80000), (1, 900, 50000, 56000), (64, 1024, 56000, 64000), (100, 256, 85000, 95000), (128, 32, 105000, 120000)):
         assert lib.tslt_workspace_bytes(5, rows, 0, alone, k_cap) == 0, (rows, k_cap)
         assert lib.tslt_workspace_bytes(5, rows, 0, shared, k_cap) > 0, (rows, k_cap)
 
