@@ -627,9 +627,16 @@ constexpr int64_t kShareWords = 512;                 // words that the workgroup
 //   bfloat16  44000 12.0 / 13.4, 12.5 / 13.6, 12.6 / 14.4, 15.1 / 15.8;  64000 13.1 / 12.6, 13.6 / 13.7, 13.6 / 14.9, 16.4 / 15.8;
 //             90000 13.6 / 12.6, 14.7 / 14.1, 14.8 / 15.2, 17.9 / 16.2
 // By sixteen runs a part / eight: binary16 64000 15.0 / 13.2, 16.3 / 14.0, 16.5 / 15.8; fp32 64000 13.3 / 12.6, 14.1 / 14.5, 90000 (4 x 4)
-// 14.7 / 15.6, bfloat16 200000 15.7 / 16.3.  By two workgroups a row (more than a third as many rows as compute units) later, with a launch between them: fp32 60000 18.4 / 18.8,
-// 76000 20.6 / 20.6, 84000 22.0 / 21.0; bfloat16 125000 19.8 / 20.0, 155000 21.1 / 20.6; binary16 56000 18.7 / 18.0; the sampled rows of 128 x 4
-// fp32 76000 44.5 / 45.1, 84000 49.4 / 48.8; by binary16's bit table 128 x 2 147456 40.8 / 40.6.
+// 14.7 / 15.6, bfloat16 200000 15.7 / 16.3.  Sets of 16 and 1024: bfloat16 64000, 1 x 4 12.8 / 12.9 and 15.6 / 15.1, 5 x 4 13.0 / 13.1 and 15.7 / 15.3; fp32
+// 44000 1 x 4 14.0 / 12.1 and 16.4 / 14.0; binary16 44000 8 x 8 15.1 / 14.3 and 17.5 / 16.8.  (Every part reads the set and gathers the row at it, so that the one
+// that goes on has it at once: gathered by that one alone, behind the masses, sets of 1024 take 0.3 to 1.4 us more.)
+// By two workgroups a row (more than a third as many rows as compute units) later; 16 x 7, 20 x 4 and the sampled rows of 128 x 4, sets of 256:
+//   fp32      60000 17.0 / 18.2, 16.9 / 16.9, 39.5 / 40.9;  76000 19.3 / 19.8, 19.1 / 18.4, 46.2 / 46.9;  90000 20.7 / 20.6, 20.6 / 19.1, 53.4 / 53.2;
+//             120000 24.3 / 23.1, 24.0 / 21.1, 62.9 / 61.9;  sets of 1024: 76000 21.5 / 22.6, 21.4 / 20.4, 55.4 / 54.9;  120000 26.8 / 27.5, 26.4 / 24.4, 73.1 / 71.0
+//   bfloat16  125000 17.2 / 17.6, 17.1 / 17.0, 40.6 / 41.5;  150000 18.7 / 18.8, 18.7 / 17.9, 46.0 / 46.5;  180000 20.4 / 19.9, 20.4 / 18.5, 52.0 / 52.2;
+//             sets of 1024: 150000 21.2 / 21.6, 21.3 / 19.9, 55.4 / 54.8
+//   binary16  52000 16.2 / 16.7, 16.3 / 16.6, 29.2 / 29.3;  60000 17.9 / 16.9, 17.8 / 16.8, 31.6 / 31.1;  72000 18.8 / 18.7, 18.8 / 18.5, 34.1 / 34.3;
+//             sets of 1024: 60000 20.2 / 19.5, 20.1 / 19.0, 39.3 / 38.5;  by the bit table 128 x 2 147456 36.6 / 36.2, 100 x 4 43.3 / 42.6
 template <typename T, typename Terms> inline int64_t share_min_V(int64_t rows) {
   const int64_t cus = compute_units();
   const bool by_two = 3 * rows > cus;

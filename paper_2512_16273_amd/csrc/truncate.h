@@ -18,9 +18,8 @@
 // vector registers without a sign to change (2.7 cycles a wave, 4.4 otherwise), binary16 is tested against the threshold as
 // packed halves and never widened, addresses are a scalar offset into a buffer (but for large batches), the complete stages have a loop without a
 // check for the row's end, and every exchange between waves behind the pass is one barrier (12 in all, 24 before).  Few long rows
-// are shared by workgroups (64 bfloat16 rows of 128256 18.0 us by one each, 16.2 by four).  us
-// before / now: 1 binary16 row of 32000, k 320 12.4 / 10.8; 64 bfloat16 rows of 128256, k 256 20.5 / 17.8; 19 binary16 rows of
-// 223104 27.7 / 23.0; 600 binary16 rows of 32000 17.7 / 15.8; 4096 bfloat16 rows of 256000, k 1024 407 / 396.
+// are shared by workgroups (truncate_parts: 64 bfloat16 rows of 128256, k 256, 17.6 us by one each, 16.1 by four).  us
+// before / now: 1 binary16 row of 32000, k 320 12.4 / 10.4; 600 binary16 rows of 32000 17.7 / 15.8; 4096 bfloat16 rows of 256000, k 1024 407 / 396.
 #pragma once
 #include "common.h"
 #include "wire.h"

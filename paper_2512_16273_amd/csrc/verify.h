@@ -267,8 +267,8 @@ __global__ __launch_bounds__(kRowThreads, kWavesPerSimd) void verify_resample_ke
 // sweep by sixteen waves, then the chain of steps after it): one workgroup of 1024 threads per (sequence, row), or p.parts of them
 // (kParts), sweeps its row once, takes the acceptance test from the sums and, if the token is rejected (or
 // the row is the bonus row), draws the replacement at once, whether or not an earlier position will turn out to
-// have been rejected (one sequence x 4, binary16 V = 32000: 26 us by kernels A and B, 14.2 by a round's kernel and a second launch, 11.8 so;
-// 8 x 8 bfloat16, V = 128256: 30.6, 17.8 by three launches, 15.9).  What a position came to it leaves in memory (handover.h); the workgroup that finds those of all its
+// have been rejected (one sequence x 4, binary16 V = 32000: 26 us by kernels A and B, 14.1 by a round's kernel and a second launch, 12.2 so;
+// 8 x 8 bfloat16, V = 128256: 30.6, 17.9 by three launches, 15.8).  What a position came to it leaves in memory (handover.h); the workgroup that finds those of all its
 // sequence keeps the draw of the first rejected position and writes the sequence's outputs.  With a workspace that has no room
 // for that a second launch does, one wave per sequence; until then a position's draw waits in its place in out_tokens, and
 // the bonus row's status in out_accept_len.
