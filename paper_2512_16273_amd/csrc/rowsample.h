@@ -614,8 +614,12 @@ __device__ __forceinline__ bool row_shared(RowWork<T>& w, double* table, const A
 
 constexpr int64_t kShareRows = 128;                  // at most, by two workgroups or more
 constexpr int64_t kShareLeastV = 40000;              // of any type
-// Masses of a row's items, of `per_vec` elements in a vector (as for row_segments).
-inline int64_t items_stride(int64_t V, int per_vec = 4) { return int64_t(row_segments(V, per_vec)) * kSubChunks + 2; }
+// Masses of a row's items, of `per_vec` elements in a vector (as for row_segments).  16-bit rows have lines of memory of their own: what several
+// XCDs write of one line goes there several times (8 x 4 binary16 rows of 100000 15.7 us side by side, 15.4 so).
+inline int64_t items_stride(int64_t V, int per_vec = 4) {
+  const int64_t n = int64_t(row_segments(V, per_vec)) * kSubChunks + 2;
+  return per_vec > 4 ? std::min((n + 15) / 16 * 16, items_stride(V)) : n;
+}
 constexpr int64_t kShareWords = 512;                 // words that the workgroups of all shared rows leave, at most
 // Workgroups that share each of `rows` rows (1: none do): as many as fill the chip, with eight runs each at least (a wave alone on its
 // SIMD is done with a run in a third of the time that four of them take; fp32 and BitTerms, whose runs cost less: sixteen where eight
